@@ -29,44 +29,39 @@ static inline size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // Launch shapes (workgroups per launch the key axis is cut for).  Fixed constants: split counts decide workspace
 // sizes and the order in which partial results are merged, so they must not vary between calls.
-constexpr int kAttnGroups = 1024;        // one sub-tile per wavefront at the 3 % keep configurations
-constexpr int kAttnGroupsShared = 512;   // several query tiles per workgroup: two resident workgroups per compute unit
-constexpr int kAttnGroupsPipe = 256;     // many sub-tiles per wavefront: one resident workgroup per compute unit
-constexpr int kLogitGroups = 4096;       // sink scoring: measured best of 1024 .. 8192 (short workgroups even out the tail of the scan)
+constexpr int kAttnGroups = 512;      // one sub-tile per slot: every workgroup resident at once, two per compute unit
+constexpr int kAttnGroupsPipe = 256;  // many sub-tiles per slot, two stages per slot: one workgroup per compute unit
+constexpr int kAttnGroupsWide = 512;  // the same where query groups share the rows: one stage per slot, two workgroups per compute unit
+constexpr int kLogitGroups = 4096;    // sink scoring, one query tile: measured best of 1024 .. 8192 (short workgroups even out the tail of the scan)
+constexpr int kLogitGroupsMany = 2048;  // several query tiles: every workgroup first loads all their rows
 
-static void plan_queries(SplitPlan& p, int max_active) {
+// `most`: 16-query tiles per query group at most.  q_pad is the same for every `most`: the rows of per-query results.
+static void plan_queries(SplitPlan& p, int max_active, int most) {
   p.q_tiles = ceil_div(max_active, kQTile);
-  p.q_tiles_per_group = p.q_tiles <= 1 ? 1 : (p.q_tiles == 2 ? 2 : kMaxQTilesPerGroup);
+  p.q_tiles_per_group = p.q_tiles <= 2 ? p.q_tiles : most;
   p.q_groups = ceil_div(p.q_tiles, p.q_tiles_per_group);
-  p.q_pad = p.q_groups * p.q_tiles_per_group * kQTile;
+  p.q_pad = p.q_tiles <= 2 ? p.q_tiles * kQTile : ceil_div(p.q_tiles, kMaxQTilesPerGroup) * kMaxQTilesPerGroup * kQTile;
 }
 
-// `round_to`: sub-tiles a workgroup consumes at a time (four wavefronts with a sub-tile each; two when the wavefronts
-// share the staged sub-tiles and the key axis advances in half rounds of two)
-static void plan_splits(SplitPlan& p, int n_heads, int target_groups, int round_to = kWavesPerGroup) {
-  const int per_head = target_groups / (n_heads * p.q_groups);
-  int per = ceil_div(p.n_sub, per_head > 0 ? per_head : 1);
-  per = ceil_div(per > 0 ? per : 1, round_to) * round_to;
-  p.per_split = per;
-  p.n_split = p.n_sub > 0 ? ceil_div(p.n_sub, per) : 1;
+// As many splits as the target allows, at least one round of four sub-tiles each
+static void plan_splits(SplitPlan& p, int n_heads, int q_groups, int target_groups) {
+  const int per_head = std::max(1, target_groups / (n_heads * q_groups));
+  p.n_split = std::max(1, std::min(per_head, ceil_div(p.n_sub, kWavesPerGroup)));
 }
 
 static void plan_attention_splits(SplitPlan& p, const focus_shape& s) {
-  plan_splits(p, s.n_heads, kAttnGroups);
-  // Many sub-tiles per wavefront (dense layers, alpha = 0.5) or several query tiles per workgroup (window-expanded
-  // queries): fewer, longer workgroups with pipelined key loops.  One sub-tile per wavefront (the 3 % keep
-  // configurations): nothing to overlap.
-  if (p.q_tiles_per_group > 1) {
-    plan_splits(p, s.n_heads, kAttnGroupsShared, 2);
-  } else if (p.per_split > kWavesPerGroup) {
-    plan_splits(p, s.n_heads, kAttnGroupsPipe);
-    p.pipelined = p.per_split > kWavesPerGroup;
+  plan_splits(p, s.n_heads, p.q_groups, kAttnGroups);
+  // Many sub-tiles per wavefront (dense layers, alpha = 0.5): fewer, longer workgroups with double-buffered key loops.
+  // One sub-tile per wavefront (the 3 % keep configurations): nothing to overlap.
+  if (p.n_split * kWavesPerGroup < p.n_sub) {
+    plan_splits(p, s.n_heads, p.q_groups, p.q_groups > 1 ? kAttnGroupsWide : kAttnGroupsPipe);
+    p.pipelined = p.n_split * kWavesPerGroup < p.n_sub;
   }
 }
 
 SplitPlan plan_attention(const focus_shape& s, int max_active, int n_keep, int n_sink) {
   SplitPlan p;
-  plan_queries(p, max_active);
+  plan_queries(p, max_active, max_active <= 64 ? 4 : 2);
   p.n_sub = n_keep * ceil_div(s.block, kSubTile) + ceil_div(s.n_resp, kSubTile) + ceil_div(n_sink, kSubTile);
   plan_attention_splits(p, s);
   return p;
@@ -74,7 +69,7 @@ SplitPlan plan_attention(const focus_shape& s, int max_active, int n_keep, int n
 
 SplitPlan plan_attention_dense(const focus_shape& s, int max_active) {
   SplitPlan p;
-  plan_queries(p, max_active);
+  plan_queries(p, max_active, max_active <= 64 ? 4 : 2);
   p.n_sub = ceil_div(s.n_ctx + s.n_resp, kSubTile);
   plan_attention_splits(p, s);
   return p;
@@ -82,9 +77,9 @@ SplitPlan plan_attention_dense(const focus_shape& s, int max_active) {
 
 SplitPlan plan_logits(const focus_shape& s, int max_active) {
   SplitPlan p;
-  plan_queries(p, max_active);
+  plan_queries(p, max_active, kMaxQTilesPerGroup);
   p.n_sub = ceil_div(s.n_ctx + s.n_resp, kSubTile);
-  plan_splits(p, s.n_heads, kLogitGroups);
+  plan_splits(p, s.n_heads, p.q_groups, p.q_tiles_per_group > 1 ? kLogitGroupsMany : kLogitGroups);
   return p;
 }
 
@@ -172,7 +167,7 @@ static AttnWs ws_attn(const focus_shape& s, const SplitPlan& p) {
   return w;
 }
 
-static ProbeWs ws_probe_layer(const focus_shape& s, const SplitPlan& pa) {
+static ProbeWs ws_probe_layer(const focus_shape& s, const SplitPlan& pa, const SplitPlan& pl) {
   ProbeWs w;
   const size_t L = (size_t)s.n_ctx + s.n_resp;
   const AttnWs a = ws_attn(s, pa);
@@ -182,7 +177,7 @@ static ProbeWs ws_probe_layer(const focus_shape& s, const SplitPlan& pa) {
   w.lse2 = off;
   off += align_up((size_t)s.n_heads * pa.q_pad * sizeof(float));
   w.scratch = off;
-  off += align_up(sinks_two_pass(pa) ? (size_t)pa.q_groups * s.n_heads * L * sizeof(float) : spilled_logits_bytes(s));
+  off += align_up(sinks_two_pass(pl) ? (size_t)pl.q_groups * s.n_heads * L * sizeof(float) : spilled_logits_bytes(s));
   w.col_mass = off;
   off += align_up(L * sizeof(float));
   w.cand = off;
@@ -318,7 +313,7 @@ size_t focus_workspace_bytes(int32_t fn, const focus_shape* shape, int32_t max_a
       return ws_attn(*shape, plan_attention(*shape, max_active, n_keep, n_sink)).total;
     case FOCUS_FN_PROBE_LAYER:
       if (max_active < 1 || max_active > shape->n_gen) return 0;
-      return ws_probe_layer(*shape, plan_attention_dense(*shape, max_active)).total;
+      return ws_probe_layer(*shape, plan_attention_dense(*shape, max_active), plan_logits(*shape, max_active)).total;
     case FOCUS_FN_SPARSE_LAYER:
       if (max_active < 1 || max_active > shape->n_gen || n_keep < 0 || n_keep > n_b || n_sink < 0 ||
           n_sink > shape->n_ctx)
@@ -561,7 +556,8 @@ int focus_probe_layer(const void* Q, const int32_t* active_idx, const int32_t* c
   if (!aligned16(Q) || !aligned16(K) || !aligned16(V) || !aligned16(out))
     return fail(FOCUS_EINVAL, "focus_probe_layer: pointers must be 16-byte aligned");
   const SplitPlan pa = plan_attention_dense(*shape, max_active);
-  const ProbeWs w = ws_probe_layer(*shape, pa);
+  const SplitPlan pl = plan_logits(*shape, max_active);
+  const ProbeWs w = ws_probe_layer(*shape, pa, pl);
   if (!workspace || ws_bytes < w.total || !aligned16(workspace))
     return fail(FOCUS_EWORKSPACE, "focus_probe_layer: workspace needs %zu bytes, 16-byte aligned", w.total);
   hipStream_t st = static_cast<hipStream_t>(stream);
@@ -580,7 +576,6 @@ int focus_probe_layer(const void* Q, const int32_t* active_idx, const int32_t* c
                                     st, &probe);
   if (e != hipSuccess) return launch_fail("focus_probe_layer(attention)", e);
   if (two_pass) {  // more queries: one more pass over K turns the known row log-sum-exps into column sums
-    const SplitPlan pl = plan_logits(*shape, max_active);
     e = launch_qk_logits(Q, active_idx, counts, max_active, K, *shape, pl, 2, nullptr, nullptr, lse2, scratch, st);
     if (e != hipSuccess) return launch_fail("focus_probe_layer(column sums)", e);
   }
@@ -588,7 +583,7 @@ int focus_probe_layer(const void* Q, const int32_t* active_idx, const int32_t* c
   const bool prefilter = !tournament && sink_prefilter_fits(shape->n_ctx, n_sink, S);
   int32_t* cand = (tournament || prefilter) ? reinterpret_cast<int32_t*>(ws + w.cand) : nullptr;
   uint32_t* cand_keys = reinterpret_cast<uint32_t*>(ws + w.cand) + kTournamentMaxCand;
-  e = launch_column_mass(scratch, two_pass, lse2, counts, max_active, two_pass ? pa.q_groups * shape->n_heads : shape->n_heads,
+  e = launch_column_mass(scratch, two_pass, lse2, counts, max_active, two_pass ? pl.q_groups * shape->n_heads : shape->n_heads,
                          shape->n_heads, L, S, shape->n_ctx, prefilter ? kPrefilterNominees : n_sink, cand, cand ? cand_keys : nullptr, st);
   if (e != hipSuccess) return launch_fail("focus_probe_layer(column mass)", e);
   if (tournament) {

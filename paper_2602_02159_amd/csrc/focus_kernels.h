@@ -18,10 +18,13 @@ constexpr int kMaxQTilesPerGroup = 4;
 static inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
 static inline int64_t ceil_div64(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-// How the key axis of an MFMA kernel is cut: n_sub sub-tiles per head, `per_split` consecutive sub-tiles
-// per workgroup, n_split workgroups per (head, query group).
+// How the key axis of an MFMA kernel is cut: n_sub sub-tiles per head, n_split workgroups per (head, query group).  The
+// splits take turns: split s works on the rounds of four sub-tiles (one per wavefront) s, s + n_split, s + 2 n_split, ...
+// All of them are equally long up to one round, and together they sweep one window of K and V.  (Contiguous ranges per split
+// start at multiples of a length that is often close to a power of two, which puts all workgroups on the same memory
+// channels: the 32K dense layer with 30 queries takes 96 us that way, 89 us this way.)
 struct SplitPlan {
-  int n_sub, per_split, n_split;
+  int n_sub, n_split;
   bool pipelined = false;  // attention only: wavefronts walk several sub-tiles, use the double-buffered key loop
   int q_tiles, q_tiles_per_group, q_groups, q_pad;  // q_pad = 16 * q_tiles
 };

@@ -1,9 +1,10 @@
-// The three MFMA kernels (64-lane wavefronts):
+// The MFMA kernels (64-lane wavefronts):
 //
 //   sparse_attn_kernel   Eq. 8 + Eq. 9: gathers the kept blocks, the sinks and the response rows of K / V and
-//                        runs a split-KV online-softmax attention of the active queries over them
+//                        runs a split-KV online-softmax attention of up to 16 active queries over them
 //                        (v_mfma_f32_16x16x32_bf16).  The same kernel with every row kept is the dense layer (probe
 //                        layer, dense comparison).
+//   wide_attn_kernel     the same for more than 16 queries (v_mfma_f32_32x32x16_bf16; described where it is defined).
 //   refresh_attn_kernel  block entry (Alg. 1): dense attention of EVERY position over every key, the one MFMA-bound
 //                        launch of the method (v_mfma_f32_32x32x16_bf16; described where it is defined).
 //   qk_logits_kernel     Eq. 6: scaled logits of the active queries against every key of the probe layer with the
@@ -11,12 +12,10 @@
 //                        queries — the probabilities summed over the queries (16x16x32).
 //
 // Work decomposition.  The key axis of one head is cut into sub-tiles of 32 rows, staged in LDS with an XOR
-// swizzle (applied on the global side of the load) so that the operand reads are conflict free.  How a workgroup
-// walks them depends on the launch (see sparse_attn_kernel): with at most 16 queries a wavefront owns a sub-tile
-// from the memory request to the MFMAs — in the sparse step the rows go from HBM straight into the wavefront's
-// private slice of LDS (global_load_lds_dwordx4: no staging registers, no ds_write), wavefronts never wait for each
-// other inside the key loop and meet once, at the end, to merge their softmax states; with more queries the
-// wavefronts take one 16-query tile each and share the staged sub-tiles.
+// swizzle (applied on the global side of the load) so that the operand reads are conflict free.  The rows go from HBM
+// straight into a slot of LDS (global_load_lds_dwordx4: no staging registers, no ds_write); with at most 16 queries a
+// wavefront owns a sub-tile from the memory request to the MFMAs, wavefronts never wait for each other inside the key loop
+// and meet once, at the end, to merge their softmax states.
 //
 // MFMA layout used (16x16x32, D[i][j] += sum_k A[i][k] B[k][j]; lane = 16*g + c):
 //   A operand: lane holds A[i = c][k = 8g .. 8g+7];  B operand: lane holds B[k = 8g .. 8g+7][j = c];
@@ -54,6 +53,12 @@ struct Geo {
 template <int D>
 __device__ __forceinline__ int stage_off(int row, int chunk) {
   return row * Geo<D>::kRowBytes + ((chunk ^ (row & (Geo<D>::kChunks - 1))) << 4);
+}
+
+// swizzle of a V stage that is read in transposed 32x32x16 operands (see read_v_operand32)
+template <int D>
+__device__ __forceinline__ int vstage_swz(int row) {
+  return D == 128 ? (row & 3) << 2 : ((row >> 1) & 1) << 2;
 }
 
 // cache policy of the K/V row loads: non-temporal (every row is read once per launch)
@@ -200,7 +205,8 @@ __device__ __forceinline__ int subtile_row(const SubTile& t, int slot, int last)
 // address per sub-tile plus per-lane byte offsets that depend on the lane and the load only (the compiler keeps them
 // across a key loop), so a request costs no per-lane address arithmetic; ragged and scattered sub-tiles work out a row
 // per lane and load.
-template <int D, int NL>
+// VSWZ: the rows are swizzled for the transposed reads of the 32x32 tiles (vstage_swz) instead of for row reads.
+template <int D, int NL, bool VSWZ = false, int POLICY = kStreamPolicy>
 __device__ __forceinline__ void issue_subtile_part(const uint16_t* __restrict__ base, int64_t sn, const SubTile& t, char* stage,
                                                    int lane, int first) {
   using G = Geo<D>;
@@ -208,30 +214,37 @@ __device__ __forceinline__ void issue_subtile_part(const uint16_t* __restrict__ 
   typedef __attribute__((address_space(3))) void* lptr_t;
   const int sub = lane / G::kChunks, pos = lane % G::kChunks;
   if (t.kind == 0 && t.vmask == 0xffffffffu && sn < (int64_t(1) << 26)) {  // wave-uniform; 31 rows of the stride fit 32 bits
+    // load i starts rows_per_load * i rows further down (scalar), so the per-lane offset depends on i only through the
+    // swizzle: at most four different ones per matrix
     const char* tile = reinterpret_cast<const char*>(base + (int64_t)__builtin_amdgcn_readfirstlane(t.row0) * sn);
+    const uint32_t lane_row = (uint32_t)sub * (uint32_t)(sn * 2);  // a sub-tile spans < 4 GB
 #pragma unroll
     for (int i = 0; i < NL; ++i) {
       const int slot = (first + i) * G::kRowsPerLoad + sub;
-      const int chunk = pos ^ (slot & (G::kChunks - 1));
-      const uint32_t off = (uint32_t)slot * (uint32_t)(sn * 2) + (uint32_t)(chunk * 16);  // a sub-tile spans < 4 GB
-      __builtin_amdgcn_global_load_lds((gptr_t)(tile + off), (lptr_t)(stage + (first + i) * 1024), 16, 0, kStreamPolicy);
+      const int chunk = pos ^ (VSWZ ? vstage_swz<D>(slot) : (slot & (G::kChunks - 1)));
+      const char* rows = tile + (int64_t)((first + i) * G::kRowsPerLoad) * (sn * 2);
+      __builtin_amdgcn_global_load_lds((gptr_t)(rows + (lane_row + (uint32_t)(chunk * 16))), (lptr_t)(stage + (first + i) * 1024), 16, 0,
+                                       POLICY);
     }
     return;
   }
   const int last = 31 - __builtin_clz(t.vmask);
+  int lane_now = lane;  // ragged and scattered sub-tiles are rare: nothing of theirs is kept in registers across a key loop
+  asm volatile("" : "+v"(lane_now));
+  const int sub_now = lane_now / G::kChunks, pos_now = lane_now % G::kChunks;
 #pragma unroll
   for (int i = 0; i < NL; ++i) {
-    const int slot = (first + i) * G::kRowsPerLoad + sub;
+    const int slot = (first + i) * G::kRowsPerLoad + sub_now;
     const int row = subtile_row(t, slot, last);
-    const int chunk = pos ^ (slot & (G::kChunks - 1));
+    const int chunk = pos_now ^ (VSWZ ? vstage_swz<D>(slot) : (slot & (G::kChunks - 1)));
     const uint16_t* src = base + (int64_t)row * sn + chunk * 8;
-    __builtin_amdgcn_global_load_lds((gptr_t)src, (lptr_t)(stage + (first + i) * 1024), 16, 0, kStreamPolicy);
+    __builtin_amdgcn_global_load_lds((gptr_t)src, (lptr_t)(stage + (first + i) * 1024), 16, 0, POLICY);
   }
 }
-template <int D>
+template <int D, bool VSWZ = false, int POLICY = kStreamPolicy>
 __device__ __forceinline__ void issue_subtile(const uint16_t* __restrict__ base, int64_t sn, const SubTile& t, char* stage,
                                               int lane) {
-  issue_subtile_part<D, Geo<D>::kLoads>(base, sn, t, stage, lane, 0);
+  issue_subtile_part<D, Geo<D>::kLoads, VSWZ, POLICY>(base, sn, t, stage, lane, 0);
 }
 
 typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
@@ -333,6 +346,30 @@ __device__ __forceinline__ bf16x8 read_v_operand(const char* stageV, int ct, int
   return __builtin_bit_cast(bf16x8, both);
 }
 
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+// A operand of O^T += V^T P^T (32x32x16) for d tile `dt` and k-step `ks`: lane (dcol = lane % 32, hh) needs
+// V[16 ks + 8 (e / 4) + 4 hh + e % 4][32 dt + dcol], e = 0..7 — two transposed reads of four consecutive rows each.
+// A V staged for the 32x32 tiles is only ever read this way — one instruction touches eight rows (four per half of the
+// wavefront) and 64 bytes of each — so its rows are swizzled for that: rows that would fall on the same banks
+// (consecutive rows at d = 128, every other row at d = 64) get different 64-byte segments.
+template <int D>
+__device__ __forceinline__ int vstage_off(int row, int chunk) {
+  return row * Geo<D>::kRowBytes + ((chunk ^ vstage_swz<D>(row)) << 4);
+}
+template <int D>
+__device__ __forceinline__ bf16x8 read_v_operand32(const char* stageV, int dt, int ks, int lane) {
+  const int s = lane & 15, b = lane >> 4;
+  const int row = 16 * ks + 4 * (b >> 1) + (s >> 2);
+  const int col = 32 * dt + 16 * (b & 1) + 4 * (s & 3);
+  const int off0 = vstage_off<D>(row, col >> 3) + (col & 7) * 2;
+  const int off1 = vstage_off<D>(row + 8, col >> 3) + (col & 7) * 2;
+  typedef shortx4 __attribute__((address_space(3))) * lds_ptr;
+  const shortx4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(stageV + off0));
+  const shortx4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(stageV + off1));
+  struct { shortx4 a, b; } both = {lo, hi};
+  return __builtin_bit_cast(bf16x8, both);
+}
+
 // Scaled logits of one 32-key sub-tile (contiguous rows row0 .., row0 a multiple of 32) against up to 16 queries, kept
 // for the column-mass kernel in the layout [head][key quad][query][key within the quad] (fp32): a lane holds, per
 // 16-key tile, the logits of ONE query for four consecutive keys — one 16-byte store — and the 64 lanes of a store
@@ -405,7 +442,7 @@ struct AttnArgs {
   float* part_ml;  // [H, q_pad, n_split, 2]
   int64_t qsh, qsn, ksh, ksn, vsh, vsn, osh, osn;
   int H, M, N, B, n_b, n_gen, n_keep, n_sink, max_active;
-  int sub_per_block, n_sub, per_split, n_split, q_pad;
+  int sub_per_block, n_sub, n_split, q_pad, q_groups;
   float scale_log2;
   // fused layer path only: per-head partial relevances in, scores / kept blocks out
   const float* rel_part;  // [H, n_b]
@@ -413,7 +450,6 @@ struct AttnArgs {
   int32_t* kept_out;      // [n_keep]
   int n_focus_max;
   // dense (probe) layer only
-  int groups_first;   // grid x = query group, z = key split (see the kernel)
   int dense_rows;     // > 0: attend to all of the first dense_rows = M + N key rows, block and sink lists unused
   float* logits_out;  // [H, ceil(L / 4), 16, 4] scaled base-2 logits of the (at most 16) active queries (spill_logits), or null
   float* lse2_out;    // [H, q_pad] base-2 log-sum-exp per row (+inf for an empty row), or null
@@ -473,70 +509,94 @@ __device__ __forceinline__ void merge_splits(const float* __restrict__ part_o, c
   if (lse2 && write_lse) lse2[(int64_t)h * q_pad + a] = lsum > 0.f ? mrun + __builtin_amdgcn_logf(lsum) : INFINITY;
 }
 
-// One workgroup works on one (head, key split, group of QT query tiles); the key axis is walked in rounds of four
-// 32-row sub-tiles ("slots").
-//
-// QT = 1 (up to 16 active queries), four wavefronts: every wavefront owns its slot end to end — it stages the
-//   sub-tile, multiplies it against the one query tile and keeps its own running softmax; the four states are merged
-//   at the end.
-// QT = 2 / 4 (17..32 / 33..64 active queries per group), four / eight wavefronts: the staged sub-tiles are shared and
-//   the key axis advances in half rounds of two sub-tiles.  Wavefront w works for query tile w % QT on member
-//   w / QT of the half round's pair; meanwhile the rows of the next two sub-tiles travel from HBM straight into the
-//   other LDS buffer (each wavefront requests its share: one K or V tile with four wavefronts, half of one with eight;
-//   LDS-direct loads, no staging registers, no LDS stores).  Every K/V byte is fetched once per workgroup, every
-//   wavefront carries the accumulators of ONE query tile, and two workgroups per compute unit put 2 (QT = 2) or 4
-//   (QT = 4) wavefronts on each SIMD: a lone wavefront cannot hide the LDS and MFMA latencies of its own chain
-//   (measured: ~1 us per sub-tile and query tile, four times the arithmetic).
+// What the attention kernels prepare before their first K/V request.
+// R_b = (1 / (|I_focus| H)) sum_h part[h, b] for b = threadIdx.x (n_b <= 256 = blockDim.x), then Top-C into kept_sh; the
+// workgroup with `writer` set also writes scores and kept blocks out.  First use of `sm`.
+__device__ __forceinline__ void rank_blocks(const AttnArgs& p, int32_t* kept_sh, TopkShared& sm, bool writer) {
+  const int tid = threadIdx.x;
+  float r = 0.f;
+  if (tid < p.n_b) r = sum_partials(p.rel_part, p.H, p.n_b, tid);
+  const int n_f = p.counts ? min(max(p.counts[0], 0), p.n_focus_max) : p.n_focus_max;
+  r *= n_f > 0 ? 1.f / ((float)n_f * (float)p.H) : 0.f;
+  auto keyfn = [=](int, uint32_t& key) -> bool {
+    key = order_key(r);
+    return true;
+  };
+  block_topk<kFusedMaxBlocks, true>(keyfn, p.n_b, p.n_keep, kept_sh, nullptr, nullptr, sm);
+  if (writer) {
+    if (p.scores_out && tid < p.n_b) p.scores_out[tid] = r;
+    if (tid < p.n_keep) p.kept_out[tid] = kept_sh[tid];
+  }
+}
+
+// Workgroups whose key range reaches the sink sub-tiles prepare the union of Eq. 8 once: a bitmap of the kept blocks, and
+// whether the sink list is strictly ascending (then it cannot name a position twice).
+struct SinkUnion {
+  const uint32_t* kept_bits;  // see locate_subtile; null when there is none
+  int ascending;
+};
+__device__ __forceinline__ SinkUnion prepare_union(const AttnArgs& p, int split, const int32_t* kept_blocks, uint32_t* bits_sh,
+                                                   int* unsorted_sh) {
+  SinkUnion u;
+  u.kept_bits = nullptr;
+  u.ascending = -1;
+  const int first_sink_sub = p.n_keep * p.sub_per_block + (p.N + kSubTile - 1) / kSubTile;
+  const int n_round = (p.n_sub + kWavesPerGroup - 1) / kWavesPerGroup;                      // rounds of four sub-tiles ...
+  const int last = n_round - 1 - (n_round - 1 - split) % p.n_split;                         // ... the last one of this split
+  if (p.dense_rows == 0 && p.n_sink > 0 && (last + 1) * kWavesPerGroup > first_sink_sub) {  // uniform over the workgroup
+    const bool bitmap = p.n_keep > 0 && p.n_b <= kBitmapBlocks;
+    const int words = bitmap ? (p.n_b + 31) >> 5 : 0;
+    for (int i = threadIdx.x; i < words; i += blockDim.x) bits_sh[i] = 0u;
+    if (threadIdx.x == 0) *unsorted_sh = 0;
+    __syncthreads();
+    if (bitmap) {
+      for (int i = threadIdx.x; i < p.n_keep; i += blockDim.x) {
+        const int b = kept_blocks[i];
+        if (b >= 0 && b < p.n_b) atomicOr(&bits_sh[b >> 5], 1u << (b & 31));
+      }
+    }
+    for (int i = threadIdx.x; i + 1 < p.n_sink; i += blockDim.x)
+      if (p.sink_idx[i + 1] <= p.sink_idx[i]) *unsorted_sh = 1;
+    __syncthreads();
+    if (bitmap) u.kept_bits = bits_sh;
+    u.ascending = *unsorted_sh ? 0 : 1;
+  }
+  return u;
+}
+
+// Up to 16 active queries.  One workgroup works on one (head, key split); the key axis is walked in rounds of four 32-row
+// sub-tiles ("slots"), and every one of its four wavefronts owns its slot end to end — it stages the sub-tile, multiplies it
+// against the one query tile and keeps its own running softmax; the four states are merged at the end.
 //
 // FUSE bit 0 clear: kept_blocks comes from memory.
 // FUSE bit 0 set (fused layer path): the workgroup first assembles R_b from the per-head partial relevances and ranks
 // them itself — every workgroup repeats this small computation instead of waiting for a separate Top-C kernel.
-// FUSE bit 2 set (QT = 1, dense probe layer): the scaled logits of every (query, key) are also written out, so that
+// FUSE bit 2 set (dense probe layer): the scaled logits of every (query, key) are also written out, so that
 // the column attention mass of Eq. 6 needs no QK^T pass of its own.
-// FUSE bit 1 set (QT = 1 only): double-buffered key loop for launches in which a wavefront walks several sub-tiles
+// FUSE bit 1 set: double-buffered key loop for launches in which a wavefront walks several sub-tiles
 // (the dense comparison, the probe layer): the next sub-tile's rows travel HBM -> LDS into the wavefront's second
 // stage while the current one is multiplied, so one wavefront per SIMD keeps both the memory pipe and the matrix
 // cores busy.
 // In every case a second, small kernel merges the key splits.  (Letting the last workgroup of a head merge them
 // behind device-scope fences was measured: the fences cost ~10 us per launch, more than the launch they save.)
-template <int D, int QT, int FUSE>
-__global__ __launch_bounds__((QT == 4 ? 512 : 256), (QT == 4 ? 4 : ((FUSE & 2) == 0 ? 2 : 1))) void sparse_attn_kernel(
-    const AttnArgs p) {
+template <int D, int FUSE>
+__global__ __launch_bounds__(256, (FUSE & 2) == 0 ? 2 : 1) void sparse_attn_kernel(const AttnArgs p) {
   using G = Geo<D>;
   constexpr bool FUSED = (FUSE & 1) != 0;                // Top-C in the prologue
-  constexpr bool SHARED = QT > 1;                        // staged sub-tiles are shared by the wavefronts
-  constexpr bool PIPE = (FUSE & 2) != 0;                 // QT = 1 only: two K/V stages per wavefront
-  constexpr bool SPILL = (FUSE & 4) != 0;                // QT = 1, dense: also write the scaled logits (sink scoring)
-  static_assert(!SPILL || QT == 1, "logits are spilled for one query tile only");
-  static_assert(!(PIPE && SHARED), "shared sub-tiles have their own pipelining");
-  constexpr int W = QT == 4 ? 2 * kWavesPerGroup : kWavesPerGroup;  // wavefronts in the workgroup
-  constexpr int KG = W / QT;                             // wavefronts per query tile, each on its own slots
-  constexpr int NLH = G::kLoads / (W / kWavesPerGroup);  // SHARED: loads per wavefront and half round
-  static_assert(!SHARED || KG == 2, "a half round holds two sub-tiles");
+  constexpr bool PIPE = (FUSE & 2) != 0;                 // two K/V stages per wavefront
+  constexpr bool SPILL = (FUSE & 4) != 0;                // dense: also write the scaled logits (sink scoring)
   constexpr int kBufBytes = 2 * G::kStageBytes;          // one slot: K stage + V stage of a sub-tile
-  constexpr int kMergeBytes = 16 * D * 4;                // one wavefront's O tile in the final merge
-  static_assert(QT == 1 || QT == 2 || QT == 4, "query tiles per workgroup");
+  static_assert(16 * D * 4 <= kBufBytes, "a wavefront's O tile fits its stage");
   // Two buffers of four slots; the second exists in the double-buffered variant only.
-  // (SHARED: buffer A holds the two slots of the even half rounds, buffer B those of the odd ones — two separate arrays,
-  // so that the compiler can tell an LDS-direct load into one from the operand reads of the other.)
-  __shared__ __attribute__((aligned(16))) char ldsA[(SHARED ? 2 : kWavesPerGroup) * kBufBytes];
-  __shared__ __attribute__((aligned(16))) char ldsB[PIPE ? kWavesPerGroup * kBufBytes : (SHARED ? 2 * kBufBytes : 16)];
-  static_assert(!SHARED || 4 * kMergeBytes <= 2 * kBufBytes, "merge scratch of four wavefronts fits one buffer");
-  __shared__ uint32_t maskA[kWavesPerGroup];  // SHARED: the keys of each slot that take part
-  __shared__ float2 ml_sh[W][16];             // final merge: running maximum and sum per wavefront and query
+  __shared__ __attribute__((aligned(16))) char ldsA[kWavesPerGroup * kBufBytes];
+  __shared__ __attribute__((aligned(16))) char ldsB[PIPE ? kWavesPerGroup * kBufBytes : 16];
+  __shared__ float2 ml_sh[kWavesPerGroup][16];  // final merge: running maximum and sum per wavefront and query
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c = lane & 15, g = lane >> 4;
-  // Grid: (key split, head, query group) — or, with several query groups, (query group, head, key split): the
-  // workgroups that run side by side then belong to one head and walk the same K/V rows at about the same time, so
-  // that each XCD's L2 serves a row to all of them after fetching it once.
-  const int split = p.groups_first ? blockIdx.z : blockIdx.x, h = blockIdx.y, qg = p.groups_first ? blockIdx.x : blockIdx.z;
-  const int qt = wave % QT, kg = wave / QT;
-  const int q0 = (qg * QT + qt) * kQTile;  // first position in the active list of this wavefront's query tile
-
-  const int slot = wave & (kWavesPerGroup - 1);  // QT = 1: the slot this wavefront owns
-  char* stageK = ldsA + slot * kBufBytes;
+  const int split = blockIdx.x, h = blockIdx.y;
+  char* stageK = ldsA + wave * kBufBytes;  // the slot this wavefront owns
   char* stageV = stageK + G::kStageBytes;
   const uint16_t* Qh = p.Q + (int64_t)h * p.qsh;
   const uint16_t* Kh = p.K + (int64_t)h * p.ksh;
@@ -551,98 +611,30 @@ __global__ __launch_bounds__((QT == 4 ? 512 : 256), (QT == 4 ? 4 : ((FUSE & 2) =
   bf16x8 q[1][G::kKSteps];
   int qrow_early = -1;
   if (FUSED) {
-    qrow_early = fetch_q_row(p.active_idx, q0, p.max_active, p.n_gen, lane);
+    qrow_early = fetch_q_row(p.active_idx, 0, p.max_active, p.n_gen, lane);
     load_q_tile<D>(q[0], Qh, p.qsn, qrow_early, lane);
   }
   if (FUSED) {
-    // R_b = (1 / (|I_focus| H)) sum_h part[h, b] for b = threadIdx.x (n_b <= 256), then Top-C
-    const int tid = threadIdx.x;
-    float r = 0.f;
-    if (tid < p.n_b) r = sum_partials(p.rel_part, p.H, p.n_b, tid);
-    const int n_f = p.counts ? min(max(p.counts[0], 0), p.n_focus_max) : p.n_focus_max;
-    r *= n_f > 0 ? 1.f / ((float)n_f * (float)p.H) : 0.f;
-    auto keyfn = [=](int, uint32_t& key) -> bool {
-      key = order_key(r);
-      return true;
-    };
-    block_topk<kFusedMaxBlocks, true>(keyfn, p.n_b, p.n_keep, kept_sh, nullptr, nullptr, topk_sm);  // n_b <= 256 = blockDim.x; first use of topk_sm
-    if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0) {
-      if (p.scores_out && tid < p.n_b) p.scores_out[tid] = r;
-      if (tid < p.n_keep) p.kept_out[tid] = kept_sh[tid];
-    }
+    rank_blocks(p, kept_sh, topk_sm, blockIdx.x == 0 && blockIdx.y == 0);
     kept_blocks = kept_sh;
   }
-
-  // Workgroups whose key range reaches the sink sub-tiles prepare the union of Eq. 8 once: a bitmap of the kept
-  // blocks, and whether the sink list is strictly ascending (then it cannot name a position twice).
   __shared__ uint32_t kept_bits_sh[kBitmapBlocks / 32];
   __shared__ int sinks_unsorted_sh;
-  const uint32_t* kept_bits = nullptr;
-  int sinks_ascending = -1;
-  {
-    const int first_sink_sub = p.n_keep * p.sub_per_block + (p.N + kSubTile - 1) / kSubTile;
-    const int my_end = min((split + 1) * p.per_split, p.n_sub);
-    if (p.dense_rows == 0 && p.n_sink > 0 && my_end > first_sink_sub) {  // uniform over the workgroup
-      const bool bitmap = p.n_keep > 0 && p.n_b <= kBitmapBlocks;
-      const int words = bitmap ? (p.n_b + 31) >> 5 : 0;
-      for (int i = threadIdx.x; i < words; i += blockDim.x) kept_bits_sh[i] = 0u;
-      if (threadIdx.x == 0) sinks_unsorted_sh = 0;
-      __syncthreads();
-      if (bitmap) {
-        for (int i = threadIdx.x; i < p.n_keep; i += blockDim.x) {
-          const int b = kept_blocks[i];
-          if (b >= 0 && b < p.n_b) atomicOr(&kept_bits_sh[b >> 5], 1u << (b & 31));
-        }
-      }
-      for (int i = threadIdx.x; i + 1 < p.n_sink; i += blockDim.x)
-        if (p.sink_idx[i + 1] <= p.sink_idx[i]) sinks_unsorted_sh = 1;
-      __syncthreads();
-      if (bitmap) kept_bits = kept_bits_sh;
-      sinks_ascending = sinks_unsorted_sh ? 0 : 1;
-    }
-  }
+  const SinkUnion uni = prepare_union(p, split, kept_blocks, kept_bits_sh, &sinks_unsorted_sh);
+  const uint32_t* kept_bits = uni.kept_bits;
+  const int sinks_ascending = uni.ascending;
 
   // Order of the memory requests: the query row ids first (tiny, they return first), then the first
   // sub-tile's K and V rows as soon as its block id is known, then the query rows and the device-side count.
-  const int st_begin = split * p.per_split;
-  const int st_end = min(st_begin + p.per_split, p.n_sub);
-  int st = st_begin + slot;
-  const int qrow = FUSED ? qrow_early : fetch_q_row(p.active_idx, q0, p.max_active, p.n_gen, lane);
+  int st = split * kWavesPerGroup + wave;
+  const int st_end = p.n_sub, st_step = p.n_split * kWavesPerGroup;
+  const int qrow = FUSED ? qrow_early : fetch_q_row(p.active_idx, 0, p.max_active, p.n_gen, lane);
   SubTile t;
   t.kind = 0;
   t.row0 = 0;
   t.vmask = 0u;
   t.sink_row = 0;
-  // SHARED: wavefront w stages, per half round, loads [NLH (w >> 2), +NLH) of the K (bit 1 of w clear) or V rows of
-  // the half round's sub-tile (w & 1)
-  const int h_i = wave & 1, h_kv = (wave >> 1) & 1, h_first = (wave >> 2) * NLH;
-  // SHARED: this wavefront's share of half round ph goes straight into buffer `buf` (A for even ph, B for odd ph)
-  auto dma_half = [&](int ph, char* buf) __attribute__((always_inline)) {
-    SubTile tp;
-    tp.kind = 0;
-    tp.row0 = 0;
-    tp.vmask = 0u;
-    tp.sink_row = 0;
-    const int sub = st_begin + 2 * ph + h_i;
-    if (sub < st_end)
-      tp = locate_subtile(sub, lane, p.M, p.N, p.B, p.n_b, p.sub_per_block, kept_blocks, p.n_keep, p.sink_idx, p.n_sink, kept_bits,
-                          sinks_ascending, p.dense_rows, FUSED);
-    // (the lane id goes through an empty asm so that the per-lane byte offsets are worked out again in every half
-    // round instead of being kept in registers across the loop: this variant has none to spare)
-    int lane_now = lane;
-    asm volatile("" : "+v"(lane_now));
-    if (tp.vmask != 0u)
-      issue_subtile_part<D, NLH>(h_kv ? Vh : Kh, h_kv ? p.vsn : p.ksn, tp, buf + h_i * kBufBytes + h_kv * G::kStageBytes, lane_now,
-                                 h_first);
-    if (h_kv == 0 && h_first == 0 && lane == 0) maskA[2 * (ph & 1) + h_i] = tp.vmask;
-  };
-  // SHARED: the first two half rounds are requested before anything else is waited for (the query rows take two
-  // dependent round trips; both buffers are free until the loop starts)
-  if (SHARED) {
-    dma_half(0, ldsA);
-    if (st_begin + 2 < st_end) dma_half(1, ldsB);
-  }
-  if (!SHARED && st < st_end) {
+  if (st < st_end) {
     t = locate_subtile(st, lane, p.M, p.N, p.B, p.n_b, p.sub_per_block, kept_blocks, p.n_keep, p.sink_idx, p.n_sink, kept_bits,
                           sinks_ascending, p.dense_rows, FUSED);
     if (t.vmask != 0u) {
@@ -652,7 +644,7 @@ __global__ __launch_bounds__((QT == 4 ? 512 : 256), (QT == 4 ? 4 : ((FUSE & 2) =
   }
   if (!FUSED) load_q_tile<D>(q[0], Qh, p.qsn, qrow, lane);
   const int n_act = p.counts ? min(max(p.counts[1], 0), p.max_active) : p.max_active;
-  mask_q_tile<D>(q[0], q0, n_act, lane);
+  mask_q_tile<D>(q[0], 0, n_act, lane);
 
   float m_run = -INFINITY, l_run = 0.f;
   floatx4 o[G::kColTiles];
@@ -696,37 +688,7 @@ __global__ __launch_bounds__((QT == 4 ? 512 : 256), (QT == 4 ? 4 : ((FUSE & 2) =
     return locate_subtile(sub, lane, p.M, p.N, p.B, p.n_b, p.sub_per_block, kept_blocks, p.n_keep, p.sink_idx, p.n_sink, kept_bits,
                           sinks_ascending, p.dense_rows, FUSED);
   };
-  if (SHARED) {
-    // Half rounds of two sub-tiles (wavefront w multiplies member w / QT of the pair for query tile w % QT).  While half
-    // round ph is multiplied out of one buffer, the rows of half round ph + 1 travel from HBM straight into the other —
-    // for the whole of that time, with no staging registers and no LDS stores.  A wavefront's loads have landed when
-    // its vmcnt reaches zero; the barrier then tells everyone that all shares have landed and that the buffer just read
-    // is free.  Unrolled by two, so that every access names its buffer statically: the compiler then knows that an
-    // LDS-direct load into one buffer does not touch the operand reads of the other and does not wait for it.
-    const int n_half = (st_end - st_begin + 1) / 2;  // uniform over the workgroup
-    // a wavefront whose query tile lies past the device-side count only stages: its products would be discarded
-    const bool tile_live = q0 < n_act;
-    auto consume_buf = [&](int ph, const char* buf) __attribute__((always_inline)) {
-      const uint32_t vm = __builtin_amdgcn_readfirstlane(maskA[2 * (ph & 1) + kg]);
-      if (vm != 0u && tile_live) {
-        const char* cK = buf + kg * kBufBytes;
-        consume(cK, cK + G::kStageBytes, vm, 0);
-      }
-    };
-    wait_loads();
-    __syncthreads();  // half round 0 is staged
-    for (int ph = 0; ph < n_half; ph += 2) {
-      if (ph > 0 && ph + 1 < n_half) dma_half(ph + 1, ldsB);  // buffer B was last read in half round ph - 1, before the last barrier
-      consume_buf(ph, ldsA);
-      wait_loads();
-      __syncthreads();  // half round ph + 1 is staged; everyone is done with buffer A
-      if (ph + 1 >= n_half) break;  // uniform
-      if (ph + 2 < n_half) dma_half(ph + 2, ldsA);
-      consume_buf(ph + 1, ldsB);
-      wait_loads();
-      __syncthreads();
-    }
-  } else if (!PIPE) {
+  if (!PIPE) {
     // one sub-tile per wavefront at most (the launcher picks this variant only when a split holds no more sub-tiles
     // than the workgroup has wavefronts): no key loop, and none of its code — these launches are a few microseconds
     // long and start with a cold instruction cache, so every KB of code they walk through shows in the run time
@@ -742,7 +704,7 @@ __global__ __launch_bounds__((QT == 4 ? 512 : 256), (QT == 4 ? 4 : ((FUSE & 2) =
     // the compiler can tell that the loads into one do not touch the operand reads of the other.  No barrier: the slots
     // are private to the wavefront (which has finished reading `nxt` one step ago; wait_lds_reads makes that explicit).
     auto step = [&](const char* cur, char* nxt) __attribute__((always_inline)) {
-      const int st_next = st + kWavesPerGroup;
+      const int st_next = st + st_step;
       SubTile tn = no_tile();
       if (st_next < st_end) tn = locate(st_next);
       if (tn.vmask != 0u) {
@@ -767,16 +729,11 @@ __global__ __launch_bounds__((QT == 4 ? 512 : 256), (QT == 4 ? 4 : ((FUSE & 2) =
     }
   }
 
-  // ---- merge the wavefronts that share a query tile through LDS (the stages are free by now)
-  // scratch of wavefront w: its O tile, in the stage buffers (SHARED: four wavefronts per buffer)
-  auto merge_tile = [&](int w) __attribute__((always_inline)) -> char* {
-    return SHARED ? ((w < 4 ? ldsA : ldsB) + (w & 3) * kMergeBytes) : (ldsA + w * kMergeBytes);
-  };
-  float* myO = reinterpret_cast<float*>(merge_tile(wave));  // [16][D]
-  constexpr int kPerThread = D / 16;                                  // output columns per thread in the merge
+  // ---- merge the four wavefronts through LDS: each leaves its O tile [16][D] in its own stage
+  float* myO = reinterpret_cast<float*>(stageK);
+  constexpr int kPerThread = D / 16;  // output columns per thread in the merge
   constexpr int kVec = kPerThread / 4;
-  constexpr int kTilesPerPass = W / kWavesPerGroup;                   // 256 threads merge one query tile
-  const int mq = (threadIdx.x >> 4) & 15;                             // query of the tile this thread merges
+  const int mq = threadIdx.x >> 4;    // query this thread merges
   const int mc = (threadIdx.x & 15) * kPerThread;
   wait_loads();
   __syncthreads();  // every staged sub-tile has been consumed by everyone
@@ -784,58 +741,317 @@ __global__ __launch_bounds__((QT == 4 ? 512 : 256), (QT == 4 ? 4 : ((FUSE & 2) =
   for (int ct = 0; ct < G::kColTiles; ++ct) *reinterpret_cast<floatx4*>(myO + c * D + ct * 16 + 4 * g) = o[ct];
   if (g == 0) ml_sh[wave][c] = make_float2(m_run, l_run);
   __syncthreads();
+  float2 ml[kWavesPerGroup];
+  float4 ow[kWavesPerGroup][kVec];
 #pragma unroll
-  for (int pass = 0; pass < QT / kTilesPerPass; ++pass) {
-    const int tq = pass * kTilesPerPass + (threadIdx.x >> 8);
-    float2 ml[KG];
-    float4 ow[KG][kVec];
+  for (int w = 0; w < kWavesPerGroup; ++w) {
+    ml[w] = ml_sh[w][mq];
 #pragma unroll
-    for (int k = 0; k < KG; ++k) {
-      const int w = tq + QT * k;  // the wavefronts of query tile tq
-      ml[k] = ml_sh[w][mq];
+    for (int i = 0; i < kVec; ++i) ow[w][i] = *reinterpret_cast<const float4*>(ldsA + w * kBufBytes + (mq * D + mc + 4 * i) * 4);
+  }
+  float mmax = ml[0].x;
 #pragma unroll
-      for (int i = 0; i < kVec; ++i)
-        ow[k][i] = *reinterpret_cast<const float4*>(merge_tile(w) + (mq * D + mc + 4 * i) * 4);
+  for (int w = 1; w < kWavesPerGroup; ++w) mmax = fmaxf(mmax, ml[w].x);
+  float acc_o[kPerThread];
+#pragma unroll
+  for (int i = 0; i < kPerThread; ++i) acc_o[i] = 0.f;
+  float lsum = 0.f;
+#pragma unroll
+  for (int w = 0; w < kWavesPerGroup; ++w) {
+    const float f = ml[w].y > 0.f ? __builtin_amdgcn_exp2f(ml[w].x - mmax) : 0.f;
+    lsum += f * ml[w].y;
+#pragma unroll
+    for (int i = 0; i < kVec; ++i) {
+      acc_o[4 * i] += f * ow[w][i].x;
+      acc_o[4 * i + 1] += f * ow[w][i].y;
+      acc_o[4 * i + 2] += f * ow[w][i].z;
+      acc_o[4 * i + 3] += f * ow[w][i].w;
     }
-    float mmax = ml[0].x;
+  }
+  const int a = mq;  // position in the active list
+  if (a < n_act) {
+    if (p.n_split == 1) {
+      const float inv = lsum > 0.f ? 1.f / lsum : 0.f;
+      uint16_t* dst = p.out + (int64_t)h * p.osh + (int64_t)a * p.osn + mc;
 #pragma unroll
-    for (int k = 1; k < KG; ++k) mmax = fmaxf(mmax, ml[k].x);
-    float acc_o[kPerThread];
+      for (int i = 0; i < kPerThread; i += 2)
+        *reinterpret_cast<uint32_t*>(dst + i) = cvt_pk_bf16(acc_o[i] * inv, acc_o[i + 1] * inv);
+      if (p.lse && (threadIdx.x & 15) == 0)
+        p.lse[(int64_t)h * p.max_active + a] = lsum > 0.f ? (mmax + __builtin_amdgcn_logf(lsum)) * kLn2 : -INFINITY;
+      if (p.lse2_out && (threadIdx.x & 15) == 0)
+        p.lse2_out[(int64_t)h * p.q_pad + a] = lsum > 0.f ? mmax + __builtin_amdgcn_logf(lsum) : INFINITY;
+    } else {
+      const int64_t row = ((int64_t)h * p.q_pad + a) * p.n_split + split;
+      float* dst = p.part_o + row * D + mc;
 #pragma unroll
-    for (int i = 0; i < kPerThread; ++i) acc_o[i] = 0.f;
-    float lsum = 0.f;
+      for (int i = 0; i < kPerThread; i += 4)
+        *reinterpret_cast<float4*>(dst + i) = make_float4(acc_o[i], acc_o[i + 1], acc_o[i + 2], acc_o[i + 3]);
+      if ((threadIdx.x & 15) == 0)
+        *reinterpret_cast<float2*>(p.part_ml + 2 * row) = make_float2(lsum > 0.f ? mmax : -INFINITY, lsum);
+    }
+  }
+}
+
+// More than 16 queries: the same work decomposition as the 16-query kernel — a sub-tile goes from the memory request to the
+// MFMAs in one slot of LDS, four slots per workgroup — with 32-query tiles on v_mfma_f32_32x32x16_bf16.  A 32x32 tile takes
+// half the LDS operand reads and half the MFMA instructions of two 16-query tiles, so that the QK^T -> softmax -> PV chain of
+// an in-order wavefront fits into the time its share of HBM needs for the next sub-tile.
+//   S^T = K Q^T   lane (query = lane % 32, hh = lane / 32), register v: logit of key 8 (v / 4) + 4 hh + v % 4
+//   O^T = V^T P^T the same registers, packed to bf16, are the B operand of k-step v / 8
+// NT = 1 (up to 32 queries per query group), four wavefronts: a wavefront owns its slot; no barrier in the key loop.
+// NT = 2 (up to 64), eight wavefronts: wavefronts s and s + 4 share slot s, each stages half of its rows (K / V) and carries
+//   one query tile; one barrier per round.  (One wavefront with both tiles needs 128 accumulator registers outside the
+//   vector registers, and copying them for the rescale made its chain longer than the memory time.)  The second tile's
+//   wavefronts only stage when the device-side count leaves it empty.
+// MODE bit 0: Top-C in the prologue.  Bit 1: a slot walks several sub-tiles (key loop).  Bit 2 (with bit 1): two stages per
+// slot, the next sub-tile's rows travel while the current one is multiplied, one workgroup per compute unit; without it (NT =
+// 1) the operands are all read into registers before the next sub-tile is requested into the same stage, and two workgroups
+// per compute unit cover each other: better where several query groups share rows in the L2 and the loads return fast.
+// Bit 3: the rows are read by several query groups and should stay in the L2.
+// Bound by HBM.  32 heads, 32 832 keys, all kept: 89 us with 30 queries (6.0 TB/s; 16-query tiles on shared sub-tiles took 94),
+// 95 us with 60 (101); half of the 64-row blocks and 327 sinks: 53 us (57); 4 K/V heads, 196 queries, 16 640 keys: 28 us (42).
+// Grid: one-dimensional.  Workgroups go to the XCDs round-robin, so the query groups of one (head, key split) pair are
+// placed eight apart: they run on the same XCD at about the same time and its L2 serves their common K/V rows.
+template <int D, int NT, int MODE>
+__global__ __launch_bounds__(256 * NT, NT == 2 || (MODE & 4) == 0 ? 2 : 1) void wide_attn_kernel(const AttnArgs p) {
+  using G = Geo<D>;
+  constexpr bool FUSED = (MODE & 1) != 0, PIPE = (MODE & 2) != 0, DOUBLE = (MODE & 4) != 0;
+  static_assert(!DOUBLE || PIPE, "two stages are for the key loop");
+  static_assert(NT == 1 || DOUBLE || !PIPE, "a shared slot needs the second stage");
+  constexpr int kPolicy = (MODE & 8) != 0 ? 0 : kStreamPolicy;
+  constexpr int kKS = D / 16, kDT = D / 32;
+  constexpr int kBufBytes = 2 * G::kStageBytes;  // K stage + V stage of a sub-tile
+  constexpr int kOChunks = D / 4;                // 16-byte chunks of one fp32 output row
+  static_assert(32 * D * 4 <= kBufBytes, "an O tile fits a slot");
+  __shared__ __attribute__((aligned(16))) char ldsA[kWavesPerGroup * kBufBytes];
+  __shared__ __attribute__((aligned(16))) char ldsB[DOUBLE ? kWavesPerGroup * kBufBytes : 16];
+  __shared__ float2 ml_sh[kWavesPerGroup][32];
+  __shared__ __attribute__((aligned(16))) char topk_raw[FUSED ? sizeof(TopkShared) : 16];
+  __shared__ int32_t kept_sh[FUSED ? kFusedMaxBlocks : 1];
+  __shared__ uint32_t kept_bits_sh[kBitmapBlocks / 32];
+  __shared__ int sinks_unsorted_sh;
+
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int slot = wave & (kWavesPerGroup - 1), tile = NT == 1 ? 0 : wave >> 2;
+  const int qi = lane & 31, hh = lane >> 5;
+  const int slot8 = (int)blockIdx.x >> 3;
+  const int pair = (slot8 / p.q_groups) * 8 + (int)(blockIdx.x & 7u), qg = slot8 % p.q_groups;
+  if (pair >= p.n_split * p.H) return;  // whole workgroup
+  const int h = pair / p.n_split, split = pair - h * p.n_split;
+  if (qg > 0) {  // a query group past the device-side count has nothing to do
+    const int n = p.counts ? min(max(p.counts[1], 0), p.max_active) : p.max_active;
+    if (qg * NT * 32 >= n) return;
+  }
+  const int q0 = (qg * NT + tile) * 32;  // first query of this wavefront's tile
+  const uint16_t* Qh = p.Q + (int64_t)h * p.qsh;
+  const uint16_t* Kh = p.K + (int64_t)h * p.ksh;
+  const uint16_t* Vh = p.V + (int64_t)h * p.vsh;
+
+  int qrow = q0 + qi < p.max_active ? p.active_idx[q0 + qi] : -1;
+  if (qrow >= p.n_gen) qrow = -1;
+  bf16x8 q[kKS];  // B operand of K Q^T: lane (query, hh) holds Q[query][16 ks + 8 hh .. + 7]
+  auto load_q = [&]() __attribute__((always_inline)) {
+    const uint16_t* src = Qh + (int64_t)max(qrow, 0) * p.qsn + hh * 8;
 #pragma unroll
-    for (int k = 0; k < KG; ++k) {
-      const float f = ml[k].y > 0.f ? __builtin_amdgcn_exp2f(ml[k].x - mmax) : 0.f;
-      lsum += f * ml[k].y;
+    for (int ks = 0; ks < kKS; ++ks) q[ks] = as_bf16x8(*reinterpret_cast<const uint4*>(src + ks * 16));
+  };
+  const int32_t* kept_blocks = p.kept_blocks;
+  if (FUSED) {  // the query rows travel while the blocks are ranked
+    load_q();
+    rank_blocks(p, kept_sh, *reinterpret_cast<TopkShared*>(topk_raw), pair == 0 && qg == 0);
+    kept_blocks = kept_sh;
+  }
+  const SinkUnion uni = prepare_union(p, split, kept_blocks, kept_bits_sh, &sinks_unsorted_sh);
+
+  const int st_step = p.n_split * kWavesPerGroup;
+  auto locate = [&](int sub) __attribute__((always_inline)) {
+    SubTile t;
+    t.kind = 0;
+    t.row0 = 0;
+    t.vmask = 0u;
+    t.sink_row = 0;
+    if (sub < p.n_sub)
+      t = locate_subtile(sub, lane, p.M, p.N, p.B, p.n_b, p.sub_per_block, kept_blocks, p.n_keep, p.sink_idx, p.n_sink, uni.kept_bits,
+                         uni.ascending, p.dense_rows, FUSED);
+    return t;
+  };
+  auto request = [&](const SubTile& t, char* stage) __attribute__((always_inline)) {
+    if (t.vmask == 0u) return;
+    if (NT == 1 || tile == 0) issue_subtile<D, false, kPolicy>(Kh, p.ksn, t, stage, lane);
+    if (NT == 1 || tile == 1) issue_subtile<D, true, kPolicy>(Vh, p.vsn, t, stage + G::kStageBytes, lane);
+  };
+  auto staged = [&]() __attribute__((always_inline)) {  // every requested row of this round is in LDS
+    wait_loads();
+    if (NT > 1) __syncthreads();
+  };
+  char* slotA = ldsA + slot * kBufBytes;
+  int st = split * kWavesPerGroup + slot;
+  SubTile t = locate(st);
+  request(t, slotA);
+  if (!FUSED) load_q();
+  const int n_act = p.counts ? min(max(p.counts[1], 0), p.max_active) : p.max_active;
+  {
+    const bool live = qrow >= 0 && q0 + qi < n_act;
 #pragma unroll
-      for (int i = 0; i < kVec; ++i) {
-        acc_o[4 * i] += f * ow[k][i].x;
-        acc_o[4 * i + 1] += f * ow[k][i].y;
-        acc_o[4 * i + 2] += f * ow[k][i].z;
-        acc_o[4 * i + 3] += f * ow[k][i].w;
+    for (int ks = 0; ks < kKS; ++ks) q[ks] = live ? q[ks] : as_bf16x8(make_uint4(0u, 0u, 0u, 0u));
+  }
+  float m_run = -INFINITY, l_run = 0.f;  // l_run: this lane's share of the row sum (its 16 of every 32 keys)
+  floatx16 o[kDT];
+#pragma unroll
+  for (int dt = 0; dt < kDT; ++dt)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) o[dt][v] = 0.f;
+
+  // one staged sub-tile into the running softmax
+  auto consume = [&](auto k_operand, auto v_operand, uint32_t vmask) __attribute__((always_inline)) {
+    floatx16 acc;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < kKS; ++ks) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_operand(ks), q[ks], acc, 0, 0, 0);
+    if (vmask != 0xffffffffu) {  // wave-uniform: slots that hold no key
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[v] = ((vmask >> (8 * (v >> 2) + 4 * hh + (v & 3))) & 1u) ? acc[v] : -INFINITY;
+    }
+    float mx = fmaxf(acc[0], acc[1]);
+#pragma unroll
+    for (int v = 2; v < 16; ++v) mx = fmaxf(mx, acc[v]);
+    const uintx2 sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+    mx = fmaxf(__uint_as_float(sw.x), __uint_as_float(sw.y)) * p.scale_log2;
+    const float m_new = fmaxf(m_run, mx);
+    const float m_use = m_new == -INFINITY ? 0.f : m_new;
+    if (__ballot(m_new != m_run) != 0ull) {  // some running maximum of this wavefront moves (rare after the first sub-tiles)
+      const float alpha = __builtin_amdgcn_exp2f(m_run - m_use);
+      l_run *= alpha;
+#pragma unroll
+      for (int dt = 0; dt < kDT; ++dt) o[dt] *= alpha;
+      m_run = m_new;
+    }
+    float ps[16];
+#pragma unroll
+    for (int v = 0; v < 16; ++v) ps[v] = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[v], p.scale_log2, -m_use));
+    float sum = ps[0] + ps[1];
+#pragma unroll
+    for (int v = 2; v < 16; v += 2) sum += ps[v] + ps[v + 1];
+    l_run += sum;
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      const bf16x8 pb = as_bf16x8(make_uint4(cvt_pk_bf16(ps[8 * ks], ps[8 * ks + 1]), cvt_pk_bf16(ps[8 * ks + 2], ps[8 * ks + 3]),
+                                             cvt_pk_bf16(ps[8 * ks + 4], ps[8 * ks + 5]), cvt_pk_bf16(ps[8 * ks + 6], ps[8 * ks + 7])));
+#pragma unroll
+      for (int dt = 0; dt < kDT; ++dt) o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_operand(dt, ks), pb, o[dt], 0, 0, 0);
+    }
+  };
+  auto k_at = [&](const char* stage, int ks) __attribute__((always_inline)) {
+    return as_bf16x8(*reinterpret_cast<const uint4*>(stage + stage_off<D>(qi, 2 * ks + hh)));
+  };
+  auto v_at = [&](const char* stage, int dt, int ks) __attribute__((always_inline)) {
+    return read_v_operand32<D>(stage + G::kStageBytes, dt, ks, lane);
+  };
+  const bool tile_live = q0 < n_act;
+  if (!PIPE) {  // one sub-tile per slot at most
+    staged();
+    if (t.vmask != 0u && tile_live)
+      consume([&](int ks) { return k_at(slotA, ks); }, [&](int dt, int ks) { return v_at(slotA, dt, ks); }, t.vmask);
+  } else {
+    SubTile tn = locate(st + st_step);
+    // One round: `t` sits in `cur`.  Between the arrival of its rows and the request of the next ones lies only what has to:
+    // the operand reads the compiler would otherwise put behind the arrival of the next rows (the transposed V reads, which
+    // it cannot tell from the stage being filled), or that the request overwrites.  The sub-tile after the next is located —
+    // a block id from memory — once the request is out.
+    auto round = [&](const char* cur, char* nxt) __attribute__((always_inline)) {
+      staged();
+      bf16x8 kop[kKS], vop[2][kDT];
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int dt = 0; dt < kDT; ++dt) vop[ks][dt] = v_at(cur, dt, ks);
+      if (!DOUBLE) {
+#pragma unroll
+        for (int ks = 0; ks < kKS; ++ks) kop[ks] = k_at(cur, ks);
       }
+      wait_lds_reads();
+      request(tn, nxt);
+      const SubTile t2 = locate(st + 2 * st_step);
+      if (t.vmask != 0u && tile_live)
+        consume([&](int ks) { return DOUBLE ? k_at(cur, ks) : kop[ks]; }, [&](int dt, int ks) { return vop[ks][dt]; }, t.vmask);
+      t = tn;
+      tn = t2;
+      st += st_step;
+    };
+    if (DOUBLE) {
+      char* slotB = ldsB + slot * kBufBytes;
+      for (int first = split * kWavesPerGroup; first < p.n_sub; first += 2 * st_step) {  // uniform over the workgroup
+        round(slotA, slotB);
+        if (first + st_step < p.n_sub) round(slotB, slotA);
+      }
+    } else {
+      for (int first = split * kWavesPerGroup; first < p.n_sub; first += st_step) round(slotA, slotA);
     }
-    const int a = (qg * QT + tq) * kQTile + mq;  // position in the active list
+  }
+
+  // ---- merge the four slots, one query tile at a time, through LDS.  16-byte chunk ch of query row r sits at chunk ch ^ f(r):
+  // conflict-free for the writes (32 rows, two chunks) and the reads.
+  auto chunk_at = [&](int row, int ch) {
+    const int f = D == 128 ? ((row & 7) << 2 | row >> 3) : ((row & 7) << 1 | (row >> 3 & 1));
+    return (row * kOChunks + (ch ^ f)) * 16;
+  };
+  if (NT > 1) __syncthreads();  // the slots have been read by both wavefronts
+#pragma unroll
+  for (int n = 0; n < NT; ++n) {
+    const int qn = (qg * NT + n) * 32;
+    if (qn >= n_act) break;      // uniform
+    if (n > 0) __syncthreads();  // the previous tile has been read by everyone
+    if (NT == 1 || tile == n) {
+#pragma unroll
+      for (int dt = 0; dt < kDT; ++dt)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          *reinterpret_cast<floatx4*>(slotA + chunk_at(qi, 8 * dt + 2 * j + hh)) =
+              floatx4{o[dt][4 * j], o[dt][4 * j + 1], o[dt][4 * j + 2], o[dt][4 * j + 3]};
+      const uintx2 sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(l_run), __float_as_uint(l_run), false, false);
+      if (hh == 0) ml_sh[slot][qi] = make_float2(m_run, __uint_as_float(sw.x) + __uint_as_float(sw.y));
+    }
+    __syncthreads();
+    constexpr int kPerQuery = 8 * NT;  // threads that share a query
+    const int mq = threadIdx.x / kPerQuery, c0 = threadIdx.x % kPerQuery;  // thread = (query, chunks c0, c0 + kPerQuery, ...)
+    float2 ml[kWavesPerGroup];
+    float mmax = -INFINITY, lsum = 0.f;
+#pragma unroll
+    for (int w = 0; w < kWavesPerGroup; ++w) {
+      ml[w] = ml_sh[w][mq];
+      mmax = fmaxf(mmax, ml[w].x);
+    }
+    float f[kWavesPerGroup];
+#pragma unroll
+    for (int w = 0; w < kWavesPerGroup; ++w) {
+      f[w] = ml[w].y > 0.f ? __builtin_amdgcn_exp2f(ml[w].x - mmax) : 0.f;
+      lsum += f[w] * ml[w].y;
+    }
+    const int a = qn + mq;
     if (a < n_act) {
-      if (p.n_split == 1) {
-        const float inv = lsum > 0.f ? 1.f / lsum : 0.f;
-        uint16_t* dst = p.out + (int64_t)h * p.osh + (int64_t)a * p.osn + mc;
+      const int64_t row = ((int64_t)h * p.q_pad + a) * p.n_split + split;
+      const float inv = lsum > 0.f ? 1.f / lsum : 0.f;
 #pragma unroll
-        for (int i = 0; i < kPerThread; i += 2)
-          *reinterpret_cast<uint32_t*>(dst + i) = cvt_pk_bf16(acc_o[i] * inv, acc_o[i + 1] * inv);
-        if (p.lse && (threadIdx.x & 15) == 0)
-          p.lse[(int64_t)h * p.max_active + a] = lsum > 0.f ? (mmax + __builtin_amdgcn_logf(lsum)) * kLn2 : -INFINITY;
-        if (p.lse2_out && (threadIdx.x & 15) == 0)
-          p.lse2_out[(int64_t)h * p.q_pad + a] = lsum > 0.f ? mmax + __builtin_amdgcn_logf(lsum) : INFINITY;
-      } else {
-        const int64_t row = ((int64_t)h * p.q_pad + a) * p.n_split + split;
-        float* dst = p.part_o + row * D + mc;
+      for (int i = 0; i < kOChunks / kPerQuery; ++i) {
+        const int ch = c0 + kPerQuery * i;
+        floatx4 s = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int i = 0; i < kPerThread; i += 4)
-          *reinterpret_cast<float4*>(dst + i) = make_float4(acc_o[i], acc_o[i + 1], acc_o[i + 2], acc_o[i + 3]);
-        if ((threadIdx.x & 15) == 0)
+        for (int w = 0; w < kWavesPerGroup; ++w) s += f[w] * *reinterpret_cast<const floatx4*>(ldsA + w * kBufBytes + chunk_at(mq, ch));
+        if (p.n_split == 1)
+          *reinterpret_cast<uint2*>(p.out + (int64_t)h * p.osh + (int64_t)a * p.osn + ch * 4) =
+              make_uint2(cvt_pk_bf16(s[0] * inv, s[1] * inv), cvt_pk_bf16(s[2] * inv, s[3] * inv));
+        else
+          *reinterpret_cast<floatx4*>(p.part_o + row * D + ch * 4) = s;
+      }
+      if (c0 == 0) {
+        if (p.n_split == 1) {
+          if (p.lse) p.lse[(int64_t)h * p.max_active + a] = lsum > 0.f ? (mmax + __builtin_amdgcn_logf(lsum)) * kLn2 : -INFINITY;
+          if (p.lse2_out) p.lse2_out[(int64_t)h * p.q_pad + a] = lsum > 0.f ? mmax + __builtin_amdgcn_logf(lsum) : INFINITY;
+        } else {
           *reinterpret_cast<float2*>(p.part_ml + 2 * row) = make_float2(lsum > 0.f ? mmax : -INFINITY, lsum);
+        }
       }
     }
   }
@@ -862,26 +1078,47 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(const float* __restri
                                       blockIdx.z == 0 && (threadIdx.x & 15) == 0);
 }
 
-template <int D, int QT>
-static hipError_t launch_attn_t(const AttnArgs& a, const SplitPlan& p, bool fused, hipStream_t st) {
-  const dim3 grid = a.groups_first ? dim3(p.q_groups, a.H, p.n_split) : dim3(p.n_split, a.H, p.q_groups);
-  const bool pipe = QT == 1 && p.pipelined;  // shared sub-tiles (QT > 1) have their own pipelining
-  if (QT == 1 && !pipe && p.per_split > kWavesPerGroup) return hipErrorInvalidValue;  // the loop-free variant: one sub-tile per wavefront
-  const dim3 block(QT == 4 ? 512 : 256);
-  if (a.logits_out != nullptr) {  // dense probe layer with the logits spilled; QT == 1 by construction
-    if (QT != 1 || fused) return hipErrorInvalidValue;
-    if (pipe)
-      hipLaunchKernelGGL((sparse_attn_kernel<D, 1, 6>), grid, block, 0, st, a);
-    else
-      hipLaunchKernelGGL((sparse_attn_kernel<D, 1, 4>), grid, block, 0, st, a);
-  } else if (fused && pipe)
-    hipLaunchKernelGGL((sparse_attn_kernel<D, QT, (QT == 1 ? 3 : 1)>), grid, block, 0, st, a);
+// LOOP: the mode bits of the key loop
+template <int D, int NT, int LOOP>
+static void launch_wide_t(const AttnArgs& a, const SplitPlan& p, bool fused, hipStream_t st) {
+  const dim3 grid(ceil_div(p.n_split * a.H, 8) * 8 * p.q_groups), block(256 * NT);
+  constexpr int kKeep = LOOP & 8;
+  if (fused && p.pipelined)
+    hipLaunchKernelGGL((wide_attn_kernel<D, NT, LOOP | 1>), grid, block, 0, st, a);
   else if (fused)
-    hipLaunchKernelGGL((sparse_attn_kernel<D, QT, 1>), grid, block, 0, st, a);
-  else if (pipe)
-    hipLaunchKernelGGL((sparse_attn_kernel<D, QT, (QT == 1 ? 2 : 0)>), grid, block, 0, st, a);
+    hipLaunchKernelGGL((wide_attn_kernel<D, NT, kKeep | 1>), grid, block, 0, st, a);
+  else if (p.pipelined)
+    hipLaunchKernelGGL((wide_attn_kernel<D, NT, LOOP>), grid, block, 0, st, a);
   else
-    hipLaunchKernelGGL((sparse_attn_kernel<D, QT, 0>), grid, block, 0, st, a);
+    hipLaunchKernelGGL((wide_attn_kernel<D, NT, kKeep>), grid, block, 0, st, a);
+}
+
+template <int D>
+static hipError_t launch_attn_t(const AttnArgs& a, const SplitPlan& p, bool fused, hipStream_t st) {
+  if (!p.pipelined && p.n_split * kWavesPerGroup < p.n_sub) return hipErrorInvalidValue;  // the loop-free variants: one sub-tile per wavefront
+  const dim3 grid(p.n_split, a.H), block(256);
+  if (p.q_tiles_per_group > 1) {
+    if (a.logits_out != nullptr) return hipErrorInvalidValue;  // logits are spilled for one 16-query tile only
+    if (p.q_tiles_per_group > 2)
+      launch_wide_t<D, 2, 2 | 4>(a, p, fused, st);
+    else if (p.q_groups > 1)
+      launch_wide_t<D, 1, 2 | 8>(a, p, fused, st);
+    else
+      launch_wide_t<D, 1, 2 | 4>(a, p, fused, st);
+  } else if (a.logits_out != nullptr) {  // dense probe layer with the logits spilled
+    if (fused) return hipErrorInvalidValue;
+    if (p.pipelined)
+      hipLaunchKernelGGL((sparse_attn_kernel<D, 6>), grid, block, 0, st, a);
+    else
+      hipLaunchKernelGGL((sparse_attn_kernel<D, 4>), grid, block, 0, st, a);
+  } else if (fused && p.pipelined)
+    hipLaunchKernelGGL((sparse_attn_kernel<D, 3>), grid, block, 0, st, a);
+  else if (fused)
+    hipLaunchKernelGGL((sparse_attn_kernel<D, 1>), grid, block, 0, st, a);
+  else if (p.pipelined)
+    hipLaunchKernelGGL((sparse_attn_kernel<D, 2>), grid, block, 0, st, a);
+  else
+    hipLaunchKernelGGL((sparse_attn_kernel<D, 0>), grid, block, 0, st, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || p.n_split == 1) return e;
   if (p.n_split <= 8)
@@ -899,7 +1136,6 @@ hipError_t launch_sparse_attn(const void* Q, const int32_t* active_idx, const in
                               float* part_o, float* part_ml, const FusedTopC* fused, hipStream_t st,
                               const DenseProbe* probe) {
   AttnArgs a;
-  a.groups_first = (p.q_groups > 1 && p.n_split <= 65535) ? 1 : 0;
   a.dense_rows = probe ? s.n_ctx + s.n_resp : 0;
   a.logits_out = probe ? probe->logits_out : nullptr;
   a.lse2_out = probe ? probe->lse2_out : nullptr;
@@ -922,22 +1158,14 @@ hipError_t launch_sparse_attn(const void* Q, const int32_t* active_idx, const in
   a.n_b = ceil_div(s.n_ctx, s.block);
   a.n_gen = s.n_gen; a.n_keep = n_keep; a.n_sink = n_sink; a.max_active = max_active;
   a.sub_per_block = ceil_div(s.block, kSubTile);
-  a.n_sub = p.n_sub; a.per_split = p.per_split; a.n_split = p.n_split; a.q_pad = p.q_pad;
+  a.n_sub = p.n_sub; a.n_split = p.n_split; a.q_pad = p.q_pad;
+  a.q_groups = p.q_groups;
   a.scale_log2 = kLog2e / sqrtf((float)s.head_dim);
   a.rel_part = fused ? fused->rel_part : nullptr;
   a.scores_out = fused ? fused->scores_out : nullptr;
   a.kept_out = fused ? fused->kept_out : nullptr;
   a.n_focus_max = fused ? fused->n_focus_max : 0;
-  const bool f = fused != nullptr;
-  const int nqt = p.q_tiles_per_group;
-  if (s.head_dim == 128) {
-    if (nqt == 1) return launch_attn_t<128, 1>(a, p, f, st);
-    if (nqt == 2) return launch_attn_t<128, 2>(a, p, f, st);
-    return launch_attn_t<128, 4>(a, p, f, st);
-  }
-  if (nqt == 1) return launch_attn_t<64, 1>(a, p, f, st);
-  if (nqt == 2) return launch_attn_t<64, 2>(a, p, f, st);
-  return launch_attn_t<64, 4>(a, p, f, st);
+  return s.head_dim == 128 ? launch_attn_t<128>(a, p, fused != nullptr, st) : launch_attn_t<64>(a, p, fused != nullptr, st);
 }
 
 // =====================================================================================================
@@ -969,7 +1197,6 @@ struct RefreshArgs {
   float scale_log2;
 };
 
-typedef float floatx16 __attribute__((ext_vector_type(16)));
 // f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>): a loop whose index is a constant expression
 template <class F, int... I>
 __device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) {
@@ -978,33 +1205,6 @@ __device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int
 template <int N, class F>
 __device__ __forceinline__ void static_for(F&& f) {
   static_for_impl(f, std::make_integer_sequence<int, N>{});
-}
-
-// A operand of O^T += V^T P^T (32x32x16) for d tile `dt` and k-step `ks`: lane (dcol = lane % 32, hh) needs
-// V[16 ks + 8 (e / 4) + 4 hh + e % 4][32 dt + dcol], e = 0..7 — two transposed reads of four consecutive rows each.
-// The staged V of this kernel is only ever read this way — one instruction touches eight rows (four per half of the
-// wavefront) and 64 bytes of each — so its rows are swizzled for that: rows that would fall on the same banks
-// (consecutive rows at d = 128, every other row at d = 64) get different 64-byte segments.
-template <int D>
-__device__ __forceinline__ int vstage_swz(int row) {
-  return D == 128 ? (row & 3) << 2 : ((row >> 1) & 1) << 2;
-}
-template <int D>
-__device__ __forceinline__ int vstage_off(int row, int chunk) {
-  return row * Geo<D>::kRowBytes + ((chunk ^ vstage_swz<D>(row)) << 4);
-}
-template <int D>
-__device__ __forceinline__ bf16x8 read_v_operand32(const char* stageV, int dt, int ks, int lane) {
-  const int s = lane & 15, b = lane >> 4;
-  const int row = 16 * ks + 4 * (b >> 1) + (s >> 2);
-  const int col = 32 * dt + 16 * (b & 1) + 4 * (s & 3);
-  const int off0 = vstage_off<D>(row, col >> 3) + (col & 7) * 2;
-  const int off1 = vstage_off<D>(row + 8, col >> 3) + (col & 7) * 2;
-  typedef shortx4 __attribute__((address_space(3))) * lds_ptr;
-  const shortx4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(stageV + off0));
-  const shortx4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(stageV + off1));
-  struct { shortx4 a, b; } both = {lo, hi};
-  return __builtin_bit_cast(bf16x8, both);
 }
 
 template <int D, int NQ, int WAVES>  // NQ: 32-query tiles per wavefront; WAVES: wavefronts per workgroup
@@ -1321,7 +1521,7 @@ struct LogitArgs {
   float* colpart;     // [q_groups * H, L]                     (mode 2)
   int64_t qsh, qsn, ksh, ksn;
   int H, L, n_gen, max_active;
-  int n_sub, per_split, n_split, q_pad;
+  int n_sub, n_split, q_pad;
   float scale_log2;
 };
 
@@ -1345,9 +1545,8 @@ __global__ __launch_bounds__(256, 2) void qk_logits_kernel(const LogitArgs p) {
   const uint16_t* Qh = p.Q + (int64_t)h * p.qsh;
   const uint16_t* Kh = p.K + (int64_t)h * p.ksh;
 
-  const int st_begin = split * p.per_split;
-  const int st_end = min(st_begin + p.per_split, p.n_sub);
-  int st = st_begin + wave;
+  int st = split * kWavesPerGroup + wave;
+  const int st_end = p.n_sub, st_step = p.n_split * kWavesPerGroup;
   auto tile_of = [&](int s) {
     SubTile t;
     t.kind = 0;
@@ -1389,7 +1588,7 @@ __global__ __launch_bounds__(256, 2) void qk_logits_kernel(const LogitArgs p) {
     floatx4 acc[NQT][2];
     qk_subtile<D, NQT>(acc, stageK, q, lane);
     // the staged rows are consumed: the next sub-tile can stream in while the results are written
-    st += kWavesPerGroup;
+    st += st_step;
     if (st < st_end) {
       t = tile_of(st);
       wait_lds_reads();
@@ -1479,7 +1678,7 @@ hipError_t launch_qk_logits(const void* Q, const int32_t* active_idx, const int3
   a.qsh = s.q_stride_h; a.qsn = s.q_stride_n;
   a.ksh = s.k_stride_h; a.ksn = s.k_stride_n;
   a.H = s.n_heads; a.L = s.n_ctx + s.n_resp; a.n_gen = s.n_gen; a.max_active = max_active;
-  a.n_sub = p.n_sub; a.per_split = p.per_split; a.n_split = p.n_split; a.q_pad = p.q_pad;
+  a.n_sub = p.n_sub; a.n_split = p.n_split; a.q_pad = p.q_pad;
   a.scale_log2 = kLog2e / sqrtf((float)s.head_dim);
   const int nqt = p.q_tiles_per_group;
   if (s.head_dim == 128) {

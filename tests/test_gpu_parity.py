@@ -256,6 +256,33 @@ def test_sparse_attn(G, H, M, N, d, B, n_gen, n_act, n_keep, n_sink):
     assert np.allclose(lse.cpu().numpy(), ref_lse, atol=2e-3)
 
 
+@pytest.mark.parametrize("H,M,N,d,cap,live", [
+    (32, 2177, 40, 128, 17, 17),   # one 32-query tile, several rounds per slot, ragged last sub-tile
+    (32, 2300, 31, 128, 32, 3),    # most query slots past the device-side count
+    (32, 4200, 64, 64, 32, 32),    # d = 64; an odd number of rounds
+    (32, 2177, 40, 128, 33, 33),   # two tiles that share a slot, one query in the second
+    (32, 2240, 64, 128, 64, 32),   # ... and none
+    (32, 4200, 64, 64, 64, 64),
+    (16, 2400, 10, 128, 65, 65),   # query groups: the last one holds one query
+    (16, 2400, 10, 64, 130, 97),   # ... and one group is empty
+    (32, 900, 20, 128, 48, 40),    # one sub-tile per slot
+    (32, 300, 20, 64, 100, 70),    # ... with query groups
+    (1, 16500, 33, 128, 16, 16),   # one head: more than a hundred key splits to merge
+    (1, 16500, 33, 64, 40, 40),
+])
+def test_sparse_attn_query_tiles_and_key_splits(G, H, M, N, d, cap, live):
+    rng = np.random.default_rng(H * M + cap)
+    B, n_gen = 64, cap + 9
+    active = np.sort(rng.choice(n_gen, live, replace=False))
+    n_b = -(-M // B)
+    kept = np.sort(rng.choice(n_b, n_b - 3, replace=False))
+    out, lse, ref, ref_lse = _attn_case(G, H, M, N, d, B, n_gen, active, kept, np.sort(rng.choice(M, 45, replace=False)),
+                                        counts=G.i32([1, live]), cap=cap)
+    G.assert_attention_close(out[:, :live], ref)
+    assert np.allclose(lse.cpu().numpy()[:, :live], ref_lse, atol=2e-3)
+    assert torch.isnan(out[:, live:]).all()  # rows past the count are not written
+
+
 def test_sparse_attn_dense_reduction(G):
     # keep every block, every row a query: plain bidirectional attention over all M+N keys
     H, M, N, d, B, n_gen = 4, 3000, 72, 128, 128, 64
