@@ -455,60 +455,6 @@ struct AttnArgs {
   float* lse2_out;    // [H, q_pad] base-2 log-sum-exp per row (+inf for an empty row), or null
 };
 
-// Merge of per-split partial results for one (head, active row a): out = sum_s f_s O_s / sum_s f_s l_s with
-// f_s = exp2(m_s - running max), splits taken in index order, eight loads in flight at a time.  Thread = D/16 columns.
-template <int D, int kBatch, int kPerThread>
-__device__ __forceinline__ void merge_splits(const float* __restrict__ part_o, const float* __restrict__ part_ml, int h, int a,
-                                             int mc, int q_pad, int n_split, int max_active, int n_act, uint16_t* __restrict__ out,
-                                             int64_t osh, int64_t osn, float* __restrict__ lse, float* __restrict__ lse2,
-                                             bool write_lse) {
-  constexpr int kVec = kPerThread / 4;
-  const int64_t row0 = ((int64_t)h * q_pad + a) * n_split;
-  const float2* ml = reinterpret_cast<const float2*>(part_ml) + row0;
-  const float* po = part_o + row0 * D + mc;
-  float acc_o[kPerThread];
-#pragma unroll
-  for (int i = 0; i < kPerThread; ++i) acc_o[i] = 0.f;
-  float mrun = -INFINITY, lsum = 0.f;
-  for (int s0 = 0; s0 < n_split; s0 += kBatch) {
-    float2 v[kBatch];
-    float4 x[kBatch][kVec];
-#pragma unroll
-    for (int u = 0; u < kBatch; ++u) {
-      const int s = min(s0 + u, n_split - 1);  // clamped: stays in bounds, ignored below
-      v[u] = ml[s];
-#pragma unroll
-      for (int i = 0; i < kVec; ++i) x[u][i] = *reinterpret_cast<const float4*>(po + (int64_t)s * D + 4 * i);
-    }
-#pragma unroll
-    for (int u = 0; u < kBatch; ++u) {
-      if (s0 + u < n_split && v[u].y > 0.f) {
-        const float m_new = fmaxf(mrun, v[u].x);
-        const float f_old = __builtin_amdgcn_exp2f(mrun - m_new);
-        const float f = __builtin_amdgcn_exp2f(v[u].x - m_new);
-        lsum = lsum * f_old + f * v[u].y;
-#pragma unroll
-        for (int i = 0; i < kVec; ++i) {
-          acc_o[4 * i] = acc_o[4 * i] * f_old + f * x[u][i].x;
-          acc_o[4 * i + 1] = acc_o[4 * i + 1] * f_old + f * x[u][i].y;
-          acc_o[4 * i + 2] = acc_o[4 * i + 2] * f_old + f * x[u][i].z;
-          acc_o[4 * i + 3] = acc_o[4 * i + 3] * f_old + f * x[u][i].w;
-        }
-        mrun = m_new;
-      }
-    }
-  }
-  if (a >= n_act) return;  // rows past the device-side count: their partial results were never written and are not used
-  const float inv = lsum > 0.f ? 1.f / lsum : 0.f;
-  uint16_t* dst = out + (int64_t)h * osh + (int64_t)a * osn + mc;
-#pragma unroll
-  for (int i = 0; i < kPerThread; i += 2)
-    *reinterpret_cast<uint32_t*>(dst + i) = cvt_pk_bf16(acc_o[i] * inv, acc_o[i + 1] * inv);
-  if (lse && write_lse)
-    lse[(int64_t)h * max_active + a] = lsum > 0.f ? (mrun + __builtin_amdgcn_logf(lsum)) * kLn2 : -INFINITY;
-  if (lse2 && write_lse) lse2[(int64_t)h * q_pad + a] = lsum > 0.f ? mrun + __builtin_amdgcn_logf(lsum) : INFINITY;
-}
-
 // What the attention kernels prepare before their first K/V request.
 // R_b = (1 / (|I_focus| H)) sum_h part[h, b] for b = threadIdx.x (n_b <= 256 = blockDim.x), then Top-C into kept_sh; the
 // workgroup with `writer` set also writes scores and kept blocks out.  First use of `sm`.
@@ -1058,24 +1004,77 @@ __global__ __launch_bounds__(256 * NT, NT == 2 || (MODE & 4) == 0 ? 2 : 1) void 
 }
 
 // Merge of the per-split partial results: out = sum_s f_s O_s / sum_s f_s l_s, f_s = exp2(m_s - max m).
-// One workgroup per (head, 16 queries, 64 output columns); thread = (query, 4 columns) — the column halves of d = 128 go
-// to two workgroups, which halves what one compute unit has to pull in.  Fixed order over splits; the loads of
-// kBatch splits are issued together — and together with the load of the device-side query count, which is only looked
-// at when the row is stored — so the kernel is one memory round trip long for up to kBatch splits.
-template <int D, int kBatch>
+// One workgroup per (head, active row): thread = (split lane, 4 columns) and takes the splits sl, sl + lanes, ... in index
+// order, kBatch loads in flight; the lanes' states meet in LDS and are added in lane order (a fixed order: deterministic).
+// The loads do not wait for the device-side query count, which is only looked at when the row is stored, so up to
+// kBatch * lanes splits (32 at d = 128) cost one memory round trip.  (A workgroup per 16 rows that walked the splits one
+// after the other took 27 us at 130 splits of four heads, and as long as this one at 8.)
+template <int D>
 __global__ __launch_bounds__(256) void attn_combine_kernel(const float* __restrict__ part_o,
                                                            const float* __restrict__ part_ml,
                                                            const int32_t* __restrict__ counts, int max_active, int q_pad,
                                                            int n_split, uint16_t* __restrict__ out, int64_t osh, int64_t osn,
                                                            float* __restrict__ lse, float* __restrict__ lse2) {
-  constexpr int kPerThread = 4;
-  const int h = blockIdx.y;
-  const int a = blockIdx.x * 16 + (threadIdx.x >> 4);
-  const int mc = blockIdx.z * 64 + (threadIdx.x & 15) * kPerThread;
-  if (a >= max_active) return;  // host-side capacity of the active list; rows below it exist in the workspace
+  constexpr int kCols = D / 4, kLanes = 256 / kCols, kBatch = 4;
+  __shared__ float2 ml_sh[kLanes];
+  __shared__ __attribute__((aligned(16))) float o_sh[kLanes][D];
+  const int a = blockIdx.x, h = blockIdx.y;
+  const int sl = threadIdx.x / kCols, mc = (threadIdx.x % kCols) * 4;
   const int n_act = counts ? min(max(counts[1], 0), max_active) : max_active;
-  merge_splits<D, kBatch, kPerThread>(part_o, part_ml, h, a, mc, q_pad, n_split, max_active, n_act, out, osh, osn, lse, lse2,
-                                      blockIdx.z == 0 && (threadIdx.x & 15) == 0);
+  const int64_t row0 = ((int64_t)h * q_pad + a) * n_split;
+  const float2* ml = reinterpret_cast<const float2*>(part_ml) + row0;
+  const float* po = part_o + row0 * D + mc;
+  floatx4 acc = floatx4{0.f, 0.f, 0.f, 0.f};
+  float m = -INFINITY, l = 0.f;
+  for (int s0 = sl; s0 < n_split; s0 += kLanes * kBatch) {
+    float2 v[kBatch];
+    floatx4 x[kBatch];
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      const int s = s0 + u * kLanes;
+      v[u] = make_float2(-INFINITY, 0.f);
+      if (s < n_split) {
+        v[u] = ml[s];
+        x[u] = *reinterpret_cast<const floatx4*>(po + (int64_t)s * D);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      if (v[u].y > 0.f) {
+        const float m_new = fmaxf(m, v[u].x);
+        const float f_old = __builtin_amdgcn_exp2f(m - m_new), f = __builtin_amdgcn_exp2f(v[u].x - m_new);
+        l = l * f_old + f * v[u].y;
+        acc = acc * f_old + f * x[u];
+        m = m_new;
+      }
+    }
+  }
+  if (mc == 0) ml_sh[sl] = make_float2(m, l);
+  *reinterpret_cast<floatx4*>(&o_sh[sl][mc]) = acc;
+  __syncthreads();
+  if (threadIdx.x >= kCols || a >= n_act) return;  // rows past the count: their partial results were never written
+  float2 lane_ml[kLanes];
+  float mmax = -INFINITY;
+#pragma unroll
+  for (int i = 0; i < kLanes; ++i) {
+    lane_ml[i] = ml_sh[i];
+    mmax = fmaxf(mmax, lane_ml[i].x);
+  }
+  floatx4 o = floatx4{0.f, 0.f, 0.f, 0.f};
+  float lsum = 0.f;
+#pragma unroll
+  for (int i = 0; i < kLanes; ++i) {
+    const float f = lane_ml[i].y > 0.f ? __builtin_amdgcn_exp2f(lane_ml[i].x - mmax) : 0.f;
+    lsum += f * lane_ml[i].y;
+    o += f * *reinterpret_cast<const floatx4*>(&o_sh[i][mc]);
+  }
+  const float inv = lsum > 0.f ? 1.f / lsum : 0.f;
+  *reinterpret_cast<uint2*>(out + (int64_t)h * osh + (int64_t)a * osn + mc) =
+      make_uint2(cvt_pk_bf16(o[0] * inv, o[1] * inv), cvt_pk_bf16(o[2] * inv, o[3] * inv));
+  if (mc == 0) {
+    if (lse) lse[(int64_t)h * max_active + a] = lsum > 0.f ? (mmax + __builtin_amdgcn_logf(lsum)) * kLn2 : -INFINITY;
+    if (lse2) lse2[(int64_t)h * q_pad + a] = lsum > 0.f ? mmax + __builtin_amdgcn_logf(lsum) : INFINITY;
+  }
 }
 
 // LOOP: the mode bits of the key loop
@@ -1121,12 +1120,8 @@ static hipError_t launch_attn_t(const AttnArgs& a, const SplitPlan& p, bool fuse
     hipLaunchKernelGGL((sparse_attn_kernel<D, 0>), grid, block, 0, st, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || p.n_split == 1) return e;
-  if (p.n_split <= 8)
-    hipLaunchKernelGGL((attn_combine_kernel<D, 8>), dim3(p.q_tiles, a.H, D / 64), dim3(256), 0, st, a.part_o, a.part_ml, a.counts,
-                       a.max_active, a.q_pad, a.n_split, a.out, a.osh, a.osn, a.lse, a.lse2_out);
-  else
-    hipLaunchKernelGGL((attn_combine_kernel<D, 16>), dim3(p.q_tiles, a.H, D / 64), dim3(256), 0, st, a.part_o, a.part_ml, a.counts,
-                       a.max_active, a.q_pad, a.n_split, a.out, a.osh, a.osn, a.lse, a.lse2_out);
+  hipLaunchKernelGGL(attn_combine_kernel<D>, dim3(a.max_active, a.H), dim3(256), 0, st, a.part_o, a.part_ml, a.counts, a.max_active,
+                     a.q_pad, a.n_split, a.out, a.osh, a.osn, a.lse, a.lse2_out);
   return hipGetLastError();
 }
 
