@@ -1202,16 +1202,25 @@ __device__ __forceinline__ void static_for(F&& f) {
   static_for_impl(f, std::make_integer_sequence<int, N>{});
 }
 
-template <int D, int NQ, int WAVES>  // NQ: 32-query tiles per wavefront; WAVES: wavefronts per workgroup
-__global__ __launch_bounds__(64 * WAVES, NQ == 1 ? 2 : 1) void refresh_attn_kernel(const RefreshArgs p) {
+// keeps the computation of x in front of this point (and of the scheduling fences after it)
+__device__ __forceinline__ void pin(float& x) { asm volatile("" : "+v"(x)); }
+__device__ __forceinline__ void pin(int& x) { asm volatile("" : "+v"(x)); }
+
+constexpr int kRefreshWaves = 8;  // wavefronts per workgroup
+constexpr int kRefreshBlock = 4;  // sub-tiles between two barriers
+
+template <int D>
+__global__ __launch_bounds__(64 * kRefreshWaves, 2) void refresh_attn_kernel(const RefreshArgs p) {
   using G = Geo<D>;
   constexpr int kKS = D / 16;                    // k-steps of K Q^T
   constexpr int kDT = D / 32;                    // 32-wide d tiles of V^T P^T
-  constexpr int kBufBytes = 2 * G::kStageBytes;  // K stage + V stage of one sub-tile
-  constexpr int kShare = WAVES / 2;              // wavefronts that share the K (or the V) rows of a sub-tile
+  constexpr int NB = kRefreshBlock, kRing = 2 * NB;
+  constexpr int kShare = kRefreshWaves / 2;      // wavefronts that share the K (or the V) rows of a sub-tile
   constexpr int NL = G::kLoads / kShare;         // loads per wavefront and sub-tile
   static_assert(G::kLoads % kShare == 0 && NL >= 1, "every wavefront stages at least one load");
-  __shared__ __attribute__((aligned(16))) char stage[2][kBufBytes];
+  // K sub-tile j sits in slot (j - 1) mod kRing of its ring, V sub-tile j in slot j mod kRing: iteration t reads slot t mod kRing of both
+  __shared__ __attribute__((aligned(16))) char ringK[kRing * G::kStageBytes];
+  __shared__ __attribute__((aligned(16))) char ringV[kRing * G::kStageBytes];
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1224,7 +1233,7 @@ __global__ __launch_bounds__(64 * WAVES, NQ == 1 ? 2 : 1) void refresh_attn_kern
   const int work = (int)(blockIdx.x & 7u) * chunk + (int)(blockIdx.x >> 3);
   if (work >= p.n_work) return;  // whole workgroup
   const int h = work / p.n_qb;
-  const int q_row0 = (work - h * p.n_qb) * (32 * NQ * WAVES) + wave * (32 * NQ) + qi;  // tile n: q_row0 + 32 n
+  const int q_row = (work - h * p.n_qb) * (32 * kRefreshWaves) + wave * 32 + qi;
   const int n_tiles = (p.L + kSubTile - 1) / kSubTile;
   const int n_full = p.L / kSubTile;
 
@@ -1242,8 +1251,10 @@ __global__ __launch_bounds__(64 * WAVES, NQ == 1 ? 2 : 1) void refresh_attn_kern
     const int slot = (first + i) * G::kRowsPerLoad + lane / G::kChunks;
     voff[i] = (uint32_t)slot * (uint32_t)row_bytes + (((lane % G::kChunks) ^ swz(slot)) << 4);
   }
-  uintx4 r[NL];
-  auto fetch = [&](int t) {
+  const int lead_k = is_v ? 0 : 1;
+  // element e = sub-tile e + 1 of K, sub-tile e of V: what ring slot e mod kRing holds
+  auto fetch = [&](int e, uintx4 (&r)[NL]) __attribute__((always_inline)) {
+    const int t = e + lead_k;
     const char* base = src + (int64_t)t * tile_bytes;
     if (t >= n_full) {  // the ragged last sub-tile: slots past the end read its last row instead (masked below)
       const int last = p.L - t * kSubTile - 1;
@@ -1256,225 +1267,212 @@ __global__ __launch_bounds__(64 * WAVES, NQ == 1 ? 2 : 1) void refresh_attn_kern
 #pragma unroll
     for (int i = 0; i < NL; ++i) r[i] = __builtin_nontemporal_load(reinterpret_cast<const uintx4*>(base + voff[i]));
   };
-  // K runs one sub-tile ahead of V: iteration t multiplies K sub-tile t + 1 (the logits of the NEXT iteration, MFMA
-  // work with nothing in front of it) while the vector ALU turns the logits of sub-tile t into probabilities, then
-  // multiplies those with V sub-tile t.  K sub-tile j lives in K stage j % 2, V sub-tile j in V stage j % 2.
-  // The loop is unrolled by two so that every stage index is a compile-time constant (an LDS address is then a
-  // register fixed for the launch plus an immediate).
-  const int lead = is_v ? 0 : 1;
-  char* my_stage = stage[0] + (is_v ? G::kStageBytes : 0) + first * 1024 + lane * 16;
-  auto store = [&](int j) {  // this wavefront's rows of sub-tile j (in r) to stage j % 2
+  char* my_ring = (is_v ? ringV : ringK) + first * 1024 + lane * 16;
+  auto store = [&](int slot, const uintx4 (&r)[NL]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < NL; ++i) *reinterpret_cast<uintx4*>(my_stage + (j & 1) * kBufBytes + i * 1024) = r[i];
+    for (int i = 0; i < NL; ++i) *reinterpret_cast<uintx4*>(my_ring + slot * G::kStageBytes + i * 1024) = r[i];
   };
-  auto stage_next = [&](int t) {  // after the barrier of iteration t: K sub-tile t + 2 / V sub-tile t + 1, then request the one after
-    const int j = t + 1 + lead;
-    if (j < n_tiles) {
-      store(j);
-      if (j + 1 < n_tiles) fetch(j + 1);
-    }
-  };
-  fetch(0);
-  bf16x8 q[NQ][kKS];  // B operand of K Q^T: lane (query, hh) holds Q[query][16 ks + 8 hh .. + 7]
+  auto exists = [&](int e) { return e + lead_k < n_tiles; };
+
+  // prologue: K sub-tile 0 (element -1) and the first block of elements, all requested at once
+  uintx4 r[NL];
+  {
+    uintx4 pr[NB + 1][NL];
+    if (!is_v) fetch(-1, pr[NB]);
 #pragma unroll
-  for (int n = 0; n < NQ; ++n) {
-    const int q_row = q_row0 + 32 * n;
+    for (int e = 0; e < NB; ++e)
+      if (exists(e)) fetch(e, pr[e]);
+    if (exists(NB)) fetch(NB, r);
+    if (!is_v) store(kRing - 1, pr[NB]);
+#pragma unroll
+    for (int e = 0; e < NB; ++e)
+      if (exists(e)) store(e, pr[e]);
+  }
+  bf16x8 q[kKS];  // B operand of K Q^T: lane (query, hh) holds Q[query][16 ks + 8 hh .. + 7]
+  {
     const uint16_t* qsrc = p.Q + (int64_t)h * p.qsh + (int64_t)min(q_row, p.n_q - 1) * p.qsn + hh * 8;
 #pragma unroll
     for (int ks = 0; ks < kKS; ++ks) {
       const uint4 v = *reinterpret_cast<const uint4*>(qsrc + ks * 16);
-      q[n][ks] = as_bf16x8(q_row < p.n_q ? v : make_uint4(0u, 0u, 0u, 0u));
+      q[ks] = as_bf16x8(q_row < p.n_q ? v : make_uint4(0u, 0u, 0u, 0u));
     }
   }
-  float m_run[NQ], l_run[NQ];  // l_run: this lane's share of the row sum (its 16 of every 32 keys)
-  floatx16 o[NQ][kDT];
+  float m_run = -INFINITY, l_run = 0.f;  // l_run: this lane's share of the row sum (its 16 of every 32 keys)
+  floatx16 o[kDT];
 #pragma unroll
-  for (int n = 0; n < NQ; ++n) {
-    m_run[n] = -INFINITY;
-    l_run[n] = 0.f;
+  for (int dt = 0; dt < kDT; ++dt)
 #pragma unroll
-    for (int dt = 0; dt < kDT; ++dt)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) o[n][dt][v] = 0.f;
-  }
+    for (int v = 0; v < 16; ++v) o[dt][v] = 0.f;
   const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
+  int koff[kKS];  // byte offset of the K operand of k-step s within a slot
+#pragma unroll
+  for (int s = 0; s < kKS; ++s) {
+    koff[s] = stage_off<D>(qi, 2 * s + hh);
+    pin(koff[s]);
+  }
   // scaled row maximum of one sub-tile's logits.  Slots past the end of a ragged sub-tile hold copies of its last
   // row, so they cannot raise the maximum and need no masking here.
-  auto row_max = [&](const floatx16& a) {
+  auto row_max_lane = [&](const floatx16& a) __attribute__((always_inline)) {
     float mx = fmaxf(a[0], a[1]);
 #pragma unroll
     for (int v = 2; v < 16; ++v) mx = fmaxf(mx, a[v]);
+    return mx;
+  };
+  auto row_max = [&](float mx) __attribute__((always_inline)) {
     const uintx2 sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
     return fmaxf(__uint_as_float(sw.x), __uint_as_float(sw.y)) * p.scale_log2;
   };
-  auto rescale = [&](int n, float mx) {
-    if (__ballot(mx > m_run[n]) != 0ull) {  // some running maximum of this wavefront moves (rare after the first sub-tiles)
-      const float m_new = fmaxf(m_run[n], mx);
-      const float alpha = __builtin_amdgcn_exp2f(m_run[n] - m_new);  // 0 on the first sub-tile (m_run = -inf, m_new finite)
-      m_run[n] = m_new;
-      l_run[n] *= alpha;
+  auto rescale = [&](float mx) __attribute__((always_inline)) {
+    if (__ballot(mx > m_run) != 0ull) {  // some running maximum of this wavefront moves (rare after the first sub-tiles)
+      const float m_new = fmaxf(m_run, mx);
+      const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);  // 0 on the first sub-tile (m_run = -inf, m_new finite)
+      m_run = m_new;
+      l_run *= alpha;
 #pragma unroll
-      for (int dt = 0; dt < kDT; ++dt) o[n][dt] *= alpha;
+      for (int dt = 0; dt < kDT; ++dt) o[dt] *= alpha;
     }
   };
 
-  // prologue: K sub-tile 0 staged and multiplied; K sub-tile 1 and V sub-tile 0 staged for iteration 0
-  if (!is_v) {
-    store(0);
-    if (1 < n_tiles) fetch(1);
-  }
   __syncthreads();
-  floatx16 acc[NQ];
-  float mx[NQ];
+  floatx16 acc;
+  float mx;
 #pragma unroll
-  for (int n = 0; n < NQ; ++n) {
-#pragma unroll
-    for (int v = 0; v < 16; ++v) acc[n][v] = 0.f;
-  }
+  for (int v = 0; v < 16; ++v) acc[v] = 0.f;
 #pragma unroll
   for (int ks = 0; ks < kKS; ++ks) {
-    const bf16x8 a = as_bf16x8(*reinterpret_cast<const uint4*>(stage[0] + stage_off<D>(qi, 2 * ks + hh)));
-#pragma unroll
-    for (int n = 0; n < NQ; ++n) acc[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, q[n][ks], acc[n], 0, 0, 0);
+    const bf16x8 a = as_bf16x8(*reinterpret_cast<const uint4*>(ringK + (kRing - 1) * G::kStageBytes + koff[ks]));
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, q[ks], acc, 0, 0, 0);
   }
-#pragma unroll
-  for (int n = 0; n < NQ; ++n) mx[n] = row_max(acc[n]);
-  stage_next(-1);
+  mx = row_max(row_max_lane(acc));
 
-  // One iteration, written as NS slots of one LDS operand and NQ MFMAs each — K Q^T of sub-tile t + 1 first, then
+  // One iteration, written as NS slots of one LDS operand and one MFMA each — K Q^T of sub-tile t + 1 first, then
   // V^T P^T of sub-tile t — with scheduling fences between the slots: a wavefront issues in order, so the vector work
-  // of the other sub-tile (exponentials of sub-tile t beside the K Q^T MFMAs, the row maximum of sub-tile t + 1 beside
-  // the last V^T P^T MFMAs) has to sit between the MFMAs in program order or it would wait behind all of them.  The
-  // LDS operand of slot s + kLead is requested in slot s.  n_valid < 32 only in the last iteration (kLast), which has no
-  // K Q^T part.
-  auto body = [&](int t, auto which, auto last_tag, int n_valid) {
-    constexpr int W = decltype(which)::value;     // stage of V sub-tile t (K sub-tile t + 1 sits in the other one); -1: t % 2
-    constexpr bool kLast = decltype(last_tag)::value;
-    constexpr int NS = kKS + 2 * kDT;             // operand slots per iteration
+  // of the other sub-tile (exponentials of sub-tile t beside the first MFMAs, the row maximum of sub-tile t + 1 beside
+  // the last ones) has to sit between the MFMAs in program order or it would wait behind all of them.  The
+  // LDS operand of slot s + kLead is requested in slot s, across iterations within a block.  n_valid < 32 only in the last
+  // iteration (kLast), which has no K Q^T part.
+  constexpr int NS = kKS + 2 * kDT;             // operand slots per iteration
+  constexpr int kLead = 3;
+  bf16x8 ahead[kLead];                          // operands of the next iteration's first slots
+  // R: ring slot of this iteration, or -1: t mod kRing.  kFirst: first of a block, behind the barrier.  kMore: the next iteration belongs to the same block.
+  auto body = [&](int t, auto slot_tag, auto first_tag, auto more_tag, auto last_tag, int n_valid) __attribute__((always_inline)) {
+    constexpr int R = decltype(slot_tag)::value;
+    constexpr bool kFirst = decltype(first_tag)::value, kMore = decltype(more_tag)::value, kLast = decltype(last_tag)::value;
     constexpr int S0 = kLast ? kKS : 0;           // first slot of this iteration
-    constexpr int kLead = 3;
-    constexpr int kPer = 16 / kKS;                // logits turned into probabilities per K Q^T slot and query tile
-    __syncthreads();  // K sub-tile t + 1 and V sub-tile t are staged; everyone is done with iteration t - 1
-#pragma unroll
-    for (int n = 0; n < NQ; ++n) rescale(n, mx[n]);
-    const int w = W >= 0 ? W : (t & 1);
-    const char* sK = stage[1 - w];
-    const char* sV = stage[w] + G::kStageBytes;
-    bf16x8 op[NS];
-    auto read_op = [&](auto sc) {
-      constexpr int s = decltype(sc)::value + S0;
+    if (kFirst) __syncthreads();                  // the block is staged; everyone is done with the previous one
+    rescale(mx);
+    const int ring = R >= 0 ? R : (t & (kRing - 1));
+    const char* sK = ringK + ring * G::kStageBytes;
+    const char* sV = ringV + ring * G::kStageBytes;
+    bf16x8 op[NS + kLead];
+    auto read_op = [&](auto sc) __attribute__((always_inline)) {
+      constexpr int s = decltype(sc)::value;
       if constexpr (s < kKS)
-        op[s] = as_bf16x8(*reinterpret_cast<const uint4*>(sK + stage_off<D>(qi, 2 * s + hh)));
+        op[s] = as_bf16x8(*reinterpret_cast<const uint4*>(sK + koff[s]));
       else if constexpr (s < NS)
         op[s] = read_v_operand32<D>(sV, (s - kKS) % kDT, (s - kKS) / kDT, lane);
+      else if constexpr (kMore)
+        ahead[s - NS] = as_bf16x8(*reinterpret_cast<const uint4*>(sK + G::kStageBytes + koff[s - NS]));
     };
-    floatx16 next[NQ];
-    uint32_t pk[NQ][8];
-    float mxn[NQ];
+    floatx16 next;
+    uint32_t pk[8];
+    float mxn = 0.f;
 #pragma unroll
-    for (int n = 0; n < NQ; ++n) {
-      mxn[n] = 0.f;
-#pragma unroll
-      for (int v = 0; v < 16; ++v) next[n][v] = 0.f;
-    }
-    auto probabilities = [&](int n, int v0, int v1) {  // logits v0 .. v1 - 1 of query tile n -> packed bf16, added to the row sum
+    for (int v = 0; v < 16; ++v) next[v] = 0.f;
+    auto probabilities = [&](int v0, int v1) __attribute__((always_inline)) {  // logits v0 .. v1 - 1 -> packed bf16, added to the row sum
 #pragma unroll
       for (int v = v0; v < v1; v += 2) {
-        float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[n][v], p.scale_log2, -m_run[n]));
-        float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[n][v + 1], p.scale_log2, -m_run[n]));
+        float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[v], p.scale_log2, -m_run));
+        float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[v + 1], p.scale_log2, -m_run));
         if (kLast) {  // a ragged sub-tile: slots past the end count for nothing
           const int key = 8 * (v >> 2) + 4 * hh + (v & 3);
           p0 = key < n_valid ? p0 : 0.f;
           p1 = key + 1 < n_valid ? p1 : 0.f;
         }
-        pk[n][v >> 1] = cvt_pk_bf16(p0, p1);
-        l_run[n] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pk[n][v >> 1]), ones, l_run[n], false);
+        pk[v >> 1] = cvt_pk_bf16(p0, p1);
+        l_run = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pk[v >> 1]), ones, l_run, false);
       }
     };
-    if (kLast) {
+    if (kLast) probabilities(0, 16);
+    if constexpr (kFirst) {
+      static_for<kLead>([&](auto sc) { read_op(std::integral_constant<int, decltype(sc)::value + S0>{}); });
+    } else {
 #pragma unroll
-      for (int n = 0; n < NQ; ++n) probabilities(n, 0, 16);
+      for (int i = 0; i < kLead; ++i) op[i] = ahead[i];
     }
-    static_for<kLead>(read_op);
     __builtin_amdgcn_sched_barrier(0);
     static_for<NS - S0>([&](auto sc) {
       constexpr int s = decltype(sc)::value + S0;
-      if constexpr (s + kLead < NS) read_op(std::integral_constant<int, s + kLead - S0>{});
+      read_op(std::integral_constant<int, s + kLead>{});
       if constexpr (s < kKS) {
-#pragma unroll
-        for (int n = 0; n < NQ; ++n) {
-          next[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[s], q[n][s], next[n], 0, 0, 0);
-          probabilities(n, s * kPer, (s + 1) * kPer);
-        }
+        next = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[s], q[s], next, 0, 0, 0);
       } else {
         constexpr int ks = (s - kKS) / kDT, dt = (s - kKS) % kDT;
-#pragma unroll
-        for (int n = 0; n < NQ; ++n) {
-          const bf16x8 pb = as_bf16x8(make_uint4(pk[n][4 * ks], pk[n][4 * ks + 1], pk[n][4 * ks + 2], pk[n][4 * ks + 3]));
-          o[n][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[s], pb, o[n][dt], 0, 0, 0);
+        const bf16x8 pb = as_bf16x8(make_uint4(pk[4 * ks], pk[4 * ks + 1], pk[4 * ks + 2], pk[4 * ks + 3]));
+        o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[s], pb, o[dt], 0, 0, 0);
+      }
+      if constexpr (!kLast) {
+        if constexpr (s < kKS + kDT) {  // pair i of the logits of sub-tile t: slot i (kKS + kDT) / 8
+          static_for<8>([&](auto ic) {
+            constexpr int i = decltype(ic)::value;
+            if constexpr (i * (kKS + kDT) / 8 == s) {
+              probabilities(2 * i, 2 * i + 2);
+              pin(l_run);
+            }
+          });
         }
-        if constexpr (!kLast && s == NS - 2) {  // row maximum of sub-tile t + 1: the in-lane part
-#pragma unroll
-          for (int n = 0; n < NQ; ++n) {
-            mxn[n] = fmaxf(next[n][0], next[n][1]);
-#pragma unroll
-            for (int v = 2; v < 16; ++v) mxn[n] = fmaxf(mxn[n], next[n][v]);
+        if constexpr (s == kKS) {  // element t + NB to its slot, then request the one after
+          if (exists(t + NB)) {
+            store(R >= 0 ? (R + NB) % kRing : ((t + NB) & (kRing - 1)), r);
+            if (exists(t + NB + 1)) fetch(t + NB + 1, r);
           }
         }
-        if constexpr (!kLast && s == NS - 1) {  // ... and the exchange between the two lanes of a query
-#pragma unroll
-          for (int n = 0; n < NQ; ++n) {
-            const uintx2 sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mxn[n]), __float_as_uint(mxn[n]), false, false);
-            mxn[n] = fmaxf(__uint_as_float(sw.x), __uint_as_float(sw.y)) * p.scale_log2;
-          }
-        }
+        if constexpr (s == NS - 3) mxn = row_max_lane(next);
+        if constexpr (s == NS - 2) mxn = row_max(mxn);
       }
       __builtin_amdgcn_sched_barrier(0);
     });
     if (!kLast) {
-#pragma unroll
-      for (int n = 0; n < NQ; ++n) {
-        mx[n] = mxn[n];
-        acc[n] = next[n];
-      }
-      stage_next(t);
+      mx = mxn;
+      acc = next;
     }
   };
-  int t_body = 0;
-  for (; t_body + 2 < n_tiles; t_body += 2) {  // straight-line pairs: no exit between the two halves
-    body(t_body, std::integral_constant<int, 0>{}, std::false_type{}, kSubTile);
-    body(t_body + 1, std::integral_constant<int, 1>{}, std::false_type{}, kSubTile);
-  }
-  if (t_body + 1 < n_tiles) body(t_body, std::integral_constant<int, 0>{}, std::false_type{}, kSubTile);  // t_body is even
+  using std::integral_constant;
+  constexpr std::false_type no{};
+  constexpr std::true_type yes{};
+  const int n_iter = n_tiles - 1;
+  int t = 0;
+  for (; t + kRing <= n_iter; t += kRing)  // straight-line: both halves of the rings
+    static_for<kRing>([&](auto ic) {
+      constexpr int i = decltype(ic)::value;
+      body(t + i, integral_constant<int, i>{}, integral_constant<bool, i % NB == 0>{}, integral_constant<bool, i % NB != NB - 1>{}, no, kSubTile);
+    });
+  for (; t < n_iter; ++t) body(t, integral_constant<int, -1>{}, yes, no, no, kSubTile);
   // last sub-tile (possibly ragged): its logits are in acc already
-  body(n_tiles - 1, std::integral_constant<int, -1>{}, std::true_type{}, p.L - (n_tiles - 1) * kSubTile);
+  body(n_tiles - 1, integral_constant<int, -1>{}, yes, no, yes, p.L - (n_tiles - 1) * kSubTile);
 
   // lane (query, hh) register v of d tile dt holds O^T[32 dt + 8 (v / 4) + 4 hh + v % 4][query]: four consecutive
   // output columns per register quad.  The two lanes of a query add their halves of the row sum.
+  const uintx2 sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(l_run), __float_as_uint(l_run), false, false);
+  const float l = __uint_as_float(sw.x) + __uint_as_float(sw.y);
+  if (q_row < p.n_q) {
+    const float inv = l > 0.f ? 1.f / l : 0.f;
+    uint16_t* dst = p.out + (int64_t)h * p.osh + (int64_t)q_row * p.osn + 4 * hh;
 #pragma unroll
-  for (int n = 0; n < NQ; ++n) {
-    const uintx2 sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(l_run[n]), __float_as_uint(l_run[n]), false, false);
-    const float l = __uint_as_float(sw.x) + __uint_as_float(sw.y);
-    const int q_row = q_row0 + 32 * n;
-    if (q_row < p.n_q) {
-      const float inv = l > 0.f ? 1.f / l : 0.f;
-      uint16_t* dst = p.out + (int64_t)h * p.osh + (int64_t)q_row * p.osn + 4 * hh;
+    for (int dt = 0; dt < kDT; ++dt)
 #pragma unroll
-      for (int dt = 0; dt < kDT; ++dt)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          *reinterpret_cast<uint2*>(dst + 32 * dt + 8 * j) = make_uint2(cvt_pk_bf16(o[n][dt][4 * j] * inv, o[n][dt][4 * j + 1] * inv),
-                                                                        cvt_pk_bf16(o[n][dt][4 * j + 2] * inv, o[n][dt][4 * j + 3] * inv));
-      if (p.lse && hh == 0) p.lse[(int64_t)h * p.n_q + q_row] = l > 0.f ? (m_run[n] + __builtin_amdgcn_logf(l)) * kLn2 : -INFINITY;
-    }
+      for (int j = 0; j < 4; ++j)
+        *reinterpret_cast<uint2*>(dst + 32 * dt + 8 * j) = make_uint2(cvt_pk_bf16(o[dt][4 * j] * inv, o[dt][4 * j + 1] * inv),
+                                                                      cvt_pk_bf16(o[dt][4 * j + 2] * inv, o[dt][4 * j + 3] * inv));
+    if (p.lse && hh == 0) p.lse[(int64_t)h * p.n_q + q_row] = l > 0.f ? (m_run + __builtin_amdgcn_logf(l)) * kLn2 : -INFINITY;
   }
 }
 
-template <int D, int NQ, int WAVES>
+template <int D>
 static hipError_t launch_refresh_t(RefreshArgs& a, const focus_shape& s, hipStream_t st) {
-  a.n_qb = ceil_div(s.n_gen, 32 * NQ * WAVES);
+  a.n_qb = ceil_div(s.n_gen, 32 * kRefreshWaves);
   a.n_work = a.n_qb * s.n_heads;
-  hipLaunchKernelGGL((refresh_attn_kernel<D, NQ, WAVES>), dim3(8 * ceil_div(a.n_work, 8)), dim3(64 * WAVES), 0, st, a);
+  hipLaunchKernelGGL(refresh_attn_kernel<D>, dim3(8 * ceil_div(a.n_work, 8)), dim3(64 * kRefreshWaves), 0, st, a);
   return hipGetLastError();
 }
 
@@ -1497,8 +1495,8 @@ hipError_t launch_refresh_attn(const void* Q, const void* K, const void* V, cons
   // queries — each LDS operand feeding two MFMAs, one wavefront per SIMD with 444 registers — gives the same sharing
   // with half the LDS reads, but a lone wavefront cannot cover its own dependent vector-ALU chains: 0.82 against
   // 1.01 PFLOP/s.)
-  if (s.head_dim == 128) return launch_refresh_t<128, 1, 8>(a, s, st);
-  return launch_refresh_t<64, 1, 8>(a, s, st);
+  if (s.head_dim == 128) return launch_refresh_t<128>(a, s, st);
+  return launch_refresh_t<64>(a, s, st);
 }
 
 // =====================================================================================================
