@@ -738,12 +738,74 @@ __global__ __launch_bounds__(256, (FUSE & 2) == 0 ? 2 : 1) void sparse_attn_kern
   }
 }
 
+// One staged sub-tile of 32 keys against a tile of 32 queries (32x32x16 MFMA), into the running softmax.
+//   S^T = K Q^T   lane (query = lane % 32, hh = lane / 32), register v: logit of key 8 (v / 4) + 4 hh + v % 4
+//   O^T = V^T P^T the same registers, packed to bf16, are the B operand of k-step v / 8
+// k_operand(ks) / v_operand(dt, ks) supply the A operands; l_run is this lane's share of the row sum (its 16 of the 32 keys).
+template <int D, class KOp, class VOp>
+__device__ __forceinline__ void attend_subtile32(const KOp k_operand, const VOp v_operand, const bf16x8 (&q)[D / 16], uint32_t vmask,
+                                                 int hh, float scale_log2, float& m_run, float& l_run, floatx16 (&o)[D / 32]) {
+  constexpr int kKS = D / 16, kDT = D / 32;
+  floatx16 acc;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+#pragma unroll
+  for (int ks = 0; ks < kKS; ++ks) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_operand(ks), q[ks], acc, 0, 0, 0);
+  if (vmask != 0xffffffffu) {  // wave-uniform: slots that hold no key
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] = ((vmask >> (8 * (v >> 2) + 4 * hh + (v & 3))) & 1u) ? acc[v] : -INFINITY;
+  }
+  float mx = fmaxf(acc[0], acc[1]);
+#pragma unroll
+  for (int v = 2; v < 16; ++v) mx = fmaxf(mx, acc[v]);
+  const uintx2 sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+  mx = fmaxf(__uint_as_float(sw.x), __uint_as_float(sw.y)) * scale_log2;
+  const float m_new = fmaxf(m_run, mx);
+  const float m_use = m_new == -INFINITY ? 0.f : m_new;
+  if (__ballot(m_new != m_run) != 0ull) {  // some running maximum of this wavefront moves (rare after the first sub-tiles)
+    const float alpha = __builtin_amdgcn_exp2f(m_run - m_use);
+    l_run *= alpha;
+#pragma unroll
+    for (int dt = 0; dt < kDT; ++dt) o[dt] *= alpha;
+    m_run = m_new;
+  }
+  float ps[16];
+#pragma unroll
+  for (int v = 0; v < 16; ++v) ps[v] = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[v], scale_log2, -m_use));
+  float sum = ps[0] + ps[1];
+#pragma unroll
+  for (int v = 2; v < 16; v += 2) sum += ps[v] + ps[v + 1];
+  l_run += sum;
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks) {
+    const bf16x8 pb = as_bf16x8(make_uint4(cvt_pk_bf16(ps[8 * ks], ps[8 * ks + 1]), cvt_pk_bf16(ps[8 * ks + 2], ps[8 * ks + 3]),
+                                           cvt_pk_bf16(ps[8 * ks + 4], ps[8 * ks + 5]), cvt_pk_bf16(ps[8 * ks + 6], ps[8 * ks + 7])));
+#pragma unroll
+    for (int dt = 0; dt < kDT; ++dt) o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_operand(dt, ks), pb, o[dt], 0, 0, 0);
+  }
+}
+
+// fp32 O tile [32 queries][D] in LDS for the merge of several wavefronts: byte offset of 16-byte chunk ch of query row r.
+// Swizzled so that neither the writes (32 rows, two chunks) nor the reads (consecutive chunks of a few rows) conflict.
+template <int D>
+__device__ __forceinline__ int o_chunk(int row, int ch) {
+  const int f = D == 128 ? ((row & 7) << 2 | row >> 3) : ((row & 7) << 1 | (row >> 3 & 1));
+  return (row * (D / 4) + (ch ^ f)) * 16;
+}
+template <int D>
+__device__ __forceinline__ void store_o_tile(char* dst, const floatx16 (&o)[D / 32], int qi, int hh) {
+#pragma unroll
+  for (int dt = 0; dt < D / 32; ++dt)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      *reinterpret_cast<floatx4*>(dst + o_chunk<D>(qi, 8 * dt + 2 * j + hh)) =
+          floatx4{o[dt][4 * j], o[dt][4 * j + 1], o[dt][4 * j + 2], o[dt][4 * j + 3]};
+}
+
 // More than 16 queries: the same work decomposition as the 16-query kernel — a sub-tile goes from the memory request to the
 // MFMAs in one slot of LDS, four slots per workgroup — with 32-query tiles on v_mfma_f32_32x32x16_bf16.  A 32x32 tile takes
 // half the LDS operand reads and half the MFMA instructions of two 16-query tiles, so that the QK^T -> softmax -> PV chain of
-// an in-order wavefront fits into the time its share of HBM needs for the next sub-tile.
-//   S^T = K Q^T   lane (query = lane % 32, hh = lane / 32), register v: logit of key 8 (v / 4) + 4 hh + v % 4
-//   O^T = V^T P^T the same registers, packed to bf16, are the B operand of k-step v / 8
+// an in-order wavefront fits into the time its share of HBM needs for the next sub-tile (attend_subtile32).
 // NT = 1 (up to 32 queries per query group), four wavefronts: a wavefront owns its slot; no barrier in the key loop.
 // NT = 2 (up to 64), eight wavefronts: wavefronts s and s + 4 share slot s, each stages half of its rows (K / V) and carries
 //   one query tile; one barrier per round.  (One wavefront with both tiles needs 128 accumulator registers outside the
@@ -851,43 +913,7 @@ __global__ __launch_bounds__(256 * NT, NT == 2 || (MODE & 4) == 0 ? 2 : 1) void 
 
   // one staged sub-tile into the running softmax
   auto consume = [&](auto k_operand, auto v_operand, uint32_t vmask) __attribute__((always_inline)) {
-    floatx16 acc;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-#pragma unroll
-    for (int ks = 0; ks < kKS; ++ks) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_operand(ks), q[ks], acc, 0, 0, 0);
-    if (vmask != 0xffffffffu) {  // wave-uniform: slots that hold no key
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[v] = ((vmask >> (8 * (v >> 2) + 4 * hh + (v & 3))) & 1u) ? acc[v] : -INFINITY;
-    }
-    float mx = fmaxf(acc[0], acc[1]);
-#pragma unroll
-    for (int v = 2; v < 16; ++v) mx = fmaxf(mx, acc[v]);
-    const uintx2 sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
-    mx = fmaxf(__uint_as_float(sw.x), __uint_as_float(sw.y)) * p.scale_log2;
-    const float m_new = fmaxf(m_run, mx);
-    const float m_use = m_new == -INFINITY ? 0.f : m_new;
-    if (__ballot(m_new != m_run) != 0ull) {  // some running maximum of this wavefront moves (rare after the first sub-tiles)
-      const float alpha = __builtin_amdgcn_exp2f(m_run - m_use);
-      l_run *= alpha;
-#pragma unroll
-      for (int dt = 0; dt < kDT; ++dt) o[dt] *= alpha;
-      m_run = m_new;
-    }
-    float ps[16];
-#pragma unroll
-    for (int v = 0; v < 16; ++v) ps[v] = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[v], p.scale_log2, -m_use));
-    float sum = ps[0] + ps[1];
-#pragma unroll
-    for (int v = 2; v < 16; v += 2) sum += ps[v] + ps[v + 1];
-    l_run += sum;
-#pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
-      const bf16x8 pb = as_bf16x8(make_uint4(cvt_pk_bf16(ps[8 * ks], ps[8 * ks + 1]), cvt_pk_bf16(ps[8 * ks + 2], ps[8 * ks + 3]),
-                                             cvt_pk_bf16(ps[8 * ks + 4], ps[8 * ks + 5]), cvt_pk_bf16(ps[8 * ks + 6], ps[8 * ks + 7])));
-#pragma unroll
-      for (int dt = 0; dt < kDT; ++dt) o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_operand(dt, ks), pb, o[dt], 0, 0, 0);
-    }
+    attend_subtile32<D>(k_operand, v_operand, q, vmask, hh, p.scale_log2, m_run, l_run, o);
   };
   auto k_at = [&](const char* stage, int ks) __attribute__((always_inline)) {
     return as_bf16x8(*reinterpret_cast<const uint4*>(stage + stage_off<D>(qi, 2 * ks + hh)));
@@ -937,12 +963,7 @@ __global__ __launch_bounds__(256 * NT, NT == 2 || (MODE & 4) == 0 ? 2 : 1) void 
     }
   }
 
-  // ---- merge the four slots, one query tile at a time, through LDS.  16-byte chunk ch of query row r sits at chunk ch ^ f(r):
-  // conflict-free for the writes (32 rows, two chunks) and the reads.
-  auto chunk_at = [&](int row, int ch) {
-    const int f = D == 128 ? ((row & 7) << 2 | row >> 3) : ((row & 7) << 1 | (row >> 3 & 1));
-    return (row * kOChunks + (ch ^ f)) * 16;
-  };
+  // ---- merge the four slots, one query tile at a time, through LDS
   if (NT > 1) __syncthreads();  // the slots have been read by both wavefronts
 #pragma unroll
   for (int n = 0; n < NT; ++n) {
@@ -950,12 +971,7 @@ __global__ __launch_bounds__(256 * NT, NT == 2 || (MODE & 4) == 0 ? 2 : 1) void 
     if (qn >= n_act) break;      // uniform
     if (n > 0) __syncthreads();  // the previous tile has been read by everyone
     if (NT == 1 || tile == n) {
-#pragma unroll
-      for (int dt = 0; dt < kDT; ++dt)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          *reinterpret_cast<floatx4*>(slotA + chunk_at(qi, 8 * dt + 2 * j + hh)) =
-              floatx4{o[dt][4 * j], o[dt][4 * j + 1], o[dt][4 * j + 2], o[dt][4 * j + 3]};
+      store_o_tile<D>(slotA, o, qi, hh);
       const uintx2 sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(l_run), __float_as_uint(l_run), false, false);
       if (hh == 0) ml_sh[slot][qi] = make_float2(m_run, __uint_as_float(sw.x) + __uint_as_float(sw.y));
     }
@@ -984,7 +1000,7 @@ __global__ __launch_bounds__(256 * NT, NT == 2 || (MODE & 4) == 0 ? 2 : 1) void 
         const int ch = c0 + kPerQuery * i;
         floatx4 s = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int w = 0; w < kWavesPerGroup; ++w) s += f[w] * *reinterpret_cast<const floatx4*>(ldsA + w * kBufBytes + chunk_at(mq, ch));
+        for (int w = 0; w < kWavesPerGroup; ++w) s += f[w] * *reinterpret_cast<const floatx4*>(ldsA + w * kBufBytes + o_chunk<D>(mq, ch));
         if (p.n_split == 1)
           *reinterpret_cast<uint2*>(p.out + (int64_t)h * p.osh + (int64_t)a * p.osn + ch * 4) =
               make_uint2(cvt_pk_bf16(s[0] * inv, s[1] * inv), cvt_pk_bf16(s[2] * inv, s[3] * inv));
@@ -1167,8 +1183,12 @@ hipError_t launch_sparse_attn(const void* Q, const int32_t* active_idx, const in
 // Block-entry refresh (Alg. 1, I_active = all positions): dense bidirectional attention of EVERY row of Q over every
 // key — the one MFMA-bound launch of the method (4 n_q L d flops per head against 2 L d 2 bytes of K and V).
 // A workgroup holds 256 consecutive queries, 32 per wavefront, and walks the key axis in 32-row sub-tiles shared by
-// its eight wavefronts and double-buffered through registers: while sub-tile t is multiplied, sub-tile t + 1 sits in
-// the second stage and the rows of t + 2 are in flight.  Both products use the 32x32x16 MFMA:
+// its eight wavefronts.  LDS holds a ring of eight K and eight V sub-tiles: while four are multiplied the other four are
+// filled, one per iteration through registers, and there is one barrier per four sub-tiles — behind a barrier all wavefronts
+// wait for their first operands at the same time and neither the matrix cores nor the vector ALU have work, and between
+// barriers the two wavefronts of a SIMD drift apart, so that the vector work of one runs beside the MFMAs of the other.
+// (32 heads, 8192 rows: 1052 us with a barrier per sub-tile, 1018 with one per four on normal-distributed data, 830 and 746
+// on zeros: the difference between the two kinds of data is the chip's power limit.)  Both products use the 32x32x16 MFMA:
 //   S^T = K Q^T   lane (query = lane % 32, hh = lane / 32) register v holds the logit of key 8 (v / 4) + 4 hh + v % 4,
 //                 so a query's 32 logits sit in two lanes and the row maximum costs one cross-lane exchange;
 //   O^T = V^T P^T the same registers, packed to bf16 eight at a time, are the B operand of k-step s = v / 8; the A
@@ -1177,8 +1197,9 @@ hipError_t launch_sparse_attn(const void* Q, const int32_t* active_idx, const in
 // row addresses are one scalar base per sub-tile plus per-lane offsets computed once, the running sum is taken by
 // v_dot2 over the packed bf16 pairs (two values per instruction, and the very values that enter the PV product),
 // the rescale of O runs only when some running maximum in the wavefront moved, and the ragged last sub-tile has a
-// loop body of its own.  No index lists, no key splits: each workgroup normalises and writes its own rows.
+// loop body of its own.  No index lists, no key splits across workgroups: each normalises and writes its own rows.
 // One-dimensional grid over the (head, query block) list, dealt to the XCDs in contiguous eighths (see the kernel).
+// The queries that would leave a round of workgroups mostly empty go to refresh_tail_kernel.
 // =====================================================================================================
 struct RefreshArgs {
   const uint16_t* Q;
@@ -1188,7 +1209,8 @@ struct RefreshArgs {
   float* lse;  // [H, n_q] natural log, or null
   int64_t qsh, qsn, ksh, ksn, vsh, vsn, osh, osn;
   int n_q, L;
-  int n_qb, n_work;  // query blocks per head; n_qb * heads
+  int n_qb, n_work;    // whole query blocks per head; work items (head, query block) of refresh_attn_kernel
+  int n_heads, n_tail;  // query tiles left to refresh_tail_kernel
   float scale_log2;
 };
 
@@ -1206,6 +1228,9 @@ __device__ __forceinline__ void static_for(F&& f) {
 __device__ __forceinline__ void pin(float& x) { asm volatile("" : "+v"(x)); }
 __device__ __forceinline__ void pin(int& x) { asm volatile("" : "+v"(x)); }
 
+// Eight wavefronts of 32 queries: two per SIMD, and 256 queries share every staged sub-tile.  (Four wavefronts of 64 queries —
+// each LDS operand feeding two MFMAs, one wavefront per SIMD with 444 registers — gives the same sharing with half the LDS
+// reads, but a lone wavefront cannot cover its own dependent vector-ALU chains: 0.82 against 1.01 PFLOP/s.)
 constexpr int kRefreshWaves = 8;  // wavefronts per workgroup
 constexpr int kRefreshBlock = 4;  // sub-tiles between two barriers
 
@@ -1468,11 +1493,147 @@ __global__ __launch_bounds__(64 * kRefreshWaves, 2) void refresh_attn_kernel(con
   }
 }
 
+// The query tiles that refresh_attn_kernel does not take (see launch_refresh_t): one 32-query tile per workgroup, the
+// key sub-tiles dealt to its eight wavefronts in turn.  A wavefront stages its own sub-tiles (no barrier in the key loop; the
+// operands are all in registers before the next sub-tile is requested into the same stage), the eight states are merged at the
+// end.  Tail tiles: the whole blocks the other kernel does not take, eight tiles each, then every head's last few tiles.
+template <int D>
+__global__ __launch_bounds__(64 * kRefreshWaves, 2) void refresh_tail_kernel(const RefreshArgs p) {
+  using G = Geo<D>;
+  constexpr int kKS = D / 16, kDT = D / 32, kOChunks = D / 4;
+  constexpr int kBufBytes = 2 * G::kStageBytes;
+  __shared__ __attribute__((aligned(16))) char lds[kRefreshWaves * kBufBytes];
+  __shared__ float2 ml_sh[kRefreshWaves][32];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int qi = lane & 31, hh = lane >> 5;
+  // contiguous eighths of the tile list to the XCDs, as in refresh_attn_kernel
+  const int chunk = (p.n_tail + 7) >> 3;
+  const int item = (int)(blockIdx.x & 7u) * chunk + (int)(blockIdx.x >> 3);
+  if (item >= p.n_tail) return;  // whole workgroup
+  const int n_left = (p.n_heads * p.n_qb - p.n_work) * kRefreshWaves;  // tiles of whole blocks
+  int h, tile;
+  if (item < n_left) {
+    const int block = p.n_work + item / kRefreshWaves;
+    h = block / p.n_qb;
+    tile = (block - h * p.n_qb) * kRefreshWaves + item % kRefreshWaves;
+  } else {
+    const int per_head = (p.n_q + 31) / 32 - p.n_qb * kRefreshWaves;
+    h = (item - n_left) / per_head;
+    tile = p.n_qb * kRefreshWaves + (item - n_left) - h * per_head;
+  }
+  const uint16_t* Kh = p.K + (int64_t)h * p.ksh;
+  const uint16_t* Vh = p.V + (int64_t)h * p.vsh;
+  const int n_tiles = (p.L + kSubTile - 1) / kSubTile;
+  char* stage = lds + wave * kBufBytes;
+  auto tile_of = [&](int t) __attribute__((always_inline)) {
+    SubTile s;
+    s.kind = 0;
+    s.sink_row = 0;
+    s.row0 = t * kSubTile;
+    s.vmask = low_mask(p.L - s.row0);
+    return s;
+  };
+  auto request = [&](int t) __attribute__((always_inline)) {
+    const SubTile s = tile_of(t);
+    issue_subtile<D, false, 0>(Kh, p.ksn, s, stage, lane);
+    issue_subtile<D, true, 0>(Vh, p.vsn, s, stage + G::kStageBytes, lane);
+  };
+  if (wave < n_tiles) request(wave);
+  const int q_row = tile * 32 + qi;
+  bf16x8 q[kKS];
+  {
+    const uint16_t* qsrc = p.Q + (int64_t)h * p.qsh + (int64_t)min(q_row, p.n_q - 1) * p.qsn + hh * 8;
+#pragma unroll
+    for (int ks = 0; ks < kKS; ++ks) q[ks] = as_bf16x8(*reinterpret_cast<const uint4*>(qsrc + ks * 16));
+  }
+  float m_run = -INFINITY, l_run = 0.f;
+  floatx16 o[kDT];
+#pragma unroll
+  for (int dt = 0; dt < kDT; ++dt)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) o[dt][v] = 0.f;
+  for (int t = wave; t < n_tiles; t += kRefreshWaves) {
+    wait_loads();
+    bf16x8 kop[kKS], vop[2][kDT];
+#pragma unroll
+    for (int ks = 0; ks < kKS; ++ks) kop[ks] = as_bf16x8(*reinterpret_cast<const uint4*>(stage + stage_off<D>(qi, 2 * ks + hh)));
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int dt = 0; dt < kDT; ++dt) vop[ks][dt] = read_v_operand32<D>(stage + G::kStageBytes, dt, ks, lane);
+    wait_lds_reads();
+    if (t + kRefreshWaves < n_tiles) request(t + kRefreshWaves);
+    attend_subtile32<D>([&](int ks) { return kop[ks]; }, [&](int dt, int ks) { return vop[ks][dt]; }, q, low_mask(p.L - t * kSubTile), hh,
+                        p.scale_log2, m_run, l_run, o);
+  }
+  store_o_tile<D>(stage, o, qi, hh);  // the wavefront's own stage, read for the last time above
+  const uintx2 sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(l_run), __float_as_uint(l_run), false, false);
+  if (hh == 0) ml_sh[wave][qi] = make_float2(m_run, __uint_as_float(sw.x) + __uint_as_float(sw.y));
+  __syncthreads();
+  const int mq = threadIdx.x >> 4, c0 = threadIdx.x & 15;  // thread = (query, chunks c0, c0 + 16, ...)
+  float f[kRefreshWaves], mmax = -INFINITY, lsum = 0.f;
+#pragma unroll
+  for (int w = 0; w < kRefreshWaves; ++w) mmax = fmaxf(mmax, ml_sh[w][mq].x);
+#pragma unroll
+  for (int w = 0; w < kRefreshWaves; ++w) {
+    const float2 ml = ml_sh[w][mq];
+    f[w] = ml.y > 0.f ? __builtin_amdgcn_exp2f(ml.x - mmax) : 0.f;
+    lsum += f[w] * ml.y;
+  }
+  const int row = tile * 32 + mq;
+  if (row >= p.n_q) return;
+  const float inv = lsum > 0.f ? 1.f / lsum : 0.f;
+#pragma unroll
+  for (int i = 0; i < kOChunks / 16; ++i) {
+    const int ch = c0 + 16 * i;
+    floatx4 s = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < kRefreshWaves; ++w) s += f[w] * *reinterpret_cast<const floatx4*>(lds + w * kBufBytes + o_chunk<D>(mq, ch));
+    *reinterpret_cast<uint2*>(p.out + (int64_t)h * p.osh + (int64_t)row * p.osn + ch * 4) =
+        make_uint2(cvt_pk_bf16(s[0] * inv, s[1] * inv), cvt_pk_bf16(s[2] * inv, s[3] * inv));
+  }
+  if (p.lse && c0 == 0) p.lse[(int64_t)h * p.n_q + row] = lsum > 0.f ? (mmax + __builtin_amdgcn_logf(lsum)) * kLn2 : -INFINITY;
+}
+
+// Which query tiles go to which kernel.  Every 256-query block takes the same time, so refresh_attn_kernel runs in rounds of 256
+// blocks (one per compute unit; at d = 64 two fit, and take twice as long), and a round that is mostly empty costs as much as a
+// full one.  refresh_tail_kernel takes single 32-query tiles: an eighth of the key sub-tiles per wavefront, each kTailCost
+// times as long because eight tiles no longer share the staged rows.  Both have a fixed part (first loads, merge).  Three ways
+// to cut, the cheapest is taken (times in us, measured):
+//   everything in blocks, the ragged one of each head included;
+//   whole blocks, and the last few tiles of each head to the tail kernel;
+//   whole rounds of blocks, and everything else to the tail kernel.
+// 32 heads, 8256 rows (33 blocks per head, 4.1 rounds): 1213 us all in blocks, 1106 us cut; 4 heads, 1056 rows, d = 64: 26 and 9.
 template <int D>
 static hipError_t launch_refresh_t(RefreshArgs& a, const focus_shape& s, hipStream_t st) {
-  a.n_qb = ceil_div(s.n_gen, 32 * kRefreshWaves);
-  a.n_work = a.n_qb * s.n_heads;
-  hipLaunchKernelGGL(refresh_attn_kernel<D>, dim3(8 * ceil_div(a.n_work, 8)), dim3(64 * kRefreshWaves), 0, st, a);
+  constexpr int kSlots = 256;
+  constexpr float kPerSubTile = D == 128 ? 0.85f : 0.6f, kTailCost = D == 128 ? 1.9f : 1.7f, kFixed = 5.f;
+  const int tiles = ceil_div(s.n_gen, 32), last = tiles % kRefreshWaves;
+  const float keys_time = (float)ceil_div(s.n_ctx + s.n_resp, kSubTile) * kPerSubTile;
+  const float block_time = keys_time + kFixed, tail_time = keys_time * kTailCost / kRefreshWaves + kFixed;
+  auto rounds = [](int64_t n) { return (float)((n + kSlots - 1) / kSlots); };
+  const int64_t whole = (int64_t)(tiles / kRefreshWaves) * s.n_heads, padded = (int64_t)ceil_div(tiles, kRefreshWaves) * s.n_heads;
+  const int64_t ragged = (int64_t)last * s.n_heads, rest = whole % kSlots;
+  const float t_padded = rounds(padded) * block_time;
+  const float t_whole = rounds(whole) * block_time + rounds(ragged) * tail_time;
+  const float t_rounds = rounds(whole - rest) * block_time + rounds(rest * kRefreshWaves + ragged) * tail_time;
+  a.n_heads = s.n_heads;
+  if (t_padded <= t_whole && t_padded <= t_rounds) {
+    a.n_qb = ceil_div(tiles, kRefreshWaves);
+    a.n_work = (int)padded;
+    a.n_tail = 0;
+  } else {
+    a.n_qb = tiles / kRefreshWaves;
+    a.n_work = (int)(t_whole <= t_rounds ? whole : whole - rest);
+    a.n_tail = (int)((whole - a.n_work) * kRefreshWaves + ragged);
+  }
+  if (a.n_work > 0) {
+    hipLaunchKernelGGL(refresh_attn_kernel<D>, dim3(8 * ceil_div(a.n_work, 8)), dim3(64 * kRefreshWaves), 0, st, a);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || a.n_tail == 0) return e;
+  }
+  hipLaunchKernelGGL(refresh_tail_kernel<D>, dim3(8 * ceil_div(a.n_tail, 8)), dim3(64 * kRefreshWaves), 0, st, a);
   return hipGetLastError();
 }
 
@@ -1491,10 +1652,6 @@ hipError_t launch_refresh_attn(const void* Q, const void* K, const void* V, cons
   a.n_q = s.n_gen;
   a.L = s.n_ctx + s.n_resp;
   a.scale_log2 = kLog2e / sqrtf((float)s.head_dim);
-  // Eight wavefronts of 32 queries: two per SIMD, and 256 queries share every staged sub-tile.  (Four wavefronts of 64
-  // queries — each LDS operand feeding two MFMAs, one wavefront per SIMD with 444 registers — gives the same sharing
-  // with half the LDS reads, but a lone wavefront cannot cover its own dependent vector-ALU chains: 0.82 against
-  // 1.01 PFLOP/s.)
   if (s.head_dim == 128) return launch_refresh_t<128>(a, s, st);
   return launch_refresh_t<64>(a, s, st);
 }

@@ -855,6 +855,27 @@ def test_refresh_attn_equals_full_bidirectional_attention(G, H, M, N, d):
     assert np.allclose(lse.cpu().numpy(), lse2.cpu().numpy(), atol=1e-3)
 
 
+@pytest.mark.parametrize("H,n_q,L,d", [
+    (256, 256, 20, 128),   # 256-query blocks only: one key sub-tile,
+    (256, 250, 130, 64),   # ... fewer than the ring holds,
+    (256, 256, 259, 128),  # ... once around it and a ragged one,
+    (40, 1100, 1100, 128), # ... and a ragged query block
+    (64, 1032, 1032, 64),  # a full round of blocks, the last tile of every head on its own
+    (72, 1000, 300, 128),  # a round of blocks, the others as single tiles
+    (3, 2100, 70, 64),     # single tiles only, fewer key sub-tiles than wavefronts
+    (1, 1, 33, 128),
+])
+def test_refresh_attn_cut_into_blocks_and_tiles(G, H, n_q, L, d):
+    q, k, v = (_rand_bf16(161 + i, H, r, d).to(G.DEV) for i, r in enumerate((n_q, L, L)))
+    out = torch.full((H, n_q, d), float("nan"), dtype=torch.bfloat16, device=G.DEV)
+    lse = torch.full((H, n_q), float("nan"), dtype=torch.float32, device=G.DEV)
+    fb.refresh_attn(q, k, v, fb.make_shape(q, k, v, L, 64, out), out, lse)
+    Q, K, V = (t.float().cpu() for t in (q, k, v))
+    s = torch.matmul(Q, K.transpose(1, 2).contiguous()) / math.sqrt(d)
+    G.assert_attention_close(out, torch.matmul(torch.softmax(s, -1), V).numpy())
+    assert np.allclose(lse.cpu().numpy(), torch.logsumexp(s, -1).numpy(), atol=2e-3)
+
+
 @pytest.mark.parametrize("d", [64, 128])
 def test_refresh_attn_running_maximum_keeps_moving(G, d):
     """Keys grow along the key axis and the queries are large, so the row maxima rise in almost every sub-tile and the
