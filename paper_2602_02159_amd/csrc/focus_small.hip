@@ -822,21 +822,35 @@ __global__ __launch_bounds__(256) void token_confidence_kernel(const uint16_t* _
   }
 }
 
+// 32 lanes per row, one split each (one thread that walked the splits took 15 us for 30 of them)
+constexpr int kConfMaxSplits = 32;
 __global__ __launch_bounds__(256) void token_confidence_merge(const ConfState* __restrict__ part, int n_rows, int n_split,
                                                               int32_t* __restrict__ tokens, float* __restrict__ conf) {
-  const int row = blockIdx.x * blockDim.x + threadIdx.x;
-  if (row >= n_rows) return;
-  ConfState r = part[(int64_t)row * n_split];
-  for (int s = 1; s < n_split; ++s) r = conf_merge(r, part[(int64_t)row * n_split + s]);
-  tokens[row] = r.s > 0.f ? r.idx : -1;
-  conf[row] = r.s > 0.f ? 1.f / r.s : 0.f;
+  const int row = blockIdx.x * (256 / kConfMaxSplits) + (int)threadIdx.x / kConfMaxSplits, s = threadIdx.x % kConfMaxSplits;
+  ConfState r;
+  r.m = -INFINITY;
+  r.idx = 0x7fffffff;
+  r.s = 0.f;
+  if (row < n_rows && s < n_split) r = part[(int64_t)row * n_split + s];
+#pragma unroll
+  for (int o = 1; o < kConfMaxSplits; o <<= 1) {
+    ConfState other;
+    other.m = __shfl_xor(r.m, o, kWave);
+    other.idx = __shfl_xor(r.idx, o, kWave);
+    other.s = __shfl_xor(r.s, o, kWave);
+    r = conf_merge(r, other);
+  }
+  if (row < n_rows && s == 0) {
+    tokens[row] = r.s > 0.f ? r.idx : -1;
+    conf[row] = r.s > 0.f ? 1.f / r.s : 0.f;
+  }
 }
 
-// splits per row: enough workgroups to fill the chip, at least 64 vectors each
+// splits per row: enough workgroups to fill the chip, and as many as it takes for a thread to have its vectors in flight at once
 int token_confidence_splits(int n_rows, int vocab) {
   const int by_rows = ceil_div(1024, n_rows);
-  const int by_work = std::max(1, (vocab >> 3) / 512);
-  return std::max(1, std::min(std::min(by_rows, by_work), 32));
+  const int by_work = ceil_div(vocab >> 3, 512);
+  return std::max(1, std::min(std::min(by_rows, by_work), kConfMaxSplits));
 }
 size_t token_confidence_workspace(int n_rows, int vocab) {
   const int n_split = token_confidence_splits(n_rows, vocab);
@@ -851,38 +865,42 @@ hipError_t launch_token_confidence(const void* logits, int64_t row_stride, const
                      row_stride, masked, vocab, n_split, part, tokens, conf);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || n_split == 1) return e;
-  hipLaunchKernelGGL(token_confidence_merge, dim3(ceil_div(n_rows, 256)), dim3(256), 0, st, part, n_rows, n_split, tokens, conf);
+  hipLaunchKernelGGL(token_confidence_merge, dim3(ceil_div(n_rows, 256 / kConfMaxSplits)), dim3(256), 0, st, part, n_rows, n_split,
+                     tokens, conf);
   return hipGetLastError();
 }
 
-// Eq. 3: cache rows row_base + active_idx[a] of K and V take the new states K_new[:, a], V_new[:, a].  One workgroup
-// per (active slot, head); a thread moves one 16-byte chunk of the K or of the V row.  Entries outside the active
-// count, negative, or mapping outside [0, n_rows) are skipped.
-__global__ __launch_bounds__(64) void cache_update_kernel(uint16_t* __restrict__ Kc, uint16_t* __restrict__ Vc, int64_t ksh,
-                                                          int64_t ksn, int64_t vsh, int64_t vsn,
-                                                          const uint16_t* __restrict__ Kn, const uint16_t* __restrict__ Vn,
-                                                          int64_t nsh, int64_t nsn, const int32_t* __restrict__ active_idx,
-                                                          const int32_t* __restrict__ counts, int max_active, int row_base,
-                                                          int n_rows, int chunks) {
-  const int a = blockIdx.x, h = blockIdx.y;
-  const int n_act = counts ? min(max(counts[1], 0), max_active) : max_active;
-  if (a >= n_act) return;
+// Eq. 3: cache rows row_base + active_idx[a] of K and V take the new states K_new[:, a], V_new[:, a].  A thread moves one 16-byte
+// chunk of the K or of the V row of a slot, a workgroup 256 / (2 * chunks) slots of one head.  Nothing but latency: the new
+// state sits at the slot's own place, so it, the position and the count are requested together and the kernel is one memory
+// round trip and a store long (32 heads, 32 slots: 5.4 us when they followed each other, one 64-thread workgroup per slot; now
+// 3.5).  Entries outside the active count, negative, or mapping outside [0, n_rows) are skipped.
+__global__ __launch_bounds__(256) void cache_update_kernel(uint16_t* __restrict__ Kc, uint16_t* __restrict__ Vc, int64_t ksh,
+                                                           int64_t ksn, int64_t vsh, int64_t vsn,
+                                                           const uint16_t* __restrict__ Kn, const uint16_t* __restrict__ Vn,
+                                                           int64_t nsh, int64_t nsn, const int32_t* __restrict__ active_idx,
+                                                           const int32_t* __restrict__ counts, int max_active, int row_base,
+                                                           int n_rows, int chunks) {
+  const int per_slot = 2 * chunks;  // 16 or 32
+  const int a = blockIdx.x * (256 / per_slot) + (int)threadIdx.x / per_slot, h = blockIdx.y;
+  if (a >= max_active) return;
+  const int t = (int)threadIdx.x % per_slot;
+  const bool is_v = t >= chunks;
+  const int c = is_v ? t - chunks : t;
+  const uint4 x = *reinterpret_cast<const uint4*>((is_v ? Vn : Kn) + (int64_t)h * nsh + (int64_t)a * nsn + c * 8);
   const int i = active_idx[a];
+  const int n_act = counts ? min(max(counts[1], 0), max_active) : max_active;
   const int64_t row = (int64_t)row_base + i;
-  if (i < 0 || row < 0 || row >= n_rows) return;
-  for (int t = threadIdx.x; t < 2 * chunks; t += blockDim.x) {
-    const bool is_v = t >= chunks;
-    const int c = is_v ? t - chunks : t;
-    const uint16_t* src = (is_v ? Vn : Kn) + (int64_t)h * nsh + (int64_t)a * nsn + c * 8;
-    uint16_t* dst = is_v ? Vc + (int64_t)h * vsh + row * vsn + c * 8 : Kc + (int64_t)h * ksh + row * ksn + c * 8;
-    *reinterpret_cast<uint4*>(dst) = *reinterpret_cast<const uint4*>(src);
-  }
+  if (a >= n_act || i < 0 || row < 0 || row >= n_rows) return;
+  uint16_t* dst = is_v ? Vc + (int64_t)h * vsh + row * vsn + c * 8 : Kc + (int64_t)h * ksh + row * ksn + c * 8;
+  *reinterpret_cast<uint4*>(dst) = x;
 }
 
 hipError_t launch_cache_update(void* K_cache, void* V_cache, const focus_shape& s, const void* K_new, const void* V_new,
                                int64_t new_stride_h, int64_t new_stride_n, const int32_t* active_idx, const int32_t* counts,
                                int max_active, int row_base, hipStream_t st) {
-  hipLaunchKernelGGL(cache_update_kernel, dim3(max_active, s.n_heads), dim3(64), 0, st, static_cast<uint16_t*>(K_cache),
+  const int slots = 256 / (2 * (s.head_dim / 8));
+  hipLaunchKernelGGL(cache_update_kernel, dim3(ceil_div(max_active, slots), s.n_heads), dim3(256), 0, st, static_cast<uint16_t*>(K_cache),
                      static_cast<uint16_t*>(V_cache), s.k_stride_h, s.k_stride_n, s.v_stride_h, s.v_stride_n,
                      static_cast<const uint16_t*>(K_new), static_cast<const uint16_t*>(V_new), new_stride_h, new_stride_n,
                      active_idx, counts, max_active, row_base, s.n_ctx + s.n_resp, s.head_dim / 8);
