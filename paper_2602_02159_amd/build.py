@@ -15,7 +15,10 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libfocus_hip.so")
 SOURCES = ["focus_api.hip", "focus_small.hip", "focus_mfma.hip"]
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-fno-gpu-rdc", "-Wall", "-Wno-unused-function",
-         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
+         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         # the first 14 dwords of a kernel's scalar arguments arrive in registers: most launches of a step are two or three
+         # dependent memory round trips long, and fetching the arguments was one more
+         "-mllvm", "-amdgpu-kernarg-preload-count=14"]
 
 
 def hipcc() -> str:

@@ -455,13 +455,46 @@ struct AttnArgs {
   float* lse2_out;    // [H, q_pad] base-2 log-sum-exp per row (+inf for an empty row), or null
 };
 
+// The arguments that the first memory requests of an attention kernel need, once more as leading scalar parameters: those (14
+// dwords) are in scalar registers when a wavefront starts (-amdgpu-kernarg-preload-count), while a member of AttnArgs is a load
+// of its own in front of everything that depends on it.
+#define ATTN_FIRST_PARAMS                                                                                                  \
+  const float *rel_part, const int32_t *active_idx, const uint16_t *Q, const int32_t *counts, int n_b, int H, int max_active, \
+      int n_gen, int n_split, int n_sub
+#define ATTN_FIRST_NAMES rel_part, active_idx, Q, counts, n_b, H, max_active, n_gen, n_split, n_sub
+__device__ __forceinline__ AttnArgs with_first(AttnArgs p, ATTN_FIRST_PARAMS) {
+  p.rel_part = rel_part;
+  p.active_idx = active_idx;
+  p.Q = Q;
+  p.counts = counts;
+  p.n_b = n_b;
+  p.H = H;
+  p.max_active = max_active;
+  p.n_gen = n_gen;
+  p.n_split = n_split;
+  p.n_sub = n_sub;
+  return p;
+}
+#define ATTN_LAUNCH(kernel, grid, block, st, a)                                                                            \
+  hipLaunchKernelGGL(kernel, grid, block, 0, st, (a).rel_part, (a).active_idx, (a).Q, (a).counts, (a).n_b, (a).H, (a).max_active, \
+                     (a).n_gen, (a).n_split, (a).n_sub, a)
+
 // What the attention kernels prepare before their first K/V request.
-// R_b = (1 / (|I_focus| H)) sum_h part[h, b] for b = threadIdx.x (n_b <= 256 = blockDim.x), then Top-C into kept_sh; the
-// workgroup with `writer` set also writes scores and kept blocks out.  First use of `sm`.
-__device__ __forceinline__ void rank_blocks(const AttnArgs& p, int32_t* kept_sh, TopkShared& sm, bool writer) {
+// R_b = (1 / (|I_focus| H)) sum_h part[h, b] for b = threadIdx.x (n_b <= 256 <= blockDim.x), then Top-C into kept_sh; the
+// workgroup with `writer` set also writes scores and kept blocks out.  First use of `sm`.  `first` holds the loads of the first
+// 32 heads (first_partials), which the caller requests before it waits for anything.
+__device__ __forceinline__ void first_partials(float (&first)[32], const AttnArgs& p) {
+  const uint32_t b = min((int)threadIdx.x, p.n_b - 1);
+#pragma unroll
+  for (int h = 0; h < 32; ++h) first[h] = p.rel_part[(uint32_t)(min(h, p.H - 1) * p.n_b) + b];  // n_b <= 256: small offsets
+  __builtin_amdgcn_sched_barrier(0);  // (the scheduler would move the wait for the row ids in front of these loads)
+}
+__device__ __forceinline__ void rank_blocks(const AttnArgs& p, const float (&first)[32], int32_t* kept_sh, TopkShared& sm, bool writer) {
   const int tid = threadIdx.x;
   float r = 0.f;
-  if (tid < p.n_b) r = sum_partials(p.rel_part, p.H, p.n_b, tid);
+#pragma unroll
+  for (int h = 0; h < 32; ++h) r += h < p.H ? first[h] : 0.f;  // head by head, the order of sum_partials
+  if (p.H > 32 && tid < p.n_b) r = sum_partials(p.rel_part, p.H, p.n_b, tid, 32, r);
   const int n_f = p.counts ? min(max(p.counts[0], 0), p.n_focus_max) : p.n_focus_max;
   r *= n_f > 0 ? 1.f / ((float)n_f * (float)p.H) : 0.f;
   auto keyfn = [=](int, uint32_t& key) -> bool {
@@ -526,7 +559,8 @@ __device__ __forceinline__ SinkUnion prepare_union(const AttnArgs& p, int split,
 // In every case a second, small kernel merges the key splits.  (Letting the last workgroup of a head merge them
 // behind device-scope fences was measured: the fences cost ~10 us per launch, more than the launch they save.)
 template <int D, int FUSE>
-__global__ __launch_bounds__(256, (FUSE & 2) == 0 ? 2 : 1) void sparse_attn_kernel(const AttnArgs p) {
+__global__ __launch_bounds__(256, (FUSE & 2) == 0 ? 2 : 1) void sparse_attn_kernel(ATTN_FIRST_PARAMS, const AttnArgs args) {
+  const AttnArgs p = with_first(args, ATTN_FIRST_NAMES);
   using G = Geo<D>;
   constexpr bool FUSED = (FUSE & 1) != 0;                // Top-C in the prologue
   constexpr bool PIPE = (FUSE & 2) != 0;                 // two K/V stages per wavefront
@@ -558,10 +592,10 @@ __global__ __launch_bounds__(256, (FUSE & 2) == 0 ? 2 : 1) void sparse_attn_kern
   int qrow_early = -1;
   if (FUSED) {
     qrow_early = fetch_q_row(p.active_idx, 0, p.max_active, p.n_gen, lane);
+    float first[32];
+    first_partials(first, p);
     load_q_tile<D>(q[0], Qh, p.qsn, qrow_early, lane);
-  }
-  if (FUSED) {
-    rank_blocks(p, kept_sh, topk_sm, blockIdx.x == 0 && blockIdx.y == 0);
+    rank_blocks(p, first, kept_sh, topk_sm, blockIdx.x == 0 && blockIdx.y == 0);
     kept_blocks = kept_sh;
   }
   __shared__ uint32_t kept_bits_sh[kBitmapBlocks / 32];
@@ -821,7 +855,8 @@ __device__ __forceinline__ void store_o_tile(char* dst, const floatx16 (&o)[D / 
 // Grid: one-dimensional.  Workgroups go to the XCDs round-robin, so the query groups of one (head, key split) pair are
 // placed eight apart: they run on the same XCD at about the same time and its L2 serves their common K/V rows.
 template <int D, int NT, int MODE>
-__global__ __launch_bounds__(256 * NT, NT == 2 || (MODE & 4) == 0 ? 2 : 1) void wide_attn_kernel(const AttnArgs p) {
+__global__ __launch_bounds__(256 * NT, NT == 2 || (MODE & 4) == 0 ? 2 : 1) void wide_attn_kernel(ATTN_FIRST_PARAMS, const AttnArgs args) {
+  const AttnArgs p = with_first(args, ATTN_FIRST_NAMES);
   using G = Geo<D>;
   constexpr bool FUSED = (MODE & 1) != 0, PIPE = (MODE & 2) != 0, DOUBLE = (MODE & 4) != 0;
   static_assert(!DOUBLE || PIPE, "two stages are for the key loop");
@@ -866,8 +901,10 @@ __global__ __launch_bounds__(256 * NT, NT == 2 || (MODE & 4) == 0 ? 2 : 1) void 
   };
   const int32_t* kept_blocks = p.kept_blocks;
   if (FUSED) {  // the query rows travel while the blocks are ranked
+    float first[32];
+    first_partials(first, p);
     load_q();
-    rank_blocks(p, kept_sh, *reinterpret_cast<TopkShared*>(topk_raw), pair == 0 && qg == 0);
+    rank_blocks(p, first, kept_sh, *reinterpret_cast<TopkShared*>(topk_raw), pair == 0 && qg == 0);
     kept_blocks = kept_sh;
   }
   const SinkUnion uni = prepare_union(p, split, kept_blocks, kept_bits_sh, &sinks_unsorted_sh);
@@ -1099,13 +1136,13 @@ static void launch_wide_t(const AttnArgs& a, const SplitPlan& p, bool fused, hip
   const dim3 grid(ceil_div(p.n_split * a.H, 8) * 8 * p.q_groups), block(256 * NT);
   constexpr int kKeep = LOOP & 8;
   if (fused && p.pipelined)
-    hipLaunchKernelGGL((wide_attn_kernel<D, NT, LOOP | 1>), grid, block, 0, st, a);
+    ATTN_LAUNCH((wide_attn_kernel<D, NT, LOOP | 1>), grid, block, st, a);
   else if (fused)
-    hipLaunchKernelGGL((wide_attn_kernel<D, NT, kKeep | 1>), grid, block, 0, st, a);
+    ATTN_LAUNCH((wide_attn_kernel<D, NT, kKeep | 1>), grid, block, st, a);
   else if (p.pipelined)
-    hipLaunchKernelGGL((wide_attn_kernel<D, NT, LOOP>), grid, block, 0, st, a);
+    ATTN_LAUNCH((wide_attn_kernel<D, NT, LOOP>), grid, block, st, a);
   else
-    hipLaunchKernelGGL((wide_attn_kernel<D, NT, kKeep>), grid, block, 0, st, a);
+    ATTN_LAUNCH((wide_attn_kernel<D, NT, kKeep>), grid, block, st, a);
 }
 
 template <int D>
@@ -1123,17 +1160,17 @@ static hipError_t launch_attn_t(const AttnArgs& a, const SplitPlan& p, bool fuse
   } else if (a.logits_out != nullptr) {  // dense probe layer with the logits spilled
     if (fused) return hipErrorInvalidValue;
     if (p.pipelined)
-      hipLaunchKernelGGL((sparse_attn_kernel<D, 6>), grid, block, 0, st, a);
+      ATTN_LAUNCH((sparse_attn_kernel<D, 6>), grid, block, st, a);
     else
-      hipLaunchKernelGGL((sparse_attn_kernel<D, 4>), grid, block, 0, st, a);
+      ATTN_LAUNCH((sparse_attn_kernel<D, 4>), grid, block, st, a);
   } else if (fused && p.pipelined)
-    hipLaunchKernelGGL((sparse_attn_kernel<D, 3>), grid, block, 0, st, a);
+    ATTN_LAUNCH((sparse_attn_kernel<D, 3>), grid, block, st, a);
   else if (fused)
-    hipLaunchKernelGGL((sparse_attn_kernel<D, 1>), grid, block, 0, st, a);
+    ATTN_LAUNCH((sparse_attn_kernel<D, 1>), grid, block, st, a);
   else if (p.pipelined)
-    hipLaunchKernelGGL((sparse_attn_kernel<D, 2>), grid, block, 0, st, a);
+    ATTN_LAUNCH((sparse_attn_kernel<D, 2>), grid, block, st, a);
   else
-    hipLaunchKernelGGL((sparse_attn_kernel<D, 0>), grid, block, 0, st, a);
+    ATTN_LAUNCH((sparse_attn_kernel<D, 0>), grid, block, st, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || p.n_split == 1) return e;
   hipLaunchKernelGGL(attn_combine_kernel<D>, dim3(a.max_active, a.H), dim3(256), 0, st, a.part_o, a.part_ml, a.counts, a.max_active,
@@ -1681,7 +1718,18 @@ struct LogitArgs {
 // MODE 2: second pass for more than 16 queries: with the row log-sum-exps known, the probabilities are formed on the
 //         fly and summed over the workgroup's queries; colpart[qg * H + h, j] = sum_i P[h, i, j].
 template <int D, int NQT, int MODE>
-__global__ __launch_bounds__(256, 2) void qk_logits_kernel(const LogitArgs p) {
+__global__ __launch_bounds__(256, 2) void qk_logits_kernel(const uint16_t* K, int64_t ksh, int64_t ksn, const int32_t* active_idx, int L,
+                                                           int n_sub, int n_split, int max_active, int n_gen, const LogitArgs args) {
+  LogitArgs p = args;  // what the first requests need comes in registers, as in the attention kernels
+  p.K = K;
+  p.ksh = ksh;
+  p.ksn = ksn;
+  p.active_idx = active_idx;
+  p.L = L;
+  p.n_sub = n_sub;
+  p.n_split = n_split;
+  p.max_active = max_active;
+  p.n_gen = n_gen;
   using G = Geo<D>;
   __shared__ __attribute__((aligned(16))) char lds[kWavesPerGroup * G::kStageBytes];
   __shared__ float ml_sh[kWavesPerGroup][NQT][16][2];
@@ -1804,11 +1852,11 @@ template <int D, int NQT>
 static hipError_t launch_logits_t(const LogitArgs& a, const SplitPlan& p, int mode, hipStream_t st) {
   dim3 grid(p.n_split, a.H, p.q_groups);
   if (mode == 0)
-    hipLaunchKernelGGL((qk_logits_kernel<D, NQT, 0>), grid, dim3(256), 0, st, a);
+    hipLaunchKernelGGL((qk_logits_kernel<D, NQT, 0>), grid, dim3(256), 0, st, a.K, a.ksh, a.ksn, a.active_idx, a.L, a.n_sub, a.n_split, a.max_active, a.n_gen, a);
   else if (mode == 1)
-    hipLaunchKernelGGL((qk_logits_kernel<D, NQT, 1>), grid, dim3(256), 0, st, a);
+    hipLaunchKernelGGL((qk_logits_kernel<D, NQT, 1>), grid, dim3(256), 0, st, a.K, a.ksh, a.ksn, a.active_idx, a.L, a.n_sub, a.n_split, a.max_active, a.n_gen, a);
   else
-    hipLaunchKernelGGL((qk_logits_kernel<D, NQT, 2>), grid, dim3(256), 0, st, a);
+    hipLaunchKernelGGL((qk_logits_kernel<D, NQT, 2>), grid, dim3(256), 0, st, a.K, a.ksh, a.ksn, a.active_idx, a.L, a.n_sub, a.n_split, a.max_active, a.n_gen, a);
   return hipGetLastError();
 }
 

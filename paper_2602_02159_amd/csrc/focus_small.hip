@@ -337,11 +337,11 @@ hipError_t launch_block_means_relevance(const void* K, const void* Q, const int3
 // focus_row_sum), so the whole kernel is two dependent memory round trips long.
 // =====================================================================================================
 template <int D>
-__global__ __launch_bounds__(256) void relevance_partial_kernel(const uint16_t* __restrict__ Q, int64_t qsh, int64_t qsn,
-                                                                const int32_t* __restrict__ focus_idx,
-                                                                const int32_t* __restrict__ counts, int n_focus_max,
-                                                                int n_gen, const float* __restrict__ kbar, int n_b,
-                                                                float* __restrict__ part) {
+__global__ __launch_bounds__(256) void relevance_partial_kernel(const int32_t* __restrict__ focus_idx,
+                                                                const float* __restrict__ kbar,
+                                                                const int32_t* __restrict__ counts,
+                                                                const uint16_t* __restrict__ Q, int64_t qsh, int64_t qsn, int n_b,
+                                                                int n_focus_max, int n_gen, float* __restrict__ part) {
   constexpr int CPR = D / 8;      // lanes per block row
   constexpr int RPP = 256 / CPR;  // block rows per pass
   constexpr int PASSES = 2;
@@ -377,11 +377,11 @@ hipError_t launch_block_relevance(const void* Q, const int32_t* focus_idx, const
   const int n_b = ceil_div(s.n_ctx, s.block);
   const uint16_t* q = static_cast<const uint16_t*>(Q);
   if (s.head_dim == 128)
-    hipLaunchKernelGGL(relevance_partial_kernel<128>, dim3(ceil_div(n_b, 32), s.n_heads), dim3(256), 0, st, q, s.q_stride_h,
-                       s.q_stride_n, focus_idx, counts, n_focus_max, s.n_gen, kbar, n_b, part);
+    hipLaunchKernelGGL(relevance_partial_kernel<128>, dim3(ceil_div(n_b, 32), s.n_heads), dim3(256), 0, st, focus_idx,
+                       kbar, counts, q, s.q_stride_h, s.q_stride_n, n_b, n_focus_max, s.n_gen, part);
   else
-    hipLaunchKernelGGL(relevance_partial_kernel<64>, dim3(ceil_div(n_b, 64), s.n_heads), dim3(256), 0, st, q, s.q_stride_h,
-                       s.q_stride_n, focus_idx, counts, n_focus_max, s.n_gen, kbar, n_b, part);
+    hipLaunchKernelGGL(relevance_partial_kernel<64>, dim3(ceil_div(n_b, 64), s.n_heads), dim3(256), 0, st, focus_idx,
+                       kbar, counts, q, s.q_stride_h, s.q_stride_n, n_b, n_focus_max, s.n_gen, part);
   return hipGetLastError();
 }
 
@@ -875,12 +875,12 @@ hipError_t launch_token_confidence(const void* logits, int64_t row_stride, const
 // state sits at the slot's own place, so it, the position and the count are requested together and the kernel is one memory
 // round trip and a store long (32 heads, 32 slots: 5.4 us when they followed each other, one 64-thread workgroup per slot; now
 // 3.5).  Entries outside the active count, negative, or mapping outside [0, n_rows) are skipped.
-__global__ __launch_bounds__(256) void cache_update_kernel(uint16_t* __restrict__ Kc, uint16_t* __restrict__ Vc, int64_t ksh,
-                                                           int64_t ksn, int64_t vsh, int64_t vsn,
-                                                           const uint16_t* __restrict__ Kn, const uint16_t* __restrict__ Vn,
+__global__ __launch_bounds__(256) void cache_update_kernel(const uint16_t* __restrict__ Kn, const uint16_t* __restrict__ Vn,
                                                            int64_t nsh, int64_t nsn, const int32_t* __restrict__ active_idx,
-                                                           const int32_t* __restrict__ counts, int max_active, int row_base,
-                                                           int n_rows, int chunks) {
+                                                           const int32_t* __restrict__ counts, int max_active, int chunks,
+                                                           int row_base, int n_rows, uint16_t* __restrict__ Kc,
+                                                           uint16_t* __restrict__ Vc, int64_t ksh, int64_t ksn, int64_t vsh,
+                                                           int64_t vsn) {
   const int per_slot = 2 * chunks;  // 16 or 32
   const int a = blockIdx.x * (256 / per_slot) + (int)threadIdx.x / per_slot, h = blockIdx.y;
   if (a >= max_active) return;
@@ -900,10 +900,10 @@ hipError_t launch_cache_update(void* K_cache, void* V_cache, const focus_shape& 
                                int64_t new_stride_h, int64_t new_stride_n, const int32_t* active_idx, const int32_t* counts,
                                int max_active, int row_base, hipStream_t st) {
   const int slots = 256 / (2 * (s.head_dim / 8));
-  hipLaunchKernelGGL(cache_update_kernel, dim3(ceil_div(max_active, slots), s.n_heads), dim3(256), 0, st, static_cast<uint16_t*>(K_cache),
-                     static_cast<uint16_t*>(V_cache), s.k_stride_h, s.k_stride_n, s.v_stride_h, s.v_stride_n,
-                     static_cast<const uint16_t*>(K_new), static_cast<const uint16_t*>(V_new), new_stride_h, new_stride_n,
-                     active_idx, counts, max_active, row_base, s.n_ctx + s.n_resp, s.head_dim / 8);
+  hipLaunchKernelGGL(cache_update_kernel, dim3(ceil_div(max_active, slots), s.n_heads), dim3(256), 0, st,
+                     static_cast<const uint16_t*>(K_new), static_cast<const uint16_t*>(V_new), new_stride_h, new_stride_n, active_idx,
+                     counts, max_active, s.head_dim / 8, row_base, s.n_ctx + s.n_resp, static_cast<uint16_t*>(K_cache),
+                     static_cast<uint16_t*>(V_cache), s.k_stride_h, s.k_stride_n, s.v_stride_h, s.v_stride_n);
   return hipGetLastError();
 }
 

@@ -32,11 +32,10 @@ __device__ __forceinline__ uint32_t order_key(float x) {
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
-// sum over the n_parts per-head partial values of element j, always in the same order (32 at a time, then 8, then 1)
-// so that every kernel that assembles block relevances gets bit-identical results
-__device__ __forceinline__ float sum_partials(const float* __restrict__ part, int n_parts, int n, int j) {
-  float acc = 0.f;
-  int h = 0;
+// sum over the n_parts per-head partial values of element j, always part by part in ascending order (the loads go out 32, then
+// 8, then 1 at a time) so that every kernel that assembles block relevances gets bit-identical results; continues from part h
+// with the sum acc of the parts before it
+__device__ __forceinline__ float sum_partials(const float* __restrict__ part, int n_parts, int n, int j, int h = 0, float acc = 0.f) {
   for (; h + 32 <= n_parts; h += 32) {  // 32 independent loads: one memory round trip for 32 heads
     float v[32];
 #pragma unroll
