@@ -1,5 +1,6 @@
 // extern "C" boundary: argument validation on the host, workspace carving, launch sequencing.
 // Nothing here touches the GPU before every argument has been checked.
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -141,7 +142,7 @@ static SinkWs ws_find_sinks(const focus_shape& s, const SplitPlan& p) {
   w.col_mass = off;
   off += align_up(L * sizeof(float));
   w.cand = off;  // first-round nominees of the sink tournament: positions, then order keys
-  off += align_up((size_t)2 * kTournamentMaxCand * sizeof(int32_t));  // positions, then their keys
+  off += align_up((size_t)2 * kMaxNominees * sizeof(int32_t));  // positions, then their keys
   w.total = off;
   return w;
 }
@@ -181,9 +182,29 @@ static ProbeWs ws_probe_layer(const focus_shape& s, const SplitPlan& pa, const S
   w.col_mass = off;
   off += align_up(L * sizeof(float));
   w.cand = off;
-  off += align_up((size_t)2 * kTournamentMaxCand * sizeof(int32_t));  // positions, then their keys
+  off += align_up((size_t)2 * kMaxNominees * sizeof(int32_t));  // positions, then their keys
   w.total = off;
   return w;
+}
+
+// Second half of the sink identification: column masses S from the kept logits or per-part column sums, then Top-N_sink.  Few
+// sinks, or not too many: the 128-key groups of the column-mass kernel nominate and one workgroup decides; else a radix select.
+static int column_mass_and_sinks(const char* who, const float* src, bool two_pass, const float* lse2, const int32_t* counts, int max_active,
+                                 int q_groups, const focus_shape& s, int n_sink, float* S, char* cand_ws, int32_t* sink_idx, hipStream_t st) {
+  const bool tournament = sink_tournament_fits(s.n_ctx, n_sink), rank = !tournament && sink_rank_fits(s.n_ctx, n_sink);
+  int32_t* cand = (tournament || rank) ? reinterpret_cast<int32_t*>(cand_ws) : nullptr;
+  uint32_t* cand_keys = cand ? reinterpret_cast<uint32_t*>(cand_ws) + kMaxNominees : nullptr;
+  hipError_t e = launch_column_mass(src, two_pass, lse2, counts, max_active, two_pass ? q_groups * s.n_heads : s.n_heads, s.n_heads,
+                                    s.n_ctx + s.n_resp, S, s.n_ctx, rank ? std::min(n_sink, kRankNominees) : n_sink, cand, cand_keys, st);
+  if (e != hipSuccess) return fail(FOCUS_ELAUNCH, "%s(column mass): %s", who, hipGetErrorString(e));
+  if (tournament)
+    e = launch_sink_final(cand, cand_keys, s.n_ctx, n_sink, sink_idx, st);
+  else if (rank)
+    e = launch_sink_rank(cand, cand_keys, s.n_ctx, n_sink, S, sink_idx, st);
+  else if (n_sink > 0)
+    e = launch_reduce_topk(nullptr, 0, nullptr, 0, S, s.n_ctx, n_sink, sink_idx, st);
+  if (e != hipSuccess) return fail(FOCUS_ELAUNCH, "%s(top-N): %s", who, hipGetErrorString(e));
+  return FOCUS_OK;
 }
 
 struct LayerWs {
@@ -445,7 +466,6 @@ int focus_find_sinks(const void* Q, const int32_t* active_idx, const int32_t* co
   float* part_ml = reinterpret_cast<float*>(ws + w.part_ml);
   float* lse2 = reinterpret_cast<float*>(ws + w.lse2);
   float* S = col_mass ? col_mass : reinterpret_cast<float*>(ws + w.col_mass);
-  const int L = shape->n_ctx + shape->n_resp;
   const bool two_pass = sinks_two_pass(p);
   hipError_t e = launch_qk_logits(Q, active_idx, counts, max_active, K, *shape, p, two_pass ? 1 : 0, logits, part_ml, nullptr,
                                   nullptr, st);
@@ -456,24 +476,9 @@ int focus_find_sinks(const void* Q, const int32_t* active_idx, const int32_t* co
     e = launch_qk_logits(Q, active_idx, counts, max_active, K, *shape, p, 2, nullptr, nullptr, lse2, logits, st);
     if (e != hipSuccess) return launch_fail("focus_find_sinks(column sums)", e);
   }
-  // few sinks: the column-mass groups nominate, one small workgroup decides; many sinks: radix select over all of S
-  const bool tournament = sink_tournament_fits(shape->n_ctx, n_sink);
-  const bool prefilter = !tournament && sink_prefilter_fits(shape->n_ctx, n_sink, S);
-  int32_t* cand = (tournament || prefilter) ? reinterpret_cast<int32_t*>(ws + w.cand) : nullptr;
-  uint32_t* cand_keys = reinterpret_cast<uint32_t*>(ws + w.cand) + kTournamentMaxCand;
-  e = launch_column_mass(logits, two_pass, lse2, counts, max_active, two_pass ? p.q_groups * shape->n_heads : shape->n_heads,
-                         shape->n_heads, L, S, shape->n_ctx, prefilter ? kPrefilterNominees : n_sink, cand, cand ? cand_keys : nullptr, st);
-  if (e != hipSuccess) return launch_fail("focus_find_sinks(column mass)", e);
-  if (tournament) {
-    e = launch_sink_final(cand, cand_keys, shape->n_ctx, n_sink, sink_idx, st);
-    if (e != hipSuccess) return launch_fail("focus_find_sinks(top-N, tournament)", e);
-  } else if (prefilter) {
-    e = launch_sink_select(S, cand_keys, shape->n_ctx, n_sink, sink_idx, st);
-    if (e != hipSuccess) return launch_fail("focus_find_sinks(top-N, bound and select)", e);
-  } else if (n_sink > 0) {
-    e = launch_reduce_topk(nullptr, 0, nullptr, 0, S, shape->n_ctx, n_sink, sink_idx, st);
-    if (e != hipSuccess) return launch_fail("focus_find_sinks(top-N)", e);
-  }
+  if (int rc = column_mass_and_sinks("focus_find_sinks", logits, two_pass, lse2, counts, max_active, p.q_groups, *shape, n_sink, S, ws + w.cand,
+                                     sink_idx, st))
+    return rc;
   return FOCUS_OK;
 }
 
@@ -565,7 +570,6 @@ int focus_probe_layer(const void* Q, const int32_t* active_idx, const int32_t* c
   float* lse2 = reinterpret_cast<float*>(ws + w.lse2);
   float* scratch = reinterpret_cast<float*>(ws + w.scratch);
   float* S = col_mass ? col_mass : reinterpret_cast<float*>(ws + w.col_mass);
-  const int L = shape->n_ctx + shape->n_resp;
   const bool two_pass = sinks_two_pass(pa);
   // dense attention of the active queries over all keys; with at most 16 queries its QK^T products are kept
   DenseProbe probe;
@@ -579,23 +583,9 @@ int focus_probe_layer(const void* Q, const int32_t* active_idx, const int32_t* c
     e = launch_qk_logits(Q, active_idx, counts, max_active, K, *shape, pl, 2, nullptr, nullptr, lse2, scratch, st);
     if (e != hipSuccess) return launch_fail("focus_probe_layer(column sums)", e);
   }
-  const bool tournament = sink_tournament_fits(shape->n_ctx, n_sink);
-  const bool prefilter = !tournament && sink_prefilter_fits(shape->n_ctx, n_sink, S);
-  int32_t* cand = (tournament || prefilter) ? reinterpret_cast<int32_t*>(ws + w.cand) : nullptr;
-  uint32_t* cand_keys = reinterpret_cast<uint32_t*>(ws + w.cand) + kTournamentMaxCand;
-  e = launch_column_mass(scratch, two_pass, lse2, counts, max_active, two_pass ? pl.q_groups * shape->n_heads : shape->n_heads,
-                         shape->n_heads, L, S, shape->n_ctx, prefilter ? kPrefilterNominees : n_sink, cand, cand ? cand_keys : nullptr, st);
-  if (e != hipSuccess) return launch_fail("focus_probe_layer(column mass)", e);
-  if (tournament) {
-    e = launch_sink_final(cand, cand_keys, shape->n_ctx, n_sink, sink_idx, st);
-    if (e != hipSuccess) return launch_fail("focus_probe_layer(top-N, tournament)", e);
-  } else if (prefilter) {
-    e = launch_sink_select(S, cand_keys, shape->n_ctx, n_sink, sink_idx, st);
-    if (e != hipSuccess) return launch_fail("focus_probe_layer(top-N, bound and select)", e);
-  } else if (n_sink > 0) {
-    e = launch_reduce_topk(nullptr, 0, nullptr, 0, S, shape->n_ctx, n_sink, sink_idx, st);
-    if (e != hipSuccess) return launch_fail("focus_probe_layer(top-N)", e);
-  }
+  if (int rc = column_mass_and_sinks("focus_probe_layer", scratch, two_pass, lse2, counts, max_active, pl.q_groups, *shape, n_sink, S,
+                                     ws + w.cand, sink_idx, st))
+    return rc;
   return FOCUS_OK;
 }
 

@@ -67,6 +67,24 @@ __device__ __forceinline__ float row_sum16(float x) {
   return x;
 }
 
+// op over the 16 lanes of a DPP row / over the wavefront (op commutative and associative); every lane receives the result
+template <class Op>
+__device__ __forceinline__ uint32_t row_reduce_u32(uint32_t x, const Op op) {
+  x = op(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xB1, 0xF, 0xF, false));   // quad_perm [1,0,3,2]
+  x = op(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x4E, 0xF, 0xF, false));   // quad_perm [2,3,0,1]
+  x = op(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x141, 0xF, 0xF, false));  // row_half_mirror
+  return op(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x140, 0xF, 0xF, false));  // row_mirror
+}
+template <class Op>
+__device__ __forceinline__ uint32_t wave_reduce_u32(uint32_t x, const Op op) {
+  typedef unsigned v2u __attribute__((ext_vector_type(2)));
+  x = row_reduce_u32(x, op);
+  const v2u a = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+  x = op(a.x, a.y);
+  const v2u b = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+  return op(b.x, b.y);
+}
+
 // Workgroup exclusive scan of one uint32 per thread.  `wsum` is shared memory of at least
 // blockDim/64 + 1 words.  Returns the exclusive prefix; *total gets the sum over the workgroup.
 // Contains two barriers: every thread of the workgroup must call it.

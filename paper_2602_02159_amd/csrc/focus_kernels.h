@@ -57,20 +57,21 @@ hipError_t launch_lse_combine(const float* part_ml, int H, int q_pad, int n_spli
 // Top-N_sink, one more workgroup ranks the nominees.  Limits of that path:
 constexpr int kTournamentMaxSinks = 16;
 constexpr int kTournamentMaxCand = 4096;  // ceil(M / 128) * n_sink
+constexpr int kMaxNominees = 16384;       // of any path: what the workspaces hold
 bool sink_tournament_fits(int M, int n_sink);
-// cand: nullptr, or int32[ceil(M / 128) * n_sink] that receives the nominees (requires sink_tournament_fits);
+// cand: nullptr, or int32[ceil(M / 128) * n_sink] that receives the nominees (n_sink: nominees per group);
 // cand_keys: uint32 of the same size that receives their order keys + 1 (0 where cand holds -1); required with cand.
 // pre_reduced = false: src = scaled logits [H, ceil(L / 4), 16, 4] of at most 16 queries (written by the MFMA kernels), n_parts = H;
 // pre_reduced = true:  src = column sums [n_parts, L] from the second pass over K.
 hipError_t launch_column_mass(const float* src, bool pre_reduced, const float* lse2, const int32_t* counts, int max_active,
                               int n_parts, int H, int L, float* col_mass, int M, int n_sink, int32_t* cand, uint32_t* cand_keys,
                               hipStream_t st);
-// Many sinks (N_sink > 16, n_ctx <= 32768, N_sink <= 1.4 per 128-key group): the groups nominate kPrefilterNominees each, the
-// N_sink-th largest nominee bounds the answer from below, and the exact selection runs over what clears the bound.
-constexpr int kPrefilterNominees = 2;
-bool sink_prefilter_fits(int M, int n_sink, const float* col_mass);
-hipError_t launch_sink_select(const float* col_mass, const uint32_t* cand_keys, int M, int n_sink, int32_t* sink_idx,
-                              hipStream_t st);
+// Many sinks, or few in a long prompt (n_ctx <= 131072): the groups nominate min(kRankNominees, N_sink) each, one workgroup ranks
+// them and falls back to all positions if a group may hold more.  No requirement on the alignment of col_mass.
+constexpr int kRankNominees = 16;
+bool sink_rank_fits(int M, int n_sink);
+hipError_t launch_sink_rank(const int32_t* cand, const uint32_t* cand_keys, int M, int n_sink, const float* col_mass, int32_t* sink_idx,
+                            hipStream_t st);
 hipError_t launch_sink_final(const int32_t* cand, const uint32_t* cand_keys, int M, int n_sink, int32_t* sink_idx,
                              hipStream_t st);
 

@@ -561,7 +561,7 @@ bool sink_tournament_fits(int M, int n_sink) {
 hipError_t launch_column_mass(const float* src, bool pre_reduced, const float* lse2, const int32_t* counts, int max_active,
                               int n_parts, int H, int L, float* col_mass, int M, int n_sink, int32_t* cand, uint32_t* cand_keys,
                               hipStream_t st) {
-  if (cand != nullptr && !sink_tournament_fits(M, n_sink)) return hipErrorInvalidValue;  // n_sink: nominees per group
+  if (cand != nullptr && (n_sink < 1 || n_sink > kMaxNominees / ceil_div(M, kMassKeys))) return hipErrorInvalidValue;  // n_sink: nominees per group
   if (!pre_reduced && n_parts < 1) return hipErrorInvalidValue;
   if (pre_reduced)
     hipLaunchKernelGGL(column_mass_kernel<true>, dim3(ceil_div(L, kMassKeys)), dim3(512), 0, st, src, lse2, counts,
@@ -572,134 +572,220 @@ hipError_t launch_column_mass(const float* src, bool pre_reduced, const float* l
   return hipGetLastError();
 }
 
-// Top-N_sink beyond the tournament's limit (the paper's 1 % rule asks for hundreds of sinks), n = M <= 32768.
-// The column-mass kernel has nominated the two largest masses of every 128-key group.  The N_sink-th largest nominee
-// is a lower bound of the N_sink-th largest mass — that many positions are at least as large — so only positions
-// that reach it can be sinks: usually several hundred of the 32 768.  They are compacted in index order into LDS and
-// one wavefront selects the exact Top-N_sink among them (same total order, same tie rule, ascending output).  Only
-// if more than 1024 positions clear the bound (flat column masses) does the kernel fall back to the radix select
-// over all of them.  The bound only has to be valid, not tight: its search stops at bit kBoundLowBit and skips the bits
-// all nominees share.  Every thread keeps its run of 32 keys in registers; those loads and the load of the nominees'
-// keys (written by the column-mass kernel, one per thread) are in flight together.  col_mass must be 16-byte aligned.
-constexpr int kBoundLowBit = 10;
-__global__ __launch_bounds__(kTopkThreads) void sink_select_kernel(const float* __restrict__ col_mass,
-                                                                   const uint32_t* __restrict__ cand_keys, int n_cand, int M,
-                                                                   int n_sink, int32_t* __restrict__ sink_idx) {
-  __shared__ TopkShared sm;
-  __shared__ uint32_t cidx[kTopkThreads];
-  __shared__ uint32_t bound_sh;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int chunk = (((M + kTopkThreads - 1) / kTopkThreads) + 3) & ~3;  // <= kTopkRegKeys (launcher)
-  const int c0 = min(tid * chunk, M), c1 = min(c0 + chunk, M);
-  const uint32_t nominee = tid < n_cand ? cand_keys[tid] : 0u;  // key + 1 of a nominee, 0 = none; n_cand <= 512
-  float4 v[kTopkRegKeys / 4];
+// Top-N_sink beyond the tournament's limits (the paper's 1 % rule asks for hundreds of sinks), M <= 131072.  The column-mass
+// kernel has nominated the kRankNominees largest masses of every 128-key group (n_per = min(kRankNominees, N_sink)), in
+// ascending order of position.  One workgroup holds all nominees in registers, KPL consecutive ones per thread, and finds the
+// N_sink-th largest key two bits at a time: every wavefront counts its own keys against three thresholds with ballots, the
+// sixteen counts meet in LDS.  The bits all keys share are skipped, and the search ends as soon as exactly N_sink keys reach a
+// threshold.  Unless a group has all its nominees selected (its other keys might then belong to the answer too) that is the
+// exact Top-N_sink.  Otherwise the key found is a lower bound of the true one, and the positions that reach it, compacted in
+// index order into LDS, are ranked the same way; only if they do not fit a radix select over all positions decides.
+// 32768 keys, 327 sinks: 8 us (bounding, compacting and ranking all positions in one workgroup took 18); 131072 keys, 1310
+// sinks: 12 us (radix select: 390 us).
+template <int KPL>
+__global__ __launch_bounds__(kTopkThreads) void sink_rank_kernel(const int32_t* __restrict__ cand, const uint32_t* __restrict__ cand_keys,
+                                                                 int n_cand, int n_per, int M, int n_sink,
+                                                                 const float* __restrict__ col_mass, int32_t* __restrict__ sink_idx) {
+  constexpr int kWaves = kTopkThreads / kWave, kCap = kTopkThreads * KPL;
+  __shared__ __attribute__((aligned(16))) uint32_t keys_sh[kCap];  // positions that clear the bound: key + 1 ...
+  __shared__ __attribute__((aligned(16))) int32_t idx_sh[kCap];    // ... and index
+  __shared__ __attribute__((aligned(16))) uint32_t count_sh[2][kWaves][4];  // by round parity, wavefront, threshold
+  __shared__ uint32_t bits_sh[kWaves][2], valid_sh[kWaves], sel_sh[kWaves][2];
+  __shared__ int overflow_sh;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const unsigned long long below = (1ull << lane) - 1ull;
+  auto add = [](uint32_t a, uint32_t b) { return a + b; };
+  const int i0 = tid * KPL;
+  uint32_t kv[KPL];  // key + 1; 0 = none
+  int32_t pos[KPL];
+  auto load = [&](const uint32_t* keys, const int32_t* idx, int n) __attribute__((always_inline)) {  // whole vectors may be read past n: both buffers hold kCap entries at least
 #pragma unroll
-  for (int r4 = 0; r4 < kTopkRegKeys / 4; ++r4) {
-    const int i = c0 + 4 * r4;
-    v[r4] = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (i + 3 < c1) {
-      v[r4] = *reinterpret_cast<const float4*>(col_mass + i);
-    } else {
-      if (i < c1) v[r4].x = col_mass[i];
-      if (i + 1 < c1) v[r4].y = col_mass[i + 1];
-      if (i + 2 < c1) v[r4].z = col_mass[i + 2];
-    }
-  }
-  sm.keys[tid] = nominee;
-  uint32_t rk[kTopkRegKeys];  // key + 1, 0 = no such position
-#pragma unroll
-  for (int r4 = 0; r4 < kTopkRegKeys / 4; ++r4) {
-    const int i = c0 + 4 * r4;
-    rk[4 * r4] = i < c1 ? order_key(v[r4].x) + 1u : 0u;
-    rk[4 * r4 + 1] = i + 1 < c1 ? order_key(v[r4].y) + 1u : 0u;
-    rk[4 * r4 + 2] = i + 2 < c1 ? order_key(v[r4].z) + 1u : 0u;
-    rk[4 * r4 + 3] = i + 3 < c1 ? order_key(v[r4].w) + 1u : 0u;
-  }
-  __syncthreads();
-  if (tid < kWave) {  // a lower bound of the N_sink-th largest nominee key: bitwise search over ballot counts, 8 nominees per lane
-    uint32_t kv[8];
-    const uint4 k0 = reinterpret_cast<const uint4*>(sm.keys)[lane * 2], k1 = reinterpret_cast<const uint4*>(sm.keys)[lane * 2 + 1];
-    kv[0] = k0.x; kv[1] = k0.y; kv[2] = k0.z; kv[3] = k0.w;
-    kv[4] = k1.x; kv[5] = k1.y; kv[6] = k1.z; kv[7] = k1.w;
-    uint32_t nvalid = 0, a = 0xffffffffu, o = 0u;
-#pragma unroll
-    for (int r = 0; r < 8; ++r) {
-      nvalid += (uint32_t)__popcll(__ballot(kv[r] != 0u));
-      a &= kv[r] != 0u ? kv[r] : 0xffffffffu;
-      o |= kv[r];
+    for (int r4 = 0; r4 < KPL / 4; ++r4) {
+      const uint4 a = *reinterpret_cast<const uint4*>(keys + i0 + 4 * r4);
+      const int4 b = *reinterpret_cast<const int4*>(idx + i0 + 4 * r4);
+      kv[4 * r4] = a.x; kv[4 * r4 + 1] = a.y; kv[4 * r4 + 2] = a.z; kv[4 * r4 + 3] = a.w;
+      pos[4 * r4] = b.x; pos[4 * r4 + 1] = b.y; pos[4 * r4 + 2] = b.z; pos[4 * r4 + 3] = b.w;
     }
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-      a &= __shfl_xor(a, off, kWave);
-      o |= __shfl_xor(o, off, kWave);
+    for (int r = 0; r < KPL; ++r) kv[r] = i0 + r < n ? kv[r] : 0u;
+  };
+  load(cand_keys, cand, n_cand);
+  if (tid == 0) overflow_sh = 0;
+  for (int pass = 0;; ++pass) {  // the nominees; then, if need be, every position that clears the bound
+    uint32_t all = 0xffffffffu, any = 0u, n_mine = 0;
+#pragma unroll
+    for (int r = 0; r < KPL; ++r) {
+      all &= kv[r] != 0u ? kv[r] : 0xffffffffu;
+      any |= kv[r];
+      n_mine += (uint32_t)__popcll(__ballot(kv[r] != 0u));
     }
-    uint32_t T = 1u;  // fewer nominees than sinks asked for: every position is a candidate
-    if (nvalid >= (uint32_t)n_sink) {
-      const uint32_t same = ~(a ^ o);
-      T = 0u;
-      for (int bit = 31; bit >= kBoundLowBit; --bit) {
-        if ((same >> bit) & 1u) {
-          T |= a & (1u << bit);
-          continue;
-        }
-        const uint32_t c = T | (1u << bit);
-        uint32_t cnt = 0;
-#pragma unroll
-        for (int r = 0; r < 8; ++r) cnt += (uint32_t)__popcll(__ballot(kv[r] >= c));
-        if (cnt >= (uint32_t)n_sink) T = c;
-      }
-    }
-    if (lane == 0) bound_sh = max(T, 1u);
-  }
-  __syncthreads();
-  const uint32_t bound = bound_sh;
-  uint32_t mine = 0;
-#pragma unroll
-  for (int r = 0; r < kTopkRegKeys; ++r) mine += rk[r] >= bound;
-  uint32_t n_clear;
-  uint32_t pos = block_exclusive_scan(mine, sm.wsum, &n_clear);
-  if (n_clear <= (uint32_t)kTopkThreads) {  // uniform
-    if (tid >= (int)n_clear) sm.keys[tid] = 0u;  // the nominee keys are no longer needed (everyone passed the scan's barriers)
-#pragma unroll
-    for (int r = 0; r < kTopkRegKeys; ++r) {
-      if (rk[r] >= bound) {
-        sm.keys[pos] = rk[r];
-        cidx[pos] = (uint32_t)(c0 + r);
-        ++pos;
-      }
+    all = wave_reduce_u32(all, [](uint32_t a, uint32_t b) { return a & b; });
+    any = wave_reduce_u32(any, [](uint32_t a, uint32_t b) { return a | b; });
+    if (lane == 0) {
+      bits_sh[wave][0] = all;
+      bits_sh[wave][1] = any;
+      valid_sh[wave] = n_mine;
     }
     __syncthreads();
-    if (tid < kWave) {
-      if (n_clear <= 256u)
-        wave_topk<4, true>(sm.keys, (int)n_clear, n_sink, sink_idx, nullptr, &sm.prefix, 0, cidx);
-      else if (n_clear <= 512u)
-        wave_topk<8, true>(sm.keys, (int)n_clear, n_sink, sink_idx, nullptr, &sm.prefix, 0, cidx);
-      else
-        wave_topk<16, true>(sm.keys, (int)n_clear, n_sink, sink_idx, nullptr, &sm.prefix, 0, cidx);
+    uint32_t n_valid = 0;
+    all = 0xffffffffu;
+    any = 0u;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+      all &= bits_sh[w][0];
+      any |= bits_sh[w][1];
+      n_valid += valid_sh[w];
     }
-    return;
+    const uint32_t k = min((uint32_t)n_sink, n_valid);
+    uint32_t T = 0u;  // the k-th largest key, or one less than a threshold that exactly k keys reach; 0: all of them
+    if (k < n_valid) {
+      const int top = 31 - (int)__clz((int)(all ^ any));  // -1: all keys are equal
+      T = top < 0 ? all : (top == 31 ? 0u : all & ~((2u << top) - 1u));
+      for (int hi = top, parity = 0; hi >= 0; hi -= 2, parity ^= 1) {  // bits hi and hi - 1 (bit 0 alone in the last round of an odd count)
+        const uint32_t step = hi > 0 ? 1u << (hi - 1) : 1u;
+        uint32_t c1 = 0, c2 = 0, c3 = 0;
+#pragma unroll
+        for (int r = 0; r < KPL; ++r) {
+          c1 += (uint32_t)__popcll(__ballot(kv[r] >= (T | step)));
+          c2 += (uint32_t)__popcll(__ballot(kv[r] >= (T | (2u * step))));
+          c3 += (uint32_t)__popcll(__ballot(kv[r] >= (T | (3u * step))));
+        }
+        if (lane == 0) *reinterpret_cast<uint4*>(count_sh[parity][wave]) = make_uint4(c1, c2, c3, 0u);
+        __syncthreads();  // (the other parity's counts may still be read by slower wavefronts)
+        const uint4 row = *reinterpret_cast<const uint4*>(count_sh[parity][lane & (kWaves - 1)]);
+        const uint32_t s1 = row_reduce_u32(row.x, add), s2 = row_reduce_u32(row.y, add), s3 = row_reduce_u32(row.z, add);
+        uint32_t j = 0, cnt = 0;  // the largest threshold that at least k keys reach
+        if (s1 >= k) { j = 1; cnt = s1; }
+        if (hi > 0 && s2 >= k) { j = 2; cnt = s2; }
+        if (hi > 0 && s3 >= k) { j = 3; cnt = s3; }
+        T |= j * step;
+        if (cnt == k) {  // exactly these: "key > T" selects them and none equal to T is needed (k > 0)
+          T -= 1u;
+          break;
+        }
+      }
+    }
+    // selection in ascending order: everything above T, and the first keys equal to T until k are reached
+    uint32_t n_gt = 0, n_eq = 0, eq_before = 0;
+#pragma unroll
+    for (int r = 0; r < KPL; ++r) {
+      const unsigned long long eq = __ballot(kv[r] == T && kv[r] != 0u);
+      n_gt += (uint32_t)__popcll(__ballot(kv[r] > T));
+      n_eq += (uint32_t)__popcll(eq);
+      eq_before += (uint32_t)__popcll(eq & below);
+    }
+    if (lane == 0) {
+      sel_sh[wave][0] = n_gt;
+      sel_sh[wave][1] = n_eq;
+    }
+    __syncthreads();
+    uint32_t gt_total = 0, gt_base = 0, eq_base = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+      gt_total += sel_sh[w][0];
+      if (w < wave) {
+        gt_base += sel_sh[w][0];
+        eq_base += sel_sh[w][1];
+      }
+    }
+    const uint32_t need = k - min(gt_total, k);
+    bool sel[KPL];
+    uint32_t n_sel = 0, eq_rank = eq_base + eq_before;
+#pragma unroll
+    for (int r = 0; r < KPL; ++r) {
+      const bool eq = kv[r] == T && kv[r] != 0u;
+      sel[r] = kv[r] > T || (eq && eq_rank < need);
+      eq_rank += eq;
+      n_sel += sel[r];
+    }
+    // a group with all its nominees selected: n_per = kRankNominees of them, kRankNominees / KPL neighbouring lanes
+    if (pass == 0 && n_per == kRankNominees) {
+      unsigned long long full = __ballot(n_sel == (uint32_t)KPL);
+#pragma unroll
+      for (int w = 1; w < kRankNominees / KPL; w <<= 1) full &= full >> w;
+      constexpr unsigned long long kFirst = KPL == 16 ? ~0ull : (KPL == 8 ? 0x5555555555555555ull : 0x1111111111111111ull);
+      if ((full & kFirst) != 0ull && lane == 0) overflow_sh = 1;
+    }
+    uint32_t out = gt_base + min(eq_base, need);
+#pragma unroll
+    for (int r = 0; r < KPL; ++r) out += (uint32_t)__popcll(__ballot(sel[r]) & below);
+#pragma unroll
+    for (int r = 0; r < KPL; ++r)
+      if (sel[r]) sink_idx[out++] = pos[r];
+    for (int i = (int)k + tid; i < n_sink; i += kTopkThreads) sink_idx[i] = -1;
+    if (pass == 1) return;
+    __syncthreads();
+    if (!overflow_sh) return;  // uniform
+
+    // ---- some group may hold more: every position whose key reaches the bound (at least N_sink do).  Wavefront w walks the
+    // run [w * run, (w + 1) * run) in steps of 64 positions, 32 loads in flight: once to count, once to write.
+    const uint32_t bound = max(gt_total >= k ? T + 1u : T, 1u);
+    // (compared as floats: the order of the keys is the order of the numbers; a bound of 1 lets NaN pass as well)
+    const float bound_f = order_value(bound - 1u);
+    const bool everything = bound == 1u;
+    const int run = (M + kWaves - 1) / kWaves;
+    const int r0 = min(wave * run, M), r1 = min(r0 + run, M);
+    auto walk = [&](auto f) {
+      for (int i = r0 + lane; i - lane < r1; i += 32 * kWave) {
+        float v[32];
+#pragma unroll
+        for (int u = 0; u < 32; ++u) v[u] = col_mass[min(i + kWave * u, M - 1)];
+#pragma unroll
+        for (int u = 0; u < 32; ++u) {
+          f(i + kWave * u, v[u], __ballot(i + kWave * u < r1 && (v[u] >= bound_f || everything)));
+        }
+      }
+    };
+    uint32_t n_run = 0;
+    walk([&](int, float, unsigned long long hit) { n_run += (uint32_t)__popcll(hit); });
+    if (lane == 0) valid_sh[wave] = n_run;
+    __syncthreads();
+    uint32_t n_clear = 0, at = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+      n_clear += valid_sh[w];
+      if (w < wave) at += valid_sh[w];
+    }
+    if (n_clear > (uint32_t)kCap) break;  // uniform
+    walk([&](int i, float x, unsigned long long hit) {
+      if ((hit >> lane) & 1ull) {
+        const uint32_t dst = at + (uint32_t)__popcll(hit & below);
+        keys_sh[dst] = order_key(x) + 1u;
+        idx_sh[dst] = i;
+      }
+      at += (uint32_t)__popcll(hit);
+    });
+    __syncthreads();
+    load(keys_sh, idx_sh, (int)n_clear);
   }
+  // more positions than the workgroup holds clear the bound
+  TopkShared& sm = *reinterpret_cast<TopkShared*>(keys_sh);
+  static_assert(sizeof(TopkShared) <= sizeof(keys_sh), "the radix select's shared memory fits");
+  __syncthreads();
   auto keyfn = [=](int i, uint32_t& key) -> bool {
     key = order_key(col_mass[i]);
     return true;
   };
-  block_topk(keyfn, M, n_sink, sink_idx, nullptr, nullptr, sm, col_mass);
+  block_topk(keyfn, M, n_sink, sink_idx, nullptr, nullptr, sm, (reinterpret_cast<uintptr_t>(col_mass) & 15u) == 0 ? col_mass : nullptr);
 }
 
-// the bound-then-select path: more sinks than the tournament takes, a run of at most 32 keys per thread, and at most
-// 1.4 sinks per 128-key group (the paper's 1 % rule asks for 1.28): with two nominees per group the bound is then the
-// 0.7 quantile of the nominees or higher — closer to their minimum it lets too many positions through and the kernel
-// would pay for the bound and for the radix select
-bool sink_prefilter_fits(int M, int n_sink, const float* col_mass) {
-  return n_sink > kTournamentMaxSinks && M <= kTopkThreads * kTopkRegKeys && 10 * n_sink <= 14 * (M / kMassKeys) &&
-         (reinterpret_cast<uintptr_t>(col_mass) & 15u) == 0;
+// At most four sinks per 128-key group on average: more would often fill a group's nominees.  Up to 1024 positions one wavefront
+// ranks all of them sooner.
+bool sink_rank_fits(int M, int n_sink) {
+  const int groups = ceil_div(M, kMassKeys);
+  return n_sink >= 1 && M > kTopkThreads && groups * kRankNominees <= kMaxNominees && n_sink <= 4 * groups;
 }
 
-hipError_t launch_sink_select(const float* col_mass, const uint32_t* cand_keys, int M, int n_sink, int32_t* sink_idx,
-                              hipStream_t st) {
-  if (!sink_prefilter_fits(M, n_sink, col_mass)) return hipErrorInvalidValue;
-  const int n_cand = ceil_div(M, kMassKeys) * kPrefilterNominees;  // <= 512
-  hipLaunchKernelGGL(sink_select_kernel, dim3(1), dim3(kTopkThreads), 0, st, col_mass, cand_keys, n_cand, M, n_sink, sink_idx);
+hipError_t launch_sink_rank(const int32_t* cand, const uint32_t* cand_keys, int M, int n_sink, const float* col_mass, int32_t* sink_idx,
+                            hipStream_t st) {
+  if (!sink_rank_fits(M, n_sink)) return hipErrorInvalidValue;
+  const int n_per = std::min(kRankNominees, n_sink), n_cand = ceil_div(M, kMassKeys) * n_per;
+  if (n_cand <= 4 * kTopkThreads)
+    hipLaunchKernelGGL(sink_rank_kernel<4>, dim3(1), dim3(kTopkThreads), 0, st, cand, cand_keys, n_cand, n_per, M, n_sink, col_mass, sink_idx);
+  else if (n_cand <= 8 * kTopkThreads)
+    hipLaunchKernelGGL(sink_rank_kernel<8>, dim3(1), dim3(kTopkThreads), 0, st, cand, cand_keys, n_cand, n_per, M, n_sink, col_mass, sink_idx);
+  else
+    hipLaunchKernelGGL(sink_rank_kernel<16>, dim3(1), dim3(kTopkThreads), 0, st, cand, cand_keys, n_cand, n_per, M, n_sink, col_mass, sink_idx);
   return hipGetLastError();
 }
 

@@ -32,6 +32,11 @@ __device__ __forceinline__ uint32_t order_key(float x) {
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
+// the number whose order_key is `key` (key > 0)
+__device__ __forceinline__ float order_value(uint32_t key) {
+  return __uint_as_float((key & 0x80000000u) ? key & 0x7fffffffu : ~key);
+}
+
 // sum over the n_parts per-head partial values of element j, always part by part in ascending order (the loads go out 32, then
 // 8, then 1 at a time) so that every kernel that assembles block relevances gets bit-identical results; continues from part h
 // with the sum acc of the parts before it

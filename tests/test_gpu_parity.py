@@ -207,6 +207,28 @@ def test_find_sinks_selection_is_exact_with_many_exact_ties(G, M, N, n_sink):
     assert np.allclose(S, Sref, rtol=2e-4, atol=1e-9)
 
 
+@pytest.mark.parametrize("M,N,n_sink,n_cluster", [
+    (20000, 10, 200, 0),       # nominees of the 128-key groups suffice
+    (20000, 10, 200, 16),      # one group has exactly as many as it may nominate
+    (20000, 10, 200, 60),      # ... and many more: all positions that clear the bound
+    (32768, 64, 1000, 900),    # seven whole groups
+    (40000, 0, 1250, 1200),    # more than a workgroup ranks at once: radix select
+    (131072, 0, 16, 16),       # few sinks, too many groups for the tournament
+    (70001, 3, 700, 100),      # past 32768 positions, a ragged last group
+    (131072, 0, 1310, 3),
+    (300, 20, 9, 9),           # three groups
+])
+def test_find_sinks_that_cluster(G, M, N, n_sink, n_cluster):
+    """Sinks side by side fill the nominees of their 128-key groups; the answer must not depend on where they sit."""
+    H, d, n_gen = 2, 64, 16
+    q, k = _rand_bf16(51, H, n_gen, d), _rand_bf16(52, H, M + N, d)
+    u = q.float().mean(1, keepdim=True)
+    first = (M // 2 // 128) * 128 if M > 4096 else 100
+    k[:, first:first + n_cluster] += (6.0 * u / u.norm(dim=-1, keepdim=True)).to(torch.bfloat16)
+    col, sinks = G.gpu_find_sinks(q.to(G.DEV), G.i32([0, 2, 7]), None, k.to(G.DEV), M, 64, n_sink)
+    assert sinks.cpu().tolist() == fo.select_sinks(col.cpu().numpy().astype(np.float64), M, n_sink).tolist()
+
+
 def test_find_sinks_many_sinks_with_an_unaligned_score_buffer(G):
     """The bound-then-select path reads the column masses with 16-byte loads; a caller's score buffer that is only
     4-byte aligned takes the radix select instead and must give the same sinks."""
