@@ -85,6 +85,22 @@ __device__ __forceinline__ uint32_t wave_reduce_u32(uint32_t x, const Op op) {
   return op(b.x, b.y);
 }
 
+// Reductions over the 4 lanes with the same lane % 16, via v_permlane32_swap / v_permlane16_swap:
+// swap(x, x) returns {value of the partner in the even half/row, value of the partner in the odd half/row}.
+typedef unsigned uintx2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ float group_max(float v) {
+  uintx2 a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = fmaxf(__uint_as_float(a.x), __uint_as_float(a.y));
+  uintx2 b = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(b.x), __uint_as_float(b.y));
+}
+__device__ __forceinline__ float group_sum(float v) {
+  uintx2 a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(a.x) + __uint_as_float(a.y);
+  uintx2 b = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(b.x) + __uint_as_float(b.y);
+}
+
 // Workgroup exclusive scan of one uint32 per thread.  `wsum` is shared memory of at least
 // blockDim/64 + 1 words.  Returns the exclusive prefix; *total gets the sum over the workgroup.
 // Contains two barriers: every thread of the workgroup must call it.

@@ -16,6 +16,10 @@ constexpr int kQTile = 16;          // queries per MFMA tile
 constexpr int kMaxQTilesPerGroup = 4;
 
 static inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
+// A grid of n_x workgroups in x by n workgroups in y, continued in z: n may exceed the 65535 of one axis.
+constexpr int kGridSlice = 32768;
+static inline dim3 grid_x_yz(int n_x, int n) { return dim3(n_x, n < kGridSlice ? n : kGridSlice, ceil_div(n, kGridSlice)); }
+__device__ __forceinline__ int grid_yz() { return (int)(blockIdx.z * kGridSlice + blockIdx.y); }
 static inline int64_t ceil_div64(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // How the key axis of an MFMA kernel is cut: n_sub sub-tiles per head, n_split workgroups per (head, query group).  The

@@ -300,22 +300,6 @@ __device__ __forceinline__ void qk_subtile(floatx4 (&acc)[NQT][2], const char* s
   }
 }
 
-// Reductions over the 4 lanes that share a query (lane % 16), via v_permlane32_swap / v_permlane16_swap:
-// swap(x, x) returns {value of the partner in the even half/row, value of the partner in the odd half/row}.
-typedef unsigned uintx2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ float group_max(float v) {
-  uintx2 a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  v = fmaxf(__uint_as_float(a.x), __uint_as_float(a.y));
-  uintx2 b = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return fmaxf(__uint_as_float(b.x), __uint_as_float(b.y));
-}
-__device__ __forceinline__ float group_sum(float v) {
-  uintx2 a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  v = __uint_as_float(a.x) + __uint_as_float(a.y);
-  uintx2 b = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return __uint_as_float(b.x) + __uint_as_float(b.y);
-}
-
 // eight fp32 -> eight bf16 (round to nearest even) with v_cvt_pk_bf16_f32
 typedef float floatx2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));

@@ -180,9 +180,10 @@ hipError_t launch_reduce_topk(const float* part, int n_parts, const int32_t* cou
 // variants produce bit-identical partial relevances.
 // =====================================================================================================
 // Sum over the focus queries of Q[h, i, 8c .. 8c+7] for the calling thread's chunk c = t % (D/8).  All 256 threads
-// take part: thread (r, c) adds up the focus rows r, r + RPP, r + 2 RPP, ... (four loads in flight at a time), the
-// per-r sums meet in LDS and every thread then adds them in the order r = 0 .. RPP-1.  `first_row` is
-// focus_idx[r] fetched by the caller ahead of time (any value if r >= n_focus_max); `psum` must be free on entry.
+// take part: thread (r, c) adds up the focus rows r, r + RPP, r + 2 RPP, ... (four loads in flight at a time); the
+// per-r sums meet across the lanes of a wavefront (fixed tree), then the four wavefronts in LDS.  (Every thread adding all
+// RPP per-r sums from LDS read 128 KB of it per workgroup, 0.6 us of the 4.1 us of a relevance launch at 32K.)  `first_row`
+// is focus_idx[r] fetched by the caller ahead of time (any value if r >= n_focus_max); `psum` must be free on entry.
 template <int D>
 __device__ __forceinline__ void focus_row_sum(float (&qs)[8], const uint16_t* __restrict__ qh, int64_t qsn,
                                               const int32_t* __restrict__ focus_idx, int first_row, int n_f, int n_gen,
@@ -205,14 +206,23 @@ __device__ __forceinline__ void focus_row_sum(float (&qs)[8], const uint16_t* __
 #pragma unroll
     for (int u = 0; u < U; ++u) add_bf16x8(acc, v[u]);
   }
-  float4* pw = reinterpret_cast<float4*>(&psum[r][c * 8]);
-  pw[0] = make_float4(acc[0], acc[1], acc[2], acc[3]);
-  pw[1] = make_float4(acc[4], acc[5], acc[6], acc[7]);
+  // the values of r within a wavefront meet across lanes, the four wavefronts in LDS
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    if (CPR == 8)  // lanes 8 apart: a rotation of the DPP row
+      acc[e] += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, acc[e]), 0x128, 0xF, 0xF, false));
+    acc[e] = group_sum(acc[e]);
+  }
+  if ((threadIdx.x & 63) < CPR) {
+    float4* pw = reinterpret_cast<float4*>(&psum[threadIdx.x >> 6][c * 8]);
+    pw[0] = make_float4(acc[0], acc[1], acc[2], acc[3]);
+    pw[1] = make_float4(acc[4], acc[5], acc[6], acc[7]);
+  }
   __syncthreads();
 #pragma unroll
   for (int e = 0; e < 8; ++e) qs[e] = 0.f;
 #pragma unroll
-  for (int i = 0; i < RPP; ++i) {
+  for (int i = 0; i < 4; ++i) {
     const float4* pr = reinterpret_cast<const float4*>(&psum[i][c * 8]);
     const float4 lo = pr[0], hi = pr[1];
     qs[0] += lo.x; qs[1] += lo.y; qs[2] += lo.z; qs[3] += lo.w;
@@ -334,7 +344,9 @@ hipError_t launch_block_means_relevance(const void* K, const void* Q, const int3
 // focus queries of head h; the 1/(|I_focus| H) factor and the sum over heads are applied, in a fixed order,
 // by reduce_topk_kernel.  One workgroup per (group of blocks, head): a thread owns one 8-wide slice of d of
 // one block row.  The focus indices and the kbar loads are issued first, then the focus rows of Q (see
-// focus_row_sum), so the whole kernel is two dependent memory round trips long.
+// focus_row_sum), so the whole kernel is two dependent memory round trips long.  (Requesting all rows of Q beside the focus
+// list, to save one of them, was not faster: the list comes from the L2.)  Heads are the fast grid axis: workgroups go to the
+// XCDs round-robin, so with a multiple of eight heads those of one head share an L2 and with it the focus rows.
 // =====================================================================================================
 template <int D>
 __global__ __launch_bounds__(256) void relevance_partial_kernel(const int32_t* __restrict__ focus_idx,
@@ -345,9 +357,9 @@ __global__ __launch_bounds__(256) void relevance_partial_kernel(const int32_t* _
   constexpr int CPR = D / 8;      // lanes per block row
   constexpr int RPP = 256 / CPR;  // block rows per pass
   constexpr int PASSES = 2;
-  __shared__ __attribute__((aligned(16))) float psum[RPP][D];
+  __shared__ __attribute__((aligned(16))) float psum[4][D];
   const int t = threadIdx.x, c = t % CPR, r = t / CPR;
-  const int h = blockIdx.y, b0 = blockIdx.x * (RPP * PASSES);
+  const int h = blockIdx.x, b0 = grid_yz() * (RPP * PASSES);
   const int first_row = r < n_focus_max ? focus_idx[r] : -1;
   const int n_f = counts ? min(max(counts[0], 0), n_focus_max) : n_focus_max;
   float4 k0[PASSES], k1[PASSES];
@@ -377,10 +389,10 @@ hipError_t launch_block_relevance(const void* Q, const int32_t* focus_idx, const
   const int n_b = ceil_div(s.n_ctx, s.block);
   const uint16_t* q = static_cast<const uint16_t*>(Q);
   if (s.head_dim == 128)
-    hipLaunchKernelGGL(relevance_partial_kernel<128>, dim3(ceil_div(n_b, 32), s.n_heads), dim3(256), 0, st, focus_idx,
+    hipLaunchKernelGGL(relevance_partial_kernel<128>, grid_x_yz(s.n_heads, ceil_div(n_b, 32)), dim3(256), 0, st, focus_idx,
                        kbar, counts, q, s.q_stride_h, s.q_stride_n, n_b, n_focus_max, s.n_gen, part);
   else
-    hipLaunchKernelGGL(relevance_partial_kernel<64>, dim3(ceil_div(n_b, 64), s.n_heads), dim3(256), 0, st, focus_idx,
+    hipLaunchKernelGGL(relevance_partial_kernel<64>, grid_x_yz(s.n_heads, ceil_div(n_b, 64)), dim3(256), 0, st, focus_idx,
                        kbar, counts, q, s.q_stride_h, s.q_stride_n, n_b, n_focus_max, s.n_gen, part);
   return hipGetLastError();
 }
