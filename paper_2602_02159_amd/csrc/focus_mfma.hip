@@ -95,6 +95,8 @@ __device__ __forceinline__ uint32_t low_mask(int n) { return n >= 32 ? 0xfffffff
 //   "listed earlier": a strictly ascending list (what focus_find_sinks writes) cannot repeat an entry; `ascending`
 //   says so (1 / 0, established once by the workgroup), or -1: not known, then a scan of 64 entries per step
 //   establishes it here.  Only lists that are not ascending pay for the all-pairs comparison.
+// A list of at most one sub-tile (n_sink <= 32) costs no memory access here: lane r < n_sink holds its entry r in `few_sinks`
+// (-1 in the other lanes), requested at the start of the kernel.
 constexpr int kBitmapBlocks = 8192;  // largest n_b for which workgroups keep a bitmap of the kept blocks
 // A wave-uniform 4-byte read of global memory that no kernel writes while this one runs, issued as a scalar load: it
 // returns through the scalar cache instead of queueing behind the wavefront's vector loads (which return in order), and
@@ -107,7 +109,7 @@ __device__ __forceinline__ SubTile locate_subtile(int st, int lane, int M, int N
                                                   const int32_t* __restrict__ kept_blocks, int n_keep,
                                                   const int32_t* __restrict__ sink_idx, int n_sink,
                                                   const uint32_t* kept_bits = nullptr, int ascending = -1,
-                                                  int dense_rows = 0, bool blocks_in_lds = false) {
+                                                  int dense_rows = 0, bool blocks_in_lds = false, int few_sinks = -1) {
   SubTile t;
   t.kind = 0;
   t.row0 = 0;
@@ -141,7 +143,9 @@ __device__ __forceinline__ SubTile locate_subtile(int st, int lane, int M, int N
   t.kind = 1;
   t.row0 = st * kSubTile;
   const int e = t.row0 + lane;
-  const int mine = (lane < kSubTile && e < n_sink) ? sink_idx[e] : -1;
+  const bool few = n_sink <= kSubTile;  // the list is one sub-tile, which the caller holds in registers
+  const int mine = few ? few_sinks : ((lane < kSubTile && e < n_sink) ? sink_idx[e] : -1);
+  const int n_slots = min(n_sink - t.row0, kSubTile);
   const bool in_prompt = mine >= 0 && mine < M;
   const int my_block = in_prompt ? mine / B : -1;
   uint32_t bad = 0u;
@@ -151,14 +155,21 @@ __device__ __forceinline__ SubTile locate_subtile(int st, int lane, int M, int N
   } else {
     for (int j0 = 0; j0 < n_keep; j0 += kWave) {
       const int v = j0 + lane < n_keep ? kept_blocks[j0 + lane] : -2;
-#pragma unroll 4
-      for (int r = 0; r < kSubTile; ++r) {
-        const int sb = __shfl(my_block, r, kWave);
+      for (int r = 0; r < n_slots; ++r) {
+        const int sb = __builtin_amdgcn_readlane(my_block, r);
         if (__ballot(v == sb) != 0ull) bad |= 1u << r;
       }
     }
   }
   const int e_end = min(t.row0 + kSubTile, n_sink);
+  if (few) {
+    const int before = __shfl_up(mine, 1, kWave);
+    ascending = 1;
+    if (__ballot(lane > 0 && lane < n_sink && mine <= before) != 0ull) {
+      for (int r = 1; r < n_slots; ++r)
+        if (__ballot(mine == __builtin_amdgcn_readlane(mine, r) && lane < r) != 0ull) bad |= 1u << r;
+    }
+  }
   if (ascending < 0) {  // sink_idx[0 .. e_end) strictly ascending?
     ascending = 1;
     for (int j0 = 0; j0 + 1 < e_end; j0 += kWave) {
@@ -172,9 +183,8 @@ __device__ __forceinline__ SubTile locate_subtile(int st, int lane, int M, int N
     for (int j0 = 0; j0 < e_end; j0 += kWave) {
       const int idx = j0 + lane;
       const int v = idx < e_end ? sink_idx[idx] : -2;
-#pragma unroll 4
-      for (int r = 0; r < kSubTile; ++r) {
-        const int s = __shfl(mine, r, kWave);
+      for (int r = 0; r < n_slots; ++r) {
+        const int s = __builtin_amdgcn_readlane(mine, r);
         if (__ballot(v == s && idx < t.row0 + r) != 0ull) bad |= 1u << r;
       }
     }
@@ -493,7 +503,11 @@ __device__ __forceinline__ void rank_blocks(const AttnArgs& p, const float (&fir
 }
 
 // Workgroups whose key range reaches the sink sub-tiles prepare the union of Eq. 8 once: a bitmap of the kept blocks, and
-// whether the sink list is strictly ascending (then it cannot name a position twice).
+// whether the sink list is strictly ascending (then it cannot name a position twice).  A list of one sub-tile needs neither: its
+// wavefront holds it in registers (few_sinks; three memory round trips behind the Top-C became none, 1 us of the 32K layer).
+__device__ __forceinline__ int request_few_sinks(const AttnArgs& p, int lane) {
+  return p.n_sink <= kSubTile && lane < p.n_sink && p.dense_rows == 0 ? p.sink_idx[lane] : -1;
+}
 struct SinkUnion {
   const uint32_t* kept_bits;  // see locate_subtile; null when there is none
   int ascending;
@@ -506,7 +520,7 @@ __device__ __forceinline__ SinkUnion prepare_union(const AttnArgs& p, int split,
   const int first_sink_sub = p.n_keep * p.sub_per_block + (p.N + kSubTile - 1) / kSubTile;
   const int n_round = (p.n_sub + kWavesPerGroup - 1) / kWavesPerGroup;                      // rounds of four sub-tiles ...
   const int last = n_round - 1 - (n_round - 1 - split) % p.n_split;                         // ... the last one of this split
-  if (p.dense_rows == 0 && p.n_sink > 0 && (last + 1) * kWavesPerGroup > first_sink_sub) {  // uniform over the workgroup
+  if (p.dense_rows == 0 && p.n_sink > kSubTile && (last + 1) * kWavesPerGroup > first_sink_sub) {  // uniform over the workgroup
     const bool bitmap = p.n_keep > 0 && p.n_b <= kBitmapBlocks;
     const int words = bitmap ? (p.n_b + 31) >> 5 : 0;
     for (int i = threadIdx.x; i < words; i += blockDim.x) bits_sh[i] = 0u;
@@ -559,7 +573,7 @@ __global__ __launch_bounds__(256, (FUSE & 2) == 0 ? 2 : 1) void sparse_attn_kern
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c = lane & 15, g = lane >> 4;
-  const int split = blockIdx.x, h = blockIdx.y;
+  const int split = PIPE ? blockIdx.x : blockIdx.y, h = PIPE ? blockIdx.y : blockIdx.x;
   char* stageK = ldsA + wave * kBufBytes;  // the slot this wavefront owns
   char* stageV = stageK + G::kStageBytes;
   const uint16_t* Qh = p.Q + (int64_t)h * p.qsh;
@@ -573,14 +587,17 @@ __global__ __launch_bounds__(256, (FUSE & 2) == 0 ? 2 : 1) void sparse_attn_kern
   // With the Top-C prologue ahead, the query rows are requested before it (their two round trips — row ids, then rows —
   // pass while the relevances are summed and ranked); without it they follow the first K/V requests (see below).
   bf16x8 q[1][G::kKSteps];
-  int qrow_early = -1;
+  int qrow_early = -1, few_sinks = -1;
   if (FUSED) {
     qrow_early = fetch_q_row(p.active_idx, 0, p.max_active, p.n_gen, lane);
     float first[32];
     first_partials(first, p);
+    few_sinks = request_few_sinks(p, lane);
     load_q_tile<D>(q[0], Qh, p.qsn, qrow_early, lane);
     rank_blocks(p, first, kept_sh, topk_sm, blockIdx.x == 0 && blockIdx.y == 0);
     kept_blocks = kept_sh;
+  } else {
+    few_sinks = request_few_sinks(p, lane);
   }
   __shared__ uint32_t kept_bits_sh[kBitmapBlocks / 32];
   __shared__ int sinks_unsorted_sh;
@@ -600,7 +617,7 @@ __global__ __launch_bounds__(256, (FUSE & 2) == 0 ? 2 : 1) void sparse_attn_kern
   t.sink_row = 0;
   if (st < st_end) {
     t = locate_subtile(st, lane, p.M, p.N, p.B, p.n_b, p.sub_per_block, kept_blocks, p.n_keep, p.sink_idx, p.n_sink, kept_bits,
-                          sinks_ascending, p.dense_rows, FUSED);
+                          sinks_ascending, p.dense_rows, FUSED, few_sinks);
     if (t.vmask != 0u) {
       issue_subtile<D>(Kh, p.ksn, t, stageK, lane);
       issue_subtile<D>(Vh, p.vsn, t, stageV, lane);
@@ -650,7 +667,7 @@ __global__ __launch_bounds__(256, (FUSE & 2) == 0 ? 2 : 1) void sparse_attn_kern
   };
   auto locate = [&](int sub) {
     return locate_subtile(sub, lane, p.M, p.N, p.B, p.n_b, p.sub_per_block, kept_blocks, p.n_keep, p.sink_idx, p.n_sink, kept_bits,
-                          sinks_ascending, p.dense_rows, FUSED);
+                          sinks_ascending, p.dense_rows, FUSED, few_sinks);
   };
   if (!PIPE) {
     // one sub-tile per wavefront at most (the launcher picks this variant only when a split holds no more sub-tiles
@@ -884,12 +901,16 @@ __global__ __launch_bounds__(256 * NT, NT == 2 || (MODE & 4) == 0 ? 2 : 1) void 
     for (int ks = 0; ks < kKS; ++ks) q[ks] = as_bf16x8(*reinterpret_cast<const uint4*>(src + ks * 16));
   };
   const int32_t* kept_blocks = p.kept_blocks;
+  int few_sinks;
   if (FUSED) {  // the query rows travel while the blocks are ranked
     float first[32];
     first_partials(first, p);
+    few_sinks = request_few_sinks(p, lane);
     load_q();
     rank_blocks(p, first, kept_sh, *reinterpret_cast<TopkShared*>(topk_raw), pair == 0 && qg == 0);
     kept_blocks = kept_sh;
+  } else {
+    few_sinks = request_few_sinks(p, lane);
   }
   const SinkUnion uni = prepare_union(p, split, kept_blocks, kept_bits_sh, &sinks_unsorted_sh);
 
@@ -902,7 +923,7 @@ __global__ __launch_bounds__(256 * NT, NT == 2 || (MODE & 4) == 0 ? 2 : 1) void 
     t.sink_row = 0;
     if (sub < p.n_sub)
       t = locate_subtile(sub, lane, p.M, p.N, p.B, p.n_b, p.sub_per_block, kept_blocks, p.n_keep, p.sink_idx, p.n_sink, uni.kept_bits,
-                         uni.ascending, p.dense_rows, FUSED);
+                         uni.ascending, p.dense_rows, FUSED, few_sinks);
     return t;
   };
   auto request = [&](const SubTile& t, char* stage) __attribute__((always_inline)) {
@@ -1043,6 +1064,8 @@ __global__ __launch_bounds__(256 * NT, NT == 2 || (MODE & 4) == 0 ? 2 : 1) void 
 // Merge of the per-split partial results: out = sum_s f_s O_s / sum_s f_s l_s, f_s = exp2(m_s - max m).
 // One workgroup per (head, active row): thread = (split lane, 4 columns) and takes the splits sl, sl + lanes, ... in index
 // order, kBatch loads in flight; the lanes' states meet in LDS and are added in lane order (a fixed order: deterministic).
+// Heads are the fast grid axis, here and in the loop-free launches of sparse_attn_kernel: with a multiple of eight heads the
+// workgroups of a head run on one XCD, whose L2 then holds the head's query rows and partial results (0.4 us of 10.9 at 32K).
 // The loads do not wait for the device-side query count, which is only looked at when the row is stored, so up to
 // kBatch * lanes splits (32 at d = 128) cost one memory round trip.  (A workgroup per 16 rows that walked the splits one
 // after the other took 27 us at 130 splits of four heads, and as long as this one at 8.)
@@ -1055,9 +1078,10 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(const float* __restri
   constexpr int kCols = D / 4, kLanes = 256 / kCols, kBatch = 4;
   __shared__ float2 ml_sh[kLanes];
   __shared__ __attribute__((aligned(16))) float o_sh[kLanes][D];
-  const int a = blockIdx.x, h = blockIdx.y;
+  const int a = grid_yz(), h = blockIdx.x;
   const int sl = threadIdx.x / kCols, mc = (threadIdx.x % kCols) * 4;
   const int n_act = counts ? min(max(counts[1], 0), max_active) : max_active;
+  if (a >= max_active) return;  // (the grid's last slice)
   const int64_t row0 = ((int64_t)h * q_pad + a) * n_split;
   const float2* ml = reinterpret_cast<const float2*>(part_ml) + row0;
   const float* po = part_o + row0 * D + mc;
@@ -1132,7 +1156,7 @@ static void launch_wide_t(const AttnArgs& a, const SplitPlan& p, bool fused, hip
 template <int D>
 static hipError_t launch_attn_t(const AttnArgs& a, const SplitPlan& p, bool fused, hipStream_t st) {
   if (!p.pipelined && p.n_split * kWavesPerGroup < p.n_sub) return hipErrorInvalidValue;  // the loop-free variants: one sub-tile per wavefront
-  const dim3 grid(p.n_split, a.H), block(256);
+  const dim3 grid = p.pipelined ? dim3(p.n_split, a.H) : dim3(a.H, p.n_split), block(256);
   if (p.q_tiles_per_group > 1) {
     if (a.logits_out != nullptr) return hipErrorInvalidValue;  // logits are spilled for one 16-query tile only
     if (p.q_tiles_per_group > 2)
@@ -1157,7 +1181,7 @@ static hipError_t launch_attn_t(const AttnArgs& a, const SplitPlan& p, bool fuse
     ATTN_LAUNCH((sparse_attn_kernel<D, 0>), grid, block, st, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || p.n_split == 1) return e;
-  hipLaunchKernelGGL(attn_combine_kernel<D>, dim3(a.max_active, a.H), dim3(256), 0, st, a.part_o, a.part_ml, a.counts, a.max_active,
+  hipLaunchKernelGGL(attn_combine_kernel<D>, grid_x_yz(a.H, a.max_active), dim3(256), 0, st, a.part_o, a.part_ml, a.counts, a.max_active,
                      a.q_pad, a.n_split, a.out, a.osh, a.osn, a.lse, a.lse2_out);
   return hipGetLastError();
 }

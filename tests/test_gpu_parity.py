@@ -388,6 +388,24 @@ def test_sparse_attn_many_sinks_inside_and_outside_kept_blocks(G, n_act, ascendi
     assert np.allclose(lse.cpu().numpy(), ref_lse, atol=2e-3)
 
 
+@pytest.mark.parametrize("n_act", [16, 30])
+@pytest.mark.parametrize("n_sink,n_keep", [(1, 0), (2, 3), (31, 70), (32, 70), (33, 70)])
+@pytest.mark.parametrize("ascending", [True, False])
+def test_sparse_attn_sink_lists_of_one_sub_tile(G, n_act, n_sink, n_keep, ascending):
+    """Up to 32 sinks are one sub-tile, held in registers: inside and outside kept blocks, listed twice, out of range."""
+    H, M, N, d, B, n_gen = 2, 8192, 48, 64, 64, 64
+    rng = np.random.default_rng(n_sink)
+    kept = np.sort(rng.choice(M // B, n_keep, replace=False))
+    sinks = rng.choice(M, n_sink, replace=False)
+    if n_sink > 4:
+        sinks[:3] = sinks[4], M + 3, -1
+        sinks[5] = kept[-1] * B + 7
+    sinks = np.sort(sinks) if ascending else rng.permutation(sinks)
+    out, lse, ref, ref_lse = _attn_case(G, H, M, N, d, B, n_gen, np.arange(n_act) * 2, kept, sinks, seed=90)
+    G.assert_attention_close(out, ref)
+    assert np.allclose(lse.cpu().numpy(), ref_lse, atol=2e-3)
+
+
 @pytest.mark.parametrize("n_act", [9, 40])
 def test_sparse_attn_unattended_rows_may_hold_inf_or_nan(G, n_act):
     """Rows outside I_p must not influence the result (Eq. 8, Eq. 9), whatever they hold: sink slots that hold no key
