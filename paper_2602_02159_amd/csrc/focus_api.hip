@@ -189,13 +189,16 @@ static ProbeWs ws_probe_layer(const focus_shape& s, const SplitPlan& pa, const S
 
 // Second half of the sink identification: column masses S from the kept logits or per-part column sums, then Top-N_sink.  Few
 // sinks, or not too many: the 128-key groups of the column-mass kernel nominate and one workgroup decides; else a radix select.
-static int column_mass_and_sinks(const char* who, const float* src, bool two_pass, const float* lse2, const int32_t* counts, int max_active,
-                                 int q_groups, const focus_shape& s, int n_sink, float* S, char* cand_ws, int32_t* sink_idx, hipStream_t st) {
+// lse2: row log-sum-exps, or with n_split > 0 the statistics of the key splits (then lse_scratch takes the log-sum-exps).
+static int column_mass_and_sinks(const char* who, const float* src, bool two_pass, const float* lse2, int n_split, float* lse_scratch,
+                                 const int32_t* counts, int max_active, int q_groups, const focus_shape& s, int n_sink, float* S,
+                                 char* cand_ws, int32_t* sink_idx, hipStream_t st) {
   const bool tournament = sink_tournament_fits(s.n_ctx, n_sink), rank = !tournament && sink_rank_fits(s.n_ctx, n_sink);
   int32_t* cand = (tournament || rank) ? reinterpret_cast<int32_t*>(cand_ws) : nullptr;
   uint32_t* cand_keys = cand ? reinterpret_cast<uint32_t*>(cand_ws) + kMaxNominees : nullptr;
   hipError_t e = launch_column_mass(src, two_pass, lse2, counts, max_active, two_pass ? q_groups * s.n_heads : s.n_heads, s.n_heads,
-                                    s.n_ctx + s.n_resp, S, s.n_ctx, rank ? std::min(n_sink, kRankNominees) : n_sink, cand, cand_keys, st);
+                                    s.n_ctx + s.n_resp, S, s.n_ctx, rank ? std::min(n_sink, kRankNominees) : n_sink, cand, cand_keys, n_split,
+                                    lse_scratch, st);
   if (e != hipSuccess) return fail(FOCUS_ELAUNCH, "%s(column mass): %s", who, hipGetErrorString(e));
   if (tournament)
     e = launch_sink_final(cand, cand_keys, s.n_ctx, n_sink, sink_idx, st);
@@ -470,13 +473,13 @@ int focus_find_sinks(const void* Q, const int32_t* active_idx, const int32_t* co
   hipError_t e = launch_qk_logits(Q, active_idx, counts, max_active, K, *shape, p, two_pass ? 1 : 0, logits, part_ml, nullptr,
                                   nullptr, st);
   if (e != hipSuccess) return launch_fail("focus_find_sinks(logits)", e);
-  e = launch_lse_combine(part_ml, shape->n_heads, p.q_pad, p.n_split, lse2, st);
-  if (e != hipSuccess) return launch_fail("focus_find_sinks(lse)", e);
   if (two_pass) {
+    e = launch_lse_combine(part_ml, shape->n_heads, p.q_pad, p.n_split, lse2, st);
+    if (e != hipSuccess) return launch_fail("focus_find_sinks(lse)", e);
     e = launch_qk_logits(Q, active_idx, counts, max_active, K, *shape, p, 2, nullptr, nullptr, lse2, logits, st);
     if (e != hipSuccess) return launch_fail("focus_find_sinks(column sums)", e);
   }
-  if (int rc = column_mass_and_sinks("focus_find_sinks", logits, two_pass, lse2, counts, max_active, p.q_groups, *shape, n_sink, S, ws + w.cand,
+  if (int rc = column_mass_and_sinks("focus_find_sinks", logits, two_pass, part_ml, two_pass ? 0 : p.n_split, lse2, counts, max_active, p.q_groups, *shape, n_sink, S, ws + w.cand,
                                      sink_idx, st))
     return rc;
   return FOCUS_OK;
@@ -583,7 +586,7 @@ int focus_probe_layer(const void* Q, const int32_t* active_idx, const int32_t* c
     e = launch_qk_logits(Q, active_idx, counts, max_active, K, *shape, pl, 2, nullptr, nullptr, lse2, scratch, st);
     if (e != hipSuccess) return launch_fail("focus_probe_layer(column sums)", e);
   }
-  if (int rc = column_mass_and_sinks("focus_probe_layer", scratch, two_pass, lse2, counts, max_active, pl.q_groups, *shape, n_sink, S,
+  if (int rc = column_mass_and_sinks("focus_probe_layer", scratch, two_pass, lse2, 0, nullptr, counts, max_active, pl.q_groups, *shape, n_sink, S,
                                      ws + w.cand, sink_idx, st))
     return rc;
   return FOCUS_OK;

@@ -67,9 +67,11 @@ bool sink_tournament_fits(int M, int n_sink);
 // cand_keys: uint32 of the same size that receives their order keys + 1 (0 where cand holds -1); required with cand.
 // pre_reduced = false: src = scaled logits [H, ceil(L / 4), 16, 4] of at most 16 queries (written by the MFMA kernels), n_parts = H;
 // pre_reduced = true:  src = column sums [n_parts, L] from the second pass over K.
+// n_split > 0 (pre_reduced = false): lse2 = the statistics [H, 16, n_split, 2] of the key splits instead of the log-sum-exps
+// [H, 16], which are then formed by the same launch or by one more, into lse_scratch.
 hipError_t launch_column_mass(const float* src, bool pre_reduced, const float* lse2, const int32_t* counts, int max_active,
                               int n_parts, int H, int L, float* col_mass, int M, int n_sink, int32_t* cand, uint32_t* cand_keys,
-                              hipStream_t st);
+                              int n_split, float* lse_scratch, hipStream_t st);
 // Many sinks, or few in a long prompt (n_ctx <= 131072): the groups nominate min(kRankNominees, N_sink) each, one workgroup ranks
 // them and falls back to all positions if a group may hold more.  No requirement on the alignment of col_mass.
 constexpr int kRankNominees = 16;

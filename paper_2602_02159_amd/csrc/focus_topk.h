@@ -83,10 +83,15 @@ __device__ __forceinline__ void wave_topk(const uint32_t* keys, int n, int k, in
                                           int base = 0, const uint32_t* remap = nullptr, uint32_t* out_keys = nullptr) {
   const int lane = threadIdx.x & 63;
   uint32_t kv[KPL];
+  if constexpr (KPL == 2) {
+    const uint2 v = reinterpret_cast<const uint2*>(keys)[lane];
+    kv[0] = v.x; kv[1] = v.y;
+  } else {
 #pragma unroll
-  for (int r4 = 0; r4 < KPL / 4; ++r4) {
-    const uint4 v = reinterpret_cast<const uint4*>(keys)[lane * (KPL / 4) + r4];
-    kv[4 * r4] = v.x; kv[4 * r4 + 1] = v.y; kv[4 * r4 + 2] = v.z; kv[4 * r4 + 3] = v.w;
+    for (int r4 = 0; r4 < KPL / 4; ++r4) {
+      const uint4 v = reinterpret_cast<const uint4*>(keys)[lane * (KPL / 4) + r4];
+      kv[4 * r4] = v.x; kv[4 * r4 + 1] = v.y; kv[4 * r4 + 2] = v.z; kv[4 * r4 + 3] = v.w;
+    }
   }
   uint32_t nvalid = 0;
 #pragma unroll
@@ -94,7 +99,7 @@ __device__ __forceinline__ void wave_topk(const uint32_t* keys, int n, int k, in
   const uint32_t k_eff = min((uint32_t)max(k, 0), nvalid);
   uint32_t T = 0;
   if (k_eff > 0) {
-    uint32_t common = 0, same = 0;  // same: bits on which every candidate agrees; common: their value
+    uint32_t open_bits = 0xffffffffu;  // bits in which the candidates differ; in the others T takes what they share
     if (SKIP_COMMON) {
       uint32_t a = 0xffffffffu, o = 0u;
 #pragma unroll
@@ -102,20 +107,15 @@ __device__ __forceinline__ void wave_topk(const uint32_t* keys, int n, int k, in
         a &= kv[r] != 0u ? kv[r] : 0xffffffffu;
         o |= kv[r];
       }
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) {
-        a &= __shfl_xor(a, off, kWave);
-        o |= __shfl_xor(o, off, kWave);
-      }
-      common = a;
-      same = ~(a ^ o);
+      a = wave_reduce_u32(a, [](uint32_t x, uint32_t y) { return x & y; });
+      o = wave_reduce_u32(o, [](uint32_t x, uint32_t y) { return x | y; });
+      T = __builtin_amdgcn_readfirstlane(a);
+      open_bits = __builtin_amdgcn_readfirstlane(a ^ o);
     }
-    for (int bit = 31; bit >= 0; --bit) {
-      if (SKIP_COMMON && ((same >> bit) & 1u)) {  // wave-uniform
-        T |= common & (1u << bit);
-        continue;
-      }
-      const uint32_t cand = T | (1u << bit);
+    while (open_bits != 0u) {
+      const uint32_t top = 0x80000000u >> __builtin_clz(open_bits);
+      open_bits ^= top;
+      const uint32_t cand = T | top;
       uint32_t cnt = 0;
 #pragma unroll
       for (int r = 0; r < KPL; ++r) cnt += (uint32_t)__popcll(__ballot(kv[r] >= cand));
