@@ -9,6 +9,7 @@
  *     focus_select_queries   once per denoising step            -> I_focus, I_active
  *     focus_expand_groups    (grouped-query attention only) the same lists for the rows of all query heads of a group
  *     focus_find_sinks       once per step, at the probe layer  -> I_sink   (reused unchanged by all deeper layers)
+ *     focus_select_and_find_sinks   both of the above in one call
  *     focus_block_means      whenever the prompt K of a layer is refreshed -> K_bar (cacheable)
  *     focus_block_scores     per sparse layer                   -> R_b, B_relevant
  *     focus_sparse_attn      per sparse layer                   -> Attn
@@ -168,6 +169,14 @@ int focus_top_blocks(const float* partials, int32_t n_parts, const int32_t* coun
 int focus_find_sinks(const void* Q, const int32_t* active_idx, const int32_t* counts, int32_t max_active,
                      const void* K, const focus_shape* shape, int32_t n_sink, float* col_mass, int32_t* sink_idx,
                      void* workspace, size_t ws_bytes, void* stream);
+
+/* focus_select_queries followed by focus_find_sinks with its lists (the same arguments, the same results; n_gen is
+ * shape->n_gen, workspace that of FOCUS_FN_FIND_SINKS): for a caller whose confidence is final when the probe layer's Q and K
+ * are.  With n_gen <= 64 the selection costs no launch of its own. */
+int focus_select_and_find_sinks(const float* conf, const uint8_t* masked, int32_t k, int32_t window, int32_t lo, int32_t hi,
+                                int32_t* focus_idx, int32_t* active_idx, int32_t max_active, int32_t* counts, const void* Q,
+                                const void* K, const focus_shape* shape, int32_t n_sink, float* col_mass, int32_t* sink_idx,
+                                void* workspace, size_t ws_bytes, void* stream);
 
 /*
  * Sink-aware sparse attention (Sec. 5.3, Eq. 8 and Eq. 9).

@@ -18,7 +18,8 @@ LIB_PATH = os.path.join(_HERE, "libfocus_hip.so")
 FOCUS_OK, FOCUS_EINVAL, FOCUS_EUNSUPPORTED, FOCUS_EWORKSPACE, FOCUS_ELAUNCH = 0, -1, -2, -3, -4
 FN_BLOCK_SCORES, FN_FIND_SINKS, FN_SPARSE_ATTN, FN_SPARSE_LAYER, FN_PROBE_LAYER = 1, 2, 3, 4, 5
 
-EXPORTS = ("focus_select_queries", "focus_expand_groups", "focus_block_means", "focus_block_scores", "focus_find_sinks", "focus_sparse_attn",
+EXPORTS = ("focus_select_queries", "focus_expand_groups", "focus_block_means", "focus_block_scores", "focus_find_sinks", "focus_select_and_find_sinks",
+           "focus_sparse_attn",
            "focus_sparse_layer", "focus_sparse_layer_static", "focus_block_partials", "focus_top_blocks", "focus_probe_layer", "focus_refresh_attn", "focus_cache_refresh",
            "focus_token_confidence", "focus_token_confidence_workspace", "focus_cache_update",
            "focus_workspace_bytes", "focus_helper_k", "focus_helper_n_keep", "focus_helper_n_sink", "focus_last_error",
@@ -56,6 +57,7 @@ def lib() -> C.CDLL:
         L.focus_block_means.argtypes = [p, sp, p, p]
         L.focus_block_scores.argtypes = [p, p, p, i32, p, p, sp, i32, p, p, p, sz, p]
         L.focus_find_sinks.argtypes = [p, p, p, i32, p, sp, i32, p, p, p, sz, p]
+        L.focus_select_and_find_sinks.argtypes = [p, p, i32, i32, i32, i32, p, p, i32, p, p, p, sp, i32, p, p, p, sz, p]
         L.focus_sparse_attn.argtypes = [p, p, p, i32, p, p, sp, p, i32, p, i32, p, p, p, sz, p]
         L.focus_sparse_layer.argtypes = [p, p, p, p, i32, i32, p, p, p, sp, i32, p, i32, p, p, p, p, p, sz, p]
         L.focus_sparse_layer_static.argtypes = [p, p, p, p, i32, i32, p, p, p, sp, i32, p, i32, p, p, p, p, p]
@@ -69,7 +71,7 @@ def lib() -> C.CDLL:
         L.focus_block_partials.argtypes = [p, p, p, i32, p, p, sp, p, p]
         L.focus_top_blocks.argtypes = [p, i32, p, i32, i32, i32, p, p, p]
         for name in ("focus_select_queries", "focus_expand_groups", "focus_block_means", "focus_block_scores", "focus_find_sinks",
-                     "focus_sparse_attn", "focus_sparse_layer", "focus_sparse_layer_static", "focus_block_partials", "focus_top_blocks",
+                     "focus_select_and_find_sinks", "focus_sparse_attn", "focus_sparse_layer", "focus_sparse_layer_static", "focus_block_partials", "focus_top_blocks",
                      "focus_probe_layer", "focus_refresh_attn", "focus_token_confidence", "focus_cache_update", "focus_cache_refresh"):
             getattr(L, name).restype = C.c_int
         L.focus_workspace_bytes.argtypes = [i32, sp, i32, i32, i32]
@@ -186,6 +188,18 @@ def find_sinks(q, active_idx, counts, k, shape: Shape, n_sink: int, col_mass, si
     _check(lib().focus_find_sinks(_ptr(q), _ptr(active_idx), _ptr(counts), active_idx.numel(), _ptr(k), C.byref(shape),
                                   n_sink, _ptr(col_mass), _ptr(sink_idx), _ptr(workspace),
                                   0 if workspace is None else workspace.numel() * workspace.element_size(), _stream()))
+
+
+def select_and_find_sinks(conf, masked, k_focus: int, window: int, lo: int, hi: int, focus_idx, active_idx, counts, q, k, shape: Shape,
+                          n_sink: int, col_mass, sink_idx, workspace) -> None:
+    """select_queries followed by find_sinks with its lists."""
+    _need(conf, torch.float32, "conf")
+    _need(q, torch.bfloat16, "Q")
+    _need(k, torch.bfloat16, "K")
+    _check(lib().focus_select_and_find_sinks(_ptr(conf), _ptr(masked), k_focus, window, lo, hi, _ptr(focus_idx), _ptr(active_idx),
+                                             active_idx.numel(), _ptr(counts), _ptr(q), _ptr(k), C.byref(shape), n_sink, _ptr(col_mass),
+                                             _ptr(sink_idx), _ptr(workspace),
+                                             0 if workspace is None else workspace.numel() * workspace.element_size(), _stream()))
 
 
 def sparse_attn(q, active_idx, counts, k, v, shape: Shape, kept_blocks, n_keep: int, sink_idx, n_sink: int, out, lse,

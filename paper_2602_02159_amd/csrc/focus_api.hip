@@ -210,6 +210,59 @@ static int column_mass_and_sinks(const char* who, const float* src, bool two_pas
   return FOCUS_OK;
 }
 
+static int check_select(const char* who, const float* conf, int32_t n_gen, int32_t k, int32_t window, int32_t lo, int32_t hi,
+                        const int32_t* focus_idx, const int32_t* active_idx, int32_t max_active, const int32_t* counts) {
+  if (!conf || !focus_idx || !active_idx || !counts) return fail(FOCUS_EINVAL, "%s: NULL pointer", who);
+  if (n_gen < 1 || n_gen > 16384) return fail(FOCUS_EINVAL, "%s: n_gen=%d not in [1, 16384]", who, n_gen);
+  if (k < 1 || k > n_gen) return fail(FOCUS_EINVAL, "%s: k=%d not in [1, n_gen=%d]", who, k, n_gen);
+  if (window < 0) return fail(FOCUS_EINVAL, "%s: window=%d negative", who, window);
+  if (lo < 0 || hi > n_gen || lo >= hi) return fail(FOCUS_EINVAL, "%s: [lo=%d, hi=%d) not inside [0, %d)", who, lo, hi, n_gen);
+  const int64_t span = 2 * (int64_t)(window / 2) + 1;
+  const int64_t need = std::min<int64_t>(hi - lo, (int64_t)k * span);
+  if (max_active < need) return fail(FOCUS_EINVAL, "%s: max_active=%d < %lld", who, max_active, (long long)need);
+  return FOCUS_OK;
+}
+
+// select != nullptr: the query selection comes first, in the logits launch where the block is small enough for that.
+static int find_sinks_impl(const char* who, const SelectArgs* select, const void* Q, const int32_t* active_idx, const int32_t* counts,
+                           int32_t max_active, const void* K, const focus_shape* shape, int32_t n_sink, float* col_mass,
+                           int32_t* sink_idx, void* workspace, size_t ws_bytes, void* stream) {
+  if (int rc = check_shape(shape, true, true, false, false)) return rc;
+  if (!Q || !active_idx || !K) return fail(FOCUS_EINVAL, "%s: NULL pointer", who);
+  if (max_active < 1 || max_active > shape->n_gen) return fail(FOCUS_EINVAL, "%s: max_active=%d not in [1, n_gen]", who, max_active);
+  if (n_sink < 0 || n_sink > shape->n_ctx) return fail(FOCUS_EINVAL, "%s: n_sink=%d not in [0, n_ctx]", who, n_sink);
+  if (n_sink > 0 && !sink_idx) return fail(FOCUS_EINVAL, "%s: sink_idx is NULL", who);
+  if (!aligned16(Q) || !aligned16(K)) return fail(FOCUS_EINVAL, "%s: pointers must be 16-byte aligned", who);
+  const SplitPlan p = plan_logits(*shape, max_active);
+  const SinkWs w = ws_find_sinks(*shape, p);
+  if (!workspace || ws_bytes < w.total || !aligned16(workspace))
+    return fail(FOCUS_EWORKSPACE, "%s: workspace needs %zu bytes, 16-byte aligned", who, w.total);
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  char* ws = static_cast<char*>(workspace);
+  float* logits = reinterpret_cast<float*>(ws + w.logits);
+  float* part_ml = reinterpret_cast<float*>(ws + w.part_ml);
+  float* lse2 = reinterpret_cast<float*>(ws + w.lse2);
+  float* S = col_mass ? col_mass : reinterpret_cast<float*>(ws + w.col_mass);
+  const bool two_pass = sinks_two_pass(p);
+  hipError_t e = hipSuccess;
+  if (select != nullptr && shape->n_gen > kSelectInLogitsGen) {
+    e = launch_select_queries(select->conf, select->masked, shape->n_gen, select->k, 2 * select->half, select->lo, select->hi,
+                              select->focus_idx, select->active_idx, max_active, select->counts, st);
+    if (e != hipSuccess) return fail(FOCUS_ELAUNCH, "%s(selection): %s", who, hipGetErrorString(e));
+    select = nullptr;
+  }
+  e = launch_qk_logits(Q, active_idx, counts, max_active, K, *shape, p, two_pass ? 1 : 0, logits, part_ml, nullptr, nullptr, st, select);
+  if (e != hipSuccess) return fail(FOCUS_ELAUNCH, "%s(logits): %s", who, hipGetErrorString(e));
+  if (two_pass) {
+    e = launch_lse_combine(part_ml, shape->n_heads, p.q_pad, p.n_split, lse2, st);
+    if (e != hipSuccess) return fail(FOCUS_ELAUNCH, "%s(lse): %s", who, hipGetErrorString(e));
+    e = launch_qk_logits(Q, active_idx, counts, max_active, K, *shape, p, 2, nullptr, nullptr, lse2, logits, st);
+    if (e != hipSuccess) return fail(FOCUS_ELAUNCH, "%s(column sums): %s", who, hipGetErrorString(e));
+  }
+  return column_mass_and_sinks(who, logits, two_pass, two_pass ? lse2 : part_ml, two_pass ? 0 : p.n_split, lse2, counts, max_active,
+                               p.q_groups, *shape, n_sink, S, ws + w.cand, sink_idx, st);
+}
+
 struct LayerWs {
   size_t attn, total;
   ScoreWs sc;
@@ -352,14 +405,7 @@ size_t focus_workspace_bytes(int32_t fn, const focus_shape* shape, int32_t max_a
 int focus_select_queries(const float* conf, const uint8_t* masked, int32_t n_gen, int32_t k, int32_t window, int32_t lo,
                          int32_t hi, int32_t* focus_idx, int32_t* active_idx, int32_t max_active, int32_t* counts,
                          void* stream) {
-  if (!conf || !focus_idx || !active_idx || !counts) return fail(FOCUS_EINVAL, "focus_select_queries: NULL pointer");
-  if (n_gen < 1 || n_gen > 16384) return fail(FOCUS_EINVAL, "focus_select_queries: n_gen=%d not in [1, 16384]", n_gen);
-  if (k < 1 || k > n_gen) return fail(FOCUS_EINVAL, "focus_select_queries: k=%d not in [1, n_gen=%d]", k, n_gen);
-  if (window < 0) return fail(FOCUS_EINVAL, "focus_select_queries: window=%d negative", window);
-  if (lo < 0 || hi > n_gen || lo >= hi) return fail(FOCUS_EINVAL, "focus_select_queries: [lo=%d, hi=%d) not inside [0, %d)", lo, hi, n_gen);
-  const int64_t span = 2 * (int64_t)(window / 2) + 1;
-  const int64_t need = std::min<int64_t>(hi - lo, (int64_t)k * span);
-  if (max_active < need) return fail(FOCUS_EINVAL, "focus_select_queries: max_active=%d < %lld", max_active, (long long)need);
+  if (int rc = check_select("focus_select_queries", conf, n_gen, k, window, lo, hi, focus_idx, active_idx, max_active, counts)) return rc;
   hipError_t e = launch_select_queries(conf, masked, n_gen, k, window, lo, hi, focus_idx, active_idx, max_active, counts,
                                        static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return launch_fail("focus_select_queries", e);
@@ -453,36 +499,29 @@ int focus_top_blocks(const float* partials, int32_t n_parts, const int32_t* coun
 int focus_find_sinks(const void* Q, const int32_t* active_idx, const int32_t* counts, int32_t max_active, const void* K,
                      const focus_shape* shape, int32_t n_sink, float* col_mass, int32_t* sink_idx, void* workspace,
                      size_t ws_bytes, void* stream) {
+  return find_sinks_impl("focus_find_sinks", nullptr, Q, active_idx, counts, max_active, K, shape, n_sink, col_mass, sink_idx, workspace,
+                         ws_bytes, stream);
+}
+
+int focus_select_and_find_sinks(const float* conf, const uint8_t* masked, int32_t k, int32_t window, int32_t lo, int32_t hi,
+                                int32_t* focus_idx, int32_t* active_idx, int32_t max_active, int32_t* counts, const void* Q,
+                                const void* K, const focus_shape* shape, int32_t n_sink, float* col_mass, int32_t* sink_idx,
+                                void* workspace, size_t ws_bytes, void* stream) {
   if (int rc = check_shape(shape, true, true, false, false)) return rc;
-  if (!Q || !active_idx || !K) return fail(FOCUS_EINVAL, "focus_find_sinks: NULL pointer");
-  if (max_active < 1 || max_active > shape->n_gen) return fail(FOCUS_EINVAL, "focus_find_sinks: max_active=%d not in [1, n_gen]", max_active);
-  if (n_sink < 0 || n_sink > shape->n_ctx) return fail(FOCUS_EINVAL, "focus_find_sinks: n_sink=%d not in [0, n_ctx]", n_sink);
-  if (n_sink > 0 && !sink_idx) return fail(FOCUS_EINVAL, "focus_find_sinks: sink_idx is NULL");
-  if (!aligned16(Q) || !aligned16(K)) return fail(FOCUS_EINVAL, "focus_find_sinks: pointers must be 16-byte aligned");
-  const SplitPlan p = plan_logits(*shape, max_active);
-  const SinkWs w = ws_find_sinks(*shape, p);
-  if (!workspace || ws_bytes < w.total || !aligned16(workspace))
-    return fail(FOCUS_EWORKSPACE, "focus_find_sinks: workspace needs %zu bytes, 16-byte aligned", w.total);
-  hipStream_t st = static_cast<hipStream_t>(stream);
-  char* ws = static_cast<char*>(workspace);
-  float* logits = reinterpret_cast<float*>(ws + w.logits);
-  float* part_ml = reinterpret_cast<float*>(ws + w.part_ml);
-  float* lse2 = reinterpret_cast<float*>(ws + w.lse2);
-  float* S = col_mass ? col_mass : reinterpret_cast<float*>(ws + w.col_mass);
-  const bool two_pass = sinks_two_pass(p);
-  hipError_t e = launch_qk_logits(Q, active_idx, counts, max_active, K, *shape, p, two_pass ? 1 : 0, logits, part_ml, nullptr,
-                                  nullptr, st);
-  if (e != hipSuccess) return launch_fail("focus_find_sinks(logits)", e);
-  if (two_pass) {
-    e = launch_lse_combine(part_ml, shape->n_heads, p.q_pad, p.n_split, lse2, st);
-    if (e != hipSuccess) return launch_fail("focus_find_sinks(lse)", e);
-    e = launch_qk_logits(Q, active_idx, counts, max_active, K, *shape, p, 2, nullptr, nullptr, lse2, logits, st);
-    if (e != hipSuccess) return launch_fail("focus_find_sinks(column sums)", e);
-  }
-  if (int rc = column_mass_and_sinks("focus_find_sinks", logits, two_pass, part_ml, two_pass ? 0 : p.n_split, lse2, counts, max_active, p.q_groups, *shape, n_sink, S, ws + w.cand,
-                                     sink_idx, st))
+  if (int rc = check_select("focus_select_and_find_sinks", conf, shape->n_gen, k, window, lo, hi, focus_idx, active_idx, max_active, counts))
     return rc;
-  return FOCUS_OK;
+  SelectArgs sel;
+  sel.conf = conf;
+  sel.masked = masked;
+  sel.k = k;
+  sel.half = window / 2;
+  sel.lo = lo;
+  sel.hi = hi;
+  sel.focus_idx = focus_idx;
+  sel.active_idx = active_idx;
+  sel.counts = counts;
+  return find_sinks_impl("focus_select_and_find_sinks", &sel, Q, active_idx, counts, max_active, K, shape, n_sink, col_mass, sink_idx,
+                         workspace, ws_bytes, stream);
 }
 
 size_t focus_token_confidence_workspace(int32_t n_rows, int32_t vocab) {

@@ -96,9 +96,19 @@ hipError_t launch_cache_refresh(void* K_cache, void* V_cache, const focus_shape&
 
 // ---- MFMA kernels (focus_mfma.hip)
 // mode 0: logits [H, ceil(L / 4), 16, 4] + part_ml out (at most 16 queries); mode 1: part_ml out only; mode 2: lse2 in, colpart [q_groups * H, L] out
+// select (modes 0 and 1): the query selection (Eq. 4, Eq. 5) is made by the same launch; active_idx and counts are not read
+constexpr int kSelectInLogitsGen = 64;  // n_gen at most: a wavefront holds one position per lane
+struct SelectArgs {
+  const float* conf;
+  const uint8_t* masked;
+  int k, half, lo, hi;
+  int32_t* focus_idx;
+  int32_t* active_idx;
+  int32_t* counts;
+};
 hipError_t launch_qk_logits(const void* Q, const int32_t* active_idx, const int32_t* counts, int max_active,
                             const void* K, const focus_shape& s, const SplitPlan& p, int mode, float* logits,
-                            float* part_ml, const float* lse2, float* colpart, hipStream_t st);
+                            float* part_ml, const float* lse2, float* colpart, hipStream_t st, const SelectArgs* select = nullptr);
 // Extra arguments of the fused layer path: the attention kernel ranks the blocks itself from the per-head partial
 // relevances (n_b <= kFusedMaxBlocks).
 constexpr int kFusedMaxBlocks = 256;

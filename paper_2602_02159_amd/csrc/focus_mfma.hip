@@ -1718,14 +1718,46 @@ struct LogitArgs {
   int H, L, n_gen, max_active;
   int n_sub, n_split, q_pad;
   float scale_log2;
+  SelectArgs sel;  // SELECT only
 };
+
+// Query selection (Eq. 4: the k most confident of the still-masked positions; Eq. 5: window union) of a block of up to 64
+// positions by one wavefront, one position per lane; the focus and active sets are 64-bit masks.  Same order, ties and outputs as
+// select_queries_kernel.
+__device__ __forceinline__ unsigned long long select_positions(const SelectArgs& s, int n_gen, int max_active, int lane, bool writer) {
+  uint32_t key1 = 0u;
+  if (lane < n_gen) {
+    const uint32_t key = order_key(s.conf[lane]) + 1u;
+    key1 = s.masked == nullptr || s.masked[lane] != 0 ? key : 0u;
+  }
+  uint32_t pos, n_focus;
+  const bool sel = wave_select1(key1, s.k, pos, n_focus);
+  unsigned long long active = __ballot(sel);
+  for (int i = min(s.half, 63); i > 0; --i) active |= (active << 1) | (active >> 1);
+  active &= s.hi >= 64 ? ~0ull : (1ull << s.hi) - 1ull;
+  active &= ~((1ull << s.lo) - 1ull);  // lo < hi <= n_gen <= 64
+  if (writer) {
+    const uint32_t n_act = (uint32_t)__popcll(active);
+    if (sel) s.focus_idx[pos] = lane;
+    if (lane >= (int)n_focus && lane < s.k) s.focus_idx[lane] = -1;  // k <= n_gen
+    if ((active >> lane) & 1ull) s.active_idx[__popcll(active & ((1ull << lane) - 1ull))] = lane;
+    for (int i = (int)n_act + lane; i < max_active; i += kWave) s.active_idx[i] = -1;
+    if (lane == 0) {
+      s.counts[0] = (int32_t)n_focus;
+      s.counts[1] = (int32_t)n_act;
+    }
+  }
+  return active;
+}
 
 // MODE 0: the scaled logits are written out (for up to 16 queries re-reading 64 bytes per key and head is cheaper
 //         than a second pass over K) together with the per-split softmax statistics.
 // MODE 1: statistics only.
 // MODE 2: second pass for more than 16 queries: with the row log-sum-exps known, the probabilities are formed on the
 //         fly and summed over the workgroup's queries; colpart[qg * H + h, j] = sum_i P[h, i, j].
-template <int D, int NQT, int MODE>
+// SELECT: every wavefront makes the query selection itself, beside its first K rows, instead of reading what a launch of its own
+//         has written; the first workgroup writes the lists for everyone else (a step of 4 heads at 1K: one launch of 3 us less).
+template <int D, int NQT, int MODE, bool SELECT>
 __global__ __launch_bounds__(256, 2) void qk_logits_kernel(const uint16_t* K, int64_t ksh, int64_t ksn, const int32_t* active_idx, int L,
                                                            int n_sub, int n_split, int max_active, int n_gen, const LogitArgs args) {
   LogitArgs p = args;  // what the first requests need comes in registers, as in the attention kernels
@@ -1762,15 +1794,29 @@ __global__ __launch_bounds__(256, 2) void qk_logits_kernel(const uint16_t* K, in
     return t;
   };
   int qrow[NQT];
+  if (!SELECT) {
 #pragma unroll
-  for (int qt = 0; qt < NQT; ++qt) qrow[qt] = fetch_q_row(p.active_idx, q_base + qt * kQTile, p.max_active, p.n_gen, lane);
+    for (int qt = 0; qt < NQT; ++qt) qrow[qt] = fetch_q_row(p.active_idx, q_base + qt * kQTile, p.max_active, p.n_gen, lane);
+  }
   SubTile t = tile_of(st < st_end ? st : 0);
   if (st < st_end) issue_subtile<D>(Kh, p.ksn, t, stageK, lane);
+  int n_sel = 0;
+  if (SELECT) {
+    __shared__ int row_sh[kWavesPerGroup][kWave];  // active positions in order, per wavefront
+    const unsigned long long active = select_positions(p.sel, p.n_gen, p.max_active, lane, wave == 0 && (split | h | qg) == 0);
+    if ((active >> lane) & 1ull) row_sh[wave][__popcll(active & ((1ull << lane) - 1ull))] = lane;
+    n_sel = (int)__popcll(active);
+#pragma unroll
+    for (int qt = 0; qt < NQT; ++qt) {
+      const int a = q_base + qt * kQTile + c;
+      qrow[qt] = a < n_sel ? row_sh[wave][a & (kWave - 1)] : -1;
+    }
+  }
 
   bf16x8 q[NQT][G::kKSteps];
 #pragma unroll
   for (int qt = 0; qt < NQT; ++qt) load_q_tile<D>(q[qt], Qh, p.qsn, qrow[qt], lane);
-  const int n_act = p.counts ? min(max(p.counts[1], 0), p.max_active) : p.max_active;
+  const int n_act = SELECT ? n_sel : (p.counts ? min(max(p.counts[1], 0), p.max_active) : p.max_active);
 #pragma unroll
   for (int qt = 0; qt < NQT; ++qt) mask_q_tile<D>(q[qt], q_base + qt * kQTile, n_act, lane);
 
@@ -1857,22 +1903,37 @@ __global__ __launch_bounds__(256, 2) void qk_logits_kernel(const uint16_t* K, in
 }
 
 template <int D, int NQT>
-static hipError_t launch_logits_t(const LogitArgs& a, const SplitPlan& p, int mode, hipStream_t st) {
+static hipError_t launch_logits_t(const LogitArgs& a, const SplitPlan& p, int mode, bool select, hipStream_t st) {
   dim3 grid(p.n_split, a.H, p.q_groups);
-  if (mode == 0)
-    hipLaunchKernelGGL((qk_logits_kernel<D, NQT, 0>), grid, dim3(256), 0, st, a.K, a.ksh, a.ksn, a.active_idx, a.L, a.n_sub, a.n_split, a.max_active, a.n_gen, a);
-  else if (mode == 1)
-    hipLaunchKernelGGL((qk_logits_kernel<D, NQT, 1>), grid, dim3(256), 0, st, a.K, a.ksh, a.ksn, a.active_idx, a.L, a.n_sub, a.n_split, a.max_active, a.n_gen, a);
-  else
-    hipLaunchKernelGGL((qk_logits_kernel<D, NQT, 2>), grid, dim3(256), 0, st, a.K, a.ksh, a.ksn, a.active_idx, a.L, a.n_sub, a.n_split, a.max_active, a.n_gen, a);
+#define LOGITS_LAUNCH(MODE, SELECT)                                                                                        \
+  hipLaunchKernelGGL((qk_logits_kernel<D, NQT, MODE, SELECT>), grid, dim3(256), 0, st, a.K, a.ksh, a.ksn, a.active_idx, a.L, a.n_sub, \
+                     a.n_split, a.max_active, a.n_gen, a)
+  if constexpr (NQT == 1) {  // one tile spills its logits, several take two passes
+    if (mode != 0) return hipErrorInvalidValue;
+    if (select)
+      LOGITS_LAUNCH(0, true);
+    else
+      LOGITS_LAUNCH(0, false);
+  } else {
+    if (mode == 0) return hipErrorInvalidValue;
+    if (mode == 2)
+      LOGITS_LAUNCH(2, false);
+    else if (select)
+      LOGITS_LAUNCH(1, true);
+    else
+      LOGITS_LAUNCH(1, false);
+  }
+#undef LOGITS_LAUNCH
   return hipGetLastError();
 }
 
 // mode 0: logits + part_ml out; mode 1: part_ml out; mode 2: lse2 in, colpart out (see qk_logits_kernel)
 hipError_t launch_qk_logits(const void* Q, const int32_t* active_idx, const int32_t* counts, int max_active,
                             const void* K, const focus_shape& s, const SplitPlan& p, int mode, float* logits,
-                            float* part_ml, const float* lse2, float* colpart, hipStream_t st) {
+                            float* part_ml, const float* lse2, float* colpart, hipStream_t st, const SelectArgs* select) {
+  if (select != nullptr && (mode == 2 || s.n_gen > kSelectInLogitsGen)) return hipErrorInvalidValue;
   LogitArgs a;
+  a.sel = select ? *select : SelectArgs{};
   a.Q = static_cast<const uint16_t*>(Q);
   a.K = static_cast<const uint16_t*>(K);
   a.active_idx = active_idx;
@@ -1888,13 +1949,13 @@ hipError_t launch_qk_logits(const void* Q, const int32_t* active_idx, const int3
   a.scale_log2 = kLog2e / sqrtf((float)s.head_dim);
   const int nqt = p.q_tiles_per_group;
   if (s.head_dim == 128) {
-    if (nqt == 1) return launch_logits_t<128, 1>(a, p, mode, st);
-    if (nqt == 2) return launch_logits_t<128, 2>(a, p, mode, st);
-    return launch_logits_t<128, 4>(a, p, mode, st);
+    if (nqt == 1) return launch_logits_t<128, 1>(a, p, mode, select != nullptr, st);
+    if (nqt == 2) return launch_logits_t<128, 2>(a, p, mode, select != nullptr, st);
+    return launch_logits_t<128, 4>(a, p, mode, select != nullptr, st);
   }
-  if (nqt == 1) return launch_logits_t<64, 1>(a, p, mode, st);
-  if (nqt == 2) return launch_logits_t<64, 2>(a, p, mode, st);
-  return launch_logits_t<64, 4>(a, p, mode, st);
+  if (nqt == 1) return launch_logits_t<64, 1>(a, p, mode, select != nullptr, st);
+  if (nqt == 2) return launch_logits_t<64, 2>(a, p, mode, select != nullptr, st);
+  return launch_logits_t<64, 4>(a, p, mode, select != nullptr, st);
 }
 
 }  // namespace focus

@@ -73,6 +73,10 @@ class FocusStep:
             "find_sinks": [(L.focus_find_sinks, (p(probe[0]), p(self.active_idx), p(self.counts), self.max_active, p(probe[1]),
                                                  C.byref(s_probe), n_sink, p(self.col_mass), p(self.sink_idx), p(ws_sinks),
                                                  ws_sinks.numel()))],
+            "select_and_sinks": [(L.focus_select_and_find_sinks, (
+                p(conf), p(masked), k_focus, window, 0, self.n_gen, p(self.focus_idx), p(self.active_idx), self.max_active,
+                p(self.counts), p(probe[0]), p(probe[1]), C.byref(s_probe), n_sink, p(self.col_mass), p(self.sink_idx), p(ws_sinks),
+                ws_sinks.numel()))],
             "block_means": [], "block_scores": [], "block_scores_cached": [], "sparse_attn": [], "dense_attn": [],
             "sparse_layer": [], "sparse_layer_cached": [], "block_partials": [], "probe_layer": [],
         }
@@ -138,8 +142,11 @@ class FocusStep:
 
     def sequence(self):
         """The step's calls in order: [confidence,] queries once, sinks once at the probe layer, then every layer."""
-        seq = self.calls["confidence"] + self.calls["select"]
-        seq = seq + (self.calls["probe_layer"] if self.use_probe_layer and self.calls["probe_layer"] else self.calls["find_sinks"])
+        seq = self.calls["confidence"]
+        if self.use_probe_layer and self.calls["probe_layer"]:
+            seq = seq + self.calls["select"] + self.calls["probe_layer"]
+        else:
+            seq = seq + self.calls["select_and_sinks"]
         if self.dense:
             return seq + self.calls["dense_attn"]
         n = len(self.layers)

@@ -177,6 +177,33 @@ def test_find_sinks(G, H, M, N, d, n_gen, n_act, n_sink):
     assert torch.equal(sinks, sinks2) and np.allclose(col2.cpu().numpy(), S, rtol=1e-6)
 
 
+@pytest.mark.parametrize("n_gen,k,window,lo,hi,cap", [
+    (64, 16, 0, 0, 64, 16), (64, 4, 8, 0, 64, 36), (63, 5, 9, 3, 60, 57), (64, 64, 0, 0, 64, 64), (64, 1, 300, 0, 64, 64),
+    (1, 1, 0, 0, 1, 1), (33, 8, 2, 10, 11, 8), (65, 4, 2, 0, 65, 12), (200, 30, 3, 0, 200, 90), (64, 3, 200, 63, 64, 20)])
+def test_select_and_find_sinks_equals_the_two_calls(G, n_gen, k, window, lo, hi, cap):
+    H, M, N, d, n_sink = 3, 1500, 40, 64, 5
+    g = torch.Generator().manual_seed(n_gen + k)
+    conf = torch.rand(n_gen, generator=g)
+    conf[:n_gen // 3] = 0.5  # ties
+    masked = (torch.rand(n_gen, generator=g) < 0.7).to(torch.uint8)
+    q, kk = _rand_bf16(61, H, n_gen, d).to(G.DEV), _rand_bf16(62, H, M + N, d).to(G.DEV)
+    s = fb.make_shape(q, kk, None, M, 64)
+    ws = G.ws(fb.workspace_bytes(fb.FN_FIND_SINKS, s, cap))
+    for mask in (None, masked.to(G.DEV)):
+        res = []
+        for fused in (False, True):
+            focus, active, counts, sinks = (torch.full((n,), -7, dtype=torch.int32, device=G.DEV) for n in (k, cap, 2, n_sink))
+            col = torch.zeros(M + N, device=G.DEV)
+            if fused:
+                fb.select_and_find_sinks(conf.to(G.DEV), mask, k, window, lo, hi, focus, active, counts, q, kk, s, n_sink, col, sinks, ws)
+            else:
+                fb.select_queries(conf.to(G.DEV), mask, k, window, lo, hi, focus, active, counts)
+                fb.find_sinks(q, active, counts, kk, s, n_sink, col, sinks, ws)
+            torch.cuda.synchronize()
+            res.append((focus, active, counts, col, sinks))
+        assert all(torch.equal(a, b) for a, b in zip(*res))
+
+
 def test_find_sinks_equal_keys_fall_back_to_lowest_positions(G):
     H, M, N, d = 2, 500, 12, 64
     k = _rand_bf16(9, 1, 1, d).expand(H, M + N, d).contiguous().to(G.DEV)
