@@ -112,7 +112,7 @@ static ScoreWs ws_block_scores(const focus_shape& s) {
   const size_t n_b = ceil_div(s.n_ctx, s.block);
   ScoreWs w;
   w.part = 0;
-  w.scores = w.part + align_up((size_t)s.n_heads * n_b * sizeof(float));
+  w.scores = w.part + align_up((size_t)s.n_heads * n_b * sizeof(float));  // per head: the K scan's layout
   w.total = w.scores + align_up(n_b * sizeof(float));
   return w;
 }
@@ -205,7 +205,7 @@ static int column_mass_and_sinks(const char* who, const float* src, bool two_pas
   else if (rank)
     e = launch_sink_rank(cand, cand_keys, s.n_ctx, n_sink, S, sink_idx, st);
   else if (n_sink > 0)
-    e = launch_reduce_topk(nullptr, 0, nullptr, 0, S, s.n_ctx, n_sink, sink_idx, st);
+    e = launch_reduce_topk(nullptr, 0, 0, nullptr, 0, S, s.n_ctx, n_sink, sink_idx, st);
   if (e != hipSuccess) return fail(FOCUS_ELAUNCH, "%s(top-N): %s", who, hipGetErrorString(e));
   return FOCUS_OK;
 }
@@ -340,11 +340,12 @@ static int sparse_layer_impl(const char* who, const void* Q, const int32_t* focu
   if (!kbar)
     e = launch_block_means_relevance(K, Q, focus_idx, counts, n_focus_max, *shape, nullptr, part, st);
   else
-    e = launch_block_relevance(Q, focus_idx, counts, n_focus_max, kbar, *shape, part, st);
+    e = launch_block_relevance(Q, focus_idx, counts, n_focus_max, kbar, *shape, part, false, st);
   if (e != hipSuccess) return launch_fail("focus_sparse_layer(relevance)", e);
   if (fused) {
     FusedTopC f;
     f.rel_part = part;
+    f.per_head = kbar == nullptr;
     f.scores_out = R;
     f.kept_out = kept_blocks;
     f.n_focus_max = n_focus_max;
@@ -353,7 +354,7 @@ static int sparse_layer_impl(const char* who, const void* Q, const int32_t* focu
     if (e != hipSuccess) return launch_fail("focus_sparse_layer(attention)", e);
     return FOCUS_OK;
   }
-  e = launch_reduce_topk(part, shape->n_heads, counts, n_focus_max, R, n_b, n_keep, kept_blocks, st);
+  e = launch_reduce_topk(part, kbar ? ceil_div(shape->n_heads, kRelGroup) : shape->n_heads, shape->n_heads, counts, n_focus_max, R, n_b, n_keep, kept_blocks, st);
   if (e != hipSuccess) return launch_fail("focus_sparse_layer(top-C)", e);
   e = launch_sparse_attn(Q, active_idx, counts, max_active, K, V, *shape, kept_blocks, n_keep, sink_idx, n_sink, p, out, lse,
                          part_o, part_ml, nullptr, st);
@@ -460,9 +461,9 @@ int focus_block_scores(const void* Q, const int32_t* focus_idx, const int32_t* c
   if (!kbar)  // one scan of K gives the partial relevances directly; the means are not materialised
     e = launch_block_means_relevance(K, Q, focus_idx, counts, n_focus_max, *shape, nullptr, part, st);
   else
-    e = launch_block_relevance(Q, focus_idx, counts, n_focus_max, kbar, *shape, part, st);
+    e = launch_block_relevance(Q, focus_idx, counts, n_focus_max, kbar, *shape, part, false, st);
   if (e != hipSuccess) return launch_fail("focus_block_scores(relevance)", e);
-  e = launch_reduce_topk(part, shape->n_heads, counts, n_focus_max, R, n_b, n_keep, kept_blocks, st);
+  e = launch_reduce_topk(part, kbar ? ceil_div(shape->n_heads, kRelGroup) : shape->n_heads, shape->n_heads, counts, n_focus_max, R, n_b, n_keep, kept_blocks, st);
   if (e != hipSuccess) return launch_fail("focus_block_scores(top-C)", e);
   return FOCUS_OK;
 }
@@ -476,7 +477,7 @@ int focus_block_partials(const void* Q, const int32_t* focus_idx, const int32_t*
   if (!aligned16(Q) || (kbar && !aligned16(kbar)) || (!kbar && !aligned16(K)))
     return fail(FOCUS_EINVAL, "focus_block_partials: pointers must be 16-byte aligned");
   hipStream_t st = static_cast<hipStream_t>(stream);
-  hipError_t e = kbar ? launch_block_relevance(Q, focus_idx, counts, n_focus_max, kbar, *shape, partials, st)
+  hipError_t e = kbar ? launch_block_relevance(Q, focus_idx, counts, n_focus_max, kbar, *shape, partials, true, st)
                       : launch_block_means_relevance(K, Q, focus_idx, counts, n_focus_max, *shape, nullptr, partials, st);
   if (e != hipSuccess) return launch_fail("focus_block_partials", e);
   return FOCUS_OK;
@@ -490,7 +491,7 @@ int focus_top_blocks(const float* partials, int32_t n_parts, const int32_t* coun
   if (n_focus_max < 1) return fail(FOCUS_EINVAL, "focus_top_blocks: n_focus_max=%d", n_focus_max);
   if (n_keep < 0 || n_keep > n_blocks) return fail(FOCUS_EINVAL, "focus_top_blocks: n_keep=%d not in [0, n_blocks=%d]", n_keep, n_blocks);
   if (n_keep > 0 && !kept_blocks) return fail(FOCUS_EINVAL, "focus_top_blocks: kept_blocks is NULL");
-  hipError_t e = launch_reduce_topk(partials, n_parts, counts, n_focus_max, scores, n_blocks, n_keep, kept_blocks,
+  hipError_t e = launch_reduce_topk(partials, n_parts, n_parts, counts, n_focus_max, scores, n_blocks, n_keep, kept_blocks,
                                     static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return launch_fail("focus_top_blocks", e);
   return FOCUS_OK;

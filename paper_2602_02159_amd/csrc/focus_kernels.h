@@ -49,12 +49,14 @@ hipError_t launch_block_means(const void* K, const focus_shape& s, float* kbar, 
 // one scan of K that yields the per-head partial relevances (and, if kbar is not null, the block means)
 hipError_t launch_block_means_relevance(const void* K, const void* Q, const int32_t* focus_idx, const int32_t* counts,
                                         int n_focus_max, const focus_shape& s, float* kbar, float* part, hipStream_t st);
-// per-head partial relevances part[H, n_b] (sum over the focus queries, not yet scaled)
+constexpr int kRelGroup = 4;  // heads whose partial relevances are added before they leave a workgroup
+// partial relevances (sum over the focus queries, not yet scaled): per_head part[H, n_b], else part[ceil(H / 4), n_b], sums over
+// groups of four heads
 hipError_t launch_block_relevance(const void* Q, const int32_t* focus_idx, const int32_t* counts, int n_focus_max,
-                                  const float* kbar, const focus_shape& s, float* part, hipStream_t st);
-// values[j] = sum_h part[h, j] / (|I_focus| n_parts) when part != nullptr (else values are read), then
-// top-k over values[0..n): out[k] ascending indices
-hipError_t launch_reduce_topk(const float* part, int n_parts, const int32_t* counts, int n_focus_max, float* values, int n,
+                                  const float* kbar, const focus_shape& s, float* part, bool per_head, hipStream_t st);
+// values[j] = sum_i part[i, j] / (|I_focus| n_heads) when part != nullptr (else values are read), then top-k over values[0..n):
+// out[k] ascending indices.  n_parts = n_heads, or ceil(n_heads / 4) groups
+hipError_t launch_reduce_topk(const float* part, int n_parts, int n_heads, const int32_t* counts, int n_focus_max, float* values, int n,
                               int k, int32_t* out, hipStream_t st);
 hipError_t launch_lse_combine(const float* part_ml, int H, int q_pad, int n_split, float* lse2, hipStream_t st);
 // Sink selection as a tournament (small N_sink): every 128-key group of the column-mass kernel nominates its own
@@ -113,7 +115,8 @@ hipError_t launch_qk_logits(const void* Q, const int32_t* active_idx, const int3
 // relevances (n_b <= kFusedMaxBlocks).
 constexpr int kFusedMaxBlocks = 256;
 struct FusedTopC {
-  const float* rel_part;  // [H, n_b] from launch_block_relevance
+  const float* rel_part;  // [ceil(H / 4), n_b] from launch_block_relevance, or with per_head [H, n_b]
+  bool per_head;
   float* scores_out;      // [n_b] or null
   int32_t* kept_out;      // [n_keep]
   int n_focus_max;

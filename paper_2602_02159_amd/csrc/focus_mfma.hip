@@ -438,8 +438,9 @@ struct AttnArgs {
   int H, M, N, B, n_b, n_gen, n_keep, n_sink, max_active;
   int sub_per_block, n_sub, n_split, q_pad, q_groups;
   float scale_log2;
-  // fused layer path only: per-head partial relevances in, scores / kept blocks out
-  const float* rel_part;  // [H, n_b]
+  // fused layer path only: partial relevances in, scores / kept blocks out
+  const float* rel_part;  // [ceil(H / 4), n_b], or with rel_per_head [H, n_b]
+  bool rel_per_head;
   float* scores_out;      // [n_b] or null
   int32_t* kept_out;      // [n_keep]
   int n_focus_max;
@@ -451,7 +452,7 @@ struct AttnArgs {
 
 // The arguments that the first memory requests of an attention kernel need, once more as leading scalar parameters: those (14
 // dwords) are in scalar registers when a wavefront starts (-amdgpu-kernarg-preload-count), while a member of AttnArgs is a load
-// of its own in front of everything that depends on it.
+// of its own in front of everything that depends on it.  H arrives negative where the partial relevances are per head.
 #define ATTN_FIRST_PARAMS                                                                                                  \
   const float *rel_part, const int32_t *active_idx, const uint16_t *Q, const int32_t *counts, int n_b, int H, int max_active, \
       int n_gen, int n_split, int n_sub
@@ -462,7 +463,8 @@ __device__ __forceinline__ AttnArgs with_first(AttnArgs p, ATTN_FIRST_PARAMS) {
   p.Q = Q;
   p.counts = counts;
   p.n_b = n_b;
-  p.H = H;
+  p.H = abs(H);
+  p.rel_per_head = H < 0;
   p.max_active = max_active;
   p.n_gen = n_gen;
   p.n_split = n_split;
@@ -470,25 +472,41 @@ __device__ __forceinline__ AttnArgs with_first(AttnArgs p, ATTN_FIRST_PARAMS) {
   return p;
 }
 #define ATTN_LAUNCH(kernel, grid, block, st, a)                                                                            \
-  hipLaunchKernelGGL(kernel, grid, block, 0, st, (a).rel_part, (a).active_idx, (a).Q, (a).counts, (a).n_b, (a).H, (a).max_active, \
+  hipLaunchKernelGGL(kernel, grid, block, 0, st, (a).rel_part, (a).active_idx, (a).Q, (a).counts, (a).n_b, (a).rel_per_head ? -(a).H : (a).H, (a).max_active, \
                      (a).n_gen, (a).n_split, (a).n_sub, a)
 
 // What the attention kernels prepare before their first K/V request.
-// R_b = (1 / (|I_focus| H)) sum_h part[h, b] for b = threadIdx.x (n_b <= 256 <= blockDim.x), then Top-C into kept_sh; the
+// R_b = (1 / (|I_focus| H)) sum_h qsum^h . kbar^h_b for b = threadIdx.x (n_b <= 256 <= blockDim.x), then Top-C into kept_sh; the
 // workgroup with `writer` set also writes scores and kept blocks out.  First use of `sm`.  `first` holds the loads of the first
-// 32 heads (first_partials), which the caller requests before it waits for anything.
-__device__ __forceinline__ void first_partials(float (&first)[32], const AttnArgs& p) {
-  const uint32_t b = min((int)threadIdx.x, p.n_b - 1);
+// NP parts (first_partials), which the caller requests before it waits for anything: 32 heads in groups of four are 8 parts.
+template <int NP>
+__device__ __forceinline__ void first_partials(float (&first)[NP], const AttnArgs& p, bool per_head) {
+  const uint32_t b = min((int)threadIdx.x, p.n_b - 1);  // n_b <= 256: small offsets
+  const int last = (per_head ? p.H : (p.H + kRelGroup - 1) / kRelGroup) - 1;
 #pragma unroll
-  for (int h = 0; h < 32; ++h) first[h] = p.rel_part[(uint32_t)(min(h, p.H - 1) * p.n_b) + b];  // n_b <= 256: small offsets
+  for (int i = 0; i < NP; ++i) first[i] = p.rel_part[(uint32_t)(min(i, last) * p.n_b) + b];
   __builtin_amdgcn_sched_barrier(0);  // (the scheduler would move the wait for the row ids in front of these loads)
 }
-__device__ __forceinline__ void rank_blocks(const AttnArgs& p, const float (&first)[32], int32_t* kept_sh, TopkShared& sm, bool writer) {
+template <int NP>
+__device__ __forceinline__ void rank_blocks(const AttnArgs& p, const float (&first)[NP], bool per_head, int32_t* kept_sh, TopkShared& sm,
+                                            bool writer) {
   const int tid = threadIdx.x;
-  float r = 0.f;
+  float r = 0.f;  // the order of sum_partials
+  if (per_head) {
 #pragma unroll
-  for (int h = 0; h < 32; ++h) r += h < p.H ? first[h] : 0.f;  // head by head, the order of sum_partials
-  if (p.H > 32 && tid < p.n_b) r = sum_partials(p.rel_part, p.H, p.n_b, tid, 32, r);
+    for (int h = 0; h < NP; h += kRelGroup) {
+      float g = first[h];
+#pragma unroll
+      for (int i = 1; i < kRelGroup; ++i) g = h + i < p.H ? g + first[h + i] : g;
+      r = h < p.H ? r + g : r;
+    }
+    if (p.H > NP && tid < p.n_b) r = sum_partials(p.rel_part, p.H, false, p.n_b, tid, NP, r);
+  } else {
+    const int n_groups = (p.H + kRelGroup - 1) / kRelGroup;
+#pragma unroll
+    for (int g = 0; g < NP; ++g) r = g < n_groups ? r + first[g] : r;
+    if (n_groups > NP && tid < p.n_b) r = sum_partials(p.rel_part, n_groups, true, p.n_b, tid, NP, r);
+  }
   const int n_f = p.counts ? min(max(p.counts[0], 0), p.n_focus_max) : p.n_focus_max;
   r *= n_f > 0 ? 1.f / ((float)n_f * (float)p.H) : 0.f;
   auto keyfn = [=](int, uint32_t& key) -> bool {
@@ -548,6 +566,7 @@ __device__ __forceinline__ SinkUnion prepare_union(const AttnArgs& p, int split,
 // FUSE bit 0 clear: kept_blocks comes from memory.
 // FUSE bit 0 set (fused layer path): the workgroup first assembles R_b from the per-head partial relevances and ranks
 // them itself — every workgroup repeats this small computation instead of waiting for a separate Top-C kernel.
+// FUSE bit 3 set (with bit 0): the partial relevances come per head, from a K scan, and not per group of four heads.
 // FUSE bit 2 set (dense probe layer): the scaled logits of every (query, key) are also written out, so that
 // the column attention mass of Eq. 6 needs no QK^T pass of its own.
 // FUSE bit 1 set: double-buffered key loop for launches in which a wavefront walks several sub-tiles
@@ -563,6 +582,7 @@ __global__ __launch_bounds__(256, (FUSE & 2) == 0 ? 2 : 1) void sparse_attn_kern
   constexpr bool FUSED = (FUSE & 1) != 0;                // Top-C in the prologue
   constexpr bool PIPE = (FUSE & 2) != 0;                 // two K/V stages per wavefront
   constexpr bool SPILL = (FUSE & 4) != 0;                // dense: also write the scaled logits (sink scoring)
+  constexpr bool PER_HEAD = (FUSE & 8) != 0;             // FUSED: partial relevances per head, not per group of heads
   constexpr int kBufBytes = 2 * G::kStageBytes;          // one slot: K stage + V stage of a sub-tile
   static_assert(16 * D * 4 <= kBufBytes, "a wavefront's O tile fits its stage");
   // Two buffers of four slots; the second exists in the double-buffered variant only.
@@ -590,11 +610,11 @@ __global__ __launch_bounds__(256, (FUSE & 2) == 0 ? 2 : 1) void sparse_attn_kern
   int qrow_early = -1, few_sinks = -1;
   if (FUSED) {
     qrow_early = fetch_q_row(p.active_idx, 0, p.max_active, p.n_gen, lane);
-    float first[32];
-    first_partials(first, p);
+    float first[PER_HEAD ? 32 : 8];
+    first_partials(first, p, PER_HEAD);
     few_sinks = request_few_sinks(p, lane);
     load_q_tile<D>(q[0], Qh, p.qsn, qrow_early, lane);
-    rank_blocks(p, first, kept_sh, topk_sm, blockIdx.x == 0 && blockIdx.y == 0);
+    rank_blocks(p, first, PER_HEAD, kept_sh, topk_sm, blockIdx.x == 0 && blockIdx.y == 0);
     kept_blocks = kept_sh;
   } else {
     few_sinks = request_few_sinks(p, lane);
@@ -903,11 +923,11 @@ __global__ __launch_bounds__(256 * NT, NT == 2 || (MODE & 4) == 0 ? 2 : 1) void 
   const int32_t* kept_blocks = p.kept_blocks;
   int few_sinks;
   if (FUSED) {  // the query rows travel while the blocks are ranked
-    float first[32];
-    first_partials(first, p);
+    float first[8];  // (per head, from a K scan: the other parts are requested when they are added)
+    first_partials(first, p, p.rel_per_head);
     few_sinks = request_few_sinks(p, lane);
     load_q();
-    rank_blocks(p, first, kept_sh, *reinterpret_cast<TopkShared*>(topk_raw), pair == 0 && qg == 0);
+    rank_blocks(p, first, p.rel_per_head, kept_sh, *reinterpret_cast<TopkShared*>(topk_raw), pair == 0 && qg == 0);
     kept_blocks = kept_sh;
   } else {
     few_sinks = request_few_sinks(p, lane);
@@ -1171,8 +1191,12 @@ static hipError_t launch_attn_t(const AttnArgs& a, const SplitPlan& p, bool fuse
       ATTN_LAUNCH((sparse_attn_kernel<D, 6>), grid, block, st, a);
     else
       ATTN_LAUNCH((sparse_attn_kernel<D, 4>), grid, block, st, a);
-  } else if (fused && p.pipelined)
+  } else if (fused && p.pipelined && a.rel_per_head)
+    ATTN_LAUNCH((sparse_attn_kernel<D, 11>), grid, block, st, a);
+  else if (fused && p.pipelined)
     ATTN_LAUNCH((sparse_attn_kernel<D, 3>), grid, block, st, a);
+  else if (fused && a.rel_per_head)
+    ATTN_LAUNCH((sparse_attn_kernel<D, 9>), grid, block, st, a);
   else if (fused)
     ATTN_LAUNCH((sparse_attn_kernel<D, 1>), grid, block, st, a);
   else if (p.pipelined)
@@ -1218,6 +1242,7 @@ hipError_t launch_sparse_attn(const void* Q, const int32_t* active_idx, const in
   a.q_groups = p.q_groups;
   a.scale_log2 = kLog2e / sqrtf((float)s.head_dim);
   a.rel_part = fused ? fused->rel_part : nullptr;
+  a.rel_per_head = fused && fused->per_head;
   a.scores_out = fused ? fused->scores_out : nullptr;
   a.kept_out = fused ? fused->kept_out : nullptr;
   a.n_focus_max = fused ? fused->n_focus_max : 0;

@@ -114,14 +114,14 @@ hipError_t launch_expand_groups(const int32_t* focus_idx, int max_focus, const i
 }
 
 // =====================================================================================================
-// Top-k over a float array that may first have to be assembled from per-head partial sums:
-//   values[j] = scale * sum_{h < n_parts} part[h * n + j]   (fixed order over h), written to values_out,
+// Top-k over a float array that may first have to be assembled from partial sums:
+//   values[j] = sum_{i < n_parts} part[i * n + j] / (|I_focus| n_heads)   (fixed order, see sum_partials), written to values_out,
 // then Top-k over values[0..n).  With part == nullptr the values are read as they are.  One workgroup.
-// Used for Top-C over R_b (n_parts = H partial relevances) and Top-N_sink over S_j (n_parts = 0).
+// Used for Top-C over R_b (partial relevances) and Top-N_sink over S_j (n_parts = 0).
 // =====================================================================================================
 template <int MAXN>  // MAXN > 0: n <= min(blockDim.x, MAXN), no radix-select code
 __global__ __launch_bounds__(kTopkThreads) void reduce_topk_kernel(const float* __restrict__ part, int n_parts,
-                                                                   const int32_t* __restrict__ counts, int n_focus_max,
+                                                                   int n_heads, const int32_t* __restrict__ counts, int n_focus_max,
                                                                    float* __restrict__ values, int n, int k,
                                                                    int32_t* __restrict__ out) {
   __shared__ TopkShared sm;
@@ -129,9 +129,9 @@ __global__ __launch_bounds__(kTopkThreads) void reduce_topk_kernel(const float* 
   float mine = 0.f;
   if (part != nullptr) {
     const int n_f = counts ? min(max(counts[0], 0), n_focus_max) : n_focus_max;
-    const float scale = n_f > 0 ? 1.f / ((float)n_f * (float)n_parts) : 0.f;
+    const float scale = n_f > 0 ? 1.f / ((float)n_f * (float)n_heads) : 0.f;
     for (int j = tid; j < n; j += nt) {
-      float acc = sum_partials(part, n_parts, n, j);
+      float acc = sum_partials(part, n_parts, n_parts != n_heads, n, j);
       acc *= scale;
       values[j] = acc;
       mine = acc;  // the value of element tid when n <= nt
@@ -160,17 +160,17 @@ __global__ __launch_bounds__(kTopkThreads) void reduce_topk_kernel(const float* 
   }
 }
 
-hipError_t launch_reduce_topk(const float* part, int n_parts, const int32_t* counts, int n_focus_max, float* values, int n,
+hipError_t launch_reduce_topk(const float* part, int n_parts, int n_heads, const int32_t* counts, int n_focus_max, float* values, int n,
                               int k, int32_t* out, hipStream_t st) {
   const int threads = n <= 64 ? 64 : (n <= 256 ? 256 : kTopkThreads);
   if (n <= 256)
-    hipLaunchKernelGGL(reduce_topk_kernel<256>, dim3(1), dim3(threads), 0, st, part, n_parts, counts, n_focus_max, values, n, k,
+    hipLaunchKernelGGL(reduce_topk_kernel<256>, dim3(1), dim3(threads), 0, st, part, n_parts, n_heads, counts, n_focus_max, values, n, k,
                        out);
   else if (n <= threads)
-    hipLaunchKernelGGL(reduce_topk_kernel<1024>, dim3(1), dim3(threads), 0, st, part, n_parts, counts, n_focus_max, values, n,
+    hipLaunchKernelGGL(reduce_topk_kernel<1024>, dim3(1), dim3(threads), 0, st, part, n_parts, n_heads, counts, n_focus_max, values, n,
                        k, out);
   else
-    hipLaunchKernelGGL(reduce_topk_kernel<0>, dim3(1), dim3(threads), 0, st, part, n_parts, counts, n_focus_max, values, n,
+    hipLaunchKernelGGL(reduce_topk_kernel<0>, dim3(1), dim3(threads), 0, st, part, n_parts, n_heads, counts, n_focus_max, values, n,
                        k, out);
   return hipGetLastError();
 }
@@ -179,54 +179,48 @@ hipError_t launch_reduce_topk(const float* part, int n_parts, const int32_t* cou
 // Helpers shared by the block-relevance kernels, written once so that the K-scanning and the cached-means
 // variants produce bit-identical partial relevances.
 // =====================================================================================================
-// Sum over the focus queries of Q[h, i, 8c .. 8c+7] for the calling thread's chunk c = t % (D/8).  All 256 threads
-// take part: thread (r, c) adds up the focus rows r, r + RPP, r + 2 RPP, ... (four loads in flight at a time); the
-// per-r sums meet across the lanes of a wavefront (fixed tree), then the four wavefronts in LDS.  (Every thread adding all
-// RPP per-r sums from LDS read 128 KB of it per workgroup, 0.6 us of the 4.1 us of a relevance launch at 32K.)  `first_row`
-// is focus_idx[r] fetched by the caller ahead of time (any value if r >= n_focus_max); `psum` must be free on entry.
-template <int D>
-__device__ __forceinline__ void focus_row_sum(float (&qs)[8], const uint16_t* __restrict__ qh, int64_t qsn,
-                                              const int32_t* __restrict__ focus_idx, int first_row, int n_f, int n_gen,
-                                              float (*psum)[D]) {
-  constexpr int CPR = D / 8, RPP = 256 / CPR, U = 4;
-  const int c = threadIdx.x % CPR, r = threadIdx.x / CPR;
-  float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  for (int f0 = r; f0 < n_f; f0 += RPP * U) {
-    int rows[U];
+// Sum over the focus queries of Q[h, i, 8c .. 8c+7] by one wavefront, for the calling lane's chunk c = lane % (D/8): lane (r, c)
+// adds up the list entries r, r + R, r + 2 R, ... (U row loads in flight at a time), then the R lanes of a chunk meet (fixed
+// tree; every lane receives the total).  `entry` = focus_idx[lane], fetched by the caller ahead of time (any value past the list).
+template <int D, int U>
+__device__ __forceinline__ void add_focus_rows(float (&qs)[8], const uint16_t* __restrict__ qh, int64_t qsn,
+                                               const int32_t* __restrict__ focus_idx, int entry, int n_f, int n_gen) {
+  constexpr int CPR = D / 8, R = kWave / CPR;
+  static_assert(kWave % (R * U) == 0, "a batch lies within the entries a wavefront holds, or behind them");
+  const int lane = threadIdx.x & 63, c = lane % CPR, r = lane / CPR;
+  for (int f0 = 0; f0 < n_f; f0 += R * U) {  // uniform
+    int row[U];
+    if (f0 < kWave) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int f = f0 + u * RPP;
-      rows[u] = f < n_f ? (f == r ? first_row : focus_idx[f]) : -1;
+      for (int u = 0; u < U; ++u) row[u] = __shfl(entry, f0 + u * R + r, kWave);
+    } else {
+#pragma unroll
+      for (int u = 0; u < U; ++u) row[u] = f0 + u * R + r < n_f ? focus_idx[f0 + u * R + r] : -1;
     }
     uint4 v[U];
 #pragma unroll
     for (int u = 0; u < U; ++u)
-      v[u] = (rows[u] >= 0 && rows[u] < n_gen) ? *reinterpret_cast<const uint4*>(qh + (int64_t)rows[u] * qsn + c * 8)
-                                                : make_uint4(0u, 0u, 0u, 0u);
+      v[u] = (f0 + u * R + r < n_f && row[u] >= 0 && row[u] < n_gen) ? *reinterpret_cast<const uint4*>(qh + (int64_t)row[u] * qsn + c * 8)
+                                                                     : make_uint4(0u, 0u, 0u, 0u);
 #pragma unroll
-    for (int u = 0; u < U; ++u) add_bf16x8(acc, v[u]);
+    for (int u = 0; u < U; ++u) add_bf16x8(qs, v[u]);
   }
-  // the values of r within a wavefront meet across lanes, the four wavefronts in LDS
+}
+template <int D, bool MANY>  // MANY: twice the loads in flight for lists longer than 4 R entries
+__device__ __forceinline__ void focus_row_sum(float (&qs)[8], const uint16_t* __restrict__ qh, int64_t qsn,
+                                              const int32_t* __restrict__ focus_idx, int entry, int n_f, int n_gen) {
+  constexpr int CPR = D / 8, R = kWave / CPR;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) qs[e] = 0.f;
+  if (MANY && n_f > 4 * R)
+    add_focus_rows<D, 8>(qs, qh, qsn, focus_idx, entry, n_f, n_gen);
+  else
+    add_focus_rows<D, 4>(qs, qh, qsn, focus_idx, entry, n_f, n_gen);
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
     if (CPR == 8)  // lanes 8 apart: a rotation of the DPP row
-      acc[e] += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, acc[e]), 0x128, 0xF, 0xF, false));
-    acc[e] = group_sum(acc[e]);
-  }
-  if ((threadIdx.x & 63) < CPR) {
-    float4* pw = reinterpret_cast<float4*>(&psum[threadIdx.x >> 6][c * 8]);
-    pw[0] = make_float4(acc[0], acc[1], acc[2], acc[3]);
-    pw[1] = make_float4(acc[4], acc[5], acc[6], acc[7]);
-  }
-  __syncthreads();
-#pragma unroll
-  for (int e = 0; e < 8; ++e) qs[e] = 0.f;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const float4* pr = reinterpret_cast<const float4*>(&psum[i][c * 8]);
-    const float4 lo = pr[0], hi = pr[1];
-    qs[0] += lo.x; qs[1] += lo.y; qs[2] += lo.z; qs[3] += lo.w;
-    qs[4] += hi.x; qs[5] += hi.y; qs[6] += hi.z; qs[7] += hi.w;
+      qs[e] += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, qs[e]), 0x128, 0xF, 0xF, false));
+    qs[e] = group_sum(qs[e]);
   }
 }
 
@@ -241,8 +235,10 @@ __device__ __forceinline__ float chunk_dot_reduce(const float (&qs)[8], const fl
   dot = __builtin_fmaf(qs[5], k1.y, dot);
   dot = __builtin_fmaf(qs[6], k1.z, dot);
   dot = __builtin_fmaf(qs[7], k1.w, dot);
-#pragma unroll
-  for (int o = CPR / 2; o > 0; o >>= 1) dot += __shfl_xor(dot, o, kWave);
+  if (CPR == 16) return row_sum16(dot);
+  dot += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, dot), 0xB1, 0xF, 0xF, false));   // quad_perm [1,0,3,2]
+  dot += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, dot), 0x4E, 0xF, 0xF, false));   // quad_perm [2,3,0,1]
+  dot += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, dot), 0x141, 0xF, 0xF, false));  // row_half_mirror
   return dot;
 }
 
@@ -269,10 +265,10 @@ __global__ __launch_bounds__(256, 8) void block_means_kernel(const uint16_t* __r
   const int r0 = b * B;
   const int len = min(B, M - r0);
   const int c = threadIdx.x % TPR, rr = threadIdx.x / TPR;
-  // the focus row this thread will need at the very end is fetched now, in the shadow of the K loads
-  int first_row = -1, n_f = 0;
+  // the focus list that the first wavefront will need at the very end is fetched now, in the shadow of the K loads
+  int entry = -1, n_f = 0;
   if (WITH_REL) {
-    if (rr < n_focus_max) first_row = focus_idx[rr];
+    if ((int)threadIdx.x < min(n_focus_max, kWave)) entry = focus_idx[threadIdx.x];
     n_f = counts ? min(max(counts[0], 0), n_focus_max) : n_focus_max;
   }
   const uint16_t* base = K + (int64_t)h * sh + (int64_t)r0 * sn + c * 8;
@@ -299,10 +295,10 @@ __global__ __launch_bounds__(256, 8) void block_means_kernel(const uint16_t* __r
     if (WITH_REL) kb_sh[threadIdx.x] = mean;
   }
   if (WITH_REL) {
-    __syncthreads();  // `red` is free again, kb_sh is complete
-    float qs[8];
-    focus_row_sum<D>(qs, Q + (int64_t)h * qsh, qsn, focus_idx, first_row, n_f, n_gen, red);
-    if (threadIdx.x < kWave) {  // the first TPR lanes carry the block row; the rest of the wave only feeds the shuffles
+    __syncthreads();  // kb_sh is complete
+    if (threadIdx.x < kWave) {
+      float qs[8];
+      focus_row_sum<D, false>(qs, Q + (int64_t)h * qsh, qsn, focus_idx, entry, n_f, n_gen);
       const float4* kp = reinterpret_cast<const float4*>(kb_sh + c * 8);
       const float dot = chunk_dot_reduce<TPR>(qs, kp[0], kp[1]);
       if (threadIdx.x == 0) part[(int64_t)h * n_b + b] = dot;
@@ -340,60 +336,89 @@ hipError_t launch_block_means_relevance(const void* K, const void* Q, const int3
 }
 
 // =====================================================================================================
-// Block relevance (Eq. 7), per-head partial sums: part[h, b] = qsum^h . kbar^h_b with qsum^h the SUM of the
-// focus queries of head h; the 1/(|I_focus| H) factor and the sum over heads are applied, in a fixed order,
-// by reduce_topk_kernel.  One workgroup per (group of blocks, head): a thread owns one 8-wide slice of d of
-// one block row.  The focus indices and the kbar loads are issued first, then the focus rows of Q (see
-// focus_row_sum), so the whole kernel is two dependent memory round trips long.  (Requesting all rows of Q beside the focus
-// list, to save one of them, was not faster: the list comes from the L2.)  Heads are the fast grid axis: workgroups go to the
-// XCDs round-robin, so with a multiple of eight heads those of one head share an L2 and with it the focus rows.
+// Block relevance (Eq. 7), partial sums: qsum^h . kbar^h_b with qsum^h the SUM of the focus queries of head h; the
+// 1/(|I_focus| H) factor and the rest of the sum over heads are applied, in a fixed order, where the blocks are ranked.
+// A wavefront owns one head and P R consecutive blocks (R = 4 at d = 128, 8 at 64), a lane one 8-wide slice of d of one block
+// row; the focus indices and the kbar loads are issued first, then the focus rows of Q: two dependent memory round trips.
+// PER_HEAD: part[h, b].  Otherwise the four heads of the workgroup meet in LDS and part[h / 4, b] is their sum, so that whoever
+// ranks the blocks — every workgroup of the attention kernel, or a single one past 256 blocks — has a quarter to read.
+// Heads are the fast grid axis: workgroups go to the XCDs round-robin, so those of one head share an L2 and its focus rows.
+// Sparse layer of 32 heads with 256 blocks 15.3 -> 14.9 us (a workgroup per head and 32 blocks, its 16 focus rows summed by all
+// four wavefronts through LDS, and every attention workgroup adding 32 partial relevances per block), 4 heads at 1K 11.0 -> 10.4.
+// Two passes: eight need fewer workgroups and read the focus rows less often, and take 0.3 us more from 64 to 1024 blocks.
 // =====================================================================================================
-template <int D>
+constexpr int kRelPasses = 2;
+template <int D, bool PER_HEAD>
 __global__ __launch_bounds__(256) void relevance_partial_kernel(const int32_t* __restrict__ focus_idx,
                                                                 const float* __restrict__ kbar,
                                                                 const int32_t* __restrict__ counts,
                                                                 const uint16_t* __restrict__ Q, int64_t qsh, int64_t qsn, int n_b,
-                                                                int n_focus_max, int n_gen, float* __restrict__ part) {
-  constexpr int CPR = D / 8;      // lanes per block row
-  constexpr int RPP = 256 / CPR;  // block rows per pass
-  constexpr int PASSES = 2;
-  __shared__ __attribute__((aligned(16))) float psum[4][D];
-  const int t = threadIdx.x, c = t % CPR, r = t / CPR;
-  const int h = blockIdx.x, b0 = grid_yz() * (RPP * PASSES);
-  const int first_row = r < n_focus_max ? focus_idx[r] : -1;
-  const int n_f = counts ? min(max(counts[0], 0), n_focus_max) : n_focus_max;
-  float4 k0[PASSES], k1[PASSES];
+                                                                int H, int n_focus_max, int n_gen, float* __restrict__ part) {
+  constexpr int CPR = D / 8;        // lanes per block row
+  constexpr int R = kWave / CPR;    // block rows per pass
+  constexpr int P = kRelPasses;
+  static_assert(kRelGroup * kWave == 256, "a wavefront per head of the group");
+  __shared__ float dots[kRelGroup][P * R];
+  const int lane = threadIdx.x & 63, c = lane % CPR, r = lane / CPR;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int h = blockIdx.x * kRelGroup + wave, b0 = grid_yz() * (P * R);
+  if (h < H) {
+    const int entry = lane < n_focus_max ? focus_idx[lane] : -1;
+    const int n_f = counts ? min(max(counts[0], 0), n_focus_max) : n_focus_max;
+    float4 k0[P], k1[P];
 #pragma unroll
-  for (int p = 0; p < PASSES; ++p) {
-    const int b = b0 + p * RPP + r;
-    if (b < n_b) {
-      const float4* kp = reinterpret_cast<const float4*>(kbar + ((int64_t)h * n_b + b) * D + c * 8);
+    for (int p = 0; p < P; ++p) {
+      const float4* kp = reinterpret_cast<const float4*>(kbar + ((int64_t)h * n_b + min(b0 + p * R + r, n_b - 1)) * D + c * 8);
       k0[p] = kp[0];
       k1[p] = kp[1];
-    } else {
-      k0[p] = k1[p] = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    float qs[8];
+    focus_row_sum<D, true>(qs, Q + (int64_t)h * qsh, qsn, focus_idx, entry, n_f, n_gen);
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+      const float dot = chunk_dot_reduce<CPR>(qs, k0[p], k1[p]);
+      const int b = b0 + p * R + r;
+      if (c == 0) {
+        if (PER_HEAD) {
+          if (b < n_b) part[(int64_t)h * n_b + b] = dot;
+        } else {
+          dots[wave][p * R + r] = dot;
+        }
+      }
     }
   }
-  float qs[8];
-  focus_row_sum<D>(qs, Q + (int64_t)h * qsh, qsn, focus_idx, first_row, n_f, n_gen, psum);
+  if (PER_HEAD) return;
+  __syncthreads();
+  const int t = threadIdx.x;
+  if (t < P * R && b0 + t < n_b) {
+    float acc = dots[0][t];
 #pragma unroll
-  for (int p = 0; p < PASSES; ++p) {
-    const float dot = chunk_dot_reduce<CPR>(qs, k0[p], k1[p]);
-    const int b = b0 + p * RPP + r;
-    if (c == 0 && b < n_b) part[(int64_t)h * n_b + b] = dot;
+    for (int w = 1; w < kRelGroup; ++w) acc = (int)blockIdx.x * kRelGroup + w < H ? acc + dots[w][t] : acc;
+    part[(int64_t)blockIdx.x * n_b + b0 + t] = acc;
   }
 }
 
-hipError_t launch_block_relevance(const void* Q, const int32_t* focus_idx, const int32_t* counts, int n_focus_max,
-                                  const float* kbar, const focus_shape& s, float* part, hipStream_t st) {
+template <int D>
+static void launch_block_relevance_t(const uint16_t* q, const int32_t* focus_idx, const int32_t* counts, int n_focus_max, const float* kbar,
+                                     const focus_shape& s, float* part, bool per_head, hipStream_t st) {
   const int n_b = ceil_div(s.n_ctx, s.block);
+  const dim3 grid = grid_x_yz(ceil_div(s.n_heads, kRelGroup), ceil_div(n_b, kRelPasses * (512 / D)));
+  if (per_head)
+    hipLaunchKernelGGL((relevance_partial_kernel<D, true>), grid, dim3(256), 0, st, focus_idx, kbar, counts, q, s.q_stride_h,
+                       s.q_stride_n, n_b, s.n_heads, n_focus_max, s.n_gen, part);
+  else
+    hipLaunchKernelGGL((relevance_partial_kernel<D, false>), grid, dim3(256), 0, st, focus_idx, kbar, counts, q, s.q_stride_h,
+                       s.q_stride_n, n_b, s.n_heads, n_focus_max, s.n_gen, part);
+}
+
+hipError_t launch_block_relevance(const void* Q, const int32_t* focus_idx, const int32_t* counts, int n_focus_max,
+                                  const float* kbar, const focus_shape& s, float* part, bool per_head, hipStream_t st) {
   const uint16_t* q = static_cast<const uint16_t*>(Q);
   if (s.head_dim == 128)
-    hipLaunchKernelGGL(relevance_partial_kernel<128>, grid_x_yz(s.n_heads, ceil_div(n_b, 32)), dim3(256), 0, st, focus_idx,
-                       kbar, counts, q, s.q_stride_h, s.q_stride_n, n_b, n_focus_max, s.n_gen, part);
+    launch_block_relevance_t<128>(q, focus_idx, counts, n_focus_max, kbar, s, part, per_head, st);
   else
-    hipLaunchKernelGGL(relevance_partial_kernel<64>, grid_x_yz(s.n_heads, ceil_div(n_b, 64)), dim3(256), 0, st, focus_idx,
-                       kbar, counts, q, s.q_stride_h, s.q_stride_n, n_b, n_focus_max, s.n_gen, part);
+    launch_block_relevance_t<64>(q, focus_idx, counts, n_focus_max, kbar, s, part, per_head, st);
   return hipGetLastError();
 }
 

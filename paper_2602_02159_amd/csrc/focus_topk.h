@@ -21,6 +21,7 @@
 #pragma once
 
 #include "focus_common.h"
+#include "focus_kernels.h"
 
 namespace focus {
 
@@ -37,25 +38,39 @@ __device__ __forceinline__ float order_value(uint32_t key) {
   return __uint_as_float((key & 0x80000000u) ? key & 0x7fffffffu : ~key);
 }
 
-// sum over the n_parts per-head partial values of element j, always part by part in ascending order (the loads go out 32, then
-// 8, then 1 at a time) so that every kernel that assembles block relevances gets bit-identical results; continues from part h
-// with the sum acc of the parts before it
-__device__ __forceinline__ float sum_partials(const float* __restrict__ part, int n_parts, int n, int j, int h = 0, float acc = 0.f) {
-  for (; h + 32 <= n_parts; h += 32) {  // 32 independent loads: one memory round trip for 32 heads
+// Sum over the heads of element j's partial values, in the one order that every kernel which assembles block relevances uses: the
+// heads of a group of kRelGroup one after the other, then the groups one after the other.  grouped: part[i] is already the sum of
+// group i; else part[i] belongs to one head.  Continues behind the first `done` parts (a multiple of kRelGroup heads), whose sum is acc.
+__device__ __forceinline__ float sum_partials(const float* __restrict__ part, int n_parts, bool grouped, int n, int j, int done = 0,
+                                              float acc = 0.f) {
+  int h = done;
+  if (grouped) {
+    for (; h + 8 <= n_parts; h += 8) {  // 32 heads: one memory round trip
+      float v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = part[(int64_t)(h + u) * n + j];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) acc += v[u];
+    }
+    for (; h < n_parts; ++h) acc += part[(int64_t)h * n + j];
+    return acc;
+  }
+  for (; h + 32 <= n_parts; h += 32) {
     float v[32];
 #pragma unroll
     for (int u = 0; u < 32; ++u) v[u] = part[(int64_t)(h + u) * n + j];
 #pragma unroll
-    for (int u = 0; u < 32; ++u) acc += v[u];
+    for (int u = 0; u < 32; u += kRelGroup) acc += ((v[u] + v[u + 1]) + v[u + 2]) + v[u + 3];
   }
-  for (; h + 8 <= n_parts; h += 8) {
-    float v[8];
+  for (; h < n_parts; h += kRelGroup) {
+    float v[kRelGroup];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = part[(int64_t)(h + u) * n + j];
+    for (int u = 0; u < kRelGroup; ++u) v[u] = part[(int64_t)min(h + u, n_parts - 1) * n + j];
+    float g = v[0];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) acc += v[u];
+    for (int u = 1; u < kRelGroup; ++u) g = h + u < n_parts ? g + v[u] : g;
+    acc += g;
   }
-  for (; h < n_parts; ++h) acc += part[(int64_t)h * n + j];
   return acc;
 }
 

@@ -509,6 +509,8 @@ def test_probe_layer(G, H, M, N, d, B, n_gen, n_act, n_sink):
     (4, 2048, 32, 64, 32, 80, 8, 72, 30, 40),         # five query tiles (two groups of four), d = 64, unsorted sinks
     (3, 1500, 10, 64, 50, 40, 4, 20, 12, 33),         # two query tiles, d = 64, ragged blocks
     (2, 16384, 64, 128, 64, 64, 4, 36, 128, 163),     # the paper's proportions at 16K: half the blocks, 1 % sinks
+    (37, 1000, 8, 128, 64, 100, 90, 10, 5, 3),        # more than eight groups of heads, more than 64 focus rows
+    (33, 2000, 8, 64, 64, 100, 33, 40, 5, 3),
 ])
 def test_sparse_layer_equals_block_scores_then_sparse_attn(G, H, M, N, d, B, n_gen, n_f, n_act, n_keep, n_sink):
     rng = np.random.default_rng(M + n_keep)
