@@ -336,7 +336,7 @@ static int sparse_layer_impl(const char* who, const void* Q, const int32_t* focu
   float* part_o = reinterpret_cast<float*>(ws + w.attn + w.at.part_o);
   float* part_ml = reinterpret_cast<float*>(ws + w.attn + w.at.part_ml);
   hipError_t e;
-  const bool fused = n_b <= kFusedMaxBlocks && n_keep > 0;
+  const bool fused = n_b <= (kbar ? kFusedMaxBlocks : kFusedMaxBlocksPerHead) && n_keep > 0;
   if (!kbar)
     e = launch_block_means_relevance(K, Q, focus_idx, counts, n_focus_max, *shape, nullptr, part, st);
   else

@@ -112,8 +112,8 @@ hipError_t launch_qk_logits(const void* Q, const int32_t* active_idx, const int3
                             const void* K, const focus_shape& s, const SplitPlan& p, int mode, float* logits,
                             float* part_ml, const float* lse2, float* colpart, hipStream_t st, const SelectArgs* select = nullptr);
 // Extra arguments of the fused layer path: the attention kernel ranks the blocks itself from the per-head partial
-// relevances (n_b <= kFusedMaxBlocks).
-constexpr int kFusedMaxBlocks = 256;
+// relevances (n_b <= kFusedMaxBlocks; kFusedMaxBlocksPerHead if they come per head from a K scan).
+constexpr int kFusedMaxBlocks = 1024, kFusedMaxBlocksPerHead = 256;
 struct FusedTopC {
   const float* rel_part;  // [ceil(H / 4), n_b] from launch_block_relevance, or with per_head [H, n_b]
   bool per_head;

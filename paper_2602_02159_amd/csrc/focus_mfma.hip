@@ -476,48 +476,73 @@ __device__ __forceinline__ AttnArgs with_first(AttnArgs p, ATTN_FIRST_PARAMS) {
                      (a).n_gen, (a).n_split, (a).n_sub, a)
 
 // What the attention kernels prepare before their first K/V request.
-// R_b = (1 / (|I_focus| H)) sum_h qsum^h . kbar^h_b for b = threadIdx.x (n_b <= 256 <= blockDim.x), then Top-C into kept_sh; the
-// workgroup with `writer` set also writes scores and kept blocks out.  First use of `sm`.  `first` holds the loads of the first
-// NP parts (first_partials), which the caller requests before it waits for anything: 32 heads in groups of four are 8 parts.
-template <int NP>
-__device__ __forceinline__ void first_partials(float (&first)[NP], const AttnArgs& p, bool per_head) {
-  const uint32_t b = min((int)threadIdx.x, p.n_b - 1);  // n_b <= 256: small offsets
+// R_b = (1 / (|I_focus| H)) sum_h qsum^h . kbar^h_b, then Top-C into kept_sh; the workgroup with `writer` set also writes scores
+// and kept blocks out.  First use of `sm`.  Thread t of THREADS ranks the blocks t, t + THREADS, ...; n_b <= kFusedMaxBlocks.
+// FirstParts holds the loads of the first NP parts (32 heads in groups of four are 8 parts), which the caller requests before it
+// waits for anything.  MANY: n_b > 256, ranked by block_topk_planes — half of 512 or 30 of 1024 blocks in less time than the launch
+// of a kernel that ranks them once takes (sparse layer at 128K 34.7 -> 31.2 us, of 512 64-row blocks 62.6 -> 61.5); else the
+// tournament of block_topk_small.
+template <int NP, int THREADS, bool MANY>
+struct FirstParts {
+  static constexpr int kPlanes = MANY ? kFusedMaxBlocks / THREADS : 1;
+  float part[kPlanes][NP];
+};
+template <int NP, int THREADS, bool MANY>
+__device__ __forceinline__ void first_partials(FirstParts<NP, THREADS, MANY>& f, const AttnArgs& p, bool per_head) {
   const int last = (per_head ? p.H : (p.H + kRelGroup - 1) / kRelGroup) - 1;
 #pragma unroll
-  for (int i = 0; i < NP; ++i) first[i] = p.rel_part[(uint32_t)(min(i, last) * p.n_b) + b];
+  for (int l = 0; l < f.kPlanes; ++l) {
+    const uint32_t b = min((int)threadIdx.x + l * THREADS, p.n_b - 1);  // n_b <= 1024: small offsets
+#pragma unroll
+    for (int i = 0; i < NP; ++i) f.part[l][i] = p.rel_part[(uint32_t)(min(i, last) * p.n_b) + b];
+  }
   __builtin_amdgcn_sched_barrier(0);  // (the scheduler would move the wait for the row ids in front of these loads)
 }
-template <int NP>
-__device__ __forceinline__ void rank_blocks(const AttnArgs& p, const float (&first)[NP], bool per_head, int32_t* kept_sh, TopkShared& sm,
-                                            bool writer) {
+template <int NP, int THREADS, bool MANY>
+__device__ __forceinline__ void rank_blocks(const AttnArgs& p, const FirstParts<NP, THREADS, MANY>& f, bool per_head, int32_t* kept_sh,
+                                            TopkShared& sm, bool writer) {
+  constexpr int kPlanes = FirstParts<NP, THREADS, MANY>::kPlanes;
   const int tid = threadIdx.x;
-  float r = 0.f;  // the order of sum_partials
-  if (per_head) {
-#pragma unroll
-    for (int h = 0; h < NP; h += kRelGroup) {
-      float g = first[h];
-#pragma unroll
-      for (int i = 1; i < kRelGroup; ++i) g = h + i < p.H ? g + first[h + i] : g;
-      r = h < p.H ? r + g : r;
-    }
-    if (p.H > NP && tid < p.n_b) r = sum_partials(p.rel_part, p.H, false, p.n_b, tid, NP, r);
-  } else {
-    const int n_groups = (p.H + kRelGroup - 1) / kRelGroup;
-#pragma unroll
-    for (int g = 0; g < NP; ++g) r = g < n_groups ? r + first[g] : r;
-    if (n_groups > NP && tid < p.n_b) r = sum_partials(p.rel_part, n_groups, true, p.n_b, tid, NP, r);
-  }
   const int n_f = p.counts ? min(max(p.counts[0], 0), p.n_focus_max) : p.n_focus_max;
-  r *= n_f > 0 ? 1.f / ((float)n_f * (float)p.H) : 0.f;
-  auto keyfn = [=](int, uint32_t& key) -> bool {
-    key = order_key(r);
-    return true;
-  };
-  block_topk<kFusedMaxBlocks, true>(keyfn, p.n_b, p.n_keep, kept_sh, nullptr, nullptr, sm);
-  if (writer) {
-    if (p.scores_out && tid < p.n_b) p.scores_out[tid] = r;
-    if (tid < p.n_keep) p.kept_out[tid] = kept_sh[tid];
+  const float scale = n_f > 0 ? 1.f / ((float)n_f * (float)p.H) : 0.f;
+  const int n_groups = (p.H + kRelGroup - 1) / kRelGroup;
+  float rel[kPlanes];
+#pragma unroll
+  for (int l = 0; l < kPlanes; ++l) {
+    const float(&part)[NP] = f.part[l];
+    const int b = tid + l * THREADS;
+    float r = 0.f;  // in the order of sum_partials
+    if (per_head) {
+#pragma unroll
+      for (int h = 0; h < NP; h += kRelGroup) {
+        float g = part[h];
+#pragma unroll
+        for (int i = 1; i < kRelGroup; ++i) g = h + i < p.H ? g + part[h + i] : g;
+        r = h < p.H ? r + g : r;
+      }
+      if (p.H > NP && b < p.n_b) r = sum_partials(p.rel_part, p.H, false, p.n_b, b, NP, r);
+    } else {
+#pragma unroll
+      for (int g = 0; g < NP; ++g) r = g < n_groups ? r + part[g] : r;
+      if (n_groups > NP && b < p.n_b) r = sum_partials(p.rel_part, n_groups, true, p.n_b, b, NP, r);
+    }
+    rel[l] = r * scale;
+    if (writer && p.scores_out && b < p.n_b) p.scores_out[b] = rel[l];
   }
+  if (MANY) {
+    uint32_t key1[kPlanes];
+#pragma unroll
+    for (int l = 0; l < kPlanes; ++l) key1[l] = tid + l * THREADS < p.n_b ? order_key(rel[l]) + 1u : 0u;
+    block_topk_planes<kPlanes, THREADS>(key1, p.n_keep, kept_sh, sm);
+  } else {
+    auto keyfn = [&](int, uint32_t& key) -> bool {
+      key = order_key(rel[0]);
+      return true;
+    };
+    block_topk<256, true>(keyfn, p.n_b, p.n_keep, kept_sh, nullptr, nullptr, sm);
+  }
+  if (writer)
+    for (int i = tid; i < p.n_keep; i += THREADS) p.kept_out[i] = kept_sh[i];
 }
 
 // Workgroups whose key range reaches the sink sub-tiles prepare the union of Eq. 8 once: a bitmap of the kept blocks, and
@@ -567,6 +592,7 @@ __device__ __forceinline__ SinkUnion prepare_union(const AttnArgs& p, int split,
 // FUSE bit 0 set (fused layer path): the workgroup first assembles R_b from the per-head partial relevances and ranks
 // them itself — every workgroup repeats this small computation instead of waiting for a separate Top-C kernel.
 // FUSE bit 3 set (with bit 0): the partial relevances come per head, from a K scan, and not per group of four heads.
+// FUSE bit 4 set (with bit 0): more than 256 blocks to rank.
 // FUSE bit 2 set (dense probe layer): the scaled logits of every (query, key) are also written out, so that
 // the column attention mass of Eq. 6 needs no QK^T pass of its own.
 // FUSE bit 1 set: double-buffered key loop for launches in which a wavefront walks several sub-tiles
@@ -583,6 +609,7 @@ __global__ __launch_bounds__(256, (FUSE & 2) == 0 ? 2 : 1) void sparse_attn_kern
   constexpr bool PIPE = (FUSE & 2) != 0;                 // two K/V stages per wavefront
   constexpr bool SPILL = (FUSE & 4) != 0;                // dense: also write the scaled logits (sink scoring)
   constexpr bool PER_HEAD = (FUSE & 8) != 0;             // FUSED: partial relevances per head, not per group of heads
+  constexpr bool MANY = (FUSE & 16) != 0;                // FUSED: more than 256 blocks
   constexpr int kBufBytes = 2 * G::kStageBytes;          // one slot: K stage + V stage of a sub-tile
   static_assert(16 * D * 4 <= kBufBytes, "a wavefront's O tile fits its stage");
   // Two buffers of four slots; the second exists in the double-buffered variant only.
@@ -602,7 +629,7 @@ __global__ __launch_bounds__(256, (FUSE & 2) == 0 ? 2 : 1) void sparse_attn_kern
 
   __shared__ __attribute__((aligned(16))) char topk_raw[FUSED ? sizeof(TopkShared) : 16];
   TopkShared& topk_sm = *reinterpret_cast<TopkShared*>(topk_raw);
-  __shared__ int32_t kept_sh[FUSED ? kFusedMaxBlocks : 1];
+  __shared__ int32_t kept_sh[MANY ? kFusedMaxBlocks : (FUSED ? 256 : 1)];
   const int32_t* kept_blocks = p.kept_blocks;
   // With the Top-C prologue ahead, the query rows are requested before it (their two round trips — row ids, then rows —
   // pass while the relevances are summed and ranked); without it they follow the first K/V requests (see below).
@@ -610,7 +637,7 @@ __global__ __launch_bounds__(256, (FUSE & 2) == 0 ? 2 : 1) void sparse_attn_kern
   int qrow_early = -1, few_sinks = -1;
   if (FUSED) {
     qrow_early = fetch_q_row(p.active_idx, 0, p.max_active, p.n_gen, lane);
-    float first[PER_HEAD ? 32 : 8];
+    FirstParts<PER_HEAD ? 32 : 8, 256, MANY> first;
     first_partials(first, p, PER_HEAD);
     few_sinks = request_few_sinks(p, lane);
     load_q_tile<D>(q[0], Qh, p.qsn, qrow_early, lane);
@@ -870,7 +897,7 @@ __device__ __forceinline__ void store_o_tile(char* dst, const floatx16 (&o)[D / 
 // slot, the next sub-tile's rows travel while the current one is multiplied, one workgroup per compute unit; without it (NT =
 // 1) the operands are all read into registers before the next sub-tile is requested into the same stage, and two workgroups
 // per compute unit cover each other: better where several query groups share rows in the L2 and the loads return fast.
-// Bit 3: the rows are read by several query groups and should stay in the L2.
+// Bit 3: the rows are read by several query groups and should stay in the L2.  Bit 4 (with bit 0): more than 256 blocks to rank.
 // Bound by HBM.  32 heads, 32 832 keys, all kept: 89 us with 30 queries (6.0 TB/s; 16-query tiles on shared sub-tiles took 94),
 // 95 us with 60 (101); half of the 64-row blocks and 327 sinks: 53 us (57); 4 K/V heads, 196 queries, 16 640 keys: 28 us (42).
 // Grid: one-dimensional.  Workgroups go to the XCDs round-robin, so the query groups of one (head, key split) pair are
@@ -879,7 +906,7 @@ template <int D, int NT, int MODE>
 __global__ __launch_bounds__(256 * NT, NT == 2 || (MODE & 4) == 0 ? 2 : 1) void wide_attn_kernel(ATTN_FIRST_PARAMS, const AttnArgs args) {
   const AttnArgs p = with_first(args, ATTN_FIRST_NAMES);
   using G = Geo<D>;
-  constexpr bool FUSED = (MODE & 1) != 0, PIPE = (MODE & 2) != 0, DOUBLE = (MODE & 4) != 0;
+  constexpr bool FUSED = (MODE & 1) != 0, PIPE = (MODE & 2) != 0, DOUBLE = (MODE & 4) != 0, MANY = (MODE & 16) != 0;
   static_assert(!DOUBLE || PIPE, "two stages are for the key loop");
   static_assert(NT == 1 || DOUBLE || !PIPE, "a shared slot needs the second stage");
   constexpr int kPolicy = (MODE & 8) != 0 ? 0 : kStreamPolicy;
@@ -891,7 +918,7 @@ __global__ __launch_bounds__(256 * NT, NT == 2 || (MODE & 4) == 0 ? 2 : 1) void 
   __shared__ __attribute__((aligned(16))) char ldsB[DOUBLE ? kWavesPerGroup * kBufBytes : 16];
   __shared__ float2 ml_sh[kWavesPerGroup][32];
   __shared__ __attribute__((aligned(16))) char topk_raw[FUSED ? sizeof(TopkShared) : 16];
-  __shared__ int32_t kept_sh[FUSED ? kFusedMaxBlocks : 1];
+  __shared__ int32_t kept_sh[MANY ? kFusedMaxBlocks : (FUSED ? 256 : 1)];
   __shared__ uint32_t kept_bits_sh[kBitmapBlocks / 32];
   __shared__ int sinks_unsorted_sh;
 
@@ -923,7 +950,7 @@ __global__ __launch_bounds__(256 * NT, NT == 2 || (MODE & 4) == 0 ? 2 : 1) void 
   const int32_t* kept_blocks = p.kept_blocks;
   int few_sinks;
   if (FUSED) {  // the query rows travel while the blocks are ranked
-    float first[8];  // (per head, from a K scan: the other parts are requested when they are added)
+    FirstParts<8, 256 * NT, MANY> first;  // (per head, from a K scan: the other parts are requested when they are added)
     first_partials(first, p, p.rel_per_head);
     few_sinks = request_few_sinks(p, lane);
     load_q();
@@ -1163,7 +1190,12 @@ template <int D, int NT, int LOOP>
 static void launch_wide_t(const AttnArgs& a, const SplitPlan& p, bool fused, hipStream_t st) {
   const dim3 grid(ceil_div(p.n_split * a.H, 8) * 8 * p.q_groups), block(256 * NT);
   constexpr int kKeep = LOOP & 8;
-  if (fused && p.pipelined)
+  const bool many = a.n_b > 256;
+  if (fused && p.pipelined && many)
+    ATTN_LAUNCH((wide_attn_kernel<D, NT, LOOP | 17>), grid, block, st, a);
+  else if (fused && many)
+    ATTN_LAUNCH((wide_attn_kernel<D, NT, kKeep | 17>), grid, block, st, a);
+  else if (fused && p.pipelined)
     ATTN_LAUNCH((wide_attn_kernel<D, NT, LOOP | 1>), grid, block, st, a);
   else if (fused)
     ATTN_LAUNCH((wide_attn_kernel<D, NT, kKeep | 1>), grid, block, st, a);
@@ -1191,7 +1223,11 @@ static hipError_t launch_attn_t(const AttnArgs& a, const SplitPlan& p, bool fuse
       ATTN_LAUNCH((sparse_attn_kernel<D, 6>), grid, block, st, a);
     else
       ATTN_LAUNCH((sparse_attn_kernel<D, 4>), grid, block, st, a);
-  } else if (fused && p.pipelined && a.rel_per_head)
+  } else if (fused && p.pipelined && a.n_b > 256)
+    ATTN_LAUNCH((sparse_attn_kernel<D, 19>), grid, block, st, a);
+  else if (fused && a.n_b > 256)
+    ATTN_LAUNCH((sparse_attn_kernel<D, 17>), grid, block, st, a);
+  else if (fused && p.pipelined && a.rel_per_head)
     ATTN_LAUNCH((sparse_attn_kernel<D, 11>), grid, block, st, a);
   else if (fused && p.pipelined)
     ATTN_LAUNCH((sparse_attn_kernel<D, 3>), grid, block, st, a);

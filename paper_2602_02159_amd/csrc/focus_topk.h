@@ -211,6 +211,104 @@ __device__ __forceinline__ bool wave_select1(uint32_t key1, int k, uint32_t& pos
   return sel;
 }
 
+// Top-k among P planes of THREADS keys (thread t holds the keys of the candidates i THREADS + t, i < P; key + 1, or 0 for none),
+// same order and tie rule as wave_topk, by a workgroup of 4 or 8 wavefronts: the k-th largest key is found two bits at a time —
+// every wavefront counts its keys against three thresholds with ballots, the counts meet in LDS —, and the bits that all keys
+// share are skipped.  Writes out[0 .. k) in ascending order, tail -1.  `sm` must be free on entry; ends with a barrier.
+template <int P, int THREADS>
+__device__ __forceinline__ void block_topk_planes(const uint32_t (&key1)[P], int k_want, int32_t* out, TopkShared& sm) {
+  constexpr int W = THREADS / kWave;
+  static_assert(W == 4 || W == 8, "an entry per lane of a DPP half row");
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, entry = lane & (W - 1);
+  const unsigned long long below = (1ull << lane) - 1ull;
+  auto over_waves = [](uint32_t x, auto op) {  // the W entries that neighbouring lanes have read
+    x = op(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xB1, 0xF, 0xF, false));  // quad_perm [1,0,3,2]
+    x = op(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x4E, 0xF, 0xF, false));  // quad_perm [2,3,0,1]
+    if (W == 8) x = op(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x141, 0xF, 0xF, false));  // row_half_mirror
+    return x;
+  };
+  auto add = [](uint32_t a, uint32_t b) { return a + b; };
+  auto both = [](uint32_t a, uint32_t b) { return a & b; };
+  auto either = [](uint32_t a, uint32_t b) { return a | b; };
+  uint4* counts = reinterpret_cast<uint4*>(sm.keys);                      // [2 parities][W]
+  uint4* stats = counts + 2 * W;                                          // [W]: AND, OR, number of candidates
+  uint2* totals = reinterpret_cast<uint2*>(stats + W);                    // [P][W]: keys above and at the threshold
+  static_assert((3 * W * 16 + P * W * 8) <= (int)sizeof(sm.keys), "fits");
+  uint32_t all = 0xffffffffu, any = 0u, n_mine = 0;
+#pragma unroll
+  for (int i = 0; i < P; ++i) {
+    all &= key1[i] != 0u ? key1[i] : 0xffffffffu;
+    any |= key1[i];
+    n_mine += (uint32_t)__popcll(__ballot(key1[i] != 0u));
+  }
+  all = wave_reduce_u32(all, both);
+  any = wave_reduce_u32(any, either);
+  if (lane == 0) stats[wave] = make_uint4(all, any, n_mine, 0u);
+  __syncthreads();
+  const uint4 st = stats[entry];
+  all = __builtin_amdgcn_readfirstlane(over_waves(st.x, both));
+  any = __builtin_amdgcn_readfirstlane(over_waves(st.y, either));
+  const uint32_t n_valid = __builtin_amdgcn_readfirstlane(over_waves(st.z, add));
+  const uint32_t k = min((uint32_t)max(k_want, 0), n_valid);
+  uint32_t T = 0u;  // the k-th largest key, or one less than a threshold that exactly k keys reach; 0: all of them
+  if (k == 0u) {
+    T = 0xffffffffu;
+  } else if (k < n_valid) {
+    const int top = all == any ? -1 : 31 - (int)__clz((int)(all ^ any));  // -1: all keys are equal
+    T = top < 0 ? all : (top == 31 ? 0u : all & ~((2u << top) - 1u));
+    for (int hi = top, parity = 0; hi >= 0; hi -= 2, parity ^= 1) {  // bits hi and hi - 1 (bit 0 alone in the last round of an odd count)
+      const uint32_t step = hi > 0 ? 1u << (hi - 1) : 1u;
+      uint32_t c1 = 0, c2 = 0, c3 = 0;
+#pragma unroll
+      for (int i = 0; i < P; ++i) {
+        c1 += (uint32_t)__popcll(__ballot(key1[i] >= (T | step)));
+        c2 += (uint32_t)__popcll(__ballot(key1[i] >= (T | (2u * step))));
+        c3 += (uint32_t)__popcll(__ballot(key1[i] >= (T | (3u * step))));
+      }
+      if (lane == 0) counts[parity * W + wave] = make_uint4(c1, c2, c3, 0u);
+      __syncthreads();  // (the other parity's counts may still be read by slower wavefronts)
+      const uint4 row = counts[parity * W + entry];
+      const uint32_t s1 = __builtin_amdgcn_readfirstlane(over_waves(row.x, add)), s2 = __builtin_amdgcn_readfirstlane(over_waves(row.y, add)),
+                     s3 = __builtin_amdgcn_readfirstlane(over_waves(row.z, add));
+      uint32_t j = 0, cnt = 0;  // the largest threshold that at least k keys reach
+      if (s1 >= k) { j = 1; cnt = s1; }
+      if (hi > 0 && s2 >= k) { j = 2; cnt = s2; }
+      if (hi > 0 && s3 >= k) { j = 3; cnt = s3; }
+      T |= j * step;
+      if (cnt == k) {  // exactly these: "key > T" selects them and none equal to T is needed
+        T -= 1u;
+        break;
+      }
+    }
+  }
+  unsigned long long gt[P], eq[P];
+#pragma unroll
+  for (int i = 0; i < P; ++i) {
+    gt[i] = __ballot(key1[i] > T);
+    eq[i] = __ballot(key1[i] == T && key1[i] != 0u);
+    if (lane == 0) totals[i * W + wave] = make_uint2((uint32_t)__popcll(gt[i]), (uint32_t)__popcll(eq[i]));
+  }
+  __syncthreads();
+  uint32_t gt_base[P], eq_base[P], gt_total = 0, eq_total = 0;  // keys before this wavefront's in plane i
+#pragma unroll
+  for (int i = 0; i < P; ++i) {
+    const uint2 t = totals[i * W + entry];
+    gt_base[i] = gt_total + over_waves(entry < wave ? t.x : 0u, add);
+    eq_base[i] = eq_total + over_waves(entry < wave ? t.y : 0u, add);
+    gt_total += over_waves(t.x, add);
+    eq_total += over_waves(t.y, add);
+  }
+  const uint32_t need = k - min(gt_total, k);  // keys equal to T still to take, lowest candidates first
+#pragma unroll
+  for (int i = 0; i < P; ++i) {
+    const uint32_t eq_rank = eq_base[i] + (uint32_t)__popcll(eq[i] & below);
+    if (key1[i] > T || (key1[i] == T && key1[i] != 0u && eq_rank < need))
+      out[gt_base[i] + (uint32_t)__popcll(gt[i] & below) + min(eq_rank, need)] = i * THREADS + tid;
+  }
+  for (int i = (int)k + tid; i < k_want; i += THREADS) out[i] = -1;
+  __syncthreads();
+}
+
 // KeyFn: bool operator()(int i, uint32_t& key) const — false when i is not a candidate.
 // Top-k of n <= blockDim.x candidates (thread i supplies candidate i).  Same contract as block_topk; kept apart so
 // that kernels which only ever see small n do not carry the radix-select code (these kernels start with a cold

@@ -503,7 +503,12 @@ def test_probe_layer(G, H, M, N, d, B, n_gen, n_act, n_sink):
     (8, 4096, 64, 128, 128, 64, 16, 16, 5, 4),        # 32 blocks, several splits per head
     (3, 3000, 40, 128, 48, 48, 5, 40, 9, 7),          # ragged, three query tiles
     (2, 16384, 64, 128, 64, 64, 16, 16, 25, 4),       # exactly 256 blocks: the largest fused case
-    (2, 8192, 64, 128, 16, 64, 16, 16, 40, 4),        # 512 blocks: falls back to the separate kernels
+    (2, 8192, 64, 128, 16, 64, 16, 16, 40, 4),        # 512 blocks
+    (2, 16385, 64, 64, 64, 64, 16, 16, 30, 4),        # one block more than a workgroup has threads
+    (2, 8208, 0, 64, 16, 64, 4, 50, 257, 40),         # 513 blocks, two query tiles per slot
+    (1, 16384, 64, 128, 16, 64, 4, 20, 1024, 5),      # the most blocks that are ranked inside the attention kernel, all kept
+    (5, 16384, 7, 64, 16, 64, 9, 30, 500, 90),
+    (2, 16400, 64, 64, 16, 64, 9, 30, 11, 3),         # ... and one more
     (2, 2048, 0, 64, 128, 16, 3, 16, 16, 0),          # every block kept, no response rows, no sinks
     (4, 4096, 64, 128, 64, 64, 8, 28, 20, 6),         # two query tiles per workgroup, Top-C inside the kernel
     (4, 2048, 32, 64, 32, 80, 8, 72, 30, 40),         # five query tiles (two groups of four), d = 64, unsorted sinks
