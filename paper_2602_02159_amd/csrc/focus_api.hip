@@ -34,7 +34,11 @@ constexpr int kAttnGroups = 512;      // one sub-tile per slot: every workgroup 
 constexpr int kAttnGroupsPipe = 256;  // many sub-tiles per slot, two stages per slot: one workgroup per compute unit
 constexpr int kAttnGroupsWide = 512;  // the same where query groups share the rows: one stage per slot, two workgroups per compute unit
 constexpr int kLogitGroups = 4096;    // sink scoring, one query tile: measured best of 1024 .. 8192 (short workgroups even out the tail of the scan)
-constexpr int kLogitGroupsMany = 2048;  // several query tiles: every workgroup first loads all their rows
+// Two passes over K (more than 16 queries): every workgroup first fetches its query rows.  33 to 64 queries per group: as many
+// workgroups as are resident at once, three per compute unit.  Up to 32: four are; more of them even out the tail of a long scan,
+// as long as each has four rounds of sub-tiles.
+constexpr int kLogitGroupsMany = 768;
+constexpr int kLogitGroupsTwo = 2048, kLogitGroupsTwoMin = 512, kLogitRoundsTwo = 4;
 
 // `most`: 16-query tiles per query group at most.  q_pad is the same for every `most`: the rows of per-query results.
 static void plan_queries(SplitPlan& p, int max_active, int most) {
@@ -80,7 +84,12 @@ SplitPlan plan_logits(const focus_shape& s, int max_active) {
   SplitPlan p;
   plan_queries(p, max_active, kMaxQTilesPerGroup);
   p.n_sub = ceil_div(s.n_ctx + s.n_resp, kSubTile);
-  plan_splits(p, s.n_heads, p.q_groups, p.q_tiles_per_group > 1 ? kLogitGroupsMany : kLogitGroups);
+  plan_splits(p, s.n_heads, p.q_groups,
+              p.q_tiles_per_group == 1 ? kLogitGroups : (p.q_tiles_per_group == 2 ? kLogitGroupsTwo : kLogitGroupsMany));
+  if (p.q_tiles_per_group == 2) {
+    const int rounds = p.n_sub / kWavesPerGroup;
+    p.n_split = std::min(p.n_split, std::max(std::max(1, kLogitGroupsTwoMin / s.n_heads), rounds / kLogitRoundsTwo));
+  }
   return p;
 }
 

@@ -291,21 +291,17 @@ __device__ __forceinline__ void mask_q_tile(bf16x8 (&q)[Geo<D>::kKSteps], int q0
 }
 
 // ---------------------------------------------------------------------------------------- tile math
-// S^T tiles of one staged K sub-tile against NQT query tiles: acc[qt][kt][r] = logit of key 16kt + 4g + r.
-template <int D, int NQT>
-__device__ __forceinline__ void qk_subtile(floatx4 (&acc)[NQT][2], const char* stageK,
-                                           const bf16x8 (&q)[NQT][Geo<D>::kKSteps], int lane) {
+// S^T tiles of one staged K sub-tile: acc[kt][r] = logit of key 16kt + 4g + r.
+template <int D>
+__device__ __forceinline__ void qk_subtile(floatx4 (&acc)[2], const char* stageK, const bf16x8 (&q)[Geo<D>::kKSteps], int lane) {
   const int c = lane & 15, g = lane >> 4;
 #pragma unroll
   for (int kt = 0; kt < 2; ++kt) {
-#pragma unroll
-    for (int qt = 0; qt < NQT; ++qt) acc[qt][kt] = floatx4{0.f, 0.f, 0.f, 0.f};
+    acc[kt] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int kk = 0; kk < Geo<D>::kKSteps; ++kk) {
       const bf16x8 a = as_bf16x8(*reinterpret_cast<const uint4*>(stageK + stage_off<D>(kt * 16 + c, kk * 4 + g)));
-#pragma unroll
-      for (int qt = 0; qt < NQT; ++qt)
-        acc[qt][kt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, q[qt][kk], acc[qt][kt], 0, 0, 0);
+      acc[kt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, q[kk], acc[kt], 0, 0, 0);
     }
   }
 }
@@ -633,14 +629,14 @@ __global__ __launch_bounds__(256, (FUSE & 2) == 0 ? 2 : 1) void sparse_attn_kern
   const int32_t* kept_blocks = p.kept_blocks;
   // With the Top-C prologue ahead, the query rows are requested before it (their two round trips — row ids, then rows —
   // pass while the relevances are summed and ranked); without it they follow the first K/V requests (see below).
-  bf16x8 q[1][G::kKSteps];
+  bf16x8 q[G::kKSteps];
   int qrow_early = -1, few_sinks = -1;
   if (FUSED) {
     qrow_early = fetch_q_row(p.active_idx, 0, p.max_active, p.n_gen, lane);
     FirstParts<PER_HEAD ? 32 : 8, 256, MANY> first;
     first_partials(first, p, PER_HEAD);
     few_sinks = request_few_sinks(p, lane);
-    load_q_tile<D>(q[0], Qh, p.qsn, qrow_early, lane);
+    load_q_tile<D>(q, Qh, p.qsn, qrow_early, lane);
     rank_blocks(p, first, PER_HEAD, kept_sh, topk_sm, blockIdx.x == 0 && blockIdx.y == 0);
     kept_blocks = kept_sh;
   } else {
@@ -670,9 +666,9 @@ __global__ __launch_bounds__(256, (FUSE & 2) == 0 ? 2 : 1) void sparse_attn_kern
       issue_subtile<D>(Vh, p.vsn, t, stageV, lane);
     }
   }
-  if (!FUSED) load_q_tile<D>(q[0], Qh, p.qsn, qrow, lane);
+  if (!FUSED) load_q_tile<D>(q, Qh, p.qsn, qrow, lane);
   const int n_act = p.counts ? min(max(p.counts[1], 0), p.max_active) : p.max_active;
-  mask_q_tile<D>(q[0], 0, n_act, lane);
+  mask_q_tile<D>(q, 0, n_act, lane);
 
   float m_run = -INFINITY, l_run = 0.f;
   floatx4 o[G::kColTiles];
@@ -682,14 +678,14 @@ __global__ __launch_bounds__(256, (FUSE & 2) == 0 ? 2 : 1) void sparse_attn_kern
   bool first = true;
   floatx4 kept_logits[2];  // SPILL: the raw logits of the sub-tile just multiplied, written out by the caller (see the key loops)
   auto consume = [&](const char* sK, const char* sV, uint32_t vmask, int row0) __attribute__((always_inline)) {  // one staged sub-tile into the running softmax
-    floatx4 acc[1][2];
-    qk_subtile<D, 1>(acc, sK, q, lane);
+    floatx4 acc[2];
+    qk_subtile<D>(acc, sK, q, lane);
     if (SPILL) {
-      kept_logits[0] = acc[0][0];
-      kept_logits[1] = acc[0][1];
+      kept_logits[0] = acc[0];
+      kept_logits[1] = acc[1];
     }
     float ps[8];
-    const float alpha = softmax_step(acc[0], vmask, g, p.scale_log2, m_run, l_run, ps);
+    const float alpha = softmax_step(acc, vmask, g, p.scale_log2, m_run, l_run, ps);
     // the running maximum settles after a few sub-tiles: the rescale is skipped when it would multiply by one
     if (!first && __ballot(alpha != 1.f) != 0ull) {
 #pragma unroll
@@ -1810,15 +1806,32 @@ __device__ __forceinline__ unsigned long long select_positions(const SelectArgs&
   }
   return active;
 }
+// the same; lane a of `row` receives the a-th active position (a < their number, which is returned)
+__device__ __forceinline__ int select_rows(const SelectArgs& s, int n_gen, int max_active, int lane, bool writer, int& row) {
+  const unsigned long long active = select_positions(s, n_gen, max_active, lane, writer);
+  const unsigned long long below = (1ull << lane) - 1ull;
+  const int n = (int)__popcll(active);
+  // the active lanes go to the front, the others behind them
+  const int to = ((active >> lane) & 1ull) ? (int)__popcll(active & below) : n + (int)__popcll(~active & below);
+  row = __builtin_amdgcn_ds_permute(to << 2, lane);
+  return n;
+}
 
-// MODE 0: the scaled logits are written out (for up to 16 queries re-reading 64 bytes per key and head is cheaper
-//         than a second pass over K) together with the per-split softmax statistics.
-// MODE 1: statistics only.
-// MODE 2: second pass for more than 16 queries: with the row log-sum-exps known, the probabilities are formed on the
-//         fly and summed over the workgroup's queries; colpart[qg * H + h, j] = sum_i P[h, i, j].
+// keys [32 st, 32 st + 32) of the first L
+__device__ __forceinline__ SubTile key_subtile(int st, int L) {
+  SubTile t;
+  t.kind = 0;
+  t.sink_row = 0;
+  t.row0 = st * kSubTile;
+  t.vmask = low_mask(min(L - t.row0, kSubTile));
+  return t;
+}
+
+// Up to 16 active queries: the scaled logits are written out (re-reading 64 bytes per key and head is cheaper than a second pass
+// over K) together with the per-split softmax statistics.
 // SELECT: every wavefront makes the query selection itself, beside its first K rows, instead of reading what a launch of its own
-//         has written; the first workgroup writes the lists for everyone else (a step of 4 heads at 1K: one launch of 3 us less).
-template <int D, int NQT, int MODE, bool SELECT>
+// has written; the first workgroup writes the lists for everyone else (a step of 4 heads at 1K: one launch of 3 us less).
+template <int D, bool SELECT>
 __global__ __launch_bounds__(256, 2) void qk_logits_kernel(const uint16_t* K, int64_t ksh, int64_t ksn, const int32_t* active_idx, int L,
                                                            int n_sub, int n_split, int max_active, int n_gen, const LogitArgs args) {
   LogitArgs p = args;  // what the first requests need comes in registers, as in the attention kernels
@@ -1833,158 +1846,300 @@ __global__ __launch_bounds__(256, 2) void qk_logits_kernel(const uint16_t* K, in
   p.n_gen = n_gen;
   using G = Geo<D>;
   __shared__ __attribute__((aligned(16))) char lds[kWavesPerGroup * G::kStageBytes];
-  __shared__ float ml_sh[kWavesPerGroup][NQT][16][2];
+  __shared__ float ml_sh[kWavesPerGroup][16][2];
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c = lane & 15, g = lane >> 4;
-  const int split = blockIdx.x, h = blockIdx.y, qg = blockIdx.z;
-  const int q_base = qg * NQT * kQTile;
+  const int split = blockIdx.x, h = blockIdx.y;
   char* stageK = lds + wave * G::kStageBytes;
   const uint16_t* Qh = p.Q + (int64_t)h * p.qsh;
   const uint16_t* Kh = p.K + (int64_t)h * p.ksh;
 
   int st = split * kWavesPerGroup + wave;
   const int st_end = p.n_sub, st_step = p.n_split * kWavesPerGroup;
-  auto tile_of = [&](int s) {
-    SubTile t;
-    t.kind = 0;
-    t.sink_row = 0;
-    t.row0 = s * kSubTile;
-    t.vmask = low_mask(min(p.L - t.row0, kSubTile));
-    return t;
-  };
-  int qrow[NQT];
-  if (!SELECT) {
-#pragma unroll
-    for (int qt = 0; qt < NQT; ++qt) qrow[qt] = fetch_q_row(p.active_idx, q_base + qt * kQTile, p.max_active, p.n_gen, lane);
-  }
-  SubTile t = tile_of(st < st_end ? st : 0);
+  int qrow = -1;
+  if (!SELECT) qrow = fetch_q_row(p.active_idx, 0, p.max_active, p.n_gen, lane);
+  SubTile t = key_subtile(st < st_end ? st : 0, p.L);
   if (st < st_end) issue_subtile<D>(Kh, p.ksn, t, stageK, lane);
-  int n_sel = 0;
+  int n_act;
   if (SELECT) {
-    __shared__ int row_sh[kWavesPerGroup][kWave];  // active positions in order, per wavefront
-    const unsigned long long active = select_positions(p.sel, p.n_gen, p.max_active, lane, wave == 0 && (split | h | qg) == 0);
-    if ((active >> lane) & 1ull) row_sh[wave][__popcll(active & ((1ull << lane) - 1ull))] = lane;
-    n_sel = (int)__popcll(active);
-#pragma unroll
-    for (int qt = 0; qt < NQT; ++qt) {
-      const int a = q_base + qt * kQTile + c;
-      qrow[qt] = a < n_sel ? row_sh[wave][a & (kWave - 1)] : -1;
-    }
+    int row;
+    n_act = select_rows(p.sel, p.n_gen, p.max_active, lane, wave == 0 && (split | h) == 0, row);
+    row = __shfl(row, c, kWave);
+    qrow = c < n_act ? row : -1;
   }
 
-  bf16x8 q[NQT][G::kKSteps];
-#pragma unroll
-  for (int qt = 0; qt < NQT; ++qt) load_q_tile<D>(q[qt], Qh, p.qsn, qrow[qt], lane);
-  const int n_act = SELECT ? n_sel : (p.counts ? min(max(p.counts[1], 0), p.max_active) : p.max_active);
-#pragma unroll
-  for (int qt = 0; qt < NQT; ++qt) mask_q_tile<D>(q[qt], q_base + qt * kQTile, n_act, lane);
+  bf16x8 q[G::kKSteps];
+  load_q_tile<D>(q, Qh, p.qsn, qrow, lane);
+  if (!SELECT) n_act = p.counts ? min(max(p.counts[1], 0), p.max_active) : p.max_active;
+  mask_q_tile<D>(q, 0, n_act, lane);
 
-  float m_run[NQT], l_run[NQT];
-  float neg_lse[NQT];  // MODE 2: minus the row's log-sum-exp; -inf for rows that do not exist
-#pragma unroll
-  for (int qt = 0; qt < NQT; ++qt) {
-    m_run[qt] = -INFINITY;
-    l_run[qt] = 0.f;
-    neg_lse[qt] = 0.f;
-    if (MODE == 2) {
-      const int a = q_base + qt * kQTile + c;
-      const float z = p.lse2[(int64_t)h * p.q_pad + a];
-      neg_lse[qt] = (a < n_act && z < INFINITY) ? -z : -INFINITY;  // exp2(x - inf) = 0: the row contributes nothing
-    }
-  }
-
+  float m_run = -INFINITY, l_run = 0.f;
   while (st < st_end) {
     const SubTile cur = t;
     wait_loads();
-    floatx4 acc[NQT][2];
-    qk_subtile<D, NQT>(acc, stageK, q, lane);
+    floatx4 acc[2];
+    qk_subtile<D>(acc, stageK, q, lane);
     // the staged rows are consumed: the next sub-tile can stream in while the results are written
     st += st_step;
     if (st < st_end) {
-      t = tile_of(st);
+      t = key_subtile(st, p.L);
       wait_lds_reads();
       issue_subtile<D>(Kh, p.ksn, t, stageK, lane);
     }
-    if (MODE == 2) {
-      float colsum[8];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) colsum[e] = 0.f;
-#pragma unroll
-      for (int qt = 0; qt < NQT; ++qt) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-          colsum[e] += __builtin_amdgcn_exp2f(__builtin_fmaf(acc[qt][e >> 2][e & 3], p.scale_log2, neg_lse[qt]));
-      }
-#pragma unroll
-      for (int e = 0; e < 8; ++e) colsum[e] = row_sum16(colsum[e]);
-      if (c == 0) {
-        float* dst = p.colpart + ((int64_t)qg * p.H + h) * p.L + cur.row0;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const int slot = 16 * (e >> 2) + 4 * g + (e & 3);
-          if ((cur.vmask >> slot) & 1u) dst[slot] = colsum[e];
-        }
-      }
-    } else {
-#pragma unroll
-      for (int qt = 0; qt < NQT; ++qt) {
-        float ps[8];
-        softmax_step(acc[qt], cur.vmask, g, p.scale_log2, m_run[qt], l_run[qt], ps);
-        if (MODE == 0) spill_logits(p.logits, h, p.L, cur.row0, acc[qt], p.scale_log2, lane);  // one query tile (NQT == 1)
-      }
-    }
+    float ps[8];
+    softmax_step(acc, cur.vmask, g, p.scale_log2, m_run, l_run, ps);
+    spill_logits(p.logits, h, p.L, cur.row0, acc, p.scale_log2, lane);
   }
-  if (MODE == 2) return;
 
   if (g == 0) {
-#pragma unroll
-    for (int qt = 0; qt < NQT; ++qt) {
-      ml_sh[wave][qt][c][0] = m_run[qt];
-      ml_sh[wave][qt][c][1] = l_run[qt];
-    }
+    ml_sh[wave][c][0] = m_run;
+    ml_sh[wave][c][1] = l_run;
   }
   __syncthreads();
-  if (threadIdx.x < NQT * 16) {
-    const int qt = threadIdx.x >> 4, qc = threadIdx.x & 15;
+  if (threadIdx.x < 16) {
     float mmax = -INFINITY;
 #pragma unroll
-    for (int w = 0; w < kWavesPerGroup; ++w) mmax = fmaxf(mmax, ml_sh[w][qt][qc][0]);
+    for (int w = 0; w < kWavesPerGroup; ++w) mmax = fmaxf(mmax, ml_sh[w][threadIdx.x][0]);
     float lsum = 0.f;
 #pragma unroll
     for (int w = 0; w < kWavesPerGroup; ++w) {
-      const float l = ml_sh[w][qt][qc][1];
-      if (l > 0.f) lsum += l * __builtin_amdgcn_exp2f(ml_sh[w][qt][qc][0] - mmax);
+      const float l = ml_sh[w][threadIdx.x][1];
+      if (l > 0.f) lsum += l * __builtin_amdgcn_exp2f(ml_sh[w][threadIdx.x][0] - mmax);
     }
-    const int64_t row = ((int64_t)h * p.q_pad + q_base + qt * kQTile + qc) * p.n_split + split;
+    const int64_t row = ((int64_t)h * p.q_pad + threadIdx.x) * p.n_split + split;
     p.part_ml[2 * row] = lsum > 0.f ? mmax : -INFINITY;
     p.part_ml[2 * row + 1] = lsum;
   }
 }
 
-template <int D, int NQT>
-static hipError_t launch_logits_t(const LogitArgs& a, const SplitPlan& p, int mode, bool select, hipStream_t st) {
-  dim3 grid(p.n_split, a.H, p.q_groups);
-#define LOGITS_LAUNCH(MODE, SELECT)                                                                                        \
-  hipLaunchKernelGGL((qk_logits_kernel<D, NQT, MODE, SELECT>), grid, dim3(256), 0, st, a.K, a.ksh, a.ksn, a.active_idx, a.L, a.n_sub, \
-                     a.n_split, a.max_active, a.n_gen, a)
-  if constexpr (NQT == 1) {  // one tile spills its logits, several take two passes
-    if (mode != 0) return hipErrorInvalidValue;
-    if (select)
-      LOGITS_LAUNCH(0, true);
-    else
-      LOGITS_LAUNCH(0, false);
-  } else {
-    if (mode == 0) return hipErrorInvalidValue;
-    if (mode == 2)
-      LOGITS_LAUNCH(2, false);
-    else if (select)
-      LOGITS_LAUNCH(1, true);
-    else
-      LOGITS_LAUNCH(1, false);
+// More than 16 active queries: spilling 64 floats and more per key and head would outweigh K, so K is scanned twice.
+// MODE 1: per-split softmax statistics.
+// MODE 2: with the row log-sum-exps known, the probabilities are formed on the fly and summed over the workgroup's queries;
+//         colpart[qg * H + h, j] = sum_i P[h, i, j].
+// A workgroup has NT tiles of 32 queries (32x32x16 MFMA) and four slots, one per wavefront, which walk the key sub-tiles; the
+// operands of a sub-tile are read from its slot once, into registers, and the next one is requested before they are multiplied.
+// MODE 1 computes K Q^T (a lane holds one query's logits: the running maximum is one exchange), MODE 2 Q K^T (a lane holds one
+// key's probabilities: the sum over the queries stays in its registers).  Tiles past the device-side count are skipped.
+// SELECT (MODE 1) as in qk_logits_kernel.
+// Grid as in wide_attn_kernel: the query groups of one (head, key split) pair run on one XCD and share its rows there.
+// 32 heads, 32 832 keys, both passes and what follows them: 113 -> 106 us with 28 of 36 queries (bound by HBM), 8 256 keys, 60
+// queries 69 -> 44; 4 K/V heads, 16 640 keys, 196 queries 64 -> 36; 8 K/V heads, 60 064 keys, 400 queries 330 -> 198 (16-query tiles,
+// each wavefront fetching all query rows, query groups far apart in time).
+template <int D, int NT, int MODE, bool SELECT>
+__global__ __launch_bounds__(256, NT == 1 ? 4 : 2) void wide_logits_kernel(const uint16_t* K, int64_t ksh, int64_t ksn,
+                                                                           const int32_t* active_idx, int L, int n_sub, int n_split,
+                                                                           int max_active, int n_gen, int q_groups, const LogitArgs args) {
+  LogitArgs p = args;
+  p.K = K;
+  p.ksh = ksh;
+  p.ksn = ksn;
+  p.active_idx = active_idx;
+  p.L = L;
+  p.n_sub = n_sub;
+  p.n_split = n_split;
+  p.max_active = max_active;
+  p.n_gen = n_gen;
+  using G = Geo<D>;
+  constexpr int kKS = D / 16;
+  __shared__ __attribute__((aligned(16))) char lds[kWavesPerGroup * G::kStageBytes];
+  __shared__ __attribute__((aligned(16))) char stageQ[NT * G::kStageBytes];
+  float2 (*ml_sh)[NT * 32] = reinterpret_cast<float2 (*)[NT * 32]>(stageQ);  // [4][NT * 32], once the queries are in registers
+  static_assert(kWavesPerGroup * sizeof(float2) * 32 <= G::kStageBytes, "fits");
+
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int qi = lane & 31, hh = lane >> 5;
+  const int slot8 = (int)blockIdx.x >> 3;
+  const int pair = (slot8 / q_groups) * 8 + (int)(blockIdx.x & 7u), qg = slot8 % q_groups;
+  if (pair >= n_split * p.H) return;  // whole workgroup
+  const int h = pair / n_split, split = pair - h * n_split;
+  const int q_base = qg * NT * 32;
+  char* stageK = lds + wave * G::kStageBytes;
+  const uint16_t* Qh = p.Q + (int64_t)h * p.qsh;
+  const uint16_t* Kh = p.K + (int64_t)h * p.ksh;
+
+  int st = split * kWavesPerGroup + wave;
+  const int st_end = p.n_sub, st_step = p.n_split * kWavesPerGroup;
+  // The query rows go through LDS, a quarter per wavefront: four wavefronts fetching all of them moved more bytes than K where
+  // a wavefront walks a handful of sub-tiles.  Staged like K rows; load i of a wavefront covers kRowsPerLoad rows.
+  constexpr int kQLoads = NT * 32 / (kWavesPerGroup * G::kRowsPerLoad);
+  const int q_sub = lane / G::kChunks, q_pos = lane % G::kChunks;
+  int qrow[kQLoads];
+  bool live[NT];  // this lane's query of tile n exists
+  if (!SELECT) {
+#pragma unroll
+    for (int i = 0; i < kQLoads; ++i) {
+      const int a = q_base + (wave * kQLoads + i) * G::kRowsPerLoad + q_sub;
+      qrow[i] = a < p.max_active ? p.active_idx[a] : 0;
+    }
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+      const int a = q_base + n * 32 + qi, row = a < p.max_active ? p.active_idx[a] : -1;
+      live[n] = row >= 0 && row < p.n_gen;
+    }
   }
-#undef LOGITS_LAUNCH
+  SubTile t = key_subtile(st < st_end ? st : 0, p.L);
+  if (st < st_end) issue_subtile<D>(Kh, p.ksn, t, stageK, lane);
+  int n_act;
+  if (SELECT) {
+    int row;
+    n_act = select_rows(p.sel, p.n_gen, p.max_active, lane, wave == 0 && (pair | qg) == 0, row);
+#pragma unroll
+    for (int i = 0; i < kQLoads; ++i) {
+      const int a = q_base + (wave * kQLoads + i) * G::kRowsPerLoad + q_sub, r = __shfl(row, a & (kWave - 1), kWave);
+      qrow[i] = a < n_act ? r : 0;
+    }
+  } else {
+    n_act = p.counts ? min(max(p.counts[1], 0), p.max_active) : p.max_active;
+  }
+  {
+    typedef const __attribute__((address_space(1))) void* gptr_t;
+    typedef __attribute__((address_space(3))) void* lptr_t;
+#pragma unroll
+    for (int i = 0; i < kQLoads; ++i) {
+      const int slot = (wave * kQLoads + i) * G::kRowsPerLoad + q_sub;
+      const uint16_t* src = Qh + (int64_t)min(max(qrow[i], 0), p.n_gen - 1) * p.qsn + (q_pos ^ (slot & (G::kChunks - 1))) * 8;
+      __builtin_amdgcn_global_load_lds((gptr_t)src, (lptr_t)(stageQ + (wave * kQLoads + i) * 1024), 16, 0, 0);
+    }
+  }
+  float neg_lse[MODE == 2 ? NT : 1][16];  // MODE 2: minus the log-sum-exp of query 8 (v / 4) + 4 hh + v % 4; -inf for rows that do not exist
+  if (MODE == 2) {
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int a = q_base + n * 32 + 8 * (v >> 2) + 4 * hh + (v & 3);
+        const float z = p.lse2[(int64_t)h * p.q_pad + min(a, p.q_pad - 1)];
+        neg_lse[n][v] = (a < n_act && z < INFINITY) ? -z : -INFINITY;  // exp2(x - inf) = 0: the row contributes nothing
+      }
+    }
+  }
+  wait_loads();
+  __syncthreads();
+  bf16x8 q[NT][kKS];  // lane (query, hh) holds Q[query][16 ks + 8 hh .. + 7]
+#pragma unroll
+  for (int n = 0; n < NT; ++n) {
+    const bool exists = q_base + n * 32 + qi < n_act && (SELECT || live[n]);
+#pragma unroll
+    for (int ks = 0; ks < kKS; ++ks) {
+      const uint4 v = *reinterpret_cast<const uint4*>(stageQ + n * G::kStageBytes + stage_off<D>(qi, 2 * ks + hh));
+      q[n][ks] = as_bf16x8(exists ? v : make_uint4(0u, 0u, 0u, 0u));
+    }
+  }
+
+  float m_run[NT], l_run[NT];  // MODE 1; l_run: this lane's share of the row sum (its 16 of every 32 keys)
+#pragma unroll
+  for (int n = 0; n < NT; ++n) {
+    m_run[n] = -INFINITY;
+    l_run[n] = 0.f;
+  }
+  while (st < st_end) {
+    const SubTile cur = t;
+    wait_loads();
+    bf16x8 kop[kKS];
+#pragma unroll
+    for (int ks = 0; ks < kKS; ++ks) kop[ks] = as_bf16x8(*reinterpret_cast<const uint4*>(stageK + stage_off<D>(qi, 2 * ks + hh)));
+    st += st_step;
+    wait_lds_reads();
+    if (st < st_end) {
+      t = key_subtile(st, p.L);
+      issue_subtile<D>(Kh, p.ksn, t, stageK, lane);
+    }
+    float colsum = 0.f;
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+      if (n > 0 && q_base + n * 32 >= n_act) break;  // uniform
+      floatx16 acc;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+#pragma unroll
+      for (int ks = 0; ks < kKS; ++ks)
+        acc = MODE == 1 ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(kop[ks], q[n][ks], acc, 0, 0, 0)
+                        : __builtin_amdgcn_mfma_f32_32x32x16_bf16(q[n][ks], kop[ks], acc, 0, 0, 0);
+      if (MODE == 2) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) colsum += __builtin_amdgcn_exp2f(__builtin_fmaf(acc[v], p.scale_log2, neg_lse[n][v]));
+      } else {
+        if (cur.vmask != 0xffffffffu) {  // wave-uniform: slots that hold no key
+#pragma unroll
+          for (int v = 0; v < 16; ++v) acc[v] = ((cur.vmask >> (8 * (v >> 2) + 4 * hh + (v & 3))) & 1u) ? acc[v] : -INFINITY;
+        }
+        float mx = fmaxf(acc[0], acc[1]);
+#pragma unroll
+        for (int v = 2; v < 16; ++v) mx = fmaxf(mx, acc[v]);
+        const uintx2 sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+        const float m_new = fmaxf(m_run[n], fmaxf(__uint_as_float(sw.x), __uint_as_float(sw.y)) * p.scale_log2);
+        const float m_use = m_new == -INFINITY ? 0.f : m_new;
+        l_run[n] *= __builtin_amdgcn_exp2f(m_run[n] - m_use);
+        m_run[n] = m_new;
+        float sum[2] = {0.f, 0.f};
+#pragma unroll
+        for (int v = 0; v < 16; ++v) sum[v & 1] += __builtin_amdgcn_exp2f(__builtin_fmaf(acc[v], p.scale_log2, -m_use));
+        l_run[n] += sum[0] + sum[1];
+      }
+    }
+    if (MODE == 2) {
+      const uintx2 sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(colsum), __float_as_uint(colsum), false, false);
+      if (hh == 0 && ((cur.vmask >> qi) & 1u))
+        p.colpart[((int64_t)qg * p.H + h) * p.L + cur.row0 + qi] = __uint_as_float(sw.x) + __uint_as_float(sw.y);
+    }
+  }
+  if (MODE == 2) return;
+
+  __syncthreads();  // every wavefront has its queries in registers: stageQ is free for the statistics
+#pragma unroll
+  for (int n = 0; n < NT; ++n) {
+    const uintx2 sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(l_run[n]), __float_as_uint(l_run[n]), false, false);
+    if (hh == 0) ml_sh[wave][n * 32 + qi] = make_float2(m_run[n], __uint_as_float(sw.x) + __uint_as_float(sw.y));
+  }
+  __syncthreads();
+  if (threadIdx.x < NT * 32) {
+    float mmax = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < kWavesPerGroup; ++w) mmax = fmaxf(mmax, ml_sh[w][threadIdx.x].x);
+    float lsum = 0.f;
+#pragma unroll
+    for (int w = 0; w < kWavesPerGroup; ++w) {
+      const float2 v = ml_sh[w][threadIdx.x];
+      if (v.y > 0.f) lsum += v.y * __builtin_amdgcn_exp2f(v.x - mmax);
+    }
+    if (q_base + (int)threadIdx.x < p.q_pad) {
+      const int64_t row = ((int64_t)h * p.q_pad + q_base + threadIdx.x) * p.n_split + split;
+      *reinterpret_cast<float2*>(p.part_ml + 2 * row) = make_float2(lsum > 0.f ? mmax : -INFINITY, lsum);
+    }
+  }
+}
+
+template <int D>
+static hipError_t launch_logits_t(const LogitArgs& a, const SplitPlan& p, int mode, bool select, hipStream_t st) {
+#define LOGITS_ARGS a.K, a.ksh, a.ksn, a.active_idx, a.L, a.n_sub, a.n_split, a.max_active, a.n_gen
+  if (p.q_tiles_per_group == 1) {  // one tile spills its logits, several take two passes
+    if (mode != 0) return hipErrorInvalidValue;
+    const dim3 grid(p.n_split, a.H);
+    if (select)
+      hipLaunchKernelGGL((qk_logits_kernel<D, true>), grid, dim3(256), 0, st, LOGITS_ARGS, a);
+    else
+      hipLaunchKernelGGL((qk_logits_kernel<D, false>), grid, dim3(256), 0, st, LOGITS_ARGS, a);
+    return hipGetLastError();
+  }
+  if (mode == 0) return hipErrorInvalidValue;
+  const dim3 grid(ceil_div(p.n_split * a.H, 8) * 8 * p.q_groups);
+#define WIDE_LOGITS(NT)                                                                                                 \
+  if (mode == 2)                                                                                                        \
+    hipLaunchKernelGGL((wide_logits_kernel<D, NT, 2, false>), grid, dim3(256), 0, st, LOGITS_ARGS, p.q_groups, a);      \
+  else if (select)                                                                                                      \
+    hipLaunchKernelGGL((wide_logits_kernel<D, NT, 1, true>), grid, dim3(256), 0, st, LOGITS_ARGS, p.q_groups, a);       \
+  else                                                                                                                  \
+    hipLaunchKernelGGL((wide_logits_kernel<D, NT, 1, false>), grid, dim3(256), 0, st, LOGITS_ARGS, p.q_groups, a)
+  if (p.q_tiles_per_group == 2) {
+    WIDE_LOGITS(1);
+  } else {
+    WIDE_LOGITS(2);
+  }
+#undef WIDE_LOGITS
+#undef LOGITS_ARGS
   return hipGetLastError();
 }
 
@@ -2008,15 +2163,7 @@ hipError_t launch_qk_logits(const void* Q, const int32_t* active_idx, const int3
   a.H = s.n_heads; a.L = s.n_ctx + s.n_resp; a.n_gen = s.n_gen; a.max_active = max_active;
   a.n_sub = p.n_sub; a.n_split = p.n_split; a.q_pad = p.q_pad;
   a.scale_log2 = kLog2e / sqrtf((float)s.head_dim);
-  const int nqt = p.q_tiles_per_group;
-  if (s.head_dim == 128) {
-    if (nqt == 1) return launch_logits_t<128, 1>(a, p, mode, select != nullptr, st);
-    if (nqt == 2) return launch_logits_t<128, 2>(a, p, mode, select != nullptr, st);
-    return launch_logits_t<128, 4>(a, p, mode, select != nullptr, st);
-  }
-  if (nqt == 1) return launch_logits_t<64, 1>(a, p, mode, select != nullptr, st);
-  if (nqt == 2) return launch_logits_t<64, 2>(a, p, mode, select != nullptr, st);
-  return launch_logits_t<64, 4>(a, p, mode, select != nullptr, st);
+  return s.head_dim == 128 ? launch_logits_t<128>(a, p, mode, select != nullptr, st) : launch_logits_t<64>(a, p, mode, select != nullptr, st);
 }
 
 }  // namespace focus

@@ -154,6 +154,9 @@ def test_top_c_ties_go_to_the_lower_block(G):
 # ------------------------------------------------------------------------------------------------ stage 2b
 @pytest.mark.parametrize("H,M,N,d,n_gen,n_act,n_sink", [(2, 300, 20, 64, 16, 5, 3), (4, 1000, 40, 128, 40, 16, 10),
                                                         (3, 2050, 33, 128, 80, 72, 20), (2, 4096, 0, 64, 32, 17, 41),
+                                                        (5, 1003, 9, 128, 90, 62, 7),      # two query groups, the second past the count
+                                                        (2, 3001, 10, 64, 140, 129, 20),   # ... three, the last with one query
+                                                        (40, 2100, 5, 128, 40, 29, 5), (4, 70, 0, 128, 64, 33, 3),
                                                         (2, 32768, 64, 64, 32, 16, 327),   # the paper's 1 % rule at 32K
                                                         (2, 20000, 10, 64, 64, 28, 200),   # ragged last group, two passes
                                                         (1, 4096, 0, 64, 16, 4, 44),       # 1.4 per 128-key group: the most the bound-then-select path takes
