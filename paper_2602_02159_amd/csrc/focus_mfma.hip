@@ -475,9 +475,9 @@ __device__ __forceinline__ AttnArgs with_first(AttnArgs p, ATTN_FIRST_PARAMS) {
 // R_b = (1 / (|I_focus| H)) sum_h qsum^h . kbar^h_b, then Top-C into kept_sh; the workgroup with `writer` set also writes scores
 // and kept blocks out.  First use of `sm`.  Thread t of THREADS ranks the blocks t, t + THREADS, ...; n_b <= kFusedMaxBlocks.
 // FirstParts holds the loads of the first NP parts (32 heads in groups of four are 8 parts), which the caller requests before it
-// waits for anything.  MANY: n_b > 256, ranked by block_topk_planes — half of 512 or 30 of 1024 blocks in less time than the launch
-// of a kernel that ranks them once takes (sparse layer at 128K 34.7 -> 31.2 us, of 512 64-row blocks 62.6 -> 61.5); else the
-// tournament of block_topk_small.
+// waits for anything.  MANY: n_b > 256.  Few blocks to keep of up to 256: the tournament of block_topk_small; else
+// block_topk_planes.  Repeating it in every workgroup takes less time than the launch of a kernel that ranks the blocks once
+// (sparse layer at 128K, 30 of 1024 blocks, 34.7 -> 29.0 us; half of 512 64-row blocks 63.2 -> 60.1).
 template <int NP, int THREADS, bool MANY>
 struct FirstParts {
   static constexpr int kPlanes = MANY ? kFusedMaxBlocks / THREADS : 1;
@@ -499,6 +499,11 @@ __device__ __forceinline__ void rank_blocks(const AttnArgs& p, const FirstParts<
                                             TopkShared& sm, bool writer) {
   constexpr int kPlanes = FirstParts<NP, THREADS, MANY>::kPlanes;
   const int tid = threadIdx.x;
+  const bool tournament = !MANY && p.n_keep * (THREADS / kWave) <= kWave;  // uniform
+  if (!tournament) {
+    block_topk_clear<THREADS>(sm);
+    __syncthreads();
+  }
   const int n_f = p.counts ? min(max(p.counts[0], 0), p.n_focus_max) : p.n_focus_max;
   const float scale = n_f > 0 ? 1.f / ((float)n_f * (float)p.H) : 0.f;
   const int n_groups = (p.H + kRelGroup - 1) / kRelGroup;
@@ -525,17 +530,17 @@ __device__ __forceinline__ void rank_blocks(const AttnArgs& p, const FirstParts<
     rel[l] = r * scale;
     if (writer && p.scores_out && b < p.n_b) p.scores_out[b] = rel[l];
   }
-  if (MANY) {
-    uint32_t key1[kPlanes];
-#pragma unroll
-    for (int l = 0; l < kPlanes; ++l) key1[l] = tid + l * THREADS < p.n_b ? order_key(rel[l]) + 1u : 0u;
-    block_topk_planes<kPlanes, THREADS>(key1, p.n_keep, kept_sh, sm);
-  } else {
+  if (tournament) {
     auto keyfn = [&](int, uint32_t& key) -> bool {
       key = order_key(rel[0]);
       return true;
     };
-    block_topk<256, true>(keyfn, p.n_b, p.n_keep, kept_sh, nullptr, nullptr, sm);
+    block_topk_small<256, true>(keyfn, p.n_b, p.n_keep, kept_sh, nullptr, sm);
+  } else {
+    uint32_t key1[kPlanes];
+#pragma unroll
+    for (int l = 0; l < kPlanes; ++l) key1[l] = tid + l * THREADS < p.n_b ? order_key(rel[l]) + 1u : 0u;
+    block_topk_planes<kPlanes, THREADS>(key1, p.n_b, p.n_keep, kept_sh, sm);
   }
   if (writer)
     for (int i = tid; i < p.n_keep; i += THREADS) p.kept_out[i] = kept_sh[i];

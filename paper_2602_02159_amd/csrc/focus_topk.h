@@ -211,77 +211,70 @@ __device__ __forceinline__ bool wave_select1(uint32_t key1, int k, uint32_t& pos
   return sel;
 }
 
-// Top-k among P planes of THREADS keys (thread t holds the keys of the candidates i THREADS + t, i < P; key + 1, or 0 for none),
-// same order and tie rule as wave_topk, by a workgroup of 4 or 8 wavefronts: the k-th largest key is found two bits at a time —
-// every wavefront counts its keys against three thresholds with ballots, the counts meet in LDS —, and the bits that all keys
-// share are skipped.  Writes out[0 .. k) in ascending order, tail -1.  `sm` must be free on entry; ends with a barrier.
+// Inclusive prefix sum over the 64 lanes of a wavefront: shifts within the DPP rows of 16, then the rows' totals.
+__device__ __forceinline__ uint32_t wave_prefix_sum(uint32_t x) {
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, true);  // row_shr:1
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, true);  // row_shr:2
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, true);  // row_shr:4
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, true);  // row_shr:8
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xA, 0xF, true);  // row_bcast:15 into rows 1 and 3
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xC, 0xF, true);  // row_bcast:31 into rows 2 and 3
+  return x;
+}
+
+// Top-k among n keys in P planes of THREADS (thread t holds the keys of the candidates i THREADS + t, i < P; key + 1, 0 only past
+// n), same order and tie rule as wave_topk, by a workgroup of 4 or 8 wavefronts: a radix search of the k-th largest key, eight
+// bits per pass.  A pass is one LDS atomic per key and one barrier; every wavefront then scans the 256 counts by itself, four per
+// lane.  It ends as soon as exactly k keys reach a digit, after two passes as a rule.  Writes out[0 .. k) ascending, tail -1.
+// `sm.keys` must have been zeroed (block_topk_clear, visible after a barrier); ends with a barrier.
+template <int THREADS>
+__device__ __forceinline__ void block_topk_clear(TopkShared& sm) {
+  static_assert(sizeof(sm.keys) % (16 * THREADS) == 0 || 16 * THREADS > sizeof(sm.keys), "whole vectors");
+  if ((int)threadIdx.x * 16 < (int)sizeof(sm.keys)) reinterpret_cast<uint4*>(sm.keys)[threadIdx.x] = make_uint4(0u, 0u, 0u, 0u);
+}
 template <int P, int THREADS>
-__device__ __forceinline__ void block_topk_planes(const uint32_t (&key1)[P], int k_want, int32_t* out, TopkShared& sm) {
+__device__ __forceinline__ void block_topk_planes(const uint32_t (&key1)[P], int n, int k_want, int32_t* out, TopkShared& sm) {
   constexpr int W = THREADS / kWave;
   static_assert(W == 4 || W == 8, "an entry per lane of a DPP half row");
+  static_assert(sizeof(sm.keys) == 4 * 256 * sizeof(uint32_t), "a histogram per pass");
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, entry = lane & (W - 1);
   const unsigned long long below = (1ull << lane) - 1ull;
-  auto over_waves = [](uint32_t x, auto op) {  // the W entries that neighbouring lanes have read
-    x = op(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xB1, 0xF, 0xF, false));  // quad_perm [1,0,3,2]
-    x = op(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x4E, 0xF, 0xF, false));  // quad_perm [2,3,0,1]
-    if (W == 8) x = op(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x141, 0xF, 0xF, false));  // row_half_mirror
-    return x;
-  };
-  auto add = [](uint32_t a, uint32_t b) { return a + b; };
-  auto both = [](uint32_t a, uint32_t b) { return a & b; };
-  auto either = [](uint32_t a, uint32_t b) { return a | b; };
-  uint4* counts = reinterpret_cast<uint4*>(sm.keys);                      // [2 parities][W]
-  uint4* stats = counts + 2 * W;                                          // [W]: AND, OR, number of candidates
-  uint2* totals = reinterpret_cast<uint2*>(stats + W);                    // [P][W]: keys above and at the threshold
-  static_assert((3 * W * 16 + P * W * 8) <= (int)sizeof(sm.keys), "fits");
-  uint32_t all = 0xffffffffu, any = 0u, n_mine = 0;
+  const uint32_t k = (uint32_t)min(max(k_want, 0), n);
+  uint32_t T = k == 0u ? 0xffffffffu : 0u;  // the k-th largest key, or one less than a threshold that exactly k keys reach; 0: all
+  if (k > 0u && k < (uint32_t)n) {
+    uint32_t above = 0;  // keys whose leading digits exceed T's
 #pragma unroll
-  for (int i = 0; i < P; ++i) {
-    all &= key1[i] != 0u ? key1[i] : 0xffffffffu;
-    any |= key1[i];
-    n_mine += (uint32_t)__popcll(__ballot(key1[i] != 0u));
-  }
-  all = wave_reduce_u32(all, both);
-  any = wave_reduce_u32(any, either);
-  if (lane == 0) stats[wave] = make_uint4(all, any, n_mine, 0u);
-  __syncthreads();
-  const uint4 st = stats[entry];
-  all = __builtin_amdgcn_readfirstlane(over_waves(st.x, both));
-  any = __builtin_amdgcn_readfirstlane(over_waves(st.y, either));
-  const uint32_t n_valid = __builtin_amdgcn_readfirstlane(over_waves(st.z, add));
-  const uint32_t k = min((uint32_t)max(k_want, 0), n_valid);
-  uint32_t T = 0u;  // the k-th largest key, or one less than a threshold that exactly k keys reach; 0: all of them
-  if (k == 0u) {
-    T = 0xffffffffu;
-  } else if (k < n_valid) {
-    const int top = all == any ? -1 : 31 - (int)__clz((int)(all ^ any));  // -1: all keys are equal
-    T = top < 0 ? all : (top == 31 ? 0u : all & ~((2u << top) - 1u));
-    for (int hi = top, parity = 0; hi >= 0; hi -= 2, parity ^= 1) {  // bits hi and hi - 1 (bit 0 alone in the last round of an odd count)
-      const uint32_t step = hi > 0 ? 1u << (hi - 1) : 1u;
-      uint32_t c1 = 0, c2 = 0, c3 = 0;
+    for (int pass = 0; pass < 4; ++pass) {
+      const int shift = 24 - 8 * pass;
+      uint32_t* hist = sm.keys + 256 * pass;
 #pragma unroll
-      for (int i = 0; i < P; ++i) {
-        c1 += (uint32_t)__popcll(__ballot(key1[i] >= (T | step)));
-        c2 += (uint32_t)__popcll(__ballot(key1[i] >= (T | (2u * step))));
-        c3 += (uint32_t)__popcll(__ballot(key1[i] >= (T | (3u * step))));
-      }
-      if (lane == 0) counts[parity * W + wave] = make_uint4(c1, c2, c3, 0u);
-      __syncthreads();  // (the other parity's counts may still be read by slower wavefronts)
-      const uint4 row = counts[parity * W + entry];
-      const uint32_t s1 = __builtin_amdgcn_readfirstlane(over_waves(row.x, add)), s2 = __builtin_amdgcn_readfirstlane(over_waves(row.y, add)),
-                     s3 = __builtin_amdgcn_readfirstlane(over_waves(row.z, add));
-      uint32_t j = 0, cnt = 0;  // the largest threshold that at least k keys reach
-      if (s1 >= k) { j = 1; cnt = s1; }
-      if (hi > 0 && s2 >= k) { j = 2; cnt = s2; }
-      if (hi > 0 && s3 >= k) { j = 3; cnt = s3; }
-      T |= j * step;
-      if (cnt == k) {  // exactly these: "key > T" selects them and none equal to T is needed
-        T -= 1u;
+      for (int i = 0; i < P; ++i)
+        if (key1[i] != 0u && (pass == 0 || (key1[i] >> ((shift + 8) & 31)) == T)) atomicAdd(&hist[(key1[i] >> shift) & 255u], 1u);
+      __syncthreads();
+      const uint4 h = reinterpret_cast<const uint4*>(hist)[lane];  // digits 4 lane .. 4 lane + 3
+      const uint32_t sum = (h.x + h.y) + (h.z + h.w), incl = wave_prefix_sum(sum);
+      const uint32_t need = k - above;
+      const uint32_t a3 = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63) - incl, a2 = a3 + h.w, a1 = a2 + h.z, a0 = a1 + h.y;  // keys above the digit
+      // the digit of the k-th key: fewer than `need` keys above it, and enough with it
+      uint32_t digit = 3u, over = a3, cnt = h.w;
+      if (a2 < need && a3 + h.w < need) { digit = 2u; over = a2; cnt = h.z; }
+      if (a1 < need && a2 + h.z < need) { digit = 1u; over = a1; cnt = h.y; }
+      if (a0 < need && a1 + h.y < need) { digit = 0u; over = a0; cnt = h.x; }
+      const int src = (int)__builtin_ctzll(__ballot(over < need && over + cnt >= need));
+      digit = (uint32_t)__builtin_amdgcn_readlane((int)(digit + 4u * lane), src);
+      over = (uint32_t)__builtin_amdgcn_readlane((int)over, src);
+      cnt = (uint32_t)__builtin_amdgcn_readlane((int)cnt, src);
+      above += over;
+      T = (pass == 0 ? 0u : T << 8) | digit;
+      if (above + cnt == k) {  // exactly these: "key > T" selects them and none equal to T is needed
+        T = (T << shift) - 1u;
         break;
       }
     }
   }
   unsigned long long gt[P], eq[P];
+  uint2* totals = reinterpret_cast<uint2*>(sm.hist);  // [P][W]: keys above and at the threshold
+  static_assert(P * W * sizeof(uint2) <= sizeof(sm.hist), "fits");
 #pragma unroll
   for (int i = 0; i < P; ++i) {
     gt[i] = __ballot(key1[i] > T);
@@ -289,14 +282,20 @@ __device__ __forceinline__ void block_topk_planes(const uint32_t (&key1)[P], int
     if (lane == 0) totals[i * W + wave] = make_uint2((uint32_t)__popcll(gt[i]), (uint32_t)__popcll(eq[i]));
   }
   __syncthreads();
+  auto over_waves = [](uint32_t x) {  // sum of the W entries that neighbouring lanes have read
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xB1, 0xF, 0xF, false);  // quad_perm [1,0,3,2]
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x4E, 0xF, 0xF, false);  // quad_perm [2,3,0,1]
+    if (W == 8) x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x141, 0xF, 0xF, false);  // row_half_mirror
+    return x;
+  };
   uint32_t gt_base[P], eq_base[P], gt_total = 0, eq_total = 0;  // keys before this wavefront's in plane i
 #pragma unroll
   for (int i = 0; i < P; ++i) {
     const uint2 t = totals[i * W + entry];
-    gt_base[i] = gt_total + over_waves(entry < wave ? t.x : 0u, add);
-    eq_base[i] = eq_total + over_waves(entry < wave ? t.y : 0u, add);
-    gt_total += over_waves(t.x, add);
-    eq_total += over_waves(t.y, add);
+    gt_base[i] = gt_total + over_waves(entry < wave ? t.x : 0u);
+    eq_base[i] = eq_total + over_waves(entry < wave ? t.y : 0u);
+    gt_total += over_waves(t.x);
+    eq_total += over_waves(t.y);
   }
   const uint32_t need = k - min(gt_total, k);  // keys equal to T still to take, lowest candidates first
 #pragma unroll
