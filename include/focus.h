@@ -22,6 +22,7 @@
  *     focus_token_confidence vocabulary logits -> predicted tokens, confidences (Eq. 2): the input of the selection
  *     focus_cache_update     new K/V states of the active positions -> KV cache (Eq. 3)
  *     focus_cache_refresh    block entry: new K/V states of every position -> KV cache and K_bar in one pass
+ *     focus_block_entry      = focus_cache_refresh + focus_refresh_attn of one layer, in one call
  *
  * Conventions shared by every entry point
  *  - Pointers marked [dev] are device (HBM) addresses, [host] are host addresses.  The caller owns every
@@ -294,6 +295,12 @@ int focus_cache_update(void* K_cache, void* V_cache, const focus_shape* shape, c
  */
 int focus_cache_refresh(void* K_cache, void* V_cache, const focus_shape* shape, const void* K_new, const void* V_new,
                         int64_t new_stride_h, int64_t new_stride_n, float* kbar, void* stream);
+
+/* focus_cache_refresh and focus_refresh_attn of one layer (the attention of every position over the new states, the same
+ * results): most of the copy runs beside the attention.  shape: strides of the caches, Q and out; K_new and V_new share strides. */
+int focus_block_entry(void* K_cache, void* V_cache, const focus_shape* shape, const void* Q, const void* K_new,
+                      const void* V_new, int64_t new_stride_h, int64_t new_stride_n, float* kbar, void* out, float* lse,
+                      void* stream);
 
 /* Bytes of workspace `fn` needs for this shape; 0 on invalid arguments.  [host] only. */
 size_t focus_workspace_bytes(int32_t fn, const focus_shape* shape, int32_t max_active, int32_t n_keep,

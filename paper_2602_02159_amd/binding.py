@@ -20,7 +20,7 @@ FN_BLOCK_SCORES, FN_FIND_SINKS, FN_SPARSE_ATTN, FN_SPARSE_LAYER, FN_PROBE_LAYER 
 
 EXPORTS = ("focus_select_queries", "focus_expand_groups", "focus_block_means", "focus_block_scores", "focus_find_sinks", "focus_select_and_find_sinks",
            "focus_sparse_attn",
-           "focus_sparse_layer", "focus_sparse_layer_static", "focus_block_partials", "focus_top_blocks", "focus_probe_layer", "focus_refresh_attn", "focus_cache_refresh",
+           "focus_sparse_layer", "focus_sparse_layer_static", "focus_block_partials", "focus_top_blocks", "focus_probe_layer", "focus_refresh_attn", "focus_cache_refresh", "focus_block_entry",
            "focus_token_confidence", "focus_token_confidence_workspace", "focus_cache_update",
            "focus_workspace_bytes", "focus_helper_k", "focus_helper_n_keep", "focus_helper_n_sink", "focus_last_error",
            "focus_version")
@@ -64,6 +64,7 @@ def lib() -> C.CDLL:
         L.focus_probe_layer.argtypes = [p, p, p, i32, p, p, sp, i32, p, p, p, p, p, sz, p]
         L.focus_refresh_attn.argtypes = [p, p, p, sp, p, p, p]
         L.focus_cache_refresh.argtypes = [p, p, sp, p, p, C.c_int64, C.c_int64, p, p]
+        L.focus_block_entry.argtypes = [p, p, sp, p, p, p, C.c_int64, C.c_int64, p, p, p, p]
         L.focus_token_confidence.argtypes = [p, C.c_int64, p, i32, i32, p, p, p, sz, p]
         L.focus_token_confidence_workspace.argtypes = [i32, i32]
         L.focus_token_confidence_workspace.restype = sz
@@ -72,7 +73,7 @@ def lib() -> C.CDLL:
         L.focus_top_blocks.argtypes = [p, i32, p, i32, i32, i32, p, p, p]
         for name in ("focus_select_queries", "focus_expand_groups", "focus_block_means", "focus_block_scores", "focus_find_sinks",
                      "focus_select_and_find_sinks", "focus_sparse_attn", "focus_sparse_layer", "focus_sparse_layer_static", "focus_block_partials", "focus_top_blocks",
-                     "focus_probe_layer", "focus_refresh_attn", "focus_token_confidence", "focus_cache_update", "focus_cache_refresh"):
+                     "focus_probe_layer", "focus_refresh_attn", "focus_token_confidence", "focus_cache_update", "focus_cache_refresh", "focus_block_entry"):
             getattr(L, name).restype = C.c_int
         L.focus_workspace_bytes.argtypes = [i32, sp, i32, i32, i32]
         L.focus_workspace_bytes.restype = sz
@@ -267,6 +268,15 @@ def cache_refresh(k_cache, v_cache, shape: Shape, k_new, v_new, kbar) -> None:
         raise ValueError("K_new and V_new must share their strides, innermost 1")
     _check(lib().focus_cache_refresh(_ptr(k_cache), _ptr(v_cache), C.byref(shape), _ptr(k_new), _ptr(v_new), k_new.stride(0),
                                      k_new.stride(1), _ptr(kbar), _stream()))
+
+
+def block_entry(k_cache, v_cache, shape: Shape, q, k_new, v_new, kbar, out, lse) -> None:
+    """cache_refresh and refresh_attn of one layer in one call; k_new and v_new share their strides."""
+    assert k_new.stride() == v_new.stride() and k_new.stride(2) == 1
+    for t, name in ((q, "Q"), (k_new, "K"), (v_new, "V")):
+        _need(t, torch.bfloat16, name)
+    _check(lib().focus_block_entry(_ptr(k_cache), _ptr(v_cache), C.byref(shape), _ptr(q), _ptr(k_new), _ptr(v_new), k_new.stride(0),
+                                   k_new.stride(1), _ptr(kbar), _ptr(out), _ptr(lse), _stream()))
 
 
 def sparse_layer(q, focus_idx, active_idx, counts, k, v, kbar, shape: Shape, n_keep: int, sink_idx, n_sink: int, scores,

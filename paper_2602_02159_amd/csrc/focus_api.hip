@@ -539,18 +539,46 @@ size_t focus_token_confidence_workspace(int32_t n_rows, int32_t vocab) {
   return std::max<size_t>(token_confidence_workspace(n_rows, vocab), 16);
 }
 
+static int check_refresh_attn(const char* who, const void* Q, const void* K, const void* V, const focus_shape* shape, const void* out,
+                              int64_t k_row, int64_t v_row) {
+  if (!Q || !K || !V || !out) return fail(FOCUS_EINVAL, "%s: NULL pointer", who);
+  if (!aligned16(Q) || !aligned16(K) || !aligned16(V) || !aligned16(out))
+    return fail(FOCUS_EINVAL, "%s: pointers must be 16-byte aligned", who);
+  if ((int64_t)ceil_div(shape->n_gen, 128) * shape->n_heads > 0x3fffffff) return fail(FOCUS_EUNSUPPORTED, "%s: grid too large", who);
+  if (k_row >= (1 << 25) || v_row >= (1 << 25))  // 32-row byte offsets are kept in 32 bits
+    return fail(FOCUS_EUNSUPPORTED, "%s: K/V row stride must be below 2^25 elements", who);
+  return FOCUS_OK;
+}
+
+static int check_cache_refresh(const char* who, const void* K_cache, const void* V_cache, const focus_shape* shape, const void* K_new,
+                               const void* V_new, int64_t new_stride_h, int64_t new_stride_n, const float* kbar) {
+  if (!K_cache || !V_cache || !K_new || !V_new) return fail(FOCUS_EINVAL, "%s: NULL pointer", who);
+  if (new_stride_n < shape->head_dim || (new_stride_n & 7) || new_stride_h < 0 || (new_stride_h & 7))
+    return fail(FOCUS_EINVAL, "%s: strides of the new states invalid or not multiples of 8", who);
+  if (!aligned16(K_cache) || !aligned16(V_cache) || !aligned16(K_new) || !aligned16(V_new) || !aligned16(kbar))
+    return fail(FOCUS_EINVAL, "%s: pointers must be 16-byte aligned", who);
+  if (K_cache == K_new || V_cache == V_new) return fail(FOCUS_EINVAL, "%s: the new states must not alias the cache", who);
+  if (shape->n_heads > 65535) return fail(FOCUS_EUNSUPPORTED, "%s: more than 65535 heads", who);
+  return FOCUS_OK;
+}
+
 int focus_refresh_attn(const void* Q, const void* K, const void* V, const focus_shape* shape, void* out, float* lse,
                        void* stream) {
   if (int rc = check_shape(shape, true, true, true, true)) return rc;
-  if (!Q || !K || !V || !out) return fail(FOCUS_EINVAL, "focus_refresh_attn: NULL pointer");
-  if (!aligned16(Q) || !aligned16(K) || !aligned16(V) || !aligned16(out))
-    return fail(FOCUS_EINVAL, "focus_refresh_attn: pointers must be 16-byte aligned");
-  if ((int64_t)ceil_div(shape->n_gen, 128) * shape->n_heads > 0x3fffffff)
-    return fail(FOCUS_EUNSUPPORTED, "focus_refresh_attn: grid too large");
-  if (shape->k_stride_n >= (1 << 25) || shape->v_stride_n >= (1 << 25))  // 32-row byte offsets are kept in 32 bits
-    return fail(FOCUS_EUNSUPPORTED, "focus_refresh_attn: K/V row stride must be below 2^25 elements");
+  if (int rc = check_refresh_attn("focus_refresh_attn", Q, K, V, shape, out, shape->k_stride_n, shape->v_stride_n)) return rc;
   hipError_t e = launch_refresh_attn(Q, K, V, *shape, out, lse, static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return launch_fail("focus_refresh_attn", e);
+  return FOCUS_OK;
+}
+
+int focus_block_entry(void* K_cache, void* V_cache, const focus_shape* shape, const void* Q, const void* K_new, const void* V_new,
+                      int64_t new_stride_h, int64_t new_stride_n, float* kbar, void* out, float* lse, void* stream) {
+  if (int rc = check_shape(shape, true, true, true, true)) return rc;
+  if (int rc = check_cache_refresh("focus_block_entry", K_cache, V_cache, shape, K_new, V_new, new_stride_h, new_stride_n, kbar)) return rc;
+  if (int rc = check_refresh_attn("focus_block_entry", Q, K_new, V_new, shape, out, new_stride_n, new_stride_n)) return rc;
+  const CacheRefresh copy = cache_refresh_args(K_cache, V_cache, *shape, K_new, V_new, new_stride_h, new_stride_n, kbar);
+  hipError_t e = launch_refresh_attn(Q, K_new, V_new, *shape, out, lse, static_cast<hipStream_t>(stream), &copy);
+  if (e != hipSuccess) return launch_fail("focus_block_entry", e);
   return FOCUS_OK;
 }
 
@@ -589,15 +617,9 @@ int focus_cache_update(void* K_cache, void* V_cache, const focus_shape* shape, c
 int focus_cache_refresh(void* K_cache, void* V_cache, const focus_shape* shape, const void* K_new, const void* V_new,
                         int64_t new_stride_h, int64_t new_stride_n, float* kbar, void* stream) {
   if (int rc = check_shape(shape, false, true, true, false)) return rc;
-  if (!K_cache || !V_cache || !K_new || !V_new) return fail(FOCUS_EINVAL, "focus_cache_refresh: NULL pointer");
-  if (new_stride_n < shape->head_dim || (new_stride_n & 7) || new_stride_h < 0 || (new_stride_h & 7))
-    return fail(FOCUS_EINVAL, "focus_cache_refresh: strides of the new states invalid or not multiples of 8");
-  if (!aligned16(K_cache) || !aligned16(V_cache) || !aligned16(K_new) || !aligned16(V_new) || !aligned16(kbar))
-    return fail(FOCUS_EINVAL, "focus_cache_refresh: pointers must be 16-byte aligned");
-  if (K_cache == K_new || V_cache == V_new) return fail(FOCUS_EINVAL, "focus_cache_refresh: the new states must not alias the cache");
-  if (shape->n_heads > 65535) return fail(FOCUS_EUNSUPPORTED, "focus_cache_refresh: more than 65535 heads");
-  hipError_t e = launch_cache_refresh(K_cache, V_cache, *shape, K_new, V_new, new_stride_h, new_stride_n, kbar,
-                                      static_cast<hipStream_t>(stream));
+  if (int rc = check_cache_refresh("focus_cache_refresh", K_cache, V_cache, shape, K_new, V_new, new_stride_h, new_stride_n, kbar)) return rc;
+  const CacheRefresh p = cache_refresh_args(K_cache, V_cache, *shape, K_new, V_new, new_stride_h, new_stride_n, kbar);
+  hipError_t e = launch_cache_refresh(p, shape->head_dim, static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return launch_fail("focus_cache_refresh", e);
   return FOCUS_OK;
 }

@@ -93,8 +93,19 @@ hipError_t launch_cache_update(void* K_cache, void* V_cache, const focus_shape& 
                                int64_t new_stride_h, int64_t new_stride_n, const int32_t* active_idx, const int32_t* counts,
                                int max_active, int row_base, hipStream_t st);
 // block entry: every cache row takes its new state; block means of the prompt keys from the same pass (kbar may be null)
-hipError_t launch_cache_refresh(void* K_cache, void* V_cache, const focus_shape& s, const void* K_new, const void* V_new,
-                                int64_t new_stride_h, int64_t new_stride_n, float* kbar, hipStream_t st);
+struct CacheRefresh {
+  const uint16_t* Kn;
+  const uint16_t* Vn;
+  uint16_t* Kc;
+  uint16_t* Vc;
+  int64_t nsh, nsn, ksh, ksn, vsh, vsn;
+  int M, L, B, n_b;
+  int n_chunks, n_heads;  // chunks of B rows per head: n_b prompt blocks, then the response rows
+  float* kbar;
+};
+CacheRefresh cache_refresh_args(void* K_cache, void* V_cache, const focus_shape& s, const void* K_new, const void* V_new,
+                                int64_t new_stride_h, int64_t new_stride_n, float* kbar);
+hipError_t launch_cache_refresh(const CacheRefresh& p, int head_dim, hipStream_t st);
 
 // ---- MFMA kernels (focus_mfma.hip)
 // mode 0: logits [H, ceil(L / 4), 16, 4] + part_ml out (at most 16 queries); mode 1: part_ml out only; mode 2: lse2 in, colpart [q_groups * H, L] out
@@ -135,7 +146,8 @@ hipError_t launch_sparse_attn(const void* Q, const int32_t* active_idx, const in
                               const DenseProbe* probe = nullptr);
 
 // Block-entry refresh: dense attention of all n_gen rows of Q over all M + N keys (out [H, n_gen, d], lse [H, n_gen])
+// copy: the cache refresh of the same layer, on the side of the attention's last launch; K and V are then its new states
 hipError_t launch_refresh_attn(const void* Q, const void* K, const void* V, const focus_shape& s, void* out, float* lse,
-                               hipStream_t st);
+                               hipStream_t st, const CacheRefresh* copy = nullptr);
 
 }  // namespace focus

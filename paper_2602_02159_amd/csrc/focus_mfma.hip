@@ -29,6 +29,7 @@
 #include <type_traits>
 #include <utility>
 
+#include "focus_cache.h"
 #include "focus_common.h"
 #include "focus_kernels.h"
 #include "focus_topk.h"
@@ -1604,8 +1605,11 @@ __global__ __launch_bounds__(64 * kRefreshWaves, 2) void refresh_attn_kernel(con
 // key sub-tiles dealt to its eight wavefronts in turn.  A wavefront stages its own sub-tiles (no barrier in the key loop; the
 // operands are all in registers before the next sub-tile is requested into the same stage), the eight states are merged at the
 // end.  Tail tiles: the whole blocks the other kernel does not take, eight tiles each, then every head's last few tiles.
+// The workgroups behind those of the tail tiles make the layer's cache refresh, two chunks each (copy; none without it): the tiles
+// rarely fill the chip and leave the memory idle, while the copy needs nothing else.  32 heads: 8256 rows, tiles 77 us and copy 48
+// us one after the other, 32 832 rows 282 and 185; 4 heads, 1056 rows, d = 64: a launch less.
 template <int D>
-__global__ __launch_bounds__(64 * kRefreshWaves, 2) void refresh_tail_kernel(const RefreshArgs p) {
+__global__ __launch_bounds__(64 * kRefreshWaves, 2) void refresh_tail_kernel(const RefreshArgs p, const CacheRefresh copy) {
   using G = Geo<D>;
   constexpr int kKS = D / 16, kDT = D / 32, kOChunks = D / 4;
   constexpr int kBufBytes = 2 * G::kStageBytes;
@@ -1614,6 +1618,15 @@ __global__ __launch_bounds__(64 * kRefreshWaves, 2) void refresh_tail_kernel(con
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int qi = lane & 31, hh = lane >> 5;
+  const int n_tail_groups = (p.n_tail + 7) & ~7;
+  if ((int)blockIdx.x >= n_tail_groups) {
+    const int half = threadIdx.x >> 8, item = 2 * ((int)blockIdx.x - n_tail_groups) + half;
+    const bool live = item < copy.n_chunks * copy.n_heads;
+    const int h = live ? item / copy.n_chunks : 0;
+    static_assert(2 * 2048 * sizeof(float) <= sizeof(lds), "both halves' partial means fit");
+    cache_refresh_chunk<D>(copy, live ? item - h * copy.n_chunks : 0, h, threadIdx.x & 255, live, reinterpret_cast<float*>(lds) + half * 2048);
+    return;
+  }
   // contiguous eighths of the tile list to the XCDs, as in refresh_attn_kernel
   const int chunk = (p.n_tail + 7) >> 3;
   const int item = (int)(blockIdx.x & 7u) * chunk + (int)(blockIdx.x >> 3);
@@ -1713,7 +1726,7 @@ __global__ __launch_bounds__(64 * kRefreshWaves, 2) void refresh_tail_kernel(con
 //   whole rounds of blocks, and everything else to the tail kernel.
 // 32 heads, 8256 rows (33 blocks per head, 4.1 rounds): 1213 us all in blocks, 1106 us cut; 4 heads, 1056 rows, d = 64: 26 and 9.
 template <int D>
-static hipError_t launch_refresh_t(RefreshArgs& a, const focus_shape& s, hipStream_t st) {
+static hipError_t launch_refresh_t(RefreshArgs& a, const focus_shape& s, const CacheRefresh* copy, hipStream_t st) {
   constexpr int kSlots = 256;
   constexpr float kPerSubTile = D == 128 ? 0.85f : 0.6f, kTailCost = D == 128 ? 1.9f : 1.7f, kFixed = 5.f;
   const int tiles = ceil_div(s.n_gen, 32), last = tiles % kRefreshWaves;
@@ -1738,14 +1751,18 @@ static hipError_t launch_refresh_t(RefreshArgs& a, const focus_shape& s, hipStre
   if (a.n_work > 0) {
     hipLaunchKernelGGL(refresh_attn_kernel<D>, dim3(8 * ceil_div(a.n_work, 8)), dim3(64 * kRefreshWaves), 0, st, a);
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess || a.n_tail == 0) return e;
+    if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(refresh_tail_kernel<D>, dim3(8 * ceil_div(a.n_tail, 8)), dim3(64 * kRefreshWaves), 0, st, a);
+  if (a.n_tail == 0) return copy ? launch_cache_refresh(*copy, D, st) : hipSuccess;
+  const int64_t copies = copy ? ((int64_t)copy->n_chunks * copy->n_heads + 1) / 2 : 0;
+  if (copies > (1 << 29)) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(refresh_tail_kernel<D>, dim3(8 * ceil_div(a.n_tail, 8) + (int)copies), dim3(64 * kRefreshWaves), 0, st, a,
+                     copy ? *copy : CacheRefresh{});
   return hipGetLastError();
 }
 
 hipError_t launch_refresh_attn(const void* Q, const void* K, const void* V, const focus_shape& s, void* out, float* lse,
-                               hipStream_t st) {
+                               hipStream_t st, const CacheRefresh* copy) {
   RefreshArgs a;
   a.Q = static_cast<const uint16_t*>(Q);
   a.K = static_cast<const uint16_t*>(K);
@@ -1753,14 +1770,14 @@ hipError_t launch_refresh_attn(const void* Q, const void* K, const void* V, cons
   a.out = static_cast<uint16_t*>(out);
   a.lse = lse;
   a.qsh = s.q_stride_h; a.qsn = s.q_stride_n;
-  a.ksh = s.k_stride_h; a.ksn = s.k_stride_n;
-  a.vsh = s.v_stride_h; a.vsn = s.v_stride_n;
+  a.ksh = copy ? copy->nsh : s.k_stride_h; a.ksn = copy ? copy->nsn : s.k_stride_n;
+  a.vsh = copy ? copy->nsh : s.v_stride_h; a.vsn = copy ? copy->nsn : s.v_stride_n;
   a.osh = s.o_stride_h; a.osn = s.o_stride_n;
   a.n_q = s.n_gen;
   a.L = s.n_ctx + s.n_resp;
   a.scale_log2 = kLog2e / sqrtf((float)s.head_dim);
-  if (s.head_dim == 128) return launch_refresh_t<128>(a, s, st);
-  return launch_refresh_t<64>(a, s, st);
+  if (s.head_dim == 128) return launch_refresh_t<128>(a, s, copy, st);
+  return launch_refresh_t<64>(a, s, copy, st);
 }
 
 // =====================================================================================================

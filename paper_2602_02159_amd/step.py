@@ -193,8 +193,8 @@ class FocusDecoder:
       step          conf fp32 [n_gen] (or logits), masked u8 [n_gen],
                     q[l] bf16 [H, n_gen, d], k_new[l] / v_new[l] bf16 [H, max_active, d]: slot a = position I_active[a]
 
-    run_entry():  per layer  focus_cache_refresh (cache rows <- new states, K_bar of the sparse layers from the same pass),
-                  focus_refresh_attn (every position attends to every key)            -> out_all[l]
+    run_entry():  per layer  focus_block_entry (every position attends to every key; cache rows <- new states, K_bar of the
+                  sparse layers from the same pass)                                   -> out_all[l]
     run_step():   [focus_token_confidence,] focus_select_queries, then per layer focus_cache_update (Eq. 3: the active rows
                   take their new states before the layer attends) followed by
                     dense layer   focus_sparse_attn with every block kept
@@ -251,11 +251,9 @@ class FocusDecoder:
         self.entry_calls, self.step_calls = [], []
         for l in range(n_layers):
             s_all = shape(self.q_all[l], self.k_cache[l], self.v_cache[l], self.out_all[l])
-            self.entry_calls.append((lib.focus_cache_refresh, (
-                p(self.k_cache[l]), p(self.v_cache[l]), C.byref(s_all), p(self.k_all[l]), p(self.v_all[l]),
-                self.k_all[l].stride(0), self.k_all[l].stride(1), p(self.kbar[l]))))
-            self.entry_calls.append((lib.focus_refresh_attn, (
-                p(self.q_all[l]), p(self.k_cache[l]), p(self.v_cache[l]), C.byref(s_all), p(self.out_all[l]), None)))
+            self.entry_calls.append((lib.focus_block_entry, (
+                p(self.k_cache[l]), p(self.v_cache[l]), C.byref(s_all), p(self.q_all[l]), p(self.k_all[l]), p(self.v_all[l]),
+                self.k_all[l].stride(0), self.k_all[l].stride(1), p(self.kbar[l]), p(self.out_all[l]), None)))
         if self.logits is not None:
             ws_conf = workspace(fb.token_confidence_workspace(n_gen, vocab))
             self.step_calls.append((lib.focus_token_confidence, (

@@ -1067,6 +1067,33 @@ def test_block_entry_then_step_uses_the_refreshed_cache_and_means(G):
     assert kept_mean.cpu().tolist() == fo.top_indices(R, 6).tolist()
 
 
+@pytest.mark.parametrize("H,M,N,B,d", [
+    (4, 1024, 32, 64, 64),      # single tiles only
+    (3, 1000, 37, 128, 128),    # an odd number of chunks, ragged blocks
+    (40, 1060, 40, 64, 128),    # whole blocks, then tiles
+    (256, 256, 0, 128, 64),     # no tiles: the copy has a launch of its own
+    (1, 30, 0, 32, 128),
+])
+def test_block_entry_equals_the_two_calls(G, H, M, N, B, d):
+    L, n_b = M + N, -(-M // B)
+    store = [_rand_bf16(171 + i, L, H, d).to(G.DEV) for i in range(2)]
+    k_new, v_new = (t.transpose(0, 1) for t in store)  # strides of their own
+    q = _rand_bf16(173, H, L, d).to(G.DEV)
+    res = []
+    for fused in (False, True):
+        kc, vc, out = (torch.full((H, L, d), float("nan"), dtype=torch.bfloat16, device=G.DEV) for _ in range(3))
+        kbar, lse = torch.full((H, n_b, d), float("nan"), device=G.DEV), torch.full((H, L), float("nan"), device=G.DEV)
+        s = fb.make_shape(q, kc, vc, M, B, out)
+        if fused:
+            fb.block_entry(kc, vc, s, q, k_new, v_new, kbar, out, lse)
+        else:
+            fb.cache_refresh(kc, vc, s, k_new, v_new, kbar)
+            fb.refresh_attn(q, kc, vc, s, out, lse)
+        torch.cuda.synchronize()
+        res.append((kc, vc, kbar, out, lse))
+    assert all(torch.equal(a, b) for a, b in zip(*res))
+
+
 def test_block_entry_calls_replay_in_a_hip_graph(G):
     """The block-entry calls and the group expansion enqueue kernels only, so they can be captured: three replays, the
     outputs wiped in between, each equal to the eager result bit for bit."""
