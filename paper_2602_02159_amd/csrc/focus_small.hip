@@ -676,12 +676,11 @@ hipError_t launch_column_mass(const float* src, bool pre_reduced, const float* l
 // Top-N_sink beyond the tournament's limits (the paper's 1 % rule asks for hundreds of sinks), M <= 131072.  The column-mass
 // kernel has nominated the kRankNominees largest masses of every 128-key group (n_per = min(kRankNominees, N_sink)), in
 // ascending order of position.  One workgroup holds all nominees in registers, KPL consecutive ones per thread, and finds the
-// N_sink-th largest key two bits at a time: every wavefront counts its own keys against three thresholds with ballots, the
-// sixteen counts meet in LDS.  The bits all keys share are skipped, and the search ends as soon as exactly N_sink keys reach a
-// threshold.  Unless a group has all its nominees selected (its other keys might then belong to the answer too) that is the
+// N_sink-th largest key by a radix search, eight bits per pass.  The bits all keys share are skipped, and the search ends as soon
+// as exactly N_sink keys reach a digit.  Unless a group has all its nominees selected (its other keys might then belong to the answer too) that is the
 // exact Top-N_sink.  Otherwise the key found is a lower bound of the true one, and the positions that reach it, compacted in
 // index order into LDS, are ranked the same way; only if they do not fit a radix select over all positions decides.
-// 32768 keys, 327 sinks: 8 us (bounding, compacting and ranking all positions in one workgroup took 18); 131072 keys, 1310
+// 32768 keys, 327 sinks: 6 us (two bits per pass: 8; bounding, compacting and ranking all positions in one workgroup took 18); 131072 keys, 1310
 // sinks: 12 us (radix select: 390 us).
 template <int KPL>
 __global__ __launch_bounds__(kTopkThreads) void sink_rank_kernel(const int32_t* __restrict__ cand, const uint32_t* __restrict__ cand_keys,
@@ -690,12 +689,11 @@ __global__ __launch_bounds__(kTopkThreads) void sink_rank_kernel(const int32_t* 
   constexpr int kWaves = kTopkThreads / kWave, kCap = kTopkThreads * KPL;
   __shared__ __attribute__((aligned(16))) uint32_t keys_sh[kCap];  // positions that clear the bound: key + 1 ...
   __shared__ __attribute__((aligned(16))) int32_t idx_sh[kCap];    // ... and index
-  __shared__ __attribute__((aligned(16))) uint32_t count_sh[2][kWaves][4];  // by round parity, wavefront, threshold
+  __shared__ __attribute__((aligned(16))) uint32_t hist_sh[4][256];  // a histogram per digit
   __shared__ uint32_t bits_sh[kWaves][2], valid_sh[kWaves], sel_sh[kWaves][2];
   __shared__ int overflow_sh;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const unsigned long long below = (1ull << lane) - 1ull;
-  auto add = [](uint32_t a, uint32_t b) { return a + b; };
   const int i0 = tid * KPL;
   uint32_t kv[KPL];  // key + 1; 0 = none
   int32_t pos[KPL];
@@ -720,6 +718,7 @@ __global__ __launch_bounds__(kTopkThreads) void sink_rank_kernel(const int32_t* 
       any |= kv[r];
       n_mine += (uint32_t)__popcll(__ballot(kv[r] != 0u));
     }
+    hist_sh[tid >> 8][tid & 255] = 0u;
     all = wave_reduce_u32(all, [](uint32_t a, uint32_t b) { return a & b; });
     any = wave_reduce_u32(any, [](uint32_t a, uint32_t b) { return a | b; });
     if (lane == 0) {
@@ -740,30 +739,26 @@ __global__ __launch_bounds__(kTopkThreads) void sink_rank_kernel(const int32_t* 
     const uint32_t k = min((uint32_t)n_sink, n_valid);
     uint32_t T = 0u;  // the k-th largest key, or one less than a threshold that exactly k keys reach; 0: all of them
     if (k < n_valid) {
-      const int top = 31 - (int)__clz((int)(all ^ any));  // -1: all keys are equal
+      const int top = all == any ? -1 : 31 - (int)__clz((int)(all ^ any));  // -1: all keys are equal
       T = top < 0 ? all : (top == 31 ? 0u : all & ~((2u << top) - 1u));
-      for (int hi = top, parity = 0; hi >= 0; hi -= 2, parity ^= 1) {  // bits hi and hi - 1 (bit 0 alone in the last round of an odd count)
-        const uint32_t step = hi > 0 ? 1u << (hi - 1) : 1u;
-        uint32_t c1 = 0, c2 = 0, c3 = 0;
+      uint32_t above = 0;  // keys whose leading digits exceed T's
+      int hi = top;
+      for (int digit_no = 0; hi >= 0; ++digit_no) {  // bits hi .. shift, eight at a time: one LDS atomic per key, one barrier; every
+        const int shift = hi >= 7 ? hi - 7 : 0;      // wavefront scans the 256 counts by itself, four per lane
+        uint32_t* hist = hist_sh[digit_no];
+        const uint32_t ones = (2u << (hi - shift)) - 1u;
 #pragma unroll
-        for (int r = 0; r < KPL; ++r) {
-          c1 += (uint32_t)__popcll(__ballot(kv[r] >= (T | step)));
-          c2 += (uint32_t)__popcll(__ballot(kv[r] >= (T | (2u * step))));
-          c3 += (uint32_t)__popcll(__ballot(kv[r] >= (T | (3u * step))));
-        }
-        if (lane == 0) *reinterpret_cast<uint4*>(count_sh[parity][wave]) = make_uint4(c1, c2, c3, 0u);
-        __syncthreads();  // (the other parity's counts may still be read by slower wavefronts)
-        const uint4 row = *reinterpret_cast<const uint4*>(count_sh[parity][lane & (kWaves - 1)]);
-        const uint32_t s1 = row_reduce_u32(row.x, add), s2 = row_reduce_u32(row.y, add), s3 = row_reduce_u32(row.z, add);
-        uint32_t j = 0, cnt = 0;  // the largest threshold that at least k keys reach
-        if (s1 >= k) { j = 1; cnt = s1; }
-        if (hi > 0 && s2 >= k) { j = 2; cnt = s2; }
-        if (hi > 0 && s3 >= k) { j = 3; cnt = s3; }
-        T |= j * step;
-        if (cnt == k) {  // exactly these: "key > T" selects them and none equal to T is needed (k > 0)
+        for (int r = 0; r < KPL; ++r)
+          if (kv[r] != 0u && (hi == 31 || (kv[r] >> (hi + 1)) == (T >> (hi + 1)))) atomicAdd(&hist[(kv[r] >> shift) & ones], 1u);
+        __syncthreads();
+        const RadixDigit d = radix_digit(hist, k - above);
+        above += d.over;
+        T |= d.digit << shift;
+        if (above + d.count == k) {  // exactly these: "key > T" selects them and none equal to T is needed (k > 0)
           T -= 1u;
           break;
         }
+        hi = shift - 1;
       }
     }
     // selection in ascending order: everything above T, and the first keys equal to T until k are reached

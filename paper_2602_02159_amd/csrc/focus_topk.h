@@ -222,6 +222,28 @@ __device__ __forceinline__ uint32_t wave_prefix_sum(uint32_t x) {
   return x;
 }
 
+// The digit of the `need`-th largest key among those that a 256-bin histogram in LDS counts, how many keys exceed that digit and
+// how many have it.  Called by whole wavefronts; the histogram holds at least `need` > 0 keys.
+struct RadixDigit {
+  uint32_t digit, over, count;
+};
+__device__ __forceinline__ RadixDigit radix_digit(const uint32_t* hist, uint32_t need) {
+  const int lane = threadIdx.x & 63;
+  const uint4 h = reinterpret_cast<const uint4*>(hist)[lane];  // digits 4 lane .. 4 lane + 3
+  const uint32_t incl = wave_prefix_sum((h.x + h.y) + (h.z + h.w));
+  const uint32_t a3 = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63) - incl, a2 = a3 + h.w, a1 = a2 + h.z, a0 = a1 + h.y;  // keys above the digit
+  uint32_t digit = 3u, over = a3, cnt = h.w;
+  if (a2 < need && a3 + h.w < need) { digit = 2u; over = a2; cnt = h.z; }
+  if (a1 < need && a2 + h.z < need) { digit = 1u; over = a1; cnt = h.y; }
+  if (a0 < need && a1 + h.y < need) { digit = 0u; over = a0; cnt = h.x; }
+  const int src = (int)__builtin_ctzll(__ballot(over < need && over + cnt >= need));
+  RadixDigit d;
+  d.digit = (uint32_t)__builtin_amdgcn_readlane((int)(digit + 4u * lane), src);
+  d.over = (uint32_t)__builtin_amdgcn_readlane((int)over, src);
+  d.count = (uint32_t)__builtin_amdgcn_readlane((int)cnt, src);
+  return d;
+}
+
 // Top-k among n keys in P planes of THREADS (thread t holds the keys of the candidates i THREADS + t, i < P; key + 1, 0 only past
 // n), same order and tie rule as wave_topk, by a workgroup of 4 or 8 wavefronts: a radix search of the k-th largest key, eight
 // bits per pass.  A pass is one LDS atomic per key and one barrier; every wavefront then scans the 256 counts by itself, four per
@@ -251,22 +273,10 @@ __device__ __forceinline__ void block_topk_planes(const uint32_t (&key1)[P], int
       for (int i = 0; i < P; ++i)
         if (key1[i] != 0u && (pass == 0 || (key1[i] >> ((shift + 8) & 31)) == T)) atomicAdd(&hist[(key1[i] >> shift) & 255u], 1u);
       __syncthreads();
-      const uint4 h = reinterpret_cast<const uint4*>(hist)[lane];  // digits 4 lane .. 4 lane + 3
-      const uint32_t sum = (h.x + h.y) + (h.z + h.w), incl = wave_prefix_sum(sum);
-      const uint32_t need = k - above;
-      const uint32_t a3 = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63) - incl, a2 = a3 + h.w, a1 = a2 + h.z, a0 = a1 + h.y;  // keys above the digit
-      // the digit of the k-th key: fewer than `need` keys above it, and enough with it
-      uint32_t digit = 3u, over = a3, cnt = h.w;
-      if (a2 < need && a3 + h.w < need) { digit = 2u; over = a2; cnt = h.z; }
-      if (a1 < need && a2 + h.z < need) { digit = 1u; over = a1; cnt = h.y; }
-      if (a0 < need && a1 + h.y < need) { digit = 0u; over = a0; cnt = h.x; }
-      const int src = (int)__builtin_ctzll(__ballot(over < need && over + cnt >= need));
-      digit = (uint32_t)__builtin_amdgcn_readlane((int)(digit + 4u * lane), src);
-      over = (uint32_t)__builtin_amdgcn_readlane((int)over, src);
-      cnt = (uint32_t)__builtin_amdgcn_readlane((int)cnt, src);
-      above += over;
-      T = (pass == 0 ? 0u : T << 8) | digit;
-      if (above + cnt == k) {  // exactly these: "key > T" selects them and none equal to T is needed
+      const RadixDigit d = radix_digit(hist, k - above);
+      above += d.over;
+      T = (pass == 0 ? 0u : T << 8) | d.digit;
+      if (above + d.count == k) {  // exactly these: "key > T" selects them and none equal to T is needed
         T = (T << shift) - 1u;
         break;
       }
