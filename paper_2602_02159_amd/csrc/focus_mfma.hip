@@ -313,6 +313,11 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t cvt_pk_bf16(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector((floatx2){lo, hi}, bf16x2));
 }
+// sum + lo + hi of a packed pair, in fp32
+__device__ __forceinline__ float add_bf16_pair(float sum, uint32_t pair) {
+  const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
+  return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pair), ones, sum, false);
+}
 __device__ __forceinline__ bf16x8 pack_bf16x8(const float (&v)[8]) {
   return as_bf16x8(make_uint4(cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3]), cvt_pk_bf16(v[4], v[5]), cvt_pk_bf16(v[6], v[7])));
 }
@@ -833,9 +838,11 @@ __global__ __launch_bounds__(256, (FUSE & 2) == 0 ? 2 : 1) void sparse_attn_kern
 //   S^T = K Q^T   lane (query = lane % 32, hh = lane / 32), register v: logit of key 8 (v / 4) + 4 hh + v % 4
 //   O^T = V^T P^T the same registers, packed to bf16, are the B operand of k-step v / 8
 // k_operand(ks) / v_operand(dt, ks) supply the A operands; l_run is this lane's share of the row sum (its 16 of the 32 keys).
-template <int D, class KOp, class VOp>
+// r_run is the same for the probabilities as they enter the PV product, rounded to bf16.  SUMS: bit 0 l_run, bit 1 r_run is kept.
+template <int D, int SUMS, class KOp, class VOp>
 __device__ __forceinline__ void attend_subtile32(const KOp k_operand, const VOp v_operand, const bf16x8 (&q)[D / 16], uint32_t vmask,
-                                                 int hh, float scale_log2, float& m_run, float& l_run, floatx16 (&o)[D / 32]) {
+                                                 int hh, float scale_log2, float& m_run, float& l_run, float& r_run,
+                                                 floatx16 (&o)[D / 32]) {
   constexpr int kKS = D / 16, kDT = D / 32;
   floatx16 acc;
 #pragma unroll
@@ -855,7 +862,8 @@ __device__ __forceinline__ void attend_subtile32(const KOp k_operand, const VOp 
   const float m_use = m_new == -INFINITY ? 0.f : m_new;
   if (__ballot(m_new != m_run) != 0ull) {  // some running maximum of this wavefront moves (rare after the first sub-tiles)
     const float alpha = __builtin_amdgcn_exp2f(m_run - m_use);
-    l_run *= alpha;
+    if (SUMS & 1) l_run *= alpha;
+    if (SUMS & 2) r_run *= alpha;
 #pragma unroll
     for (int dt = 0; dt < kDT; ++dt) o[dt] *= alpha;
     m_run = m_new;
@@ -863,14 +871,18 @@ __device__ __forceinline__ void attend_subtile32(const KOp k_operand, const VOp 
   float ps[16];
 #pragma unroll
   for (int v = 0; v < 16; ++v) ps[v] = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[v], scale_log2, -m_use));
-  float sum = ps[0] + ps[1];
+  if (SUMS & 1) {
+    float sum = ps[0] + ps[1];
 #pragma unroll
-  for (int v = 2; v < 16; v += 2) sum += ps[v] + ps[v + 1];
-  l_run += sum;
+    for (int v = 2; v < 16; v += 2) sum += ps[v] + ps[v + 1];
+    l_run += sum;
+  }
 #pragma unroll
   for (int ks = 0; ks < 2; ++ks) {
-    const bf16x8 pb = as_bf16x8(make_uint4(cvt_pk_bf16(ps[8 * ks], ps[8 * ks + 1]), cvt_pk_bf16(ps[8 * ks + 2], ps[8 * ks + 3]),
-                                           cvt_pk_bf16(ps[8 * ks + 4], ps[8 * ks + 5]), cvt_pk_bf16(ps[8 * ks + 6], ps[8 * ks + 7])));
+    const uint4 pk = make_uint4(cvt_pk_bf16(ps[8 * ks], ps[8 * ks + 1]), cvt_pk_bf16(ps[8 * ks + 2], ps[8 * ks + 3]),
+                                cvt_pk_bf16(ps[8 * ks + 4], ps[8 * ks + 5]), cvt_pk_bf16(ps[8 * ks + 6], ps[8 * ks + 7]));
+    if (SUMS & 2) r_run += add_bf16_pair(add_bf16_pair(0.f, pk.x), pk.y) + add_bf16_pair(add_bf16_pair(0.f, pk.z), pk.w);
+    const bf16x8 pb = as_bf16x8(pk);
 #pragma unroll
     for (int dt = 0; dt < kDT; ++dt) o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_operand(dt, ks), pb, o[dt], 0, 0, 0);
   }
@@ -1011,7 +1023,8 @@ __global__ __launch_bounds__(256 * NT, NT == 2 || (MODE & 4) == 0 ? 2 : 1) void 
 
   // one staged sub-tile into the running softmax
   auto consume = [&](auto k_operand, auto v_operand, uint32_t vmask) __attribute__((always_inline)) {
-    attend_subtile32<D>(k_operand, v_operand, q, vmask, hh, p.scale_log2, m_run, l_run, o);
+    float unused = 0.f;
+    attend_subtile32<D, 1>(k_operand, v_operand, q, vmask, hh, p.scale_log2, m_run, l_run, unused, o);
   };
   auto k_at = [&](const char* stage, int ks) __attribute__((always_inline)) {
     return as_bf16x8(*reinterpret_cast<const uint4*>(stage + stage_off<D>(qi, 2 * ks + hh)));
@@ -1443,7 +1456,6 @@ __global__ __launch_bounds__(64 * kRefreshWaves, 2) void refresh_attn_kernel(con
   for (int dt = 0; dt < kDT; ++dt)
 #pragma unroll
     for (int v = 0; v < 16; ++v) o[dt][v] = 0.f;
-  const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
   int koff[kKS];  // byte offset of the K operand of k-step s within a slot
 #pragma unroll
   for (int s = 0; s < kKS; ++s) {
@@ -1530,7 +1542,7 @@ __global__ __launch_bounds__(64 * kRefreshWaves, 2) void refresh_attn_kernel(con
           p1 = key + 1 < n_valid ? p1 : 0.f;
         }
         pk[v >> 1] = cvt_pk_bf16(p0, p1);
-        l_run = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pk[v >> 1]), ones, l_run, false);
+        l_run = add_bf16_pair(l_run, pk[v >> 1]);
       }
     };
     if (kLast) probabilities(0, 16);
@@ -1612,16 +1624,20 @@ __global__ __launch_bounds__(64 * kRefreshWaves, 2) void refresh_attn_kernel(con
 // key sub-tiles dealt to its eight wavefronts in turn.  A wavefront stages its own sub-tiles (no barrier in the key loop; the
 // operands are all in registers before the next sub-tile is requested into the same stage), the eight states are merged at the
 // end.  Tail tiles: the whole blocks the other kernel does not take, eight tiles each, then every head's last few tiles.
+// Rows are normalised as in refresh_attn_kernel, by the sum of the rounded probabilities (the quotient is then a weighted mean of V
+// rows, and a common offset of V cancels in its rounding error: with V = 4 + noise that error is a quarter of what the unrounded sum
+// leaves).  The log-sum-exp, in which nothing cancels, is that of the unrounded sum; LSE: it is wanted.
 // The workgroups behind those of the tail tiles make the layer's cache refresh, two chunks each (copy; none without it): the tiles
 // rarely fill the chip and leave the memory idle, while the copy needs nothing else.  32 heads: 8256 rows, tiles 77 us and copy 48
 // us one after the other, 32 832 rows 282 and 185; 4 heads, 1056 rows, d = 64: a launch less.
-template <int D>
+template <int D, bool LSE>
 __global__ __launch_bounds__(64 * kRefreshWaves, 2) void refresh_tail_kernel(const RefreshArgs p, const CacheRefresh copy) {
   using G = Geo<D>;
   constexpr int kKS = D / 16, kDT = D / 32, kOChunks = D / 4;
   constexpr int kBufBytes = 2 * G::kStageBytes;
   __shared__ __attribute__((aligned(16))) char lds[kRefreshWaves * kBufBytes];
-  __shared__ float2 ml_sh[kRefreshWaves][32];
+  __shared__ float2 mr_sh[kRefreshWaves][32];  // running maximum, sum of the rounded probabilities
+  __shared__ float l_sh[LSE ? kRefreshWaves : 1][32];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int qi = lane & 31, hh = lane >> 5;
@@ -1674,7 +1690,7 @@ __global__ __launch_bounds__(64 * kRefreshWaves, 2) void refresh_tail_kernel(con
 #pragma unroll
     for (int ks = 0; ks < kKS; ++ks) q[ks] = as_bf16x8(*reinterpret_cast<const uint4*>(qsrc + ks * 16));
   }
-  float m_run = -INFINITY, l_run = 0.f;
+  float m_run = -INFINITY, l_run = 0.f, r_run = 0.f;
   floatx16 o[kDT];
 #pragma unroll
   for (int dt = 0; dt < kDT; ++dt)
@@ -1691,26 +1707,31 @@ __global__ __launch_bounds__(64 * kRefreshWaves, 2) void refresh_tail_kernel(con
       for (int dt = 0; dt < kDT; ++dt) vop[ks][dt] = read_v_operand32<D>(stage + G::kStageBytes, dt, ks, lane);
     wait_lds_reads();
     if (t + kRefreshWaves < n_tiles) request(t + kRefreshWaves);
-    attend_subtile32<D>([&](int ks) { return kop[ks]; }, [&](int dt, int ks) { return vop[ks][dt]; }, q, low_mask(p.L - t * kSubTile), hh,
-                        p.scale_log2, m_run, l_run, o);
+    attend_subtile32<D, LSE ? 3 : 2>([&](int ks) { return kop[ks]; }, [&](int dt, int ks) { return vop[ks][dt]; }, q,
+                                     low_mask(p.L - t * kSubTile), hh, p.scale_log2, m_run, l_run, r_run, o);
   }
   store_o_tile<D>(stage, o, qi, hh);  // the wavefront's own stage, read for the last time above
-  const uintx2 sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(l_run), __float_as_uint(l_run), false, false);
-  if (hh == 0) ml_sh[wave][qi] = make_float2(m_run, __uint_as_float(sw.x) + __uint_as_float(sw.y));
+  const uintx2 sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(r_run), __float_as_uint(r_run), false, false);
+  if (hh == 0) mr_sh[wave][qi] = make_float2(m_run, __uint_as_float(sw.x) + __uint_as_float(sw.y));
+  if (LSE) {
+    const uintx2 lw = __builtin_amdgcn_permlane32_swap(__float_as_uint(l_run), __float_as_uint(l_run), false, false);
+    if (hh == 0) l_sh[wave][qi] = __uint_as_float(lw.x) + __uint_as_float(lw.y);
+  }
   __syncthreads();
   const int mq = threadIdx.x >> 4, c0 = threadIdx.x & 15;  // thread = (query, chunks c0, c0 + 16, ...)
-  float f[kRefreshWaves], mmax = -INFINITY, lsum = 0.f;
+  float f[kRefreshWaves], mmax = -INFINITY, rsum = 0.f, lsum = 0.f;
 #pragma unroll
-  for (int w = 0; w < kRefreshWaves; ++w) mmax = fmaxf(mmax, ml_sh[w][mq].x);
+  for (int w = 0; w < kRefreshWaves; ++w) mmax = fmaxf(mmax, mr_sh[w][mq].x);
 #pragma unroll
   for (int w = 0; w < kRefreshWaves; ++w) {
-    const float2 ml = ml_sh[w][mq];
-    f[w] = ml.y > 0.f ? __builtin_amdgcn_exp2f(ml.x - mmax) : 0.f;
-    lsum += f[w] * ml.y;
+    const float2 mr = mr_sh[w][mq];
+    f[w] = mr.y > 0.f ? __builtin_amdgcn_exp2f(mr.x - mmax) : 0.f;
+    rsum += f[w] * mr.y;
+    if (LSE) lsum += f[w] * l_sh[w][mq];
   }
   const int row = tile * 32 + mq;
   if (row >= p.n_q) return;
-  const float inv = lsum > 0.f ? 1.f / lsum : 0.f;
+  const float inv = rsum > 0.f ? 1.f / rsum : 0.f;
 #pragma unroll
   for (int i = 0; i < kOChunks / 16; ++i) {
     const int ch = c0 + 16 * i;
@@ -1720,7 +1741,7 @@ __global__ __launch_bounds__(64 * kRefreshWaves, 2) void refresh_tail_kernel(con
     *reinterpret_cast<uint2*>(p.out + (int64_t)h * p.osh + (int64_t)row * p.osn + ch * 4) =
         make_uint2(cvt_pk_bf16(s[0] * inv, s[1] * inv), cvt_pk_bf16(s[2] * inv, s[3] * inv));
   }
-  if (p.lse && c0 == 0) p.lse[(int64_t)h * p.n_q + row] = lsum > 0.f ? (mmax + __builtin_amdgcn_logf(lsum)) * kLn2 : -INFINITY;
+  if (LSE && c0 == 0) p.lse[(int64_t)h * p.n_q + row] = lsum > 0.f ? (mmax + __builtin_amdgcn_logf(lsum)) * kLn2 : -INFINITY;
 }
 
 // Which query tiles go to which kernel.  Every 256-query block takes the same time, so refresh_attn_kernel runs in rounds of 256
@@ -1763,8 +1784,11 @@ static hipError_t launch_refresh_t(RefreshArgs& a, const focus_shape& s, const C
   if (a.n_tail == 0) return copy ? launch_cache_refresh(*copy, D, st) : hipSuccess;
   const int64_t copies = copy ? ((int64_t)copy->n_chunks * copy->n_heads + 1) / 2 : 0;
   if (copies > (1 << 29)) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(refresh_tail_kernel<D>, dim3(8 * ceil_div(a.n_tail, 8) + (int)copies), dim3(64 * kRefreshWaves), 0, st, a,
-                     copy ? *copy : CacheRefresh{});
+  const dim3 grid(8 * ceil_div(a.n_tail, 8) + (int)copies), block(64 * kRefreshWaves);
+  if (a.lse)
+    hipLaunchKernelGGL((refresh_tail_kernel<D, true>), grid, block, 0, st, a, copy ? *copy : CacheRefresh{});
+  else
+    hipLaunchKernelGGL((refresh_tail_kernel<D, false>), grid, block, 0, st, a, copy ? *copy : CacheRefresh{});
   return hipGetLastError();
 }
 

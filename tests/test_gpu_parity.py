@@ -954,6 +954,31 @@ def test_refresh_attn_cut_into_blocks_and_tiles(G, H, n_q, L, d):
 
 
 @pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("H,n_q,L", [(256, 256, 24), (256, 256, 300), (3, 40, 24), (3, 100, 300)])   # 256-query blocks; single tiles
+def test_refresh_attn_divides_by_the_probabilities_it_adds_up(G, H, n_q, L, d):
+    """Every row is normalised by the sum of the bf16 probabilities that enter the PV product, in both kernels: the output is then a
+    weighted mean of V.  With |v - c_col| <= eps it is off by at most 2^-9 max|v - o| <= 2^-8 eps (a probability is off by 2^-9 of
+    itself) before it is stored, whatever c_col; dividing by the unrounded sum would add up to 2^-9 |c_col|.  For c_col in (2, 4) the store
+    adds half a unit, 2^-7; 2e-5 is left for fp32."""
+    g = torch.Generator().manual_seed(197 + L + d)
+    q, k = ((_rand_bf16(194 + i, H, r, d).float() * 1.5).to(torch.bfloat16) for i, r in enumerate((n_q, L)))
+    eps = 2.0 ** -6                                                     # the spacing of bf16 between 2 and 4
+    col = 2.0 + eps * torch.randint(2, 126, (1, 1, d), generator=g)
+    v = (col + eps * torch.randint(-1, 2, (H, L, d), generator=g)).to(torch.bfloat16)
+    out = torch.empty(H, n_q, d, dtype=torch.bfloat16, device=G.DEV)
+    lse = torch.empty(H, n_q, device=G.DEV)
+    qd, kd, vd = (t.to(G.DEV) for t in (q, k, v))
+    fb.refresh_attn(qd, kd, vd, fb.make_shape(qd, kd, vd, L, 64, out), out, lse)
+    s = torch.matmul(q.double(), k.double().transpose(1, 2).contiguous()) / math.sqrt(d)
+    err = (out.cpu().double() - torch.matmul(torch.softmax(s, -1), v.double())).abs().max().item()
+    assert err <= 2.0 ** -7 + 2.0 ** -8 * eps + 2e-5
+    out2 = torch.empty_like(out)
+    fb.refresh_attn(qd, kd, vd, fb.make_shape(qd, kd, vd, L, 64, out2), out2, None)
+    assert torch.equal(out, out2)                                       # whether the log-sum-exp is wanted or not
+    assert np.allclose(lse.cpu().numpy(), torch.logsumexp(s, -1).numpy(), atol=2.0 ** -8)   # rounded sums are off by up to 2^-9 of themselves
+
+
+@pytest.mark.parametrize("d", [64, 128])
 def test_refresh_attn_running_maximum_keeps_moving(G, d):
     """Keys grow along the key axis and the queries are large, so the row maxima rise in almost every sub-tile and the
     softmax is close to one-hot: the rescale branch of the kernel runs all the way through, not only at the start."""
