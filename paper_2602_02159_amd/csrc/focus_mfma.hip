@@ -1753,9 +1753,13 @@ __global__ __launch_bounds__(64 * kRefreshWaves, 2) void refresh_tail_kernel(con
 //   whole blocks, and the last few tiles of each head to the tail kernel;
 //   whole rounds of blocks, and everything else to the tail kernel.
 // 32 heads, 8256 rows (33 blocks per head, 4.1 rounds): 1213 us all in blocks, 1106 us cut; 4 heads, 1056 rows, d = 64: 26 and 9.
+// A launch has fewer than 2^32 threads (kMaxGroups workgroups).  More tail tiles than that stay in blocks; more chunks of the cache
+// refresh than fit behind the tail tiles (2^24 of them: block 1, 32 heads, half a million rows) get the launch of their own that they
+// have where there is no tail.
 template <int D>
 static hipError_t launch_refresh_t(RefreshArgs& a, const focus_shape& s, const CacheRefresh* copy, hipStream_t st) {
   constexpr int kSlots = 256;
+  constexpr int64_t kMaxGroups = ((int64_t(1) << 32) - 1) / (64 * kRefreshWaves);
   constexpr float kPerSubTile = D == 128 ? 0.85f : 0.6f, kTailCost = D == 128 ? 1.9f : 1.7f, kFixed = 5.f;
   const int tiles = ceil_div(s.n_gen, 32), last = tiles % kRefreshWaves;
   const float keys_time = (float)ceil_div(s.n_ctx + s.n_resp, kSubTile) * kPerSubTile;
@@ -1767,7 +1771,8 @@ static hipError_t launch_refresh_t(RefreshArgs& a, const focus_shape& s, const C
   const float t_whole = rounds(whole) * block_time + rounds(ragged) * tail_time;
   const float t_rounds = rounds(whole - rest) * block_time + rounds(rest * kRefreshWaves + ragged) * tail_time;
   a.n_heads = s.n_heads;
-  if (t_padded <= t_whole && t_padded <= t_rounds) {
+  const bool tails_fit = rest * kRefreshWaves + ragged + 7 <= kMaxGroups;
+  if (!tails_fit || (t_padded <= t_whole && t_padded <= t_rounds)) {
     a.n_qb = ceil_div(tiles, kRefreshWaves);
     a.n_work = (int)padded;
     a.n_tail = 0;
@@ -1782,9 +1787,13 @@ static hipError_t launch_refresh_t(RefreshArgs& a, const focus_shape& s, const C
     if (e != hipSuccess) return e;
   }
   if (a.n_tail == 0) return copy ? launch_cache_refresh(*copy, D, st) : hipSuccess;
-  const int64_t copies = copy ? ((int64_t)copy->n_chunks * copy->n_heads + 1) / 2 : 0;
-  if (copies > (1 << 29)) return hipErrorInvalidValue;
-  const dim3 grid(8 * ceil_div(a.n_tail, 8) + (int)copies), block(64 * kRefreshWaves);
+  const int64_t tails = (int64_t)8 * ceil_div(a.n_tail, 8), copies = copy ? ceil_div64((int64_t)copy->n_chunks * copy->n_heads, 2) : 0;
+  if (tails + copies > kMaxGroups) {
+    hipError_t e = launch_cache_refresh(*copy, D, st);
+    if (e != hipSuccess) return e;
+    copy = nullptr;
+  }
+  const dim3 grid((uint32_t)(copy ? tails + copies : tails)), block(64 * kRefreshWaves);
   if (a.lse)
     hipLaunchKernelGGL((refresh_tail_kernel<D, true>), grid, block, 0, st, a, copy ? *copy : CacheRefresh{});
   else

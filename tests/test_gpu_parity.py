@@ -1119,6 +1119,38 @@ def test_block_entry_equals_the_two_calls(G, H, M, N, B, d):
     assert all(torch.equal(a, b) for a, b in zip(*res))
 
 
+def test_block_entry_with_more_chunks_than_one_launch_holds(G):
+    """2^24 chunks of the cache refresh do not fit behind the query tiles in one launch (fewer than 2^32 threads, 512 per two
+    chunks); with blocks of one row K_bar is K itself, and the heads share the new states so that the inputs stay small."""
+    H, M, d, n_q = 32, (1 << 19) + 3, 64, 33
+    k_new, v_new = (_rand_bf16(181 + i, 1, M, d).to(G.DEV).expand(H, M, d) for i in range(2))
+    q = _rand_bf16(183, H, n_q, d).to(G.DEV)
+    kc, vc = (torch.full((H, M, d), float("nan"), dtype=torch.bfloat16, device=G.DEV) for _ in range(2))
+    kbar = torch.full((H, M, d), float("nan"), device=G.DEV)
+    out, out2 = (torch.full((H, n_q, d), float("nan"), dtype=torch.bfloat16, device=G.DEV) for _ in range(2))
+    fb.block_entry(kc, vc, fb.make_shape(q, kc, vc, M, 1, out), q, k_new, v_new, kbar, out, None)
+    fb.refresh_attn(q, kc, vc, fb.make_shape(q, kc, vc, M, 1, out2), out2, None)
+    torch.cuda.synchronize()
+    assert torch.equal(out, out2) and not torch.isnan(out.float()).any()
+    for h in range(H):
+        assert torch.equal(kc[h], k_new[0]) and torch.equal(vc[h], v_new[0]) and torch.equal(kbar[h], k_new[0].float())
+
+
+def test_refresh_attn_with_more_tiles_than_one_launch_holds(G):
+    """Seven tiles of every head would be 2^23 tiles and more, 512 threads each, past what a launch holds; all heads share Q, K, V and
+    the output (they write the same values), and the log-sum-exp tells whether every head has run."""
+    H, n_q, d, L = (1 << 23) // 7 + 1, 224, 64, 1
+    q, k, v = (_rand_bf16(184 + i, 1, r, d).to(G.DEV).expand(H, r, d) for i, r in enumerate((n_q, L, L)))
+    store = torch.full((1, n_q, d), float("nan"), dtype=torch.bfloat16, device=G.DEV)
+    out = store.expand(H, n_q, d)
+    lse = torch.full((H, n_q), float("nan"), device=G.DEV)
+    fb.refresh_attn(q, k, v, fb.make_shape(q, k, v, L, 64, out), out, lse)
+    torch.cuda.synchronize()
+    assert torch.equal(store[0], v[0].expand(n_q, d))                   # one key
+    ref = torch.matmul(q[0].double(), k[0, 0].double()) / math.sqrt(d)
+    assert torch.allclose(lse[0].double(), ref, atol=1e-5) and torch.equal(lse, lse[:1].expand_as(lse))
+
+
 def test_block_entry_calls_replay_in_a_hip_graph(G):
     """The block-entry calls and the group expansion enqueue kernels only, so they can be captured: three replays, the
     outputs wiped in between, each equal to the eager result bit for bit."""
