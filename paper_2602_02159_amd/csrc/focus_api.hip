@@ -50,7 +50,7 @@ static void plan_queries(SplitPlan& p, int max_active, int most) {
 
 // As many splits as the target allows, at least one round of four sub-tiles each
 static void plan_splits(SplitPlan& p, int n_heads, int q_groups, int target_groups) {
-  const int per_head = std::max(1, target_groups / (n_heads * q_groups));
+  const int per_head = (int)std::max<int64_t>(1, target_groups / ((int64_t)n_heads * q_groups));
   p.n_split = std::max(1, std::min(per_head, ceil_div(p.n_sub, kWavesPerGroup)));
 }
 

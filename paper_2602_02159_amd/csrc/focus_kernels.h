@@ -21,6 +21,15 @@ constexpr int kGridSlice = 32768;
 static inline dim3 grid_x_yz(int n_x, int n) { return dim3(n_x, n < kGridSlice ? n : kGridSlice, ceil_div(n, kGridSlice)); }
 __device__ __forceinline__ int grid_yz() { return (int)(blockIdx.z * kGridSlice + blockIdx.y); }
 static inline int64_t ceil_div64(int64_t a, int64_t b) { return (a + b - 1) / b; }
+// A list of n workgroups, in slices along y: one axis of a launch has fewer than 2^32 threads, 2^23 workgroups of 512.  Slices are a
+// multiple of eight long, so that list_index() mod 8 = blockIdx.x mod 8 stays the round-robin place among the XCDs.  The last slice is
+// whole: indices of n and more occur.
+constexpr int kListSlice = 1 << 22;
+constexpr int64_t kMaxList = (int64_t(1) << 31) - kListSlice;  // list_index() is an int
+static inline dim3 grid_list(int64_t n) {
+  return dim3((uint32_t)(n < kListSlice ? n : kListSlice), (uint32_t)ceil_div64(n, kListSlice));
+}
+__device__ __forceinline__ int list_index() { return (int)(blockIdx.y * kListSlice + blockIdx.x); }
 
 // How the key axis of an MFMA kernel is cut: n_sub sub-tiles per head, n_split workgroups per (head, query group).  The
 // splits take turns: split s works on the rounds of four sub-tiles (one per wavefront) s, s + n_split, s + 2 n_split, ...
@@ -32,6 +41,11 @@ struct SplitPlan {
   bool pipelined = false;  // attention only: wavefronts walk several sub-tiles, use the double-buffered key loop
   int q_tiles, q_tiles_per_group, q_groups, q_pad;  // q_pad = 16 * q_tiles
 };
+
+// workgroups of a launch whose list has the query groups of eight (head, key split) pairs next to each other
+static inline int64_t query_group_list(const SplitPlan& p, int n_heads) {
+  return ceil_div64((int64_t)p.n_split * n_heads, 8) * 8 * p.q_groups;
+}
 
 SplitPlan plan_attention(const focus_shape& s, int max_active, int n_keep, int n_sink);
 SplitPlan plan_attention_dense(const focus_shape& s, int max_active);  // all M + N rows, no block structure

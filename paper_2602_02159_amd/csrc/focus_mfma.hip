@@ -921,7 +921,7 @@ __device__ __forceinline__ void store_o_tile(char* dst, const floatx16 (&o)[D / 
 // Bit 3: the rows are read by several query groups and should stay in the L2.  Bit 4 (with bit 0): more than 256 blocks to rank.
 // Bound by HBM.  32 heads, 32 832 keys, all kept: 89 us with 30 queries (6.0 TB/s; 16-query tiles on shared sub-tiles took 94),
 // 95 us with 60 (101); half of the 64-row blocks and 327 sinks: 53 us (57); 4 K/V heads, 196 queries, 16 640 keys: 28 us (42).
-// Grid: one-dimensional.  Workgroups go to the XCDs round-robin, so the query groups of one (head, key split) pair are
+// Grid: one list (list_index).  Workgroups go to the XCDs round-robin, so the query groups of one (head, key split) pair are
 // placed eight apart: they run on the same XCD at about the same time and its L2 serves their common K/V rows.
 template <int D, int NT, int MODE>
 __global__ __launch_bounds__(256 * NT, NT == 2 || (MODE & 4) == 0 ? 2 : 1) void wide_attn_kernel(ATTN_FIRST_PARAMS, const AttnArgs args) {
@@ -947,7 +947,7 @@ __global__ __launch_bounds__(256 * NT, NT == 2 || (MODE & 4) == 0 ? 2 : 1) void 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int slot = wave & (kWavesPerGroup - 1), tile = NT == 1 ? 0 : wave >> 2;
   const int qi = lane & 31, hh = lane >> 5;
-  const int slot8 = (int)blockIdx.x >> 3;
+  const int slot8 = list_index() >> 3;
   const int pair = (slot8 / p.q_groups) * 8 + (int)(blockIdx.x & 7u), qg = slot8 % p.q_groups;
   if (pair >= p.n_split * p.H) return;  // whole workgroup
   const int h = pair / p.n_split, split = pair - h * p.n_split;
@@ -1210,7 +1210,7 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(const float* __restri
 // LOOP: the mode bits of the key loop
 template <int D, int NT, int LOOP>
 static void launch_wide_t(const AttnArgs& a, const SplitPlan& p, bool fused, hipStream_t st) {
-  const dim3 grid(ceil_div(p.n_split * a.H, 8) * 8 * p.q_groups), block(256 * NT);
+  const dim3 grid = grid_list(query_group_list(p, a.H)), block(256 * NT);
   constexpr int kKeep = LOOP & 8;
   const bool many = a.n_b > 256;
   if (fused && p.pipelined && many)
@@ -1233,6 +1233,7 @@ static hipError_t launch_attn_t(const AttnArgs& a, const SplitPlan& p, bool fuse
   const dim3 grid = p.pipelined ? dim3(p.n_split, a.H) : dim3(a.H, p.n_split), block(256);
   if (p.q_tiles_per_group > 1) {
     if (a.logits_out != nullptr) return hipErrorInvalidValue;  // logits are spilled for one 16-query tile only
+    if (query_group_list(p, a.H) > kMaxList) return hipErrorInvalidValue;
     if (p.q_tiles_per_group > 2)
       launch_wide_t<D, 2, 2 | 4>(a, p, fused, st);
     else if (p.q_groups > 1)
@@ -2013,7 +2014,7 @@ __global__ __launch_bounds__(256, NT == 1 ? 4 : 2) void wide_logits_kernel(const
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int qi = lane & 31, hh = lane >> 5;
-  const int slot8 = (int)blockIdx.x >> 3;
+  const int slot8 = list_index() >> 3;
   const int pair = (slot8 / q_groups) * 8 + (int)(blockIdx.x & 7u), qg = slot8 % q_groups;
   if (pair >= n_split * p.H) return;  // whole workgroup
   const int h = pair / n_split, split = pair - h * n_split;
@@ -2194,8 +2195,8 @@ static hipError_t launch_logits_t(const LogitArgs& a, const SplitPlan& p, int mo
       hipLaunchKernelGGL((qk_logits_kernel<D, false, false>), grid, dim3(256), 0, st, LOGITS_ARGS, a);
     return hipGetLastError();
   }
-  if (mode == 0) return hipErrorInvalidValue;
-  const dim3 grid(ceil_div(p.n_split * a.H, 8) * 8 * p.q_groups);
+  if (mode == 0 || query_group_list(p, a.H) > kMaxList) return hipErrorInvalidValue;
+  const dim3 grid = grid_list(query_group_list(p, a.H));
 #define WIDE_LOGITS(NT)                                                                                                 \
   if (mode == 2)                                                                                                        \
     hipLaunchKernelGGL((wide_logits_kernel<D, NT, 2, false>), grid, dim3(256), 0, st, LOGITS_ARGS, p.q_groups, a);      \

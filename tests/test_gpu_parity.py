@@ -462,6 +462,31 @@ def test_sparse_attn_unattended_rows_may_hold_inf_or_nan(G, n_act):
     assert np.allclose(lse.cpu().numpy(), ref_lse, atol=2e-3)
 
 
+@pytest.mark.parametrize("probe,H", [(False, 1 << 13), (True, 1 << 14)])
+def test_more_query_groups_than_one_grid_axis_holds(G, probe, H):
+    """2^24 workgroups of 256 threads (heads x query groups) do not fit the 2^32 threads of one grid axis.  All heads share Q, K, V and
+    the output, where they write the same values; the log-sum-exps, and the column mass in the probe layer, tell whether all have run."""
+    n_q, d, L = 1 << 16, 64, 1
+    q, k, v = (_rand_bf16(310 + i, 1, r, d).to(G.DEV).expand(H, r, d) for i, r in enumerate((n_q, L, L)))
+    store = torch.full((1, n_q, d), float("nan"), dtype=torch.bfloat16, device=G.DEV)
+    out, lse = store.expand(H, n_q, d), torch.full((H, n_q), float("nan"), device=G.DEV)
+    s = fb.make_shape(q, k, v, L, 64, out)
+    active, one, col = torch.arange(n_q, dtype=torch.int32, device=G.DEV), G.i32([0]), torch.full((L,), float("nan"), device=G.DEV)
+    w = G.ws(fb.workspace_bytes(fb.FN_PROBE_LAYER if probe else fb.FN_SPARSE_ATTN, s, n_q, 1, 0))
+    if probe:
+        sinks = G.i32(None, 1)
+        fb.probe_layer(q, active, None, k, v, s, 1, out, lse, col, sinks, w)
+        assert col.item() == 1.0 and sinks.item() == 0                  # sums of powers of two
+    else:
+        fb.sparse_attn(q, active, None, k, v, s, one, 1, None, 0, out, lse, w)
+    torch.cuda.synchronize()
+    assert torch.equal(store[0], v[0].expand(n_q, d))                   # one key
+    ref = torch.matmul(q[0].double(), k[0, 0].double()) / math.sqrt(d)
+    assert torch.allclose(lse[0].double(), ref, atol=1e-5)
+    for h in range(0, H, 1 << 10):
+        assert torch.equal(lse[h:h + (1 << 10)], lse[:1].expand(1 << 10, n_q))
+
+
 # ------------------------------------------------------------------------------------------------ probe layer
 @pytest.mark.parametrize("H,M,N,d,B,n_gen,n_act,n_sink", [
     (4, 1024, 32, 64, 64, 32, 8, 2),          # the tiny shape: a single key split
