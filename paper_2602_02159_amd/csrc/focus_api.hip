@@ -277,12 +277,15 @@ struct LayerWs {
   ScoreWs sc;
   AttnWs at;
 };
+// Past kFusedMaxBlocks the blocks are ranked by a launch of their own, which is the last to read the relevances: the attention's
+// partial results then take their place.  (One after the other, 50 000 blocks and more of 32 heads could exceed the scratch array of
+// focus_sparse_layer_static by the few per cent that the splits of the attention had grown.)
 static LayerWs ws_layer(const focus_shape& s, const SplitPlan& p) {
   LayerWs w;
   w.sc = ws_block_scores(s);
   w.at = ws_attn(s, p);
-  w.attn = w.sc.total;
-  w.total = w.attn + w.at.total;
+  w.attn = ceil_div(s.n_ctx, s.block) > kFusedMaxBlocks ? 0 : w.sc.total;
+  w.total = std::max(w.sc.total, w.attn + w.at.total);
   return w;
 }
 

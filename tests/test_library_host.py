@@ -57,6 +57,16 @@ def test_workspace_sizes(L):
     assert fb.workspace_bytes(fb.FN_FIND_SINKS, _shape(head_dim=96), 8) == 0
 
 
+@pytest.mark.parametrize("H,d,M,N,B,n_gen,n_act,n_keep,n_sink", [
+    (8, 128, 174753, 256, 1, 64, 15, 509, 0), (32, 128, 96231, 32, 2, 16, 13, 163, 4), (32, 64, 449902, 0, 8, 32, 4, 195, 0),
+    (5, 128, 4390741, 256, 16, 128, 11, 835, 16), (1, 64, 1838849, 1, 2, 16, 11, 5244, 16)])
+def test_layers_of_many_blocks_fit_the_static_scratch_array(L, H, d, M, N, B, n_gen, n_act, n_keep, n_sink):
+    """Shapes within 6 % of the 8 MiB of focus_sparse_layer_static, with block relevances of 5 MB and more."""
+    s = _shape(n_heads=H, head_dim=d, n_ctx=M, n_resp=N, block=B, n_gen=n_gen)
+    assert fb.workspace_bytes(fb.FN_BLOCK_SCORES, s) > (4 << 20)
+    assert 0 < fb.workspace_bytes(fb.FN_SPARSE_LAYER, s, n_act, n_keep, n_sink) <= (8 << 20)
+
+
 def test_bad_arguments_are_rejected_on_the_host(L):
     fake = C.c_void_p(4096)  # never dereferenced: validation fails first
     s = _shape()

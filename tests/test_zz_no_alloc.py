@@ -84,6 +84,26 @@ def test_static_scratch_entry_point_matches_the_workspace_one_twice_in_a_row():
     assert torch.equal(a[2], b3[2])
 
 
+def test_static_scratch_entry_point_with_relevances_and_partial_results_in_the_same_place():
+    # 40 003 blocks: ranked by a launch of their own, after which the attention's partial results overwrite their relevances
+    H, M, N, d, B, n_gen, n_keep = 8, 40003, 100, 128, 1, 64, 509
+    g = torch.Generator(device=DEV).manual_seed(12)
+    q, k, v = (torch.randn(H, r, d, generator=g, device=DEV).to(torch.bfloat16) for r in (n_gen, M + N, M + N))
+    kbar = k[:, :M].float().contiguous()
+    focus, active = (torch.arange(n, dtype=torch.int32, device=DEV) for n in (6, 15))
+    none = torch.empty(0, dtype=torch.int32, device=DEV)
+    a, b = _both(q, k, v, M, B, focus, active, None, n_keep, none, kbar)
+    _same(a, b, 15)
+    s = fb.make_shape(q, k, v, M, B, a[2])
+    scores, kept = torch.full((M,), float("nan"), device=DEV), torch.full((n_keep,), -7, dtype=torch.int32, device=DEV)
+    out, lse = torch.full_like(a[2], float("nan")), torch.full_like(a[3], float("nan"))
+    ws = [torch.empty(fb.workspace_bytes(fn, s, 15, n_keep, 0), dtype=torch.uint8, device=DEV) for fn in (fb.FN_BLOCK_SCORES, fb.FN_SPARSE_ATTN)]
+    fb.block_scores(q, focus, None, None, kbar, s, n_keep, scores, kept, ws[0])
+    fb.sparse_attn(q, active, None, k, v, s, kept, n_keep, None, 0, out, lse, ws[1])
+    torch.cuda.synchronize()
+    _same(a, (scores, kept, out, lse), 15)
+
+
 def test_static_scratch_entry_point_rejects_shapes_beyond_its_array():
     # 64 active queries over half of 512 blocks (the paper's own hyper-parameters at 32K) need more than 8 MiB of partial results
     L = fb.lib()
