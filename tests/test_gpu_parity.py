@@ -207,6 +207,44 @@ def test_select_and_find_sinks_equals_the_two_calls(G, n_gen, k, window, lo, hi,
         assert all(torch.equal(a, b) for a, b in zip(*res))
 
 
+@pytest.mark.parametrize("d", [64, 128])
+def test_select_and_find_sinks_with_logits_past_the_memory_side_cache(G, d):
+    """More than 200 MB of spilled logits, written non-temporally, with the selection in the same launch: the two calls' results bit
+    for bit, and column masses that agree with fp64."""
+    H, M, N, n_gen, k, n_sink = 32, 102500, 37, 48, 13, 5
+    L = M + N
+    assert H * L * 64 > 200 << 20
+    g = torch.Generator(device=G.DEV).manual_seed(330 + d)
+    q, kk = (torch.randn(H, r, d, generator=g, device=G.DEV).to(torch.bfloat16) for r in (n_gen, L))
+    planted = torch.tensor([0, 31, 50001, 77777, M - 1], device=G.DEV)   # clear winners among the masses
+    kk[:, planted] += 3.0 * q.float().mean(1, keepdim=True).to(torch.bfloat16) * torch.arange(5, 10, device=G.DEV).view(1, 5, 1)
+    conf = torch.rand(n_gen, generator=g, device=G.DEV)
+    masked = (torch.rand(n_gen, generator=g, device=G.DEV) < 0.7).to(torch.uint8)
+    s = fb.make_shape(q, kk, None, M, 128)
+    res = []
+    for fused in (False, True):
+        focus, active, counts, sinks = G.i32(None, k), G.i32(None, k), G.i32(None, 2), G.i32(None, n_sink)
+        col = torch.full((L,), float("nan"), device=G.DEV)
+        w = G.ws(fb.workspace_bytes(fb.FN_FIND_SINKS, s, k))
+        if fused:
+            fb.select_and_find_sinks(conf, masked, k, 0, 0, n_gen, focus, active, counts, q, kk, s, n_sink, col, sinks, w)
+        else:
+            fb.select_queries(conf, masked, k, 0, 0, n_gen, focus, active, counts)
+            fb.find_sinks(q, active, counts, kk, s, n_sink, col, sinks, w)
+        torch.cuda.synchronize()
+        res.append((focus, active, counts, col, sinks))
+    assert all(torch.equal(a, b) for a, b in zip(*res))
+    _, active, counts, col, sinks = res[0]
+    rows = active[:int(counts[1])].long()
+    S = torch.zeros(L, dtype=torch.float64, device=G.DEV)
+    for h in range(H):
+        z = torch.matmul(q[h, rows].double(), kk[h].double().T.contiguous()) / math.sqrt(d)
+        S += torch.softmax(z, -1).mean(0) / H
+    assert torch.allclose(col.double(), S, rtol=2e-4, atol=1e-9)
+    assert fo.decision_margin(S.cpu().numpy(), n_sink, np.arange(L) < M) > 1e-5
+    assert sinks.cpu().tolist() == fo.select_sinks(S.cpu().numpy(), M, n_sink).tolist()
+
+
 def test_find_sinks_equal_keys_fall_back_to_lowest_positions(G):
     H, M, N, d = 2, 500, 12, 64
     k = _rand_bf16(9, 1, 1, d).expand(H, M + N, d).contiguous().to(G.DEV)
@@ -457,6 +495,36 @@ def test_sparse_attn_unattended_rows_may_hold_inf_or_nan(G, n_act):
     v[:, bad] = float("nan")
     v[:, 0] = float("inf")                                       # row 0 is not attended
     assert not attended[0]
+    out, lse = G.gpu_sparse_attn(q.to(G.DEV), G.i32(active), None, k.to(G.DEV), v.to(G.DEV), M, B, G.i32(kept), G.i32(sinks))
+    G.assert_attention_close(out, ref)
+    assert np.allclose(lse.cpu().numpy(), ref_lse, atol=2e-3)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("H,n_act,loop", [
+    (2, 20, False), (2, 100, False),                             # one 32-query tile, several query groups: a sub-tile per slot
+    (64, 16, True), (64, 20, True), (64, 40, True), (32, 100, True),   # one, one, two tiles and query groups: slots walk several sub-tiles
+])
+def test_sparse_attn_unattended_rows_may_hold_inf_or_nan_in_every_kernel(G, H, n_act, loop, d):
+    """As above, for every tiling of the queries, with and without a key loop; a sink list of more than one sub-tile, unsorted, with
+    entries in kept blocks, repeated, negative and past the prompt."""
+    M, N, B, n_gen = 2500, 21, 48, 112
+    n_b = -(-M // B)                                             # 53 blocks, the last one ragged (rows 2496 .. 2499)
+    rng = np.random.default_rng(78 + n_act)
+    kept = np.sort(rng.choice(n_b - 1, 29, replace=False)).tolist() + [n_b - 1]
+    sinks = rng.permutation(np.concatenate([rng.choice(M, 36, replace=False), [kept[0] * B, -1, M, 7, 7, 2 * M]])).tolist()
+    n_sub, per_head = 30 * 2 + 1 + 2, max(1, 512 // (H * (-(-n_act // 32) if n_act > 64 else 1)))
+    assert (per_head * 4 < n_sub) == loop                        # the split plan: 512 workgroups, four sub-tiles each at a time
+    active = np.sort(rng.choice(n_gen, n_act, replace=False))
+    q, k, v = (_rand_bf16(320 + i, H, r, d) for i, r in enumerate((n_gen, M + N, M + N)))
+    I_p = fo.attention_index_set(sinks, kept, M, B)
+    attended = np.zeros(M + N, bool)
+    attended[I_p] = True
+    attended[M:] = True
+    ref, ref_lse = fo.sparse_attention(G.to_np(q), active, G.to_np(k), G.to_np(v), I_p, M)
+    bad = torch.tensor(~attended)
+    k[:, bad] = float("inf")
+    v[:, bad] = float("nan")
     out, lse = G.gpu_sparse_attn(q.to(G.DEV), G.i32(active), None, k.to(G.DEV), v.to(G.DEV), M, B, G.i32(kept), G.i32(sinks))
     G.assert_attention_close(out, ref)
     assert np.allclose(lse.cpu().numpy(), ref_lse, atol=2e-3)
