@@ -201,9 +201,9 @@ int focus_sparse_attn(const void* Q, const int32_t* active_idx, const int32_t* c
  * One sparse layer of Alg. 1 in a single call: block relevance (Eq. 7), Top-C, index union (Eq. 8) and sparse
  * attention (Eq. 9) — exactly focus_block_scores followed by focus_sparse_attn, with the same arguments and
  * bit-identical outputs (scores, kept_blocks, out, lse), but in three kernel launches instead of four: the
- * attention kernel ranks the blocks itself from the per-head partial relevances instead of waiting for a
- * separate Top-C kernel.  kbar NULL: the first launch scans K and forms the block means on the fly.
- * With more than 256 prompt blocks the call falls back to the separate kernels.
+ * attention kernel ranks the blocks itself from the partial relevances instead of waiting for a separate Top-C
+ * kernel.  kbar NULL: the first launch scans K and forms the block means on the fly.
+ * With more than 1024 prompt blocks (kbar NULL: more than 256) the call falls back to the separate kernels.
  */
 int focus_sparse_layer(const void* Q, const int32_t* focus_idx, const int32_t* active_idx, const int32_t* counts,
                        int32_t n_focus_max, int32_t max_active, const void* K, const void* V, const float* kbar,

@@ -150,14 +150,14 @@ static SinkWs ws_find_sinks(const focus_shape& s, const SplitPlan& p) {
   off += align_up((size_t)s.n_heads * p.q_pad * sizeof(float));
   w.col_mass = off;
   off += align_up(L * sizeof(float));
-  w.cand = off;  // first-round nominees of the sink tournament: positions, then order keys
-  off += align_up((size_t)2 * kMaxNominees * sizeof(int32_t));  // positions, then their keys
+  w.cand = off;  // nominees of the 128-key groups: positions, then their keys
+  off += align_up((size_t)2 * kMaxNominees * sizeof(int32_t));
   w.total = off;
   return w;
 }
 
 struct ProbeWs {
-  size_t part_o, part_ml, lse2, scratch, col_mass, cand, total;  // scratch: logits [H, L, 16] or column sums [q_groups H, L]
+  size_t part_o, part_ml, lse2, scratch, col_mass, cand, total;  // scratch: logits [H, ceil(L / 4), 16, 4] or column sums [q_groups H, L]
 };
 struct AttnWs {
   size_t part_o, part_ml, total;
@@ -190,14 +190,15 @@ static ProbeWs ws_probe_layer(const focus_shape& s, const SplitPlan& pa, const S
   off += align_up(sinks_two_pass(pl) ? (size_t)pl.q_groups * s.n_heads * L * sizeof(float) : spilled_logits_bytes(s));
   w.col_mass = off;
   off += align_up(L * sizeof(float));
-  w.cand = off;
-  off += align_up((size_t)2 * kMaxNominees * sizeof(int32_t));  // positions, then their keys
+  w.cand = off;  // as above
+  off += align_up((size_t)2 * kMaxNominees * sizeof(int32_t));
   w.total = off;
   return w;
 }
 
 // Second half of the sink identification: column masses S from the kept logits or per-part column sums, then Top-N_sink.  Few
-// sinks, or not too many: the 128-key groups of the column-mass kernel nominate and one workgroup decides; else a radix select.
+// sinks, or not too many: the 128-key groups of the column-mass kernel nominate and one workgroup decides (a tournament of up to 16
+// sinks, or a ranking of all nominees); else a radix select.
 // lse2: row log-sum-exps, or with n_split > 0 the statistics of the key splits (then lse_scratch takes the log-sum-exps).
 static int column_mass_and_sinks(const char* who, const float* src, bool two_pass, const float* lse2, int n_split, float* lse_scratch,
                                  const int32_t* counts, int max_active, int q_groups, const focus_shape& s, int n_sink, float* S,

@@ -136,8 +136,8 @@ struct SelectArgs {
 hipError_t launch_qk_logits(const void* Q, const int32_t* active_idx, const int32_t* counts, int max_active,
                             const void* K, const focus_shape& s, const SplitPlan& p, int mode, float* logits,
                             float* part_ml, const float* lse2, float* colpart, hipStream_t st, const SelectArgs* select = nullptr);
-// Extra arguments of the fused layer path: the attention kernel ranks the blocks itself from the per-head partial
-// relevances (n_b <= kFusedMaxBlocks; kFusedMaxBlocksPerHead if they come per head from a K scan).
+// Extra arguments of the fused layer path: the attention kernel ranks the blocks itself from the partial relevances
+// (n_b <= kFusedMaxBlocks; kFusedMaxBlocksPerHead if they come per head from a K scan).
 constexpr int kFusedMaxBlocks = 1024, kFusedMaxBlocksPerHead = 256;
 struct FusedTopC {
   const float* rel_part;  // [ceil(H / 4), n_b] from launch_block_relevance, or with per_head [H, n_b]
@@ -150,7 +150,7 @@ struct FusedTopC {
 // plan_attention_dense); optionally the scaled logits (at most 16 active queries) and the base-2 row log-sum-exps are
 // written for the sink scoring that follows.
 struct DenseProbe {
-  float* logits_out;  // [H, M + N, 16] or null
+  float* logits_out;  // [H, ceil((M + N) / 4), 16 queries, 4 keys] or null
   float* lse2_out;    // [H, q_pad] or null
 };
 hipError_t launch_sparse_attn(const void* Q, const int32_t* active_idx, const int32_t* counts, int max_active,

@@ -5,17 +5,20 @@
 //                        (v_mfma_f32_16x16x32_bf16).  The same kernel with every row kept is the dense layer (probe
 //                        layer, dense comparison).
 //   wide_attn_kernel     the same for more than 16 queries (v_mfma_f32_32x32x16_bf16; described where it is defined).
+//   attn_combine_kernel  merges the key splits of the two kernels above.
 //   refresh_attn_kernel  block entry (Alg. 1): dense attention of EVERY position over every key, the one MFMA-bound
 //                        launch of the method (v_mfma_f32_32x32x16_bf16; described where it is defined).
-//   qk_logits_kernel     Eq. 6: scaled logits of the active queries against every key of the probe layer with the
-//                        per-split row maxima / sums of the softmax normaliser, or — second pass, for more than 16
-//                        queries — the probabilities summed over the queries (16x16x32).
+//   refresh_tail_kernel  the query tiles the former leaves over, with the layer's cache refresh beside them.
+//   qk_logits_kernel     Eq. 6, up to 16 active queries: their scaled logits against every key of the probe layer, written
+//                        out, with the per-split row maxima / sums of the softmax normaliser (v_mfma_f32_16x16x32_bf16).
+//   wide_logits_kernel   the same for more than 16 queries, in two passes over K (v_mfma_f32_32x32x16_bf16): the normalisers,
+//                        then the probabilities summed over the queries.
 //
 // Work decomposition.  The key axis of one head is cut into sub-tiles of 32 rows, staged in LDS with an XOR
 // swizzle (applied on the global side of the load) so that the operand reads are conflict free.  The rows go from HBM
-// straight into a slot of LDS (global_load_lds_dwordx4: no staging registers, no ds_write); with at most 16 queries a
-// wavefront owns a sub-tile from the memory request to the MFMAs, wavefronts never wait for each other inside the key loop
-// and meet once, at the end, to merge their softmax states.
+// straight into a slot of LDS (global_load_lds_dwordx4: no staging registers, no ds_write; refresh_attn_kernel alone goes
+// through registers).  With up to 32 queries in a group a wavefront owns a sub-tile from the memory request to the MFMAs,
+// wavefronts never wait for each other inside the key loop and meet once, at the end, to merge their softmax states.
 //
 // MFMA layout used (16x16x32, D[i][j] += sum_k A[i][k] B[k][j]; lane = 16*g + c):
 //   A operand: lane holds A[i = c][k = 8g .. 8g+7];  B operand: lane holds B[k = 8g .. 8g+7][j = c];
@@ -603,7 +606,7 @@ __device__ __forceinline__ SinkUnion prepare_union(const AttnArgs& p, int split,
 // against the one query tile and keeps its own running softmax; the four states are merged at the end.
 //
 // FUSE bit 0 clear: kept_blocks comes from memory.
-// FUSE bit 0 set (fused layer path): the workgroup first assembles R_b from the per-head partial relevances and ranks
+// FUSE bit 0 set (fused layer path): the workgroup first assembles R_b from the partial relevances and ranks
 // them itself — every workgroup repeats this small computation instead of waiting for a separate Top-C kernel.
 // FUSE bit 3 set (with bit 0): the partial relevances come per head, from a K scan, and not per group of four heads.
 // FUSE bit 4 set (with bit 0): more than 256 blocks to rank.
@@ -2214,7 +2217,7 @@ static hipError_t launch_logits_t(const LogitArgs& a, const SplitPlan& p, int mo
   return hipGetLastError();
 }
 
-// mode 0: logits + part_ml out; mode 1: part_ml out; mode 2: lse2 in, colpart out (see qk_logits_kernel)
+// mode 0: logits + part_ml out; mode 1: part_ml out; mode 2: lse2 in, colpart out (0: qk_logits_kernel; 1, 2: wide_logits_kernel)
 hipError_t launch_qk_logits(const void* Q, const int32_t* active_idx, const int32_t* counts, int max_active,
                             const void* K, const focus_shape& s, const SplitPlan& p, int mode, float* logits,
                             float* part_ml, const float* lse2, float* colpart, hipStream_t st, const SelectArgs* select) {

@@ -342,7 +342,7 @@ hipError_t launch_block_means_relevance(const void* K, const void* Q, const int3
 // A wavefront owns one head and P R consecutive blocks (R = 4 at d = 128, 8 at 64), a lane one 8-wide slice of d of one block
 // row; the focus indices and the kbar loads are issued first, then the focus rows of Q: two dependent memory round trips.
 // PER_HEAD: part[h, b].  Otherwise the four heads of the workgroup meet in LDS and part[h / 4, b] is their sum, so that whoever
-// ranks the blocks — every workgroup of the attention kernel, or a single one past 256 blocks — has a quarter to read.
+// ranks the blocks — every workgroup of the attention kernel, or a single one past 1024 blocks — has a quarter to read.
 // Heads are the fast grid axis: workgroups go to the XCDs round-robin, so those of one head share an L2 and its focus rows.
 // Sparse layer of 32 heads with 256 blocks 15.3 -> 14.9 us (a workgroup per head and 32 blocks, its 16 focus rows summed by all
 // four wavefronts through LDS, and every attention workgroup adding 32 partial relevances per block), 4 heads at 1K 11.0 -> 10.4.
@@ -467,10 +467,10 @@ hipError_t launch_lse_combine(const float* part_ml, int H, int q_pad, int n_spli
 //   PRE = true:  `src` holds per-part column sums [n_parts, L] (already summed over a part's queries); thread
 //                (key, part group pg) adds parts pg, pg + 4, ..., eight loads in flight, then the four groups are added.
 // S_j = total / (H * n_act).
-// With cand != nullptr (small N_sink) the workgroup also plays the first round of the sink tournament: the n_sink
-// largest masses among its own prompt positions (j < M; ties to the lower j) go to cand[wg * n_sink ..], ascending,
-// padded with -1, and their order keys + 1 to cand_keys at the same places (0 beside a -1).  The overall Top-N_sink is
-// a subset of the union of these lists (sink_final_kernel).
+// With cand != nullptr the workgroup also nominates: the n_sink largest masses among its own prompt positions (j < M; ties to
+// the lower j) go to cand[wg * n_sink ..], ascending, padded with -1, and their order keys + 1 to cand_keys at the same places
+// (0 beside a -1).  With n_sink = N_sink the overall Top-N_sink is a subset of the union of these lists (sink_final_kernel); with
+// fewer nominees per group sink_rank_kernel sees to the groups that may hold more.
 constexpr int kMassKeys = 128;
 
 // LSE (with PRE = false): lse2 holds the softmax statistics (max, sum) of n_split key splits per row, [H, 16, n_split], instead,

@@ -4,7 +4,7 @@
 // Order: larger value first, ties to the lower index; -0.0 == +0.0; NaN below every number.
 // Output: the selected indices in ascending order, then -1 up to k, and the count.
 //
-// Three paths, one workgroup each:
+// Paths, one workgroup each (block_topk: the first three; block_topk_planes, inside the attention kernels: the fourth):
 //   * n <= 256, small k : every wavefront selects among its own 64 candidates (one key per lane) by a bitwise
 //                     search over ballot popcounts (at most 32 steps; it ends as soon as exactly k keys clear the
 //                     threshold under test), then one wavefront selects among the winners.
@@ -17,7 +17,10 @@
 //                     keys equal to T are still needed; an ordered compaction then emits every key > T and the
 //                     first needed keys == T in index order.  Runs longer than 32 keys per thread re-read
 //                     memory in every pass.
-// Both are deterministic: nothing depends on the order in which atomics land.
+//   * up to 1024 keys in registers, a few per thread of 4 or 8 wavefronts: a radix search of the k-th largest key with an
+//                     LDS histogram per pass, which every wavefront scans by itself (block_topk_planes).
+// Many sinks go through sink_rank_kernel (focus_small.hip), which shares radix_digit.
+// All are deterministic: nothing depends on the order in which atomics land.
 #pragma once
 
 #include "focus_common.h"

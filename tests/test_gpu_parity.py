@@ -598,7 +598,7 @@ def test_probe_layer(G, H, M, N, d, B, n_gen, n_act, n_sink):
     (4, 1024, 32, 64, 64, 32, 8, 8, 4, 2),
     (8, 4096, 64, 128, 128, 64, 16, 16, 5, 4),        # 32 blocks, several splits per head
     (3, 3000, 40, 128, 48, 48, 5, 40, 9, 7),          # ragged, three query tiles
-    (2, 16384, 64, 128, 64, 64, 16, 16, 25, 4),       # exactly 256 blocks: the largest fused case
+    (2, 16384, 64, 128, 64, 64, 16, 16, 25, 4),       # exactly 256 blocks: the most with one key per thread of the ranking
     (2, 8192, 64, 128, 16, 64, 16, 16, 40, 4),        # 512 blocks
     (2, 16385, 64, 64, 64, 64, 16, 16, 30, 4),        # one block more than a workgroup has threads
     (2, 8208, 0, 64, 16, 64, 4, 50, 257, 40),         # 513 blocks, two query tiles per slot
