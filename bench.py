@@ -4,7 +4,7 @@
     python bench.py [--gpus 1] [--steps K] [--warmup W] [--workload stack32k]
 
 A "step" is one non-block-entry denoising step (Alg. 1) over the 32-layer, 32K-context workload: query selection
-once, sink identification once at the probe layer (16), then for each of the 15 sparse layers (17..31) one
+and sink identification once at the probe layer (16; one focus_select_and_find_sinks call), then for each of the 15 sparse layers (17..31) one
 focus_sparse_layer call (block relevance from the block means cached at the block entry, Top-C, sparse attention).
 Before the clock starts the block entry is played once: focus_cache_refresh writes every layer's K/V cache and emits
 the block means K_bar, which stay frozen until the next block entry (Eq. 3: prompt keys are not refreshed in between).
@@ -35,6 +35,19 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0
 PMC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic_{}.json")
 
 
+def kernel_sources_sha16() -> str:
+    """Hash of the kernel sources without comments and white space: whether a stored profile belongs to the present kernels."""
+    import glob
+    import hashlib
+    import re
+    h = hashlib.sha256()
+    for path in sorted(glob.glob(os.path.join(ROOT, "paper_2602_02159_amd", "csrc", "*.h*"))):
+        if path.endswith((".h", ".hip")):
+            with open(path) as fh:
+                h.update(re.sub(r"\s+", "", re.sub(r"//[^\n]*", "", fh.read())).encode())
+    return h.hexdigest()[:16]
+
+
 def parse_pmc(fetch_db: str, write_db: str, workload: str) -> int:
     """Per-kernel HBM traffic from two `rocprofv3 --pmc` runs of `bench.py --mode pmc` (FETCH_SIZE, then WRITE_SIZE;
     both in KiB per dispatch), each scaled by what the same counter reads for the 1 GiB calibration copy."""
@@ -61,7 +74,7 @@ def parse_pmc(fetch_db: str, write_db: str, workload: str) -> int:
     kf, kw = copy_kernel(fetch), copy_kernel(write)
     f_scale = copy_bytes / (max(fetch[kf]) * 1024.0) if kf else 1.0   # true bytes per counted byte
     w_scale = copy_bytes / (max(write[kw]) * 1024.0) if kw else 1.0
-    res = {"workload": workload, "unit": "bytes per dispatch", "calibration": {
+    res = {"workload": workload, "unit": "bytes per dispatch", "kernel_sources_sha16": kernel_sources_sha16(), "calibration": {
         "copy_bytes": copy_bytes, "copy_kernel_fetch": kf, "copy_kernel_write": kw,
         "FETCH_SIZE_KiB_for_copy": max(fetch[kf]) if kf else None, "WRITE_SIZE_KiB_for_copy": max(write[kw]) if kw else None,
         "fetch_scale": f_scale, "write_scale": w_scale}, "kernels": {}}
@@ -347,8 +360,8 @@ def main() -> int:
                       "find_sinks", "probe_layer", "select"):
             st.issue(stage)
             sync()
-        # block entry: the cache rewrite, and the dense attention of every position at an eighth of the query rows
-        # (the counters are ratios; a launch over all rows would run twenty times longer under the profiler)
+        # block entry: the cache rewrite, the dense attention of every position at an eighth of the query rows (the counters are
+        # ratios; a launch over all rows would run twenty times longer under the profiler), and both in one call
         q0, k0, v0 = st.layers[0]
         kc, vc = torch.empty_like(k0), torch.empty_like(v0)
         kb = torch.empty(w.n_heads, w.n_blocks, w.head_dim, dtype=torch.float32, device=dev)
@@ -357,6 +370,8 @@ def main() -> int:
         q_part = torch.randn(w.n_heads, w.n_kv // 8, w.head_dim, device=dev).to(torch.bfloat16)
         o_part = torch.empty_like(q_part)
         fb.refresh_attn(q_part, k0, v0, fb.make_shape(q_part, k0, v0, w.n_ctx, w.block, o_part), o_part, None)
+        sync()
+        fb.block_entry(kc, vc, fb.make_shape(q_part, kc, vc, w.n_ctx, w.block, o_part), q_part, k0, v0, kb, o_part, None)
         sync()
         print(json.dumps({"mode": "pmc", "copy_bytes": int(src.numel() * 4), "workload": w.name}))
         return 0
@@ -399,6 +414,7 @@ def main() -> int:
     alg["block_scores"] = {"bytes": alg["block_partials"]["bytes"] + n_b * H * 4 + n_b * 4, "flops": alg["block_partials"]["flops"]}
     alg["sparse_layer_cached"] = {"bytes": alg["block_scores_cached"]["bytes"] + alg["sparse_attn"]["bytes"],
                                   "flops": alg["block_scores_cached"]["flops"] + alg["sparse_attn"]["flops"]}
+    alg["select_and_sinks"] = {key: alg["select"][key] + alg["find_sinks"][key] for key in ("bytes", "flops")}
     alg["sparse_layer"] = {"bytes": alg["block_scores"]["bytes"] + alg["sparse_attn"]["bytes"],
                            "flops": alg["block_scores"]["flops"] + alg["sparse_attn"]["flops"]}
 
@@ -496,10 +512,10 @@ def main() -> int:
         return e0.elapsed_time(e1) * 1e3 / n_launch  # microseconds per launch
 
     stages = {}
-    per_step_count = {"select": 1, "find_sinks": 1, "block_means": 0, "block_partials": 0, "block_scores_cached": n_sparse,
+    per_step_count = {"select": 0, "find_sinks": 0, "select_and_sinks": 1, "block_means": 0, "block_partials": 0, "block_scores_cached": n_sparse,
                       "block_scores": 0, "sparse_attn": n_sparse, "dense_attn": 0, "sparse_layer": 0,
                       "sparse_layer_cached": n_sparse, "probe_layer": 0}
-    for stage in ("select", "find_sinks", "block_means", "block_partials", "block_scores_cached", "block_scores", "sparse_attn", "dense_attn",
+    for stage in ("select", "find_sinks", "select_and_sinks", "block_means", "block_partials", "block_scores_cached", "block_scores", "sparse_attn", "dense_attn",
                   "sparse_layer_cached", "sparse_layer", "probe_layer"):
         us = time_stage(steps_obj, stage, args.kernel_reps)
         a = alg[stage]
@@ -508,6 +524,7 @@ def main() -> int:
                          "GBps": round(a["bytes"] / us * 1e-3, 1), "TFLOPps": round(a["flops"] / us * 1e-6, 3),
                          "hbm_frac": round(a["bytes"] / us * 1e-3 / HBM_PEAK_GBS, 4)}
     stages["sparse_layer_cached"]["note"] = "the step's per-layer call: relevance from cached means, attention with Top-C inside, combine"
+    stages["select_and_sinks"]["note"] = "the step's first call: query selection and sink identification; the two alone stand beside it"
     stages["sparse_attn"]["note"] = "focus_sparse_attn alone (attention kernel + split combine), kept blocks given"
     stages["block_means"]["note"] = stages["block_partials"]["note"] = "K scan: once per block entry (Eq. 3), not part of the step"
 
@@ -605,44 +622,76 @@ def main() -> int:
                                         "alg_flops": int(fl), "GBps": round(2 * 2 * L * H * d * 2 / us * 1e-3, 1),
                                         "TFLOPps": round(fl / us * 1e-6, 1), "mfma_frac": round(fl / us * 1e-6 / MFMA_BF16_PEAK_TFLOPS, 4),
                                         "bound": "mfma"}
-        del q_all, out_all
+        # what a block entry calls per layer: the same attention over new states, with the caches and K_bar written beside it
+        kc, vc = torch.empty_like(k0), torch.empty_like(v0)
+        kb = torch.empty(H, n_b, d, dtype=torch.float32, device=dev)
+        s_entry = fb.make_shape(q_all, kc, vc, M, w.block, out_all)
+        call = lambda: fb.block_entry(kc, vc, s_entry, q_all, k0, v0, kb, out_all, None)
+        call()
+        sync()
+        e0.record()
+        for _ in range(3):
+            call()
+        e1.record()
+        sync()
+        us = e0.elapsed_time(e1) * 1e3 / 3
+        eb = 6 * L * H * d * 2 + H * n_b * d * 4
+        stages["block_entry_layer"] = {"us_per_launch": round(us, 1), "launches_per_step": 0, "alg_bytes": int(eb), "alg_flops": int(fl),
+                                       "GBps": round(eb / us * 1e-3, 1), "TFLOPps": round(fl / us * 1e-6, 1),
+                                       "mfma_frac": round(fl / us * 1e-6 / MFMA_BF16_PEAK_TFLOPS, 4), "bound": "mfma",
+                                       "note": "focus_block_entry: full_refresh_layer and cache_refresh in one call"}
+        del q_all, out_all, kc, vc, kb
 
     # ---- roofline of the step's dominant stage.  The step calls focus_sparse_layer; its attention part is timed through
     # focus_sparse_attn, which runs the same attention kernel (without the Top-C prologue) and the same combine kernel.
-    in_step = ("select", "find_sinks", "block_scores_cached", "sparse_attn")
+    in_step = ("select_and_sinks", "block_scores_cached", "sparse_attn")
     share = {s: stages[s]["us_per_launch"] * per_step_count[s] for s in in_step}
     dom = max(share, key=share.get)
     ds = stages[dom]
-    cap_q = st0.max_active                              # the launchers plan for the capacity of the active list
-    qtw = 1 if cap_q <= 16 else (2 if cap_q <= 32 else 4)   # query tiles per workgroup they pick
 
-    def attn_traffic(workload_name, qt):
+    def attn_kernel(cap, wl, h):
+        """Name of the attention kernel that focus_sparse_attn launches for `cap` query slots (the launchers plan for the capacity of
+        the active list), as the profiler prints it: up to 16 queries, up to 32, up to 64, groups of 32."""
+        n_sub = wl.n_keep * -(-wl.block // 32) + -(-wl.n_resp // 32) + -(-wl.n_sink // 32)
+        groups = -(-cap // 32) if cap > 64 else 1
+        loop = max(1, 512 // (h * groups)) * 4 < n_sub   # a slot walks several sub-tiles
+        if cap <= 16:
+            return f"sparse_attn_kernel<{wl.head_dim}, {2 if loop else 0}>"
+        tiles, bits = (1, 8) if cap > 64 else (2 if cap > 32 else 1, 0)
+        return f"wide_attn_kernel<{wl.head_dim}, {tiles}, {bits + ((2 if cap > 64 else 6) if loop else 0)}>"
+
+    def attn_traffic(wl, kernel):
         """HBM bytes of one focus_sparse_attn call (attention kernel: rows fetched + split partials written; combine: partials
-        re-read + output written) from the stored rocprofv3 --pmc run of this script (--mode pmc, --parse-pmc)."""
+        re-read + output written) from the stored rocprofv3 --pmc run of this script (--mode pmc, --parse-pmc), and where they come
+        from.  None, with the reason, when that run was of other kernels."""
+        path = PMC_FILE.format(wl.name)
+        name = os.path.relpath(path, ROOT)
         try:
-            with open(PMC_FILE.format(workload_name)) as fh:
+            with open(path) as fh:
                 pmc = json.load(fh)
-            total = 0
-            hit = False
-            for name, v in pmc["kernels"].items():
-                if f"sparse_attn_kernel<{d}, {qt}, 0>" in name:   # a name the dense comparison shares: the smallest dispatch is the sparse one
-                    total += int(v["fetch_bytes_min"] + v["write_bytes_min"])
-                    hit = True
-                elif "attn_combine_kernel" in name:
-                    total += int(v["fetch_bytes_min"] + v["write_bytes_min"])
-            return total if hit else None
-        except (OSError, KeyError, ValueError):
-            return None
+        except (OSError, ValueError) as e:
+            return None, f"{name}: {e}"
+        if pmc.get("kernel_sources_sha16") != kernel_sources_sha16():
+            return None, f"{name} was recorded with other kernel sources"
+        found = {}
+        for want in (kernel, f"attn_combine_kernel<{wl.head_dim}>"):
+            # the dense comparison may share a name: the smallest dispatch is the sparse one
+            found[want] = [v["fetch_bytes_min"] + v["write_bytes_min"] for key, v in pmc["kernels"].items() if want + "(" in key]
+        missing = [want for want, v in found.items() if len(v) != 1]
+        if missing:
+            return None, f"{name} has no entry for {', '.join(missing)}"
+        return int(sum(v[0] for v in found.values())), (f"{name}: a separate rocprofv3 --pmc run of `bench.py --mode pmc` (FETCH_SIZE, "
+                                                        "WRITE_SIZE) with the same kernel sources, not measured in this run")
 
-    kernel_names = {"sparse_attn": f"sparse_attn_kernel<{d}, {qtw}, 0> + attn_combine_kernel<{d}> (one focus_sparse_attn call; in the step the "
-                                   f"attention kernel is the <{d}, {qtw}, 1> variant with the Top-C prologue)",
-                    "find_sinks": f"qk_logits_kernel<{d}, {qtw}, {0 if qtw == 1 else 1}> and the rest of the sink chain",
-                    "block_scores_cached": f"relevance_partial_kernel<{d}> + reduce_topk_kernel", "select": "select_queries_kernel"}
-    traffic = attn_traffic(w.name, qtw) if dom == "sparse_attn" else None
+    attn_name = attn_kernel(st0.max_active, w, H)
+    kernel_names = {"sparse_attn": f"{attn_name} + attn_combine_kernel<{d}> (one focus_sparse_attn call; in the step the attention kernel is "
+                                   "its variant with the Top-C prologue)",
+                    "select_and_sinks": "qk_logits_kernel / wide_logits_kernel and the rest of the sink chain",
+                    "block_scores_cached": f"relevance_partial_kernel<{d}, false> + reduce_topk_kernel"}
+    traffic, traffic_source = attn_traffic(w, attn_name) if dom == "sparse_attn" else (None, None)
     roofline = {"bound": "hbm", "kernel": kernel_names[dom], "stage": dom, "achieved": ds["GBps"], "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": ds["hbm_frac"], "traffic": traffic,
-                "traffic_source": None if traffic is None else f"profiles/hbm_traffic_{w.name}.json: a separate rocprofv3 --pmc run of "
-                                  "`bench.py --mode pmc` (FETCH_SIZE, WRITE_SIZE), not measured in this run",
+                "traffic_source": traffic_source,
                 "us_per_launch": ds["us_per_launch"], "alg_bytes_per_launch": ds["alg_bytes"],
                 "launches_per_step": per_step_count[dom], "launch_floor_us": round(launch_floor_us, 3)}
 
@@ -667,14 +716,13 @@ def main() -> int:
         us_pl = time_stage(p_objs, "sparse_layer_cached", 8)
         us_pd = time_stage(p_objs, "dense_attn", 4)
         us_ps = time_stage(p_objs, "find_sinks", 4)
-        cap_p = p_objs[0].max_active
-        qt_p = 1 if cap_p <= 16 else (2 if cap_p <= 32 else 4)
-        tr_p = attn_traffic(wp.name, qt_p)
+        attn_p = attn_kernel(p_objs[0].max_active, wp, wp.n_heads)
+        tr_p, tr_p_source = attn_traffic(wp, attn_p)
         roofline_paper = {"bound": "hbm", "workload": "paper32k", "stage": "sparse_attn",
-                          "kernel": f"sparse_attn_kernel<{wp.head_dim}, {qt_p}, 0> + attn_combine_kernel<{wp.head_dim}> (one focus_sparse_attn call)",
+                          "kernel": f"{attn_p} + attn_combine_kernel<{wp.head_dim}> (one focus_sparse_attn call)",
                           "achieved": round(bytes_p / us_p * 1e-3, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                           "frac": round(bytes_p / us_p * 1e-3 / HBM_PEAK_GBS, 4), "traffic": tr_p,
-                          "traffic_source": None if tr_p is None else "profiles/hbm_traffic_paper32k.json (separate rocprofv3 --pmc run)",
+                          "traffic_source": tr_p_source,
                           "us_per_launch": round(us_p, 3), "alg_bytes_per_launch": int(bytes_p), "TFLOPps": round(flops_p / us_p * 1e-6, 1),
                           "n_queries": nq_p, "mean_keys_attended": keys_p, "n_keep": wp.n_keep, "n_sink": wp.n_sink, "block": wp.block,
                           "us_sparse_layer_cached": round(us_pl, 3), "us_dense_attn_same_queries": round(us_pd, 3),
@@ -771,9 +819,10 @@ def main() -> int:
         "roofline_paper32k": roofline_paper,
         # not part of the step: the one MFMA-bound launch of the method (block entry, every position attends to every key)
         "roofline_block_entry": None if "full_refresh_layer" not in stages else {
-            "bound": "mfma", "kernel": f"refresh_attn_kernel<{d}, 1, 8>", "achieved": stages["full_refresh_layer"]["TFLOPps"],
+            "bound": "mfma", "kernel": f"refresh_attn_kernel<{d}> + refresh_tail_kernel<{d}, false> (one focus_refresh_attn call)", "achieved": stages["full_refresh_layer"]["TFLOPps"],
             "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": stages["full_refresh_layer"]["mfma_frac"],
-            "us_per_launch": stages["full_refresh_layer"]["us_per_launch"], "flops_per_launch": stages["full_refresh_layer"]["alg_flops"]},
+            "us_per_launch": stages["full_refresh_layer"]["us_per_launch"],
+            "us_per_focus_block_entry": stages["block_entry_layer"]["us_per_launch"], "flops_per_launch": stages["full_refresh_layer"]["alg_flops"]},
         "stages": stages, "cpu_baseline": cpu, "parity_vs_oracle": parity, "input_gen_s": round(gen_s, 1),
     }
     print(json.dumps(out))

@@ -77,7 +77,10 @@ hipError_t launch_lse_combine(const float* part_ml, int H, int q_pad, int n_spli
 // Top-N_sink, one more workgroup ranks the nominees.  Limits of that path:
 constexpr int kTournamentMaxSinks = 16;
 constexpr int kTournamentMaxCand = 4096;  // ceil(M / 128) * n_sink
-constexpr int kMaxNominees = 16384;       // of any path: what the workspaces hold
+// Of any path: what the workspaces hold, and the sixteen nominees a thread of sink_rank_kernel keeps in registers.  Prompts past 131072
+// rows, whose groups nominate more, are left to the radix select over all masses (16 queries, 32 heads: sink chain 292 us at 131072
+// rows, 669 at 131200); longer runs per thread have not been tried.
+constexpr int kMaxNominees = 16384;
 bool sink_tournament_fits(int M, int n_sink);
 // cand: nullptr, or int32[ceil(M / 128) * n_sink] that receives the nominees (n_sink: nominees per group);
 // cand_keys: uint32 of the same size that receives their order keys + 1 (0 where cand holds -1); required with cand.
@@ -137,7 +140,10 @@ hipError_t launch_qk_logits(const void* Q, const int32_t* active_idx, const int3
                             const void* K, const focus_shape& s, const SplitPlan& p, int mode, float* logits,
                             float* part_ml, const float* lse2, float* colpart, hipStream_t st, const SelectArgs* select = nullptr);
 // Extra arguments of the fused layer path: the attention kernel ranks the blocks itself from the partial relevances
-// (n_b <= kFusedMaxBlocks; kFusedMaxBlocksPerHead if they come per head from a K scan).
+// (n_b <= kFusedMaxBlocks; kFusedMaxBlocksPerHead if they come per head from a K scan).  The limits are what the prologues are built
+// for: four keys a thread of four wavefronts, and from a K scan, whose 32 parts per key would be read by every workgroup, one.  Past them
+// a launch of one workgroup ranks the blocks and costs more than the blocks themselves (32 heads, 16 queries, 30 blocks of 64 kept:
+// 1024 blocks 19.3 us, 1025 blocks 35.4, 2048 blocks 39.5); a prologue of eight keys a thread has not been tried.
 constexpr int kFusedMaxBlocks = 1024, kFusedMaxBlocksPerHead = 256;
 struct FusedTopC {
   const float* rel_part;  // [ceil(H / 4), n_b] from launch_block_relevance, or with per_head [H, n_b]
