@@ -450,6 +450,8 @@ struct AttnArgs {
   int H, M, N, B, n_b, n_gen, n_keep, n_sink, max_active;
   int sub_per_block, n_sub, n_split, q_pad, q_groups;
   float scale_log2;
+  uint32_t head_turn;                // (2^32 - 1) / H      see SplitRounds
+  int split_rounds, split_rounds_more;  // every split has so many rounds, the first so many splits one more
   // fused layer path only: partial relevances in, scores / kept blocks out
   const float* rel_part;  // [ceil(H / 4), n_b], or with rel_per_head [H, n_b]
   bool rel_per_head;
@@ -601,6 +603,28 @@ __device__ __forceinline__ SinkUnion prepare_union(const AttnArgs& p, int split,
   return u;
 }
 
+// The rounds of four sub-tiles of one key split (see SplitPlan) in the order in which a key loop takes them: head h begins h / H of the
+// way down the list and wraps around.  All heads sweep their keys at the same time, and with the same place in the sweep the rows
+// being fetched are the head stride apart, which for some lengths keeps meeting the same memory channels (32 heads, 16 queries:
+// 33 024 rows 92 us from the top for every head, 87.5 this way; 32 832 rows 86.5 either way; 256 of 512 blocks, 256 response
+// rows, 25 queries, whole layer 66 and 60).
+struct SplitRounds {
+  int first, step, n_rounds, turn, n_sub;
+  __device__ __forceinline__ SplitRounds(const AttnArgs& p, int split, int h) {
+    first = split * kWavesPerGroup;
+    step = p.n_split * kWavesPerGroup;
+    n_sub = p.n_sub;
+    n_rounds = p.split_rounds + (split < p.split_rounds_more);
+    turn = (int)__umulhi((uint32_t)h * p.head_turn, (uint32_t)n_rounds);  // < n_rounds
+  }
+  // sub-tile of slot `slot` in the i-th round; n_sub or more: none
+  __device__ __forceinline__ int sub(int i, int slot) const {
+    if (i >= n_rounds) return n_sub;
+    const int r = i + turn;
+    return first + slot + (r >= n_rounds ? r - n_rounds : r) * step;
+  }
+};
+
 // Up to 16 active queries.  One workgroup works on one (head, key split); the key axis is walked in rounds of four 32-row
 // sub-tiles ("slots"), and every one of its four wavefronts owns its slot end to end — it stages the sub-tile, multiplies it
 // against the one query tile and keeps its own running softmax; the four states are merged at the end.
@@ -671,8 +695,9 @@ __global__ __launch_bounds__(256, (FUSE & 2) == 0 ? 2 : 1) void sparse_attn_kern
 
   // Order of the memory requests: the query row ids first (tiny, they return first), then the first
   // sub-tile's K and V rows as soon as its block id is known, then the query rows and the device-side count.
-  int st = split * kWavesPerGroup + wave;
-  const int st_end = p.n_sub, st_step = p.n_split * kWavesPerGroup;
+  const int st_end = p.n_sub;
+  const SplitRounds rounds(p, split, h);
+  const int st = PIPE ? rounds.sub(0, wave) : split * kWavesPerGroup + wave;
   const int qrow = FUSED ? qrow_early : fetch_q_row(p.active_idx, 0, p.max_active, p.n_gen, lane);
   SubTile t;
   t.kind = 0;
@@ -748,8 +773,9 @@ __global__ __launch_bounds__(256, (FUSE & 2) == 0 ? 2 : 1) void sparse_attn_kern
     // for afterwards, so they travel for the whole multiplication.  `cur` and `nxt` are slots of two separate arrays:
     // the compiler can tell that the loads into one do not touch the operand reads of the other.  No barrier: the slots
     // are private to the wavefront (which has finished reading `nxt` one step ago; wait_lds_reads makes that explicit).
+    int round = 0;
     auto step = [&](const char* cur, char* nxt) __attribute__((always_inline)) {
-      const int st_next = st + st_step;
+      const int st_next = rounds.sub(++round, wave);
       SubTile tn = no_tile();
       if (st_next < st_end) tn = locate(st_next);
       if (tn.vmask != 0u) {
@@ -763,14 +789,13 @@ __global__ __launch_bounds__(256, (FUSE & 2) == 0 ? 2 : 1) void sparse_attn_kern
       // instead of being waited for together with the loads
       if (SPILL && t.vmask != 0u) spill_logits(p.logits_out, h, p.dense_rows, t.row0, kept_logits, p.scale_log2, lane);
       t = tn;
-      st = st_next;
     };
     char* mineA = ldsA + wave * kBufBytes;
     char* mineB = ldsB + wave * kBufBytes;
     wait_loads();  // the first sub-tile
-    while (st < st_end) {
+    while (round < rounds.n_rounds) {
       step(mineA, mineB);
-      if (st < st_end) step(mineB, mineA);
+      if (round < rounds.n_rounds) step(mineB, mineA);
     }
   }
 
@@ -985,7 +1010,7 @@ __global__ __launch_bounds__(256 * NT, NT == 2 || (MODE & 4) == 0 ? 2 : 1) void 
   }
   const SinkUnion uni = prepare_union(p, split, kept_blocks, kept_bits_sh, &sinks_unsorted_sh);
 
-  const int st_step = p.n_split * kWavesPerGroup;
+  const SplitRounds rounds(p, split, h);
   auto locate = [&](int sub) __attribute__((always_inline)) {
     SubTile t;
     t.kind = 0;
@@ -1007,8 +1032,7 @@ __global__ __launch_bounds__(256 * NT, NT == 2 || (MODE & 4) == 0 ? 2 : 1) void 
     if (NT > 1) __syncthreads();
   };
   char* slotA = ldsA + slot * kBufBytes;
-  int st = split * kWavesPerGroup + slot;
-  SubTile t = locate(st);
+  SubTile t = locate(PIPE ? rounds.sub(0, slot) : split * kWavesPerGroup + slot);
   request(t, slotA);
   if (!FUSED) load_q();
   const int n_act = p.counts ? min(max(p.counts[1], 0), p.max_active) : p.max_active;
@@ -1041,7 +1065,8 @@ __global__ __launch_bounds__(256 * NT, NT == 2 || (MODE & 4) == 0 ? 2 : 1) void 
     if (t.vmask != 0u && tile_live)
       consume([&](int ks) { return k_at(slotA, ks); }, [&](int dt, int ks) { return v_at(slotA, dt, ks); }, t.vmask);
   } else {
-    SubTile tn = locate(st + st_step);
+    SubTile tn = locate(rounds.sub(1, slot));
+    int i = 0;
     // One round: `t` sits in `cur`.  Between the arrival of its rows and the request of the next ones lies only what has to:
     // the operand reads the compiler would otherwise put behind the arrival of the next rows (the transposed V reads, which
     // it cannot tell from the stage being filled), or that the request overwrites.  The sub-tile after the next is located —
@@ -1059,21 +1084,21 @@ __global__ __launch_bounds__(256 * NT, NT == 2 || (MODE & 4) == 0 ? 2 : 1) void 
       }
       wait_lds_reads();
       request(tn, nxt);
-      const SubTile t2 = locate(st + 2 * st_step);
+      const SubTile t2 = locate(rounds.sub(i + 2, slot));
       if (t.vmask != 0u && tile_live)
         consume([&](int ks) { return DOUBLE ? k_at(cur, ks) : kop[ks]; }, [&](int dt, int ks) { return vop[ks][dt]; }, t.vmask);
       t = tn;
       tn = t2;
-      st += st_step;
+      ++i;
     };
     if (DOUBLE) {
       char* slotB = ldsB + slot * kBufBytes;
-      for (int first = split * kWavesPerGroup; first < p.n_sub; first += 2 * st_step) {  // uniform over the workgroup
+      while (i < rounds.n_rounds) {  // uniform over the workgroup
         round(slotA, slotB);
-        if (first + st_step < p.n_sub) round(slotB, slotA);
+        if (i < rounds.n_rounds) round(slotB, slotA);
       }
     } else {
-      for (int first = split * kWavesPerGroup; first < p.n_sub; first += st_step) round(slotA, slotA);
+      while (i < rounds.n_rounds) round(slotA, slotA);
     }
   }
 
@@ -1303,6 +1328,9 @@ hipError_t launch_sparse_attn(const void* Q, const int32_t* active_idx, const in
   a.n_sub = p.n_sub; a.n_split = p.n_split; a.q_pad = p.q_pad;
   a.q_groups = p.q_groups;
   a.scale_log2 = kLog2e / sqrtf((float)s.head_dim);
+  a.head_turn = 0xffffffffu / (uint32_t)s.n_heads;
+  a.split_rounds = ceil_div(p.n_sub, kWavesPerGroup) / p.n_split;
+  a.split_rounds_more = ceil_div(p.n_sub, kWavesPerGroup) % p.n_split;
   a.rel_part = fused ? fused->rel_part : nullptr;
   a.rel_per_head = fused && fused->per_head;
   a.scores_out = fused ? fused->scores_out : nullptr;

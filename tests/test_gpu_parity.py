@@ -373,6 +373,22 @@ def test_sparse_attn_query_tiles_and_key_splits(G, H, M, N, d, cap, live):
     assert torch.isnan(out[:, live:]).all()  # rows past the count are not written
 
 
+@pytest.mark.parametrize("n_act", [16, 30, 50])
+@pytest.mark.parametrize("H,M,N,d", [
+    (5, 20001, 30, 64),                        # 51 splits of two or three rounds, the last one ragged
+    (64, 1300, 5, 128),                        # four splits of 64 heads: every starting place several times
+    (300, 700, 9, 64),                         # more heads than rounds, one split
+    (1, 40000, 64, 128),
+])
+def test_sparse_attn_heads_begin_at_different_places(G, H, M, N, d, n_act):
+    q, k, v = (_rand_bf16(65 + i, H, r, d).to(G.DEV) for i, r in enumerate((n_act, M + N, M + N)))
+    act = np.arange(n_act)
+    out, lse = G.gpu_sparse_attn(q, G.i32(act), None, k, v, M, 64, G.i32(np.arange(-(-M // 64))), None)
+    ref, ref_lse = fo.sparse_attention(G.to_np(q), act, G.to_np(k), G.to_np(v), np.arange(M), M)
+    G.assert_attention_close(out, ref)
+    assert np.allclose(lse.cpu().numpy(), ref_lse, atol=2e-3)
+
+
 def test_sparse_attn_dense_reduction(G):
     # keep every block, every row a query: plain bidirectional attention over all M+N keys
     H, M, N, d, B, n_gen = 4, 3000, 72, 128, 128, 64
