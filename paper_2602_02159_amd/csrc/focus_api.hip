@@ -33,7 +33,13 @@ static inline size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 constexpr int kAttnGroups = 512;      // one sub-tile per slot: every workgroup resident at once, two per compute unit
 constexpr int kAttnGroupsPipe = 256;  // many sub-tiles per slot, two stages per slot: one workgroup per compute unit
 constexpr int kAttnGroupsWide = 512;  // the same where query groups share the rows: one stage per slot, two workgroups per compute unit
-constexpr int kLogitGroups = 4096;    // sink scoring, one query tile: measured best of 1024 .. 8192 (short workgroups even out the tail of the scan)
+constexpr int kLogitGroups = 4096;    // sink scoring, one query tile: at most so many (short workgroups even out the tail of the scan) ...
+// ... with four rounds of sub-tiles each where they are all resident at once, else two, so that a workgroup's start passes beside the
+// others' rows and there are fewer statistics to merge; but one workgroup per compute unit as long as that leaves one round each.
+// Sink chain in us with one, two and four rounds: 16 heads, 32 832 keys 47.1, 42.5, 42.7; 8 heads 34.5, 26.9, 27.2; 32 heads, 8256
+// keys 32.5, 29.2, 28.9, 16 448 keys -, 46.2, 46.4, 32 832 keys -, 74.6, 76.6; 1056 keys in 9 and 8 splits 16.0, 14.9; 2112 keys in
+// 17 and 8 splits 19.3, 16.6.
+constexpr int kLogitGroupsMin = 256, kLogitGroupsResident = 1024;
 // Two passes over K (more than 16 queries): every workgroup first fetches its query rows.  33 to 64 queries per group: as many
 // workgroups as are resident at once, three per compute unit.  Up to 32: four are; more of them even out the tail of a long scan,
 // as long as each has four rounds of sub-tiles.
@@ -86,6 +92,10 @@ SplitPlan plan_logits(const focus_shape& s, int max_active) {
   p.n_sub = ceil_div(s.n_ctx + s.n_resp, kSubTile);
   plan_splits(p, s.n_heads, p.q_groups,
               p.q_tiles_per_group == 1 ? kLogitGroups : (p.q_tiles_per_group == 2 ? kLogitGroupsTwo : kLogitGroupsMany));
+  if (p.q_tiles_per_group == 1) {
+    const int rounds = p.n_sub / kWavesPerGroup, few = std::max(std::max(1, kLogitGroupsMin / s.n_heads), rounds / 4);
+    p.n_split = std::min(p.n_split, (int64_t)few * s.n_heads <= kLogitGroupsResident ? few : std::max(1, rounds / 2));
+  }
   if (p.q_tiles_per_group == 2) {
     const int rounds = p.n_sub / kWavesPerGroup;
     p.n_split = std::min(p.n_split, std::max(std::max(1, kLogitGroupsTwoMin / s.n_heads), rounds / kLogitRoundsTwo));
@@ -264,9 +274,12 @@ static int find_sinks_impl(const char* who, const SelectArgs* select, const void
   e = launch_qk_logits(Q, active_idx, counts, max_active, K, *shape, p, two_pass ? 1 : 0, logits, part_ml, nullptr, nullptr, st, select);
   if (e != hipSuccess) return fail(FOCUS_ELAUNCH, "%s(logits): %s", who, hipGetErrorString(e));
   if (two_pass) {
-    e = launch_lse_combine(part_ml, shape->n_heads, p.q_pad, p.n_split, lse2, st);
-    if (e != hipSuccess) return fail(FOCUS_ELAUNCH, "%s(lse): %s", who, hipGetErrorString(e));
-    e = launch_qk_logits(Q, active_idx, counts, max_active, K, *shape, p, 2, nullptr, nullptr, lse2, logits, st);
+    const bool in_logits = lse_in_logits(p);
+    if (!in_logits) {
+      e = launch_lse_combine(part_ml, shape->n_heads, p.q_pad, p.n_split, lse2, st);
+      if (e != hipSuccess) return fail(FOCUS_ELAUNCH, "%s(lse): %s", who, hipGetErrorString(e));
+    }
+    e = launch_qk_logits(Q, active_idx, counts, max_active, K, *shape, p, 2, nullptr, in_logits ? part_ml : nullptr, lse2, logits, st);
     if (e != hipSuccess) return fail(FOCUS_ELAUNCH, "%s(column sums): %s", who, hipGetErrorString(e));
   }
   return column_mass_and_sinks(who, logits, two_pass, two_pass ? lse2 : part_ml, two_pass ? 0 : p.n_split, lse2, counts, max_active,

@@ -57,13 +57,18 @@ __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v) {
   return v;
 }
 
+template <int CTRL>
+__device__ __forceinline__ float lane_dpp(float x) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xF, 0xF, false));
+}
+
 // sum of x over the 16 lanes of a DPP row (the lanes that hold the 16 queries of a tile for the same keys); every
 // lane of the row receives the total
 __device__ __forceinline__ float row_sum16(float x) {
-  x += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0xB1, 0xF, 0xF, false));   // quad_perm [1,0,3,2]
-  x += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x4E, 0xF, 0xF, false));   // quad_perm [2,3,0,1]
-  x += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x141, 0xF, 0xF, false));  // row_half_mirror
-  x += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x140, 0xF, 0xF, false));  // row_mirror
+  x += lane_dpp<0xB1>(x);   // quad_perm [1,0,3,2]
+  x += lane_dpp<0x4E>(x);   // quad_perm [2,3,0,1]
+  x += lane_dpp<0x141>(x);  // row_half_mirror
+  x += lane_dpp<0x140>(x);  // row_mirror
   return x;
 }
 
@@ -142,6 +147,43 @@ __device__ __forceinline__ uint32_t block_flag_scan(bool flag, uint32_t* wsum, u
   }
   *total = tot;
   return base + (uint32_t)__popcll(b & ((1ull << lane) - 1ull));
+}
+
+// Softmax statistics of the key splits: float2 (maximum, sum) [H, n_split, q_pad], so that neighbouring threads read neighbouring
+// queries.  An empty split holds (-inf, 0).
+struct RowState {
+  float m, l;
+};
+// adds N of them without a branch; those without a positive sum (empty, NaN) count for nothing
+template <int N>
+__device__ __forceinline__ void add_splits(RowState& r, const float2 (&v)[N]) {
+  float m = r.m;
+#pragma unroll
+  for (int u = 0; u < N; ++u) m = fmaxf(m, v[u].y > 0.f ? v[u].x : -INFINITY);
+  const float z = m == -INFINITY ? 0.f : m;
+  float l = r.l * __builtin_amdgcn_exp2f(r.m - z);
+#pragma unroll
+  for (int u = 0; u < N; ++u) l += v[u].y > 0.f ? v[u].y * __builtin_amdgcn_exp2f(v[u].x - z) : 0.f;
+  r.m = m;
+  r.l = l;
+}
+__device__ __forceinline__ float lse_of(const RowState& r) { return r.l > 0.f ? r.m + __builtin_amdgcn_logf(r.l) : INFINITY; }  // v_log_f32 is log2
+// splits first, first + step, ... of one row, N loads at a time; `row` = its place in the first split, `stride` = rows per split
+constexpr int kSplitsInFlight = 8;
+template <int N = kSplitsInFlight>
+__device__ __forceinline__ RowState add_row_splits(const float2* row, int64_t stride, int first, int step, int n_split) {
+  RowState r{-INFINITY, 0.f};
+  for (int s0 = first; s0 < n_split; s0 += N * step) {
+    float2 v[N];
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+      const int s = s0 + u * step;
+      v[u] = row[(int64_t)min(s, n_split - 1) * stride];
+      if (s >= n_split) v[u] = make_float2(-INFINITY, 0.f);
+    }
+    add_splits(r, v);
+  }
+  return r;
 }
 
 }  // namespace focus

@@ -72,6 +72,7 @@ hipError_t launch_block_relevance(const void* Q, const int32_t* focus_idx, const
 // out[k] ascending indices.  n_parts = n_heads, or ceil(n_heads / 4) groups
 hipError_t launch_reduce_topk(const float* part, int n_parts, int n_heads, const int32_t* counts, int n_focus_max, float* values, int n,
                               int k, int32_t* out, hipStream_t st);
+// part_ml [H, n_split, q_pad, 2] -> lse2 [H, q_pad]
 hipError_t launch_lse_combine(const float* part_ml, int H, int q_pad, int n_split, float* lse2, hipStream_t st);
 // Sink selection as a tournament (small N_sink): every 128-key group of the column-mass kernel nominates its own
 // Top-N_sink, one more workgroup ranks the nominees.  Limits of that path:
@@ -86,7 +87,7 @@ bool sink_tournament_fits(int M, int n_sink);
 // cand_keys: uint32 of the same size that receives their order keys + 1 (0 where cand holds -1); required with cand.
 // pre_reduced = false: src = scaled logits [H, ceil(L / 4), 16, 4] of at most 16 queries (written by the MFMA kernels), n_parts = H;
 // pre_reduced = true:  src = column sums [n_parts, L] from the second pass over K.
-// n_split > 0 (pre_reduced = false): lse2 = the statistics [H, 16, n_split, 2] of the key splits instead of the log-sum-exps
+// n_split > 0 (pre_reduced = false): lse2 = the statistics [H, n_split, 16, 2] of the key splits instead of the log-sum-exps
 // [H, 16], which are then formed by the same launch or by one more, into lse_scratch.
 hipError_t launch_column_mass(const float* src, bool pre_reduced, const float* lse2, const int32_t* counts, int max_active,
                               int n_parts, int H, int L, float* col_mass, int M, int n_sink, int32_t* cand, uint32_t* cand_keys,
@@ -125,8 +126,10 @@ CacheRefresh cache_refresh_args(void* K_cache, void* V_cache, const focus_shape&
 hipError_t launch_cache_refresh(const CacheRefresh& p, int head_dim, hipStream_t st);
 
 // ---- MFMA kernels (focus_mfma.hip)
-// mode 0: logits [H, ceil(L / 4), 16, 4] + part_ml out (at most 16 queries); mode 1: part_ml out only; mode 2: lse2 in, colpart [q_groups * H, L] out
+// mode 0: logits [H, ceil(L / 4), 16, 4] + part_ml out (at most 16 queries); mode 1: part_ml out only; mode 2: lse2 in, or part_ml of
+// mode 1 (not null; lse_in_logits), colpart [q_groups * H, L] out
 // select (modes 0 and 1): the query selection (Eq. 4, Eq. 5) is made by the same launch; active_idx and counts are not read
+bool lse_in_logits(const SplitPlan& p);  // mode 2 may form the log-sum-exps itself
 constexpr int kSelectInLogitsGen = 64;  // n_gen at most: a wavefront holds one position per lane
 struct SelectArgs {
   const float* conf;

@@ -1862,7 +1862,7 @@ struct LogitArgs {
   const int32_t* active_idx;
   const int32_t* counts;
   float* logits;      // [H, ceil(L / 4), 16, 4]: see spill_logits  (mode 0, at most 16 queries)
-  float* part_ml;     // [H, q_pad, n_split, 2]                (modes 0, 1)
+  float* part_ml;     // [H, n_split, q_pad, 2]                (modes 0, 1)
   const float* lse2;  // [H, q_pad] base-2 log-sum-exp per row (mode 2)
   float* colpart;     // [q_groups * H, L]                     (mode 2)
   int64_t qsh, qsn, ksh, ksn;
@@ -2002,9 +2002,8 @@ __global__ __launch_bounds__(256, 2) void qk_logits_kernel(const uint16_t* K, in
       const float l = ml_sh[w][threadIdx.x][1];
       if (l > 0.f) lsum += l * __builtin_amdgcn_exp2f(ml_sh[w][threadIdx.x][0] - mmax);
     }
-    const int64_t row = ((int64_t)h * p.q_pad + threadIdx.x) * p.n_split + split;
-    p.part_ml[2 * row] = lsum > 0.f ? mmax : -INFINITY;
-    p.part_ml[2 * row + 1] = lsum;
+    const int64_t row = ((int64_t)h * p.n_split + split) * 16 + threadIdx.x;
+    *reinterpret_cast<float2*>(p.part_ml + 2 * row) = make_float2(lsum > 0.f ? mmax : -INFINITY, lsum);
   }
 }
 
@@ -2012,6 +2011,8 @@ __global__ __launch_bounds__(256, 2) void qk_logits_kernel(const uint16_t* K, in
 // MODE 1: per-split softmax statistics.
 // MODE 2: with the row log-sum-exps known, the probabilities are formed on the fly and summed over the workgroup's queries;
 //         colpart[qg * H + h, j] = sum_i P[h, i, j].
+// MODE 3: the same from the statistics of MODE 1, of which every workgroup forms the log-sum-exps of its queries itself, beside its
+//         first K rows (lse_in_logits).
 // A workgroup has NT tiles of 32 queries (32x32x16 MFMA) and four slots, one per wavefront, which walk the key sub-tiles; the
 // operands of a sub-tile are read from its slot once, into registers, and the next one is requested before they are multiplied.
 // MODE 1 computes K Q^T (a lane holds one query's logits: the running maximum is one exchange), MODE 2 Q K^T (a lane holds one
@@ -2037,6 +2038,7 @@ __global__ __launch_bounds__(256, NT == 1 ? 4 : 2) void wide_logits_kernel(const
   p.n_gen = n_gen;
   using G = Geo<D>;
   constexpr int kKS = D / 16;
+  constexpr bool SUMS = MODE >= 2;
   __shared__ __attribute__((aligned(16))) char lds[kWavesPerGroup * G::kStageBytes];
   __shared__ __attribute__((aligned(16))) char stageQ[NT * G::kStageBytes];
   float2 (*ml_sh)[NT * 32] = reinterpret_cast<float2 (*)[NT * 32]>(stageQ);  // [4][NT * 32], once the queries are in registers
@@ -2098,18 +2100,26 @@ __global__ __launch_bounds__(256, NT == 1 ? 4 : 2) void wide_logits_kernel(const
       __builtin_amdgcn_global_load_lds((gptr_t)src, (lptr_t)(stageQ + (wave * kQLoads + i) * 1024), 16, 0, 0);
     }
   }
-  float neg_lse[MODE == 2 ? NT : 1][16];  // MODE 2: minus the log-sum-exp of query 8 (v / 4) + 4 hh + v % 4; -inf for rows that do not exist
+  float neg_lse[SUMS ? NT : 1][16];  // minus the log-sum-exp of query 8 (v / 4) + 4 hh + v % 4; -inf for rows that do not exist
+  auto set_lse = [&](int n, int v, int a, float z) __attribute__((always_inline)) {
+    neg_lse[n][v] = (a < n_act && z < INFINITY) ? -z : -INFINITY;  // exp2(x - inf) = 0: the row contributes nothing
+  };
   if (MODE == 2) {
 #pragma unroll
     for (int n = 0; n < NT; ++n) {
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         const int a = q_base + n * 32 + 8 * (v >> 2) + 4 * hh + (v & 3);
-        const float z = p.lse2[(int64_t)h * p.q_pad + min(a, p.q_pad - 1)];
-        neg_lse[n][v] = (a < n_act && z < INFINITY) ? -z : -INFINITY;  // exp2(x - inf) = 0: the row contributes nothing
+        set_lse(n, v, a, p.lse2[(int64_t)h * p.q_pad + min(a, p.q_pad - 1)]);
       }
     }
   }
+  // MODE 3: thread = (query, split lane) adds up its share of the statistics; they meet in stageQ once the queries are in registers
+  constexpr int kRowLanes = 256 / (NT * 32);
+  RowState mine{-INFINITY, 0.f};
+  if (MODE == 3)
+    mine = add_row_splits(reinterpret_cast<const float2*>(p.part_ml) + (int64_t)h * n_split * p.q_pad + q_base + threadIdx.x % (NT * 32),
+                          p.q_pad, threadIdx.x / (NT * 32), kRowLanes, n_split);
   wait_loads();
   __syncthreads();
   bf16x8 q[NT][kKS];  // lane (query, hh) holds Q[query][16 ks + 8 hh .. + 7]
@@ -2120,6 +2130,24 @@ __global__ __launch_bounds__(256, NT == 1 ? 4 : 2) void wide_logits_kernel(const
     for (int ks = 0; ks < kKS; ++ks) {
       const uint4 v = *reinterpret_cast<const uint4*>(stageQ + n * G::kStageBytes + stage_off<D>(qi, 2 * ks + hh));
       q[n][ks] = as_bf16x8(exists ? v : make_uint4(0u, 0u, 0u, 0u));
+    }
+  }
+  if (MODE == 3) {
+    float2* lane_sh = reinterpret_cast<float2*>(stageQ);  // [kRowLanes][NT * 32]
+    float* lse_sh = reinterpret_cast<float*>(stageQ + 256 * sizeof(float2));
+    static_assert(256 * sizeof(float2) + NT * 32 * sizeof(float) <= NT * G::kStageBytes, "fits");
+    __syncthreads();  // every wavefront has its queries in registers
+    lane_sh[threadIdx.x] = make_float2(mine.m, mine.l);
+    __syncthreads();
+    if (threadIdx.x < NT * 32) lse_sh[threadIdx.x] = lse_of(add_row_splits(lane_sh + threadIdx.x, NT * 32, 0, 1, kRowLanes));
+    __syncthreads();
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int i = n * 32 + 8 * (v >> 2) + 4 * hh + (v & 3);
+        set_lse(n, v, q_base + i, lse_sh[i]);
+      }
     }
   }
 
@@ -2152,7 +2180,7 @@ __global__ __launch_bounds__(256, NT == 1 ? 4 : 2) void wide_logits_kernel(const
       for (int ks = 0; ks < kKS; ++ks)
         acc = MODE == 1 ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(kop[ks], q[n][ks], acc, 0, 0, 0)
                         : __builtin_amdgcn_mfma_f32_32x32x16_bf16(q[n][ks], kop[ks], acc, 0, 0, 0);
-      if (MODE == 2) {
+      if (SUMS) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) colsum += __builtin_amdgcn_exp2f(__builtin_fmaf(acc[v], p.scale_log2, neg_lse[n][v]));
       } else {
@@ -2174,13 +2202,13 @@ __global__ __launch_bounds__(256, NT == 1 ? 4 : 2) void wide_logits_kernel(const
         l_run[n] += sum[0] + sum[1];
       }
     }
-    if (MODE == 2) {
+    if (SUMS) {
       const uintx2 sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(colsum), __float_as_uint(colsum), false, false);
       if (hh == 0 && ((cur.vmask >> qi) & 1u))
         p.colpart[((int64_t)qg * p.H + h) * p.L + cur.row0 + qi] = __uint_as_float(sw.x) + __uint_as_float(sw.y);
     }
   }
-  if (MODE == 2) return;
+  if (SUMS) return;
 
   __syncthreads();  // every wavefront has its queries in registers: stageQ is free for the statistics
 #pragma unroll
@@ -2200,7 +2228,7 @@ __global__ __launch_bounds__(256, NT == 1 ? 4 : 2) void wide_logits_kernel(const
       if (v.y > 0.f) lsum += v.y * __builtin_amdgcn_exp2f(v.x - mmax);
     }
     if (q_base + (int)threadIdx.x < p.q_pad) {
-      const int64_t row = ((int64_t)h * p.q_pad + q_base + threadIdx.x) * p.n_split + split;
+      const int64_t row = ((int64_t)h * p.n_split + split) * p.q_pad + q_base + threadIdx.x;
       *reinterpret_cast<float2*>(p.part_ml + 2 * row) = make_float2(lsum > 0.f ? mmax : -INFINITY, lsum);
     }
   }
@@ -2229,7 +2257,9 @@ static hipError_t launch_logits_t(const LogitArgs& a, const SplitPlan& p, int mo
   if (mode == 0 || query_group_list(p, a.H) > kMaxList) return hipErrorInvalidValue;
   const dim3 grid = grid_list(query_group_list(p, a.H));
 #define WIDE_LOGITS(NT)                                                                                                 \
-  if (mode == 2)                                                                                                        \
+  if (mode == 2 && a.part_ml != nullptr)                                                                                \
+    hipLaunchKernelGGL((wide_logits_kernel<D, NT, 3, false>), grid, dim3(256), 0, st, LOGITS_ARGS, p.q_groups, a);      \
+  else if (mode == 2)                                                                                                   \
     hipLaunchKernelGGL((wide_logits_kernel<D, NT, 2, false>), grid, dim3(256), 0, st, LOGITS_ARGS, p.q_groups, a);      \
   else if (select)                                                                                                      \
     hipLaunchKernelGGL((wide_logits_kernel<D, NT, 1, true>), grid, dim3(256), 0, st, LOGITS_ARGS, p.q_groups, a);       \
@@ -2244,6 +2274,11 @@ static hipError_t launch_logits_t(const LogitArgs& a, const SplitPlan& p, int mo
 #undef LOGITS_ARGS
   return hipGetLastError();
 }
+
+// Up to four batches of statistics per thread: about as long as a launch of lse_combine_kernel would take (sink chain with that launch
+// and without: 4 heads, 8256 keys, 36 queries, 65 splits 22.2 and 21.1 us; 65 600 keys, d = 64, 192 splits 28.8 and 30.0; 32 heads,
+// 32 832 keys, 24 splits 105.2 and 102.6).
+bool lse_in_logits(const SplitPlan& p) { return p.n_split <= 4 * kSplitsInFlight * (p.q_tiles_per_group == 2 ? 8 : 4); }
 
 // mode 0: logits + part_ml out; mode 1: part_ml out; mode 2: lse2 in, colpart out (0: qk_logits_kernel; 1, 2: wide_logits_kernel)
 hipError_t launch_qk_logits(const void* Q, const int32_t* active_idx, const int32_t* counts, int max_active,

@@ -428,32 +428,24 @@ hipError_t launch_block_relevance(const void* Q, const int32_t* focus_idx, const
 // domain) and per-split row maxima / sums; here the row log-sum-exp is assembled and the column mass
 // S_j = mean over (head, active query) of exp2(logit - lse) is accumulated in a fixed order.
 // =====================================================================================================
-__global__ __launch_bounds__(256) void lse_combine_kernel(const float* __restrict__ part_ml, int rows, int n_split,
-                                                          float* __restrict__ lse2) {
-  // one wavefront per row r = h * q_pad + q; lanes stride over the splits, so the loads are independent
-  const int r = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (r >= rows) return;
-  const float2* p = reinterpret_cast<const float2*>(part_ml) + (int64_t)r * n_split;
-  float m = -INFINITY, l = 0.f;
-  for (int s = lane; s < n_split; s += kWave) {
-    const float2 v = p[s];
-    if (v.y > 0.f) {
-      const float m_new = fmaxf(m, v.x);
-      l = l * __builtin_amdgcn_exp2f(m - m_new) + v.y * __builtin_amdgcn_exp2f(v.x - m_new);
-      m = m_new;
-    }
-  }
-  float mmax = m;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) mmax = fmaxf(mmax, __shfl_xor(mmax, o, kWave));
-  float ls = l > 0.f ? l * __builtin_amdgcn_exp2f(m - mmax) : 0.f;
-  ls = wave_sum(ls);
-  if (lane == 0) lse2[r] = ls > 0.f ? mmax + __builtin_amdgcn_logf(ls) : INFINITY;  // v_log_f32 is log2
+// One workgroup per head and 16 queries: thread = (query, split lane); up to 256 splits are one memory round trip.
+constexpr int kCombineLanes = 32;
+__global__ __launch_bounds__(16 * kCombineLanes) void lse_combine_kernel(const float* __restrict__ part_ml, int q_pad, int n_split, float* __restrict__ lse2) {
+  constexpr int kWaves = kCombineLanes / 4;
+  __shared__ float2 wave_sh[kWaves][16];
+  const int q = threadIdx.x & 15, sl = threadIdx.x >> 4;
+  const int64_t tile = blockIdx.x;  // h * (q_pad / 16) + query tile
+  const int tiles = q_pad >> 4, h = (int)(tile / tiles), q0 = (int)(tile - (int64_t)h * tiles) * 16;
+  const RowState r = add_row_splits(reinterpret_cast<const float2*>(part_ml) + (int64_t)h * n_split * q_pad + q0 + q, q_pad, sl, kCombineLanes, n_split);
+  const float m = group_max(r.m);  // the four lanes of a query in this wavefront
+  const float l = group_sum(r.l > 0.f ? r.l * __builtin_amdgcn_exp2f(r.m - m) : 0.f);
+  if ((threadIdx.x & 63) < 16) wave_sh[threadIdx.x >> 6][q] = make_float2(m, l);
+  __syncthreads();
+  if (threadIdx.x < 16) lse2[tile * 16 + q] = lse_of(add_row_splits(&wave_sh[0][q], 16, 0, 1, kWaves));
 }
 
 hipError_t launch_lse_combine(const float* part_ml, int H, int q_pad, int n_split, float* lse2, hipStream_t st) {
-  const int rows = H * q_pad;
-  hipLaunchKernelGGL(lse_combine_kernel, dim3(ceil_div(rows, 4)), dim3(256), 0, st, part_ml, rows, n_split, lse2);
+  hipLaunchKernelGGL(lse_combine_kernel, dim3(H * (q_pad / 16)), dim3(16 * kCombineLanes), 0, st, part_ml, q_pad, n_split, lse2);
   return hipGetLastError();
 }
 
@@ -473,11 +465,12 @@ hipError_t launch_lse_combine(const float* part_ml, int H, int q_pad, int n_spli
 // fewer nominees per group sink_rank_kernel sees to the groups that may hold more.
 constexpr int kMassKeys = 128;
 
-// LSE (with PRE = false): lse2 holds the softmax statistics (max, sum) of n_split key splits per row, [H, 16, n_split], instead,
-// and every workgroup forms the log-sum-exps itself, eight lanes per row, while its first logits travel: up to kLseRows rows and
-// kLseInMassBytes of statistics that is cheaper than a launch of lse_combine_kernel (sink chain of 4 heads, 1056 keys, 5 KB: 14.0
-// -> 12.0 us; 4 heads, 8224 keys, 33 KB: 16.9 -> 15.6; 16 heads, 4064 keys, 65 KB: 19.5 -> 20.4).
-constexpr int kLseRows = 1024, kLseInMassBytes = 40960;
+// LSE (with PRE = false): lse2 holds the softmax statistics (max, sum) of n_split key splits per row, [H, n_split, 16], instead,
+// and every workgroup forms the log-sum-exps itself, thread = (split lane, row), while its first logits travel: up to kLseRows rows and
+// kLseInMassBytes of statistics that takes no longer than a launch of lse_combine_kernel (sink chain, with that launch and without:
+// 32 heads, 4160 keys, 64 KB: 20.9 and 20.0 us; 8256 keys, 64 KB: 30.0 and 28.9; 128 KB: 29.2 and 29.5; 16 448 keys, 64 KB 47.5 and
+// 47.9; 8 heads, 8256 keys, 32 KB: 16.3 and 15.3; 4 heads, 1056 keys, 5 KB: 14.0 and 12.0).
+constexpr int kLseRows = 1024, kLseInMassBytes = 65536;
 static bool lse_fits_column_mass(int H, int n_split) { return H * 16 <= kLseRows && (int64_t)H * 16 * n_split * 8 <= kLseInMassBytes; }
 
 template <bool PRE, bool LSE>
@@ -533,29 +526,20 @@ __global__ __launch_bounds__(512) void column_mass_kernel(const float* __restric
       if (LSE) {
         if (h0 == 0) {  // uniform
           const float2* ml = reinterpret_cast<const float2*>(lse2);
-          const int rows = H * 16, sl = threadIdx.x & 7;
-          for (int row = threadIdx.x >> 3; row < rows; row += 64) {
-            float m = -INFINITY, l = 0.f;
-            for (int s0 = sl; s0 < n_split; s0 += 32) {
-              float2 v[4];
-#pragma unroll
-              for (int u = 0; u < 4; ++u) v[u] = s0 + 8 * u < n_split ? ml[row * n_split + s0 + 8 * u] : make_float2(-INFINITY, 0.f);
-#pragma unroll
-              for (int u = 0; u < 4; ++u) {
-                if (v[u].y > 0.f) {
-                  const float m_new = fmaxf(m, v[u].x);
-                  l = l * __builtin_amdgcn_exp2f(m - m_new) + v[u].y * __builtin_amdgcn_exp2f(v[u].x - m_new);
-                  m = m_new;
-                }
-              }
-            }
-            float mmax = m;
-#pragma unroll
-            for (int o = 4; o > 0; o >>= 1) mmax = fmaxf(mmax, __shfl_xor(mmax, o, kWave));
-            float ls = l > 0.f ? l * __builtin_amdgcn_exp2f(m - mmax) : 0.f;
-#pragma unroll
-            for (int o = 4; o > 0; o >>= 1) ls += __shfl_xor(ls, o, kWave);
-            if (sl == 0) lse_sh[row] = ls > 0.f ? mmax + __builtin_amdgcn_logf(ls) : INFINITY;  // v_log_f32 is log2
+          const int rows = H * 16, lanes = rows <= 64 ? 8 : (rows <= 128 ? 4 : (rows <= 256 ? 2 : 1));  // neighbouring lanes per row
+          const int sl = threadIdx.x & (lanes - 1), per_turn = 512 / lanes;
+          for (int row = threadIdx.x / lanes; row < rows; row += per_turn) {
+            const float2* first = ml + (row >> 4) * n_split * 16 + (row & 15);
+            const RowState r = n_split <= 2 * lanes ? add_row_splits<2>(first, 16, sl, lanes, n_split) : add_row_splits(first, 16, sl, lanes, n_split);
+            float m = r.m;
+            if (lanes > 1) m = fmaxf(m, lane_dpp<0xB1>(m));   // quad_perm [1,0,3,2]
+            if (lanes > 2) m = fmaxf(m, lane_dpp<0x4E>(m));   // quad_perm [2,3,0,1]
+            if (lanes > 4) m = fmaxf(m, lane_dpp<0x141>(m));  // row_half_mirror
+            float l = r.l > 0.f ? r.l * __builtin_amdgcn_exp2f(r.m - m) : 0.f;
+            if (lanes > 1) l += lane_dpp<0xB1>(l);
+            if (lanes > 2) l += lane_dpp<0x4E>(l);
+            if (lanes > 4) l += lane_dpp<0x141>(l);
+            if (sl == 0) lse_sh[row] = lse_of(RowState{m, l});
           }
           __syncthreads();
         }

@@ -180,6 +180,34 @@ def test_find_sinks(G, H, M, N, d, n_gen, n_act, n_sink):
     assert torch.equal(sinks, sinks2) and np.allclose(col2.cpu().numpy(), S, rtol=1e-6)
 
 
+@pytest.mark.parametrize("H,M,N,d,n_act", [
+    (1, 32, 0, 64, 3),          # one split of one sub-tile
+    (1, 8192, 64, 128, 16),     # one head: 65 splits, added up by eight threads per row in the column-mass kernel
+    (3, 2049, 0, 64, 16),       # 17 splits: one more than two per thread
+    (3, 2048, 0, 64, 16),       # 16
+    (8, 3000, 7, 64, 5),        # four threads per row
+    (9, 3000, 7, 64, 16),       # two
+    (31, 600, 3, 64, 7),        # 496 rows: one thread each
+    (33, 600, 3, 64, 16),       # 528 rows: two turns
+    (64, 1100, 0, 64, 16),      # 1024 rows, the most; four splits
+    (65, 1100, 0, 64, 16),      # one head more: a launch of its own adds the splits up
+    (2, 131072, 0, 64, 16),     # 256 splits: the most statistics
+    (8, 33000, 0, 64, 16),      # the same for eight heads
+    (8, 33600, 0, 64, 16),      # 65 splits: too many
+    (1, 32768, 64, 64, 30),     # two passes, 65 splits: eight threads per row in the second pass
+    (8, 33000, 0, 64, 20),      # 65 splits
+    (1, 131072, 64, 64, 17),    # 257 splits: the first that need the launch
+    (1, 16000, 0, 64, 50),      # two query tiles, 125 splits, four threads per row
+    (1, 16500, 0, 128, 50),     # 129 splits: the first that need the launch
+    (3, 40, 0, 128, 100)])      # two query groups, one split
+def test_find_sinks_statistics_of_the_key_splits(G, H, M, N, d, n_act):
+    q, k = _rand_bf16(16, H, n_act, d).to(G.DEV), _rand_bf16(17, H, M + N, d).to(G.DEV)
+    act = np.arange(n_act)
+    col, _ = G.gpu_find_sinks(q, G.i32(act), None, k, M, 64, 1)
+    S, Sref = col.cpu().numpy().astype(np.float64), fo.sink_scores(G.to_np(q), act, G.to_np(k))
+    assert np.allclose(S, Sref, rtol=2e-4, atol=1e-9) and S.sum() == pytest.approx(1.0, abs=1e-4)
+
+
 @pytest.mark.parametrize("n_gen,k,window,lo,hi,cap", [
     (64, 16, 0, 0, 64, 16), (64, 4, 8, 0, 64, 36), (63, 5, 9, 3, 60, 57), (64, 64, 0, 0, 64, 64), (64, 1, 300, 0, 64, 64),
     (1, 1, 0, 0, 1, 1), (33, 8, 2, 10, 11, 8), (65, 4, 2, 0, 65, 12), (200, 30, 3, 0, 200, 90), (64, 3, 200, 63, 64, 20)])
