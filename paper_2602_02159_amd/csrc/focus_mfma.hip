@@ -464,6 +464,20 @@ struct AttnArgs {
   float* lse2_out;    // [H, q_pad] base-2 log-sum-exp per row (+inf for an empty row), or null
 };
 
+// |I_focus| and |I_active| as they lie in memory (or the capacities of the lists): scalar loads that a kernel requests at its start and
+// waits for once its first vector loads are out (one that first looked whether its query group is past the count, and read the other
+// count when the relevances had come, spent two memory round trips on it: layers of more than 16 queries 0.3 to 0.7 us).
+struct Counts {
+  int focus, active;
+  __device__ __forceinline__ explicit Counts(const AttnArgs& p) : focus(p.n_focus_max), active(p.max_active) {
+    if (p.counts) {
+      focus = p.counts[0];
+      active = p.counts[1];
+    }
+  }
+  __device__ __forceinline__ int n_active(const AttnArgs& p) const { return min(max(active, 0), p.max_active); }
+};
+
 // The arguments that the first memory requests of an attention kernel need, once more as leading scalar parameters: those (14
 // dwords) are in scalar registers when a wavefront starts (-amdgpu-kernarg-preload-count), while a member of AttnArgs is a load
 // of its own in front of everything that depends on it.  H arrives negative where the partial relevances are per head.
@@ -471,6 +485,10 @@ struct AttnArgs {
   const float *rel_part, const int32_t *active_idx, const uint16_t *Q, const int32_t *counts, int n_b, int H, int max_active, \
       int n_gen, int n_split, int n_sub
 #define ATTN_FIRST_NAMES rel_part, active_idx, Q, counts, n_b, H, max_active, n_gen, n_split, n_sub
+// wide_attn_kernel: n_gen is needed later, the number of query groups at once
+#define WIDE_FIRST_PARAMS                                                                                                     \
+  const float *rel_part, const int32_t *active_idx, const uint16_t *Q, const int32_t *counts, int n_b, int H, int max_active, \
+      int q_groups, int n_split, int n_sub
 __device__ __forceinline__ AttnArgs with_first(AttnArgs p, ATTN_FIRST_PARAMS) {
   p.rel_part = rel_part;
   p.active_idx = active_idx;
@@ -485,6 +503,9 @@ __device__ __forceinline__ AttnArgs with_first(AttnArgs p, ATTN_FIRST_PARAMS) {
   p.n_sub = n_sub;
   return p;
 }
+#define WIDE_LAUNCH(kernel, grid, block, st, a)                                                                            \
+  hipLaunchKernelGGL(kernel, grid, block, 0, st, (a).rel_part, (a).active_idx, (a).Q, (a).counts, (a).n_b, (a).rel_per_head ? -(a).H : (a).H, (a).max_active, \
+                     (a).q_groups, (a).n_split, (a).n_sub, a)
 #define ATTN_LAUNCH(kernel, grid, block, st, a)                                                                            \
   hipLaunchKernelGGL(kernel, grid, block, 0, st, (a).rel_part, (a).active_idx, (a).Q, (a).counts, (a).n_b, (a).rel_per_head ? -(a).H : (a).H, (a).max_active, \
                      (a).n_gen, (a).n_split, (a).n_sub, a)
@@ -513,8 +534,8 @@ __device__ __forceinline__ void first_partials(FirstParts<NP, THREADS, MANY>& f,
   __builtin_amdgcn_sched_barrier(0);  // (the scheduler would move the wait for the row ids in front of these loads)
 }
 template <int NP, int THREADS, bool MANY>
-__device__ __forceinline__ void rank_blocks(const AttnArgs& p, const FirstParts<NP, THREADS, MANY>& f, bool per_head, int32_t* kept_sh,
-                                            TopkShared& sm, bool writer) {
+__device__ __forceinline__ void rank_blocks(const AttnArgs& p, const FirstParts<NP, THREADS, MANY>& f, bool per_head, int n_focus,
+                                            int32_t* kept_sh, TopkShared& sm, bool writer) {
   constexpr int kPlanes = FirstParts<NP, THREADS, MANY>::kPlanes;
   const int tid = threadIdx.x;
   const bool tournament = !MANY && p.n_keep * (THREADS / kWave) <= kWave;  // uniform
@@ -522,7 +543,7 @@ __device__ __forceinline__ void rank_blocks(const AttnArgs& p, const FirstParts<
     block_topk_clear<THREADS>(sm);
     __syncthreads();
   }
-  const int n_f = p.counts ? min(max(p.counts[0], 0), p.n_focus_max) : p.n_focus_max;
+  const int n_f = min(max(n_focus, 0), p.n_focus_max);
   const float scale = n_f > 0 ? 1.f / ((float)n_f * (float)p.H) : 0.f;
   const int n_groups = (p.H + kRelGroup - 1) / kRelGroup;
   float rel[kPlanes];
@@ -662,6 +683,7 @@ __global__ __launch_bounds__(256, (FUSE & 2) == 0 ? 2 : 1) void sparse_attn_kern
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c = lane & 15, g = lane >> 4;
   const int split = PIPE ? blockIdx.x : blockIdx.y, h = PIPE ? blockIdx.y : blockIdx.x;
+  const Counts counted(p);
   char* stageK = ldsA + wave * kBufBytes;  // the slot this wavefront owns
   char* stageV = stageK + G::kStageBytes;
   const uint16_t* Qh = p.Q + (int64_t)h * p.qsh;
@@ -682,7 +704,7 @@ __global__ __launch_bounds__(256, (FUSE & 2) == 0 ? 2 : 1) void sparse_attn_kern
     first_partials(first, p, PER_HEAD);
     few_sinks = request_few_sinks(p, lane);
     load_q_tile<D>(q, Qh, p.qsn, qrow_early, lane);
-    rank_blocks(p, first, PER_HEAD, kept_sh, topk_sm, blockIdx.x == 0 && blockIdx.y == 0);
+    rank_blocks(p, first, PER_HEAD, counted.focus, kept_sh, topk_sm, blockIdx.x == 0 && blockIdx.y == 0);
     kept_blocks = kept_sh;
   } else {
     few_sinks = request_few_sinks(p, lane);
@@ -713,7 +735,7 @@ __global__ __launch_bounds__(256, (FUSE & 2) == 0 ? 2 : 1) void sparse_attn_kern
     }
   }
   if (!FUSED) load_q_tile<D>(q, Qh, p.qsn, qrow, lane);
-  const int n_act = p.counts ? min(max(p.counts[1], 0), p.max_active) : p.max_active;
+  const int n_act = counted.n_active(p);
   mask_q_tile<D>(q, 0, n_act, lane);
 
   float m_run = -INFINITY, l_run = 0.f;
@@ -948,8 +970,9 @@ __device__ __forceinline__ void store_o_tile(char* dst, const floatx16 (&o)[D / 
 // Grid: one list (list_index).  Workgroups go to the XCDs round-robin, so the query groups of one (head, key split) pair are
 // placed eight apart: they run on the same XCD at about the same time and its L2 serves their common K/V rows.
 template <int D, int NT, int MODE>
-__global__ __launch_bounds__(256 * NT, NT == 2 || (MODE & 4) == 0 ? 2 : 1) void wide_attn_kernel(ATTN_FIRST_PARAMS, const AttnArgs args) {
-  const AttnArgs p = with_first(args, ATTN_FIRST_NAMES);
+__global__ __launch_bounds__(256 * NT, NT == 2 || (MODE & 4) == 0 ? 2 : 1) void wide_attn_kernel(WIDE_FIRST_PARAMS, const AttnArgs args) {
+  AttnArgs p = with_first(args, rel_part, active_idx, Q, counts, n_b, H, max_active, args.n_gen, n_split, n_sub);
+  p.q_groups = q_groups;
   using G = Geo<D>;
   constexpr bool FUSED = (MODE & 1) != 0, PIPE = (MODE & 2) != 0, DOUBLE = (MODE & 4) != 0, MANY = (MODE & 16) != 0;
   static_assert(!DOUBLE || PIPE, "two stages are for the key loop");
@@ -972,13 +995,15 @@ __global__ __launch_bounds__(256 * NT, NT == 2 || (MODE & 4) == 0 ? 2 : 1) void 
   const int slot = wave & (kWavesPerGroup - 1), tile = NT == 1 ? 0 : wave >> 2;
   const int qi = lane & 31, hh = lane >> 5;
   const int slot8 = list_index() >> 3;
-  const int pair = (slot8 / p.q_groups) * 8 + (int)(blockIdx.x & 7u), qg = slot8 % p.q_groups;
+  int first8 = slot8, qg = 0;
+  if (p.q_groups > 1) {
+    first8 = slot8 / p.q_groups;
+    qg = slot8 - first8 * p.q_groups;
+  }
+  const int pair = first8 * 8 + (int)(blockIdx.x & 7u);
   if (pair >= p.n_split * p.H) return;  // whole workgroup
   const int h = pair / p.n_split, split = pair - h * p.n_split;
-  if (qg > 0) {  // a query group past the device-side count has nothing to do
-    const int n = p.counts ? min(max(p.counts[1], 0), p.max_active) : p.max_active;
-    if (qg * NT * 32 >= n) return;
-  }
+  const Counts counted(p);
   const int q0 = (qg * NT + tile) * 32;  // first query of this wavefront's tile
   const uint16_t* Qh = p.Q + (int64_t)h * p.qsh;
   const uint16_t* Kh = p.K + (int64_t)h * p.ksh;
@@ -998,11 +1023,13 @@ __global__ __launch_bounds__(256 * NT, NT == 2 || (MODE & 4) == 0 ? 2 : 1) void 
     FirstParts<8, 256 * NT, MANY> first;  // (per head, from a K scan: the other parts are requested when they are added)
     first_partials(first, p, p.rel_per_head);
     few_sinks = request_few_sinks(p, lane);
+    if (qg > 0 && qg * NT * 32 >= counted.n_active(p)) return;  // a query group past the device-side count has nothing to do
     load_q();
-    rank_blocks(p, first, p.rel_per_head, kept_sh, *reinterpret_cast<TopkShared*>(topk_raw), pair == 0 && qg == 0);
+    rank_blocks(p, first, p.rel_per_head, counted.focus, kept_sh, *reinterpret_cast<TopkShared*>(topk_raw), pair == 0 && qg == 0);
     kept_blocks = kept_sh;
   } else {
     few_sinks = request_few_sinks(p, lane);
+    if (qg > 0 && qg * NT * 32 >= counted.n_active(p)) return;
   }
   const SinkUnion uni = prepare_union(p, split, kept_blocks, kept_bits_sh, &sinks_unsorted_sh);
 
@@ -1031,7 +1058,7 @@ __global__ __launch_bounds__(256 * NT, NT == 2 || (MODE & 4) == 0 ? 2 : 1) void 
   SubTile t = locate(PIPE ? rounds.sub(0, slot) : split * kWavesPerGroup + slot);
   request(t, slotA);
   if (!FUSED) load_q();
-  const int n_act = p.counts ? min(max(p.counts[1], 0), p.max_active) : p.max_active;
+  const int n_act = counted.n_active(p);
   {
     const bool live = qrow >= 0 && q0 + qi < n_act;
 #pragma unroll
@@ -1238,17 +1265,17 @@ static void launch_wide_t(const AttnArgs& a, const SplitPlan& p, bool fused, hip
   constexpr int kKeep = LOOP & 8;
   const bool many = a.n_b > 256;
   if (fused && p.pipelined && many)
-    ATTN_LAUNCH((wide_attn_kernel<D, NT, LOOP | 17>), grid, block, st, a);
+    WIDE_LAUNCH((wide_attn_kernel<D, NT, LOOP | 17>), grid, block, st, a);
   else if (fused && many)
-    ATTN_LAUNCH((wide_attn_kernel<D, NT, kKeep | 17>), grid, block, st, a);
+    WIDE_LAUNCH((wide_attn_kernel<D, NT, kKeep | 17>), grid, block, st, a);
   else if (fused && p.pipelined)
-    ATTN_LAUNCH((wide_attn_kernel<D, NT, LOOP | 1>), grid, block, st, a);
+    WIDE_LAUNCH((wide_attn_kernel<D, NT, LOOP | 1>), grid, block, st, a);
   else if (fused)
-    ATTN_LAUNCH((wide_attn_kernel<D, NT, kKeep | 1>), grid, block, st, a);
+    WIDE_LAUNCH((wide_attn_kernel<D, NT, kKeep | 1>), grid, block, st, a);
   else if (p.pipelined)
-    ATTN_LAUNCH((wide_attn_kernel<D, NT, LOOP>), grid, block, st, a);
+    WIDE_LAUNCH((wide_attn_kernel<D, NT, LOOP>), grid, block, st, a);
   else
-    ATTN_LAUNCH((wide_attn_kernel<D, NT, kKeep>), grid, block, st, a);
+    WIDE_LAUNCH((wide_attn_kernel<D, NT, kKeep>), grid, block, st, a);
 }
 
 template <int D>
