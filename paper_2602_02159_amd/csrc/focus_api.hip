@@ -31,6 +31,13 @@ static inline size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 // Launch shapes (workgroups per launch the key axis is cut for).  Fixed constants: split counts decide workspace
 // sizes and the order in which partial results are merged, so they must not vary between calls.
 constexpr int kAttnGroups = 512;      // one sub-tile per slot: every workgroup resident at once, two per compute unit
+// d = 64, up to 16 queries: half the LDS and few registers, twice as many are resident.  One sub-tile per wavefront up to 128 a head
+// (32 heads, 67 sub-tiles 15.5 -> 13.9 us per layer, 123 17.1 -> 15.4), then two workgroups per compute unit (131 17.9 -> 16.7, 259
+// 23.2 -> 21.8, 1026 51.7 -> 46.5), as long as no more than 64 partial results per row come of it: merging them costs a memory round
+// trip for every 64 (4 heads, 1004 sub-tiles: 18.4 us in 64 splits, 23.6 in 251).  32-query tiles (24 queries) gain at 67 sub-tiles
+// only (16.6 -> 15.4) and lose from 91 on; nor does the probe layer gain, whose kernel also writes its logits (1026 sub-tiles 80.0 ->
+// 80.7).
+constexpr int kAttnGroupsSmall = 1024, kAttnGroupsSmallPipe = 512, kAttnSplitsSmall = 64;
 constexpr int kAttnGroupsPipe = 256;  // many sub-tiles per slot, two stages per slot: one workgroup per compute unit
 constexpr int kAttnGroupsWide = 512;  // the same where query groups share the rows: one stage per slot, two workgroups per compute unit
 constexpr int kLogitGroups = 4096;    // sink scoring, one query tile: at most so many (short workgroups even out the tail of the scan) ...
@@ -60,12 +67,14 @@ static void plan_splits(SplitPlan& p, int n_heads, int q_groups, int target_grou
   p.n_split = std::max(1, std::min(per_head, ceil_div(p.n_sub, kWavesPerGroup)));
 }
 
-static void plan_attention_splits(SplitPlan& p, const focus_shape& s) {
-  plan_splits(p, s.n_heads, p.q_groups, kAttnGroups);
+static void plan_attention_splits(SplitPlan& p, const focus_shape& s, bool logits_out) {
+  const bool d64 = s.head_dim == 64 && p.q_tiles == 1 && !logits_out;
+  auto small = [&](int groups) { return d64 && groups / s.n_heads <= kAttnSplitsSmall; };
+  plan_splits(p, s.n_heads, p.q_groups, small(kAttnGroupsSmall) ? kAttnGroupsSmall : kAttnGroups);
   // Many sub-tiles per wavefront (dense layers, alpha = 0.5): fewer, longer workgroups with double-buffered key loops.
   // One sub-tile per wavefront (the 3 % keep configurations): nothing to overlap.
   if (p.n_split * kWavesPerGroup < p.n_sub) {
-    plan_splits(p, s.n_heads, p.q_groups, p.q_groups > 1 ? kAttnGroupsWide : kAttnGroupsPipe);
+    plan_splits(p, s.n_heads, p.q_groups, small(kAttnGroupsSmallPipe) ? kAttnGroupsSmallPipe : (p.q_groups > 1 ? kAttnGroupsWide : kAttnGroupsPipe));
     p.pipelined = p.n_split * kWavesPerGroup < p.n_sub;
   }
 }
@@ -74,7 +83,7 @@ SplitPlan plan_attention(const focus_shape& s, int max_active, int n_keep, int n
   SplitPlan p;
   plan_queries(p, max_active, max_active <= 64 ? 4 : 2);
   p.n_sub = n_keep * ceil_div(s.block, kSubTile) + ceil_div(s.n_resp, kSubTile) + ceil_div(n_sink, kSubTile);
-  plan_attention_splits(p, s);
+  plan_attention_splits(p, s, false);
   return p;
 }
 
@@ -82,7 +91,7 @@ SplitPlan plan_attention_dense(const focus_shape& s, int max_active) {
   SplitPlan p;
   plan_queries(p, max_active, max_active <= 64 ? 4 : 2);
   p.n_sub = ceil_div(s.n_ctx + s.n_resp, kSubTile);
-  plan_attention_splits(p, s);
+  plan_attention_splits(p, s, p.q_tiles == 1);
   return p;
 }
 

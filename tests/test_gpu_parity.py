@@ -401,6 +401,21 @@ def test_sparse_attn_query_tiles_and_key_splits(G, H, M, N, d, cap, live):
     assert torch.isnan(out[:, live:]).all()  # rows past the count are not written
 
 
+@pytest.mark.parametrize("H,M,N", [
+    (32, 4096, 0),      # 128 sub-tiles of 32 heads: the most with one per wavefront, 32 splits
+    (32, 4096, 5),      # one more: a key loop in 16 splits
+    (16, 8192, 0), (16, 8192, 1),      # 64 splits, and 32
+    (15, 4500, 3),      # fewer heads would take more than 64 splits
+    (8, 8000, 30)])
+def test_sparse_attn_few_queries_of_64_columns(G, H, M, N):
+    q, k, v = (_rand_bf16(75 + i, H, r, 64).to(G.DEV) for i, r in enumerate((16, M + N, M + N)))
+    kept = np.arange(-(-M // 32))
+    out, lse = G.gpu_sparse_attn(q, G.i32(np.arange(16)), G.i32([0, 11]), k, v, M, 32, G.i32(kept), None)
+    ref, ref_lse = fo.sparse_attention(G.to_np(q), np.arange(11), G.to_np(k), G.to_np(v), np.arange(M), M)
+    G.assert_attention_close(out[:, :11], ref)
+    assert np.allclose(lse[:, :11].cpu().numpy(), ref_lse, atol=2e-3)
+
+
 @pytest.mark.parametrize("n_act", [16, 30, 50])
 @pytest.mark.parametrize("H,M,N,d", [
     (5, 20001, 30, 64),                        # 51 splits of two or three rounds, the last one ragged
