@@ -40,13 +40,15 @@ constexpr int kAttnGroups = 512;      // one sub-tile per slot: every workgroup 
 constexpr int kAttnGroupsSmall = 1024, kAttnGroupsSmallPipe = 512, kAttnSplitsSmall = 64;
 constexpr int kAttnGroupsPipe = 256;  // many sub-tiles per slot, two stages per slot: one workgroup per compute unit
 constexpr int kAttnGroupsWide = 512;  // the same where query groups share the rows: one stage per slot, two workgroups per compute unit
-constexpr int kLogitGroups = 4096;    // sink scoring, one query tile: at most so many (short workgroups even out the tail of the scan) ...
-// ... with four rounds of sub-tiles each where they are all resident at once, else two, so that a workgroup's start passes beside the
-// others' rows and there are fewer statistics to merge; but one workgroup per compute unit as long as that leaves one round each.
-// Sink chain in us with one, two and four rounds: 16 heads, 32 832 keys 47.1, 42.5, 42.7; 8 heads 34.5, 26.9, 27.2; 32 heads, 8256
-// keys 32.5, 29.2, 28.9, 16 448 keys -, 46.2, 46.4, 32 832 keys -, 74.6, 76.6; 1056 keys in 9 and 8 splits 16.0, 14.9; 2112 keys in
-// 17 and 8 splits 19.3, 16.6.
-constexpr int kLogitGroupsMin = 256, kLogitGroupsResident = 1024;
+// Sink scoring, one query tile.  About four rounds of sub-tiles per workgroup where all workgroups are resident at once (1024), so that a
+// workgroup's start passes beside the others' rows and there are few statistics to merge, and the same number of workgroups for every
+// compute unit: with 17 instead of 16 splits of 32 heads some have a third more to do.  Past that, or where one split would have a
+// fifth round that nothing runs beside, two rounds in up to kLogitGroups workgroups: short ones even out the tail of the scan.
+// Sink chain in us (splits): 32 heads, 8256 keys 32.5 (65), 31.2 (13), 29.2 (16), 33.0 (17), 29.2 (32); 10 100 keys 34.3 (12), 32.2 (16),
+// 36.8 (19), 32.5 (24); 15 986 keys 43.8 (31), 42.0 (32); 16 448 keys 46.5 (32), 48.7 (33), 44.9 (65); 32 832 keys 75.4 (128), 73.5
+// (129), 78.6 (257); 1056 keys 16.0 (9), 14.9 (8); 16 heads, 32 832 keys 47.1 (256), 42.7 (128), 42.7 (64), 45.6 (65); 8 heads 34.5
+// (256), 26.9 (128), 27.2 (64).
+constexpr int kLogitGroups = 4096, kLogitGroupsResident = 1024, kLogitGroupsCu = 256, kLogitRounds = 4;
 // Two passes over K (more than 16 queries): every workgroup first fetches its query rows.  33 to 64 queries per group: as many
 // workgroups as are resident at once, three per compute unit.  Up to 32: four are; more of them even out the tail of a long scan,
 // as long as each has four rounds of sub-tiles.
@@ -102,8 +104,15 @@ SplitPlan plan_logits(const focus_shape& s, int max_active) {
   plan_splits(p, s.n_heads, p.q_groups,
               p.q_tiles_per_group == 1 ? kLogitGroups : (p.q_tiles_per_group == 2 ? kLogitGroupsTwo : kLogitGroupsMany));
   if (p.q_tiles_per_group == 1) {
-    const int rounds = p.n_sub / kWavesPerGroup, few = std::max(std::max(1, kLogitGroupsMin / s.n_heads), rounds / 4);
-    p.n_split = std::min(p.n_split, (int64_t)few * s.n_heads <= kLogitGroupsResident ? few : std::max(1, rounds / 2));
+    const int rounds = ceil_div(p.n_sub, kWavesPerGroup), step = std::max(1, kLogitGroupsCu / s.n_heads);
+    const int n = step * std::max(1, (rounds + step * kLogitRounds / 2) / (step * kLogitRounds));  // the nearest multiple of step
+    const int64_t groups = (int64_t)n * s.n_heads;
+    const bool lone_round = rounds > n * kLogitRounds && groups + (int64_t)step * s.n_heads > kLogitGroupsResident;
+    const int most = std::max(1, kLogitGroups / s.n_heads);
+    if (groups <= kLogitGroupsResident && !lone_round)
+      p.n_split = std::min(rounds, n);
+    else  // (one split more than the limit where that saves a lone round)
+      p.n_split = ceil_div(rounds, 2) <= most + 1 ? ceil_div(rounds, 2) : most;
   }
   if (p.q_tiles_per_group == 2) {
     const int rounds = p.n_sub / kWavesPerGroup;

@@ -471,7 +471,7 @@ constexpr int kMassKeys = 128;
 // 32 heads, 4160 keys, 64 KB: 20.9 and 20.0 us; 8256 keys, 64 KB: 30.0 and 28.9; 128 KB: 29.2 and 29.5; 16 448 keys, 64 KB 47.5 and
 // 47.9; 8 heads, 8256 keys, 32 KB: 16.3 and 15.3; 4 heads, 1056 keys, 5 KB: 14.0 and 12.0).
 constexpr int kLseRows = 1024, kLseInMassBytes = 65536;
-static bool lse_fits_column_mass(int H, int n_split) { return H * 16 <= kLseRows && (int64_t)H * 16 * n_split * 8 <= kLseInMassBytes; }
+bool lse_fits_column_mass(int H, int n_split) { return H * 16 <= kLseRows && (int64_t)H * 16 * n_split * 8 <= kLseInMassBytes; }
 
 template <bool PRE, bool LSE>
 __global__ __launch_bounds__(512) void column_mass_kernel(const float* __restrict__ src, const float* __restrict__ lse2,

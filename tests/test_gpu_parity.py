@@ -193,7 +193,9 @@ def test_find_sinks(G, H, M, N, d, n_gen, n_act, n_sink):
     (65, 1100, 0, 64, 16),      # one head more: a launch of its own adds the splits up
     (2, 131072, 0, 64, 16),     # 256 splits: the most statistics
     (8, 33000, 0, 64, 16),      # the same for eight heads
-    (8, 33600, 0, 64, 16),      # 65 splits: too many
+    (8, 45000, 0, 64, 16),      # 96 splits: too many
+    (32, 8200, 56, 64, 16),     # 65 rounds in 16 splits, one of them with a fifth
+    (32, 16400, 0, 64, 16),     # 129 rounds: two each
     (1, 32768, 64, 64, 30),     # two passes, 65 splits: eight threads per row in the second pass
     (8, 33000, 0, 64, 20),      # 65 splits
     (1, 131072, 64, 64, 17),    # 257 splits: the first that need the launch
