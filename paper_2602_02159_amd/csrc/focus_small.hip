@@ -453,9 +453,11 @@ hipError_t launch_lse_combine(const float* part_ml, int H, int q_pad, int n_spli
 //   PRE = false: `src` holds the scaled logits of at most 16 active queries in the layout
 //                [head][key quad][query][key within the quad] (fp32) and lse2 their row log-sum-exps [H, 16].  Lane
 //                (query c, quad qd) of wavefront w owns the four keys of quad 4 w + qd for query c: one 16-byte load
-//                per head, the 64 lanes of a load instruction reading 1 KB of consecutive bytes; sixteen heads are in
-//                flight at a time.  It adds exp2(logit - lse) over the heads in head order; the sixteen queries of a
-//                quad are then summed across the lanes of a DPP row (fixed tree).
+//                per head, the 64 lanes of a load instruction reading 1 KB of consecutive bytes; HEADS heads are in
+//                flight at a time: sixteen, or four or eight where there are just so many (past the last head a load repeats
+//                it: 4 heads, 1056 keys 10.6 -> 10.0 us, 32 832 keys 19.4 -> 18.5; but 3 heads at 16 448 keys 17.1 with
+//                sixteen, 17.8 with four, and 6 heads 21.2 and 22.0 with eight).  It adds exp2(logit - lse) over the heads in
+//                head order; the sixteen queries of a quad are then summed across the lanes of a DPP row (fixed tree).
 //   PRE = true:  `src` holds per-part column sums [n_parts, L] (already summed over a part's queries); thread
 //                (key, part group pg) adds parts pg, pg + 4, ..., eight loads in flight, then the four groups are added.
 // S_j = total / (H * n_act).
@@ -473,7 +475,7 @@ constexpr int kMassKeys = 128;
 constexpr int kLseRows = 1024, kLseInMassBytes = 65536;
 bool lse_fits_column_mass(int H, int n_split) { return H * 16 <= kLseRows && (int64_t)H * 16 * n_split * 8 <= kLseInMassBytes; }
 
-template <bool PRE, bool LSE>
+template <bool PRE, bool LSE, int HEADS>
 __global__ __launch_bounds__(512) void column_mass_kernel(const float* __restrict__ src, const float* __restrict__ lse2,
                                                           const int32_t* __restrict__ counts, int max_active, int n_parts,
                                                           int H, int L, float* __restrict__ col_mass, int M, int n_sink,
@@ -505,7 +507,7 @@ __global__ __launch_bounds__(512) void column_mass_kernel(const float* __restric
     __syncthreads();
     if (pg == 0) mass_sh[kj] = ((red[0][kj] + red[1][kj]) + (red[2][kj] + red[3][kj])) * norm;
   } else {
-    constexpr int kHeadsInFlight = 16;
+    constexpr int kHeadsInFlight = HEADS;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int c = lane & 15, qd = lane >> 4;
     const int quad_local = wave * 4 + qd;                                    // 0 .. 31
@@ -638,22 +640,31 @@ hipError_t launch_column_mass(const float* src, bool pre_reduced, const float* l
   if (!pre_reduced && n_parts < 1) return hipErrorInvalidValue;
   const dim3 grid(ceil_div(L, kMassKeys));
   if (pre_reduced) {
-    hipLaunchKernelGGL((column_mass_kernel<true, false>), grid, dim3(512), 0, st, src, lse2, counts, max_active, n_parts, H, L, col_mass,
+    hipLaunchKernelGGL((column_mass_kernel<true, false, 1>), grid, dim3(512), 0, st, src, lse2, counts, max_active, n_parts, H, L, col_mass,
                        M, n_sink, cand, cand_keys, 0);
     return hipGetLastError();
   }
-  if (n_split > 0 && lse_fits_column_mass(H, n_split)) {
-    hipLaunchKernelGGL((column_mass_kernel<false, true>), grid, dim3(512), 0, st, src, lse2, counts, max_active, n_parts, H, L, col_mass,
-                       M, n_sink, cand, cand_keys, n_split);
-    return hipGetLastError();
-  }
-  if (n_split > 0) {
+  const bool lse = n_split > 0 && lse_fits_column_mass(H, n_split);
+  if (n_split > 0 && !lse) {
     const hipError_t e = launch_lse_combine(lse2, H, 16, n_split, lse_scratch, st);
     if (e != hipSuccess) return e;
     lse2 = lse_scratch;
   }
-  hipLaunchKernelGGL((column_mass_kernel<false, false>), grid, dim3(512), 0, st, src, lse2, counts, max_active, n_parts, H, L, col_mass,
-                     M, n_sink, cand, cand_keys, 0);
+#define COLUMN_MASS(HEADS)                                                                                                       \
+  if (lse)                                                                                                                       \
+    hipLaunchKernelGGL((column_mass_kernel<false, true, HEADS>), grid, dim3(512), 0, st, src, lse2, counts, max_active, n_parts, H, L, \
+                       col_mass, M, n_sink, cand, cand_keys, n_split);                                                           \
+  else                                                                                                                           \
+    hipLaunchKernelGGL((column_mass_kernel<false, false, HEADS>), grid, dim3(512), 0, st, src, lse2, counts, max_active, n_parts, H, L, \
+                       col_mass, M, n_sink, cand, cand_keys, 0)
+  if (n_parts == 4) {
+    COLUMN_MASS(4);
+  } else if (n_parts == 8) {
+    COLUMN_MASS(8);
+  } else {
+    COLUMN_MASS(16);
+  }
+#undef COLUMN_MASS
   return hipGetLastError();
 }
 

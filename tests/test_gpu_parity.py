@@ -185,7 +185,8 @@ def test_find_sinks(G, H, M, N, d, n_gen, n_act, n_sink):
     (1, 8192, 64, 128, 16),     # one head: 65 splits, added up by eight threads per row in the column-mass kernel
     (3, 2049, 0, 64, 16),       # 17 splits: one more than two per thread
     (3, 2048, 0, 64, 16),       # 16
-    (8, 3000, 7, 64, 5),        # four threads per row
+    (4, 3000, 7, 64, 9),        # four heads in flight
+    (8, 3000, 7, 64, 5),        # eight; four threads per row
     (9, 3000, 7, 64, 16),       # two
     (31, 600, 3, 64, 7),        # 496 rows: one thread each
     (33, 600, 3, 64, 16),       # 528 rows: two turns
