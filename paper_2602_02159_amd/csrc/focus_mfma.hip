@@ -374,8 +374,6 @@ __device__ __forceinline__ bf16x8 read_v_operand32(const char* stageV, int dt, i
 // 16-key tile, the logits of ONE query for four consecutive keys — one 16-byte store — and the 64 lanes of a store
 // instruction cover 1 KB of consecutive bytes (query fastest, then the four quads of the tile).  Quads that start at or
 // past key L are not written; the padding keys of the last quad hold finite values nobody reads.
-// PAST_CACHE: more than the memory-side cache holds, so that nothing is gained by keeping them on their way.
-template <bool PAST_CACHE = false>
 __device__ __forceinline__ void spill_logits(float* __restrict__ logits, int h, int L, int row0, const floatx4 (&acc)[2],
                                              float scale_log2, int lane) {
   const int c = lane & 15, g = lane >> 4;
@@ -385,10 +383,7 @@ __device__ __forceinline__ void spill_logits(float* __restrict__ logits, int h, 
     const int key0 = row0 + 16 * kt + 4 * g;
     if (key0 < L) {
       floatx4* dst = reinterpret_cast<floatx4*>(logits + (((int64_t)h * n_quads + (key0 >> 2)) * 16 + c) * 4);
-      if (PAST_CACHE)
-        __builtin_nontemporal_store(acc[kt] * scale_log2, dst);
-      else
-        *dst = acc[kt] * scale_log2;
+      *dst = acc[kt] * scale_log2;
     }
   }
 }
@@ -1948,7 +1943,7 @@ __device__ __forceinline__ SubTile key_subtile(int st, int L) {
 // over K) together with the per-split softmax statistics.
 // SELECT: every wavefront makes the query selection itself, beside its first K rows, instead of reading what a launch of its own
 // has written; the first workgroup writes the lists for everyone else (a step of 4 heads at 1K: one launch of 3 us less).
-template <int D, bool SELECT, bool PAST_CACHE>
+template <int D, bool SELECT>
 __global__ __launch_bounds__(256, 2) void qk_logits_kernel(const uint16_t* K, int64_t ksh, int64_t ksn, const int32_t* active_idx, int L,
                                                            int n_sub, int n_split, int max_active, int n_gen, const LogitArgs args) {
   LogitArgs p = args;  // what the first requests need comes in registers, as in the attention kernels
@@ -2007,7 +2002,7 @@ __global__ __launch_bounds__(256, 2) void qk_logits_kernel(const uint16_t* K, in
     }
     float ps[8];
     softmax_step(acc, cur.vmask, g, p.scale_log2, m_run, l_run, ps);
-    spill_logits<PAST_CACHE>(p.logits, h, p.L, cur.row0, acc, p.scale_log2, lane);
+    spill_logits(p.logits, h, p.L, cur.row0, acc, p.scale_log2, lane);
   }
 
   if (g == 0) {
@@ -2263,18 +2258,10 @@ static hipError_t launch_logits_t(const LogitArgs& a, const SplitPlan& p, int mo
   if (p.q_tiles_per_group == 1) {  // one tile spills its logits, several take two passes
     if (mode != 0) return hipErrorInvalidValue;
     const dim3 grid(p.n_split, a.H);
-    // Spilled logits that fit the 256 MB memory-side cache are read back from it; beyond, non-temporal stores keep them from
-    // displacing K (32 heads, 131136 keys, 269 MB: sink chain 301 -> 294 us; at 65600 keys, 134 MB, they cost 10 of 141).
-    constexpr int64_t kMemorySideCache = (int64_t)200 << 20;
-    const bool past = (int64_t)a.H * a.L * 64 > kMemorySideCache;
-    if (select && past)
-      hipLaunchKernelGGL((qk_logits_kernel<D, true, true>), grid, dim3(256), 0, st, LOGITS_ARGS, a);
-    else if (select)
-      hipLaunchKernelGGL((qk_logits_kernel<D, true, false>), grid, dim3(256), 0, st, LOGITS_ARGS, a);
-    else if (past)
-      hipLaunchKernelGGL((qk_logits_kernel<D, false, true>), grid, dim3(256), 0, st, LOGITS_ARGS, a);
+    if (select)
+      hipLaunchKernelGGL((qk_logits_kernel<D, true>), grid, dim3(256), 0, st, LOGITS_ARGS, a);
     else
-      hipLaunchKernelGGL((qk_logits_kernel<D, false, false>), grid, dim3(256), 0, st, LOGITS_ARGS, a);
+      hipLaunchKernelGGL((qk_logits_kernel<D, false>), grid, dim3(256), 0, st, LOGITS_ARGS, a);
     return hipGetLastError();
   }
   if (mode == 0 || query_group_list(p, a.H) > kMaxList) return hipErrorInvalidValue;

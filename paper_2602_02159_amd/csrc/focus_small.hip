@@ -458,6 +458,9 @@ hipError_t launch_lse_combine(const float* part_ml, int H, int q_pad, int n_spli
 //                it: 4 heads, 1056 keys 10.6 -> 10.0 us, 32 832 keys 19.4 -> 18.5; but 3 heads at 16 448 keys 17.1 with
 //                sixteen, 17.8 with four, and 6 heads 21.2 and 22.0 with eight).  It adds exp2(logit - lse) over the heads in
 //                head order; the sixteen queries of a quad are then summed across the lanes of a DPP row (fixed tree).
+//                PAST_CACHE: more logits than the 256 MB memory-side cache holds beside what else was written, heads in
+//                descending order and without a place in that cache: it has kept the last heads that were written, and reading
+//                the first ones first would displace them (kMemorySideCache).
 //   PRE = true:  `src` holds per-part column sums [n_parts, L] (already summed over a part's queries); thread
 //                (key, part group pg) adds parts pg, pg + 4, ..., eight loads in flight, then the four groups are added.
 // S_j = total / (H * n_act).
@@ -475,7 +478,7 @@ constexpr int kMassKeys = 128;
 constexpr int kLseRows = 1024, kLseInMassBytes = 65536;
 bool lse_fits_column_mass(int H, int n_split) { return H * 16 <= kLseRows && (int64_t)H * 16 * n_split * 8 <= kLseInMassBytes; }
 
-template <bool PRE, bool LSE, int HEADS>
+template <bool PRE, bool LSE, int HEADS, bool PAST_CACHE>
 __global__ __launch_bounds__(512) void column_mass_kernel(const float* __restrict__ src, const float* __restrict__ lse2,
                                                           const int32_t* __restrict__ counts, int max_active, int n_parts,
                                                           int H, int L, float* __restrict__ col_mass, int M, int n_sink,
@@ -522,8 +525,13 @@ __global__ __launch_bounds__(512) void column_mass_kernel(const float* __restric
 #pragma unroll
       for (int u = 0; u < kHeadsInFlight; ++u) {
         const int h = min(h0 + u, n_parts - 1);  // clamped: stays in bounds, ignored below
-        x[u] = base[(int64_t)h * n_quads * 16];
-        if (!LSE) z[u] = lse2[(int64_t)h * 16 + c];
+        if (PAST_CACHE) {
+          x[u] = __builtin_bit_cast(float4, load_stream16(base + (int64_t)(n_parts - 1 - h) * n_quads * 16));
+          z[u] = lse2[(int64_t)(n_parts - 1 - h) * 16 + c];
+        } else {
+          x[u] = base[(int64_t)h * n_quads * 16];
+          if (!LSE) z[u] = lse2[(int64_t)h * 16 + c];
+        }
       }
       if (LSE) {
         if (h0 == 0) {  // uniform
@@ -640,7 +648,7 @@ hipError_t launch_column_mass(const float* src, bool pre_reduced, const float* l
   if (!pre_reduced && n_parts < 1) return hipErrorInvalidValue;
   const dim3 grid(ceil_div(L, kMassKeys));
   if (pre_reduced) {
-    hipLaunchKernelGGL((column_mass_kernel<true, false, 1>), grid, dim3(512), 0, st, src, lse2, counts, max_active, n_parts, H, L, col_mass,
+    hipLaunchKernelGGL((column_mass_kernel<true, false, 1, false>), grid, dim3(512), 0, st, src, lse2, counts, max_active, n_parts, H, L, col_mass,
                        M, n_sink, cand, cand_keys, 0);
     return hipGetLastError();
   }
@@ -650,14 +658,21 @@ hipError_t launch_column_mass(const float* src, bool pre_reduced, const float* l
     if (e != hipSuccess) return e;
     lse2 = lse_scratch;
   }
+  // Sink chain, 16 queries of 32 heads (logits written non-temporally and read in ascending order; so; so but read plainly): 131136
+  // keys, 269 MB 287, 263, 264 us; 40 heads, 336 MB 372, 321 to 345, 372; 64 heads, 537 MB 591, 542 to 580, 605; up to 200 MB there is nothing
+  // between them but 1.2 us for the plain reads at 32832 keys.
+  constexpr int64_t kMemorySideCache = (int64_t)200 << 20;
 #define COLUMN_MASS(HEADS)                                                                                                       \
   if (lse)                                                                                                                       \
-    hipLaunchKernelGGL((column_mass_kernel<false, true, HEADS>), grid, dim3(512), 0, st, src, lse2, counts, max_active, n_parts, H, L, \
+    hipLaunchKernelGGL((column_mass_kernel<false, true, HEADS, false>), grid, dim3(512), 0, st, src, lse2, counts, max_active, n_parts, H, L, \
                        col_mass, M, n_sink, cand, cand_keys, n_split);                                                           \
   else                                                                                                                           \
-    hipLaunchKernelGGL((column_mass_kernel<false, false, HEADS>), grid, dim3(512), 0, st, src, lse2, counts, max_active, n_parts, H, L, \
+    hipLaunchKernelGGL((column_mass_kernel<false, false, HEADS, false>), grid, dim3(512), 0, st, src, lse2, counts, max_active, n_parts, H, L, \
                        col_mass, M, n_sink, cand, cand_keys, 0)
-  if (n_parts == 4) {
+  if (!lse && n_parts > 8 && (int64_t)n_parts * L * 64 > kMemorySideCache) {
+    hipLaunchKernelGGL((column_mass_kernel<false, false, 16, true>), grid, dim3(512), 0, st, src, lse2, counts, max_active, n_parts, H, L,
+                       col_mass, M, n_sink, cand, cand_keys, 0);
+  } else if (n_parts == 4) {
     COLUMN_MASS(4);
   } else if (n_parts == 8) {
     COLUMN_MASS(8);
