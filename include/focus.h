@@ -203,7 +203,8 @@ int focus_sparse_attn(const void* Q, const int32_t* active_idx, const int32_t* c
  * bit-identical outputs (scores, kept_blocks, out, lse), but in three kernel launches instead of four: the
  * attention kernel ranks the blocks itself from the partial relevances instead of waiting for a separate Top-C
  * kernel.  kbar NULL: the first launch scans K and forms the block means on the fly.
- * With more than 1024 prompt blocks (kbar NULL: more than 256) the call falls back to the separate kernels.
+ * With more than 2048 prompt blocks (kbar NULL: more than 256), or more than 1024 and less workspace than
+ * focus_workspace_bytes says, the call falls back to the separate kernels.
  */
 int focus_sparse_layer(const void* Q, const int32_t* focus_idx, const int32_t* active_idx, const int32_t* counts,
                        int32_t n_focus_max, int32_t max_active, const void* K, const void* V, const float* kbar,

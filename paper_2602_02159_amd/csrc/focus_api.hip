@@ -304,20 +304,27 @@ static int find_sinks_impl(const char* who, const SelectArgs* select, const void
                                p.q_groups, *shape, n_sink, S, ws + w.cand, sink_idx, st);
 }
 
+constexpr size_t kStaticScratchBytes = (size_t)8 << 20;  // the array of focus_sparse_layer_static
+
 struct LayerWs {
-  size_t attn, total;
+  size_t attn, need, total;  // need <= total: with less than total, more than kFusedManyBlocks blocks are ranked by a launch of their own
   ScoreWs sc;
   AttnWs at;
 };
-// Past kFusedMaxBlocks the blocks are ranked by a launch of their own, which is the last to read the relevances: the attention's
-// partial results then take their place.  (One after the other, 50 000 blocks and more of 32 heads could exceed the scratch array of
-// focus_sparse_layer_static by the few per cent that the splits of the attention had grown.)
+// A launch that ranks the blocks is the last to read the relevances, and the attention's partial results may take their place; inside
+// the attention kernel both are in use.  Up to kFusedManyBlocks blocks the two always have places of their own.  (Were that so for any
+// number, 50 000 blocks and more of 32 heads could exceed the scratch array of focus_sparse_layer_static by the few per cent that the
+// splits of the attention had grown.)
 static LayerWs ws_layer(const focus_shape& s, const SplitPlan& p) {
+  const int n_b = ceil_div(s.n_ctx, s.block);
   LayerWs w;
   w.sc = ws_block_scores(s);
   w.at = ws_attn(s, p);
-  w.attn = ceil_div(s.n_ctx, s.block) > kFusedMaxBlocks ? 0 : w.sc.total;
-  w.total = std::max(w.sc.total, w.attn + w.at.total);
+  w.attn = w.sc.total;
+  const size_t apart = w.attn + w.at.total, shared = std::max(w.sc.total, w.at.total);
+  w.need = n_b > kFusedManyBlocks ? shared : apart;
+  w.total = n_b > kFusedMaxBlocks ? shared : apart;
+  if (w.need <= kStaticScratchBytes && w.total > kStaticScratchBytes) w.total = w.need;  // (what the static call takes shows in the size)
   return w;
 }
 
@@ -325,7 +332,6 @@ static LayerWs ws_layer(const focus_shape& s, const SplitPlan& p) {
 // One array per GPU, resident from the moment the library's code object is loaded on that GPU until the process ends.
 // In host code the array's name is only a stand-in: its device address is looked up once per device with
 // hipGetSymbolAddress and that pointer is what the kernels receive.
-constexpr size_t kStaticScratchBytes = (size_t)8 << 20;
 static __device__ __align__(256) unsigned char g_static_scratch[kStaticScratchBytes];
 constexpr int kMaxDevices = 64;
 static void* g_scratch_addr[kMaxDevices];  // by device ordinal; nullptr = not looked up yet
@@ -365,22 +371,24 @@ static int sparse_layer_impl(const char* who, const void* Q, const int32_t* focu
   const SplitPlan p = plan_attention(*shape, max_active, n_keep, n_sink);
   const LayerWs w = ws_layer(*shape, p);
   if (static_scratch) {  // every argument has been checked by now: look the built-in array up (first call on a device) and use it
-    if (kStaticScratchBytes < w.total)
+    if (kStaticScratchBytes < w.need)
       return fail(FOCUS_EWORKSPACE, "%s: this shape needs %zu bytes of scratch, the built-in array holds %zu; use focus_sparse_layer with a caller workspace",
-                  who, w.total, kStaticScratchBytes);
+                  who, w.need, kStaticScratchBytes);
     if (int rc = static_scratch_ptr(&workspace)) return rc;
     ws_bytes = kStaticScratchBytes;
   }
-  if (!workspace || ws_bytes < w.total || !aligned16(workspace))
-    return fail(FOCUS_EWORKSPACE, "%s: workspace needs %zu bytes, 16-byte aligned", who, w.total);
+  if (!workspace || ws_bytes < w.need || !aligned16(workspace))
+    return fail(FOCUS_EWORKSPACE, "%s: workspace needs %zu bytes, 16-byte aligned", who, w.need);
   hipStream_t st = static_cast<hipStream_t>(stream);
   char* ws = static_cast<char*>(workspace);
+  const bool apart = ws_bytes >= w.attn + w.at.total;  // (else n_b > kFusedManyBlocks)
+  const bool fused = n_b <= (kbar ? kFusedMaxBlocks : kFusedMaxBlocksPerHead) && n_keep > 0 && apart;
+  const size_t attn = apart ? w.attn : 0;
   float* part = reinterpret_cast<float*>(ws + w.sc.part);
   float* R = scores ? scores : reinterpret_cast<float*>(ws + w.sc.scores);
-  float* part_o = reinterpret_cast<float*>(ws + w.attn + w.at.part_o);
-  float* part_ml = reinterpret_cast<float*>(ws + w.attn + w.at.part_ml);
+  float* part_o = reinterpret_cast<float*>(ws + attn + w.at.part_o);
+  float* part_ml = reinterpret_cast<float*>(ws + attn + w.at.part_ml);
   hipError_t e;
-  const bool fused = n_b <= (kbar ? kFusedMaxBlocks : kFusedMaxBlocksPerHead) && n_keep > 0;
   if (!kbar)
     e = launch_block_means_relevance(K, Q, focus_idx, counts, n_focus_max, *shape, nullptr, part, st);
   else

@@ -145,10 +145,11 @@ hipError_t launch_qk_logits(const void* Q, const int32_t* active_idx, const int3
                             float* part_ml, const float* lse2, float* colpart, hipStream_t st, const SelectArgs* select = nullptr);
 // Extra arguments of the fused layer path: the attention kernel ranks the blocks itself from the partial relevances
 // (n_b <= kFusedMaxBlocks; kFusedMaxBlocksPerHead if they come per head from a K scan).  The limits are what the prologues are built
-// for: four keys a thread of four wavefronts, and from a K scan, whose 32 parts per key would be read by every workgroup, one.  Past them
-// a launch of one workgroup ranks the blocks and costs more than the blocks themselves (32 heads, 16 queries, 30 blocks of 64 kept:
-// 1024 blocks 19.3 us, 1025 blocks 35.4, 2048 blocks 39.5); a prologue of eight keys a thread has not been tried.
-constexpr int kFusedMaxBlocks = 1024, kFusedMaxBlocksPerHead = 256;
+// for: one, four or eight keys a thread of four wavefronts, and from a K scan, whose 32 parts per key would be read by every workgroup,
+// one.  Past them a launch of one workgroup ranks the blocks and costs more than the blocks themselves (16 queries,
+// 30 blocks of 64 kept, launch and prologue: 32 heads, 1025 blocks 36.2 and 22.0 us a layer, 2048 blocks 39.8 and 25.1; 4 heads, 2048 blocks
+// 28.8 and 15.5; 1024 blocks with four keys a thread 19.9).
+constexpr int kFusedManyBlocks = 1024, kFusedMaxBlocks = 2048, kFusedMaxBlocksPerHead = 256;
 struct FusedTopC {
   const float* rel_part;  // [ceil(H / 4), n_b] from launch_block_relevance, or with per_head [H, n_b]
   bool per_head;

@@ -509,31 +509,31 @@ __device__ __forceinline__ AttnArgs with_first(AttnArgs p, ATTN_FIRST_PARAMS) {
 // R_b = (1 / (|I_focus| H)) sum_h qsum^h . kbar^h_b, then Top-C into kept_sh; the workgroup with `writer` set also writes scores
 // and kept blocks out.  First use of `sm`.  Thread t of THREADS ranks the blocks t, t + THREADS, ...; n_b <= kFusedMaxBlocks.
 // FirstParts holds the loads of the first NP parts (32 heads in groups of four are 8 parts), which the caller requests before it
-// waits for anything.  MANY: n_b > 256.  Few blocks to keep of up to 256: the tournament of block_topk_small; else
+// waits for anything.  BLOCKS: the most blocks of the variant, 256, kFusedManyBlocks or kFusedMaxBlocks.  Few blocks to keep of up to 256: the tournament of block_topk_small; else
 // block_topk_planes.  Repeating it in every workgroup takes less time than the launch of a kernel that ranks the blocks once
 // (sparse layer at 128K, 30 of 1024 blocks, 34.7 -> 29.0 us; half of 512 64-row blocks 63.2 -> 60.1).
-template <int NP, int THREADS, bool MANY>
+template <int NP, int THREADS, int BLOCKS>
 struct FirstParts {
-  static constexpr int kPlanes = MANY ? kFusedMaxBlocks / THREADS : 1;
+  static constexpr int kPlanes = BLOCKS > 256 ? BLOCKS / THREADS : 1;
   float part[kPlanes][NP];
 };
-template <int NP, int THREADS, bool MANY>
-__device__ __forceinline__ void first_partials(FirstParts<NP, THREADS, MANY>& f, const AttnArgs& p, bool per_head) {
+template <int NP, int THREADS, int BLOCKS>
+__device__ __forceinline__ void first_partials(FirstParts<NP, THREADS, BLOCKS>& f, const AttnArgs& p, bool per_head) {
   const int last = (per_head ? p.H : (p.H + kRelGroup - 1) / kRelGroup) - 1;
 #pragma unroll
   for (int l = 0; l < f.kPlanes; ++l) {
-    const uint32_t b = min((int)threadIdx.x + l * THREADS, p.n_b - 1);  // n_b <= 1024: small offsets
+    const uint32_t b = min((int)threadIdx.x + l * THREADS, p.n_b - 1);  // n_b <= kFusedMaxBlocks: small offsets
 #pragma unroll
     for (int i = 0; i < NP; ++i) f.part[l][i] = p.rel_part[(uint32_t)(min(i, last) * p.n_b) + b];
   }
   __builtin_amdgcn_sched_barrier(0);  // (the scheduler would move the wait for the row ids in front of these loads)
 }
-template <int NP, int THREADS, bool MANY>
-__device__ __forceinline__ void rank_blocks(const AttnArgs& p, const FirstParts<NP, THREADS, MANY>& f, bool per_head, int n_focus,
+template <int NP, int THREADS, int BLOCKS>
+__device__ __forceinline__ void rank_blocks(const AttnArgs& p, const FirstParts<NP, THREADS, BLOCKS>& f, bool per_head, int n_focus,
                                             int32_t* kept_sh, TopkShared& sm, bool writer) {
-  constexpr int kPlanes = FirstParts<NP, THREADS, MANY>::kPlanes;
+  constexpr int kPlanes = FirstParts<NP, THREADS, BLOCKS>::kPlanes;
   const int tid = threadIdx.x;
-  const bool tournament = !MANY && p.n_keep * (THREADS / kWave) <= kWave;  // uniform
+  const bool tournament = BLOCKS <= 256 && p.n_keep * (THREADS / kWave) <= kWave;  // uniform
   if (!tournament) {
     block_topk_clear<THREADS>(sm);
     __syncthreads();
@@ -666,7 +666,7 @@ __global__ __launch_bounds__(256, (FUSE & 2) == 0 ? 2 : 1) void sparse_attn_kern
   constexpr bool PIPE = (FUSE & 2) != 0;                 // two K/V stages per wavefront
   constexpr bool SPILL = (FUSE & 4) != 0;                // dense: also write the scaled logits (sink scoring)
   constexpr bool PER_HEAD = (FUSE & 8) != 0;             // FUSED: partial relevances per head, not per group of heads
-  constexpr bool MANY = (FUSE & 16) != 0;                // FUSED: more than 256 blocks
+  constexpr int BLOCKS = (FUSE & 32) != 0 ? kFusedMaxBlocks : ((FUSE & 16) != 0 ? kFusedManyBlocks : 256);  // FUSED: the most blocks to rank
   constexpr int kBufBytes = 2 * G::kStageBytes;          // one slot: K stage + V stage of a sub-tile
   static_assert(16 * D * 4 <= kBufBytes, "a wavefront's O tile fits its stage");
   // Two buffers of four slots; the second exists in the double-buffered variant only.
@@ -687,7 +687,7 @@ __global__ __launch_bounds__(256, (FUSE & 2) == 0 ? 2 : 1) void sparse_attn_kern
 
   __shared__ __attribute__((aligned(16))) char topk_raw[FUSED ? sizeof(TopkShared) : 16];
   TopkShared& topk_sm = *reinterpret_cast<TopkShared*>(topk_raw);
-  __shared__ int32_t kept_sh[MANY ? kFusedMaxBlocks : (FUSED ? 256 : 1)];
+  __shared__ int32_t kept_sh[FUSED ? BLOCKS : 1];
   const int32_t* kept_blocks = p.kept_blocks;
   // With the Top-C prologue ahead, the query rows are requested before it (their two round trips — row ids, then rows —
   // pass while the relevances are summed and ranked); without it they follow the first K/V requests (see below).
@@ -695,7 +695,7 @@ __global__ __launch_bounds__(256, (FUSE & 2) == 0 ? 2 : 1) void sparse_attn_kern
   int qrow_early = -1, few_sinks = -1;
   if (FUSED) {
     qrow_early = fetch_q_row(p.active_idx, 0, p.max_active, p.n_gen, lane);
-    FirstParts<PER_HEAD ? 32 : 8, 256, MANY> first;
+    FirstParts<PER_HEAD ? 32 : 8, 256, BLOCKS> first;
     first_partials(first, p, PER_HEAD);
     few_sinks = request_few_sinks(p, lane);
     load_q_tile<D>(q, Qh, p.qsn, qrow_early, lane);
@@ -959,7 +959,8 @@ __device__ __forceinline__ void store_o_tile(char* dst, const floatx16 (&o)[D / 
 // slot, the next sub-tile's rows travel while the current one is multiplied, one workgroup per compute unit; without it (NT =
 // 1) the operands are all read into registers before the next sub-tile is requested into the same stage, and two workgroups
 // per compute unit cover each other: better where several query groups share rows in the L2 and the loads return fast.
-// Bit 3: the rows are read by several query groups and should stay in the L2.  Bit 4 (with bit 0): more than 256 blocks to rank.
+// Bit 3: the rows are read by several query groups and should stay in the L2.  Bits 4 and 5 (with bit 0): more than 256 blocks to rank, up to
+// kFusedManyBlocks or kFusedMaxBlocks.
 // Bound by HBM.  32 heads, 32 832 keys, all kept: 89 us with 30 queries (6.0 TB/s; 16-query tiles on shared sub-tiles took 94),
 // 95 us with 60 (101); half of the 64-row blocks and 327 sinks: 53 us (57); 4 K/V heads, 196 queries, 16 640 keys: 28 us (42).
 // Grid: one list (list_index).  Workgroups go to the XCDs round-robin, so the query groups of one (head, key split) pair are
@@ -969,7 +970,8 @@ __global__ __launch_bounds__(256 * NT, NT == 2 || (MODE & 4) == 0 ? 2 : 1) void 
   AttnArgs p = with_first(args, rel_part, active_idx, Q, counts, n_b, H, max_active, args.n_gen, n_split, n_sub);
   p.q_groups = q_groups;
   using G = Geo<D>;
-  constexpr bool FUSED = (MODE & 1) != 0, PIPE = (MODE & 2) != 0, DOUBLE = (MODE & 4) != 0, MANY = (MODE & 16) != 0;
+  constexpr bool FUSED = (MODE & 1) != 0, PIPE = (MODE & 2) != 0, DOUBLE = (MODE & 4) != 0;
+  constexpr int BLOCKS = (MODE & 32) != 0 ? kFusedMaxBlocks : ((MODE & 16) != 0 ? kFusedManyBlocks : 256);
   static_assert(!DOUBLE || PIPE, "two stages are for the key loop");
   static_assert(NT == 1 || DOUBLE || !PIPE, "a shared slot needs the second stage");
   constexpr int kPolicy = (MODE & 8) != 0 ? 0 : kStreamPolicy;
@@ -981,7 +983,7 @@ __global__ __launch_bounds__(256 * NT, NT == 2 || (MODE & 4) == 0 ? 2 : 1) void 
   __shared__ __attribute__((aligned(16))) char ldsB[DOUBLE ? kWavesPerGroup * kBufBytes : 16];
   __shared__ float2 ml_sh[kWavesPerGroup][32];
   __shared__ __attribute__((aligned(16))) char topk_raw[FUSED ? sizeof(TopkShared) : 16];
-  __shared__ int32_t kept_sh[MANY ? kFusedMaxBlocks : (FUSED ? 256 : 1)];
+  __shared__ int32_t kept_sh[FUSED ? BLOCKS : 1];
   __shared__ uint32_t kept_bits_sh[kBitmapBlocks / 32];
   __shared__ int sinks_unsorted_sh;
 
@@ -1015,7 +1017,7 @@ __global__ __launch_bounds__(256 * NT, NT == 2 || (MODE & 4) == 0 ? 2 : 1) void 
   const int32_t* kept_blocks = p.kept_blocks;
   int few_sinks;
   if (FUSED) {  // the query rows travel while the blocks are ranked
-    FirstParts<8, 256 * NT, MANY> first;  // (per head, from a K scan: the other parts are requested when they are added)
+    FirstParts<8, 256 * NT, BLOCKS> first;  // (per head, from a K scan: the other parts are requested when they are added)
     first_partials(first, p, p.rel_per_head);
     few_sinks = request_few_sinks(p, lane);
     if (qg > 0 && qg * NT * 32 >= counted.n_active(p)) return;  // a query group past the device-side count has nothing to do
@@ -1258,8 +1260,12 @@ template <int D, int NT, int LOOP>
 static void launch_wide_t(const AttnArgs& a, const SplitPlan& p, bool fused, hipStream_t st) {
   const dim3 grid = grid_list(query_group_list(p, a.H)), block(256 * NT);
   constexpr int kKeep = LOOP & 8;
-  const bool many = a.n_b > 256;
-  if (fused && p.pipelined && many)
+  const bool many = a.n_b > 256, most = a.n_b > kFusedManyBlocks;
+  if (fused && p.pipelined && most)
+    WIDE_LAUNCH((wide_attn_kernel<D, NT, LOOP | 33>), grid, block, st, a);
+  else if (fused && most)
+    WIDE_LAUNCH((wide_attn_kernel<D, NT, kKeep | 33>), grid, block, st, a);
+  else if (fused && p.pipelined && many)
     WIDE_LAUNCH((wide_attn_kernel<D, NT, LOOP | 17>), grid, block, st, a);
   else if (fused && many)
     WIDE_LAUNCH((wide_attn_kernel<D, NT, kKeep | 17>), grid, block, st, a);
@@ -1292,7 +1298,11 @@ static hipError_t launch_attn_t(const AttnArgs& a, const SplitPlan& p, bool fuse
       ATTN_LAUNCH((sparse_attn_kernel<D, 6>), grid, block, st, a);
     else
       ATTN_LAUNCH((sparse_attn_kernel<D, 4>), grid, block, st, a);
-  } else if (fused && p.pipelined && a.n_b > 256)
+  } else if (fused && p.pipelined && a.n_b > kFusedManyBlocks)
+    ATTN_LAUNCH((sparse_attn_kernel<D, 35>), grid, block, st, a);
+  else if (fused && a.n_b > kFusedManyBlocks)
+    ATTN_LAUNCH((sparse_attn_kernel<D, 33>), grid, block, st, a);
+  else if (fused && p.pipelined && a.n_b > 256)
     ATTN_LAUNCH((sparse_attn_kernel<D, 19>), grid, block, st, a);
   else if (fused && a.n_b > 256)
     ATTN_LAUNCH((sparse_attn_kernel<D, 17>), grid, block, st, a);

@@ -17,7 +17,7 @@
 //                     keys equal to T are still needed; an ordered compaction then emits every key > T and the
 //                     first needed keys == T in index order.  Runs longer than 32 keys per thread re-read
 //                     memory in every pass.
-//   * up to 1024 keys in registers, a few per thread of 4 or 8 wavefronts: a radix search of the k-th largest key with an
+//   * up to 2048 keys in registers, up to eight per thread of 4 or 8 wavefronts: a radix search of the k-th largest key with an
 //                     LDS histogram per pass, which every wavefront scans by itself (block_topk_planes).
 // Many sinks go through sink_rank_kernel (focus_small.hip), which shares radix_digit.
 // All are deterministic: nothing depends on the order in which atomics land.

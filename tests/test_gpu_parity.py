@@ -240,7 +240,7 @@ def test_select_and_find_sinks_equals_the_two_calls(G, n_gen, k, window, lo, hi,
 
 @pytest.mark.parametrize("d", [64, 128])
 def test_select_and_find_sinks_with_logits_past_the_memory_side_cache(G, d):
-    """More than 200 MB of spilled logits, written non-temporally, with the selection in the same launch: the two calls' results bit
+    """More than 200 MB of spilled logits, read back non-temporally, with the selection in the same launch: the two calls' results bit
     for bit, and column masses that agree with fp64."""
     H, M, N, n_gen, k, n_sink = 32, 102500, 37, 48, 13, 5
     L = M + N
@@ -664,7 +664,7 @@ def test_probe_layer(G, H, M, N, d, B, n_gen, n_act, n_sink):
     (2, 8192, 64, 128, 16, 64, 16, 16, 40, 4),        # 512 blocks
     (2, 16385, 64, 64, 64, 64, 16, 16, 30, 4),        # one block more than a workgroup has threads
     (2, 8208, 0, 64, 16, 64, 4, 50, 257, 40),         # 513 blocks, two query tiles per slot
-    (1, 16384, 64, 128, 16, 64, 4, 20, 1024, 5),      # the most blocks that are ranked inside the attention kernel, all kept
+    (1, 16384, 64, 128, 16, 64, 4, 20, 1024, 5),      # the most blocks with four keys per thread of the ranking, all kept
     (5, 16384, 7, 64, 16, 64, 9, 30, 500, 90),
     (2, 16400, 64, 64, 16, 64, 9, 30, 11, 3),         # ... and one more
     (2, 2048, 0, 64, 128, 16, 3, 16, 16, 0),          # every block kept, no response rows, no sinks
@@ -694,6 +694,40 @@ def test_sparse_layer_equals_block_scores_then_sparse_attn(G, H, M, N, d, B, n_g
                          [] if sinks is None else sinks.cpu().numpy(), M, B, n_keep)
     assert kept.cpu().tolist() == lay["blocks"].tolist()
     G.assert_attention_close(out, lay["out"])
+
+
+@pytest.mark.parametrize("H,M,N,d,B,n_act,n_keep,n_sink", [
+    (2, 1025, 64, 128, 1, 16, 30, 4),       # one block more than four keys per thread
+    (9, 32768, 33, 64, 16, 16, 7, 3),       # 2048 blocks, the most; two groups of heads, one with one head
+    (2, 2048, 5, 64, 1, 40, 2048, 0),       # ... all kept, two query tiles of 32
+    (3, 24001, 40, 128, 16, 24, 900, 240),  # 1501 blocks, one tile of 32, a key loop
+    (40, 1700, 16, 128, 1, 16, 1600, 17),   # ten groups of heads: more parts than are requested first
+    (2, 1100, 16, 64, 1, 70, 300, 33),      # several query groups
+    (2, 2049, 64, 128, 1, 16, 30, 4),       # one more than the most: a launch ranks them
+])
+def test_sparse_layer_of_many_blocks(G, H, M, N, d, B, n_act, n_keep, n_sink):
+    """Ranked inside the attention kernel or, with the least workspace, by a launch of its own: the same as the separate calls."""
+    rng, n_gen = np.random.default_rng(M), 80
+    q, k, v = (_rand_bf16(91 + i, H, r, d).to(G.DEV) for i, r in enumerate((n_gen, M + N, M + N)))
+    k[:, 3 * B:4 * B] = k[:, 7 * B:8 * B]                   # equal relevances: ties go to the lower block
+    focus, active = (G.i32(np.sort(rng.choice(n_gen, n, replace=False))) for n in (9, n_act))
+    sinks = G.i32(rng.choice(M, n_sink, replace=False)) if n_sink else None
+    counts = G.i32([9, n_act])
+    scores, kept = G.gpu_block_scores(q, focus, counts, k, None, M, B, n_keep)
+    out, lse = G.gpu_sparse_attn(q, active, counts, k, v, M, B, kept, sinks)
+    kbar = G.gpu_block_means(k, M, B)
+    o2 = torch.empty_like(out)
+    s = fb.make_shape(q, k, v, M, B, o2)
+    least = max(fb.workspace_bytes(fb.FN_BLOCK_SCORES, s), fb.workspace_bytes(fb.FN_SPARSE_ATTN, s, n_act, n_keep, n_sink))
+    full = fb.workspace_bytes(fb.FN_SPARSE_LAYER, s, n_act, n_keep, n_sink)
+    assert full >= least
+    for nbytes in (full, least, full):
+        s2, k2, l2 = torch.full_like(scores, -1.0), torch.full_like(kept, -9), torch.empty_like(lse)
+        o2.fill_(7.0)
+        fb.sparse_layer(q, focus, active, counts, k, v, kbar, s, n_keep, sinks, n_sink, s2, k2, o2, l2, G.ws(nbytes))
+        torch.cuda.synchronize()
+        assert torch.equal(s2, scores) and torch.equal(k2, kept)
+        assert torch.equal(o2, out) and torch.equal(l2, lse)
 
 
 # ------------------------------------------------------------------------------------------------ whole layer on the workloads
