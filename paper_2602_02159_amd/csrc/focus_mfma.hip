@@ -961,8 +961,8 @@ __device__ __forceinline__ void store_o_tile(char* dst, const floatx16 (&o)[D / 
 // per compute unit cover each other: better where several query groups share rows in the L2 and the loads return fast.
 // Bit 3: the rows are read by several query groups and should stay in the L2.  Bits 4 and 5 (with bit 0): more than 256 blocks to rank, up to
 // kFusedManyBlocks or kFusedMaxBlocks.
-// Bound by HBM.  32 heads, 32 832 keys, all kept: 89 us with 30 queries (6.0 TB/s; 16-query tiles on shared sub-tiles took 94),
-// 95 us with 60 (101); half of the 64-row blocks and 327 sinks: 53 us (57); 4 K/V heads, 196 queries, 16 640 keys: 28 us (42).
+// Bound by HBM.  32 heads, 32 832 keys, all kept: 87 us with 28 queries (6.2 TB/s; 16-query tiles on shared sub-tiles took 94),
+// 93 us with 64 (101); half of the 64-row blocks and 327 sinks: 51 us (57); 4 K/V heads, 196 queries, 16 640 keys: 28 us (42).
 // Grid: one list (list_index).  Workgroups go to the XCDs round-robin, so the query groups of one (head, key split) pair are
 // placed eight apart: they run on the same XCD at about the same time and its L2 serves their common K/V rows.
 template <int D, int NT, int MODE>
