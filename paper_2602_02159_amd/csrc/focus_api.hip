@@ -31,10 +31,12 @@ static inline size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 // Launch shapes (workgroups per launch the key axis is cut for).  Fixed constants: split counts decide workspace
 // sizes and the order in which partial results are merged, so they must not vary between calls.
 constexpr int kAttnGroups = 512;      // one sub-tile per slot: every workgroup resident at once, two per compute unit
-// d = 64, up to 16 queries: half the LDS and few registers, twice as many are resident.  One sub-tile per wavefront up to 128 a head
-// (32 heads, 67 sub-tiles 15.5 -> 13.9 us per layer, 123 17.1 -> 15.4), then two workgroups per compute unit (131 17.9 -> 16.7, 259
-// 23.2 -> 21.8, 1026 51.7 -> 46.5), as long as no more than 64 partial results per row come of it: merging them costs a memory round
-// trip for every 64 (4 heads, 1004 sub-tiles: 18.4 us in 64 splits, 23.6 in 251).  32-query tiles (24 queries) gain at 67 sub-tiles
+// d = 64, up to 16 queries: half the LDS and few registers, twice as many are resident (four per compute unit without a key loop, whatever
+// number of blocks they rank: at most 40 548 bytes, which the kernel asserts; two with one).  One sub-tile per wavefront up to 128 a head
+// (32 heads, whole layer against 512 workgroups, 256 blocks to rank: 67 sub-tiles 15.5 -> 13.9 us, 123 17.1 -> 15.4; 512 blocks: 65
+// sub-tiles 16.8 -> 15.1, 97 18.2 -> 16.5, 127 19.4 -> 18.1; 2048 blocks: 65 21.6 -> 20.7, 97 23.1 -> 22.6, 127 23.6 and 23.6), then two
+// workgroups per compute unit (131 17.9 -> 16.7, 259 23.2 -> 21.8, 1026 51.7 -> 46.5), as long as no more than 64 partial results per row
+// come of it: merging them costs a memory round trip for every 64 (4 heads, 1004 sub-tiles: 18.4 us in 64 splits, 23.6 in 251).  32-query tiles (24 queries) gain at 67 sub-tiles
 // only (16.6 -> 15.4) and lose from 91 on; nor does the probe layer gain, whose kernel also writes its logits (1026 sub-tiles 80.0 ->
 // 80.7).
 constexpr int kAttnGroupsSmall = 1024, kAttnGroupsSmallPipe = 512, kAttnSplitsSmall = 64;

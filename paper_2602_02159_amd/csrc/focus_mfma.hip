@@ -109,8 +109,10 @@ __device__ __forceinline__ int32_t uniform_load(const int32_t* ptr) {
   typedef const __attribute__((address_space(4))) int32_t* cptr_t;
   return *(cptr_t)(uintptr_t)ptr;
 }
+__device__ __forceinline__ int32_t uniform_load(const uint16_t* ptr) { return *ptr; }  // (lists of 16 bits lie in LDS: KeptList)
+template <class Id>
 __device__ __forceinline__ SubTile locate_subtile(int st, int lane, int M, int N, int B, int n_b, int sub_per_block,
-                                                  const int32_t* __restrict__ kept_blocks, int n_keep,
+                                                  const Id* __restrict__ kept_blocks, int n_keep,
                                                   const int32_t* __restrict__ sink_idx, int n_sink,
                                                   const uint32_t* kept_bits = nullptr, int ascending = -1,
                                                   int dense_rows = 0, bool blocks_in_lds = false, int few_sinks = -1) {
@@ -505,6 +507,25 @@ __device__ __forceinline__ AttnArgs with_first(AttnArgs p, ATTN_FIRST_PARAMS) {
   hipLaunchKernelGGL(kernel, grid, block, 0, st, (a).rel_part, (a).active_idx, (a).Q, (a).counts, (a).n_b, (a).rel_per_head ? -(a).H : (a).H, (a).max_active, \
                      (a).n_gen, (a).n_split, (a).n_sub, a)
 
+// Where a workgroup that ranks the blocks itself keeps the list.  Up to 256 blocks: beside the ranking's scratch memory.  More: in 16 bits
+// per block, in the place of the histograms, which everyone has read by then; beside them and in 32 bits a workgroup of
+// sparse_attn_kernel<64, .> without a key loop took 43 620 bytes (up to 1024 blocks) and 47 716 (2048), and of the four that the plan
+// of the key splits counts on per compute unit (kAttnGroupsSmall) three fitted (32 heads, d = 64, whole layer: 512 blocks, 97 sub-tiles
+// 20.4 -> 16.5 us, 127 21.7 -> 18.1; 2048 blocks 27.9 -> 22.6, 29.3 -> 23.6).
+template <bool FUSED, int BLOCKS>
+struct KeptList {
+  static constexpr bool kInScratch = FUSED && BLOCKS > 256;
+  using Id = std::conditional_t<kInScratch, uint16_t, int32_t>;
+  static constexpr int kEntriesBeside = FUSED && !kInScratch ? BLOCKS : 1;
+  static_assert(!kInScratch || BLOCKS * sizeof(Id) <= sizeof(TopkShared::keys), "fits the histograms");
+  static __device__ __forceinline__ Id* place(char* scratch, int32_t* beside) {
+    if constexpr (kInScratch)
+      return reinterpret_cast<Id*>(reinterpret_cast<TopkShared*>(scratch)->keys);
+    else
+      return beside;
+  }
+};
+
 // What the attention kernels prepare before their first K/V request.
 // R_b = (1 / (|I_focus| H)) sum_h qsum^h . kbar^h_b, then Top-C into kept_sh; the workgroup with `writer` set also writes scores
 // and kept blocks out.  First use of `sm`.  Thread t of THREADS ranks the blocks t, t + THREADS, ...; n_b <= kFusedMaxBlocks.
@@ -530,7 +551,7 @@ __device__ __forceinline__ void first_partials(FirstParts<NP, THREADS, BLOCKS>& 
 }
 template <int NP, int THREADS, int BLOCKS>
 __device__ __forceinline__ void rank_blocks(const AttnArgs& p, const FirstParts<NP, THREADS, BLOCKS>& f, bool per_head, int n_focus,
-                                            int32_t* kept_sh, TopkShared& sm, bool writer) {
+                                            typename KeptList<true, BLOCKS>::Id* kept_sh, TopkShared& sm, bool writer) {
   constexpr int kPlanes = FirstParts<NP, THREADS, BLOCKS>::kPlanes;
   const int tid = threadIdx.x;
   const bool tournament = BLOCKS <= 256 && p.n_keep * (THREADS / kWave) <= kWave;  // uniform
@@ -569,7 +590,7 @@ __device__ __forceinline__ void rank_blocks(const AttnArgs& p, const FirstParts<
       key = order_key(rel[0]);
       return true;
     };
-    block_topk_small<256, true>(keyfn, p.n_b, p.n_keep, kept_sh, nullptr, sm);
+    if constexpr (BLOCKS <= 256) block_topk_small<256, true>(keyfn, p.n_b, p.n_keep, kept_sh, nullptr, sm);
   } else {
     uint32_t key1[kPlanes];
 #pragma unroll
@@ -590,7 +611,8 @@ struct SinkUnion {
   const uint32_t* kept_bits;  // see locate_subtile; null when there is none
   int ascending;
 };
-__device__ __forceinline__ SinkUnion prepare_union(const AttnArgs& p, int split, const int32_t* kept_blocks, uint32_t* bits_sh,
+template <class Id>
+__device__ __forceinline__ SinkUnion prepare_union(const AttnArgs& p, int split, const Id* kept_blocks, uint32_t* bits_sh,
                                                    int* unsorted_sh) {
   SinkUnion u;
   u.kept_bits = nullptr;
@@ -687,8 +709,11 @@ __global__ __launch_bounds__(256, (FUSE & 2) == 0 ? 2 : 1) void sparse_attn_kern
 
   __shared__ __attribute__((aligned(16))) char topk_raw[FUSED ? sizeof(TopkShared) : 16];
   TopkShared& topk_sm = *reinterpret_cast<TopkShared*>(topk_raw);
-  __shared__ int32_t kept_sh[FUSED ? BLOCKS : 1];
-  const int32_t* kept_blocks = p.kept_blocks;
+  using Kept = KeptList<FUSED, BLOCKS>;
+  __shared__ int32_t kept_beside[Kept::kEntriesBeside];
+  typename Kept::Id* kept_sh = Kept::place(topk_raw, kept_beside);
+  const typename Kept::Id* kept_blocks = kept_sh;
+  if constexpr (!FUSED) kept_blocks = p.kept_blocks;
   // With the Top-C prologue ahead, the query rows are requested before it (their two round trips — row ids, then rows —
   // pass while the relevances are summed and ranked); without it they follow the first K/V requests (see below).
   bf16x8 q[G::kKSteps];
@@ -700,12 +725,14 @@ __global__ __launch_bounds__(256, (FUSE & 2) == 0 ? 2 : 1) void sparse_attn_kern
     few_sinks = request_few_sinks(p, lane);
     load_q_tile<D>(q, Qh, p.qsn, qrow_early, lane);
     rank_blocks(p, first, PER_HEAD, counted.focus, kept_sh, topk_sm, blockIdx.x == 0 && blockIdx.y == 0);
-    kept_blocks = kept_sh;
   } else {
     few_sinks = request_few_sinks(p, lane);
   }
   __shared__ uint32_t kept_bits_sh[kBitmapBlocks / 32];
   __shared__ int sinks_unsorted_sh;
+  static_assert(D == 128 || PIPE ||
+                    4 * (sizeof(ldsA) + sizeof(ldsB) + sizeof(ml_sh) + sizeof(topk_raw) + sizeof(kept_beside) + sizeof(kept_bits_sh) + 16) <= 163840,
+                "four workgroups share a compute unit (kAttnGroupsSmall)");
   const SinkUnion uni = prepare_union(p, split, kept_blocks, kept_bits_sh, &sinks_unsorted_sh);
   const uint32_t* kept_bits = uni.kept_bits;
   const int sinks_ascending = uni.ascending;
@@ -983,7 +1010,8 @@ __global__ __launch_bounds__(256 * NT, NT == 2 || (MODE & 4) == 0 ? 2 : 1) void 
   __shared__ __attribute__((aligned(16))) char ldsB[DOUBLE ? kWavesPerGroup * kBufBytes : 16];
   __shared__ float2 ml_sh[kWavesPerGroup][32];
   __shared__ __attribute__((aligned(16))) char topk_raw[FUSED ? sizeof(TopkShared) : 16];
-  __shared__ int32_t kept_sh[FUSED ? BLOCKS : 1];
+  using Kept = KeptList<FUSED, BLOCKS>;
+  __shared__ int32_t kept_beside[Kept::kEntriesBeside];
   __shared__ uint32_t kept_bits_sh[kBitmapBlocks / 32];
   __shared__ int sinks_unsorted_sh;
 
@@ -1014,7 +1042,9 @@ __global__ __launch_bounds__(256 * NT, NT == 2 || (MODE & 4) == 0 ? 2 : 1) void 
 #pragma unroll
     for (int ks = 0; ks < kKS; ++ks) q[ks] = as_bf16x8(*reinterpret_cast<const uint4*>(src + ks * 16));
   };
-  const int32_t* kept_blocks = p.kept_blocks;
+  typename Kept::Id* kept_sh = Kept::place(topk_raw, kept_beside);
+  const typename Kept::Id* kept_blocks = kept_sh;
+  if constexpr (!FUSED) kept_blocks = p.kept_blocks;
   int few_sinks;
   if (FUSED) {  // the query rows travel while the blocks are ranked
     FirstParts<8, 256 * NT, BLOCKS> first;  // (per head, from a K scan: the other parts are requested when they are added)
@@ -1023,7 +1053,6 @@ __global__ __launch_bounds__(256 * NT, NT == 2 || (MODE & 4) == 0 ? 2 : 1) void 
     if (qg > 0 && qg * NT * 32 >= counted.n_active(p)) return;  // a query group past the device-side count has nothing to do
     load_q();
     rank_blocks(p, first, p.rel_per_head, counted.focus, kept_sh, *reinterpret_cast<TopkShared*>(topk_raw), pair == 0 && qg == 0);
-    kept_blocks = kept_sh;
   } else {
     few_sinks = request_few_sinks(p, lane);
     if (qg > 0 && qg * NT * 32 >= counted.n_active(p)) return;

@@ -251,14 +251,15 @@ __device__ __forceinline__ RadixDigit radix_digit(const uint32_t* hist, uint32_t
 // n), same order and tie rule as wave_topk, by a workgroup of 4 or 8 wavefronts: a radix search of the k-th largest key, eight
 // bits per pass.  A pass is one LDS atomic per key and one barrier; every wavefront then scans the 256 counts by itself, four per
 // lane.  It ends as soon as exactly k keys reach a digit, after two passes as a rule.  Writes out[0 .. k) ascending, tail -1.
-// `sm.keys` must have been zeroed (block_topk_clear, visible after a barrier); ends with a barrier.
+// `sm.keys` must have been zeroed (block_topk_clear, visible after a barrier); ends with a barrier.  `out` may lie over sm.keys: between the
+// last look at a histogram and the first entry of the list there is a barrier.  (Entries of 16 bits: 65535 instead of -1.)
 template <int THREADS>
 __device__ __forceinline__ void block_topk_clear(TopkShared& sm) {
   static_assert(sizeof(sm.keys) % (16 * THREADS) == 0 || 16 * THREADS > sizeof(sm.keys), "whole vectors");
   if ((int)threadIdx.x * 16 < (int)sizeof(sm.keys)) reinterpret_cast<uint4*>(sm.keys)[threadIdx.x] = make_uint4(0u, 0u, 0u, 0u);
 }
-template <int P, int THREADS>
-__device__ __forceinline__ void block_topk_planes(const uint32_t (&key1)[P], int n, int k_want, int32_t* out, TopkShared& sm) {
+template <int P, int THREADS, class Id>
+__device__ __forceinline__ void block_topk_planes(const uint32_t (&key1)[P], int n, int k_want, Id* out, TopkShared& sm) {
   constexpr int W = THREADS / kWave;
   static_assert(W == 4 || W == 8, "an entry per lane of a DPP half row");
   static_assert(sizeof(sm.keys) == 4 * 256 * sizeof(uint32_t), "a histogram per pass");
@@ -315,9 +316,9 @@ __device__ __forceinline__ void block_topk_planes(const uint32_t (&key1)[P], int
   for (int i = 0; i < P; ++i) {
     const uint32_t eq_rank = eq_base[i] + (uint32_t)__popcll(eq[i] & below);
     if (key1[i] > T || (key1[i] == T && key1[i] != 0u && eq_rank < need))
-      out[gt_base[i] + (uint32_t)__popcll(gt[i] & below) + min(eq_rank, need)] = i * THREADS + tid;
+      out[gt_base[i] + (uint32_t)__popcll(gt[i] & below) + min(eq_rank, need)] = (Id)(i * THREADS + tid);
   }
-  for (int i = (int)k + tid; i < k_want; i += THREADS) out[i] = -1;
+  for (int i = (int)k + tid; i < k_want; i += THREADS) out[i] = (Id)-1;
   __syncthreads();
 }
 

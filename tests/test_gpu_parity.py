@@ -672,6 +672,12 @@ def test_probe_layer(G, H, M, N, d, B, n_gen, n_act, n_sink):
     (4, 2048, 32, 64, 32, 80, 8, 72, 30, 40),         # five query tiles (two groups of four), d = 64, unsorted sinks
     (3, 1500, 10, 64, 50, 40, 4, 20, 12, 33),         # two query tiles, d = 64, ragged blocks
     (2, 16384, 64, 128, 64, 64, 4, 36, 128, 163),     # the paper's proportions at 16K: half the blocks, 1 % sinks
+    (32, 4096, 64, 64, 16, 64, 16, 16, 64, 4),        # d = 64, 256 blocks: 17 splits of four sub-tiles
+    (16, 4096, 30, 64, 16, 64, 8, 16, 250, 4),        # 63 splits
+    (32, 16384, 64, 64, 16, 64, 4, 16, 125, 4),       # 1024 blocks: 32 splits; the list lies over the histograms, as in the next three
+    (32, 4112, 64, 64, 16, 64, 16, 9, 94, 40),        # 257 blocks, 25 splits, two sub-tiles of sinks
+    (32, 32768, 33, 64, 16, 64, 8, 11, 124, 3),       # 2048 blocks: 32 splits
+    (3, 32768, 5, 64, 16, 64, 5, 16, 2048, 35),       # all of them kept: the whole place is in use, key loop
     (37, 1000, 8, 128, 64, 100, 90, 10, 5, 3),        # more than eight groups of heads, more than 64 focus rows
     (33, 2000, 8, 64, 64, 100, 33, 40, 5, 3),
 ])
