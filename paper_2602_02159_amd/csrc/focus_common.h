@@ -168,7 +168,9 @@ __device__ __forceinline__ void add_splits(RowState& r, const float2 (&v)[N]) {
   r.l = l;
 }
 __device__ __forceinline__ float lse_of(const RowState& r) { return r.l > 0.f ? r.m + __builtin_amdgcn_logf(r.l) : INFINITY; }  // v_log_f32 is log2
-// splits first, first + step, ... of one row, N loads at a time; `row` = its place in the first split, `stride` = rows per split
+// splits first, first + step, ... of one row, N loads at a time; `row` = its place in the first split, `stride` = rows per split.
+// The scheduling fence keeps the loads of a batch together: without it the compiler waited for each of them in the variants of
+// column_mass_kernel that hold few heads, to stay within 64 registers, and a batch was eight memory round trips.
 constexpr int kSplitsInFlight = 8;
 template <int N = kSplitsInFlight>
 __device__ __forceinline__ RowState add_row_splits(const float2* row, int64_t stride, int first, int step, int n_split) {
@@ -179,8 +181,11 @@ __device__ __forceinline__ RowState add_row_splits(const float2* row, int64_t st
     for (int u = 0; u < N; ++u) {
       const int s = s0 + u * step;
       v[u] = row[(int64_t)min(s, n_split - 1) * stride];
-      if (s >= n_split) v[u] = make_float2(-INFINITY, 0.f);
     }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < N; ++u)
+      if (s0 + u * step >= n_split) v[u] = make_float2(-INFINITY, 0.f);
     add_splits(r, v);
   }
   return r;
