@@ -454,10 +454,12 @@ hipError_t launch_lse_combine(const float* part_ml, int H, int q_pad, int n_spli
 //                [head][key quad][query][key within the quad] (fp32) and lse2 their row log-sum-exps [H, 16].  Lane
 //                (query c, quad qd) of wavefront w owns the four keys of quad 4 w + qd for query c: one 16-byte load
 //                per head, the 64 lanes of a load instruction reading 1 KB of consecutive bytes; HEADS heads are in
-//                flight at a time: sixteen, or four or eight where there are just so many (past the last head a load repeats
-//                it: 4 heads, 1056 keys 10.6 -> 10.0 us, 32 832 keys 19.4 -> 18.5; but 3 heads at 16 448 keys 17.1 with
-//                sixteen, 17.8 with four, and 6 heads 21.2 and 22.0 with eight).  It adds exp2(logit - lse) over the heads in
-//                head order; the sixteen queries of a quad are then summed across the lanes of a DPP row (fixed tree).
+//                flight at a time, the smallest of four, eight and sixteen that holds all of them, else sixteen: with fewer in
+//                flight there are fewer registers, so that more workgroups share a compute unit, and less code to fetch (sink chain:
+//                1 head, 1088 keys 10.3 -> 9.3 us, 131 136 keys 34.4 -> 29.0; 3 heads, 16 448 keys 17.3 -> 16.4; 6 heads, 8256 keys
+//                15.7 -> 15.0).  That a load past the last head repeats it costs nothing (1 to 8 heads, up to 32 832 keys: sixteen
+//                in flight with the absent ones left out take as long).  It adds exp2(logit - lse) over the heads in head order; the
+//                sixteen queries of a quad are then summed across the lanes of a DPP row (fixed tree).
 //                PAST_CACHE: more logits than the 256 MB memory-side cache holds beside what else was written, heads in
 //                descending order and without a place in that cache: it has kept the last heads that were written, and reading
 //                the first ones first would displace them (kMemorySideCache).
@@ -672,9 +674,9 @@ hipError_t launch_column_mass(const float* src, bool pre_reduced, const float* l
   if (!lse && n_parts > 8 && (int64_t)n_parts * L * 64 > kMemorySideCache) {
     hipLaunchKernelGGL((column_mass_kernel<false, false, 16, true>), grid, dim3(512), 0, st, src, lse2, counts, max_active, n_parts, H, L,
                        col_mass, M, n_sink, cand, cand_keys, 0);
-  } else if (n_parts == 4) {
+  } else if (n_parts <= 4) {
     COLUMN_MASS(4);
-  } else if (n_parts == 8) {
+  } else if (n_parts <= 8) {
     COLUMN_MASS(8);
   } else {
     COLUMN_MASS(16);

@@ -185,9 +185,12 @@ def test_find_sinks(G, H, M, N, d, n_gen, n_act, n_sink):
     (1, 8192, 64, 128, 16),     # one head: 65 splits, added up by eight threads per row in the column-mass kernel
     (3, 2049, 0, 64, 16),       # 17 splits: one more than two per thread
     (3, 2048, 0, 64, 16),       # 16
-    (4, 3000, 7, 64, 9),        # four heads in flight
-    (8, 3000, 7, 64, 5),        # eight; four threads per row
-    (9, 3000, 7, 64, 16),       # two
+    (4, 3000, 7, 64, 9),        # four heads, all in flight
+    (2, 3000, 7, 64, 16),       # two, with four in flight
+    (5, 3000, 7, 64, 16),       # five, with eight; four threads per row
+    (7, 3000, 7, 128, 16),
+    (8, 3000, 7, 64, 5),        # eight
+    (9, 3000, 7, 64, 16),       # nine, with sixteen; two threads per row
     (31, 600, 3, 64, 7),        # 496 rows: one thread each
     (33, 600, 3, 64, 16),       # 528 rows: two turns
     (64, 1100, 0, 64, 16),      # 1024 rows, the most; four splits
