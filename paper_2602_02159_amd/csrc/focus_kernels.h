@@ -89,7 +89,6 @@ bool sink_tournament_fits(int M, int n_sink);
 // pre_reduced = true:  src = column sums [n_parts, L] from the second pass over K.
 // n_split > 0 (pre_reduced = false): lse2 = the statistics [H, n_split, 16, 2] of the key splits instead of the log-sum-exps
 // [H, 16], which are then formed by the same launch or by one more, into lse_scratch.
-bool lse_fits_column_mass(int H, int n_split);  // formed by the same launch
 hipError_t launch_column_mass(const float* src, bool pre_reduced, const float* lse2, const int32_t* counts, int max_active,
                               int n_parts, int H, int L, float* col_mass, int M, int n_sink, int32_t* cand, uint32_t* cand_keys,
                               int n_split, float* lse_scratch, hipStream_t st);

@@ -473,12 +473,19 @@ hipError_t launch_lse_combine(const float* part_ml, int H, int q_pad, int n_spli
 constexpr int kMassKeys = 128;
 
 // LSE (with PRE = false): lse2 holds the softmax statistics (max, sum) of n_split key splits per row, [H, n_split, 16], instead,
-// and every workgroup forms the log-sum-exps itself, thread = (split lane, row), while its first logits travel: up to kLseRows rows and
-// kLseInMassBytes of statistics that takes no longer than a launch of lse_combine_kernel (sink chain, with that launch and without:
-// 32 heads, 4160 keys, 64 KB: 20.9 and 20.0 us; 8256 keys, 64 KB: 30.0 and 28.9; 128 KB: 29.2 and 29.5; 16 448 keys, 64 KB 47.5 and
-// 47.9; 8 heads, 8256 keys, 32 KB: 16.3 and 15.3; 4 heads, 1056 keys, 5 KB: 14.0 and 12.0).
-constexpr int kLseRows = 1024, kLseInMassBytes = 65536;
-bool lse_fits_column_mass(int H, int n_split) { return H * 16 <= kLseRows && (int64_t)H * 16 * n_split * 8 <= kLseInMassBytes; }
+// and every workgroup forms the log-sum-exps itself, thread = (split lane, row), while its first logits travel.  Every workgroup reads
+// all of the statistics, and what that costs goes with the bytes that all of them together take from the L2s: up to
+// kLseInMassBytes it is no more than a launch of lse_combine_kernel.  Sink chain in us with that launch and without it, bytes in all: 32
+// heads, 4160 keys 21.8 and 20.6 (1.1 MB), 8256 keys 29.6 and 28.8 (4.3 MB), 16 448 keys 45.1 and 48.9 (34 MB); 8 heads, 8256 keys 16.6
+// and 16.4 (2.1 MB), 16 448 21.7 and 21.5 (4.2 MB), 24 640 24.1 and 25.5 (13 MB), 32 832 26.9 and 30.8 (17 MB); 1 head, 8256 keys 12.3
+// and 11.5 (0.5 MB), 24 640 14.6 and 15.1 (4.8 MB), 32 832 15.0 and 16.0 (8.4 MB), 131 136 22.4 and 28.9 (34 MB); 4 heads, 1056 keys
+// 11.8 and 10.2 (0.04 MB).
+constexpr int kLseRows = 1024;
+constexpr int64_t kLseInMassBytes = 5000000;
+static bool lse_in_column_mass(int H, int n_split, int n_workgroups) {
+  const int64_t bytes = (int64_t)H * 16 * n_split * (int64_t)sizeof(float2);
+  return H * 16 <= kLseRows && bytes * n_workgroups <= kLseInMassBytes;
+}
 
 template <bool PRE, bool LSE, int HEADS, bool PAST_CACHE>
 __global__ __launch_bounds__(512) void column_mass_kernel(const float* __restrict__ src, const float* __restrict__ lse2,
@@ -654,7 +661,7 @@ hipError_t launch_column_mass(const float* src, bool pre_reduced, const float* l
                        M, n_sink, cand, cand_keys, 0);
     return hipGetLastError();
   }
-  const bool lse = n_split > 0 && lse_fits_column_mass(H, n_split);
+  const bool lse = n_split > 0 && lse_in_column_mass(H, n_split, (int)grid.x);
   if (n_split > 0 && !lse) {
     const hipError_t e = launch_lse_combine(lse2, H, 16, n_split, lse_scratch, st);
     if (e != hipSuccess) return e;

@@ -194,10 +194,13 @@ def test_find_sinks(G, H, M, N, d, n_gen, n_act, n_sink):
     (31, 600, 3, 64, 7),        # 496 rows: one thread each
     (33, 600, 3, 64, 16),       # 528 rows: two turns
     (64, 1100, 0, 64, 16),      # 1024 rows, the most; four splits
-    (65, 1100, 0, 64, 16),      # one head more: a launch of its own adds the splits up
-    (2, 131072, 0, 64, 16),     # 256 splits: the most statistics
-    (8, 33000, 0, 64, 16),      # the same for eight heads
-    (8, 45000, 0, 64, 16),      # 96 splits: too many
+    (65, 1100, 0, 64, 16),      # one head more: the launch
+    (1, 25216, 0, 64, 16),      # 197 splits, 4.97 MB of statistics read by all workgroups together
+    (1, 25217, 0, 64, 16),      # 198 splits, 5.02 MB: a launch of its own adds the splits up
+    (2, 131072, 0, 64, 16),     # 256 splits
+    (8, 19456, 0, 64, 16),      # 32 splits of eight heads, 4.98 MB
+    (8, 33000, 0, 64, 16),      # 64 splits, 17 MB
+    (8, 45000, 0, 64, 16),      # 96 splits: three batches per thread of the launch
     (32, 8200, 56, 64, 16),     # 65 rounds in 16 splits, one of them with a fifth
     (32, 16400, 0, 64, 16),     # 129 rounds: two each
     (1, 32768, 64, 64, 30),     # two passes, 65 splits: eight threads per row in the second pass
