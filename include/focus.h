@@ -57,7 +57,7 @@ typedef enum focus_status {
   FOCUS_OK = 0,
   FOCUS_EINVAL = -1,       /* a NULL pointer, a size or a count out of range, a misaligned stride */
   FOCUS_EUNSUPPORTED = -2, /* a shape the kernels are not built for (head_dim other than 64 / 128, ...) */
-  FOCUS_EWORKSPACE = -3,   /* workspace NULL or smaller than focus_workspace_bytes() */
+  FOCUS_EWORKSPACE = -3,   /* workspace NULL or too small: see focus_workspace_bytes() */
   FOCUS_ELAUNCH = -4       /* the HIP runtime refused a launch */
 } focus_status;
 
@@ -203,8 +203,8 @@ int focus_sparse_attn(const void* Q, const int32_t* active_idx, const int32_t* c
  * bit-identical outputs (scores, kept_blocks, out, lse), but in three kernel launches instead of four: the
  * attention kernel ranks the blocks itself from the partial relevances instead of waiting for a separate Top-C
  * kernel.  kbar NULL: the first launch scans K and forms the block means on the fly.
- * With more than 2048 prompt blocks (kbar NULL: more than 256), or more than 1024 and less workspace than
- * focus_workspace_bytes says, the call falls back to the separate kernels.
+ * With more than 2048 prompt blocks (kbar NULL: more than 256), or more than 1024 and less workspace than the sum of what
+ * focus_block_scores and focus_sparse_attn need, the call falls back to the separate kernels.
  */
 int focus_sparse_layer(const void* Q, const int32_t* focus_idx, const int32_t* active_idx, const int32_t* counts,
                        int32_t n_focus_max, int32_t max_active, const void* K, const void* V, const float* kbar,
@@ -303,7 +303,18 @@ int focus_block_entry(void* K_cache, void* V_cache, const focus_shape* shape, co
                       const void* V_new, int64_t new_stride_h, int64_t new_stride_n, float* kbar, void* out, float* lse,
                       void* stream);
 
-/* Bytes of workspace `fn` needs for this shape; 0 on invalid arguments.  [host] only. */
+/*
+ * Bytes of workspace `fn` needs for this shape; 0 on invalid arguments.  [host] only.  With less a call is refused
+ * (FOCUS_EWORKSPACE), but for these, which have a slower way that takes less:
+ *  - focus_sparse_attn and focus_sparse_layer, head_dim 64 and up to 16 active queries: down to a quarter; the keys are cut for
+ *    fewer workgroups (the results are equal to rounding, not bit for bit);
+ *  - focus_sparse_layer, more than 1024 blocks: down to the larger of FOCUS_FN_BLOCK_SCORES and FOCUS_FN_SPARSE_ATTN; the blocks
+ *    are ranked by a launch of their own (the same bits).  For 1025 to 2048 blocks whose sum of the two exceeds 8 MiB while the
+ *    larger does not, the larger is also what this function says, so that "at most 8 MiB" stays the condition of
+ *    focus_sparse_layer_static: a caller with a workspace of its own gets the faster way there by handing over that sum (with 256
+ *    bytes to spare);
+ *  - focus_find_sinks and focus_select_and_find_sinks, up to 16 active queries: sometimes one key split less.
+ */
 size_t focus_workspace_bytes(int32_t fn, const focus_shape* shape, int32_t max_active, int32_t n_keep,
                              int32_t n_sink);
 

@@ -71,8 +71,8 @@ static void plan_splits(SplitPlan& p, int n_heads, int q_groups, int target_grou
   p.n_split = std::max(1, std::min(per_head, ceil_div(p.n_sub, kWavesPerGroup)));
 }
 
-static void plan_attention_splits(SplitPlan& p, const focus_shape& s, bool logits_out) {
-  const bool d64 = s.head_dim == 64 && p.q_tiles == 1 && !logits_out;
+static void plan_attention_splits(SplitPlan& p, const focus_shape& s, bool logits_out, bool lean) {
+  const bool d64 = s.head_dim == 64 && p.q_tiles == 1 && !logits_out && !lean;
   auto small = [&](int groups) { return d64 && groups / s.n_heads <= kAttnSplitsSmall; };
   plan_splits(p, s.n_heads, p.q_groups, small(kAttnGroupsSmall) ? kAttnGroupsSmall : kAttnGroups);
   // Many sub-tiles per wavefront (dense layers, alpha = 0.5): fewer, longer workgroups with double-buffered key loops.
@@ -83,11 +83,11 @@ static void plan_attention_splits(SplitPlan& p, const focus_shape& s, bool logit
   }
 }
 
-SplitPlan plan_attention(const focus_shape& s, int max_active, int n_keep, int n_sink) {
+SplitPlan plan_attention(const focus_shape& s, int max_active, int n_keep, int n_sink, bool lean) {
   SplitPlan p;
   plan_queries(p, max_active, max_active <= 64 ? 4 : 2);
   p.n_sub = n_keep * ceil_div(s.block, kSubTile) + ceil_div(s.n_resp, kSubTile) + ceil_div(n_sink, kSubTile);
-  plan_attention_splits(p, s, false);
+  plan_attention_splits(p, s, false, lean);
   return p;
 }
 
@@ -95,16 +95,14 @@ SplitPlan plan_attention_dense(const focus_shape& s, int max_active) {
   SplitPlan p;
   plan_queries(p, max_active, max_active <= 64 ? 4 : 2);
   p.n_sub = ceil_div(s.n_ctx + s.n_resp, kSubTile);
-  plan_attention_splits(p, s, p.q_tiles == 1);
+  plan_attention_splits(p, s, p.q_tiles == 1, false);
   return p;
 }
 
-SplitPlan plan_logits(const focus_shape& s, int max_active) {
+SplitPlan plan_logits(const focus_shape& s, int max_active, bool lean) {
   SplitPlan p;
   plan_queries(p, max_active, kMaxQTilesPerGroup);
   p.n_sub = ceil_div(s.n_ctx + s.n_resp, kSubTile);
-  plan_splits(p, s.n_heads, p.q_groups,
-              p.q_tiles_per_group == 1 ? kLogitGroups : (p.q_tiles_per_group == 2 ? kLogitGroupsTwo : kLogitGroupsMany));
   if (p.q_tiles_per_group == 1) {
     const int rounds = ceil_div(p.n_sub, kWavesPerGroup), step = std::max(1, kLogitGroupsCu / s.n_heads);
     const int n = step * std::max(1, (rounds + step * kLogitRounds / 2) / (step * kLogitRounds));  // the nearest multiple of step
@@ -114,8 +112,10 @@ SplitPlan plan_logits(const focus_shape& s, int max_active) {
     if (groups <= kLogitGroupsResident && !lone_round)
       p.n_split = std::min(rounds, n);
     else  // (one split more than the limit where that saves a lone round)
-      p.n_split = ceil_div(rounds, 2) <= most + 1 ? ceil_div(rounds, 2) : most;
+      p.n_split = ceil_div(rounds, 2) <= most + (lean ? 0 : 1) ? ceil_div(rounds, 2) : most;
+    return p;
   }
+  plan_splits(p, s.n_heads, p.q_groups, p.q_tiles_per_group == 2 ? kLogitGroupsTwo : kLogitGroupsMany);
   if (p.q_tiles_per_group == 2) {
     const int rounds = p.n_sub / kWavesPerGroup;
     p.n_split = std::min(p.n_split, std::max(std::max(1, kLogitGroupsTwoMin / s.n_heads), rounds / kLogitRoundsTwo));
@@ -273,8 +273,9 @@ static int find_sinks_impl(const char* who, const SelectArgs* select, const void
   if (n_sink < 0 || n_sink > shape->n_ctx) return fail(FOCUS_EINVAL, "%s: n_sink=%d not in [0, n_ctx]", who, n_sink);
   if (n_sink > 0 && !sink_idx) return fail(FOCUS_EINVAL, "%s: sink_idx is NULL", who);
   if (!aligned16(Q) || !aligned16(K)) return fail(FOCUS_EINVAL, "%s: pointers must be 16-byte aligned", who);
-  const SplitPlan p = plan_logits(*shape, max_active);
-  const SinkWs w = ws_find_sinks(*shape, p);
+  SplitPlan p = plan_logits(*shape, max_active);
+  SinkWs w = ws_find_sinks(*shape, p);
+  if (ws_bytes < w.total) w = ws_find_sinks(*shape, p = plan_logits(*shape, max_active, true));
   if (!workspace || ws_bytes < w.total || !aligned16(workspace))
     return fail(FOCUS_EWORKSPACE, "%s: workspace needs %zu bytes, 16-byte aligned", who, w.total);
   hipStream_t st = static_cast<hipStream_t>(stream);
@@ -370,8 +371,9 @@ static int sparse_layer_impl(const char* who, const void* Q, const int32_t* focu
   if ((n_keep > 0 && !kept_blocks) || (n_sink > 0 && !sink_idx)) return fail(FOCUS_EINVAL, "%s: index array is NULL", who);
   if (!aligned16(Q) || !aligned16(K) || !aligned16(V) || !aligned16(out) || (kbar && !aligned16(kbar)))
     return fail(FOCUS_EINVAL, "%s: pointers must be 16-byte aligned", who);
-  const SplitPlan p = plan_attention(*shape, max_active, n_keep, n_sink);
-  const LayerWs w = ws_layer(*shape, p);
+  SplitPlan p = plan_attention(*shape, max_active, n_keep, n_sink);
+  LayerWs w = ws_layer(*shape, p);
+  if (!static_scratch && ws_bytes < w.need) w = ws_layer(*shape, p = plan_attention(*shape, max_active, n_keep, n_sink, true));
   if (static_scratch) {  // every argument has been checked by now: look the built-in array up (first call on a device) and use it
     if (kStaticScratchBytes < w.need)
       return fail(FOCUS_EWORKSPACE, "%s: this shape needs %zu bytes of scratch, the built-in array holds %zu; use focus_sparse_layer with a caller workspace",
@@ -721,8 +723,9 @@ int focus_sparse_attn(const void* Q, const int32_t* active_idx, const int32_t* c
   if ((n_keep > 0 && !kept_blocks) || (n_sink > 0 && !sink_idx)) return fail(FOCUS_EINVAL, "focus_sparse_attn: index array is NULL");
   if (!aligned16(Q) || !aligned16(K) || !aligned16(V) || !aligned16(out))
     return fail(FOCUS_EINVAL, "focus_sparse_attn: pointers must be 16-byte aligned");
-  const SplitPlan p = plan_attention(*shape, max_active, n_keep, n_sink);
-  const AttnWs w = ws_attn(*shape, p);
+  SplitPlan p = plan_attention(*shape, max_active, n_keep, n_sink);
+  AttnWs w = ws_attn(*shape, p);
+  if (!workspace || ws_bytes < w.total) w = ws_attn(*shape, p = plan_attention(*shape, max_active, n_keep, n_sink, true));
   if (p.n_split > 1 && (!workspace || ws_bytes < w.total || !aligned16(workspace)))
     return fail(FOCUS_EWORKSPACE, "focus_sparse_attn: workspace needs %zu bytes, 16-byte aligned", w.total);
   char* ws = static_cast<char*>(workspace);

@@ -47,9 +47,11 @@ static inline int64_t query_group_list(const SplitPlan& p, int n_heads) {
   return ceil_div64((int64_t)p.n_split * n_heads, 8) * 8 * p.q_groups;
 }
 
-SplitPlan plan_attention(const focus_shape& s, int max_active, int n_keep, int n_sink);
+// lean: the plan with fewer key splits that a workspace too small for the other's partial results is given (focus_workspace_bytes
+// speaks of the other; it must never refuse what it took before the splits of some shapes grew)
+SplitPlan plan_attention(const focus_shape& s, int max_active, int n_keep, int n_sink, bool lean = false);
 SplitPlan plan_attention_dense(const focus_shape& s, int max_active);  // all M + N rows, no block structure
-SplitPlan plan_logits(const focus_shape& s, int max_active);
+SplitPlan plan_logits(const focus_shape& s, int max_active, bool lean = false);
 
 // ---- small kernels (focus_small.hip)
 hipError_t launch_select_queries(const float* conf, const uint8_t* masked, int n_gen, int k, int window, int lo,

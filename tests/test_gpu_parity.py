@@ -282,6 +282,23 @@ def test_select_and_find_sinks_with_logits_past_the_memory_side_cache(G, d):
     assert sinks.cpu().tolist() == fo.select_sinks(S.cpu().numpy(), M, n_sink).tolist()
 
 
+def test_find_sinks_with_the_workspace_of_one_key_split_less(G):
+    """32 heads, 257 rounds: 129 splits, and 128 where their statistics do not fit; a byte less is refused."""
+    H, M, N, d, n_act = 32, 32768, 64, 64, 16
+    q, k = _rand_bf16(26, H, n_act, d).to(G.DEV), _rand_bf16(27, H, M + N, d).to(G.DEV)
+    active, s = G.i32(np.arange(n_act)), fb.make_shape(q, k, None, M, 64)
+    full = fb.workspace_bytes(fb.FN_FIND_SINKS, s, n_act)
+    least = full - H * n_act * 8
+    col, sinks = G.gpu_find_sinks(q, active, None, k, M, 64, 3)
+    col2, sinks2, buf = torch.empty_like(col), torch.empty_like(sinks), torch.full((full,), 0x5B, dtype=torch.uint8, device=G.DEV)
+    fb.find_sinks(q, active, None, k, s, 3, col2, sinks2, buf[:least])
+    torch.cuda.synchronize()
+    assert bool((buf[least:] == 0x5B).all()) and torch.equal(sinks, sinks2)
+    assert torch.allclose(col, col2, rtol=1e-5, atol=1e-12)
+    with pytest.raises(fb.FocusError):
+        fb.find_sinks(q, active, None, k, s, 3, col2, sinks2, buf[:least - 1])
+
+
 def test_find_sinks_equal_keys_fall_back_to_lowest_positions(G):
     H, M, N, d = 2, 500, 12, 64
     k = _rand_bf16(9, 1, 1, d).expand(H, M + N, d).contiguous().to(G.DEV)
@@ -740,6 +757,48 @@ def test_sparse_layer_of_many_blocks(G, H, M, N, d, B, n_act, n_keep, n_sink):
         torch.cuda.synchronize()
         assert torch.equal(s2, scores) and torch.equal(k2, kept)
         assert torch.equal(o2, out) and torch.equal(l2, lse)
+
+
+@pytest.mark.parametrize("H,M,N,B,n_keep,splits", [
+    (32, 4096, 0, 32, 128, 8),    # 32 splits with the full workspace; with the least a key loop in 8
+    (32, 4096, 64, 64, 32, 8),    # 17, and a key loop in 8
+    (16, 8192, 1, 32, 256, 16),   # a key loop in 32 and in 16
+    (300, 256, 0, 32, 8, 1),      # 2, and a key loop in one: no workspace at all
+])
+def test_least_workspace_of_64_columns(G, H, M, N, B, n_keep, splits):
+    """d = 64, up to 16 queries: the workspace of fewer key splits is taken, too, one byte less is not, and nothing is written past it."""
+    d, n_act = 64, 11
+    q, k, v = (_rand_bf16(121 + i, H, r, d).to(G.DEV) for i, r in enumerate((16, M + N, M + N)))
+    focus, active, counts = G.i32(np.arange(4)), G.i32(np.arange(16)), G.i32([4, n_act])
+    up = lambda x: (x + 255) // 256 * 256
+    least = up(H * 16 * splits * d * 4) + up(H * 16 * splits * 8) if splits > 1 else 0
+    kbar = G.gpu_block_means(k, M, B)
+    scores, kept = G.gpu_block_scores(q, focus, counts, k, kbar, M, B, n_keep)
+    out = torch.empty((H, 16, d), dtype=torch.bfloat16, device=G.DEV)
+    s = fb.make_shape(q, k, v, M, B, out)
+    assert fb.workspace_bytes(fb.FN_SPARSE_ATTN, s, 16, n_keep, 0) > max(least, 256)
+    rows = np.concatenate([np.arange(b * B, min((b + 1) * B, M)) for b in kept.tolist()])
+    ref, ref_lse = fo.sparse_attention(G.to_np(q), np.arange(n_act), G.to_np(k), G.to_np(v), rows, M)
+    extra = fb.workspace_bytes(fb.FN_BLOCK_SCORES, s)
+    for layer, nbytes in ((False, least), (True, extra + max(least, 256))):
+        buf = torch.full((nbytes + 4096,), 0x5B, dtype=torch.uint8, device=G.DEV)
+        lse, s2, k2 = torch.full((H, 16), 9.0, device=G.DEV), torch.empty_like(scores), torch.empty_like(kept)
+
+        def call(w):
+            if layer:
+                fb.sparse_layer(q, focus, active, counts, k, v, kbar, s, n_keep, None, 0, s2, k2, out, lse, w)
+            else:
+                fb.sparse_attn(q, active, counts, k, v, s, kept, n_keep, None, 0, out, lse, w if nbytes else None)
+        out.fill_(7.0)
+        call(buf[:nbytes])
+        torch.cuda.synchronize()
+        assert bool((buf[nbytes:] == 0x5B).all())
+        assert not layer or (torch.equal(s2, scores) and torch.equal(k2, kept))
+        G.assert_attention_close(out[:, :n_act], ref)
+        assert np.allclose(lse[:, :n_act].cpu().numpy(), ref_lse, atol=2e-3)
+        if nbytes:
+            with pytest.raises(fb.FocusError):
+                call(buf[:nbytes - 1])
 
 
 # ------------------------------------------------------------------------------------------------ whole layer on the workloads
