@@ -2304,6 +2304,7 @@ static hipError_t launch_logits_t(const LogitArgs& a, const SplitPlan& p, int mo
     return hipGetLastError();
   }
   if (mode == 0 || query_group_list(p, a.H) > kMaxList) return hipErrorInvalidValue;
+  if (a.q_pad != p.q_groups * p.q_tiles_per_group * kQTile) return hipErrorInvalidValue;  // MODE 3 reads the statistics of whole query groups
   const dim3 grid = grid_list(query_group_list(p, a.H));
 #define WIDE_LOGITS(NT)                                                                                                 \
   if (mode == 2 && a.part_ml != nullptr)                                                                                \
