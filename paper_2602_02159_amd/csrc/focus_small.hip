@@ -342,7 +342,7 @@ hipError_t launch_block_means_relevance(const void* K, const void* Q, const int3
 // A wavefront owns one head and P R consecutive blocks (R = 4 at d = 128, 8 at 64), a lane one 8-wide slice of d of one block
 // row; the focus indices and the kbar loads are issued first, then the focus rows of Q: two dependent memory round trips.
 // PER_HEAD: part[h, b].  Otherwise the four heads of the workgroup meet in LDS and part[h / 4, b] is their sum, so that whoever
-// ranks the blocks — every workgroup of the attention kernel, or a single one past 1024 blocks — has a quarter to read.
+// ranks the blocks — every workgroup of the attention kernel, or a single one past kFusedMaxBlocks — has a quarter to read.
 // Heads are the fast grid axis: workgroups go to the XCDs round-robin, so those of one head share an L2 and its focus rows.
 // Sparse layer of 32 heads with 256 blocks 15.3 -> 14.9 us (a workgroup per head and 32 blocks, its 16 focus rows summed by all
 // four wavefronts through LDS, and every attention workgroup adding 32 partial relevances per block), 4 heads at 1K 11.0 -> 10.4.
@@ -460,9 +460,9 @@ hipError_t launch_lse_combine(const float* part_ml, int H, int q_pad, int n_spli
 //                15.7 -> 15.0).  That a load past the last head repeats it costs nothing (1 to 8 heads, up to 32 832 keys: sixteen
 //                in flight with the absent ones left out take as long).  It adds exp2(logit - lse) over the heads in head order; the
 //                sixteen queries of a quad are then summed across the lanes of a DPP row (fixed tree).
-//                PAST_CACHE: more logits than the 256 MB memory-side cache holds beside what else was written, heads in
-//                descending order and without a place in that cache: it has kept the last heads that were written, and reading
-//                the first ones first would displace them (kMemorySideCache).
+//                PAST_CACHE: more logits than the 256 MB memory-side cache holds: heads in descending order and without a place in
+//                that cache, which has kept the last heads that were written; reading the first ones first would displace them
+//                (kMemorySideCache).
 //   PRE = true:  `src` holds per-part column sums [n_parts, L] (already summed over a part's queries); thread
 //                (key, part group pg) adds parts pg, pg + 4, ..., eight loads in flight, then the four groups are added.
 // S_j = total / (H * n_act).
@@ -667,9 +667,11 @@ hipError_t launch_column_mass(const float* src, bool pre_reduced, const float* l
     if (e != hipSuccess) return e;
     lse2 = lse_scratch;
   }
-  // Sink chain, 16 queries of 32 heads (logits written non-temporally and read in ascending order; so; so but read plainly): 131136
-  // keys, 269 MB 287, 263, 264 us; 40 heads, 336 MB 372, 321 to 345, 372; 64 heads, 537 MB 591, 542 to 580, 605; up to 200 MB there is nothing
-  // between them but 1.2 us for the plain reads at 32832 keys.
+  // Sink chain in us, 16 queries, 131 136 keys (logits read plainly in ascending order; plainly in descending; non-temporally in
+  // ascending; non-temporally in descending): 32 heads, 269 MB 268, 267, 266, 268; 40 heads, 336 MB 373, 364, 351, 345; 64 heads, 537 MB
+  // 623, 617, 585, 579.  At 134 and 210 MB all four are alike, too; at 67 MB (32 832 keys) the plain ones take 1.2 us less.  (All with
+  // plain stores.  Written non-temporally, as they were past 200 MB: 268 -> 285, 345 -> 364, 579 -> 577; 65 600 keys of 32 heads 138 -> 147.)
+  // Up to eight heads, which would need 400 000 keys and more, are left to the plain reads: not measured.
   constexpr int64_t kMemorySideCache = (int64_t)200 << 20;
 #define COLUMN_MASS(HEADS)                                                                                                       \
   if (lse)                                                                                                                       \

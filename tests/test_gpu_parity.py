@@ -244,11 +244,11 @@ def test_select_and_find_sinks_equals_the_two_calls(G, n_gen, k, window, lo, hi,
         assert all(torch.equal(a, b) for a, b in zip(*res))
 
 
-@pytest.mark.parametrize("d", [64, 128])
-def test_select_and_find_sinks_with_logits_past_the_memory_side_cache(G, d):
-    """More than 200 MB of spilled logits, read back non-temporally, with the selection in the same launch: the two calls' results bit
-    for bit, and column masses that agree with fp64."""
-    H, M, N, n_gen, k, n_sink = 32, 102500, 37, 48, 13, 5
+@pytest.mark.parametrize("H,d", [(32, 64), (32, 128), (33, 64), (40, 128)])   # whole batches of sixteen heads, and not
+def test_select_and_find_sinks_with_logits_past_the_memory_side_cache(G, H, d):
+    """More than 200 MB of spilled logits, read back non-temporally from the last head on, with the selection in the same launch: the two
+    calls' results bit for bit, and column masses that agree with fp64."""
+    M, N, n_gen, k, n_sink = (200 << 20) // (64 * H) + 100, 37, 48, 13, 5
     L = M + N
     assert H * L * 64 > 200 << 20
     g = torch.Generator(device=G.DEV).manual_seed(330 + d)
@@ -277,6 +277,27 @@ def test_select_and_find_sinks_with_logits_past_the_memory_side_cache(G, d):
     for h in range(H):
         z = torch.matmul(q[h, rows].double(), kk[h].double().T.contiguous()) / math.sqrt(d)
         S += torch.softmax(z, -1).mean(0) / H
+    assert torch.allclose(col.double(), S, rtol=2e-4, atol=1e-9)
+    assert fo.decision_margin(S.cpu().numpy(), n_sink, np.arange(L) < M) > 1e-5
+    assert sinks.cpu().tolist() == fo.select_sinks(S.cpu().numpy(), M, n_sink).tolist()
+
+
+def test_probe_layer_with_logits_past_the_memory_side_cache(G):
+    """The same way back for logits that the probe layer's attention has kept, with a last batch of one head."""
+    H, M, N, d, n_gen, n_act, n_sink = 33, 99400, 37, 64, 16, 13, 5
+    L = M + N
+    assert H * L * 64 > 200 << 20
+    g = torch.Generator(device=G.DEV).manual_seed(340)
+    q, k, v = (torch.randn(H, r, d, generator=g, device=G.DEV).to(torch.bfloat16) for r in (n_gen, L, L))
+    planted = torch.tensor([0, 31, 50001, 77777, M - 1], device=G.DEV)
+    k[:, planted] += 3.0 * q.float().mean(1, keepdim=True).to(torch.bfloat16) * torch.arange(5, 10, device=G.DEV).view(1, 5, 1)
+    out, _, col, sinks = G.gpu_probe_layer(q, G.i32(np.arange(n_gen)), G.i32([0, n_act]), k, v, M, 128, n_sink)
+    S, ref = torch.zeros(L, dtype=torch.float64, device=G.DEV), []
+    for h in range(H):
+        p = torch.softmax(torch.matmul(q[h, :n_act].double(), k[h].double().T.contiguous()) / math.sqrt(d), -1)
+        S += p.mean(0) / H
+        ref.append(torch.matmul(p, v[h].double()))
+    G.assert_attention_close(out[:, :n_act], torch.stack(ref).cpu().numpy())
     assert torch.allclose(col.double(), S, rtol=2e-4, atol=1e-9)
     assert fo.decision_margin(S.cpu().numpy(), n_sink, np.arange(L) < M) > 1e-5
     assert sinks.cpu().tolist() == fo.select_sinks(S.cpu().numpy(), M, n_sink).tolist()
