@@ -169,10 +169,11 @@ __device__ __forceinline__ void add_splits(RowState& r, const float2 (&v)[N]) {
 }
 __device__ __forceinline__ float lse_of(const RowState& r) { return r.l > 0.f ? r.m + __builtin_amdgcn_logf(r.l) : INFINITY; }  // v_log_f32 is log2
 // splits first, first + step, ... of one row, N loads at a time; `row` = its place in the first split, `stride` = rows per split.
-// The scheduling fence keeps the loads of a batch together: without it the compiler waited for each of them in the variants of
-// column_mass_kernel that hold few heads, to stay within 64 registers, and a batch was eight memory round trips.
+// FENCE: a scheduling fence keeps the loads of a batch together.  Without it the compiler waited for each of them in the variants of
+// column_mass_kernel that hold few heads, to stay within 64 registers, and a batch was eight memory round trips.  Where they are
+// together anyway it costs a little (32 heads, 8256 keys, one-layer step: 0.3 of 41 us).
 constexpr int kSplitsInFlight = 8;
-template <int N = kSplitsInFlight>
+template <int N = kSplitsInFlight, bool FENCE = false>
 __device__ __forceinline__ RowState add_row_splits(const float2* row, int64_t stride, int first, int step, int n_split) {
   RowState r{-INFINITY, 0.f};
   for (int s0 = first; s0 < n_split; s0 += N * step) {
@@ -181,11 +182,14 @@ __device__ __forceinline__ RowState add_row_splits(const float2* row, int64_t st
     for (int u = 0; u < N; ++u) {
       const int s = s0 + u * step;
       v[u] = row[(int64_t)min(s, n_split - 1) * stride];
+      if (!FENCE && s >= n_split) v[u] = make_float2(-INFINITY, 0.f);
     }
-    __builtin_amdgcn_sched_barrier(0);
+    if (FENCE) {
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int u = 0; u < N; ++u)
-      if (s0 + u * step >= n_split) v[u] = make_float2(-INFINITY, 0.f);
+      for (int u = 0; u < N; ++u)
+        if (s0 + u * step >= n_split) v[u] = make_float2(-INFINITY, 0.f);
+    }
     add_splits(r, v);
   }
   return r;

@@ -549,7 +549,8 @@ __global__ __launch_bounds__(512) void column_mass_kernel(const float* __restric
           const int sl = threadIdx.x & (lanes - 1), per_turn = 512 / lanes;
           for (int row = threadIdx.x / lanes; row < rows; row += per_turn) {
             const float2* first = ml + (row >> 4) * n_split * 16 + (row & 15);
-            const RowState r = n_split <= 2 * lanes ? add_row_splits<2>(first, 16, sl, lanes, n_split) : add_row_splits(first, 16, sl, lanes, n_split);
+            const RowState r = n_split <= 2 * lanes ? add_row_splits<2>(first, 16, sl, lanes, n_split)
+                                                         : add_row_splits<kSplitsInFlight, HEADS <= 8>(first, 16, sl, lanes, n_split);
             float m = r.m;
             if (lanes > 1) m = fmaxf(m, lane_dpp<0xB1>(m));   // quad_perm [1,0,3,2]
             if (lanes > 2) m = fmaxf(m, lane_dpp<0x4E>(m));   // quad_perm [2,3,0,1]
