@@ -67,6 +67,18 @@ def test_layers_of_many_blocks_fit_the_static_scratch_array(L, H, d, M, N, B, n_
     assert 0 < fb.workspace_bytes(fb.FN_SPARSE_LAYER, s, n_act, n_keep, n_sink) <= (8 << 20)
 
 
+def test_layer_workspace_around_the_static_scratch_array(L):
+    """1025 to 2048 blocks: the size is the sum of the two parts, but where only the larger of them fits 8 MiB it is that one."""
+    sizes = lambda H: [fb.workspace_bytes(fn, _shape(n_heads=H, head_dim=128, n_ctx=65536, n_resp=32, block=32, n_gen=32), 32, 62, 0)
+                       for fn in (fb.FN_BLOCK_SCORES, fb.FN_SPARSE_ATTN, fb.FN_SPARSE_LAYER)]
+    scores, attn, layer = sizes(30)
+    assert layer == scores + attn <= 8 << 20
+    scores, attn, layer = sizes(31)
+    assert scores + attn > 8 << 20 and layer == attn <= 8 << 20
+    scores, attn, layer = sizes(32)
+    assert layer == scores + attn > 8 << 20 and attn > 8 << 20
+
+
 def test_bad_arguments_are_rejected_on_the_host(L):
     fake = C.c_void_p(4096)  # never dereferenced: validation fails first
     s = _shape()
