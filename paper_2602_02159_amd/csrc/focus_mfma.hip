@@ -70,6 +70,14 @@ constexpr int kStreamPolicy = 2;
 
 // s_waitcnt vmcnt(0): every outstanding global load, LDS-direct ones included, has landed
 __device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }
+// s_waitcnt vmcnt(N): every global load and store but the N issued last has completed
+template <int N>
+__device__ __forceinline__ void wait_loads_but() {
+  static_assert(N < 64, "six bits");
+  __builtin_amdgcn_sched_barrier(0);
+  __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
+  __builtin_amdgcn_sched_barrier(0);
+}
 // s_waitcnt lgkmcnt(0): every LDS read of this wavefront has returned.  Placed before an LDS-direct load that
 // overwrites a stage the wavefront has just read: that write-after-read order is not covered by vmcnt, and the fence
 // keeps the compiler from moving the load above the wait.
@@ -110,42 +118,12 @@ __device__ __forceinline__ int32_t uniform_load(const int32_t* ptr) {
   return *(cptr_t)(uintptr_t)ptr;
 }
 __device__ __forceinline__ int32_t uniform_load(const uint16_t* ptr) { return *ptr; }  // (lists of 16 bits lie in LDS: KeptList)
+// Sub-tile `st` of the sink list
 template <class Id>
-__device__ __forceinline__ SubTile locate_subtile(int st, int lane, int M, int N, int B, int n_b, int sub_per_block,
-                                                  const Id* __restrict__ kept_blocks, int n_keep,
-                                                  const int32_t* __restrict__ sink_idx, int n_sink,
-                                                  const uint32_t* kept_bits = nullptr, int ascending = -1,
-                                                  int dense_rows = 0, bool blocks_in_lds = false, int few_sinks = -1) {
+__device__ __forceinline__ SubTile locate_sinks(int st, int lane, int M, int B, const Id* __restrict__ kept_blocks, int n_keep,
+                                                const int32_t* __restrict__ sink_idx, int n_sink, const uint32_t* kept_bits, int ascending,
+                                                int few_sinks) {
   SubTile t;
-  t.kind = 0;
-  t.row0 = 0;
-  t.vmask = 0u;
-  t.sink_row = 0;
-  if (dense_rows > 0) {  // every key row takes part (dense layers): sub-tile st is rows [32 st, 32 st + 32)
-    t.row0 = st * kSubTile;
-    t.vmask = low_mask(min(dense_rows - t.row0, kSubTile));
-    return t;
-  }
-  const int n_blk_sub = n_keep * sub_per_block;
-  const int n_resp_sub = (N + kSubTile - 1) / kSubTile;
-  if (st < n_blk_sub) {
-    const int slot = st / sub_per_block, sub = st % sub_per_block;
-    const int b = blocks_in_lds ? kept_blocks[slot] : uniform_load(kept_blocks + slot);
-    if (b < 0 || b >= n_b) return t;
-    const int first = b * B + sub * kSubTile;
-    const int end = min(min((b + 1) * B, M), first + kSubTile);
-    t.row0 = first;
-    t.vmask = low_mask(end - first);
-    return t;
-  }
-  st -= n_blk_sub;
-  if (st < n_resp_sub) {
-    const int first = M + st * kSubTile;
-    t.row0 = first;
-    t.vmask = low_mask(min(M + N - first, kSubTile));
-    return t;
-  }
-  st -= n_resp_sub;
   t.kind = 1;
   t.row0 = st * kSubTile;
   const int e = t.row0 + lane;
@@ -200,6 +178,44 @@ __device__ __forceinline__ SubTile locate_subtile(int st, int lane, int M, int N
   const int fallback = __shfl(mine, t.vmask != 0u ? __builtin_ctz(t.vmask) : 0, kWave);
   t.sink_row = ((t.vmask >> (lane & 31)) & 1u) ? mine : fallback;
   return t;
+}
+
+template <class Id>
+__device__ __forceinline__ SubTile locate_subtile(int st, int lane, int M, int N, int B, int n_b, int sub_per_block,
+                                                  const Id* __restrict__ kept_blocks, int n_keep,
+                                                  const int32_t* __restrict__ sink_idx, int n_sink,
+                                                  const uint32_t* kept_bits = nullptr, int ascending = -1,
+                                                  int dense_rows = 0, bool blocks_in_lds = false, int few_sinks = -1) {
+  SubTile t;
+  t.kind = 0;
+  t.row0 = 0;
+  t.vmask = 0u;
+  t.sink_row = 0;
+  if (dense_rows > 0) {  // every key row takes part (dense layers): sub-tile st is rows [32 st, 32 st + 32)
+    t.row0 = st * kSubTile;
+    t.vmask = low_mask(min(dense_rows - t.row0, kSubTile));
+    return t;
+  }
+  const int n_blk_sub = n_keep * sub_per_block;
+  const int n_resp_sub = (N + kSubTile - 1) / kSubTile;
+  if (st < n_blk_sub) {
+    const int slot = st / sub_per_block, sub = st % sub_per_block;
+    const int b = blocks_in_lds ? kept_blocks[slot] : uniform_load(kept_blocks + slot);
+    if (b < 0 || b >= n_b) return t;
+    const int first = b * B + sub * kSubTile;
+    const int end = min(min((b + 1) * B, M), first + kSubTile);
+    t.row0 = first;
+    t.vmask = low_mask(end - first);
+    return t;
+  }
+  st -= n_blk_sub;
+  if (st < n_resp_sub) {
+    const int first = M + st * kSubTile;
+    t.row0 = first;
+    t.vmask = low_mask(min(M + N - first, kSubTile));
+    return t;
+  }
+  return locate_sinks(st - n_resp_sub, lane, M, B, kept_blocks, n_keep, sink_idx, n_sink, kept_bits, ascending, few_sinks);
 }
 
 // Row of K/V that staged slot `slot` of sub-tile t reads.  Every slot reads a row of the key set, also the slots that
@@ -345,6 +361,70 @@ __device__ __forceinline__ bf16x8 read_v_operand(const char* stageV, int ct, int
   const shortx4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(stageV + off1));
   struct { shortx4 a, b; } both = {lo, hi};
   return __builtin_bit_cast(bf16x8, both);
+}
+
+// All K (V) operands of a staged sub-tile into registers, complete on return.  Key loops that request the next K rows while the V
+// rows of this sub-tile are still under way need the reads outside the compiler's sight: it would wait for every outstanding
+// LDS-direct load in front of them.  The callers wait for the rows (wait_loads_but).  Stages are aligned to 256 bytes, so that the
+// swizzle of a chunk is an exclusive or of the address.
+__device__ __forceinline__ uint32_t lds_address(const char* p) {
+  typedef const __attribute__((address_space(3))) char* lds_ptr;
+  return (uint32_t)(uintptr_t)(lds_ptr)p;
+}
+template <int D>
+__device__ __forceinline__ void read_k_operands16(bf16x8 (&k)[2][D / 32], const char* stageK, int lane) {
+  const uint32_t a = lds_address(stageK) + stage_off<D>(lane & 15, lane >> 4);  // chunk 4 kk + g, row 16 kt + c
+  if constexpr (D == 128) {
+    asm volatile(
+        "ds_read_b128 %0, %8\n\tds_read_b128 %1, %9\n\tds_read_b128 %2, %10\n\tds_read_b128 %3, %11\n\t"
+        "ds_read_b128 %4, %8 offset:4096\n\tds_read_b128 %5, %9 offset:4096\n\tds_read_b128 %6, %10 offset:4096\n\t"
+        "ds_read_b128 %7, %11 offset:4096\n\ts_waitcnt lgkmcnt(0)"
+        : "=&v"(k[0][0]), "=&v"(k[0][1]), "=&v"(k[0][2]), "=&v"(k[0][3]), "=&v"(k[1][0]), "=&v"(k[1][1]), "=&v"(k[1][2]), "=&v"(k[1][3])
+        : "v"(a), "v"(a ^ 64u), "v"(a ^ 128u), "v"(a ^ 192u)
+        : "memory");
+  } else {
+    asm volatile(
+        "ds_read_b128 %0, %4\n\tds_read_b128 %1, %5\n\tds_read_b128 %2, %4 offset:2048\n\tds_read_b128 %3, %5 offset:2048\n\t"
+        "s_waitcnt lgkmcnt(0)"
+        : "=&v"(k[0][0]), "=&v"(k[0][1]), "=&v"(k[1][0]), "=&v"(k[1][1])
+        : "v"(a), "v"(a ^ 64u)
+        : "memory");
+  }
+}
+template <int D>
+__device__ __forceinline__ void read_v_operands16(bf16x8 (&v)[D / 16], const char* stageV, int lane) {
+  const int s = lane & 15, g = lane >> 4, col = 4 * (s & 3);
+  const uint32_t a = lds_address(stageV) + stage_off<D>(4 * g + (s >> 2), col >> 3) + (col & 7) * 2;  // column tile ct: chunk 2 ct further
+  shortx4 r[D / 16][2];
+  if constexpr (D == 128) {
+    asm volatile(
+        "ds_read_b64_tr_b16 %0, %16\n\tds_read_b64_tr_b16 %1, %16 offset:4096\n\t"
+        "ds_read_b64_tr_b16 %2, %17\n\tds_read_b64_tr_b16 %3, %17 offset:4096\n\t"
+        "ds_read_b64_tr_b16 %4, %18\n\tds_read_b64_tr_b16 %5, %18 offset:4096\n\t"
+        "ds_read_b64_tr_b16 %6, %19\n\tds_read_b64_tr_b16 %7, %19 offset:4096\n\t"
+        "ds_read_b64_tr_b16 %8, %20\n\tds_read_b64_tr_b16 %9, %20 offset:4096\n\t"
+        "ds_read_b64_tr_b16 %10, %21\n\tds_read_b64_tr_b16 %11, %21 offset:4096\n\t"
+        "ds_read_b64_tr_b16 %12, %22\n\tds_read_b64_tr_b16 %13, %22 offset:4096\n\t"
+        "ds_read_b64_tr_b16 %14, %23\n\tds_read_b64_tr_b16 %15, %23 offset:4096\n\ts_waitcnt lgkmcnt(0)"
+        : "=&v"(r[0][0]), "=&v"(r[0][1]), "=&v"(r[1][0]), "=&v"(r[1][1]), "=&v"(r[2][0]), "=&v"(r[2][1]), "=&v"(r[3][0]), "=&v"(r[3][1]),
+          "=&v"(r[4][0]), "=&v"(r[4][1]), "=&v"(r[5][0]), "=&v"(r[5][1]), "=&v"(r[6][0]), "=&v"(r[6][1]), "=&v"(r[7][0]), "=&v"(r[7][1])
+        : "v"(a), "v"(a ^ 32u), "v"(a ^ 64u), "v"(a ^ 96u), "v"(a ^ 128u), "v"(a ^ 160u), "v"(a ^ 192u), "v"(a ^ 224u)
+        : "memory");
+  } else {
+    asm volatile(
+        "ds_read_b64_tr_b16 %0, %8\n\tds_read_b64_tr_b16 %1, %8 offset:2048\n\t"
+        "ds_read_b64_tr_b16 %2, %9\n\tds_read_b64_tr_b16 %3, %9 offset:2048\n\t"
+        "ds_read_b64_tr_b16 %4, %10\n\tds_read_b64_tr_b16 %5, %10 offset:2048\n\t"
+        "ds_read_b64_tr_b16 %6, %11\n\tds_read_b64_tr_b16 %7, %11 offset:2048\n\ts_waitcnt lgkmcnt(0)"
+        : "=&v"(r[0][0]), "=&v"(r[0][1]), "=&v"(r[1][0]), "=&v"(r[1][1]), "=&v"(r[2][0]), "=&v"(r[2][1]), "=&v"(r[3][0]), "=&v"(r[3][1])
+        : "v"(a), "v"(a ^ 32u), "v"(a ^ 64u), "v"(a ^ 96u)
+        : "memory");
+  }
+#pragma unroll
+  for (int ct = 0; ct < D / 16; ++ct) {
+    struct { shortx4 a, b; } both = {r[ct][0], r[ct][1]};
+    v[ct] = __builtin_bit_cast(bf16x8, both);
+  }
 }
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
@@ -663,6 +743,64 @@ struct SplitRounds {
   }
 };
 
+// The sub-tiles of 64 rounds at a time, lane i those of round i0 + i: a key loop takes them by lane reads, where working one out per round
+// put a division and the wait for a block id in front of the products.  n: rows, -1: sub-tile row0 of the sink list.
+struct RoundTable {
+  int row0, n;
+};
+template <class Id>
+__device__ __forceinline__ RoundTable tabulate_rounds(const AttnArgs& p, const SplitRounds& rounds, int slot, int i0, int lane, const Id* kept_blocks) {
+  RoundTable r{0, 0};
+  int sub = rounds.sub(i0 + lane, slot);
+  if (sub >= p.n_sub) return r;
+  if (p.dense_rows > 0) {
+    r.row0 = sub * kSubTile;
+    r.n = min(p.dense_rows - r.row0, kSubTile);
+    return r;
+  }
+  const int n_blk_sub = p.n_keep * p.sub_per_block, n_resp_sub = (p.N + kSubTile - 1) / kSubTile;
+  if (sub < n_blk_sub) {
+    const int i = sub / p.sub_per_block, b = kept_blocks[i];
+    if (b >= 0 && b < p.n_b) {
+      r.row0 = b * p.B + (sub - i * p.sub_per_block) * kSubTile;
+      r.n = max(min(min((b + 1) * p.B, p.M) - r.row0, kSubTile), 0);
+    }
+    return r;
+  }
+  sub -= n_blk_sub;
+  if (sub < n_resp_sub) {
+    r.row0 = p.M + sub * kSubTile;
+    r.n = min(p.M + p.N - r.row0, kSubTile);
+  } else {
+    r.row0 = sub - n_resp_sub;
+    r.n = -1;
+  }
+  return r;
+}
+// rounds 0, 1, 2, ... of a slot, one call each
+template <class Id>
+struct RoundList {
+  const AttnArgs& p;
+  const SplitRounds& rounds;
+  const SinkUnion& uni;
+  const Id* kept_blocks;
+  int slot, lane, few_sinks, next = 0;
+  RoundTable table{0, 0};
+  __device__ __forceinline__ SubTile take() {
+    const int i = next & (kWave - 1);
+    if (i == 0) table = tabulate_rounds(p, rounds, slot, next, lane, kept_blocks);
+    ++next;
+    const int n = __builtin_amdgcn_readlane(table.n, i), row0 = __builtin_amdgcn_readlane(table.row0, i);
+    if (n < 0) return locate_sinks(row0, lane, p.M, p.B, kept_blocks, p.n_keep, p.sink_idx, p.n_sink, uni.kept_bits, uni.ascending, few_sinks);
+    SubTile t;
+    t.kind = 0;
+    t.row0 = row0;
+    t.vmask = low_mask(n);
+    t.sink_row = 0;
+    return t;
+  }
+};
+
 // Up to 16 active queries.  One workgroup works on one (head, key split); the key axis is walked in rounds of four 32-row
 // sub-tiles ("slots"), and every one of its four wavefronts owns its slot end to end — it stages the sub-tile, multiplies it
 // against the one query tile and keeps its own running softmax; the four states are merged at the end.
@@ -674,26 +812,24 @@ struct SplitRounds {
 // FUSE bit 4 set (with bit 0): more than 256 blocks to rank.
 // FUSE bit 2 set (dense probe layer): the scaled logits of every (query, key) are also written out, so that
 // the column attention mass of Eq. 6 needs no QK^T pass of its own.
-// FUSE bit 1 set: double-buffered key loop for launches in which a wavefront walks several sub-tiles
-// (the dense comparison, the probe layer): the next sub-tile's rows travel HBM -> LDS into the wavefront's second
-// stage while the current one is multiplied, so one wavefront per SIMD keeps both the memory pipe and the matrix
-// cores busy.
+// FUSE bit 1 set: key loop, for launches in which a wavefront walks several sub-tiles (the dense comparison, the probe layer).  As in
+// wide_attn_kernel with NT = 1 the K and V rows of the one stage travel separately.  Against two stages and a request for the pair: 32
+// heads, 8256 keys 30.3 -> 28.3 us a call, 32 832 keys 86.3 -> 85.1; 8 heads, 16 448 keys 20.6 -> 18.9; 30 of 1024 blocks, whole layer
+// 27.0 -> 26.1; probe layer of 32 832 keys 130.4 -> 128.7.
 // In every case a second, small kernel merges the key splits.  (Letting the last workgroup of a head merge them
 // behind device-scope fences was measured: the fences cost ~10 us per launch, more than the launch they save.)
 template <int D, int FUSE>
-__global__ __launch_bounds__(256, (FUSE & 2) == 0 ? 2 : 1) void sparse_attn_kernel(ATTN_FIRST_PARAMS, const AttnArgs args) {
+__global__ __launch_bounds__(256, 2) void sparse_attn_kernel(ATTN_FIRST_PARAMS, const AttnArgs args) {
   const AttnArgs p = with_first(args, ATTN_FIRST_NAMES);
   using G = Geo<D>;
   constexpr bool FUSED = (FUSE & 1) != 0;                // Top-C in the prologue
-  constexpr bool PIPE = (FUSE & 2) != 0;                 // two K/V stages per wavefront
+  constexpr bool PIPE = (FUSE & 2) != 0;                 // key loop
   constexpr bool SPILL = (FUSE & 4) != 0;                // dense: also write the scaled logits (sink scoring)
   constexpr bool PER_HEAD = (FUSE & 8) != 0;             // FUSED: partial relevances per head, not per group of heads
   constexpr int BLOCKS = (FUSE & 32) != 0 ? kFusedMaxBlocks : ((FUSE & 16) != 0 ? kFusedManyBlocks : 256);  // FUSED: the most blocks to rank
   constexpr int kBufBytes = 2 * G::kStageBytes;          // one slot: K stage + V stage of a sub-tile
   static_assert(16 * D * 4 <= kBufBytes, "a wavefront's O tile fits its stage");
-  // Two buffers of four slots; the second exists in the double-buffered variant only.
-  __shared__ __attribute__((aligned(16))) char ldsA[kWavesPerGroup * kBufBytes];
-  __shared__ __attribute__((aligned(16))) char ldsB[PIPE ? kWavesPerGroup * kBufBytes : 16];
+  __shared__ __attribute__((aligned(256))) char ldsA[kWavesPerGroup * kBufBytes];
   __shared__ float2 ml_sh[kWavesPerGroup][16];  // final merge: running maximum and sum per wavefront and query
 
   const int lane = threadIdx.x & 63;
@@ -731,7 +867,7 @@ __global__ __launch_bounds__(256, (FUSE & 2) == 0 ? 2 : 1) void sparse_attn_kern
   __shared__ uint32_t kept_bits_sh[kBitmapBlocks / 32];
   __shared__ int sinks_unsorted_sh;
   static_assert(D == 128 || PIPE ||
-                    4 * (sizeof(ldsA) + sizeof(ldsB) + sizeof(ml_sh) + sizeof(topk_raw) + sizeof(kept_beside) + sizeof(kept_bits_sh) + 16) <= 163840,
+                    4 * (sizeof(ldsA) + sizeof(ml_sh) + sizeof(topk_raw) + sizeof(kept_beside) + sizeof(kept_bits_sh) + 16) <= 163840,
                 "four workgroups share a compute unit (kAttnGroupsSmall)");
   const SinkUnion uni = prepare_union(p, split, kept_blocks, kept_bits_sh, &sinks_unsorted_sh);
   const uint32_t* kept_bits = uni.kept_bits;
@@ -741,14 +877,21 @@ __global__ __launch_bounds__(256, (FUSE & 2) == 0 ? 2 : 1) void sparse_attn_kern
   // sub-tile's K and V rows as soon as its block id is known, then the query rows and the device-side count.
   const int st_end = p.n_sub;
   const SplitRounds rounds(p, split, h);
-  const int st = PIPE ? rounds.sub(0, wave) : split * kWavesPerGroup + wave;
+  const int st = split * kWavesPerGroup + wave;
   const int qrow = FUSED ? qrow_early : fetch_q_row(p.active_idx, 0, p.max_active, p.n_gen, lane);
   SubTile t;
   t.kind = 0;
   t.row0 = 0;
   t.vmask = 0u;
   t.sink_row = 0;
-  if (st < st_end) {
+  RoundList<typename Kept::Id> list{p, rounds, uni, kept_blocks, wave, lane, few_sinks};
+  if (PIPE) {
+    t = list.take();
+    if (t.vmask != 0u) {
+      issue_subtile<D>(Kh, p.ksn, t, stageK, lane);
+      issue_subtile<D>(Vh, p.vsn, t, stageV, lane);
+    }
+  } else if (st < st_end) {
     t = locate_subtile(st, lane, p.M, p.N, p.B, p.n_b, p.sub_per_block, kept_blocks, p.n_keep, p.sink_idx, p.n_sink, kept_bits,
                           sinks_ascending, p.dense_rows, FUSED, few_sinks);
     if (t.vmask != 0u) {
@@ -790,18 +933,6 @@ __global__ __launch_bounds__(256, (FUSE & 2) == 0 ? 2 : 1) void sparse_attn_kern
     }
     first = false;
   };
-  auto no_tile = []() {
-    SubTile e;
-    e.kind = 0;
-    e.row0 = 0;
-    e.vmask = 0u;
-    e.sink_row = 0;
-    return e;
-  };
-  auto locate = [&](int sub) {
-    return locate_subtile(sub, lane, p.M, p.N, p.B, p.n_b, p.sub_per_block, kept_blocks, p.n_keep, p.sink_idx, p.n_sink, kept_bits,
-                          sinks_ascending, p.dense_rows, FUSED, few_sinks);
-  };
   if (!PIPE) {
     // one sub-tile per wavefront at most (the launcher picks this variant only when a split holds no more sub-tiles
     // than the workgroup has wavefronts): no key loop, and none of its code — these launches are a few microseconds
@@ -812,34 +943,57 @@ __global__ __launch_bounds__(256, (FUSE & 2) == 0 ? 2 : 1) void sparse_attn_kern
       if (SPILL) spill_logits(p.logits_out, h, p.dense_rows, t.row0, kept_logits, p.scale_log2, lane);  // contiguous rows only (dense)
     }
   } else {
-    // One step: the sub-tile `t` sits in this wavefront's slot of `cur`; the rows of the next one are requested straight
-    // into its slot of `nxt` (LDS-direct: no staging registers, no LDS stores) before `t` is multiplied, and are waited
-    // for afterwards, so they travel for the whole multiplication.  `cur` and `nxt` are slots of two separate arrays:
-    // the compiler can tell that the loads into one do not touch the operand reads of the other.  No barrier: the slots
-    // are private to the wavefront (which has finished reading `nxt` one step ago; wait_lds_reads makes that explicit).
-    int round = 0;
-    auto step = [&](const char* cur, char* nxt) __attribute__((always_inline)) {
-      const int st_next = rounds.sub(++round, wave);
-      SubTile tn = no_tile();
-      if (st_next < st_end) tn = locate(st_next);
-      if (tn.vmask != 0u) {
-        wait_lds_reads();
-        issue_subtile<D>(Kh, p.ksn, tn, nxt, lane);
-        issue_subtile<D>(Vh, p.vsn, tn, nxt + G::kStageBytes, lane);
+    // One stage, whose K and V rows travel separately (see wide_attn_kernel): the next K rows are requested as soon as the present ones
+    // are in registers, then the V rows likewise.  No barrier: the slots are private to the wavefront.
+    // SPILL: the logits go out behind the request of the next V rows.  A whole sub-tile is two stores; they are counted, so that
+    // nothing waits for them; those of a ragged one count for nothing and are waited for.
+    constexpr int kStores = 2;
+    SubTile tn = list.take();
+    bool stored = false;  // two stores behind the V rows under way
+    for (int i = 0; i < rounds.n_rounds; ++i) {
+      const bool here = t.vmask != 0u, more = tn.vmask != 0u;  // wave-uniform
+      floatx4 acc[2];
+      bf16x8 kop[2][G::kKSteps], vop[G::kColTiles], pb;
+      if (here) {
+        if (SPILL && stored)
+          wait_loads_but<G::kLoads + kStores>();
+        else
+          wait_loads_but<G::kLoads>();  // all but the V rows
+        read_k_operands16<D>(kop, stageK, lane);
       }
-      if (t.vmask != 0u) consume(cur, cur + G::kStageBytes, t.vmask, t.row0);
-      wait_loads();
-      // the logits go out after the wait, not before it: the stores then have the whole next step to complete
-      // instead of being waited for together with the loads
-      if (SPILL && t.vmask != 0u) spill_logits(p.logits_out, h, p.dense_rows, t.row0, kept_logits, p.scale_log2, lane);
+      if (more) issue_subtile<D>(Kh, p.ksn, tn, stageK, lane);
+      if (here) {
+#pragma unroll
+        for (int kt = 0; kt < 2; ++kt) {
+          acc[kt] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int kk = 0; kk < G::kKSteps; ++kk) acc[kt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kop[kt][kk], q[kk], acc[kt], 0, 0, 0);
+        }
+        float ps[8];
+        const float alpha = softmax_step(acc, t.vmask, g, p.scale_log2, m_run, l_run, ps);
+        if (!first && __ballot(alpha != 1.f) != 0ull) {
+#pragma unroll
+          for (int ct = 0; ct < G::kColTiles; ++ct) o[ct] *= alpha;
+        }
+        pb = pack_bf16x8(ps);
+        first = false;
+        if (!more)
+          wait_loads();
+        else if (SPILL && stored)
+          wait_loads_but<G::kLoads + kStores>();
+        else
+          wait_loads_but<G::kLoads>();  // all but the next K rows
+        read_v_operands16<D>(vop, stageV, lane);
+      }
+      if (more) issue_subtile<D>(Vh, p.vsn, tn, stageV, lane);
+      if (here) {
+#pragma unroll
+        for (int ct = 0; ct < G::kColTiles; ++ct) o[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vop[ct], pb, o[ct], 0, 0, 0);
+        if (SPILL) spill_logits(p.logits_out, h, p.dense_rows, t.row0, acc, p.scale_log2, lane);
+      }
+      stored = here && t.vmask == 0xffffffffu;
       t = tn;
-    };
-    char* mineA = ldsA + wave * kBufBytes;
-    char* mineB = ldsB + wave * kBufBytes;
-    wait_loads();  // the first sub-tile
-    while (round < rounds.n_rounds) {
-      step(mineA, mineB);
-      if (round < rounds.n_rounds) step(mineB, mineA);
+      tn = list.take();
     }
   }
 
@@ -901,15 +1055,75 @@ __global__ __launch_bounds__(256, (FUSE & 2) == 0 ? 2 : 1) void sparse_attn_kern
   }
 }
 
+// All operands of a sub-tile for the 32x32 tiles (read_k_operands16).
+template <int D>
+__device__ __forceinline__ void read_k_operands32(bf16x8 (&k)[D / 16], const char* stageK, int lane) {
+  const uint32_t a = lds_address(stageK) + stage_off<D>(lane & 31, lane >> 5);  // chunk 2 ks + hh: 32 ks added to the swizzled place
+  if constexpr (D == 128) {
+    asm volatile(
+        "ds_read_b128 %0, %8\n\tds_read_b128 %1, %9\n\tds_read_b128 %2, %10\n\tds_read_b128 %3, %11\n\t"
+        "ds_read_b128 %4, %12\n\tds_read_b128 %5, %13\n\tds_read_b128 %6, %14\n\tds_read_b128 %7, %15\n\ts_waitcnt lgkmcnt(0)"
+        : "=&v"(k[0]), "=&v"(k[1]), "=&v"(k[2]), "=&v"(k[3]), "=&v"(k[4]), "=&v"(k[5]), "=&v"(k[6]), "=&v"(k[7])
+        : "v"(a), "v"(a ^ 32u), "v"(a ^ 64u), "v"(a ^ 96u), "v"(a ^ 128u), "v"(a ^ 160u), "v"(a ^ 192u), "v"(a ^ 224u)
+        : "memory");
+  } else {
+    asm volatile(
+        "ds_read_b128 %0, %4\n\tds_read_b128 %1, %5\n\tds_read_b128 %2, %6\n\tds_read_b128 %3, %7\n\ts_waitcnt lgkmcnt(0)"
+        : "=&v"(k[0]), "=&v"(k[1]), "=&v"(k[2]), "=&v"(k[3])
+        : "v"(a), "v"(a ^ 32u), "v"(a ^ 64u), "v"(a ^ 96u)
+        : "memory");
+  }
+}
+template <int D>
+__device__ __forceinline__ void read_v_operands32(bf16x8 (&v)[2][D / 32], const char* stageV, int lane) {
+  const int s = lane & 15, b = lane >> 4;
+  const int row = 4 * (b >> 1) + (s >> 2), col = 16 * (b & 1) + 4 * (s & 3);
+  const uint32_t a = lds_address(stageV) + vstage_off<D>(row, col >> 3) + (col & 7) * 2;  // d tile dt: chunk 4 dt further, k-step ks: row 16 ks
+  shortx4 r[2][D / 32][2];
+  if constexpr (D == 128) {
+    asm volatile(
+        "ds_read_b64_tr_b16 %0, %16\n\tds_read_b64_tr_b16 %1, %16 offset:2048\n\t"
+        "ds_read_b64_tr_b16 %2, %17\n\tds_read_b64_tr_b16 %3, %17 offset:2048\n\t"
+        "ds_read_b64_tr_b16 %4, %18\n\tds_read_b64_tr_b16 %5, %18 offset:2048\n\t"
+        "ds_read_b64_tr_b16 %6, %19\n\tds_read_b64_tr_b16 %7, %19 offset:2048\n\t"
+        "ds_read_b64_tr_b16 %8, %16 offset:4096\n\tds_read_b64_tr_b16 %9, %16 offset:6144\n\t"
+        "ds_read_b64_tr_b16 %10, %17 offset:4096\n\tds_read_b64_tr_b16 %11, %17 offset:6144\n\t"
+        "ds_read_b64_tr_b16 %12, %18 offset:4096\n\tds_read_b64_tr_b16 %13, %18 offset:6144\n\t"
+        "ds_read_b64_tr_b16 %14, %19 offset:4096\n\tds_read_b64_tr_b16 %15, %19 offset:6144\n\ts_waitcnt lgkmcnt(0)"
+        : "=&v"(r[0][0][0]), "=&v"(r[0][0][1]), "=&v"(r[0][1][0]), "=&v"(r[0][1][1]), "=&v"(r[0][2][0]), "=&v"(r[0][2][1]),
+          "=&v"(r[0][3][0]), "=&v"(r[0][3][1]), "=&v"(r[1][0][0]), "=&v"(r[1][0][1]), "=&v"(r[1][1][0]), "=&v"(r[1][1][1]),
+          "=&v"(r[1][2][0]), "=&v"(r[1][2][1]), "=&v"(r[1][3][0]), "=&v"(r[1][3][1])
+        : "v"(a), "v"(a ^ 64u), "v"(a ^ 128u), "v"(a ^ 192u)
+        : "memory");
+  } else {
+    asm volatile(
+        "ds_read_b64_tr_b16 %0, %8\n\tds_read_b64_tr_b16 %1, %8 offset:1024\n\t"
+        "ds_read_b64_tr_b16 %2, %9\n\tds_read_b64_tr_b16 %3, %9 offset:1024\n\t"
+        "ds_read_b64_tr_b16 %4, %8 offset:2048\n\tds_read_b64_tr_b16 %5, %8 offset:3072\n\t"
+        "ds_read_b64_tr_b16 %6, %9 offset:2048\n\tds_read_b64_tr_b16 %7, %9 offset:3072\n\ts_waitcnt lgkmcnt(0)"
+        : "=&v"(r[0][0][0]), "=&v"(r[0][0][1]), "=&v"(r[0][1][0]), "=&v"(r[0][1][1]), "=&v"(r[1][0][0]), "=&v"(r[1][0][1]),
+          "=&v"(r[1][1][0]), "=&v"(r[1][1][1])
+        : "v"(a), "v"(a ^ 64u)
+        : "memory");
+  }
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+    for (int dt = 0; dt < D / 32; ++dt) {
+      struct { shortx4 a, b; } both = {r[ks][dt][0], r[ks][dt][1]};
+      v[ks][dt] = __builtin_bit_cast(bf16x8, both);
+    }
+}
+
 // One staged sub-tile of 32 keys against a tile of 32 queries (32x32x16 MFMA), into the running softmax.
 //   S^T = K Q^T   lane (query = lane % 32, hh = lane / 32), register v: logit of key 8 (v / 4) + 4 hh + v % 4
 //   O^T = V^T P^T the same registers, packed to bf16, are the B operand of k-step v / 8
 // k_operand(ks) / v_operand(dt, ks) supply the A operands; l_run is this lane's share of the row sum (its 16 of the 32 keys).
 // r_run is the same for the probabilities as they enter the PV product, rounded to bf16.  SUMS: bit 0 l_run, bit 1 r_run is kept.
-template <int D, int SUMS, class KOp, class VOp>
-__device__ __forceinline__ void attend_subtile32(const KOp k_operand, const VOp v_operand, const bf16x8 (&q)[D / 16], uint32_t vmask,
-                                                 int hh, float scale_log2, float& m_run, float& l_run, float& r_run,
-                                                 floatx16 (&o)[D / 32]) {
+// First half: logits, running maximum and sums (l_run; r_run is only rescaled), the probabilities ps.
+template <int D, int SUMS, class KOp>
+__device__ __forceinline__ void probabilities32(const KOp k_operand, const bf16x8 (&q)[D / 16], uint32_t vmask, int hh, float scale_log2,
+                                                float& m_run, float& l_run, float& r_run, floatx16 (&o)[D / 32], float (&ps)[16]) {
   constexpr int kKS = D / 16, kDT = D / 32;
   floatx16 acc;
 #pragma unroll
@@ -935,7 +1149,6 @@ __device__ __forceinline__ void attend_subtile32(const KOp k_operand, const VOp 
     for (int dt = 0; dt < kDT; ++dt) o[dt] *= alpha;
     m_run = m_new;
   }
-  float ps[16];
 #pragma unroll
   for (int v = 0; v < 16; ++v) ps[v] = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[v], scale_log2, -m_use));
   if (SUMS & 1) {
@@ -944,10 +1157,22 @@ __device__ __forceinline__ void attend_subtile32(const KOp k_operand, const VOp 
     for (int v = 2; v < 16; v += 2) sum += ps[v] + ps[v + 1];
     l_run += sum;
   }
+}
+// the eight of k-step ks, packed
+__device__ __forceinline__ uint4 pack_probabilities(const float (&ps)[16], int ks) {
+  return make_uint4(cvt_pk_bf16(ps[8 * ks], ps[8 * ks + 1]), cvt_pk_bf16(ps[8 * ks + 2], ps[8 * ks + 3]),
+                    cvt_pk_bf16(ps[8 * ks + 4], ps[8 * ks + 5]), cvt_pk_bf16(ps[8 * ks + 6], ps[8 * ks + 7]));
+}
+template <int D, int SUMS, class KOp, class VOp>
+__device__ __forceinline__ void attend_subtile32(const KOp k_operand, const VOp v_operand, const bf16x8 (&q)[D / 16], uint32_t vmask,
+                                                 int hh, float scale_log2, float& m_run, float& l_run, float& r_run,
+                                                 floatx16 (&o)[D / 32]) {
+  constexpr int kDT = D / 32;
+  float ps[16];
+  probabilities32<D, SUMS>(k_operand, q, vmask, hh, scale_log2, m_run, l_run, r_run, o, ps);
 #pragma unroll
   for (int ks = 0; ks < 2; ++ks) {
-    const uint4 pk = make_uint4(cvt_pk_bf16(ps[8 * ks], ps[8 * ks + 1]), cvt_pk_bf16(ps[8 * ks + 2], ps[8 * ks + 3]),
-                                cvt_pk_bf16(ps[8 * ks + 4], ps[8 * ks + 5]), cvt_pk_bf16(ps[8 * ks + 6], ps[8 * ks + 7]));
+    const uint4 pk = pack_probabilities(ps, ks);
     if (SUMS & 2) r_run += add_bf16_pair(add_bf16_pair(0.f, pk.x), pk.y) + add_bf16_pair(add_bf16_pair(0.f, pk.z), pk.w);
     const bf16x8 pb = as_bf16x8(pk);
 #pragma unroll
@@ -974,39 +1199,41 @@ __device__ __forceinline__ void store_o_tile(char* dst, const floatx16 (&o)[D / 
 }
 
 // More than 16 queries: the same work decomposition as the 16-query kernel — a sub-tile goes from the memory request to the
-// MFMAs in one slot of LDS, four slots per workgroup — with 32-query tiles on v_mfma_f32_32x32x16_bf16.  A 32x32 tile takes
+// MFMAs in one slot of LDS — with 32-query tiles on v_mfma_f32_32x32x16_bf16.  A 32x32 tile takes
 // half the LDS operand reads and half the MFMA instructions of two 16-query tiles, so that the QK^T -> softmax -> PV chain of
-// an in-order wavefront fits into the time its share of HBM needs for the next sub-tile (attend_subtile32).
+// an in-order wavefront fits into the time its share of HBM needs for the next sub-tile (probabilities32, add_values32).
 // NT = 1 (up to 32 queries per query group), four wavefronts: a wavefront owns its slot; no barrier in the key loop.
 // NT = 2 (up to 64), eight wavefronts: wavefronts s and s + 4 share slot s, each stages half of its rows (K / V) and carries
-//   one query tile; one barrier per round.  (One wavefront with both tiles needs 128 accumulator registers outside the
+//   one query tile; two stages per slot, one barrier per round.  (One wavefront with both tiles needs 128 accumulator registers outside the
 //   vector registers, and copying them for the rescale made its chain longer than the memory time.)  The second tile's
 //   wavefronts only stage when the device-side count leaves it empty.
-// MODE bit 0: Top-C in the prologue.  Bit 1: a slot walks several sub-tiles (key loop).  Bit 2 (with bit 1): two stages per
-// slot, the next sub-tile's rows travel while the current one is multiplied, one workgroup per compute unit; without it (NT =
-// 1) the operands are all read into registers before the next sub-tile is requested into the same stage, and two workgroups
-// per compute unit cover each other: better where several query groups share rows in the L2 and the loads return fast.
-// Bit 3: the rows are read by several query groups and should stay in the L2.  Bits 4 and 5 (with bit 0): more than 256 blocks to rank, up to
-// kFusedManyBlocks or kFusedMaxBlocks.
+// MODE bit 0: Top-C in the prologue.  Bit 1: a slot walks several sub-tiles (key loop).  Bit 3: the rows are read by several query groups
+// and should stay in the L2.  Bits 4 and 5 (with bit 0): more than 256 blocks to rank, up to kFusedManyBlocks or kFusedMaxBlocks.
+// NT = 1 has one stage per slot, whose K and V rows travel separately: the next K rows are requested as soon as the present ones are in
+// registers, then the V rows likewise, so that a wavefront always has one of the two under way.  Loads alone, in that order, read 538 MB in
+// 77 us (7.0 TB/s); a pair of K and V requested at a time, when the pair before it has come, 80 us.  With the products around them what is left of that is
+// (two stages per slot, pairs, before): 8256 keys, 32 heads, 28 queries 30.7 -> 29.9 us a call; 256 of 512 blocks, 256 response rows and
+// 327 sinks, 25 queries 54.9 -> 54.0; 32 832 keys the same.  The rows of several query groups come from the L2, where waiting for both at
+// once is the better one (196 queries on 4 K/V heads, 16 640 keys 25.9 and 26.3).
 // Bound by HBM.  32 heads, 32 832 keys, all kept: 87 us with 28 queries (6.2 TB/s; 16-query tiles on shared sub-tiles took 94),
-// 93 us with 64 (101); half of the 64-row blocks and 327 sinks: 51 us (57); 4 K/V heads, 196 queries, 16 640 keys: 28 us (42).
+// 93 us with 64 (101); half of the 64-row blocks and 327 sinks: 51 us (57).
 // Grid: one list (list_index).  Workgroups go to the XCDs round-robin, so the query groups of one (head, key split) pair are
 // placed eight apart: they run on the same XCD at about the same time and its L2 serves their common K/V rows.
 template <int D, int NT, int MODE>
-__global__ __launch_bounds__(256 * NT, NT == 2 || (MODE & 4) == 0 ? 2 : 1) void wide_attn_kernel(WIDE_FIRST_PARAMS, const AttnArgs args) {
+__global__ __launch_bounds__(256 * NT, 2) void wide_attn_kernel(WIDE_FIRST_PARAMS, const AttnArgs args) {
   AttnArgs p = with_first(args, rel_part, active_idx, Q, counts, n_b, H, max_active, args.n_gen, n_split, n_sub);
   p.q_groups = q_groups;
   using G = Geo<D>;
-  constexpr bool FUSED = (MODE & 1) != 0, PIPE = (MODE & 2) != 0, DOUBLE = (MODE & 4) != 0;
+  constexpr bool FUSED = (MODE & 1) != 0, PIPE = (MODE & 2) != 0;
+  constexpr bool DOUBLE = NT == 2 && PIPE;                   // two stages per slot
+  constexpr bool APART = NT == 1 && PIPE && (MODE & 8) == 0;  // K and V rows travel separately
   constexpr int BLOCKS = (MODE & 32) != 0 ? kFusedMaxBlocks : ((MODE & 16) != 0 ? kFusedManyBlocks : 256);
-  static_assert(!DOUBLE || PIPE, "two stages are for the key loop");
-  static_assert(NT == 1 || DOUBLE || !PIPE, "a shared slot needs the second stage");
   constexpr int kPolicy = (MODE & 8) != 0 ? 0 : kStreamPolicy;
   constexpr int kKS = D / 16, kDT = D / 32;
   constexpr int kBufBytes = 2 * G::kStageBytes;  // K stage + V stage of a sub-tile
   constexpr int kOChunks = D / 4;                // 16-byte chunks of one fp32 output row
   static_assert(32 * D * 4 <= kBufBytes, "an O tile fits a slot");
-  __shared__ __attribute__((aligned(16))) char ldsA[kWavesPerGroup * kBufBytes];
+  __shared__ __attribute__((aligned(256))) char ldsA[kWavesPerGroup * kBufBytes];
   __shared__ __attribute__((aligned(16))) char ldsB[DOUBLE ? kWavesPerGroup * kBufBytes : 16];
   __shared__ float2 ml_sh[kWavesPerGroup][32];
   __shared__ __attribute__((aligned(16))) char topk_raw[FUSED ? sizeof(TopkShared) : 16];
@@ -1081,7 +1308,8 @@ __global__ __launch_bounds__(256 * NT, NT == 2 || (MODE & 4) == 0 ? 2 : 1) void 
     if (NT > 1) __syncthreads();
   };
   char* slotA = ldsA + slot * kBufBytes;
-  SubTile t = locate(PIPE ? rounds.sub(0, slot) : split * kWavesPerGroup + slot);
+  RoundList<typename Kept::Id> list{p, rounds, uni, kept_blocks, slot, lane, few_sinks};
+  SubTile t = APART ? list.take() : locate(PIPE ? rounds.sub(0, slot) : split * kWavesPerGroup + slot);
   request(t, slotA);
   if (!FUSED) load_q();
   const int n_act = counted.n_active(p);
@@ -1113,6 +1341,37 @@ __global__ __launch_bounds__(256 * NT, NT == 2 || (MODE & 4) == 0 ? 2 : 1) void 
     staged();
     if (t.vmask != 0u && tile_live)
       consume([&](int ks) { return k_at(slotA, ks); }, [&](int dt, int ks) { return v_at(slotA, dt, ks); }, t.vmask);
+  } else if constexpr (APART) {
+    SubTile tn = list.take();
+    for (int i = 0; i < rounds.n_rounds; ++i) {
+      const bool here = t.vmask != 0u, more = tn.vmask != 0u;  // wave-uniform
+      bf16x8 kop[kKS], vop[2][kDT], pb[2];
+      if (here) {
+        wait_loads_but<G::kLoads>();  // all but the V rows
+        read_k_operands32<D>(kop, slotA, lane);
+      }
+      if (more) issue_subtile<D, false, kPolicy>(Kh, p.ksn, tn, slotA, lane);
+      if (here) {
+        float ps[16];
+        probabilities32<D, 1>([&](int ks) { return kop[ks]; }, q, t.vmask, hh, p.scale_log2, m_run, l_run, l_run, o, ps);
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) pb[ks] = as_bf16x8(pack_probabilities(ps, ks));
+        if (more)
+          wait_loads_but<G::kLoads>();  // all but the next K rows
+        else
+          wait_loads();
+        read_v_operands32<D>(vop, slotA + G::kStageBytes, lane);
+      }
+      if (more) issue_subtile<D, true, kPolicy>(Vh, p.vsn, tn, slotA + G::kStageBytes, lane);
+      if (here) {
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+          for (int dt = 0; dt < kDT; ++dt) o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vop[ks][dt], pb[ks], o[dt], 0, 0, 0);
+      }
+      t = tn;
+      tn = list.take();
+    }
   } else {
     SubTile tn = locate(rounds.sub(1, slot));
     int i = 0;
@@ -1316,11 +1575,11 @@ static hipError_t launch_attn_t(const AttnArgs& a, const SplitPlan& p, bool fuse
     if (a.logits_out != nullptr) return hipErrorInvalidValue;  // logits are spilled for one 16-query tile only
     if (query_group_list(p, a.H) > kMaxList) return hipErrorInvalidValue;
     if (p.q_tiles_per_group > 2)
-      launch_wide_t<D, 2, 2 | 4>(a, p, fused, st);
+      launch_wide_t<D, 2, 2>(a, p, fused, st);
     else if (p.q_groups > 1)
       launch_wide_t<D, 1, 2 | 8>(a, p, fused, st);
     else
-      launch_wide_t<D, 1, 2 | 4>(a, p, fused, st);
+      launch_wide_t<D, 1, 2>(a, p, fused, st);
   } else if (a.logits_out != nullptr) {  // dense probe layer with the logits spilled
     if (fused) return hipErrorInvalidValue;
     if (p.pipelined)

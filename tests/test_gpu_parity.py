@@ -479,6 +479,38 @@ def test_sparse_attn_heads_begin_at_different_places(G, H, M, N, d, n_act):
     assert np.allclose(lse.cpu().numpy(), ref_lse, atol=2e-3)
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("n_act,M", [
+    (16, 8180), (30, 8180),     # 64 rounds per slot, the last one ragged
+    (16, 8200), (30, 8200),     # 65: the table of the sub-tiles is made twice
+])
+def test_key_loop_of_many_rounds(G, d, n_act, M):
+    """One key split of four slots, with block ids outside the prompt in between (rounds in which a slot has nothing to do), responses and
+    more sinks than one sub-tile holds; the probe layer, which writes its logits on the way, over the same rows."""
+    H, N, B = 257, 3, 32
+    q, k, v = (_rand_bf16(85 + i, H, r, d).to(G.DEV) for i, r in enumerate((n_act, M + N, M + N)))
+    act, n_b = np.arange(n_act), -(-M // B)
+    kept = np.arange(n_b)
+    skipped = np.concatenate([np.arange(3, n_b, 41), np.arange(100, 104)])
+    listed = kept.copy()
+    listed[skipped] = np.where(np.arange(len(skipped)) % 2, -1, n_b + 5)
+    sinks = np.sort(np.concatenate([skipped * B + 1, np.arange(0, M, 300)]))
+    out, lse = G.gpu_sparse_attn(q, G.i32(act), None, k, v, M, B, G.i32(listed), G.i32(sinks))
+    some = [0, 1, 128, 256]
+    I_p = fo.attention_index_set(sinks, np.setdiff1d(kept, skipped), M, B)
+    ref, ref_lse = fo.sparse_attention(G.to_np(q[some]), act, G.to_np(k[some]), G.to_np(v[some]), I_p, M)
+    G.assert_attention_close(out[some], ref)
+    assert np.allclose(lse[some].cpu().numpy(), ref_lse, atol=2e-3)
+    out, lse, col, top = G.gpu_probe_layer(q, G.i32(act), None, k, v, M, B, 4)
+    ref, ref_lse = fo.sparse_attention(G.to_np(q[some]), act, G.to_np(k[some]), G.to_np(v[some]), np.arange(M), M)
+    G.assert_attention_close(out[some], ref)
+    assert np.allclose(lse[some].cpu().numpy(), ref_lse, atol=2e-3)
+    logits = torch.matmul(q.float(), k.float().transpose(1, 2).contiguous()) / d ** 0.5
+    mass = torch.softmax(logits, -1).mean((0, 1))
+    assert torch.allclose(col, mass, rtol=2e-4, atol=1e-9)   # the bar of test_find_sinks
+    assert top.cpu().tolist() == fo.select_sinks(col.cpu().numpy().astype(np.float64), M, 4).tolist()
+
+
 def test_sparse_attn_dense_reduction(G):
     # keep every block, every row a query: plain bidirectional attention over all M+N keys
     H, M, N, d, B, n_gen = 4, 3000, 72, 128, 128, 64
