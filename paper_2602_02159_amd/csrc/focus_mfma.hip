@@ -2241,7 +2241,8 @@ __device__ __forceinline__ SubTile key_subtile(int st, int L) {
 // over K) together with the per-split softmax statistics.
 // SELECT: every wavefront makes the query selection itself, beside its first K rows, instead of reading what a launch of its own
 // has written; the first workgroup writes the lists for everyone else (a step of 4 heads at 1K: one launch of 3 us less).
-template <int D, bool SELECT>
+// STAGES = 2: the sub-tile after the next travels as well; which launches take it, and what it gives, at logits_in_two_stages.
+template <int D, bool SELECT, int STAGES>
 __global__ __launch_bounds__(256, 2) void qk_logits_kernel(const uint16_t* K, int64_t ksh, int64_t ksn, const int32_t* active_idx, int L,
                                                            int n_sub, int n_split, int max_active, int n_gen, const LogitArgs args) {
   LogitArgs p = args;  // what the first requests need comes in registers, as in the attention kernels
@@ -2255,7 +2256,7 @@ __global__ __launch_bounds__(256, 2) void qk_logits_kernel(const uint16_t* K, in
   p.max_active = max_active;
   p.n_gen = n_gen;
   using G = Geo<D>;
-  __shared__ __attribute__((aligned(16))) char lds[kWavesPerGroup * G::kStageBytes];
+  __shared__ __attribute__((aligned(256))) char lds[STAGES * kWavesPerGroup * G::kStageBytes];
   __shared__ float ml_sh[kWavesPerGroup][16][2];
 
   const int lane = threadIdx.x & 63;
@@ -2286,7 +2287,46 @@ __global__ __launch_bounds__(256, 2) void qk_logits_kernel(const uint16_t* K, in
   mask_q_tile<D>(q, 0, n_act, lane);
 
   float m_run = -INFINITY, l_run = 0.f;
-  while (st < st_end) {
+  if constexpr (STAGES == 2) {
+    constexpr int kStores = 2;  // of a whole sub-tile's logits: counted, so that nothing waits for them; a ragged one's are waited for
+    char *here = stageK, *there = stageK + kWavesPerGroup * G::kStageBytes;
+    int next = st + st_step;
+    SubTile tn = key_subtile(next < st_end ? next : 0, p.L);
+    if (next < st_end) issue_subtile<D>(Kh, p.ksn, tn, there, lane);
+    bool stored = false;  // the stores behind the rows under way
+    while (st < st_end) {
+      if (next >= st_end)
+        wait_loads();
+      else if (stored)
+        wait_loads_but<G::kLoads + kStores>();
+      else
+        wait_loads_but<G::kLoads>();
+      bf16x8 kop[2][G::kKSteps];
+      read_k_operands16<D>(kop, here, lane);
+      const int after = next + st_step;
+      const SubTile ta = key_subtile(after < st_end ? after : 0, p.L);
+      if (after < st_end) issue_subtile<D>(Kh, p.ksn, ta, here, lane);
+      floatx4 acc[2];
+#pragma unroll
+      for (int kt = 0; kt < 2; ++kt) {
+        acc[kt] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kk = 0; kk < G::kKSteps; ++kk) acc[kt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kop[kt][kk], q[kk], acc[kt], 0, 0, 0);
+      }
+      float ps[8];
+      softmax_step(acc, t.vmask, g, p.scale_log2, m_run, l_run, ps);
+      spill_logits(p.logits, h, p.L, t.row0, acc, p.scale_log2, lane);
+      stored = after < st_end && t.vmask == 0xffffffffu;
+      t = tn;
+      tn = ta;
+      st = next;
+      next = after;
+      char* const other = here;
+      here = there;
+      there = other;
+    }
+  }
+  while (st < st_end) {  // (STAGES = 1)
     const SubTile cur = t;
     wait_loads();
     floatx4 acc[2];
@@ -2550,16 +2590,31 @@ __global__ __launch_bounds__(256, NT == 1 ? 4 : 2) void wide_logits_kernel(const
   }
 }
 
+// One query tile: two stages per wavefront where the workgroups (two of them share a compute unit then, four with one stage) are
+// resident at once all the same, or are many and long.  Sink chain with one stage and with two: 32 heads, 8256 keys, 16 splits 29.4 and
+// 28.7 us, 4160 keys, 8 splits 20.9 and 19.9; 16 heads, 8256 keys 20.2 and 19.2; 4 heads, 32 832 keys 21.1 and 20.2; 32 heads, 131 136
+// keys, 4096 workgroups of eight rounds 264 and 259; but 15 986 keys, 1024 workgroups of four rounds 43.4 and 44.2, 32 832 keys, 4128 of
+// two 75.3 and 81.0.
+static bool logits_in_two_stages(const SplitPlan& p, int n_heads) {
+  const int rounds = ceil_div(p.n_sub, kWavesPerGroup);
+  return rounds >= 4 * p.n_split && ((int64_t)p.n_split * n_heads <= 512 || rounds >= 8 * p.n_split);
+}
+
 template <int D>
 static hipError_t launch_logits_t(const LogitArgs& a, const SplitPlan& p, int mode, bool select, hipStream_t st) {
 #define LOGITS_ARGS a.K, a.ksh, a.ksn, a.active_idx, a.L, a.n_sub, a.n_split, a.max_active, a.n_gen
   if (p.q_tiles_per_group == 1) {  // one tile spills its logits, several take two passes
     if (mode != 0) return hipErrorInvalidValue;
     const dim3 grid(p.n_split, a.H);
-    if (select)
-      hipLaunchKernelGGL((qk_logits_kernel<D, true>), grid, dim3(256), 0, st, LOGITS_ARGS, a);
+    const bool two = logits_in_two_stages(p, a.H);
+    if (select && two)
+      hipLaunchKernelGGL((qk_logits_kernel<D, true, 2>), grid, dim3(256), 0, st, LOGITS_ARGS, a);
+    else if (select)
+      hipLaunchKernelGGL((qk_logits_kernel<D, true, 1>), grid, dim3(256), 0, st, LOGITS_ARGS, a);
+    else if (two)
+      hipLaunchKernelGGL((qk_logits_kernel<D, false, 2>), grid, dim3(256), 0, st, LOGITS_ARGS, a);
     else
-      hipLaunchKernelGGL((qk_logits_kernel<D, false>), grid, dim3(256), 0, st, LOGITS_ARGS, a);
+      hipLaunchKernelGGL((qk_logits_kernel<D, false, 1>), grid, dim3(256), 0, st, LOGITS_ARGS, a);
     return hipGetLastError();
   }
   if (mode == 0 || query_group_list(p, a.H) > kMaxList) return hipErrorInvalidValue;

@@ -217,6 +217,25 @@ def test_find_sinks_statistics_of_the_key_splits(G, H, M, N, d, n_act):
     assert np.allclose(S, Sref, rtol=2e-4, atol=1e-9) and S.sum() == pytest.approx(1.0, abs=1e-4)
 
 
+@pytest.mark.parametrize("H,L,d", [
+    (32, 4096, 128),     # four rounds per wavefront everywhere: the fewest that take two stages
+    (32, 4095, 128),     # ... the last sub-tile ragged
+    (32, 4064, 128),     # ... and a sub-tile less: wavefronts of three rounds
+    (32, 4097, 64),      # five rounds in one split, one row in the last
+    (1, 131105, 128),    # 256 splits
+    (600, 9001, 64),     # twelve rounds in 3600 workgroups
+    (33, 8230, 128),     # 462 workgroups; splits of four and of five rounds
+])
+def test_find_sinks_in_two_stages(G, H, L, d):
+    q, k = _rand_bf16(18, H, 16, d).to(G.DEV), _rand_bf16(19, H, L, d).to(G.DEV)
+    col, top = G.gpu_find_sinks(q, G.i32(np.arange(13)), None, k, L - 3, 64, 4)
+    mass = torch.zeros(L, dtype=torch.float64, device=G.DEV)
+    for h in range(H):
+        mass += torch.softmax(q[h, :13].double() @ k[h].double().t() / d ** 0.5, -1).mean(0)
+    assert torch.allclose(col.double(), mass / H, rtol=2e-4, atol=1e-9)      # the bar of test_find_sinks
+    assert top.cpu().tolist() == fo.select_sinks(col.cpu().numpy().astype(np.float64), L - 3, 4).tolist()
+
+
 @pytest.mark.parametrize("n_gen,k,window,lo,hi,cap", [
     (64, 16, 0, 0, 64, 16), (64, 4, 8, 0, 64, 36), (63, 5, 9, 3, 60, 57), (64, 64, 0, 0, 64, 64), (64, 1, 300, 0, 64, 64),
     (1, 1, 0, 0, 1, 1), (33, 8, 2, 10, 11, 8), (65, 4, 2, 0, 65, 12), (200, 30, 3, 0, 200, 90), (64, 3, 200, 63, 64, 20)])
