@@ -28,6 +28,7 @@
 // exponentiated values already sit in B-operand layout for the second product O^T[dcol][query] = V^T . P^T,
 // where the contraction slot (g, e) stands for key 16*(e/4) + 4g + (e%4) of the sub-tile on both operands.
 // The V^T operand is read from the row-major staged tile with the transposing LDS read ds_read_b64_tr_b16.
+#include <algorithm>
 #include <cstdlib>
 #include <type_traits>
 #include <utility>
@@ -1120,6 +1121,8 @@ __device__ __forceinline__ void read_v_operands32(bf16x8 (&v)[2][D / 32], const 
 //   O^T = V^T P^T the same registers, packed to bf16, are the B operand of k-step v / 8
 // k_operand(ks) / v_operand(dt, ks) supply the A operands; l_run is this lane's share of the row sum (its 16 of the 32 keys).
 // r_run is the same for the probabilities as they enter the PV product, rounded to bf16.  SUMS: bit 0 l_run, bit 1 r_run is kept.
+// Bit 2: O is rescaled for every sub-tile, also by one.  Where the compiler kept two copies of O for the two sides of that branch (the
+// 32-query tiles of a block entry at d = 64) the moves between them cost more than the products.
 // First half: logits, running maximum and sums (l_run; r_run is only rescaled), the probabilities ps.
 template <int D, int SUMS, class KOp>
 __device__ __forceinline__ void probabilities32(const KOp k_operand, const bf16x8 (&q)[D / 16], uint32_t vmask, int hh, float scale_log2,
@@ -1141,7 +1144,7 @@ __device__ __forceinline__ void probabilities32(const KOp k_operand, const bf16x
   mx = fmaxf(__uint_as_float(sw.x), __uint_as_float(sw.y)) * scale_log2;
   const float m_new = fmaxf(m_run, mx);
   const float m_use = m_new == -INFINITY ? 0.f : m_new;
-  if (__ballot(m_new != m_run) != 0ull) {  // some running maximum of this wavefront moves (rare after the first sub-tiles)
+  if ((SUMS & 4) || __ballot(m_new != m_run) != 0ull) {  // some running maximum of this wavefront moves (rare after the first sub-tiles)
     const float alpha = __builtin_amdgcn_exp2f(m_run - m_use);
     if (SUMS & 1) l_run *= alpha;
     if (SUMS & 2) r_run *= alpha;
@@ -1978,8 +1981,11 @@ __global__ __launch_bounds__(64 * kRefreshWaves, 2) void refresh_attn_kernel(con
 // The workgroups behind those of the tail tiles make the layer's cache refresh, two chunks each (copy; none without it): the tiles
 // rarely fill the chip and leave the memory idle, while the copy needs nothing else.  32 heads: 8256 rows, tiles 77 us and copy 48
 // us one after the other, 32 832 rows 282 and 185; 4 heads, 1056 rows, d = 64: a launch less.
+// Bound by the vector ALU: a sub-tile of a tile takes a wavefront about a thousand cycles.  d = 64: O is rescaled for every sub-tile, which takes
+// 90 register moves and 30 registers less than doing it where a maximum has moved, so that two workgroups fit a compute unit.  Block
+// entry: 4 heads, 1056 rows 10.1 -> 9.5 us; 8 heads, 1056 rows 16.7 -> 13.8; 16 heads, 1532 rows 32.5 -> 25.3; 4 heads, 6032 rows 84 -> 67.
 template <int D, bool LSE>
-__global__ __launch_bounds__(64 * kRefreshWaves, 2) void refresh_tail_kernel(const RefreshArgs p, const CacheRefresh copy) {
+__global__ __launch_bounds__(64 * kRefreshWaves, D == 64 ? 4 : 2) void refresh_tail_kernel(const RefreshArgs p, const CacheRefresh copy) {
   using G = Geo<D>;
   constexpr int kKS = D / 16, kDT = D / 32, kOChunks = D / 4;
   constexpr int kBufBytes = 2 * G::kStageBytes;
@@ -2055,7 +2061,7 @@ __global__ __launch_bounds__(64 * kRefreshWaves, 2) void refresh_tail_kernel(con
       for (int dt = 0; dt < kDT; ++dt) vop[ks][dt] = read_v_operand32<D>(stage + G::kStageBytes, dt, ks, lane);
     wait_lds_reads();
     if (t + kRefreshWaves < n_tiles) request(t + kRefreshWaves);
-    attend_subtile32<D, LSE ? 3 : 2>([&](int ks) { return kop[ks]; }, [&](int dt, int ks) { return vop[ks][dt]; }, q,
+    attend_subtile32<D, (LSE ? 3 : 2) | (D == 64 ? 4 : 0)>([&](int ks) { return kop[ks]; }, [&](int dt, int ks) { return vop[ks][dt]; }, q,
                                      low_mask(p.L - t * kSubTile), hh, p.scale_log2, m_run, l_run, r_run, o);
   }
   store_o_tile<D>(stage, o, qi, hh);  // the wavefront's own stage, read for the last time above
@@ -2094,13 +2100,16 @@ __global__ __launch_bounds__(64 * kRefreshWaves, 2) void refresh_tail_kernel(con
 
 // Which query tiles go to which kernel.  Every 256-query block takes the same time, so refresh_attn_kernel runs in rounds of 256
 // blocks (one per compute unit; at d = 64 two fit, and take twice as long), and a round that is mostly empty costs as much as a
-// full one.  refresh_tail_kernel takes single 32-query tiles: an eighth of the key sub-tiles per wavefront, each kTailCost
-// times as long because eight tiles no longer share the staged rows.  Both have a fixed part (first loads, merge).  Three ways
-// to cut, the cheapest is taken (times in us, measured):
+// full one.  refresh_tail_kernel takes single 32-query tiles: an eighth of the key sub-tiles per wavefront, each about twice
+// (d = 64: four times) as long because eight tiles no longer share the staged rows.  At d = 64 two tiles share a compute unit and hardly
+// slow each other down, and 512 of them need not come in whole rounds.  Both have a fixed part (first loads, merge).  Three ways
+// to cut, the cheapest is taken (times in us, measured; the cache refresh is left out, with which the cut must not change):
 //   everything in blocks, the ragged one of each head included;
 //   whole blocks, and the last few tiles of each head to the tail kernel;
 //   whole rounds of blocks, and everything else to the tail kernel.
-// 32 heads, 8256 rows (33 blocks per head, 4.1 rounds): 1213 us all in blocks, 1106 us cut; 4 heads, 1056 rows, d = 64: 26 and 9.
+// 32 heads, 8256 rows (33 blocks per head, 4.1 rounds): 1213 us all in blocks, 1106 us cut; 4 heads, 1056 rows, d = 64: 26 and 8.
+// d = 64, block entry in blocks and in tiles: 32 heads, 1032 rows 35.1 and 29.6; 16 heads, 2032 52.4 and 39.1, 3032 71.3 and 73.2, 4032 95.5 and
+// 118; 8 heads, 4032 85 and 64, 6032 119 and 130.
 // A launch has fewer than 2^32 threads (kMaxGroups workgroups).  More tail tiles than that stay in blocks; more chunks of the cache
 // refresh than fit behind the tail tiles (2^24 of them: block 1, 32 heads, half a million rows) get the launch of their own that they
 // have where there is no tail.
@@ -2108,16 +2117,16 @@ template <int D>
 static hipError_t launch_refresh_t(RefreshArgs& a, const focus_shape& s, const CacheRefresh* copy, hipStream_t st) {
   constexpr int kSlots = 256;
   constexpr int64_t kMaxGroups = ((int64_t(1) << 32) - 1) / (64 * kRefreshWaves);
-  constexpr float kPerSubTile = D == 128 ? 0.85f : 0.6f, kTailCost = D == 128 ? 1.9f : 1.7f, kFixed = 5.f;
   const int tiles = ceil_div(s.n_gen, 32), last = tiles % kRefreshWaves;
-  const float keys_time = (float)ceil_div(s.n_ctx + s.n_resp, kSubTile) * kPerSubTile;
-  const float block_time = keys_time + kFixed, tail_time = keys_time * kTailCost / kRefreshWaves + kFixed;
+  const float sub = (float)ceil_div(s.n_ctx + s.n_resp, kSubTile);
+  const float block_time = D == 128 ? 0.85f * sub + 5.f : 0.5f * sub + 12.f, tail_time = D == 128 ? 0.2f * sub + 5.f : 0.23f * sub + 3.f;
   auto rounds = [](int64_t n) { return (float)((n + kSlots - 1) / kSlots); };
+  auto tail_rounds = [&](int64_t n) { return D == 128 || n == 0 ? rounds(n) : std::max(1.f, (float)n / (2 * kSlots)); };
   const int64_t whole = (int64_t)(tiles / kRefreshWaves) * s.n_heads, padded = (int64_t)ceil_div(tiles, kRefreshWaves) * s.n_heads;
   const int64_t ragged = (int64_t)last * s.n_heads, rest = whole % kSlots;
   const float t_padded = rounds(padded) * block_time;
-  const float t_whole = rounds(whole) * block_time + rounds(ragged) * tail_time;
-  const float t_rounds = rounds(whole - rest) * block_time + rounds(rest * kRefreshWaves + ragged) * tail_time;
+  const float t_whole = rounds(whole) * block_time + tail_rounds(ragged) * tail_time;
+  const float t_rounds = rounds(whole - rest) * block_time + tail_rounds(rest * kRefreshWaves + ragged) * tail_time;
   a.n_heads = s.n_heads;
   const bool tails_fit = rest * kRefreshWaves + ragged + 7 <= kMaxGroups;
   if (!tails_fit || (t_padded <= t_whole && t_padded <= t_rounds)) {
@@ -2142,10 +2151,13 @@ static hipError_t launch_refresh_t(RefreshArgs& a, const focus_shape& s, const C
     copy = nullptr;
   }
   const dim3 grid((uint32_t)(copy ? tails + copies : tails)), block(64 * kRefreshWaves);
+  // d = 64: a few tiles among many chunks, which is what long prompts leave over, have a compute unit each (LDS that nobody uses sees to
+  // it): they are the last to finish, and a chunk beside them costs more than it gains (32 heads, 8256 rows 694 us, 698 without).
+  const uint32_t alone = D == 64 && copy && a.n_tail <= kSlots / 2 ? 32768 : 0;
   if (a.lse)
-    hipLaunchKernelGGL((refresh_tail_kernel<D, true>), grid, block, 0, st, a, copy ? *copy : CacheRefresh{});
+    hipLaunchKernelGGL((refresh_tail_kernel<D, true>), grid, block, alone, st, a, copy ? *copy : CacheRefresh{});
   else
-    hipLaunchKernelGGL((refresh_tail_kernel<D, false>), grid, block, 0, st, a, copy ? *copy : CacheRefresh{});
+    hipLaunchKernelGGL((refresh_tail_kernel<D, false>), grid, block, alone, st, a, copy ? *copy : CacheRefresh{});
   return hipGetLastError();
 }
 

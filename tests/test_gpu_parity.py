@@ -1285,6 +1285,30 @@ def test_refresh_attn_cut_into_blocks_and_tiles(G, H, n_q, L, d):
     assert np.allclose(lse.cpu().numpy(), torch.logsumexp(s, -1).numpy(), atol=2e-3)
 
 
+@pytest.mark.parametrize("offset", [0.0, 40.0])      # 40: the maximum of a row moves with nearly every sub-tile
+@pytest.mark.parametrize("H,n_q,L", [
+    (8, 1024, 255),      # 256 tiles of 64 columns: one per compute unit; a sub-tile per wavefront, the last ragged
+    (9, 1000, 257),      # 288: two of them share some; a second sub-tile for one wavefront
+    (8, 2080, 2080),     # 520: more than are resident at once
+    (32, 1032, 1032),    # whole blocks and a ragged one of 32 heads, all as tiles
+])
+def test_refresh_attn_tiles_of_64_columns(G, H, n_q, L, offset):
+    d = 64
+    q, k, v = (_rand_bf16(191 + i, H, r, d).to(G.DEV) for i, r in enumerate((n_q, L, L)))
+    k += (offset / L * torch.arange(L, device=G.DEV)[None, :, None] * torch.sign(q[:, :1].float())).to(torch.bfloat16)
+    out = torch.full((H, n_q, d), float("nan"), dtype=torch.bfloat16, device=G.DEV)
+    lse = torch.full((H, n_q), float("nan"), dtype=torch.float32, device=G.DEV)
+    fb.refresh_attn(q, k, v, fb.make_shape(q, k, v, L, 64, out), out, lse)
+    Q, K, V = (t.float().cpu() for t in (q, k, v))
+    s = torch.matmul(Q, K.transpose(1, 2).contiguous()) / math.sqrt(d)
+    G.assert_attention_close(out, torch.matmul(torch.softmax(s, -1), V).numpy())
+    # the log-sum-exps of the tiles are those of unrounded sums; their size scales the fp32 rounding of the logits
+    assert np.allclose(lse.cpu().numpy(), torch.logsumexp(s, -1).numpy(), atol=2e-3, rtol=1e-5)
+    out2 = torch.zeros_like(out)
+    fb.refresh_attn(q, k, v, fb.make_shape(q, k, v, L, 64, out2), out2, None)
+    assert torch.equal(out, out2)
+
+
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("H,n_q,L", [(256, 256, 24), (256, 256, 300), (3, 40, 24), (3, 100, 300)])   # 256-query blocks; single tiles
 def test_refresh_attn_divides_by_the_probabilities_it_adds_up(G, H, n_q, L, d):
