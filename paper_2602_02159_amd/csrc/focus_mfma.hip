@@ -635,7 +635,9 @@ __device__ __forceinline__ void rank_blocks(const AttnArgs& p, const FirstParts<
                                             typename KeptList<true, BLOCKS>::Id* kept_sh, TopkShared& sm, bool writer) {
   constexpr int kPlanes = FirstParts<NP, THREADS, BLOCKS>::kPlanes;
   const int tid = threadIdx.x;
-  const bool tournament = BLOCKS <= 256 && p.n_keep * (THREADS / kWave) <= kWave;  // uniform
+  // more than eight wavefronts (one_split_waves: at most 256 blocks, at most 16 to keep): the first four rank
+  constexpr int kRankWaves = THREADS > 512 ? 4 : THREADS / kWave;
+  const bool tournament = BLOCKS <= 256 && (THREADS > 512 || p.n_keep * kRankWaves <= kWave);  // uniform
   if (!tournament) {
     block_topk_clear<THREADS>(sm);
     __syncthreads();
@@ -671,8 +673,9 @@ __device__ __forceinline__ void rank_blocks(const AttnArgs& p, const FirstParts<
       key = order_key(rel[0]);
       return true;
     };
-    if constexpr (BLOCKS <= 256) block_topk_small<256, true>(keyfn, p.n_b, p.n_keep, kept_sh, nullptr, sm);
-  } else {
+    if constexpr (BLOCKS <= 256)
+      block_topk_small<256, true, (THREADS > 512 ? kRankWaves : 0)>(keyfn, p.n_b, p.n_keep, kept_sh, nullptr, sm);
+  } else if constexpr (THREADS <= 512) {
     uint32_t key1[kPlanes];
 #pragma unroll
     for (int l = 0; l < kPlanes; ++l) key1[l] = tid + l * THREADS < p.n_b ? order_key(rel[l]) + 1u : 0u;
@@ -817,10 +820,11 @@ struct RoundList {
 // wide_attn_kernel with NT = 1 the K and V rows of the one stage travel separately.  Against two stages and a request for the pair: 32
 // heads, 8256 keys 30.3 -> 28.3 us a call, 32 832 keys 86.3 -> 85.1; 8 heads, 16 448 keys 20.6 -> 18.9; 30 of 1024 blocks, whole layer
 // 27.0 -> 26.1; probe layer of 32 832 keys 130.4 -> 128.7.
-// In every case a second, small kernel merges the key splits.  (Letting the last workgroup of a head merge them
-// behind device-scope fences was measured: the fences cost ~10 us per launch, more than the launch they save.)
-template <int D, int FUSE>
-__global__ __launch_bounds__(256, 2) void sparse_attn_kernel(ATTN_FIRST_PARAMS, const AttnArgs args) {
+// WAVES: four, and a second, small kernel merges the key splits.  (Letting the last workgroup of a head merge them
+// behind device-scope fences was measured: the fences cost ~10 us per launch, more than the launch they save.)  Eight, twelve or sixteen
+// for the one workgroup of a head with a short key list, which writes the output itself (one_split_waves); the first 256 threads store.
+template <int D, int FUSE, int WAVES>
+__global__ __launch_bounds__(64 * WAVES, WAVES == 4 ? 2 : WAVES / 4) void sparse_attn_kernel(ATTN_FIRST_PARAMS, const AttnArgs args) {
   const AttnArgs p = with_first(args, ATTN_FIRST_NAMES);
   using G = Geo<D>;
   constexpr bool FUSED = (FUSE & 1) != 0;                // Top-C in the prologue
@@ -830,8 +834,8 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_kernel(ATTN_FIRST_PARAMS, 
   constexpr int BLOCKS = (FUSE & 32) != 0 ? kFusedMaxBlocks : ((FUSE & 16) != 0 ? kFusedManyBlocks : 256);  // FUSED: the most blocks to rank
   constexpr int kBufBytes = 2 * G::kStageBytes;          // one slot: K stage + V stage of a sub-tile
   static_assert(16 * D * 4 <= kBufBytes, "a wavefront's O tile fits its stage");
-  __shared__ __attribute__((aligned(256))) char ldsA[kWavesPerGroup * kBufBytes];
-  __shared__ float2 ml_sh[kWavesPerGroup][16];  // final merge: running maximum and sum per wavefront and query
+  __shared__ __attribute__((aligned(256))) char ldsA[WAVES * kBufBytes];
+  __shared__ float2 ml_sh[WAVES][16];  // final merge: running maximum and sum per wavefront and query
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -857,7 +861,7 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_kernel(ATTN_FIRST_PARAMS, 
   int qrow_early = -1, few_sinks = -1;
   if (FUSED) {
     qrow_early = fetch_q_row(p.active_idx, 0, p.max_active, p.n_gen, lane);
-    FirstParts<PER_HEAD ? 32 : 8, 256, BLOCKS> first;
+    FirstParts<PER_HEAD ? 32 : 8, 64 * WAVES, BLOCKS> first;
     first_partials(first, p, PER_HEAD);
     few_sinks = request_few_sinks(p, lane);
     load_q_tile<D>(q, Qh, p.qsn, qrow_early, lane);
@@ -867,7 +871,8 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_kernel(ATTN_FIRST_PARAMS, 
   }
   __shared__ uint32_t kept_bits_sh[kBitmapBlocks / 32];
   __shared__ int sinks_unsorted_sh;
-  static_assert(D == 128 || PIPE ||
+  static_assert(WAVES == 4 || (!PIPE && BLOCKS <= 256), "one split, a sub-tile per wavefront");
+  static_assert(D == 128 || PIPE || WAVES > 4 ||
                     4 * (sizeof(ldsA) + sizeof(ml_sh) + sizeof(topk_raw) + sizeof(kept_beside) + sizeof(kept_bits_sh) + 16) <= 163840,
                 "four workgroups share a compute unit (kAttnGroupsSmall)");
   const SinkUnion uni = prepare_union(p, split, kept_blocks, kept_bits_sh, &sinks_unsorted_sh);
@@ -878,7 +883,7 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_kernel(ATTN_FIRST_PARAMS, 
   // sub-tile's K and V rows as soon as its block id is known, then the query rows and the device-side count.
   const int st_end = p.n_sub;
   const SplitRounds rounds(p, split, h);
-  const int st = split * kWavesPerGroup + wave;
+  const int st = split * WAVES + wave;
   const int qrow = FUSED ? qrow_early : fetch_q_row(p.active_idx, 0, p.max_active, p.n_gen, lane);
   SubTile t;
   t.kind = 0;
@@ -1012,30 +1017,30 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_kernel(ATTN_FIRST_PARAMS, 
   for (int ct = 0; ct < G::kColTiles; ++ct) *chunk_at(wave, c, 4 * ct + g) = o[ct];
   if (g == 0) ml_sh[wave][c] = make_float2(m_run, l_run);
   __syncthreads();
-  float2 ml[kWavesPerGroup];
-  floatx4 ow[kWavesPerGroup][kVec];
+  float2 ml[WAVES];
+  floatx4 ow[WAVES][kVec];
 #pragma unroll
-  for (int w = 0; w < kWavesPerGroup; ++w) {
-    ml[w] = ml_sh[w][mq];
+  for (int w = 0; w < WAVES; ++w) {
+    ml[w] = ml_sh[w][WAVES == 4 ? mq : mq & 15];
 #pragma unroll
-    for (int i = 0; i < kVec; ++i) ow[w][i] = *chunk_at(w, mq, mc + 16 * i);
+    for (int i = 0; i < kVec; ++i) ow[w][i] = *chunk_at(w, WAVES == 4 ? mq : mq & 15, mc + 16 * i);
   }
   float mmax = ml[0].x;
 #pragma unroll
-  for (int w = 1; w < kWavesPerGroup; ++w) mmax = fmaxf(mmax, ml[w].x);
+  for (int w = 1; w < WAVES; ++w) mmax = fmaxf(mmax, ml[w].x);
   floatx4 acc_o[kVec];
 #pragma unroll
   for (int i = 0; i < kVec; ++i) acc_o[i] = floatx4{0.f, 0.f, 0.f, 0.f};
   float lsum = 0.f;
 #pragma unroll
-  for (int w = 0; w < kWavesPerGroup; ++w) {
+  for (int w = 0; w < WAVES; ++w) {
     const float f = ml[w].y > 0.f ? __builtin_amdgcn_exp2f(ml[w].x - mmax) : 0.f;
     lsum += f * ml[w].y;
 #pragma unroll
     for (int i = 0; i < kVec; ++i) acc_o[i] += f * ow[w][i];
   }
   const int a = mq;  // position in the active list
-  if (a < n_act) {
+  if (a < n_act && (WAVES == 4 || a < 16)) {
     if (p.n_split == 1) {
       const float inv = lsum > 0.f ? 1.f / lsum : 0.f;
       uint16_t* dst = p.out + (int64_t)h * p.osh + (int64_t)a * p.osn + mc * 4;
@@ -1570,9 +1575,40 @@ static void launch_wide_t(const AttnArgs& a, const SplitPlan& p, bool fused, hip
     WIDE_LAUNCH((wide_attn_kernel<D, NT, kKeep>), grid, block, st, a);
 }
 
+// Few sub-tiles per head: one workgroup of more wavefronts takes them all, a sub-tile each, and there are no partial results and no launch
+// that merges them (what a plan of two to four splits spends most on: a kernel boundary and a memory round trip, 3 us).  One compute unit
+// then fetches the head's K and V rows, 128 KB at most (about 45 bytes a clock), and its LDS holds them: eight sub-tiles at d = 128,
+// sixteen at d = 64, where the two ways meet.  Whole layer, splits -> this way: d = 64, 4 heads, 10 sub-tiles 10.8 -> 9.2 us; 32 heads, 6
+// sub-tiles 11.1 -> 9.2, 13 of 256 blocks 12.0 -> 11.1, attention alone with 15 8.1 -> 8.0; 256 heads, 14 sub-tiles 16.9 -> 14.1; d = 128,
+// 4 heads, 8 sub-tiles 11.9 -> 10.8, 64 heads 12.5 -> 12.0, 256 heads 19.9 -> 15.8.  More than 256 blocks (whose ranking takes every
+// thread of a smaller workgroup) stay with the splits, ranked here or before: the bits of the output do not depend on that.
+// Returns 0 for the plan's splits.  Scratch memory is asked for as for the splits.
+template <int D>
+static int one_split_waves(const AttnArgs& a, const SplitPlan& p) {
+  constexpr int kMost = D == 64 ? 16 : 8;
+  if (p.q_tiles != 1 || p.n_split == 1 || p.pipelined || p.n_sub > kMost || a.logits_out != nullptr || a.n_b > 256) return 0;
+  return D == 128 || p.n_sub <= 8 ? 8 : (p.n_sub <= 12 ? 12 : 16);
+}
+template <int D, int WAVES>
+static hipError_t launch_one_split(AttnArgs a, bool fused, hipStream_t st) {
+  const dim3 grid(a.H), block(64 * WAVES);
+  a.n_split = 1;
+  if (fused && a.rel_per_head)
+    ATTN_LAUNCH((sparse_attn_kernel<D, 9, WAVES>), grid, block, st, a);
+  else if (fused)
+    ATTN_LAUNCH((sparse_attn_kernel<D, 1, WAVES>), grid, block, st, a);
+  else
+    ATTN_LAUNCH((sparse_attn_kernel<D, 0, WAVES>), grid, block, st, a);
+  return hipGetLastError();
+}
+
 template <int D>
 static hipError_t launch_attn_t(const AttnArgs& a, const SplitPlan& p, bool fused, hipStream_t st) {
   if (!p.pipelined && p.n_split * kWavesPerGroup < p.n_sub) return hipErrorInvalidValue;  // the loop-free variants: one sub-tile per wavefront
+  const int waves = one_split_waves<D>(a, p);
+  if (waves == 16) return launch_one_split<D, D == 64 ? 16 : 8>(a, fused, st);
+  if (waves == 12) return launch_one_split<D, D == 64 ? 12 : 8>(a, fused, st);
+  if (waves == 8) return launch_one_split<D, 8>(a, fused, st);
   const dim3 grid = p.pipelined ? dim3(p.n_split, a.H) : dim3(a.H, p.n_split), block(256);
   if (p.q_tiles_per_group > 1) {
     if (a.logits_out != nullptr) return hipErrorInvalidValue;  // logits are spilled for one 16-query tile only
@@ -1586,29 +1622,29 @@ static hipError_t launch_attn_t(const AttnArgs& a, const SplitPlan& p, bool fuse
   } else if (a.logits_out != nullptr) {  // dense probe layer with the logits spilled
     if (fused) return hipErrorInvalidValue;
     if (p.pipelined)
-      ATTN_LAUNCH((sparse_attn_kernel<D, 6>), grid, block, st, a);
+      ATTN_LAUNCH((sparse_attn_kernel<D, 6, 4>), grid, block, st, a);
     else
-      ATTN_LAUNCH((sparse_attn_kernel<D, 4>), grid, block, st, a);
+      ATTN_LAUNCH((sparse_attn_kernel<D, 4, 4>), grid, block, st, a);
   } else if (fused && p.pipelined && a.n_b > kFusedManyBlocks)
-    ATTN_LAUNCH((sparse_attn_kernel<D, 35>), grid, block, st, a);
+    ATTN_LAUNCH((sparse_attn_kernel<D, 35, 4>), grid, block, st, a);
   else if (fused && a.n_b > kFusedManyBlocks)
-    ATTN_LAUNCH((sparse_attn_kernel<D, 33>), grid, block, st, a);
+    ATTN_LAUNCH((sparse_attn_kernel<D, 33, 4>), grid, block, st, a);
   else if (fused && p.pipelined && a.n_b > 256)
-    ATTN_LAUNCH((sparse_attn_kernel<D, 19>), grid, block, st, a);
+    ATTN_LAUNCH((sparse_attn_kernel<D, 19, 4>), grid, block, st, a);
   else if (fused && a.n_b > 256)
-    ATTN_LAUNCH((sparse_attn_kernel<D, 17>), grid, block, st, a);
+    ATTN_LAUNCH((sparse_attn_kernel<D, 17, 4>), grid, block, st, a);
   else if (fused && p.pipelined && a.rel_per_head)
-    ATTN_LAUNCH((sparse_attn_kernel<D, 11>), grid, block, st, a);
+    ATTN_LAUNCH((sparse_attn_kernel<D, 11, 4>), grid, block, st, a);
   else if (fused && p.pipelined)
-    ATTN_LAUNCH((sparse_attn_kernel<D, 3>), grid, block, st, a);
+    ATTN_LAUNCH((sparse_attn_kernel<D, 3, 4>), grid, block, st, a);
   else if (fused && a.rel_per_head)
-    ATTN_LAUNCH((sparse_attn_kernel<D, 9>), grid, block, st, a);
+    ATTN_LAUNCH((sparse_attn_kernel<D, 9, 4>), grid, block, st, a);
   else if (fused)
-    ATTN_LAUNCH((sparse_attn_kernel<D, 1>), grid, block, st, a);
+    ATTN_LAUNCH((sparse_attn_kernel<D, 1, 4>), grid, block, st, a);
   else if (p.pipelined)
-    ATTN_LAUNCH((sparse_attn_kernel<D, 2>), grid, block, st, a);
+    ATTN_LAUNCH((sparse_attn_kernel<D, 2, 4>), grid, block, st, a);
   else
-    ATTN_LAUNCH((sparse_attn_kernel<D, 0>), grid, block, st, a);
+    ATTN_LAUNCH((sparse_attn_kernel<D, 0, 4>), grid, block, st, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || p.n_split == 1) return e;
   hipLaunchKernelGGL(attn_combine_kernel<D>, grid_x_yz(a.H, a.max_active), dim3(256), 0, st, a.part_o, a.part_ml, a.counts, a.max_active,

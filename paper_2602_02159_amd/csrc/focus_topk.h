@@ -332,15 +332,21 @@ __device__ __forceinline__ void block_topk_planes(const uint32_t (&key1)[P], int
 //    wavefront selects the top k of those.
 //  - otherwise the keys go to LDS and ONE wavefront selects among all of them (wave_topk) while the others wait.
 // FRESH: the caller vouches that nobody is still reading `sm` from an earlier use (saves a barrier).
-template <int MAXN = kTopkThreads, bool FRESH = false, class KeyFn>
+// WAVES > 0: only the first WAVES wavefronts of the workgroup have candidates (n <= 64 WAVES) and take part in the tournament.
+template <int MAXN = kTopkThreads, bool FRESH = false, int WAVES = 0, class KeyFn>
 __device__ __forceinline__ uint32_t block_topk_small(const KeyFn keyfn, int n, int k, int32_t* out, uint8_t* flags,
                                                      TopkShared& sm) {
   const int tid = threadIdx.x, nt = blockDim.x;
   uint32_t mykey = 0;
   const bool myvalid = tid < n && keyfn(tid, mykey);
   const uint32_t key1 = myvalid ? mykey + 1u : 0u;  // threads past n hold 0: not a candidate
-  const int n_waves = nt >> 6;
+  const int n_waves = WAVES > 0 ? WAVES : nt >> 6;
   if (MAXN <= 256 && max(k, 0) * n_waves <= kWave) {
+    if (WAVES > 0 && (tid >> 6) >= WAVES) {  // the two barriers of the others
+      __syncthreads();
+      __syncthreads();
+      return sm.prefix;
+    }
     uint32_t pos, cnt;
     const bool sel = wave_select1(key1, k, pos, cnt);
     if (n_waves == 1) {  // a single wavefront: no LDS, no barrier

@@ -530,6 +530,57 @@ def test_key_loop_of_many_rounds(G, d, n_act, M):
     assert top.cpu().tolist() == fo.select_sinks(col.cpu().numpy().astype(np.float64), M, 4).tolist()
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("H,M,N,B,n_act,n_keep,n_sink", [
+    (3, 700, 0, 32, 16, 5, 0),       # five sub-tiles: one more than the wavefronts of a split
+    (2, 701, 33, 32, 11, 4, 32),     # seven, the last rows of the prompt, of the responses and a full list of sinks
+    (2, 512, 1, 2, 1, 6, 3),         # eight, the most at d = 128; 256 blocks, the most
+    (2, 514, 1, 2, 1, 6, 3),         # 257
+    (33, 1000, 30, 64, 16, 3, 40),   # nine; sinks in two sub-tiles, against the bitmap of the kept blocks
+    (2, 1000, 30, 64, 7, 4, 60),     # eleven
+    (2, 4000, 64, 16, 16, 10, 7),    # thirteen
+    (600, 300, 20, 16, 5, 15, 0),    # sixteen, the most at d = 64; more heads than one round of workgroups
+    (2, 4000, 20, 16, 5, 16, 0),     # seventeen
+])
+def test_sparse_attn_of_few_sub_tiles(G, d, H, M, N, B, n_act, n_keep, n_sink):
+    """One workgroup per head or a plan of key splits: attention alone and the whole layer, per head and head-averaged relevances, with
+    ids outside the prompt, padding of the active list and rows past it left alone."""
+    rng, n_gen = np.random.default_rng(n_sink + M), 20
+    q, k, v = (_rand_bf16(141 + i, H, r, d).to(G.DEV) for i, r in enumerate((n_gen, M + N, M + N)))
+    k[:, 3 * B:4 * B] = k[:, 7 * B:8 * B]                   # equal relevances: ties go to the lower block
+    some = list(range(0, H, max(1, H // 4)))
+    act = np.sort(rng.choice(n_gen, n_act, replace=False))
+    focus, active = G.i32(np.arange(3)), G.i32(np.concatenate([act, [0] * (16 - n_act)]))
+    counts, sinks = G.i32([3, n_act]), G.i32(rng.choice(M, n_sink, replace=False)) if n_sink else None
+    sink_rows = sinks.cpu().numpy() if n_sink else []
+    kbar = G.gpu_block_means(k, M, B)
+    scores, kept = G.gpu_block_scores(q, focus, counts, k, kbar, M, B, n_keep)
+    out = torch.empty((H, 16, d), dtype=torch.bfloat16, device=G.DEV)
+    lse, s2, k2 = torch.empty((H, 16), device=G.DEV), torch.empty_like(scores), torch.empty_like(kept)
+    s = fb.make_shape(q, k, v, M, B, out)
+
+    def check(blocks):
+        rows = fo.attention_index_set(sink_rows, blocks, M, B)
+        ref, ref_lse = fo.sparse_attention(G.to_np(q[some]), act, G.to_np(k[some]), G.to_np(v[some]), rows, M)
+        G.assert_attention_close(out[some, :n_act], ref)
+        assert np.allclose(lse[some, :n_act].cpu().numpy(), ref_lse, atol=2e-3)
+        assert bool((out[:, n_act:] == 7).all()) and bool((lse[:, n_act:] == 9).all())
+
+    listed = kept.clone()
+    listed[-1] = -1
+    listed[0] = -(-M // B)
+    buf = G.ws(fb.workspace_bytes(fb.FN_SPARSE_ATTN, s, 16, n_keep, n_sink))
+    out.fill_(7.0), lse.fill_(9.0)
+    fb.sparse_attn(q, active, counts, k, v, s, listed, n_keep, sinks, n_sink, out, lse, buf)
+    check(kept.cpu().numpy()[1:-1])
+    for mean_k in (kbar, None):
+        out.fill_(7.0), lse.fill_(9.0)
+        fb.sparse_layer(q, focus, active, counts, k, v, mean_k, s, n_keep, sinks, n_sink, s2, k2, out, lse,
+                        G.ws(fb.workspace_bytes(fb.FN_SPARSE_LAYER, s, 16, n_keep, n_sink)))
+        assert torch.equal(k2, kept) and (mean_k is None or torch.equal(s2, scores))
+        check(kept.cpu().numpy())
+
+
 def test_sparse_attn_dense_reduction(G):
     # keep every block, every row a query: plain bidirectional attention over all M+N keys
     H, M, N, d, B, n_gen = 4, 3000, 72, 128, 128, 64
