@@ -195,4 +195,71 @@ __device__ __forceinline__ RowState add_row_splits(const float2* row, int64_t st
   return r;
 }
 
+// =====================================================================================================
+// Helpers shared by the block-relevance kernels and the attention kernel that works the relevances out itself, written once so that the
+// K-scanning and the cached-means variants produce bit-identical partial relevances.
+// =====================================================================================================
+// Sum over the focus queries of Q[h, i, 8c .. 8c+7] by one wavefront, for the calling lane's chunk c = lane % (D/8): lane (r, c)
+// adds up the list entries r, r + R, r + 2 R, ... (U row loads in flight at a time), then the R lanes of a chunk meet (fixed
+// tree; every lane receives the total).  `entry` = focus_idx[lane], fetched by the caller ahead of time (any value past the list).
+template <int D, int U>
+__device__ __forceinline__ void add_focus_rows(float (&qs)[8], const uint16_t* __restrict__ qh, int64_t qsn,
+                                               const int32_t* __restrict__ focus_idx, int entry, int n_f, int n_gen) {
+  constexpr int CPR = D / 8, R = kWave / CPR;
+  static_assert(kWave % (R * U) == 0, "a batch lies within the entries a wavefront holds, or behind them");
+  const int lane = threadIdx.x & 63, c = lane % CPR, r = lane / CPR;
+  for (int f0 = 0; f0 < n_f; f0 += R * U) {  // uniform
+    int row[U];
+    if (f0 < kWave) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) row[u] = __shfl(entry, f0 + u * R + r, kWave);
+    } else {
+#pragma unroll
+      for (int u = 0; u < U; ++u) row[u] = f0 + u * R + r < n_f ? focus_idx[f0 + u * R + r] : -1;
+    }
+    uint4 v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      v[u] = (f0 + u * R + r < n_f && row[u] >= 0 && row[u] < n_gen) ? *reinterpret_cast<const uint4*>(qh + (int64_t)row[u] * qsn + c * 8)
+                                                                     : make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+    for (int u = 0; u < U; ++u) add_bf16x8(qs, v[u]);
+  }
+}
+template <int D, bool MANY>  // MANY: twice the loads in flight for lists longer than 4 R entries
+__device__ __forceinline__ void focus_row_sum(float (&qs)[8], const uint16_t* __restrict__ qh, int64_t qsn,
+                                              const int32_t* __restrict__ focus_idx, int entry, int n_f, int n_gen) {
+  constexpr int CPR = D / 8, R = kWave / CPR;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) qs[e] = 0.f;
+  if (MANY && n_f > 4 * R)
+    add_focus_rows<D, 8>(qs, qh, qsn, focus_idx, entry, n_f, n_gen);
+  else
+    add_focus_rows<D, 4>(qs, qh, qsn, focus_idx, entry, n_f, n_gen);
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    if (CPR == 8)  // lanes 8 apart: a rotation of the DPP row
+      qs[e] += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, qs[e]), 0x128, 0xF, 0xF, false));
+    qs[e] = group_sum(qs[e]);
+  }
+}
+
+// dot product of one 8-wide chunk, fixed fused-multiply-add order, then the sum over the CPR lanes of a block row
+template <int CPR>
+__device__ __forceinline__ float chunk_dot_reduce(const float (&qs)[8], const float4& k0, const float4& k1) {
+  float dot = qs[0] * k0.x;
+  dot = __builtin_fmaf(qs[1], k0.y, dot);
+  dot = __builtin_fmaf(qs[2], k0.z, dot);
+  dot = __builtin_fmaf(qs[3], k0.w, dot);
+  dot = __builtin_fmaf(qs[4], k1.x, dot);
+  dot = __builtin_fmaf(qs[5], k1.y, dot);
+  dot = __builtin_fmaf(qs[6], k1.z, dot);
+  dot = __builtin_fmaf(qs[7], k1.w, dot);
+  if (CPR == 16) return row_sum16(dot);
+  dot += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, dot), 0xB1, 0xF, 0xF, false));   // quad_perm [1,0,3,2]
+  dot += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, dot), 0x4E, 0xF, 0xF, false));   // quad_perm [2,3,0,1]
+  dot += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, dot), 0x141, 0xF, 0xF, false));  // row_half_mirror
+  return dot;
+}
+
 }  // namespace focus

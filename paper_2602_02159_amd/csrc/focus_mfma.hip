@@ -531,8 +531,9 @@ struct AttnArgs {
   uint32_t head_turn;                // (2^32 - 1) / H      see SplitRounds
   int split_rounds, split_rounds_more;  // every split has so many rounds, the first so many splits one more
   // fused layer path only: partial relevances in, scores / kept blocks out
-  const float* rel_part;  // [ceil(H / 4), n_b], or with rel_per_head [H, n_b]
+  const float* rel_part;  // [ceil(H / 4), n_b], or with rel_per_head [H, n_b]; with focus_idx the representative keys [H, n_b, D]
   bool rel_per_head;
+  const int32_t* focus_idx;  // or null
   float* scores_out;      // [n_b] or null
   int32_t* kept_out;      // [n_keep]
   int n_focus_max;
@@ -629,6 +630,47 @@ __device__ __forceinline__ void first_partials(FirstParts<NP, THREADS, BLOCKS>& 
     for (int i = 0; i < NP; ++i) f.part[l][i] = p.rel_part[(uint32_t)(min(i, last) * p.n_b) + b];
   }
   __builtin_amdgcn_sched_barrier(0);  // (the scheduler would move the wait for the row ids in front of these loads)
+}
+// The whole relevance in the attention kernel (relevance_in_attention): a wavefront takes one head and kInnerBlocks consecutive blocks, all
+// of its representative keys requested before the focus rows, and the sums of the groups of four heads go to the thread that ranks the
+// block, in the order of relevance_partial_kernel.
+constexpr int kInnerBlocks = 16, kInnerGroups = 4;  // WAVES <= 16 heads
+template <int D, int WAVES, int NP, int BLOCKS>
+__device__ __forceinline__ void relevance_parts(FirstParts<NP, 64 * WAVES, BLOCKS>& f, const AttnArgs& p, int entry, int n_focus, float* dots,
+                                                int wave, int lane) {
+  constexpr int CPR = D / 8, R = kWave / CPR, P = kInnerBlocks / R;
+  static_assert(WAVES <= kInnerGroups * kRelGroup && kInnerGroups <= NP && FirstParts<NP, 64 * WAVES, BLOCKS>::kPlanes == 1,
+                "a thread ranks one block and holds the sums of all groups");
+  const int c = lane % CPR, r = lane / CPR;
+  const int per_head = (p.n_b + kInnerBlocks - 1) / kInnerBlocks;
+  const int h = wave / per_head, b0 = (wave - h * per_head) * kInnerBlocks;
+  if (h < p.H) {
+    float4 k0[P], k1[P];
+#pragma unroll
+    for (int i = 0; i < P; ++i) {
+      const float4* kp = reinterpret_cast<const float4*>(p.rel_part + ((int64_t)h * p.n_b + min(b0 + i * R + r, p.n_b - 1)) * D + c * 8);
+      k0[i] = kp[0];
+      k1[i] = kp[1];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    float qs[8];
+    focus_row_sum<D, true>(qs, p.Q + (int64_t)h * p.qsh, p.qsn, p.focus_idx, entry, min(max(n_focus, 0), p.n_focus_max), p.n_gen);
+#pragma unroll
+    for (int i = 0; i < P; ++i) {
+      const float dot = chunk_dot_reduce<CPR>(qs, k0[i], k1[i]);
+      if (c == 0) dots[wave * kInnerBlocks + i * R + r] = dot;
+    }
+  }
+  __syncthreads();
+  const int b = min((int)threadIdx.x, p.n_b - 1);
+#pragma unroll
+  for (int g = 0; g < kInnerGroups; ++g) {
+    const int h0 = g * kRelGroup;
+    float acc = h0 < p.H ? dots[h0 * per_head * kInnerBlocks + b] : 0.f;
+#pragma unroll
+    for (int w = 1; w < kRelGroup; ++w) acc = h0 + w < p.H ? acc + dots[(h0 + w) * per_head * kInnerBlocks + b] : acc;
+    f.part[0][g] = acc;
+  }
 }
 template <int NP, int THREADS, int BLOCKS>
 __device__ __forceinline__ void rank_blocks(const AttnArgs& p, const FirstParts<NP, THREADS, BLOCKS>& f, bool per_head, int n_focus,
@@ -812,6 +854,7 @@ struct RoundList {
 // FUSE bit 0 clear: kept_blocks comes from memory.
 // FUSE bit 0 set (fused layer path): the workgroup first assembles R_b from the partial relevances and ranks
 // them itself — every workgroup repeats this small computation instead of waiting for a separate Top-C kernel.
+// FUSE bit 6 set (with bit 0): and works the partial relevances out, too (relevance_parts).
 // FUSE bit 3 set (with bit 0): the partial relevances come per head, from a K scan, and not per group of four heads.
 // FUSE bit 4 set (with bit 0): more than 256 blocks to rank.
 // FUSE bit 2 set (dense probe layer): the scaled logits of every (query, key) are also written out, so that
@@ -832,6 +875,8 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 4 ? 2 : WAVES / 4) void sparse
   constexpr bool SPILL = (FUSE & 4) != 0;                // dense: also write the scaled logits (sink scoring)
   constexpr bool PER_HEAD = (FUSE & 8) != 0;             // FUSED: partial relevances per head, not per group of heads
   constexpr int BLOCKS = (FUSE & 32) != 0 ? kFusedMaxBlocks : ((FUSE & 16) != 0 ? kFusedManyBlocks : 256);  // FUSED: the most blocks to rank
+  constexpr bool INNER = (FUSE & 64) != 0;               // FUSED: the relevances, too
+  static_assert(!INNER || (FUSED && !PER_HEAD && WAVES > 4), "one workgroup per head");
   constexpr int kBufBytes = 2 * G::kStageBytes;          // one slot: K stage + V stage of a sub-tile
   static_assert(16 * D * 4 <= kBufBytes, "a wavefront's O tile fits its stage");
   __shared__ __attribute__((aligned(256))) char ldsA[WAVES * kBufBytes];
@@ -855,6 +900,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 4 ? 2 : WAVES / 4) void sparse
   typename Kept::Id* kept_sh = Kept::place(topk_raw, kept_beside);
   const typename Kept::Id* kept_blocks = kept_sh;
   if constexpr (!FUSED) kept_blocks = p.kept_blocks;
+  __shared__ float dots_sh[INNER ? WAVES * kInnerBlocks : 1];
   // With the Top-C prologue ahead, the query rows are requested before it (their two round trips — row ids, then rows —
   // pass while the relevances are summed and ranked); without it they follow the first K/V requests (see below).
   bf16x8 q[G::kKSteps];
@@ -862,9 +908,16 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 4 ? 2 : WAVES / 4) void sparse
   if (FUSED) {
     qrow_early = fetch_q_row(p.active_idx, 0, p.max_active, p.n_gen, lane);
     FirstParts<PER_HEAD ? 32 : 8, 64 * WAVES, BLOCKS> first;
-    first_partials(first, p, PER_HEAD);
-    few_sinks = request_few_sinks(p, lane);
-    load_q_tile<D>(q, Qh, p.qsn, qrow_early, lane);
+    if constexpr (INNER) {
+      const int entry = lane < p.n_focus_max ? p.focus_idx[lane] : -1;
+      few_sinks = request_few_sinks(p, lane);
+      load_q_tile<D>(q, Qh, p.qsn, qrow_early, lane);
+      relevance_parts<D, WAVES>(first, p, entry, counted.focus, dots_sh, wave, lane);
+    } else {
+      first_partials(first, p, PER_HEAD);
+      few_sinks = request_few_sinks(p, lane);
+      load_q_tile<D>(q, Qh, p.qsn, qrow_early, lane);
+    }
     rank_blocks(p, first, PER_HEAD, counted.focus, kept_sh, topk_sm, blockIdx.x == 0 && blockIdx.y == 0);
   } else {
     few_sinks = request_few_sinks(p, lane);
@@ -1583,17 +1636,25 @@ static void launch_wide_t(const AttnArgs& a, const SplitPlan& p, bool fused, hip
 // 4 heads, 8 sub-tiles 11.9 -> 10.8, 64 heads 12.5 -> 12.0, 256 heads 19.9 -> 15.8.  More than 256 blocks (whose ranking takes every
 // thread of a smaller workgroup) stay with the splits, ranked here or before: the bits of the output do not depend on that.
 // Returns 0 for the plan's splits.  Scratch memory is asked for as for the splits.
-template <int D>
-static int one_split_waves(const AttnArgs& a, const SplitPlan& p) {
-  constexpr int kMost = D == 64 ? 16 : 8;
-  if (p.q_tiles != 1 || p.n_split == 1 || p.pipelined || p.n_sub > kMost || a.logits_out != nullptr || a.n_b > 256) return 0;
-  return D == 128 || p.n_sub <= 8 ? 8 : (p.n_sub <= 12 ? 12 : 16);
+static int one_split_waves(int head_dim, int n_b, const SplitPlan& p) {
+  const int most = head_dim == 64 ? 16 : 8;
+  if (p.q_tiles != 1 || p.n_split == 1 || p.pipelined || p.n_sub > most || n_b > 256) return 0;
+  return p.n_sub <= 8 ? 8 : (p.n_sub <= 12 ? 12 : 16);
+}
+// Such a workgroup works the relevances of all heads out itself where its wavefronts do that in one go (16 blocks of a head each): a
+// launch less, against one more memory round trip in this one.  Whole layer with that launch and without: d = 64, 4 heads, 16 blocks,
+// 10 sub-tiles 9.2 -> 8.1 us; d = 128, 4 heads, 32 blocks, 8 sub-tiles 10.8 -> 10.4.
+bool relevance_in_attention(const focus_shape& s, const SplitPlan& p) {
+  const int n_b = ceil_div(s.n_ctx, s.block), waves = one_split_waves(s.head_dim, n_b, p);
+  return (int64_t)s.n_heads * ceil_div(n_b, kInnerBlocks) <= waves;
 }
 template <int D, int WAVES>
 static hipError_t launch_one_split(AttnArgs a, bool fused, hipStream_t st) {
   const dim3 grid(a.H), block(64 * WAVES);
   a.n_split = 1;
-  if (fused && a.rel_per_head)
+  if (fused && a.focus_idx != nullptr)
+    ATTN_LAUNCH((sparse_attn_kernel<D, 65, WAVES>), grid, block, st, a);
+  else if (fused && a.rel_per_head)
     ATTN_LAUNCH((sparse_attn_kernel<D, 9, WAVES>), grid, block, st, a);
   else if (fused)
     ATTN_LAUNCH((sparse_attn_kernel<D, 1, WAVES>), grid, block, st, a);
@@ -1605,7 +1666,8 @@ static hipError_t launch_one_split(AttnArgs a, bool fused, hipStream_t st) {
 template <int D>
 static hipError_t launch_attn_t(const AttnArgs& a, const SplitPlan& p, bool fused, hipStream_t st) {
   if (!p.pipelined && p.n_split * kWavesPerGroup < p.n_sub) return hipErrorInvalidValue;  // the loop-free variants: one sub-tile per wavefront
-  const int waves = one_split_waves<D>(a, p);
+  const int waves = a.logits_out == nullptr ? one_split_waves(D, a.n_b, p) : 0;
+  if (a.focus_idx != nullptr && waves == 0) return hipErrorInvalidValue;
   if (waves == 16) return launch_one_split<D, D == 64 ? 16 : 8>(a, fused, st);
   if (waves == 12) return launch_one_split<D, D == 64 ? 12 : 8>(a, fused, st);
   if (waves == 8) return launch_one_split<D, 8>(a, fused, st);
@@ -1686,7 +1748,8 @@ hipError_t launch_sparse_attn(const void* Q, const int32_t* active_idx, const in
   a.head_turn = 0xffffffffu / (uint32_t)s.n_heads;
   a.split_rounds = ceil_div(p.n_sub, kWavesPerGroup) / p.n_split;
   a.split_rounds_more = ceil_div(p.n_sub, kWavesPerGroup) % p.n_split;
-  a.rel_part = fused ? fused->rel_part : nullptr;
+  a.focus_idx = fused && fused->kbar ? fused->focus_idx : nullptr;
+  a.rel_part = fused ? (fused->kbar ? fused->kbar : fused->rel_part) : nullptr;
   a.rel_per_head = fused && fused->per_head;
   a.scores_out = fused ? fused->scores_out : nullptr;
   a.kept_out = fused ? fused->kept_out : nullptr;

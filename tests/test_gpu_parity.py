@@ -581,6 +581,40 @@ def test_sparse_attn_of_few_sub_tiles(G, d, H, M, N, B, n_act, n_keep, n_sink):
         check(kept.cpu().numpy())
 
 
+@pytest.mark.parametrize("H,M,d,B,n_keep,n_sink,n_focus,over", [
+    (8, 256, 128, 16, 7, 3, 16, False),      # eight wavefronts, eight heads of sixteen blocks
+    (4, 1024, 128, 32, 6, 2, 70, False),     # ... of two times sixteen, more focus rows than lanes
+    (4, 1056, 128, 32, 6, 2, 1, False),      # ... of three times: relevances by a launch
+    (9, 256, 128, 16, 7, 0, 9, False),       # nine heads: by a launch
+    (12, 200, 64, 16, 10, 5, 33, False),     # twelve wavefronts, three groups of heads; a ragged last block
+    (5, 700, 64, 16, 13, 5, 40, False),      # sixteen; two groups, one with one head, and a wavefront with nothing to do
+    (16, 100, 64, 8, 13, 40, 5, False),      # four groups
+    (1, 4096, 64, 16, 15, 0, 80, False),     # one head, 256 blocks
+    (8, 256, 128, 16, 7, 3, 16, True),       # the output lies over the queries: by a launch
+])
+def test_relevance_in_the_attention_kernel(G, H, M, d, B, n_keep, n_sink, n_focus, over):
+    """Short key lists of few heads: scores, blocks and output of the whole layer are bit for bit those of the separate calls."""
+    rng, n_gen, N, n_act = np.random.default_rng(M + n_focus), 80, 32, 16
+    q, k, v = (_rand_bf16(151 + i, H, r, d).to(G.DEV) for i, r in enumerate((n_gen, M + N, M + N)))
+    k[:, 3 * B:4 * B] = k[:, 7 * B:8 * B]                   # equal relevances: ties go to the lower block
+    focus = np.sort(rng.choice(n_gen, n_focus, replace=False))
+    focus[n_focus // 2] = n_gen if n_focus > 1 else focus[0]   # an entry past the block adds nothing
+    focus, active = G.i32(focus), G.i32(np.arange(n_act))
+    counts = G.i32([max(1, n_focus - 1), n_act])
+    sinks = G.i32(rng.choice(M, n_sink, replace=False)) if n_sink else None
+    kbar = G.gpu_block_means(k, M, B)
+    scores, kept = G.gpu_block_scores(q, focus, counts, k, kbar, M, B, n_keep)
+    out, lse = G.gpu_sparse_attn(q, active, counts, k, v, M, B, kept, sinks)
+    o2 = q[:, :n_act] if over else torch.empty_like(out)
+    s2, k2, l2 = torch.empty_like(scores), torch.empty_like(kept), torch.empty_like(lse)
+    s = fb.make_shape(q, k, v, M, B, o2)
+    fb.sparse_layer(q, focus, active, counts, k, v, kbar, s, n_keep, sinks, n_sink, s2, k2, o2, l2,
+                    G.ws(fb.workspace_bytes(fb.FN_SPARSE_LAYER, s, n_act, n_keep, n_sink)))
+    torch.cuda.synchronize()
+    assert torch.equal(s2, scores) and torch.equal(k2, kept) and torch.equal(l2, lse)
+    assert torch.equal(o2, out)
+
+
 def test_sparse_attn_dense_reduction(G):
     # keep every block, every row a query: plain bidirectional attention over all M+N keys
     H, M, N, d, B, n_gen = 4, 3000, 72, 128, 128, 64
