@@ -456,15 +456,18 @@ __device__ __forceinline__ bf16x8 read_v_operand32(const char* stageV, int dt, i
 // for the column-mass kernel in the layout [head][key quad][query][key within the quad] (fp32): a lane holds, per
 // 16-key tile, the logits of ONE query for four consecutive keys — one 16-byte store — and the 64 lanes of a store
 // instruction cover 1 KB of consecutive bytes (query fastest, then the four quads of the tile).  Quads that start at or
-// past key L are not written; the padding keys of the last quad hold finite values nobody reads.
-__device__ __forceinline__ void spill_logits(float* __restrict__ logits, int h, int L, int row0, const floatx4 (&acc)[2],
+// past key L are not written; the padding keys of the last quad hold finite values nobody reads.  Neither are the slots of queries past
+// the capacity n_q of the list, and the column-mass kernel does not fetch them: at eight queries half of the traffic beside K (32 heads, sink
+// chain of 8192 keys 28.8 -> 26.7 us, 32 832 73.5 -> 67.1, 131 136 255 -> 232; probe layer of 32 832 128 -> 118; four queries take as
+// long as eight, a line of 128 bytes; sixteen as before).  The device-side count would come too late for the second kernel's first loads.
+__device__ __forceinline__ void spill_logits(float* __restrict__ logits, int h, int L, int n_q, int row0, const floatx4 (&acc)[2],
                                              float scale_log2, int lane) {
   const int c = lane & 15, g = lane >> 4;
   const int64_t n_quads = (L + 3) >> 2;
 #pragma unroll
   for (int kt = 0; kt < 2; ++kt) {
     const int key0 = row0 + 16 * kt + 4 * g;
-    if (key0 < L) {
+    if (key0 < L && c < n_q) {
       floatx4* dst = reinterpret_cast<floatx4*>(logits + (((int64_t)h * n_quads + (key0 >> 2)) * 16 + c) * 4);
       *dst = acc[kt] * scale_log2;
     }
@@ -999,7 +1002,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 4 ? 2 : WAVES / 4) void sparse
     if (t.vmask != 0u) {
       wait_loads();
       consume(stageK, stageV, t.vmask, t.row0);
-      if (SPILL) spill_logits(p.logits_out, h, p.dense_rows, t.row0, kept_logits, p.scale_log2, lane);  // contiguous rows only (dense)
+      if (SPILL) spill_logits(p.logits_out, h, p.dense_rows, p.max_active, t.row0, kept_logits, p.scale_log2, lane);  // contiguous rows only (dense)
     }
   } else {
     // One stage, whose K and V rows travel separately (see wide_attn_kernel): the next K rows are requested as soon as the present ones
@@ -1048,7 +1051,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 4 ? 2 : WAVES / 4) void sparse
       if (here) {
 #pragma unroll
         for (int ct = 0; ct < G::kColTiles; ++ct) o[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vop[ct], pb, o[ct], 0, 0, 0);
-        if (SPILL) spill_logits(p.logits_out, h, p.dense_rows, t.row0, acc, p.scale_log2, lane);
+        if (SPILL) spill_logits(p.logits_out, h, p.dense_rows, p.max_active, t.row0, acc, p.scale_log2, lane);
       }
       stored = here && t.vmask == 0xffffffffu;
       t = tn;
@@ -2426,7 +2429,7 @@ __global__ __launch_bounds__(256, 2) void qk_logits_kernel(const uint16_t* K, in
       }
       float ps[8];
       softmax_step(acc, t.vmask, g, p.scale_log2, m_run, l_run, ps);
-      spill_logits(p.logits, h, p.L, t.row0, acc, p.scale_log2, lane);
+      spill_logits(p.logits, h, p.L, p.max_active, t.row0, acc, p.scale_log2, lane);
       stored = after < st_end && t.vmask == 0xffffffffu;
       t = tn;
       tn = ta;
@@ -2451,7 +2454,7 @@ __global__ __launch_bounds__(256, 2) void qk_logits_kernel(const uint16_t* K, in
     }
     float ps[8];
     softmax_step(acc, cur.vmask, g, p.scale_log2, m_run, l_run, ps);
-    spill_logits(p.logits, h, p.L, cur.row0, acc, p.scale_log2, lane);
+    spill_logits(p.logits, h, p.L, p.max_active, cur.row0, acc, p.scale_log2, lane);
   }
 
   if (g == 0) {

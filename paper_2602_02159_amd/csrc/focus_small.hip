@@ -460,7 +460,7 @@ __global__ __launch_bounds__(512) void column_mass_kernel(const float* __restric
     const int64_t quad = (int64_t)blockIdx.x * (kMassKeys / 4) + quad_local;  // key quad of this lane
     float acc[4] = {0.f, 0.f, 0.f, 0.f};
     // (quads past the end repeat the last one; their masses are not looked at)
-    const float4* base = reinterpret_cast<const float4*>(src) + (quad < n_quads ? quad : n_quads - 1) * 16 + c;
+    const float4* base = reinterpret_cast<const float4*>(src) + (quad < n_quads ? quad : n_quads - 1) * 16 + min(c, max_active - 1);
     for (int h0 = 0; h0 < n_parts; h0 += kHeadsInFlight) {
       float4 x[kHeadsInFlight];
       float z[kHeadsInFlight];

@@ -339,6 +339,30 @@ def test_find_sinks_with_the_workspace_of_one_key_split_less(G):
         fb.find_sinks(q, active, None, k, s, 3, col2, sinks2, buf[:least - 1])
 
 
+@pytest.mark.parametrize("H,M,N,d", [(3, 700, 5, 64), (2, 4100, 30, 128), (18, 900, 1, 128)])
+@pytest.mark.parametrize("cap,n_act", [(1, 1), (3, 2), (8, 8), (9, 7), (15, 15), (16, 5)])
+def test_logits_of_fewer_than_sixteen_queries(G, H, M, N, d, cap, n_act):
+    """The slots past the capacity are neither written nor read: scratch memory that is NaN before changes nothing."""
+    q, k, v = (_rand_bf16(161 + i, H, r, d).to(G.DEV) for i, r in enumerate((16, M + N, M + N)))
+    rows = np.sort(np.random.default_rng(cap).choice(16, cap, replace=False))
+    active, counts = G.i32(rows), G.i32([1, n_act])
+    logits = torch.matmul(q[:, rows[:n_act]].float(), k.float().transpose(1, 2).contiguous()) / d ** 0.5
+    mass = torch.softmax(logits, -1).mean((0, 1))
+    out = torch.empty((H, cap, d), dtype=torch.bfloat16, device=G.DEV)
+    s = fb.make_shape(q, k, v, M, 64, out)
+    for probe in (False, True):
+        nbytes = fb.workspace_bytes(fb.FN_PROBE_LAYER if probe else fb.FN_FIND_SINKS, s, cap)
+        buf = torch.full((nbytes,), 0xFF, dtype=torch.uint8, device=G.DEV)   # NaN wherever it is read as floats
+        col, sinks = torch.empty(M + N, device=G.DEV), G.i32(np.zeros(4))
+        if probe:
+            fb.probe_layer(q, active, counts, k, v, s, 4, out, None, col, sinks, buf)
+        else:
+            fb.find_sinks(q, active, counts, k, s, 4, col, sinks, buf)
+        torch.cuda.synchronize()
+        assert torch.allclose(col, mass, rtol=2e-4, atol=1e-9)   # the bar of test_find_sinks
+        assert sinks.cpu().tolist() == fo.select_sinks(col.cpu().numpy().astype(np.float64), M, 4).tolist()
+
+
 def test_find_sinks_equal_keys_fall_back_to_lowest_positions(G):
     H, M, N, d = 2, 500, 12, 64
     k = _rand_bf16(9, 1, 1, d).expand(H, M + N, d).contiguous().to(G.DEV)
