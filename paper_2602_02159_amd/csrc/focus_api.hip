@@ -356,12 +356,6 @@ static int static_scratch_ptr(void** out) {
   return FOCUS_OK;
 }
 
-static bool output_over_queries(const void* Q, const void* out, int max_active, const focus_shape& s) {
-  auto bytes = [&](int64_t sh, int64_t sn, int rows) { return 2 * ((s.n_heads - 1) * sh + (rows - 1) * sn + s.head_dim); };
-  const uintptr_t q = reinterpret_cast<uintptr_t>(Q), o = reinterpret_cast<uintptr_t>(out);
-  return s.o_stride_h < 0 || (q < o + (uintptr_t)bytes(s.o_stride_h, s.o_stride_n, max_active) && o < q + (uintptr_t)bytes(s.q_stride_h, s.q_stride_n, s.n_gen));
-}
-
 static int sparse_layer_impl(const char* who, const void* Q, const int32_t* focus_idx, const int32_t* active_idx,
                              const int32_t* counts, int32_t n_focus_max, int32_t max_active, const void* K, const void* V,
                              const float* kbar, const focus_shape* shape, int32_t n_keep, const int32_t* sink_idx,
@@ -399,7 +393,6 @@ static int sparse_layer_impl(const char* who, const void* Q, const int32_t* focu
   float* part_o = reinterpret_cast<float*>(ws + attn + w.at.part_o);
   float* part_ml = reinterpret_cast<float*>(ws + attn + w.at.part_ml);
   hipError_t e = hipSuccess;
-  // (every workgroup of that kernel reads the focus rows of all heads: not with an output that lies over them)
   const bool inner = fused && kbar && relevance_in_attention(*shape, p) && !output_over_queries(Q, out, max_active, *shape);
   if (!kbar)
     e = launch_block_means_relevance(K, Q, focus_idx, counts, n_focus_max, *shape, nullptr, part, st);

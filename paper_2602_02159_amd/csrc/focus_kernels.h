@@ -160,7 +160,8 @@ struct FusedTopC {
   const float* kbar = nullptr;  // relevance_in_attention: there are no partial relevances, the kernel works them out
   const int32_t* focus_idx = nullptr;
 };
-bool relevance_in_attention(const focus_shape& s, const SplitPlan& p);
+bool relevance_in_attention(const focus_shape& s, const SplitPlan& p);  // unless output_over_queries
+bool output_over_queries(const void* Q, const void* out, int max_active, const focus_shape& s);
 // Dense (probe) layer: every one of the M + N key rows is attended (kept_blocks / sink_idx unused, plan from
 // plan_attention_dense); optionally the scaled logits (at most 16 active queries) and the base-2 row log-sum-exps are
 // written for the sink scoring that follows.

@@ -1644,6 +1644,12 @@ static int one_split_waves(int head_dim, int n_b, const SplitPlan& p) {
   if (p.q_tiles != 1 || p.n_split == 1 || p.pipelined || p.n_sub > most || n_b > 256) return 0;
   return p.n_sub <= 8 ? 8 : (p.n_sub <= 12 ? 12 : 16);
 }
+// The workgroup of one head would write its output while those of others still read their queries
+bool output_over_queries(const void* Q, const void* out, int max_active, const focus_shape& s) {
+  auto bytes = [&](int64_t sh, int64_t sn, int rows) { return 2 * ((s.n_heads - 1) * sh + (rows - 1) * sn + s.head_dim); };
+  const uintptr_t q = reinterpret_cast<uintptr_t>(Q), o = reinterpret_cast<uintptr_t>(out);
+  return s.o_stride_h < 0 || (q < o + (uintptr_t)bytes(s.o_stride_h, s.o_stride_n, max_active) && o < q + (uintptr_t)bytes(s.q_stride_h, s.q_stride_n, s.n_gen));
+}
 // Such a workgroup works the relevances of all heads out itself where its wavefronts do that in one go (16 blocks of a head each): a
 // launch less, against one more memory round trip in this one.  Whole layer with that launch and without: d = 64, 4 heads, 16 blocks,
 // 10 sub-tiles 9.2 -> 8.1 us; d = 128, 4 heads, 32 blocks, 8 sub-tiles 10.8 -> 10.4.
@@ -1667,9 +1673,9 @@ static hipError_t launch_one_split(AttnArgs a, bool fused, hipStream_t st) {
 }
 
 template <int D>
-static hipError_t launch_attn_t(const AttnArgs& a, const SplitPlan& p, bool fused, hipStream_t st) {
+static hipError_t launch_attn_t(const AttnArgs& a, const SplitPlan& p, bool fused, bool output_apart, hipStream_t st) {
   if (!p.pipelined && p.n_split * kWavesPerGroup < p.n_sub) return hipErrorInvalidValue;  // the loop-free variants: one sub-tile per wavefront
-  const int waves = a.logits_out == nullptr ? one_split_waves(D, a.n_b, p) : 0;
+  const int waves = a.logits_out == nullptr && output_apart ? one_split_waves(D, a.n_b, p) : 0;
   if (a.focus_idx != nullptr && waves == 0) return hipErrorInvalidValue;
   if (waves == 16) return launch_one_split<D, D == 64 ? 16 : 8>(a, fused, st);
   if (waves == 12) return launch_one_split<D, D == 64 ? 12 : 8>(a, fused, st);
@@ -1757,7 +1763,8 @@ hipError_t launch_sparse_attn(const void* Q, const int32_t* active_idx, const in
   a.scores_out = fused ? fused->scores_out : nullptr;
   a.kept_out = fused ? fused->kept_out : nullptr;
   a.n_focus_max = fused ? fused->n_focus_max : 0;
-  return s.head_dim == 128 ? launch_attn_t<128>(a, p, fused != nullptr, st) : launch_attn_t<64>(a, p, fused != nullptr, st);
+  const bool apart = !output_over_queries(Q, out, max_active, s);
+  return s.head_dim == 128 ? launch_attn_t<128>(a, p, fused != nullptr, apart, st) : launch_attn_t<64>(a, p, fused != nullptr, apart, st);
 }
 
 // =====================================================================================================

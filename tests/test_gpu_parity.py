@@ -614,7 +614,7 @@ def test_sparse_attn_of_few_sub_tiles(G, d, H, M, N, B, n_act, n_keep, n_sink):
     (5, 700, 64, 16, 13, 5, 40, False),      # sixteen; two groups, one with one head, and a wavefront with nothing to do
     (16, 100, 64, 8, 13, 40, 5, False),      # four groups
     (1, 4096, 64, 16, 15, 0, 80, False),     # one head, 256 blocks
-    (8, 256, 128, 16, 7, 3, 16, True),       # the output lies over the queries: by a launch
+    (8, 256, 128, 16, 7, 3, 16, True),       # the output lies over the queries: key splits, relevances by a launch
 ])
 def test_relevance_in_the_attention_kernel(G, H, M, d, B, n_keep, n_sink, n_focus, over):
     """Short key lists of few heads: scores, blocks and output of the whole layer are bit for bit those of the separate calls."""
@@ -635,8 +635,12 @@ def test_relevance_in_the_attention_kernel(G, H, M, d, B, n_keep, n_sink, n_focu
     fb.sparse_layer(q, focus, active, counts, k, v, kbar, s, n_keep, sinks, n_sink, s2, k2, o2, l2,
                     G.ws(fb.workspace_bytes(fb.FN_SPARSE_LAYER, s, n_act, n_keep, n_sink)))
     torch.cuda.synchronize()
-    assert torch.equal(s2, scores) and torch.equal(k2, kept) and torch.equal(l2, lse)
-    assert torch.equal(o2, out)
+    assert torch.equal(s2, scores) and torch.equal(k2, kept)
+    if over:  # the merge of the splits rounds in other places
+        G.assert_attention_close(o2, out.double().cpu().numpy())
+        assert torch.allclose(l2, lse, atol=2e-3)
+    else:
+        assert torch.equal(o2, out) and torch.equal(l2, lse)
 
 
 def test_sparse_attn_dense_reduction(G):
