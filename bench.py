@@ -656,9 +656,12 @@ def main() -> int:
         groups = -(-cap // 32) if cap > 64 else 1
         loop = max(1, 512 // (h * groups)) * 4 < n_sub   # a slot walks several sub-tiles
         if cap <= 16:
-            return f"sparse_attn_kernel<{wl.head_dim}, {2 if loop else 0}>"
+            few = 16 if wl.head_dim == 64 else 8   # sub-tiles that one workgroup per head takes, without a combine launch
+            if not loop and 4 < n_sub <= few and -(-wl.n_ctx // wl.block) <= 256:
+                return f"sparse_attn_kernel<{wl.head_dim}, 0, {8 if n_sub <= 8 else (12 if n_sub <= 12 else 16)}>"
+            return f"sparse_attn_kernel<{wl.head_dim}, {2 if loop else 0}, 4>"
         tiles, bits = (1, 8) if cap > 64 else (2 if cap > 32 else 1, 0)
-        return f"wide_attn_kernel<{wl.head_dim}, {tiles}, {bits + ((2 if cap > 64 else 6) if loop else 0)}>"
+        return f"wide_attn_kernel<{wl.head_dim}, {tiles}, {bits + (2 if loop else 0)}>"
 
     def attn_traffic(wl, kernel):
         """HBM bytes of one focus_sparse_attn call (attention kernel: rows fetched + split partials written; combine: partials
@@ -674,7 +677,8 @@ def main() -> int:
         if pmc.get("kernel_sources_sha16") != kernel_sources_sha16():
             return None, f"{name} was recorded with other kernel sources"
         found = {}
-        for want in (kernel, f"attn_combine_kernel<{wl.head_dim}>"):
+        one_split = kernel.startswith("sparse_attn_kernel") and not kernel.endswith(", 4>")
+        for want in (kernel,) if one_split else (kernel, f"attn_combine_kernel<{wl.head_dim}>"):
             # the dense comparison may share a name: the smallest dispatch is the sparse one
             found[want] = [v["fetch_bytes_min"] + v["write_bytes_min"] for key, v in pmc["kernels"].items() if want + "(" in key]
         missing = [want for want, v in found.items() if len(v) != 1]
