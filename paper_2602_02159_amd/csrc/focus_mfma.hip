@@ -534,9 +534,9 @@ struct AttnArgs {
   uint32_t head_turn;                // (2^32 - 1) / H      see SplitRounds
   int split_rounds, split_rounds_more;  // every split has so many rounds, the first so many splits one more
   // fused layer path only: partial relevances in, scores / kept blocks out
-  const float* rel_part;  // [ceil(H / 4), n_b], or with rel_per_head [H, n_b]; with focus_idx the representative keys [H, n_b, D]
+  // (where the kernel works the relevances out itself rel_part is the representative keys [H, n_b, D] and kept_blocks the focus rows' ids)
+  const float* rel_part;  // [ceil(H / 4), n_b], or with rel_per_head [H, n_b]
   bool rel_per_head;
-  const int32_t* focus_idx;  // or null
   float* scores_out;      // [n_b] or null
   int32_t* kept_out;      // [n_keep]
   int n_focus_max;
@@ -657,7 +657,7 @@ __device__ __forceinline__ void relevance_parts(FirstParts<NP, 64 * WAVES, BLOCK
     }
     __builtin_amdgcn_sched_barrier(0);
     float qs[8];
-    focus_row_sum<D, true>(qs, p.Q + (int64_t)h * p.qsh, p.qsn, p.focus_idx, entry, min(max(n_focus, 0), p.n_focus_max), p.n_gen);
+    focus_row_sum<D, true>(qs, p.Q + (int64_t)h * p.qsh, p.qsn, p.kept_blocks, entry, min(max(n_focus, 0), p.n_focus_max), p.n_gen);
 #pragma unroll
     for (int i = 0; i < P; ++i) {
       const float dot = chunk_dot_reduce<CPR>(qs, k0[i], k1[i]);
@@ -912,7 +912,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 4 ? 2 : WAVES / 4) void sparse
     qrow_early = fetch_q_row(p.active_idx, 0, p.max_active, p.n_gen, lane);
     FirstParts<PER_HEAD ? 32 : 8, 64 * WAVES, BLOCKS> first;
     if constexpr (INNER) {
-      const int entry = lane < p.n_focus_max ? p.focus_idx[lane] : -1;
+      const int entry = lane < p.n_focus_max ? p.kept_blocks[lane] : -1;
       few_sinks = request_few_sinks(p, lane);
       load_q_tile<D>(q, Qh, p.qsn, qrow_early, lane);
       relevance_parts<D, WAVES>(first, p, entry, counted.focus, dots_sh, wave, lane);
@@ -1661,7 +1661,7 @@ template <int D, int WAVES>
 static hipError_t launch_one_split(AttnArgs a, bool fused, hipStream_t st) {
   const dim3 grid(a.H), block(64 * WAVES);
   a.n_split = 1;
-  if (fused && a.focus_idx != nullptr)
+  if (fused && a.kept_blocks != nullptr)
     ATTN_LAUNCH((sparse_attn_kernel<D, 65, WAVES>), grid, block, st, a);
   else if (fused && a.rel_per_head)
     ATTN_LAUNCH((sparse_attn_kernel<D, 9, WAVES>), grid, block, st, a);
@@ -1676,7 +1676,7 @@ template <int D>
 static hipError_t launch_attn_t(const AttnArgs& a, const SplitPlan& p, bool fused, bool output_apart, hipStream_t st) {
   if (!p.pipelined && p.n_split * kWavesPerGroup < p.n_sub) return hipErrorInvalidValue;  // the loop-free variants: one sub-tile per wavefront
   const int waves = a.logits_out == nullptr && output_apart ? one_split_waves(D, a.n_b, p) : 0;
-  if (a.focus_idx != nullptr && waves == 0) return hipErrorInvalidValue;
+  if (fused && a.kept_blocks != nullptr && waves == 0) return hipErrorInvalidValue;
   if (waves == 16) return launch_one_split<D, D == 64 ? 16 : 8>(a, fused, st);
   if (waves == 12) return launch_one_split<D, D == 64 ? 12 : 8>(a, fused, st);
   if (waves == 8) return launch_one_split<D, 8>(a, fused, st);
@@ -1757,7 +1757,7 @@ hipError_t launch_sparse_attn(const void* Q, const int32_t* active_idx, const in
   a.head_turn = 0xffffffffu / (uint32_t)s.n_heads;
   a.split_rounds = ceil_div(p.n_sub, kWavesPerGroup) / p.n_split;
   a.split_rounds_more = ceil_div(p.n_sub, kWavesPerGroup) % p.n_split;
-  a.focus_idx = fused && fused->kbar ? fused->focus_idx : nullptr;
+  if (fused) a.kept_blocks = fused->kbar ? fused->focus_idx : nullptr;
   a.rel_part = fused ? (fused->kbar ? fused->kbar : fused->rel_part) : nullptr;
   a.rel_per_head = fused && fused->per_head;
   a.scores_out = fused ? fused->scores_out : nullptr;
