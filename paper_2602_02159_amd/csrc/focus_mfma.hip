@@ -1607,6 +1607,60 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(const float* __restri
   }
 }
 
+// Up to N splits: a wavefront per (head, active row), every lane with D / 64 columns of all of them: N loads, no LDS and no barrier.  The
+// same operations in the same order as above, where every lane then has one split.  Bound by the one memory round trip and the
+// launch.  Whole layer, above -> this way: 32 heads, 8 splits, 256 blocks 14.40 -> 14.27 us, 125 blocks 13.65 -> 13.38; d = 64, 7 splits
+// 11.95 -> 11.15; 16 heads, d = 64, 14 splits 11.48 -> 11.22.  With more than 4 KB of partial results per row the single wavefront takes
+// longer than four (d = 128: 16 heads, 13 splits 13.85 -> 13.94, 8 heads, 21 splits 12.8 -> 14.4), and four rows per workgroup take 0.05 more.
+// Several query groups (4 heads, 252 rows: 25.7 and 26.0 us) keep the workgroup per row.
+template <int D, int N>
+__global__ __launch_bounds__(64) void attn_combine_few_kernel(const float* __restrict__ part_o, const float* __restrict__ part_ml,
+                                                              const int32_t* __restrict__ counts, int max_active, int q_pad,
+                                                              int n_split, uint16_t* __restrict__ out, int64_t osh, int64_t osn,
+                                                              float* __restrict__ lse, float* __restrict__ lse2) {
+  constexpr int kVec = D / 64;
+  const int a = grid_yz(), h = blockIdx.x, mc = threadIdx.x * kVec;
+  if (a >= max_active) return;  // (the grid's last slice)
+  const int n_act = counts ? min(max(counts[1], 0), max_active) : max_active;
+  const int64_t row0 = ((int64_t)h * q_pad + a) * n_split;
+  const float2* ml = reinterpret_cast<const float2*>(part_ml) + row0;
+  const float* po = part_o + row0 * D + mc;
+  float2 v[N];
+  float x[N][kVec];
+#pragma unroll
+  for (int u = 0; u < N; ++u) {
+    const int s = min(u, n_split - 1);
+    v[u] = ml[s];
+#pragma unroll
+    for (int i = 0; i < kVec; ++i) x[u][i] = po[(int64_t)s * D + i];
+  }
+  if (a >= n_act) return;  // rows past the count: their partial results were never written
+  float mmax = -INFINITY;
+#pragma unroll
+  for (int u = 0; u < N; ++u) {
+    if (u >= n_split || !(v[u].y > 0.f)) v[u] = make_float2(-INFINITY, 0.f);
+    mmax = fmaxf(mmax, v[u].x);
+  }
+  float o[kVec] = {}, lsum = 0.f;
+#pragma unroll
+  for (int u = 0; u < N; ++u) {
+    const float f = v[u].y > 0.f ? __builtin_amdgcn_exp2f(v[u].x - mmax) : 0.f;
+    lsum += f * v[u].y;
+#pragma unroll
+    for (int i = 0; i < kVec; ++i) o[i] += f * (v[u].y > 0.f ? x[u][i] : 0.f);
+  }
+  const float inv = lsum > 0.f ? 1.f / lsum : 0.f;
+  uint16_t* dst = out + (int64_t)h * osh + (int64_t)a * osn + mc;
+  if constexpr (kVec == 2)
+    *reinterpret_cast<uint32_t*>(dst) = cvt_pk_bf16(o[0] * inv, o[1] * inv);
+  else
+    *dst = (uint16_t)cvt_pk_bf16(o[0] * inv, 0.f);
+  if (mc == 0) {
+    if (lse) lse[(int64_t)h * max_active + a] = lsum > 0.f ? (mmax + __builtin_amdgcn_logf(lsum)) * kLn2 : -INFINITY;
+    if (lse2) lse2[(int64_t)h * q_pad + a] = lsum > 0.f ? mmax + __builtin_amdgcn_logf(lsum) : INFINITY;
+  }
+}
+
 // LOOP: the mode bits of the key loop
 template <int D, int NT, int LOOP>
 static void launch_wide_t(const AttnArgs& a, const SplitPlan& p, bool fused, hipStream_t st) {
@@ -1718,8 +1772,15 @@ static hipError_t launch_attn_t(const AttnArgs& a, const SplitPlan& p, bool fuse
     ATTN_LAUNCH((sparse_attn_kernel<D, 0, 4>), grid, block, st, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || p.n_split == 1) return e;
-  hipLaunchKernelGGL(attn_combine_kernel<D>, grid_x_yz(a.H, a.max_active), dim3(256), 0, st, a.part_o, a.part_ml, a.counts, a.max_active,
-                     a.q_pad, a.n_split, a.out, a.osh, a.osn, a.lse, a.lse2_out);
+  if (p.q_groups == 1 && p.n_split <= 8)
+    hipLaunchKernelGGL((attn_combine_few_kernel<D, 8>), grid_x_yz(a.H, a.max_active), dim3(64), 0, st, a.part_o, a.part_ml, a.counts, a.max_active,
+                       a.q_pad, a.n_split, a.out, a.osh, a.osn, a.lse, a.lse2_out);
+  else if (p.q_groups == 1 && p.n_split * D <= 1024)  // (d = 64)
+    hipLaunchKernelGGL((attn_combine_few_kernel<D, 1024 / D>), grid_x_yz(a.H, a.max_active), dim3(64), 0, st, a.part_o, a.part_ml, a.counts, a.max_active,
+                       a.q_pad, a.n_split, a.out, a.osh, a.osn, a.lse, a.lse2_out);
+  else
+    hipLaunchKernelGGL(attn_combine_kernel<D>, grid_x_yz(a.H, a.max_active), dim3(256), 0, st, a.part_o, a.part_ml, a.counts, a.max_active,
+                       a.q_pad, a.n_split, a.out, a.osh, a.osn, a.lse, a.lse2_out);
   return hipGetLastError();
 }
 

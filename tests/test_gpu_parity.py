@@ -643,6 +643,29 @@ def test_relevance_in_the_attention_kernel(G, H, M, d, B, n_keep, n_sink, n_focu
         assert torch.equal(o2, out) and torch.equal(l2, lse)
 
 
+@pytest.mark.parametrize("H,d,n_keep,n_act", [
+    (32, 128, 5, 16), (32, 128, 16, 9), (28, 128, 18, 16),   # three key splits, eight, nine
+    (64, 64, 9, 16), (64, 64, 32, 13), (60, 64, 34, 16),     # five, sixteen, seventeen
+    (40, 128, 12, 40),                                       # more rows than one query tile
+])
+def test_combine_of_few_splits(G, H, d, n_keep, n_act):
+    """A wavefront or a workgroup merges the splits of a row: an empty split (ids outside the prompt), lse, rows past the count left alone."""
+    M, B, N, cap = 4096, 64, 0, n_act + 2
+    q, k, v = (_rand_bf16(171 + i, H, r, d).to(G.DEV) for i, r in enumerate((cap, M + N, M + N)))
+    listed = np.arange(0, 64, 64 // n_keep)[:n_keep]
+    listed[:2] = [-1, 64]                                    # the four sub-tiles of the first split
+    out = torch.full((H, cap, d), 7.0, dtype=torch.bfloat16, device=G.DEV)
+    lse = torch.full((H, cap), 9.0, device=G.DEV)
+    s = fb.make_shape(q, k, v, M, B, out)
+    buf = torch.full((fb.workspace_bytes(fb.FN_SPARSE_ATTN, s, cap, n_keep, 0),), 0xFF, dtype=torch.uint8, device=G.DEV)
+    fb.sparse_attn(q, G.i32(np.arange(cap)), G.i32([1, n_act]), k, v, s, G.i32(listed), n_keep, None, 0, out, lse, buf)
+    some, act = [0, H // 2, H - 1], np.arange(n_act)
+    ref, ref_lse = fo.sparse_attention(G.to_np(q[some]), act, G.to_np(k[some]), G.to_np(v[some]), fo.attention_index_set([], listed[2:], M, B), M)
+    G.assert_attention_close(out[some, :n_act], ref)
+    assert np.allclose(lse[some, :n_act].cpu().numpy(), ref_lse, atol=2e-3)
+    assert bool((out[:, n_act:] == 7).all()) and bool((lse[:, n_act:] == 9).all())
+
+
 def test_sparse_attn_dense_reduction(G):
     # keep every block, every row a query: plain bidirectional attention over all M+N keys
     H, M, N, d, B, n_gen = 4, 3000, 72, 128, 128, 64
