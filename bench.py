@@ -663,6 +663,10 @@ def main() -> int:
         tiles, bits = (1, 8) if cap > 64 else (2 if cap > 32 else 1, 0)
         return f"wide_attn_kernel<{wl.head_dim}, {tiles}, {bits + (2 if loop else 0)}>"
 
+    def combine_kernel(wl):
+        """The kernel that merges the key splits of such a call: a wavefront per row up to eight splits (every workload here), or a workgroup."""
+        return f"attn_combine_few_kernel<{wl.head_dim}, 8>" if wl.n_heads >= 32 else f"attn_combine_kernel<{wl.head_dim}>"
+
     def attn_traffic(wl, kernel):
         """HBM bytes of one focus_sparse_attn call (attention kernel: rows fetched + split partials written; combine: partials
         re-read + output written) from the stored rocprofv3 --pmc run of this script (--mode pmc, --parse-pmc), and where they come
@@ -678,7 +682,7 @@ def main() -> int:
             return None, f"{name} was recorded with other kernel sources"
         found = {}
         one_split = kernel.startswith("sparse_attn_kernel") and not kernel.endswith(", 4>")
-        for want in (kernel,) if one_split else (kernel, f"attn_combine_kernel<{wl.head_dim}>"):
+        for want in (kernel,) if one_split else (kernel, combine_kernel(wl)):
             # the dense comparison may share a name: the smallest dispatch is the sparse one
             found[want] = [v["fetch_bytes_min"] + v["write_bytes_min"] for key, v in pmc["kernels"].items() if want + "(" in key]
         missing = [want for want, v in found.items() if len(v) != 1]
@@ -688,7 +692,7 @@ def main() -> int:
                                                         "WRITE_SIZE) with the same kernel sources, not measured in this run")
 
     attn_name = attn_kernel(st0.max_active, w, H)
-    kernel_names = {"sparse_attn": f"{attn_name} + attn_combine_kernel<{d}> (one focus_sparse_attn call; in the step the attention kernel is "
+    kernel_names = {"sparse_attn": f"{attn_name} + {combine_kernel(w)} (one focus_sparse_attn call; in the step the attention kernel is "
                                    "its variant with the Top-C prologue)",
                     "select_and_sinks": "qk_logits_kernel / wide_logits_kernel and the rest of the sink chain",
                     "block_scores_cached": f"relevance_partial_kernel<{d}, false> + reduce_topk_kernel"}
@@ -723,7 +727,7 @@ def main() -> int:
         attn_p = attn_kernel(p_objs[0].max_active, wp, wp.n_heads)
         tr_p, tr_p_source = attn_traffic(wp, attn_p)
         roofline_paper = {"bound": "hbm", "workload": "paper32k", "stage": "sparse_attn",
-                          "kernel": f"{attn_p} + attn_combine_kernel<{wp.head_dim}> (one focus_sparse_attn call)",
+                          "kernel": f"{attn_p} + {combine_kernel(wp)} (one focus_sparse_attn call)",
                           "achieved": round(bytes_p / us_p * 1e-3, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                           "frac": round(bytes_p / us_p * 1e-3 / HBM_PEAK_GBS, 4), "traffic": tr_p,
                           "traffic_source": tr_p_source,
