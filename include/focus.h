@@ -232,8 +232,10 @@ int focus_sparse_layer_static(const void* Q, const int32_t* focus_idx, const int
 /*
  * The probe layer in one call: a dense layer of Alg. 1 (l <= l_dense: every key is attended, queries restricted to
  * I_active) whose attention also yields the sinks (Sec. 5.3: the attention of the last dense layer is the probe).
- *   out, lse     what focus_sparse_attn returns with every block kept and no sinks (the key axis is cut into 32-row
- *                tiles without regard to block boundaries, so bit-identical when M and B are multiples of 32)
+ *   out, lse     what focus_sparse_attn returns with every block kept and no sinks.  The key axis is cut into 32-row tiles
+ *                without regard to block boundaries, so bit-identical when M is a multiple of B and B of 32, else to
+ *                rounding; so also, with head_dim 64, up to 16 queries and eight heads or more, for more than
+ *                4 * floor(512 / n_heads) tiles, which this call cuts for fewer workgroups
  *   col_mass, sink_idx   S_j and I_sink of Eq. 6 as in focus_find_sinks; col_mass may be NULL
  * With at most 16 active queries the QK^T products of the attention are kept and reused, so K is read once for both
  * results; with more, one extra pass over K turns the attention's row log-sum-exps into column sums.  The column

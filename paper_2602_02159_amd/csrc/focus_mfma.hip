@@ -1692,6 +1692,9 @@ static void launch_wide_t(const AttnArgs& a, const SplitPlan& p, bool fused, hip
 // sub-tiles 11.1 -> 9.2, 13 of 256 blocks 12.0 -> 11.1, attention alone with 15 8.1 -> 8.0; 256 heads, 14 sub-tiles 16.9 -> 14.1; d = 128,
 // 4 heads, 8 sub-tiles 11.9 -> 10.8, 64 heads 12.5 -> 12.0, 256 heads 19.9 -> 15.8.  More than 256 blocks (whose ranking takes every
 // thread of a smaller workgroup) stay with the splits, ranked here or before: the bits of the output do not depend on that.
+// The probe layer goes the same way, or its output would not have the bits of the attention over all blocks (32-row tiles, heads, splits ->
+// this way: d = 64, 8 tiles, 4 heads 11.8 -> 10.3 us, 11 tiles, 32 heads 15.5 -> 15.0, 16 tiles, 4 heads 12.1 -> 11.8, 32 heads 16.7 and 17.1, 128
+// heads 32.0 -> 31.4; d = 128, 8 tiles, 4 heads 13.3 -> 12.8, 32 heads 16.5 -> 16.0, 128 heads 30.3 -> 29.2).
 // Returns 0 for the plan's splits.  Scratch memory is asked for as for the splits.
 static int one_split_waves(int head_dim, int n_b, const SplitPlan& p) {
   const int most = head_dim == 64 ? 16 : 8;
@@ -1715,7 +1718,9 @@ template <int D, int WAVES>
 static hipError_t launch_one_split(AttnArgs a, bool fused, hipStream_t st) {
   const dim3 grid(a.H), block(64 * WAVES);
   a.n_split = 1;
-  if (fused && a.kept_blocks != nullptr)
+  if (a.logits_out != nullptr)
+    ATTN_LAUNCH((sparse_attn_kernel<D, 4, WAVES>), grid, block, st, a);
+  else if (fused && a.kept_blocks != nullptr)
     ATTN_LAUNCH((sparse_attn_kernel<D, 65, WAVES>), grid, block, st, a);
   else if (fused && a.rel_per_head)
     ATTN_LAUNCH((sparse_attn_kernel<D, 9, WAVES>), grid, block, st, a);
@@ -1729,7 +1734,8 @@ static hipError_t launch_one_split(AttnArgs a, bool fused, hipStream_t st) {
 template <int D>
 static hipError_t launch_attn_t(const AttnArgs& a, const SplitPlan& p, bool fused, bool output_apart, hipStream_t st) {
   if (!p.pipelined && p.n_split * kWavesPerGroup < p.n_sub) return hipErrorInvalidValue;  // the loop-free variants: one sub-tile per wavefront
-  const int waves = a.logits_out == nullptr && output_apart ? one_split_waves(D, a.n_b, p) : 0;
+  if (fused && a.logits_out != nullptr) return hipErrorInvalidValue;
+  const int waves = output_apart ? one_split_waves(D, a.n_b, p) : 0;
   if (fused && a.kept_blocks != nullptr && waves == 0) return hipErrorInvalidValue;
   if (waves == 16) return launch_one_split<D, D == 64 ? 16 : 8>(a, fused, st);
   if (waves == 12) return launch_one_split<D, D == 64 ? 12 : 8>(a, fused, st);
@@ -1745,7 +1751,6 @@ static hipError_t launch_attn_t(const AttnArgs& a, const SplitPlan& p, bool fuse
     else
       launch_wide_t<D, 1, 2>(a, p, fused, st);
   } else if (a.logits_out != nullptr) {  // dense probe layer with the logits spilled
-    if (fused) return hipErrorInvalidValue;
     if (p.pipelined)
       ATTN_LAUNCH((sparse_attn_kernel<D, 6, 4>), grid, block, st, a);
     else

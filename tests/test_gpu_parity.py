@@ -855,6 +855,13 @@ def test_more_query_groups_than_one_grid_axis_holds(G, probe, H):
     (2, 8192, 64, 128, 128, 64, 16, 20),      # several splits, radix Top-N
     (2, 4100, 30, 128, 64, 64, 28, 7),        # two query tiles: column sums from a second pass over K
     (2, 3000, 0, 64, 64, 96, 72, 41),         # five query tiles (two groups), d = 64, no response rows
+    (3, 96, 33, 128, 32, 32, 16, 4),          # five sub-tiles, the fewest that one workgroup of eight wavefronts takes
+    (2, 256, 0, 128, 64, 64, 5, 3),           # eight, the most at d = 128
+    (2, 224, 33, 128, 32, 40, 16, 2),         # nine
+    (40, 128, 1, 64, 32, 64, 14, 1),          # d = 64: five
+    (3, 320, 30, 64, 64, 64, 9, 3),           # eleven, for twelve wavefronts
+    (2, 480, 20, 64, 32, 40, 14, 2),          # sixteen, the most
+    (2, 512, 20, 64, 32, 40, 14, 2),          # seventeen
 ])
 def test_probe_layer(G, H, M, N, d, B, n_gen, n_act, n_sink):
     """Dense attention of the active queries over every key plus the sinks it implies, in one call: the attention equals
@@ -867,7 +874,7 @@ def test_probe_layer(G, H, M, N, d, B, n_gen, n_act, n_sink):
     out, lse, col, sinks = G.gpu_probe_layer(q, active, counts, k, v, M, B, n_sink)
     n_b = -(-M // B)
     out_d, lse_d = G.gpu_sparse_attn(q, active, counts, k, v, M, B, G.i32(np.arange(n_b)), None)
-    if M % 32 == 0 and B % 32 == 0:    # the 32-row tiles of both paths coincide: same arithmetic in the same order
+    if M % B == 0 and B % 32 == 0:     # the 32-row tiles of both paths coincide: same arithmetic in the same order
         assert torch.equal(out[:, :n_act], out_d[:, :n_act]) and torch.equal(lse[:, :n_act], lse_d[:, :n_act])
     else:                              # the dense path tiles the key axis without regard to block boundaries
         assert np.allclose(G.to_np(out[:, :n_act]), G.to_np(out_d[:, :n_act]), atol=2e-3)
