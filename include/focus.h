@@ -33,6 +33,9 @@
  *  - Q is bf16 [H, n_gen, d]; K and V are bf16 [H, M+N, d] (rows 0..M-1 prompt, rows M..M+N-1 response);
  *    strides are in elements, the innermost (d) stride is 1, every row start must be 16-byte aligned
  *    (base pointers 16-byte aligned, row strides multiples of 8).
+ *  - An output must not share memory with an input, another output or the workspace of the same call, except where an
+ *    entry point updates a tensor in place.  (Which inputs have been read by the time an output is written depends on
+ *    the launch shape.)
  *  - `stream` is a hipStream_t (NULL = the null stream).  Calls only enqueue work: they never synchronise,
  *    and index sets stay on the device from one call to the next.
  *  - Every top-k orders by (value descending, index ascending), -0.0 equal to +0.0, NaN below every

@@ -393,7 +393,19 @@ static int sparse_layer_impl(const char* who, const void* Q, const int32_t* focu
   float* part_o = reinterpret_cast<float*>(ws + attn + w.at.part_o);
   float* part_ml = reinterpret_cast<float*>(ws + attn + w.at.part_ml);
   hipError_t e = hipSuccess;
-  const bool inner = fused && kbar && relevance_in_attention(*shape, p) && !output_over_queries(Q, out, max_active, *shape);
+  // (one launch then reads what a launch of its own had read before any output was written: as in attention_outputs_apart)
+  auto relevance_inputs_apart = [&]() {
+    const Extent read[] = {extent(Q, shape->q_stride_h, shape->q_stride_n, shape->n_heads, shape->n_gen, shape->head_dim),
+                           extent(kbar, (int64_t)shape->n_heads * n_b * shape->head_dim * 4), extent(focus_idx, (int64_t)n_focus_max * 4)};
+    const Extent written[] = {extent(out, shape->o_stride_h, shape->o_stride_n, shape->n_heads, max_active, shape->head_dim),
+                              extent(lse, (int64_t)shape->n_heads * max_active * 4), extent(R, (int64_t)n_b * 4), extent(kept_blocks, (int64_t)n_keep * 4)};
+    for (const Extent& r : read)
+      for (const Extent& o : written)
+        if (r.meets(o)) return false;
+    return true;
+  };
+  const bool inner = fused && kbar && relevance_in_attention(*shape, p) && relevance_inputs_apart() &&
+                     attention_outputs_apart(Q, active_idx, max_active, K, V, *shape, nullptr, 0, sink_idx, n_sink, out, lse);
   if (!kbar)
     e = launch_block_means_relevance(K, Q, focus_idx, counts, n_focus_max, *shape, nullptr, part, st);
   else if (!inner)

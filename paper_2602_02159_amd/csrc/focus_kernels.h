@@ -160,8 +160,31 @@ struct FusedTopC {
   const float* kbar = nullptr;  // relevance_in_attention: there are no partial relevances, the kernel works them out
   const int32_t* focus_idx = nullptr;
 };
-bool relevance_in_attention(const focus_shape& s, const SplitPlan& p);  // unless output_over_queries
-bool output_over_queries(const void* Q, const void* out, int max_active, const focus_shape& s);
+bool relevance_in_attention(const focus_shape& s, const SplitPlan& p);  // unless outputs and inputs share memory (sparse_layer_impl)
+
+// Memory that a call reads or writes: nothing (lo = hi), or the bytes [lo, hi) from the first to the last row of a tensor, those between
+// its rows included.
+struct Extent {
+  uintptr_t lo = 0, hi = 0;
+  bool meets(const Extent& o) const { return lo < o.hi && o.lo < hi; }
+};
+static inline Extent extent(const void* p, int64_t bytes) {
+  Extent e;
+  if (p != nullptr && bytes > 0) {
+    e.lo = reinterpret_cast<uintptr_t>(p);
+    e.hi = e.lo + (uintptr_t)bytes;
+  }
+  return e;
+}
+// bf16 [heads, rows, d]; the heads may lie in descending order
+static inline Extent extent(const void* p, int64_t stride_h, int64_t stride_n, int heads, int64_t rows, int d) {
+  const int64_t last = 2 * (heads - 1) * stride_h;
+  const void* first = p == nullptr ? nullptr : static_cast<const char*>(p) + (last < 0 ? last : 0);
+  return extent(first, (last < 0 ? -last : last) + 2 * ((rows - 1) * stride_n + d));
+}
+// True where the outputs of an attention call lie clear of what its attention kernel reads
+bool attention_outputs_apart(const void* Q, const int32_t* active_idx, int max_active, const void* K, const void* V, const focus_shape& s,
+                             const int32_t* kept_blocks, int n_keep, const int32_t* sink_idx, int n_sink, const void* out, const float* lse);
 // Dense (probe) layer: every one of the M + N key rows is attended (kept_blocks / sink_idx unused, plan from
 // plan_attention_dense); optionally the scaled logits (at most 16 active queries) and the base-2 row log-sum-exps are
 // written for the sink scoring that follows.

@@ -1701,11 +1701,20 @@ static int one_split_waves(int head_dim, int n_b, const SplitPlan& p) {
   if (p.q_tiles != 1 || p.n_split == 1 || p.pipelined || p.n_sub > most || n_b > 256) return 0;
   return p.n_sub <= 8 ? 8 : (p.n_sub <= 12 ? 12 : 16);
 }
-// The workgroup of one head would write its output while those of others still read their queries
-bool output_over_queries(const void* Q, const void* out, int max_active, const focus_shape& s) {
-  auto bytes = [&](int64_t sh, int64_t sn, int rows) { return 2 * ((s.n_heads - 1) * sh + (rows - 1) * sn + s.head_dim); };
-  const uintptr_t q = reinterpret_cast<uintptr_t>(Q), o = reinterpret_cast<uintptr_t>(out);
-  return s.o_stride_h < 0 || (q < o + (uintptr_t)bytes(s.o_stride_h, s.o_stride_n, max_active) && o < q + (uintptr_t)bytes(s.q_stride_h, s.q_stride_n, s.n_gen));
+// The workgroup of one head writes its output while those of others still read their inputs, where with key splits the launch that merges
+// them writes it when everyone has read everything.  Calls whose outputs share memory with an input, which the interface does not ask
+// anyone to take, therefore keep the splits and give what they always gave.  (The counts are read by the merging launch, too.)
+bool attention_outputs_apart(const void* Q, const int32_t* active_idx, int max_active, const void* K, const void* V, const focus_shape& s,
+                             const int32_t* kept_blocks, int n_keep, const int32_t* sink_idx, int n_sink, const void* out, const float* lse) {
+  const int64_t L = (int64_t)s.n_ctx + s.n_resp;
+  const Extent read[] = {extent(Q, s.q_stride_h, s.q_stride_n, s.n_heads, s.n_gen, s.head_dim),
+                         extent(K, s.k_stride_h, s.k_stride_n, s.n_heads, L, s.head_dim),
+                         extent(V, s.v_stride_h, s.v_stride_n, s.n_heads, L, s.head_dim),
+                         extent(active_idx, (int64_t)max_active * 4), extent(kept_blocks, (int64_t)n_keep * 4), extent(sink_idx, (int64_t)n_sink * 4)};
+  const Extent o = extent(out, s.o_stride_h, s.o_stride_n, s.n_heads, max_active, s.head_dim), l = extent(lse, (int64_t)s.n_heads * max_active * 4);
+  for (const Extent& r : read)
+    if (o.meets(r) || l.meets(r)) return false;
+  return true;
 }
 // Such a workgroup works the relevances of all heads out itself where its wavefronts do that in one go (16 blocks of a head each): a
 // launch less, against one more memory round trip in this one.  Whole layer with that launch and without: d = 64, 4 heads, 16 blocks,
@@ -1829,7 +1838,7 @@ hipError_t launch_sparse_attn(const void* Q, const int32_t* active_idx, const in
   a.scores_out = fused ? fused->scores_out : nullptr;
   a.kept_out = fused ? fused->kept_out : nullptr;
   a.n_focus_max = fused ? fused->n_focus_max : 0;
-  const bool apart = !output_over_queries(Q, out, max_active, s);
+  const bool apart = attention_outputs_apart(Q, active_idx, max_active, K, V, s, kept_blocks, n_keep, sink_idx, n_sink, out, lse);
   return s.head_dim == 128 ? launch_attn_t<128>(a, p, fused != nullptr, apart, st) : launch_attn_t<64>(a, p, fused != nullptr, apart, st);
 }
 

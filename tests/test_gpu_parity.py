@@ -643,6 +643,59 @@ def test_relevance_in_the_attention_kernel(G, H, M, d, B, n_keep, n_sink, n_focu
         assert torch.equal(o2, out) and torch.equal(l2, lse)
 
 
+@pytest.mark.parametrize("d,H,n_keep,n_sink", [
+    (128, 120, 6, 2), (128, 4, 6, 2),      # eight sub-tiles; with four heads the relevances come from the attention kernel
+    (64, 100, 6, 2), (64, 60, 13, 40),     # eight, sixteen
+    (64, 4, 11, 5),                        # thirteen, relevances in the attention kernel
+])
+@pytest.mark.parametrize("over", ["queries", "queries_reversed", "keys", "values", "means", "focus"])
+def test_outputs_that_share_memory_with_an_input(G, d, H, n_keep, n_sink, over):
+    """Short key lists whose output (a compact tensor, so that the rows of one head lie on those of other heads), log-sum-exps, scores or
+    block list lie over an input: read before they are written, as with key splits."""
+    M, B, N, n_gen, cap = 512, 16, 20, 40, 16
+    rng = np.random.default_rng(H + d)
+    src = [_rand_bf16(201 + i, H, r, d).to(G.DEV) for i, r in enumerate((n_gen, M + N, M + N))]
+    active, counts = G.i32(np.sort(rng.choice(n_gen, cap, replace=False))), G.i32([9, cap])
+    rows, sinks = G.i32(np.sort(rng.choice(n_gen, max(9, n_keep), replace=False))), G.i32(rng.choice(M, n_sink, replace=False))
+    means, n_b = G.gpu_block_means(src[1], M, B), M // B
+
+    for call in ("attention", "layer", "scan"):
+        if over in ("means", "focus") and call != "layer":
+            continue
+        got = []
+        for shared in (False, True):
+            q, k, v = (t.clone() for t in src)
+            kbar, focus = means.clone(), rows.clone()
+            out = torch.empty((H, cap, d), dtype=torch.bfloat16, device=G.DEV)
+            lse = torch.empty((H, cap), device=G.DEV)
+            scores, kept = torch.empty(n_b, device=G.DEV), G.i32(np.zeros(n_keep))
+            if shared:
+                if over in ("queries", "queries_reversed", "keys", "values"):
+                    out = {"keys": k, "values": v}.get(over, q).view(-1)[:H * cap * d].view(H, cap, d)
+                elif over == "means":   # the log-sum-exps at its start, the scores at its end
+                    lse, scores = kbar.view(-1)[:H * cap].view(H, cap), kbar.view(-1)[-n_b:]
+                else:
+                    kept = focus[:n_keep]
+            s = fb.make_shape(q, k, v, M, B, out)
+            reverse, first = over == "queries_reversed" and shared, out
+            if reverse:   # heads in descending order: the first one last
+                s.o_stride_h, first = -s.o_stride_h, out[H - 1]
+            if call == "attention":
+                blocks = G.i32(np.arange(1, 2 * n_keep, 2))
+                fb.sparse_attn(q, active, counts, k, v, s, blocks, n_keep, sinks, n_sink, first, lse,
+                               G.ws(fb.workspace_bytes(fb.FN_SPARSE_ATTN, s, cap, n_keep, n_sink)))
+            else:
+                fb.sparse_layer(q, focus, active, counts, k, v, kbar if call == "layer" else None, s, n_keep, sinks, n_sink, scores, kept, first, lse,
+                                G.ws(fb.workspace_bytes(fb.FN_SPARSE_LAYER, s, cap, n_keep, n_sink)))
+            torch.cuda.synchronize()
+            got.append((out.flip(0) if reverse else out.clone(), lse.clone(), scores.clone(), kept.clone()))
+        (o0, l0, s0, k0), (o1, l1, s1, k1) = got
+        G.assert_attention_close(o1, o0.double().cpu().numpy())   # the merge of the splits rounds in other places
+        assert torch.allclose(l0, l1, atol=2e-3)
+        if call != "attention":
+            assert torch.equal(s0, s1) and torch.equal(k0, k1)
+
+
 @pytest.mark.parametrize("H,d,n_keep,n_act", [
     (32, 128, 5, 16), (32, 128, 16, 9), (28, 128, 18, 16),   # three key splits, eight, nine
     (64, 64, 9, 16), (64, 64, 32, 13), (60, 64, 34, 16),     # five, sixteen, seventeen
