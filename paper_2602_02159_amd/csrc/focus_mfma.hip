@@ -460,12 +460,15 @@ __device__ __forceinline__ bf16x8 read_v_operand32(const char* stageV, int dt, i
 // the capacity n_q of the list, and the column-mass kernel does not fetch them: at eight queries half of the traffic beside K (32 heads, sink
 // chain of 8192 keys 28.8 -> 26.7 us, 32 832 73.5 -> 67.1, 131 136 255 -> 232; probe layer of 32 832 128 -> 118; four queries take as
 // long as eight, a line of 128 bytes; sixteen as before).  The device-side count would come too late for the second kernel's first loads.
+// n_q >= 1, which the launchers check: a whole sub-tile is then kSpillStores store instructions, whatever the list, and the key loops count
+// them among the requests under way.
+constexpr int kSpillStores = 2;
 __device__ __forceinline__ void spill_logits(float* __restrict__ logits, int h, int L, int n_q, int row0, const floatx4 (&acc)[2],
                                              float scale_log2, int lane) {
   const int c = lane & 15, g = lane >> 4;
   const int64_t n_quads = (L + 3) >> 2;
 #pragma unroll
-  for (int kt = 0; kt < 2; ++kt) {
+  for (int kt = 0; kt < kSpillStores; ++kt) {
     const int key0 = row0 + 16 * kt + 4 * g;
     if (key0 < L && c < n_q) {
       floatx4* dst = reinterpret_cast<floatx4*>(logits + (((int64_t)h * n_quads + (key0 >> 2)) * 16 + c) * 4);
@@ -1009,7 +1012,6 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 4 ? 2 : WAVES / 4) void sparse
     // are in registers, then the V rows likewise.  No barrier: the slots are private to the wavefront.
     // SPILL: the logits go out behind the request of the next V rows.  A whole sub-tile is two stores; they are counted, so that
     // nothing waits for them; those of a ragged one count for nothing and are waited for.
-    constexpr int kStores = 2;
     SubTile tn = list.take();
     bool stored = false;  // two stores behind the V rows under way
     for (int i = 0; i < rounds.n_rounds; ++i) {
@@ -1018,7 +1020,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 4 ? 2 : WAVES / 4) void sparse
       bf16x8 kop[2][G::kKSteps], vop[G::kColTiles], pb;
       if (here) {
         if (SPILL && stored)
-          wait_loads_but<G::kLoads + kStores>();
+          wait_loads_but<G::kLoads + kSpillStores>();
         else
           wait_loads_but<G::kLoads>();  // all but the V rows
         read_k_operands16<D>(kop, stageK, lane);
@@ -1042,7 +1044,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 4 ? 2 : WAVES / 4) void sparse
         if (!more)
           wait_loads();
         else if (SPILL && stored)
-          wait_loads_but<G::kLoads + kStores>();
+          wait_loads_but<G::kLoads + kSpillStores>();
         else
           wait_loads_but<G::kLoads>();  // all but the next K rows
         read_v_operands16<D>(vop, stageV, lane);
@@ -1725,6 +1727,7 @@ bool relevance_in_attention(const focus_shape& s, const SplitPlan& p) {
 }
 template <int D, int WAVES>
 static hipError_t launch_one_split(AttnArgs a, bool fused, hipStream_t st) {
+  if (a.n_sub > WAVES) return hipErrorInvalidValue;  // no key loop: the rest would be left out
   const dim3 grid(a.H), block(64 * WAVES);
   a.n_split = 1;
   if (a.logits_out != nullptr)
@@ -1746,9 +1749,11 @@ static hipError_t launch_attn_t(const AttnArgs& a, const SplitPlan& p, bool fuse
   if (fused && a.logits_out != nullptr) return hipErrorInvalidValue;
   const int waves = output_apart ? one_split_waves(D, a.n_b, p) : 0;
   if (fused && a.kept_blocks != nullptr && waves == 0) return hipErrorInvalidValue;
-  if (waves == 16) return launch_one_split<D, D == 64 ? 16 : 8>(a, fused, st);
-  if (waves == 12) return launch_one_split<D, D == 64 ? 12 : 8>(a, fused, st);
-  if (waves == 8) return launch_one_split<D, 8>(a, fused, st);
+  if constexpr (D == 64) {
+    if (waves == 16) return launch_one_split<D, 16>(a, fused, st);
+    if (waves == 12) return launch_one_split<D, 12>(a, fused, st);
+  }
+  if (waves != 0) return launch_one_split<D, 8>(a, fused, st);
   const dim3 grid = p.pipelined ? dim3(p.n_split, a.H) : dim3(a.H, p.n_split), block(256);
   if (p.q_tiles_per_group > 1) {
     if (a.logits_out != nullptr) return hipErrorInvalidValue;  // logits are spilled for one 16-query tile only
@@ -1803,6 +1808,7 @@ hipError_t launch_sparse_attn(const void* Q, const int32_t* active_idx, const in
                               const int32_t* sink_idx, int n_sink, const SplitPlan& p, void* out, float* lse,
                               float* part_o, float* part_ml, const FusedTopC* fused, hipStream_t st,
                               const DenseProbe* probe) {
+  if (max_active < 1) return hipErrorInvalidValue;
   AttnArgs a;
   a.dense_rows = probe ? s.n_ctx + s.n_resp : 0;
   a.logits_out = probe ? probe->logits_out : nullptr;
@@ -2484,7 +2490,7 @@ __global__ __launch_bounds__(256, 2) void qk_logits_kernel(const uint16_t* K, in
 
   float m_run = -INFINITY, l_run = 0.f;
   if constexpr (STAGES == 2) {
-    constexpr int kStores = 2;  // of a whole sub-tile's logits: counted, so that nothing waits for them; a ragged one's are waited for
+    // the stores of a whole sub-tile's logits are counted, so that nothing waits for them; a ragged one's are waited for
     char *here = stageK, *there = stageK + kWavesPerGroup * G::kStageBytes;
     int next = st + st_step;
     SubTile tn = key_subtile(next < st_end ? next : 0, p.L);
@@ -2494,7 +2500,7 @@ __global__ __launch_bounds__(256, 2) void qk_logits_kernel(const uint16_t* K, in
       if (next >= st_end)
         wait_loads();
       else if (stored)
-        wait_loads_but<G::kLoads + kStores>();
+        wait_loads_but<G::kLoads + kSpillStores>();
       else
         wait_loads_but<G::kLoads>();
       bf16x8 kop[2][G::kKSteps];
@@ -2844,7 +2850,7 @@ bool lse_in_logits(const SplitPlan& p) { return p.n_split <= 4 * kSplitsInFlight
 hipError_t launch_qk_logits(const void* Q, const int32_t* active_idx, const int32_t* counts, int max_active,
                             const void* K, const focus_shape& s, const SplitPlan& p, int mode, float* logits,
                             float* part_ml, const float* lse2, float* colpart, hipStream_t st, const SelectArgs* select) {
-  if (select != nullptr && (mode == 2 || s.n_gen > kSelectInLogitsGen)) return hipErrorInvalidValue;
+  if (max_active < 1 || (select != nullptr && (mode == 2 || s.n_gen > kSelectInLogitsGen))) return hipErrorInvalidValue;
   LogitArgs a;
   a.sel = select ? *select : SelectArgs{};
   a.Q = static_cast<const uint16_t*>(Q);

@@ -588,7 +588,7 @@ hipError_t launch_column_mass(const float* src, bool pre_reduced, const float* l
                               int n_parts, int H, int L, float* col_mass, int M, int n_sink, int32_t* cand, uint32_t* cand_keys,
                               int n_split, float* lse_scratch, hipStream_t st) {
   if (cand != nullptr && (n_sink < 1 || n_sink > kMaxNominees / ceil_div(M, kMassKeys))) return hipErrorInvalidValue;  // n_sink: nominees per group
-  if (!pre_reduced && n_parts < 1) return hipErrorInvalidValue;
+  if (!pre_reduced && (n_parts < 1 || max_active < 1)) return hipErrorInvalidValue;
   const dim3 grid(ceil_div(L, kMassKeys));
   if (pre_reduced) {
     hipLaunchKernelGGL((column_mass_kernel<true, false, 1, false>), grid, dim3(512), 0, st, src, lse2, counts, max_active, n_parts, H, L, col_mass,
