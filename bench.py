@@ -48,6 +48,33 @@ def kernel_sources_sha16() -> str:
     return h.hexdigest()[:16]
 
 
+def attention_kernels(wl, cap: int) -> list[str]:
+    """Names of the kernels that focus_sparse_attn launches for `cap` query slots (the launchers plan for the capacity of the active
+    list), as the profiler prints them: the attention kernel, and the one that merges the key splits where there are several."""
+    d, h = wl.head_dim, wl.n_heads
+    n_sub = wl.n_keep * -(-wl.block // 32) + -(-wl.n_resp // 32) + -(-wl.n_sink // 32)   # tiles of 32 keys
+    groups = -(-cap // 32) if cap > 64 else 1
+    splits = lambda target: min(max(1, target // (h * groups)), max(1, -(-n_sub // 4)))
+    small = lambda target: d == 64 and cap <= 16 and target // h <= 64
+    n_split = splits(1024 if small(1024) else 512)
+    if n_split * 4 < n_sub:
+        n_split = splits(512 if groups > 1 or small(512) else 256)
+    loop = n_split * 4 < n_sub                         # a wavefront walks several tiles
+    few = 16 if d == 64 else 8                         # tiles that one workgroup per head takes
+    if cap > 16:
+        tiles, bits = (1, 8) if cap > 64 else (2 if cap > 32 else 1, 0)
+        attn = f"wide_attn_kernel<{d}, {tiles}, {bits + (2 if loop else 0)}>"
+    elif n_split > 1 and not loop and n_sub <= few and -(-wl.n_ctx // wl.block) <= 256:
+        return [f"sparse_attn_kernel<{d}, 0, {8 if n_sub <= 8 else (12 if n_sub <= 12 else 16)}>"]
+    else:
+        attn = f"sparse_attn_kernel<{d}, {2 if loop else 0}, 4>"
+    if n_split == 1:
+        return [attn]
+    if groups == 1 and n_split <= 1024 // d:           # a wavefront per row; else a workgroup
+        return [attn, f"attn_combine_few_kernel<{d}, {8 if n_split <= 8 else 16}>"]
+    return [attn, f"attn_combine_kernel<{d}>"]
+
+
 def parse_pmc(fetch_db: str, write_db: str, workload: str) -> int:
     """Per-kernel HBM traffic from two `rocprofv3 --pmc` runs of `bench.py --mode pmc` (FETCH_SIZE, then WRITE_SIZE;
     both in KiB per dispatch), each scaled by what the same counter reads for the 1 GiB calibration copy."""
@@ -649,25 +676,7 @@ def main() -> int:
     dom = max(share, key=share.get)
     ds = stages[dom]
 
-    def attn_kernel(cap, wl, h):
-        """Name of the attention kernel that focus_sparse_attn launches for `cap` query slots (the launchers plan for the capacity of
-        the active list), as the profiler prints it: up to 16 queries, up to 32, up to 64, groups of 32."""
-        n_sub = wl.n_keep * -(-wl.block // 32) + -(-wl.n_resp // 32) + -(-wl.n_sink // 32)
-        groups = -(-cap // 32) if cap > 64 else 1
-        loop = max(1, 512 // (h * groups)) * 4 < n_sub   # a slot walks several sub-tiles
-        if cap <= 16:
-            few = 16 if wl.head_dim == 64 else 8   # sub-tiles that one workgroup per head takes, without a combine launch
-            if not loop and 4 < n_sub <= few and -(-wl.n_ctx // wl.block) <= 256:
-                return f"sparse_attn_kernel<{wl.head_dim}, 0, {8 if n_sub <= 8 else (12 if n_sub <= 12 else 16)}>"
-            return f"sparse_attn_kernel<{wl.head_dim}, {2 if loop else 0}, 4>"
-        tiles, bits = (1, 8) if cap > 64 else (2 if cap > 32 else 1, 0)
-        return f"wide_attn_kernel<{wl.head_dim}, {tiles}, {bits + (2 if loop else 0)}>"
-
-    def combine_kernel(wl):
-        """The kernel that merges the key splits of such a call: a wavefront per row up to eight splits (every workload here), or a workgroup."""
-        return f"attn_combine_few_kernel<{wl.head_dim}, 8>" if wl.n_heads >= 32 else f"attn_combine_kernel<{wl.head_dim}>"
-
-    def attn_traffic(wl, kernel):
+    def attn_traffic(wl, kernels):
         """HBM bytes of one focus_sparse_attn call (attention kernel: rows fetched + split partials written; combine: partials
         re-read + output written) from the stored rocprofv3 --pmc run of this script (--mode pmc, --parse-pmc), and where they come
         from.  None, with the reason, when that run was of other kernels."""
@@ -681,8 +690,7 @@ def main() -> int:
         if pmc.get("kernel_sources_sha16") != kernel_sources_sha16():
             return None, f"{name} was recorded with other kernel sources"
         found = {}
-        one_split = kernel.startswith("sparse_attn_kernel") and not kernel.endswith(", 4>")
-        for want in (kernel,) if one_split else (kernel, combine_kernel(wl)):
+        for want in kernels:
             # the dense comparison may share a name: the smallest dispatch is the sparse one
             found[want] = [v["fetch_bytes_min"] + v["write_bytes_min"] for key, v in pmc["kernels"].items() if want + "(" in key]
         missing = [want for want, v in found.items() if len(v) != 1]
@@ -691,12 +699,12 @@ def main() -> int:
         return int(sum(v[0] for v in found.values())), (f"{name}: a separate rocprofv3 --pmc run of `bench.py --mode pmc` (FETCH_SIZE, "
                                                         "WRITE_SIZE) with the same kernel sources, not measured in this run")
 
-    attn_name = attn_kernel(st0.max_active, w, H)
-    kernel_names = {"sparse_attn": f"{attn_name} + {combine_kernel(w)} (one focus_sparse_attn call; in the step the attention kernel is "
+    attn_names = attention_kernels(w, st0.max_active)
+    kernel_names = {"sparse_attn": f"{' + '.join(attn_names)} (one focus_sparse_attn call; in the step the attention kernel is "
                                    "its variant with the Top-C prologue)",
                     "select_and_sinks": "qk_logits_kernel / wide_logits_kernel and the rest of the sink chain",
                     "block_scores_cached": f"relevance_partial_kernel<{d}, false> + reduce_topk_kernel"}
-    traffic, traffic_source = attn_traffic(w, attn_name) if dom == "sparse_attn" else (None, None)
+    traffic, traffic_source = attn_traffic(w, attn_names) if dom == "sparse_attn" else (None, None)
     roofline = {"bound": "hbm", "kernel": kernel_names[dom], "stage": dom, "achieved": ds["GBps"], "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": ds["hbm_frac"], "traffic": traffic,
                 "traffic_source": traffic_source,
@@ -724,10 +732,10 @@ def main() -> int:
         us_pl = time_stage(p_objs, "sparse_layer_cached", 8)
         us_pd = time_stage(p_objs, "dense_attn", 4)
         us_ps = time_stage(p_objs, "find_sinks", 4)
-        attn_p = attn_kernel(p_objs[0].max_active, wp, wp.n_heads)
+        attn_p = attention_kernels(wp, p_objs[0].max_active)
         tr_p, tr_p_source = attn_traffic(wp, attn_p)
         roofline_paper = {"bound": "hbm", "workload": "paper32k", "stage": "sparse_attn",
-                          "kernel": f"{attn_p} + {combine_kernel(wp)} (one focus_sparse_attn call)",
+                          "kernel": f"{' + '.join(attn_p)} (one focus_sparse_attn call)",
                           "achieved": round(bytes_p / us_p * 1e-3, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                           "frac": round(bytes_p / us_p * 1e-3 / HBM_PEAK_GBS, 4), "traffic": tr_p,
                           "traffic_source": tr_p_source,

@@ -2,6 +2,7 @@
 import importlib.util
 import json
 import os
+from types import SimpleNamespace
 
 import numpy as np
 import pytest
@@ -80,3 +81,25 @@ def test_strong_sink_variant_makes_planted_keys_the_sinks():
     S = fo.sink_scores(Q, active, K)
     assert fo.select_sinks(S, w.n_ctx, w.n_sink).tolist() == list(w.sink_positions)
     assert S[list(w.sink_positions)].sum() > 0.2      # they hold a large share of all attention mass
+
+
+@pytest.mark.parametrize("shape,cap,names", [   # as a kernel trace of such focus_sparse_attn calls lists them
+    ((32, 128, 32768, 64, 128, 7, 4), 16, ["sparse_attn_kernel<128, 0, 4>", "attn_combine_few_kernel<128, 8>"]),
+    ((28, 128, 8192, 0, 64, 18, 0), 16, ["sparse_attn_kernel<128, 0, 4>", "attn_combine_kernel<128>"]),          # nine key splits
+    ((16, 128, 8192, 64, 64, 14, 4), 16, ["sparse_attn_kernel<128, 0, 4>", "attn_combine_few_kernel<128, 8>"]),  # eight, few heads
+    ((60, 64, 4096, 0, 64, 17, 0), 16, ["sparse_attn_kernel<64, 0, 4>", "attn_combine_few_kernel<64, 16>"]),
+    ((32, 64, 4096, 64, 64, 50, 0), 16, ["sparse_attn_kernel<64, 0, 4>", "attn_combine_kernel<64>"]),
+    ((4, 64, 1024, 32, 64, 4, 2), 8, ["sparse_attn_kernel<64, 0, 12>"]),
+    ((4, 128, 256, 8, 16, 6, 2), 16, ["sparse_attn_kernel<128, 0, 8>"]),
+    ((600, 64, 300, 20, 16, 15, 0), 16, ["sparse_attn_kernel<64, 2, 4>"]),
+    ((33, 128, 200, 20, 32, 3, 0), 10, ["sparse_attn_kernel<128, 0, 4>"]),
+    ((32, 128, 32768, 256, 64, 256, 327), 25, ["wide_attn_kernel<128, 1, 2>", "attn_combine_few_kernel<128, 8>"]),
+    ((4, 128, 16384, 256, 64, 26, 40), 200, ["wide_attn_kernel<128, 1, 8>", "attn_combine_kernel<128>"]),
+    ((32, 128, 8192, 64, 64, 128, 0), 50, ["wide_attn_kernel<128, 2, 2>", "attn_combine_few_kernel<128, 8>"]),
+])
+def test_benchmark_names_the_kernels_that_an_attention_call_launches(shape, cap, names):
+    spec = importlib.util.spec_from_file_location("bench", os.path.join(os.path.dirname(HERE), "bench.py"))
+    bench = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(bench)
+    fields = ("n_heads", "head_dim", "n_ctx", "n_resp", "block", "n_keep", "n_sink")
+    assert bench.attention_kernels(SimpleNamespace(**dict(zip(fields, shape))), cap) == names
