@@ -203,9 +203,10 @@ int focus_sparse_attn(const void* Q, const int32_t* active_idx, const int32_t* c
 /*
  * One sparse layer of Alg. 1 in a single call: block relevance (Eq. 7), Top-C, index union (Eq. 8) and sparse
  * attention (Eq. 9) — exactly focus_block_scores followed by focus_sparse_attn, with the same arguments and
- * bit-identical outputs (scores, kept_blocks, out, lse), but in three kernel launches instead of four: the
+ * bit-identical outputs (scores, kept_blocks, out, lse), but in up to three kernel launches instead of up to four: the
  * attention kernel ranks the blocks itself from the partial relevances instead of waiting for a separate Top-C
- * kernel.  kbar NULL: the first launch scans K and forms the block means on the fly.
+ * kernel (short key lists of few heads need one launch: it forms the relevances, too, and writes the output itself).
+ * kbar NULL: the first launch scans K and forms the block means on the fly.
  * With more than 2048 prompt blocks (kbar NULL: more than 256), or more than 1024 and less workspace than the sum of what
  * focus_block_scores and focus_sparse_attn need, the call falls back to the separate kernels.
  */

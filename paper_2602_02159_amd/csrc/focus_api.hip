@@ -40,7 +40,12 @@ constexpr int kAttnGroups = 512;      // one sub-tile per slot: every workgroup 
 // only (16.6 -> 15.4) and lose from 91 on; nor does the probe layer gain, whose kernel also writes its logits (1026 sub-tiles 80.0 ->
 // 80.7).
 constexpr int kAttnGroupsSmall = 1024, kAttnGroupsSmallPipe = 512, kAttnSplitsSmall = 64;
-constexpr int kAttnGroupsPipe = 256;  // many sub-tiles per slot, two stages per slot: one workgroup per compute unit
+// Many sub-tiles per slot: one workgroup per compute unit.  With up to 32 queries, whose slots have one stage, two would be resident, but
+// one keeps enough under way, and two leave twice the partial results (256 workgroups and 512, a call: 32 heads, 8256 keys 26.7 and 28.9
+// us, 32 832 keys 84.0 and 86.8; 28 queries 28.3 and 31.3, 86.2 and 90.6; half of 512 blocks, 25 queries 51.0 and 53.3; 8 heads, 16 448
+// keys 18.6 and 19.8; 4 heads, d = 64, 28 queries, 32 832 keys 13.7 and 15.3; probe layer of 32 832 keys 128.2 and 129.7).  33 to 64
+// queries have two stages, and LDS for one.
+constexpr int kAttnGroupsPipe = 256;
 constexpr int kAttnGroupsWide = 512;  // the same where query groups share the rows: one stage per slot, two workgroups per compute unit
 // Sink scoring, one query tile.  About four rounds of sub-tiles per workgroup where all workgroups are resident at once (1024), so that a
 // workgroup's start passes beside the others' rows and there are few statistics to merge, and the same number of workgroups for every
@@ -75,7 +80,7 @@ static void plan_attention_splits(SplitPlan& p, const focus_shape& s, bool logit
   const bool d64 = s.head_dim == 64 && p.q_tiles == 1 && !logits_out && !lean;
   auto small = [&](int groups) { return d64 && groups / s.n_heads <= kAttnSplitsSmall; };
   plan_splits(p, s.n_heads, p.q_groups, small(kAttnGroupsSmall) ? kAttnGroupsSmall : kAttnGroups);
-  // Many sub-tiles per wavefront (dense layers, alpha = 0.5): fewer, longer workgroups with double-buffered key loops.
+  // Many sub-tiles per wavefront (dense layers, alpha = 0.5): fewer, longer workgroups with key loops.
   // One sub-tile per wavefront (the 3 % keep configurations): nothing to overlap.
   if (p.n_split * kWavesPerGroup < p.n_sub) {
     plan_splits(p, s.n_heads, p.q_groups, small(kAttnGroupsSmallPipe) ? kAttnGroupsSmallPipe : (p.q_groups > 1 ? kAttnGroupsWide : kAttnGroupsPipe));

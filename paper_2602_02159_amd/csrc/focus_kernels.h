@@ -38,7 +38,7 @@ __device__ __forceinline__ int list_index() { return (int)(blockIdx.y * kListSli
 // channels: the 32K dense layer with 30 queries takes 96 us that way, 89 us this way.)
 struct SplitPlan {
   int n_sub, n_split;
-  bool pipelined = false;  // attention only: wavefronts walk several sub-tiles, use the double-buffered key loop
+  bool pipelined = false;  // attention only: wavefronts walk several sub-tiles, use the key loop
   int q_tiles, q_tiles_per_group, q_groups, q_pad;  // q_pad = 16 * q_tiles
 };
 

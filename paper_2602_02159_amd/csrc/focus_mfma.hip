@@ -5,7 +5,7 @@
 //                        (v_mfma_f32_16x16x32_bf16).  The same kernel with every row kept is the dense layer (probe
 //                        layer, dense comparison).
 //   wide_attn_kernel     the same for more than 16 queries (v_mfma_f32_32x32x16_bf16; described where it is defined).
-//   attn_combine_kernel  merges the key splits of the two kernels above.
+//   attn_combine_kernel, attn_combine_few_kernel   merge the key splits of the two kernels above.
 //   refresh_attn_kernel  block entry (Alg. 1): dense attention of EVERY position over every key, the one MFMA-bound
 //                        launch of the method (v_mfma_f32_32x32x16_bf16; described where it is defined).
 //   refresh_tail_kernel  the query tiles the former leaves over, with the layer's cache refresh beside them.
@@ -870,7 +870,7 @@ struct RoundList {
 // heads, 8256 keys 30.3 -> 28.3 us a call, 32 832 keys 86.3 -> 85.1; 8 heads, 16 448 keys 20.6 -> 18.9; 30 of 1024 blocks, whole layer
 // 27.0 -> 26.1; probe layer of 32 832 keys 130.4 -> 128.7.
 // WAVES: four, and a second, small kernel merges the key splits.  (Letting the last workgroup of a head merge them
-// behind device-scope fences was measured: the fences cost ~10 us per launch, more than the launch they save.)  Eight, twelve or sixteen
+// behind device-scope fences was measured on earlier forms: the fences cost several times what the launch does.)  Eight, twelve or sixteen
 // for the one workgroup of a head with a short key list, which writes the output itself (one_split_waves); the first 256 threads store.
 template <int D, int FUSE, int WAVES>
 __global__ __launch_bounds__(64 * WAVES, WAVES == 4 ? 2 : WAVES / 4) void sparse_attn_kernel(ATTN_FIRST_PARAMS, const AttnArgs args) {
@@ -1267,7 +1267,7 @@ __device__ __forceinline__ void store_o_tile(char* dst, const floatx16 (&o)[D / 
 // More than 16 queries: the same work decomposition as the 16-query kernel — a sub-tile goes from the memory request to the
 // MFMAs in one slot of LDS — with 32-query tiles on v_mfma_f32_32x32x16_bf16.  A 32x32 tile takes
 // half the LDS operand reads and half the MFMA instructions of two 16-query tiles, so that the QK^T -> softmax -> PV chain of
-// an in-order wavefront fits into the time its share of HBM needs for the next sub-tile (probabilities32, add_values32).
+// an in-order wavefront fits into the time its share of HBM needs for the next sub-tile (probabilities32).
 // NT = 1 (up to 32 queries per query group), four wavefronts: a wavefront owns its slot; no barrier in the key loop.
 // NT = 2 (up to 64), eight wavefronts: wavefronts s and s + 4 share slot s, each stages half of its rows (K / V) and carries
 //   one query tile; two stages per slot, one barrier per round.  (One wavefront with both tiles needs 128 accumulator registers outside the
@@ -1693,7 +1693,10 @@ static void launch_wide_t(const AttnArgs& a, const SplitPlan& p, bool fused, hip
 // sixteen at d = 64, where the two ways meet.  Whole layer, splits -> this way: d = 64, 4 heads, 10 sub-tiles 10.8 -> 9.2 us; 32 heads, 6
 // sub-tiles 11.1 -> 9.2, 13 of 256 blocks 12.0 -> 11.1, attention alone with 15 8.1 -> 8.0; 256 heads, 14 sub-tiles 16.9 -> 14.1; d = 128,
 // 4 heads, 8 sub-tiles 11.9 -> 10.8, 64 heads 12.5 -> 12.0, 256 heads 19.9 -> 15.8.  More than 256 blocks (whose ranking takes every
-// thread of a smaller workgroup) stay with the splits, ranked here or before: the bits of the output do not depend on that.
+// thread of a smaller workgroup) stay with the splits, ranked here or before: the bits of the output do not depend on that.  So do more
+// heads than leave a plan with two splits (d = 64 more than 512, d = 128 more than 256): one workgroup of four wavefronts per head, with a
+// key loop.  Twelve wavefronts, against sixteen for the same nine to twelve sub-tiles: 4 heads, whole layer 7.5 and 7.8 us, 32 heads 9.8 and
+// 10.1, 128 heads 11.4 and 11.6, 256 heads 13.4 and 13.7.
 // The probe layer goes the same way, or its output would not have the bits of the attention over all blocks (32-row tiles, heads, splits ->
 // this way: d = 64, 8 tiles, 4 heads 11.8 -> 10.3 us, 11 tiles, 32 heads 15.5 -> 15.0, 16 tiles, 4 heads 12.1 -> 11.8, 32 heads 16.7 and 17.1, 128
 // heads 32.0 -> 31.4; d = 128, 8 tiles, 4 heads 13.3 -> 12.8, 32 heads 16.5 -> 16.0, 128 heads 30.3 -> 29.2).
@@ -2341,8 +2344,10 @@ static hipError_t launch_refresh_t(RefreshArgs& a, const focus_shape& s, const C
     copy = nullptr;
   }
   const dim3 grid((uint32_t)(copy ? tails + copies : tails)), block(64 * kRefreshWaves);
-  // d = 64: a few tiles among many chunks, which is what long prompts leave over, have a compute unit each (LDS that nobody uses sees to
-  // it): they are the last to finish, and a chunk beside them costs more than it gains (32 heads, 8256 rows 694 us, 698 without).
+  // d = 64: up to 128 tiles, which is what long prompts leave over, have a compute unit each (LDS that nobody uses sees to it): they are the
+  // last to finish, and a chunk beside them costs more than it gains.  Layer with and without, medians of 24 pairs in turn: 32 heads, 4104
+  // rows 193.8 and 195.8 us, 8256 rows 660.4 and 663.8; 8 heads, 8256 rows 209.1 and 210.0; 16 heads, 16 404 rows 1255.7 and 1258.9; 4
+  // heads, 16 404 rows 394.1 and 395.3.
   const uint32_t alone = D == 64 && copy && a.n_tail <= kSlots / 2 ? 32768 : 0;
   if (a.lse)
     hipLaunchKernelGGL((refresh_tail_kernel<D, true>), grid, block, alone, st, a, copy ? *copy : CacheRefresh{});
@@ -2796,7 +2801,10 @@ __global__ __launch_bounds__(256, NT == 1 ? 4 : 2) void wide_logits_kernel(const
 // resident at once all the same, or are many and long.  Sink chain with one stage and with two: 32 heads, 8256 keys, 16 splits 29.4 and
 // 28.7 us, 4160 keys, 8 splits 20.9 and 19.9; 16 heads, 8256 keys 20.2 and 19.2; 4 heads, 32 832 keys 21.1 and 20.2; 32 heads, 131 136
 // keys, 4096 workgroups of eight rounds 264 and 259; but 15 986 keys, 1024 workgroups of four rounds 43.4 and 44.2, 32 832 keys, 4128 of
-// two 75.3 and 81.0.
+// two 75.3 and 81.0.  The same, 4096 workgroups of 32 to 128 heads: 49 216 keys, three rounds 106 and 108; 65 600, four 137.5 and 136.0;
+// 98 368, six 201.5 and 197.4; 120 064, seven 240.5 and 233.3 (so the line could lie lower, at four rounds); eight and more: 64 heads,
+// 65 600 keys 272 and 265, 128 heads, 32 832 keys 285 and 278, d = 64 185 and 183; 64 heads, d = 64, 80 064 keys 219 and 215; 32 heads,
+// 200 064 keys 914 and 904.
 static bool logits_in_two_stages(const SplitPlan& p, int n_heads) {
   const int rounds = ceil_div(p.n_sub, kWavesPerGroup);
   return rounds >= 4 * p.n_split && ((int64_t)p.n_split * n_heads <= 512 || rounds >= 8 * p.n_split);

@@ -563,7 +563,9 @@ def test_key_loop_of_many_rounds(G, d, n_act, M):
     (33, 1000, 30, 64, 16, 3, 40),   # nine; sinks in two sub-tiles, against the bitmap of the kept blocks
     (2, 1000, 30, 64, 7, 4, 60),     # eleven
     (2, 4000, 64, 16, 16, 10, 7),    # thirteen
-    (600, 300, 20, 16, 5, 15, 0),    # sixteen, the most at d = 64; more heads than one round of workgroups
+    (256, 300, 20, 16, 5, 15, 0),    # sixteen, the most at d = 64, with the most heads that get four key splits else
+    (512, 150, 20, 16, 5, 7, 0),     # eight, with the most heads that get two
+    (600, 300, 20, 16, 5, 15, 0),    # sixteen for more heads than that: a key loop
     (2, 4000, 20, 16, 5, 16, 0),     # seventeen
 ])
 def test_sparse_attn_of_few_sub_tiles(G, d, H, M, N, B, n_act, n_keep, n_sink):
@@ -611,7 +613,7 @@ def test_sparse_attn_of_few_sub_tiles(G, d, H, M, N, B, n_act, n_keep, n_sink):
     (4, 1056, 128, 32, 6, 2, 1, False),      # ... of three times: relevances by a launch
     (9, 256, 128, 16, 7, 0, 9, False),       # nine heads: by a launch
     (12, 200, 64, 16, 10, 5, 33, False),     # twelve wavefronts, three groups of heads; a ragged last block
-    (5, 700, 64, 16, 13, 5, 40, False),      # sixteen; two groups, one with one head, and a wavefront with nothing to do
+    (5, 700, 64, 16, 13, 5, 40, False),      # sixteen, for fifteen sub-tiles; two groups, one with one head
     (16, 100, 64, 8, 13, 40, 5, False),      # four groups
     (1, 4096, 64, 16, 15, 0, 80, False),     # one head, 256 blocks
     (8, 256, 128, 16, 7, 3, 16, True),       # the output lies over the queries: key splits, relevances by a launch
@@ -1649,6 +1651,9 @@ def test_block_entry_then_step_uses_the_refreshed_cache_and_means(G):
     (3, 1000, 37, 128, 128),    # an odd number of chunks, ragged blocks
     (40, 1060, 40, 64, 128),    # whole blocks, then tiles
     (256, 256, 0, 128, 64),     # no tiles: the copy has a launch of its own
+    (128, 500, 44, 50, 64),     # whole blocks and 128 tiles of 64 columns, which get a compute unit each beside the chunks of the copy
+    (129, 500, 44, 50, 64),     # 145 tiles, which share theirs
+    (1, 30, 0, 32, 64),
     (1, 30, 0, 32, 128),
 ])
 def test_block_entry_equals_the_two_calls(G, H, M, N, B, d):
