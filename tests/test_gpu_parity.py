@@ -650,10 +650,10 @@ def test_relevance_in_the_attention_kernel(G, H, M, d, B, n_keep, n_sink, n_focu
     (64, 100, 6, 2), (64, 60, 13, 40),     # eight, sixteen
     (64, 4, 11, 5),                        # thirteen, relevances in the attention kernel
 ])
-@pytest.mark.parametrize("over", ["queries", "queries_reversed", "keys", "values", "means", "focus"])
+@pytest.mark.parametrize("over", ["queries", "queries_reversed", "reversed", "keys", "values", "means", "focus"])
 def test_outputs_that_share_memory_with_an_input(G, d, H, n_keep, n_sink, over):
     """Short key lists whose output (a compact tensor, so that the rows of one head lie on those of other heads), log-sum-exps, scores or
-    block list lie over an input: read before they are written, as with key splits."""
+    block list lie over an input: read before they are written, as with key splits.  ("reversed": only the heads in descending order.)"""
     M, B, N, n_gen, cap = 512, 16, 20, 40, 16
     rng = np.random.default_rng(H + d)
     src = [_rand_bf16(201 + i, H, r, d).to(G.DEV) for i, r in enumerate((n_gen, M + N, M + N))]
@@ -676,10 +676,10 @@ def test_outputs_that_share_memory_with_an_input(G, d, H, n_keep, n_sink, over):
                     out = {"keys": k, "values": v}.get(over, q).view(-1)[:H * cap * d].view(H, cap, d)
                 elif over == "means":   # the log-sum-exps at its start, the scores at its end
                     lse, scores = kbar.view(-1)[:H * cap].view(H, cap), kbar.view(-1)[-n_b:]
-                else:
+                elif over == "focus":
                     kept = focus[:n_keep]
             s = fb.make_shape(q, k, v, M, B, out)
-            reverse, first = over == "queries_reversed" and shared, out
+            reverse, first = over.endswith("reversed") and shared, out
             if reverse:   # heads in descending order: the first one last
                 s.o_stride_h, first = -s.o_stride_h, out[H - 1]
             if call == "attention":
