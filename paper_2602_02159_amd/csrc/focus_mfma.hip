@@ -1873,7 +1873,11 @@ hipError_t launch_sparse_attn(const void* Q, const int32_t* active_idx, const in
 // the rescale of O runs only when some running maximum in the wavefront moved, and the ragged last sub-tile has a
 // loop body of its own.  No index lists, no key splits across workgroups: each normalises and writes its own rows.
 // One-dimensional grid over the (head, query block) list, dealt to the XCDs in contiguous eighths (see the kernel).
-// The queries that would leave a round of workgroups mostly empty go to refresh_tail_kernel.
+// PARTS = 2: a half block of 128 queries.  Four wavefronts carry its tiles over the even key sub-tiles, four over the odd ones, each four with
+// rings of their own (half as long: a barrier per two sub-tiles), and the two states of a tile are added at the end.  A
+// workgroup then fetches and stores twice the rows per product and takes 0.55 us where a block takes 0.83 (32-row sub-tile of 256 workgroups at
+// d = 128), which is less than an empty half of a round costs.  LSE: the log-sum-exps are wanted; they are then those of the unrounded sums.
+// The queries that would leave a round of workgroups mostly empty go there or to refresh_tail_kernel (cut_refresh).
 // =====================================================================================================
 struct RefreshArgs {
   const uint16_t* Q;
@@ -1885,6 +1889,8 @@ struct RefreshArgs {
   int n_q, L;
   int n_qb, n_work;    // whole query blocks per head; work items (head, query block) of refresh_attn_kernel
   int n_heads, n_tail;  // query tiles left to refresh_tail_kernel
+  // half blocks of four tiles (refresh_attn_kernel<., 2, .>): so many of whole blocks, then so many of every head's last tiles
+  int n_half_whole, n_half_head;
   float scale_log2;
 };
 
@@ -1907,39 +1913,67 @@ __device__ __forceinline__ void pin(int& x) { asm volatile("" : "+v"(x)); }
 // reads, but a lone wavefront cannot cover its own dependent vector-ALU chains: 0.82 against 1.01 PFLOP/s.)
 constexpr int kRefreshWaves = 8;  // wavefronts per workgroup
 constexpr int kRefreshBlock = 4;  // sub-tiles between two barriers
+constexpr int kHalfTiles = kRefreshWaves / 2;  // query tiles of a half block
 
-template <int D>
-__global__ __launch_bounds__(64 * kRefreshWaves, 2) void refresh_attn_kernel(const RefreshArgs p) {
+template <int D, int PARTS, bool LSE>
+__global__ __launch_bounds__(64 * kRefreshWaves, 2) void refresh_attn_kernel(const RefreshArgs p, const CacheRefresh copy) {
   using G = Geo<D>;
   constexpr int kKS = D / 16;                    // k-steps of K Q^T
   constexpr int kDT = D / 32;                    // 32-wide d tiles of V^T P^T
-  constexpr int NB = kRefreshBlock, kRing = 2 * NB;
-  constexpr int kShare = kRefreshWaves / 2;      // wavefronts that share the K (or the V) rows of a sub-tile
+  constexpr int NB = kRefreshBlock / PARTS, kRing = 2 * NB;
+  constexpr int kPartWaves = kRefreshWaves / PARTS;  // query tiles of a workgroup
+  constexpr int kShare = kPartWaves / 2;         // wavefronts that share the K (or the V) rows of a sub-tile
   constexpr int NL = G::kLoads / kShare;         // loads per wavefront and sub-tile
   static_assert(G::kLoads % kShare == 0 && NL >= 1, "every wavefront stages at least one load");
   // K sub-tile j sits in slot (j - 1) mod kRing of its ring, V sub-tile j in slot j mod kRing: iteration t reads slot t mod kRing of both
-  __shared__ __attribute__((aligned(16))) char ringK[kRing * G::kStageBytes];
-  __shared__ __attribute__((aligned(16))) char ringV[kRing * G::kStageBytes];
+  __shared__ __attribute__((aligned(16))) char ringsK[PARTS * kRing * G::kStageBytes];
+  __shared__ __attribute__((aligned(16))) char ringsV[PARTS * kRing * G::kStageBytes];
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int part = PARTS == 1 ? 0 : wave / kPartWaves, tile = PARTS == 1 ? wave : wave % kPartWaves;
   const int qi = lane & 31, hh = lane >> 5;
   // Workgroups are handed to the 8 XCDs round-robin in launch order, and each XCD has its own L2.  Launch slot i is
   // therefore given work item (i % 8) * chunk + i / 8 of the (head, query block) list: an XCD walks one contiguous
   // eighth of the list, so the workgroups resident on it at any time are neighbouring query blocks of ONE head and
   // stream the same K/V rows through its L2 together.
-  const int chunk = (p.n_work + 7) >> 3;
+  const int n_items = PARTS == 1 ? p.n_work : p.n_half_whole + p.n_half_head * p.n_heads;
+  const int chunk = (n_items + 7) >> 3;
+  if (PARTS > 1 && (int)blockIdx.x >= 8 * chunk) {  // the layer's cache refresh on the side, as in refresh_tail_kernel
+    const int half = threadIdx.x >> 8, item = 2 * ((int)blockIdx.x - 8 * chunk) + half;
+    const bool live = item < copy.n_chunks * copy.n_heads;
+    const int ch = live ? item / copy.n_chunks : 0;
+    static_assert(2 * 2048 * sizeof(float) <= sizeof(ringsK), "both halves' partial means fit");
+    cache_refresh_chunk<D>(copy, live ? item - ch * copy.n_chunks : 0, ch, threadIdx.x & 255, live, reinterpret_cast<float*>(ringsK) + half * 2048);
+    return;
+  }
   const int work = (int)(blockIdx.x & 7u) * chunk + (int)(blockIdx.x >> 3);
-  if (work >= p.n_work) return;  // whole workgroup
-  const int h = work / p.n_qb;
-  const int q_row = (work - h * p.n_qb) * (32 * kRefreshWaves) + wave * 32 + qi;
-  const int n_tiles = (p.L + kSubTile - 1) / kSubTile;
+  if (work >= n_items) return;  // whole workgroup
+  int h, tile0;  // first query tile
+  if (PARTS == 1) {
+    h = work / p.n_qb;
+    tile0 = (work - h * p.n_qb) * kRefreshWaves;
+  } else if (work < p.n_half_whole) {
+    const int block = p.n_work + work / PARTS;
+    h = block / p.n_qb;
+    tile0 = (block - h * p.n_qb) * kRefreshWaves + work % PARTS * kPartWaves;
+  } else {
+    const int i = work - p.n_half_whole;
+    h = i / p.n_half_head;
+    tile0 = p.n_qb * kRefreshWaves + (i - h * p.n_half_head) * kPartWaves;
+  }
+  const int q_row = (tile0 + tile) * 32 + qi;
+  // Sub-tiles: n_keys of the head; a part takes those with its remainder mod PARTS, n_tiles for each of them (one may be past the end)
+  const int n_keys = (p.L + kSubTile - 1) / kSubTile;
+  const int n_tiles = (n_keys + PARTS - 1) / PARTS;
   const int n_full = p.L / kSubTile;
+  char* ringK = ringsK + part * (kRing * G::kStageBytes);
+  char* ringV = ringsV + part * (kRing * G::kStageBytes);
 
   // this wavefront's share of every sub-tile: the first half of the wavefronts split the K rows, the second half the
   // V rows.  Row addresses: a scalar base that moves by 32 rows per sub-tile plus per-lane byte offsets fixed for the launch.
-  const bool is_v = wave >= kShare;
-  const int first = (wave % kShare) * NL;
+  const bool is_v = tile >= kShare;
+  const int first = (tile % kShare) * NL;
   const char* src = reinterpret_cast<const char*>(is_v ? p.V + (int64_t)h * p.vsh : p.K + (int64_t)h * p.ksh);
   const int64_t row_bytes = (is_v ? p.vsn : p.ksn) * 2;
   const int64_t tile_bytes = row_bytes * kSubTile;
@@ -1953,7 +1987,8 @@ __global__ __launch_bounds__(64 * kRefreshWaves, 2) void refresh_attn_kernel(con
   const int lead_k = is_v ? 0 : 1;
   // element e = sub-tile e + 1 of K, sub-tile e of V: what ring slot e mod kRing holds
   auto fetch = [&](int e, uintx4 (&r)[NL]) __attribute__((always_inline)) {
-    const int t = e + lead_k;
+    int t = (e + lead_k) * PARTS + part;
+    if (PARTS > 1) t = min(t, n_keys - 1);  // past the end: any rows of the key set, all masked
     const char* base = src + (int64_t)t * tile_bytes;
     if (t >= n_full) {  // the ragged last sub-tile: slots past the end read its last row instead (masked below)
       const int last = p.L - t * kSubTile - 1;
@@ -1997,6 +2032,7 @@ __global__ __launch_bounds__(64 * kRefreshWaves, 2) void refresh_attn_kernel(con
     }
   }
   float m_run = -INFINITY, l_run = 0.f;  // l_run: this lane's share of the row sum (its 16 of every 32 keys)
+  float u_run = 0.f;                     // LSE: the same of the probabilities before they are rounded
   floatx16 o[kDT];
 #pragma unroll
   for (int dt = 0; dt < kDT; ++dt)
@@ -2008,6 +2044,20 @@ __global__ __launch_bounds__(64 * kRefreshWaves, 2) void refresh_attn_kernel(con
     koff[s] = stage_off<D>(qi, 2 * s + hh);
     pin(koff[s]);
   }
+  int vaddr[kDT];  // LDS address of the V operand of d tile dt in slot 0 (read_v_operand32)
+#pragma unroll
+  for (int dt = 0; dt < kDT; ++dt) {
+    const int row = 4 * (lane >> 5) + ((lane & 15) >> 2), col = 32 * dt + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+    vaddr[dt] = (int)lds_address(ringV) + vstage_off<D>(row, col >> 3) + (col & 7) * 2;
+    pin(vaddr[dt]);
+  }
+  auto v_operand = [&](int slot, int dt, int ks) __attribute__((always_inline)) {  // rows 16 ks, 16 ks + 8 further: the same swizzle
+    typedef shortx4 __attribute__((address_space(3))) * lds_ptr;
+    const uint32_t at = (uint32_t)(vaddr[dt] + slot * G::kStageBytes + 16 * ks * G::kRowBytes);
+    struct { shortx4 a, b; } both = {__builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(uintptr_t)at),
+                                     __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(uintptr_t)(at + 8 * G::kRowBytes))};
+    return __builtin_bit_cast(bf16x8, both);
+  };
   // scaled row maximum of one sub-tile's logits.  Slots past the end of a ragged sub-tile hold copies of its last
   // row, so they cannot raise the maximum and need no masking here.
   auto row_max_lane = [&](const floatx16& a) __attribute__((always_inline)) {
@@ -2026,6 +2076,7 @@ __global__ __launch_bounds__(64 * kRefreshWaves, 2) void refresh_attn_kernel(con
       const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);  // 0 on the first sub-tile (m_run = -inf, m_new finite)
       m_run = m_new;
       l_run *= alpha;
+      if (LSE) u_run *= alpha;
 #pragma unroll
       for (int dt = 0; dt < kDT; ++dt) o[dt] *= alpha;
     }
@@ -2061,17 +2112,18 @@ __global__ __launch_bounds__(64 * kRefreshWaves, 2) void refresh_attn_kernel(con
     rescale(mx);
     const int ring = R >= 0 ? R : (t & (kRing - 1));
     const char* sK = ringK + ring * G::kStageBytes;
-    const char* sV = ringV + ring * G::kStageBytes;
     bf16x8 op[NS + kLead];
     auto read_op = [&](auto sc) __attribute__((always_inline)) {
       constexpr int s = decltype(sc)::value;
       if constexpr (s < kKS)
         op[s] = as_bf16x8(*reinterpret_cast<const uint4*>(sK + koff[s]));
       else if constexpr (s < NS)
-        op[s] = read_v_operand32<D>(sV, (s - kKS) % kDT, (s - kKS) / kDT, lane);
+        op[s] = v_operand(ring, (s - kKS) % kDT, (s - kKS) / kDT);
       else if constexpr (kMore)
         ahead[s - NS] = as_bf16x8(*reinterpret_cast<const uint4*>(sK + G::kStageBytes + koff[s - NS]));
     };
+    // (the keys of one part may all have a logit of -inf where those of the other do not)
+    const float m_use = PARTS > 1 && m_run == -INFINITY ? 0.f : m_run;
     floatx16 next;
     uint32_t pk[8];
     float mxn = 0.f;
@@ -2080,8 +2132,8 @@ __global__ __launch_bounds__(64 * kRefreshWaves, 2) void refresh_attn_kernel(con
     auto probabilities = [&](int v0, int v1) __attribute__((always_inline)) {  // logits v0 .. v1 - 1 -> packed bf16, added to the row sum
 #pragma unroll
       for (int v = v0; v < v1; v += 2) {
-        float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[v], p.scale_log2, -m_run));
-        float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[v + 1], p.scale_log2, -m_run));
+        float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[v], p.scale_log2, -m_use));
+        float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[v + 1], p.scale_log2, -m_use));
         if (kLast) {  // a ragged sub-tile: slots past the end count for nothing
           const int key = 8 * (v >> 2) + 4 * hh + (v & 3);
           p0 = key < n_valid ? p0 : 0.f;
@@ -2089,6 +2141,7 @@ __global__ __launch_bounds__(64 * kRefreshWaves, 2) void refresh_attn_kernel(con
         }
         pk[v >> 1] = cvt_pk_bf16(p0, p1);
         l_run = add_bf16_pair(l_run, pk[v >> 1]);
+        if (LSE) u_run += p0 + p1;
       }
     };
     if (kLast) probabilities(0, 16);
@@ -2147,12 +2200,46 @@ __global__ __launch_bounds__(64 * kRefreshWaves, 2) void refresh_attn_kernel(con
     });
   for (; t < n_iter; ++t) body(t, integral_constant<int, -1>{}, yes, no, no, kSubTile);
   // last sub-tile (possibly ragged): its logits are in acc already
-  body(n_tiles - 1, integral_constant<int, -1>{}, yes, no, yes, p.L - (n_tiles - 1) * kSubTile);
+  const int n_last = p.L - ((n_tiles - 1) * PARTS + part) * kSubTile;
+  if (PARTS == 1 || n_last > 0)  // wave-uniform
+    body(n_tiles - 1, integral_constant<int, -1>{}, yes, no, yes, n_last);
+  else
+    __syncthreads();  // (body's)
 
   // lane (query, hh) register v of d tile dt holds O^T[32 dt + 8 (v / 4) + 4 hh + v % 4][query]: four consecutive
   // output columns per register quad.  The two lanes of a query add their halves of the row sum.
   const uintx2 sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(l_run), __float_as_uint(l_run), false, false);
-  const float l = __uint_as_float(sw.x) + __uint_as_float(sw.y);
+  float l = __uint_as_float(sw.x) + __uint_as_float(sw.y), l_exact = l;
+  if (LSE) {
+    const uintx2 uw = __builtin_amdgcn_permlane32_swap(__float_as_uint(u_run), __float_as_uint(u_run), false, false);
+    l_exact = __uint_as_float(uw.x) + __uint_as_float(uw.y);
+  }
+  if constexpr (PARTS > 1) {  // the parts of a tile hold the same elements in the same lanes: through LDS, 16 bytes of a lane at a time
+    static_assert(PARTS == 2 && kPartWaves * 32 * D * 4 <= (int)sizeof(ringsK) && kPartWaves * 64 * 16 <= (int)sizeof(ringsV), "the tiles of one part fit");
+    floatx4* o_sh = reinterpret_cast<floatx4*>(ringsK) + tile * (32 * D / 4) + lane;
+    floatx4* ml_sh = reinterpret_cast<floatx4*>(ringsV) + tile * 64 + lane;
+    __syncthreads();  // the rings have been read by everyone
+    if (part != 0) {
+#pragma unroll
+      for (int i = 0; i < 4 * kDT; ++i)
+        o_sh[64 * i] = floatx4{o[i >> 2][4 * (i & 3)], o[i >> 2][4 * (i & 3) + 1], o[i >> 2][4 * (i & 3) + 2], o[i >> 2][4 * (i & 3) + 3]};
+      *ml_sh = floatx4{m_run, l, l_exact, 0.f};
+    }
+    __syncthreads();
+    if (part != 0) return;
+    const floatx4 other = *ml_sh;
+    const float m_all = fmaxf(m_run, other[0]);
+    const float f0 = l > 0.f ? __builtin_amdgcn_exp2f(m_run - m_all) : 0.f, f1 = other[1] > 0.f ? __builtin_amdgcn_exp2f(other[0] - m_all) : 0.f;
+    m_run = m_all;
+    l = f0 * l + f1 * other[1];
+    l_exact = f0 * l_exact + f1 * other[2];
+#pragma unroll
+    for (int i = 0; i < 4 * kDT; ++i) {
+      const floatx4 x = o_sh[64 * i];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) o[i >> 2][4 * (i & 3) + j] = f0 * o[i >> 2][4 * (i & 3) + j] + f1 * x[j];
+    }
+  }
   if (q_row < p.n_q) {
     const float inv = l > 0.f ? 1.f / l : 0.f;
     uint16_t* dst = p.out + (int64_t)h * p.osh + (int64_t)q_row * p.osn + 4 * hh;
@@ -2162,14 +2249,15 @@ __global__ __launch_bounds__(64 * kRefreshWaves, 2) void refresh_attn_kernel(con
       for (int j = 0; j < 4; ++j)
         *reinterpret_cast<uint2*>(dst + 32 * dt + 8 * j) = make_uint2(cvt_pk_bf16(o[dt][4 * j] * inv, o[dt][4 * j + 1] * inv),
                                                                       cvt_pk_bf16(o[dt][4 * j + 2] * inv, o[dt][4 * j + 3] * inv));
-    if (p.lse && hh == 0) p.lse[(int64_t)h * p.n_q + q_row] = l > 0.f ? (m_run + __builtin_amdgcn_logf(l)) * kLn2 : -INFINITY;
+    if ((PARTS == 1 || LSE) && p.lse && hh == 0)
+      p.lse[(int64_t)h * p.n_q + q_row] = l_exact > 0.f ? (m_run + __builtin_amdgcn_logf(l_exact)) * kLn2 : -INFINITY;
   }
 }
 
-// The query tiles that refresh_attn_kernel does not take (see launch_refresh_t): one 32-query tile per workgroup, the
+// The query tiles that refresh_attn_kernel does not take (see cut_refresh): one 32-query tile per workgroup, the
 // key sub-tiles dealt to its eight wavefronts in turn.  A wavefront stages its own sub-tiles (no barrier in the key loop; the
 // operands are all in registers before the next sub-tile is requested into the same stage), the eight states are merged at the
-// end.  Tail tiles: the whole blocks the other kernel does not take, eight tiles each, then every head's last few tiles.
+// end.  Tail tiles: those of whole blocks that the other kernel does not take, then every head's last few tiles.
 // Rows are normalised as in refresh_attn_kernel, by the sum of the rounded probabilities (the quotient is then a weighted mean of V
 // rows, and a common offset of V cancels in its rounding error: with V = 4 + noise that error is a quarter of what the unrounded sum
 // leaves).  The log-sum-exp, in which nothing cancels, is that of the unrounded sum; LSE: it is wanted.
@@ -2203,16 +2291,17 @@ __global__ __launch_bounds__(64 * kRefreshWaves, D == 64 ? 4 : 2) void refresh_t
   const int chunk = (p.n_tail + 7) >> 3;
   const int item = (int)(blockIdx.x & 7u) * chunk + (int)(blockIdx.x >> 3);
   if (item >= p.n_tail) return;  // whole workgroup
-  const int n_left = (p.n_heads * p.n_qb - p.n_work) * kRefreshWaves;  // tiles of whole blocks
+  const int done = p.n_work * kRefreshWaves + p.n_half_whole * kHalfTiles;  // tiles of whole blocks: taken, and left
+  const int n_left = p.n_heads * p.n_qb * kRefreshWaves - done;
   int h, tile;
   if (item < n_left) {
-    const int block = p.n_work + item / kRefreshWaves;
+    const int block = (done + item) / kRefreshWaves;
     h = block / p.n_qb;
-    tile = (block - h * p.n_qb) * kRefreshWaves + item % kRefreshWaves;
+    tile = done + item - h * p.n_qb * kRefreshWaves;
   } else {
-    const int per_head = (p.n_q + 31) / 32 - p.n_qb * kRefreshWaves;
+    const int first = p.n_qb * kRefreshWaves + p.n_half_head * kHalfTiles, per_head = (p.n_q + 31) / 32 - first;
     h = (item - n_left) / per_head;
-    tile = p.n_qb * kRefreshWaves + (item - n_left) - h * per_head;
+    tile = first + (item - n_left) - h * per_head;
   }
   const uint16_t* Kh = p.K + (int64_t)h * p.ksh;
   const uint16_t* Vh = p.V + (int64_t)h * p.vsh;
@@ -2295,62 +2384,105 @@ __global__ __launch_bounds__(64 * kRefreshWaves, D == 64 ? 4 : 2) void refresh_t
 
 // Which query tiles go to which kernel.  Every 256-query block takes the same time, so refresh_attn_kernel runs in rounds of 256
 // blocks (one per compute unit; at d = 64 two fit, and take twice as long), and a round that is mostly empty costs as much as a
-// full one.  refresh_tail_kernel takes single 32-query tiles: an eighth of the key sub-tiles per wavefront, each about twice
+// full one.  Half blocks of four tiles, every key sub-tile for half of the wavefronts, take two thirds of a block's time.
+// refresh_tail_kernel takes single 32-query tiles: an eighth of the key sub-tiles per wavefront, each about twice
 // (d = 64: four times) as long because eight tiles no longer share the staged rows.  At d = 64 two tiles share a compute unit and hardly
-// slow each other down, and 512 of them need not come in whole rounds.  Both have a fixed part (first loads, merge).  Three ways
+// slow each other down, and 512 of them need not come in whole rounds.  All have a fixed part (first loads, merge).  The ways
 // to cut, the cheapest is taken (times in us, measured; the cache refresh is left out, with which the cut must not change):
 //   everything in blocks, the ragged one of each head included;
-//   whole blocks, and the last few tiles of each head to the tail kernel;
-//   whole rounds of blocks, and everything else to the tail kernel.
+//   whole blocks, or whole rounds of them, and of the rest
+//     all in halves, with every head's last tiles in halves, the last of them padded or not;
+//     whole rounds of halves, and single tiles; or single tiles only.
+// Block entry without halves and with them, d = 128: 32 heads, 2741 rows 185 -> 159 us, 2991 rows 219 -> 189, 4900 rows 487 -> 432; 8
+// heads, 4096 rows 117 -> 88, 11 691 rows 669 -> 575; 4 heads, 8192 rows 219 -> 154, 9003 rows 275 -> 240; d = 64: 32 heads, 2991 rows 122 ->
+// 116; 8 heads, 4096 rows 62.6 -> 54.6.  Where a round of blocks is full or nearly so they lose (d = 64: 8 heads, 8192 rows 166 and 185).
 // 32 heads, 8256 rows (33 blocks per head, 4.1 rounds): 1213 us all in blocks, 1106 us cut; 4 heads, 1056 rows, d = 64: 26 and 8.
 // d = 64, block entry in blocks and in tiles: 32 heads, 1032 rows 35.1 and 29.6; 16 heads, 2032 52.4 and 39.1, 3032 71.3 and 73.2, 4032 95.5 and
 // 118; 8 heads, 4032 85 and 64, 6032 119 and 130.
 // A launch has fewer than 2^32 threads (kMaxGroups workgroups).  More tail tiles than that stay in blocks; more chunks of the cache
 // refresh than fit behind the tail tiles (2^24 of them: block 1, 32 heads, half a million rows) get the launch of their own that they
 // have where there is no tail.
-template <int D>
-static hipError_t launch_refresh_t(RefreshArgs& a, const focus_shape& s, const CacheRefresh* copy, hipStream_t st) {
+struct RefreshCut {
+  int n_qb = 0, n_work = 0, half_whole = 0, half_head = 0;
+  int64_t n_half = 0, n_tail = 0;
+  float time = 0.f;
+};
+static RefreshCut cut_refresh(int head_dim, int n_heads, int n_q, int L) {
   constexpr int kSlots = 256;
   constexpr int64_t kMaxGroups = ((int64_t(1) << 32) - 1) / (64 * kRefreshWaves);
-  const int tiles = ceil_div(s.n_gen, 32), last = tiles % kRefreshWaves;
-  const float sub = (float)ceil_div(s.n_ctx + s.n_resp, kSubTile);
-  const float block_time = D == 128 ? 0.85f * sub + 5.f : 0.5f * sub + 12.f, tail_time = D == 128 ? 0.2f * sub + 5.f : 0.23f * sub + 3.f;
+  const int tiles = ceil_div(n_q, 32), last = tiles % kRefreshWaves;
+  const float sub = (float)ceil_div(L, kSubTile);
+  const bool d128 = head_dim == 128;
+  const float block_time = d128 ? 0.85f * sub + 5.f : 0.5f * sub + 12.f, tail_time = d128 ? 0.2f * sub + 5.f : 0.23f * sub + 3.f;
+  const float half_time = d128 ? 0.55f * sub + 10.f : 0.31f * sub + 10.f;
   auto rounds = [](int64_t n) { return (float)((n + kSlots - 1) / kSlots); };
-  auto tail_rounds = [&](int64_t n) { return D == 128 || n == 0 ? rounds(n) : std::max(1.f, (float)n / (2 * kSlots)); };
-  const int64_t whole = (int64_t)(tiles / kRefreshWaves) * s.n_heads, padded = (int64_t)ceil_div(tiles, kRefreshWaves) * s.n_heads;
-  const int64_t ragged = (int64_t)last * s.n_heads, rest = whole % kSlots;
-  const float t_padded = rounds(padded) * block_time;
-  const float t_whole = rounds(whole) * block_time + tail_rounds(ragged) * tail_time;
-  const float t_rounds = rounds(whole - rest) * block_time + tail_rounds(rest * kRefreshWaves + ragged) * tail_time;
-  a.n_heads = s.n_heads;
-  const bool tails_fit = rest * kRefreshWaves + ragged + 7 <= kMaxGroups;
-  if (!tails_fit || (t_padded <= t_whole && t_padded <= t_rounds)) {
-    a.n_qb = ceil_div(tiles, kRefreshWaves);
-    a.n_work = (int)padded;
-    a.n_tail = 0;
-  } else {
-    a.n_qb = tiles / kRefreshWaves;
-    a.n_work = (int)(t_whole <= t_rounds ? whole : whole - rest);
-    a.n_tail = (int)((whole - a.n_work) * kRefreshWaves + ragged);
+  auto tail_rounds = [&](int64_t n) { return d128 || n == 0 ? rounds(n) : std::max(1.f, (float)n / (2 * kSlots)); };
+  const int64_t whole = (int64_t)(tiles / kRefreshWaves) * n_heads, padded = (int64_t)ceil_div(tiles, kRefreshWaves) * n_heads;
+  RefreshCut best;
+  best.n_qb = ceil_div(tiles, kRefreshWaves);
+  best.n_work = (int)padded;
+  best.time = rounds(padded) * block_time;
+  auto consider = [&](int64_t work, int64_t half_whole, int half_head) {
+    RefreshCut c;
+    c.n_qb = tiles / kRefreshWaves;
+    c.n_work = (int)work;
+    c.half_whole = (int)half_whole;
+    c.half_head = half_head;
+    c.n_half = half_whole + (int64_t)half_head * n_heads;
+    c.n_tail = (2 * (whole - work) - half_whole) * kHalfTiles + (int64_t)std::max(0, last - half_head * kHalfTiles) * n_heads;
+    if (c.n_half + 7 > kMaxGroups || c.n_tail + 7 > kMaxGroups) return;
+    c.time = rounds(work) * block_time + rounds(c.n_half) * half_time + tail_rounds(c.n_tail) * tail_time;
+    if (c.time < best.time) best = c;
+  };
+  const int64_t rest = whole % kSlots;
+  for (int64_t work : {whole, whole - rest}) {
+    const int64_t halves = 2 * (whole - work);
+    for (int half_head = 0; half_head <= ceil_div(last, kHalfTiles); ++half_head) consider(work, halves, half_head);
+    consider(work, halves - halves % kSlots, 0);
+    consider(work, 0, 0);
   }
-  if (a.n_work > 0) {
-    hipLaunchKernelGGL(refresh_attn_kernel<D>, dim3(8 * ceil_div(a.n_work, 8)), dim3(64 * kRefreshWaves), 0, st, a);
+  return best;
+}
+template <int D>
+static hipError_t launch_refresh_t(RefreshArgs& a, const focus_shape& s, const CacheRefresh* copy, hipStream_t st) {
+  constexpr int64_t kMaxGroups = ((int64_t(1) << 32) - 1) / (64 * kRefreshWaves);
+  const RefreshCut cut = cut_refresh(D, s.n_heads, s.n_gen, s.n_ctx + s.n_resp);
+  a.n_heads = s.n_heads;
+  a.n_qb = cut.n_qb;
+  a.n_work = cut.n_work;
+  a.n_half_whole = cut.half_whole;
+  a.n_half_head = cut.half_head;
+  a.n_tail = (int)cut.n_tail;
+  const dim3 block(64 * kRefreshWaves);
+  const int64_t copies = copy ? ceil_div64((int64_t)copy->n_chunks * copy->n_heads, 2) : 0;
+  auto list = [](int64_t n) { return (int64_t)8 * ceil_div64(n, 8); };
+  if (cut.n_work > 0) {
+    hipLaunchKernelGGL((refresh_attn_kernel<D, 1, false>), dim3((uint32_t)list(cut.n_work)), block, 0, st, a, CacheRefresh{});
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  if (a.n_tail == 0) return copy ? launch_cache_refresh(*copy, D, st) : hipSuccess;
-  const int64_t tails = (int64_t)8 * ceil_div(a.n_tail, 8), copies = copy ? ceil_div64((int64_t)copy->n_chunks * copy->n_heads, 2) : 0;
-  if (tails + copies > kMaxGroups) {
+  if (copy != nullptr && (cut.n_half + cut.n_tail == 0 || list(cut.n_tail > 0 ? cut.n_tail : cut.n_half) + copies > kMaxGroups)) {
     hipError_t e = launch_cache_refresh(*copy, D, st);
     if (e != hipSuccess) return e;
     copy = nullptr;
   }
-  const dim3 grid((uint32_t)(copy ? tails + copies : tails)), block(64 * kRefreshWaves);
+  if (cut.n_half > 0) {
+    const bool with = copy != nullptr && cut.n_tail == 0;
+    const dim3 grid((uint32_t)(list(cut.n_half) + (with ? copies : 0)));
+    if (a.lse)
+      hipLaunchKernelGGL((refresh_attn_kernel<D, 2, true>), grid, block, 0, st, a, with ? *copy : CacheRefresh{});
+    else
+      hipLaunchKernelGGL((refresh_attn_kernel<D, 2, false>), grid, block, 0, st, a, with ? *copy : CacheRefresh{});
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || cut.n_tail == 0) return e;
+  }
+  if (cut.n_tail == 0) return hipSuccess;
+  const dim3 grid((uint32_t)(list(cut.n_tail) + (copy ? copies : 0)));
   // d = 64: up to 128 tiles, which is what long prompts leave over, have a compute unit each (LDS that nobody uses sees to it): they are the
   // last to finish, and a chunk beside them costs more than it gains.  Layer with and without, medians of 24 pairs in turn: 32 heads, 4104
   // rows 193.8 and 195.8 us, 8256 rows 660.4 and 663.8; 8 heads, 8256 rows 209.1 and 210.0; 16 heads, 16 404 rows 1255.7 and 1258.9; 4
   // heads, 16 404 rows 394.1 and 395.3.
-  const uint32_t alone = D == 64 && copy && a.n_tail <= kSlots / 2 ? 32768 : 0;
+  const uint32_t alone = D == 64 && copy && cut.n_tail <= 128 ? 32768 : 0;
   if (a.lse)
     hipLaunchKernelGGL((refresh_tail_kernel<D, true>), grid, block, alone, st, a, copy ? *copy : CacheRefresh{});
   else

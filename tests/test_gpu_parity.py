@@ -1484,6 +1484,33 @@ def test_refresh_attn_cut_into_blocks_and_tiles(G, H, n_q, L, d):
 
 
 @pytest.mark.parametrize("offset", [0.0, 40.0])      # 40: the maximum of a row moves with nearly every sub-tile
+@pytest.mark.parametrize("H,n_q,L,d", [
+    (64, 512, 577, 128),   # 256 half blocks: an odd number of key sub-tiles, the last of one row
+    (64, 512, 640, 128),   # ... an even number of whole ones
+    (64, 470, 1000, 128),  # half blocks of every head's last seven tiles as well, the last tile ragged and one missing
+    (70, 512, 3300, 128),  # a round of half blocks, the others as single tiles
+    (96, 1024, 672, 128),  # a round of blocks, then a round of half blocks; an odd number of whole sub-tiles
+    (64, 512, 1100, 64),   # half blocks of 64 columns, a ragged last sub-tile of one half
+    (64, 500, 1121, 64),   # ... and of the other
+])
+def test_refresh_attn_half_blocks(G, H, n_q, L, d, offset):
+    q, k, v = (_rand_bf16(171 + i, H, r, d).to(G.DEV) for i, r in enumerate((n_q, L, L)))
+    k += (offset / L * torch.arange(L, device=G.DEV)[None, :, None] * torch.sign(q[:, :1].float())).to(torch.bfloat16)
+    out = torch.full((H, n_q, d), float("nan"), dtype=torch.bfloat16, device=G.DEV)
+    lse = torch.full((H, n_q), float("nan"), dtype=torch.float32, device=G.DEV)
+    fb.refresh_attn(q, k, v, fb.make_shape(q, k, v, L, 64, out), out, lse)
+    # float64 on the device, a head at a time: float32 would leave the large logits 2e-5 of themselves
+    for h in range(0, H, 9):
+        s = torch.matmul(q[h].double(), k[h].double().t()) / math.sqrt(d)
+        G.assert_attention_close(out[h], torch.matmul(torch.softmax(s, -1), v[h].double()).cpu().numpy())
+        # sums of rounded probabilities (whole blocks) are off by up to 2^-9 of themselves; the size of a logit scales its fp32 rounding
+        assert torch.allclose(lse[h].double(), torch.logsumexp(s, -1), atol=2.0 ** -8, rtol=1e-5)
+    out2 = torch.zeros_like(out)
+    fb.refresh_attn(q, k, v, fb.make_shape(q, k, v, L, 64, out2), out2, None)
+    assert torch.equal(out, out2)
+
+
+@pytest.mark.parametrize("offset", [0.0, 40.0])      # 40: the maximum of a row moves with nearly every sub-tile
 @pytest.mark.parametrize("H,n_q,L", [
     (8, 1024, 255),      # 256 tiles of 64 columns: one per compute unit; a sub-tile per wavefront, the last ragged
     (9, 1000, 257),      # 288: two of them share some; a second sub-tile for one wavefront
