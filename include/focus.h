@@ -21,6 +21,7 @@
  * and, around the step (Sec. 3):
  *     focus_token_confidence vocabulary logits -> predicted tokens, confidences (Eq. 2): the input of the selection
  *     focus_cache_update     new K/V states of the active positions -> KV cache (Eq. 3)
+ *     focus_update_sparse_layer   = focus_cache_update + focus_sparse_layer of one layer, in one call
  *     focus_cache_refresh    block entry: new K/V states of every position -> KV cache and K_bar in one pass
  *     focus_block_entry      = focus_cache_refresh + focus_refresh_attn of one layer, in one call
  *
@@ -290,6 +291,15 @@ size_t focus_token_confidence_workspace(int32_t n_rows, int32_t vocab);
 int focus_cache_update(void* K_cache, void* V_cache, const focus_shape* shape, const void* K_new, const void* V_new,
                        int64_t new_stride_h, int64_t new_stride_n, const int32_t* active_idx, const int32_t* counts,
                        int32_t max_active, int32_t row_base, void* stream);
+
+/* focus_cache_update and then focus_sparse_layer of one layer over the updated caches, in one call with the same results; with kbar the update
+ * is made beside the relevances, which read nothing of the caches (short key lists of few heads and kbar NULL: a launch of its own).
+ * shape: strides of the caches, Q and out. */
+int focus_update_sparse_layer(void* K_cache, void* V_cache, const void* K_new, const void* V_new, int64_t new_stride_h, int64_t new_stride_n,
+                              int32_t row_base, const void* Q, const int32_t* focus_idx, const int32_t* active_idx, const int32_t* counts,
+                              int32_t n_focus_max, int32_t max_active, const float* kbar, const focus_shape* shape, int32_t n_keep,
+                              const int32_t* sink_idx, int32_t n_sink, float* scores, int32_t* kept_blocks, void* out, float* lse,
+                              void* workspace, size_t ws_bytes, void* stream);
 
 /*
  * Block-entry cache refresh (Alg. 1: when a generation block starts, every position is recomputed and the whole KV

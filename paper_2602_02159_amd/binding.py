@@ -21,7 +21,7 @@ FN_BLOCK_SCORES, FN_FIND_SINKS, FN_SPARSE_ATTN, FN_SPARSE_LAYER, FN_PROBE_LAYER 
 EXPORTS = ("focus_select_queries", "focus_expand_groups", "focus_block_means", "focus_block_scores", "focus_find_sinks", "focus_select_and_find_sinks",
            "focus_sparse_attn",
            "focus_sparse_layer", "focus_sparse_layer_static", "focus_block_partials", "focus_top_blocks", "focus_probe_layer", "focus_refresh_attn", "focus_cache_refresh", "focus_block_entry",
-           "focus_token_confidence", "focus_token_confidence_workspace", "focus_cache_update",
+           "focus_token_confidence", "focus_token_confidence_workspace", "focus_cache_update", "focus_update_sparse_layer",
            "focus_workspace_bytes", "focus_helper_k", "focus_helper_n_keep", "focus_helper_n_sink", "focus_last_error",
            "focus_version")
 
@@ -69,11 +69,12 @@ def lib() -> C.CDLL:
         L.focus_token_confidence_workspace.argtypes = [i32, i32]
         L.focus_token_confidence_workspace.restype = sz
         L.focus_cache_update.argtypes = [p, p, sp, p, p, C.c_int64, C.c_int64, p, p, i32, i32, p]
+        L.focus_update_sparse_layer.argtypes = [p, p, p, p, C.c_int64, C.c_int64, i32, p, p, p, p, i32, i32, p, sp, i32, p, i32, p, p, p, p, p, sz, p]
         L.focus_block_partials.argtypes = [p, p, p, i32, p, p, sp, p, p]
         L.focus_top_blocks.argtypes = [p, i32, p, i32, i32, i32, p, p, p]
         for name in ("focus_select_queries", "focus_expand_groups", "focus_block_means", "focus_block_scores", "focus_find_sinks",
                      "focus_select_and_find_sinks", "focus_sparse_attn", "focus_sparse_layer", "focus_sparse_layer_static", "focus_block_partials", "focus_top_blocks",
-                     "focus_probe_layer", "focus_refresh_attn", "focus_token_confidence", "focus_cache_update", "focus_cache_refresh", "focus_block_entry"):
+                     "focus_probe_layer", "focus_refresh_attn", "focus_token_confidence", "focus_cache_update", "focus_update_sparse_layer", "focus_cache_refresh", "focus_block_entry"):
             getattr(L, name).restype = C.c_int
         L.focus_workspace_bytes.argtypes = [i32, sp, i32, i32, i32]
         L.focus_workspace_bytes.restype = sz
@@ -289,6 +290,20 @@ def sparse_layer(q, focus_idx, active_idx, counts, k, v, kbar, shape: Shape, n_k
                                     active_idx.numel(), _ptr(k), _ptr(v), _ptr(kbar), C.byref(shape), n_keep, _ptr(sink_idx),
                                     n_sink, _ptr(scores), _ptr(kept_blocks), _ptr(out), _ptr(lse), _ptr(workspace),
                                     0 if workspace is None else workspace.numel() * workspace.element_size(), _stream()))
+
+
+def update_sparse_layer(k_cache, v_cache, k_new, v_new, row_base: int, q, focus_idx, active_idx, counts, kbar, shape: Shape, n_keep: int,
+                        sink_idx, n_sink: int, scores, kept_blocks, out, lse, workspace) -> None:
+    """cache_update and sparse_layer of one layer in one call; k_new and v_new share their strides."""
+    for t, name in ((k_cache, "K_cache"), (v_cache, "V_cache"), (k_new, "K_new"), (v_new, "V_new"), (q, "Q"), (out, "out")):
+        _need(t, torch.bfloat16, name)
+    if k_new.stride() != v_new.stride() or k_new.stride(2) != 1:
+        raise ValueError("K_new and V_new must share their strides, innermost 1")
+    _check(lib().focus_update_sparse_layer(_ptr(k_cache), _ptr(v_cache), _ptr(k_new), _ptr(v_new), k_new.stride(0), k_new.stride(1), row_base,
+                                           _ptr(q), _ptr(focus_idx), _ptr(active_idx), _ptr(counts), focus_idx.numel(), active_idx.numel(),
+                                           _ptr(kbar), C.byref(shape), n_keep, _ptr(sink_idx), n_sink, _ptr(scores), _ptr(kept_blocks),
+                                           _ptr(out), _ptr(lse), _ptr(workspace),
+                                           0 if workspace is None else workspace.numel() * workspace.element_size(), _stream()))
 
 
 def sparse_layer_static(q, focus_idx, active_idx, counts, k, v, kbar, shape: Shape, n_keep: int, sink_idx, n_sink: int, scores,

@@ -361,11 +361,23 @@ static int static_scratch_ptr(void** out) {
   return FOCUS_OK;
 }
 
+static int check_cache_update(const char* who, const void* K_cache, const void* V_cache, const focus_shape* shape, const void* K_new,
+                              const void* V_new, int64_t new_stride_h, int64_t new_stride_n, const int32_t* active_idx, int32_t max_active) {
+  if (int rc = check_shape(shape, false, true, true, false)) return rc;
+  if (!K_cache || !V_cache || !K_new || !V_new || !active_idx) return fail(FOCUS_EINVAL, "%s: NULL pointer", who);
+  if (max_active < 1 || max_active > 65535) return fail(FOCUS_EINVAL, "%s: max_active=%d not in [1, 65535]", who, max_active);
+  if (new_stride_n < shape->head_dim || (new_stride_n & 7) || new_stride_h < 0 || (new_stride_h & 7))
+    return fail(FOCUS_EINVAL, "%s: strides of the new states invalid or not multiples of 8", who);
+  if (!aligned16(K_cache) || !aligned16(V_cache) || !aligned16(K_new) || !aligned16(V_new))
+    return fail(FOCUS_EINVAL, "%s: pointers must be 16-byte aligned", who);
+  return FOCUS_OK;
+}
+
 static int sparse_layer_impl(const char* who, const void* Q, const int32_t* focus_idx, const int32_t* active_idx,
                              const int32_t* counts, int32_t n_focus_max, int32_t max_active, const void* K, const void* V,
                              const float* kbar, const focus_shape* shape, int32_t n_keep, const int32_t* sink_idx,
                              int32_t n_sink, float* scores, int32_t* kept_blocks, void* out, float* lse, void* workspace,
-                             size_t ws_bytes, bool static_scratch, void* stream) {
+                             size_t ws_bytes, bool static_scratch, void* stream, const CacheUpdate* update = nullptr) {
   if (int rc = check_shape(shape, true, true, true, true)) return rc;
   if (!Q || !focus_idx || !active_idx || !K || !V || !out) return fail(FOCUS_EINVAL, "%s: NULL pointer", who);
   const int n_b = ceil_div(shape->n_ctx, shape->block);
@@ -411,10 +423,15 @@ static int sparse_layer_impl(const char* who, const void* Q, const int32_t* focu
   };
   const bool inner = fused && kbar && relevance_in_attention(*shape, p) && relevance_inputs_apart() &&
                      attention_outputs_apart(Q, active_idx, max_active, K, V, *shape, nullptr, 0, sink_idx, n_sink, out, lse);
+  if (update != nullptr && (!kbar || inner)) {  // no launch that reads nothing of the cache
+    e = launch_cache_update(*update, shape->head_dim, st);
+    if (e != hipSuccess) return launch_fail("focus_sparse_layer(cache update)", e);
+    update = nullptr;
+  }
   if (!kbar)
     e = launch_block_means_relevance(K, Q, focus_idx, counts, n_focus_max, *shape, nullptr, part, st);
   else if (!inner)
-    e = launch_block_relevance(Q, focus_idx, counts, n_focus_max, kbar, *shape, part, false, st);
+    e = launch_block_relevance(Q, focus_idx, counts, n_focus_max, kbar, *shape, part, false, st, update);
   if (e != hipSuccess) return launch_fail("focus_sparse_layer(relevance)", e);
   if (fused) {
     FusedTopC f;
@@ -670,17 +687,22 @@ int focus_token_confidence(const void* logits, int64_t row_stride, const uint8_t
 int focus_cache_update(void* K_cache, void* V_cache, const focus_shape* shape, const void* K_new, const void* V_new,
                        int64_t new_stride_h, int64_t new_stride_n, const int32_t* active_idx, const int32_t* counts,
                        int32_t max_active, int32_t row_base, void* stream) {
-  if (int rc = check_shape(shape, false, true, true, false)) return rc;
-  if (!K_cache || !V_cache || !K_new || !V_new || !active_idx) return fail(FOCUS_EINVAL, "focus_cache_update: NULL pointer");
-  if (max_active < 1 || max_active > 65535) return fail(FOCUS_EINVAL, "focus_cache_update: max_active=%d not in [1, 65535]", max_active);
-  if (new_stride_n < shape->head_dim || (new_stride_n & 7) || new_stride_h < 0 || (new_stride_h & 7))
-    return fail(FOCUS_EINVAL, "focus_cache_update: strides of the new states invalid or not multiples of 8");
-  if (!aligned16(K_cache) || !aligned16(V_cache) || !aligned16(K_new) || !aligned16(V_new))
-    return fail(FOCUS_EINVAL, "focus_cache_update: pointers must be 16-byte aligned");
-  hipError_t e = launch_cache_update(K_cache, V_cache, *shape, K_new, V_new, new_stride_h, new_stride_n, active_idx, counts,
-                                     max_active, row_base, static_cast<hipStream_t>(stream));
+  if (int rc = check_cache_update("focus_cache_update", K_cache, V_cache, shape, K_new, V_new, new_stride_h, new_stride_n, active_idx, max_active)) return rc;
+  const CacheUpdate u = cache_update_args(K_cache, V_cache, *shape, K_new, V_new, new_stride_h, new_stride_n, active_idx, counts, max_active, row_base);
+  hipError_t e = launch_cache_update(u, shape->head_dim, static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return launch_fail("focus_cache_update", e);
   return FOCUS_OK;
+}
+
+int focus_update_sparse_layer(void* K_cache, void* V_cache, const void* K_new, const void* V_new, int64_t new_stride_h, int64_t new_stride_n,
+                              int32_t row_base, const void* Q, const int32_t* focus_idx, const int32_t* active_idx, const int32_t* counts,
+                              int32_t n_focus_max, int32_t max_active, const float* kbar, const focus_shape* shape, int32_t n_keep,
+                              const int32_t* sink_idx, int32_t n_sink, float* scores, int32_t* kept_blocks, void* out, float* lse,
+                              void* workspace, size_t ws_bytes, void* stream) {
+  if (int rc = check_cache_update("focus_update_sparse_layer", K_cache, V_cache, shape, K_new, V_new, new_stride_h, new_stride_n, active_idx, max_active)) return rc;
+  const CacheUpdate u = cache_update_args(K_cache, V_cache, *shape, K_new, V_new, new_stride_h, new_stride_n, active_idx, counts, max_active, row_base);
+  return sparse_layer_impl("focus_update_sparse_layer", Q, focus_idx, active_idx, counts, n_focus_max, max_active, K_cache, V_cache, kbar, shape,
+                           n_keep, sink_idx, n_sink, scores, kept_blocks, out, lse, workspace, ws_bytes, false, stream, &u);
 }
 
 int focus_cache_refresh(void* K_cache, void* V_cache, const focus_shape* shape, const void* K_new, const void* V_new,

@@ -66,10 +66,26 @@ hipError_t launch_block_means(const void* K, const focus_shape& s, float* kbar, 
 hipError_t launch_block_means_relevance(const void* K, const void* Q, const int32_t* focus_idx, const int32_t* counts,
                                         int n_focus_max, const focus_shape& s, float* kbar, float* part, hipStream_t st);
 constexpr int kRelGroup = 4;  // heads whose partial relevances are added before they leave a workgroup
+// Eq. 3: new K/V states of the active positions, to be scattered into the cache
+struct CacheUpdate {
+  const uint16_t* Kn;
+  const uint16_t* Vn;
+  uint16_t* Kc;
+  uint16_t* Vc;
+  int64_t nsh, nsn, ksh, ksn, vsh, vsn;
+  const int32_t* active_idx;
+  const int32_t* counts;
+  int max_active, row_base, n_rows, n_heads;
+};
+CacheUpdate cache_update_args(void* K_cache, void* V_cache, const focus_shape& s, const void* K_new, const void* V_new,
+                              int64_t new_stride_h, int64_t new_stride_n, const int32_t* active_idx, const int32_t* counts,
+                              int max_active, int row_base);
+// update: made by workgroups of the same launch
 // partial relevances (sum over the focus queries, not yet scaled): per_head part[H, n_b], else part[ceil(H / 4), n_b], sums over
 // groups of four heads
 hipError_t launch_block_relevance(const void* Q, const int32_t* focus_idx, const int32_t* counts, int n_focus_max,
-                                  const float* kbar, const focus_shape& s, float* part, bool per_head, hipStream_t st);
+                                  const float* kbar, const focus_shape& s, float* part, bool per_head, hipStream_t st,
+                                  const CacheUpdate* update = nullptr);
 // values[j] = sum_i part[i, j] / (|I_focus| n_heads) when part != nullptr (else values are read), then top-k over values[0..n):
 // out[k] ascending indices.  n_parts = n_heads, or ceil(n_heads / 4) groups
 hipError_t launch_reduce_topk(const float* part, int n_parts, int n_heads, const int32_t* counts, int n_focus_max, float* values, int n,
@@ -108,10 +124,7 @@ hipError_t launch_sink_final(const int32_t* cand, const uint32_t* cand_keys, int
 size_t token_confidence_workspace(int n_rows, int vocab);
 hipError_t launch_token_confidence(const void* logits, int64_t row_stride, const uint8_t* masked, int n_rows, int vocab,
                                    int32_t* tokens, float* conf, void* workspace, hipStream_t st);
-// Eq. 3: scatter the new K/V states of the active positions into the cache (strides of the cache from the shape)
-hipError_t launch_cache_update(void* K_cache, void* V_cache, const focus_shape& s, const void* K_new, const void* V_new,
-                               int64_t new_stride_h, int64_t new_stride_n, const int32_t* active_idx, const int32_t* counts,
-                               int max_active, int row_base, hipStream_t st);
+hipError_t launch_cache_update(const CacheUpdate& u, int head_dim, hipStream_t st);
 // block entry: every cache row takes its new state; block means of the prompt keys from the same pass (kbar may be null)
 struct CacheRefresh {
   const uint16_t* Kn;

@@ -196,10 +196,10 @@ class FocusDecoder:
     run_entry():  per layer  focus_block_entry (every position attends to every key; cache rows <- new states, K_bar of the
                   sparse layers from the same pass)                                   -> out_all[l]
     run_step():   [focus_token_confidence,] focus_select_queries, then per layer focus_cache_update (Eq. 3: the active rows
-                  take their new states before the layer attends) followed by
+                  take their new states before the layer attends; a sparse layer makes it in the same call) followed by
                     dense layer   focus_sparse_attn with every block kept
                     probe layer   focus_probe_layer (dense attention + I_sink)
-                    sparse layer  focus_sparse_layer with the K_bar cached at the block entry -> out[l], kept[l], scores[l]
+                    sparse layer  focus_update_sparse_layer with the K_bar cached at the block entry -> out[l], kept[l], scores[l]
     `row_base` is the cache row of position 0 of the generation block.
     """
 
@@ -264,9 +264,10 @@ class FocusDecoder:
             p(self.counts))))
         for l in range(n_layers):
             s = shape(self.q[l], self.k_cache[l], self.v_cache[l], self.out[l])
-            self.step_calls.append((lib.focus_cache_update, (
-                p(self.k_cache[l]), p(self.v_cache[l]), C.byref(s), p(self.k_new[l]), p(self.v_new[l]), self.k_new[l].stride(0),
-                self.k_new[l].stride(1), p(self.active_idx), p(self.counts), self.max_active, row_base)))
+            if not self.is_sparse(l):
+                self.step_calls.append((lib.focus_cache_update, (
+                    p(self.k_cache[l]), p(self.v_cache[l]), C.byref(s), p(self.k_new[l]), p(self.v_new[l]), self.k_new[l].stride(0),
+                    self.k_new[l].stride(1), p(self.active_idx), p(self.counts), self.max_active, row_base)))
             if l == l_dense:
                 ws = workspace(fb.workspace_bytes(fb.FN_PROBE_LAYER, s, self.max_active))
                 self.step_calls.append((lib.focus_probe_layer, (
@@ -274,9 +275,10 @@ class FocusDecoder:
                     C.byref(s), n_sink, p(self.out[l]), None, p(self.col_mass), p(self.sink_idx), p(ws), ws.numel())))
             elif self.is_sparse(l):
                 ws = workspace(fb.workspace_bytes(fb.FN_SPARSE_LAYER, s, self.max_active, n_keep, n_sink))
-                self.step_calls.append((lib.focus_sparse_layer, (
-                    p(self.q[l]), p(self.focus_idx), p(self.active_idx), p(self.counts), k_focus, self.max_active,
-                    p(self.k_cache[l]), p(self.v_cache[l]), p(self.kbar[l]), C.byref(s), n_keep, p(self.sink_idx), n_sink,
+                self.step_calls.append((lib.focus_update_sparse_layer, (
+                    p(self.k_cache[l]), p(self.v_cache[l]), p(self.k_new[l]), p(self.v_new[l]), self.k_new[l].stride(0),
+                    self.k_new[l].stride(1), row_base, p(self.q[l]), p(self.focus_idx), p(self.active_idx), p(self.counts), k_focus,
+                    self.max_active, p(self.kbar[l]), C.byref(s), n_keep, p(self.sink_idx), n_sink,
                     p(self.scores[l]), p(self.kept[l]), p(self.out[l]), None, p(ws), ws.numel())))
             else:
                 ws = workspace(fb.workspace_bytes(fb.FN_SPARSE_ATTN, s, self.max_active, self.n_b, 0))

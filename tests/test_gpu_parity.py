@@ -1923,3 +1923,40 @@ def test_cache_update(G, H, M, N, d, cap, n_act, base):
     fb.cache_update(kc, vc, s, kn, vn, G.i32([-5, span, span + 7] + [-1] * (cap - 3)), None, base)
     torch.cuda.synchronize()
     assert torch.equal(kc, k2) and torch.equal(vc, v2)
+
+
+@pytest.mark.parametrize("H,M,N,d,B,n_gen,n_act,n_keep,means", [
+    (32, 2048, 64, 128, 64, 64, 36, 9, "cached"),    # the update beside the relevances: five workgroups per head,
+    (6, 1000, 40, 64, 16, 33, 17, 20, "cached"),     # ... more of them than the relevances have, a ragged last one
+    (1, 70000, 16, 64, 32, 16, 16, 40, "cached"),    # ... one head, many slices of relevances, ranked by a launch of their own
+    (4, 256, 8, 128, 16, 8, 5, 3, "cached"),         # one launch for the layer: the update has its own
+    (5, 700, 30, 128, 64, 30, 9, 4, "scan"),         # block means from K, which the update may touch
+])
+def test_update_and_sparse_layer_in_one_call(G, H, M, N, d, B, n_gen, n_act, n_keep, means):
+    """The caches and outputs of the two calls one after the other, bit for bit; entries that are negative or map outside the cache are skipped."""
+    L, n_sink, base = M + N, 3, M - 2                                       # (the first positions lie in the prompt)
+    q, kn, vn = (_rand_bf16(301 + i, H, r, d).to(G.DEV) for i, r in enumerate((n_gen, n_gen, n_gen)))
+    rng = np.random.default_rng(M)
+    act = np.sort(rng.choice(min(n_gen, N + 2), n_act, replace=False)).tolist()
+    lst = act + [N + 5] + [-1] * n_gen
+    active, counts = G.i32(lst[:n_gen]), G.i32([2, n_act])
+    focus, sinks = G.i32(act[:2]), G.i32([0, 7, M // 2])
+    kbar = _rand_bf16(307, H, -(-M // B), d).float().to(G.DEV) if means == "cached" else None
+    res = []
+    for together in (False, True):
+        kc = _rand_bf16(305, L, H, d).to(G.DEV).permute(1, 0, 2)             # cache stored [L, H, d]
+        vc = _rand_bf16(306, H, L, d).to(G.DEV)
+        out = torch.zeros((H, n_gen, d), dtype=torch.bfloat16, device=G.DEV)
+        lse, scores, kept = torch.zeros((H, n_gen), device=G.DEV), torch.zeros(-(-M // B), device=G.DEV), G.i32(None, n_keep)
+        s = fb.make_shape(q, kc, vc, M, B, out)
+        ws = G.ws(fb.workspace_bytes(fb.FN_SPARSE_LAYER, s, n_gen, n_keep, n_sink))
+        if together:
+            fb.update_sparse_layer(kc, vc, kn, vn, base, q, focus, active, counts, kbar, s, n_keep, sinks, n_sink, scores, kept, out, lse, ws)
+        else:
+            fb.cache_update(kc, vc, s, kn, vn, active, counts, base)
+            fb.sparse_layer(q, focus, active, counts, kc, vc, kbar, s, n_keep, sinks, n_sink, scores, kept, out, lse, ws)
+        res.append((kc, vc, scores, kept, out[:, :n_act], lse[:, :n_act]))
+    torch.cuda.synchronize()
+    assert torch.equal(res[0][0][:, base + act[0]], kn[:, 0])
+    for a, b in zip(*res):
+        assert torch.equal(a, b)
