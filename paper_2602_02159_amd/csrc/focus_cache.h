@@ -13,9 +13,10 @@ namespace focus {
 // cover the response rows (copied only).  The mean is accumulated in exactly the order block_means_kernel uses
 // (thread (rr, c): rows rr, rr + RPP, ... of its 16-byte column slice; then the RPP partial rows in order), so the
 // two kernels give bit-identical K_bar.  t = thread 0 .. 255; `red`: RPP rows of D floats; `live` = false: no chunk (the barrier
-// is met all the same).
+// is met all the same).  TOGETHER: the rows of K and V are requested at once (one memory round trip instead of two, twice the registers), for
+// the few workgroups that run beside an attention launch; a launch of nothing else is bound by the memory and wants many small ones.
 typedef unsigned uintx4_t __attribute__((ext_vector_type(4)));
-template <int D>
+template <int D, bool TOGETHER = false>
 __device__ __forceinline__ void cache_refresh_chunk(const CacheRefresh& p, int b, int h, int t, bool live, float* red) {
   constexpr int TPR = D / 8;
   constexpr int RPP = 256 / TPR;
@@ -30,11 +31,19 @@ __device__ __forceinline__ void cache_refresh_chunk(const CacheRefresh& p, int b
   uint16_t* vdst = p.Vc + (int64_t)h * p.vsh + (int64_t)r0 * p.vsn + c * 8;
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   for (int r = rr; r < len; r += RPP * UNROLL) {
-    uint4 v[UNROLL];
+    uint4 v[UNROLL], w[UNROLL];
 #pragma unroll
     for (int u = 0; u < UNROLL; ++u) {
       const int row = r + u * RPP;
       v[u] = row < len ? load_stream16(ksrc + (int64_t)row * p.nsn) : make_uint4(0, 0, 0, 0);
+    }
+    if constexpr (TOGETHER) {
+#pragma unroll
+      for (int u = 0; u < UNROLL; ++u) {
+        const int row = r + u * RPP;
+        if (row < len) w[u] = load_stream16(vsrc + (int64_t)row * p.nsn);
+      }
+      __builtin_amdgcn_sched_barrier(0);
     }
 #pragma unroll
     for (int u = 0; u < UNROLL; ++u) {
@@ -42,8 +51,15 @@ __device__ __forceinline__ void cache_refresh_chunk(const CacheRefresh& p, int b
       add_bf16x8(acc, v[u]);
       if (row < len) __builtin_nontemporal_store(__builtin_bit_cast(uintx4_t, v[u]), reinterpret_cast<uintx4_t*>(kdst + (int64_t)row * p.ksn));
     }
+    if constexpr (TOGETHER) {
+#pragma unroll
+      for (int u = 0; u < UNROLL; ++u) {
+        const int row = r + u * RPP;
+        if (row < len) __builtin_nontemporal_store(__builtin_bit_cast(uintx4_t, w[u]), reinterpret_cast<uintx4_t*>(vdst + (int64_t)row * p.vsn));
+      }
+    }
   }
-  for (int r = rr; r < len; r += RPP * UNROLL) {
+  for (int r = rr; !TOGETHER && r < len; r += RPP * UNROLL) {
     uint4 v[UNROLL];
 #pragma unroll
     for (int u = 0; u < UNROLL; ++u) {

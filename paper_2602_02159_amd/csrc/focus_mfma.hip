@@ -1878,6 +1878,10 @@ hipError_t launch_sparse_attn(const void* Q, const int32_t* active_idx, const in
 // workgroup then fetches and stores twice the rows per product and takes 0.55 us where a block takes 0.83 (32-row sub-tile of 256 workgroups at
 // d = 128), which is less than an empty half of a round costs.  LSE: the log-sum-exps are wanted; they are then those of the unrounded sums.
 // The queries that would leave a round of workgroups mostly empty go there or to refresh_tail_kernel (cut_refresh).
+// COPY: the workgroups behind those of the items make the layer's cache refresh, where this is the layer's last attention launch, instead of a
+// launch of their own (which short prompts feel: block entry, 32 heads, 1160 rows 51.6 -> 42.9 us, 8192 rows 1032 -> 1020; 8 heads, 5823 rows
+// 165 -> 155; d = 64: 32 heads, 1811 rows 49.5 -> 45.7, 8 heads, 14 913 rows 514 -> 504).  At d = 64 the rows of K and V are requested one after the
+// other: both at once take the registers of a second workgroup (14 913 rows 525).
 // =====================================================================================================
 struct RefreshArgs {
   const uint16_t* Q;
@@ -1915,7 +1919,7 @@ constexpr int kRefreshWaves = 8;  // wavefronts per workgroup
 constexpr int kRefreshBlock = 4;  // sub-tiles between two barriers
 constexpr int kHalfTiles = kRefreshWaves / 2;  // query tiles of a half block
 
-template <int D, int PARTS, bool LSE>
+template <int D, int PARTS, bool LSE, bool COPY>
 __global__ __launch_bounds__(64 * kRefreshWaves, 2) void refresh_attn_kernel(const RefreshArgs p, const CacheRefresh copy) {
   using G = Geo<D>;
   constexpr int kKS = D / 16;                    // k-steps of K Q^T
@@ -1939,12 +1943,12 @@ __global__ __launch_bounds__(64 * kRefreshWaves, 2) void refresh_attn_kernel(con
   // stream the same K/V rows through its L2 together.
   const int n_items = PARTS == 1 ? p.n_work : p.n_half_whole + p.n_half_head * p.n_heads;
   const int chunk = (n_items + 7) >> 3;
-  if (PARTS > 1 && (int)blockIdx.x >= 8 * chunk) {  // the layer's cache refresh on the side, as in refresh_tail_kernel
+  if (COPY && (int)blockIdx.x >= 8 * chunk) {  // the layer's cache refresh on the side, as in refresh_tail_kernel
     const int half = threadIdx.x >> 8, item = 2 * ((int)blockIdx.x - 8 * chunk) + half;
     const bool live = item < copy.n_chunks * copy.n_heads;
     const int ch = live ? item / copy.n_chunks : 0;
     static_assert(2 * 2048 * sizeof(float) <= sizeof(ringsK), "both halves' partial means fit");
-    cache_refresh_chunk<D>(copy, live ? item - ch * copy.n_chunks : 0, ch, threadIdx.x & 255, live, reinterpret_cast<float*>(ringsK) + half * 2048);
+    cache_refresh_chunk<D, D == 128>(copy, live ? item - ch * copy.n_chunks : 0, ch, threadIdx.x & 255, live, reinterpret_cast<float*>(ringsK) + half * 2048);
     return;
   }
   const int work = (int)(blockIdx.x & 7u) * chunk + (int)(blockIdx.x >> 3);
@@ -2456,23 +2460,26 @@ static hipError_t launch_refresh_t(RefreshArgs& a, const focus_shape& s, const C
   const dim3 block(64 * kRefreshWaves);
   const int64_t copies = copy ? ceil_div64((int64_t)copy->n_chunks * copy->n_heads, 2) : 0;
   auto list = [](int64_t n) { return (int64_t)8 * ceil_div64(n, 8); };
-  if (cut.n_work > 0) {
-    hipLaunchKernelGGL((refresh_attn_kernel<D, 1, false>), dim3((uint32_t)list(cut.n_work)), block, 0, st, a, CacheRefresh{});
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  if (copy != nullptr && (cut.n_half + cut.n_tail == 0 || list(cut.n_tail > 0 ? cut.n_tail : cut.n_half) + copies > kMaxGroups)) {
+  if (copy != nullptr && list(cut.n_tail > 0 ? cut.n_tail : (cut.n_half > 0 ? cut.n_half : cut.n_work)) + copies > kMaxGroups) {
     hipError_t e = launch_cache_refresh(*copy, D, st);
     if (e != hipSuccess) return e;
     copy = nullptr;
+  }
+  if (cut.n_work > 0) {
+    if (copy != nullptr && cut.n_half + cut.n_tail == 0)
+      hipLaunchKernelGGL((refresh_attn_kernel<D, 1, false, true>), dim3((uint32_t)(list(cut.n_work) + copies)), block, 0, st, a, *copy);
+    else
+      hipLaunchKernelGGL((refresh_attn_kernel<D, 1, false, false>), dim3((uint32_t)list(cut.n_work)), block, 0, st, a, CacheRefresh{});
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
   }
   if (cut.n_half > 0) {
     const bool with = copy != nullptr && cut.n_tail == 0;
     const dim3 grid((uint32_t)(list(cut.n_half) + (with ? copies : 0)));
     if (a.lse)
-      hipLaunchKernelGGL((refresh_attn_kernel<D, 2, true>), grid, block, 0, st, a, with ? *copy : CacheRefresh{});
+      hipLaunchKernelGGL((refresh_attn_kernel<D, 2, true, true>), grid, block, 0, st, a, with ? *copy : CacheRefresh{});
     else
-      hipLaunchKernelGGL((refresh_attn_kernel<D, 2, false>), grid, block, 0, st, a, with ? *copy : CacheRefresh{});
+      hipLaunchKernelGGL((refresh_attn_kernel<D, 2, false, true>), grid, block, 0, st, a, with ? *copy : CacheRefresh{});
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || cut.n_tail == 0) return e;
   }
