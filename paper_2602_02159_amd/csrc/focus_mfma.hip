@@ -1874,7 +1874,8 @@ hipError_t launch_sparse_attn(const void* Q, const int32_t* active_idx, const in
 // loop body of its own.  No index lists, no key splits across workgroups: each normalises and writes its own rows.
 // One-dimensional grid over the (head, query block) list, dealt to the XCDs in contiguous eighths (see the kernel).
 // PARTS = 2: a half block of 128 queries.  Four wavefronts carry its tiles over the even key sub-tiles, four over the odd ones, each four with
-// rings of their own (half as long: a barrier per two sub-tiles), and the two states of a tile are added at the end.  A
+// rings of their own (half as long: a barrier per two sub-tiles), and the two states of a tile are added at the end.  (PARTS = 4: a quarter, 64
+// queries, every fourth sub-tile, a barrier each.)  A
 // workgroup then fetches and stores twice the rows per product and takes 0.55 us where a block takes 0.83 (32-row sub-tile of 256 workgroups at
 // d = 128), which is less than an empty half of a round costs.  LSE: the log-sum-exps are wanted; they are then those of the unrounded sums.
 // The queries that would leave a round of workgroups mostly empty go there or to refresh_tail_kernel (cut_refresh).
@@ -1893,8 +1894,8 @@ struct RefreshArgs {
   int n_q, L;
   int n_qb, n_work;    // whole query blocks per head; work items (head, query block) of refresh_attn_kernel
   int n_heads, n_tail;  // query tiles left to refresh_tail_kernel
-  // half blocks of four tiles (refresh_attn_kernel<., 2, .>): so many of whole blocks, then so many of every head's last tiles
-  int n_half_whole, n_half_head;
+  // parts of blocks (refresh_attn_kernel<., 2 | 4, .>), of part_tiles tiles: so many of whole blocks, then so many of every head's last tiles
+  int n_part_whole, n_part_head, part_tiles;
   float scale_log2;
 };
 
@@ -1917,7 +1918,6 @@ __device__ __forceinline__ void pin(int& x) { asm volatile("" : "+v"(x)); }
 // reads, but a lone wavefront cannot cover its own dependent vector-ALU chains: 0.82 against 1.01 PFLOP/s.)
 constexpr int kRefreshWaves = 8;  // wavefronts per workgroup
 constexpr int kRefreshBlock = 4;  // sub-tiles between two barriers
-constexpr int kHalfTiles = kRefreshWaves / 2;  // query tiles of a half block
 
 template <int D, int PARTS, bool LSE, bool COPY>
 __global__ __launch_bounds__(64 * kRefreshWaves, 2) void refresh_attn_kernel(const RefreshArgs p, const CacheRefresh copy) {
@@ -1941,7 +1941,7 @@ __global__ __launch_bounds__(64 * kRefreshWaves, 2) void refresh_attn_kernel(con
   // therefore given work item (i % 8) * chunk + i / 8 of the (head, query block) list: an XCD walks one contiguous
   // eighth of the list, so the workgroups resident on it at any time are neighbouring query blocks of ONE head and
   // stream the same K/V rows through its L2 together.
-  const int n_items = PARTS == 1 ? p.n_work : p.n_half_whole + p.n_half_head * p.n_heads;
+  const int n_items = PARTS == 1 ? p.n_work : p.n_part_whole + p.n_part_head * p.n_heads;
   const int chunk = (n_items + 7) >> 3;
   if (COPY && (int)blockIdx.x >= 8 * chunk) {  // the layer's cache refresh on the side, as in refresh_tail_kernel
     const int half = threadIdx.x >> 8, item = 2 * ((int)blockIdx.x - 8 * chunk) + half;
@@ -1957,14 +1957,14 @@ __global__ __launch_bounds__(64 * kRefreshWaves, 2) void refresh_attn_kernel(con
   if (PARTS == 1) {
     h = work / p.n_qb;
     tile0 = (work - h * p.n_qb) * kRefreshWaves;
-  } else if (work < p.n_half_whole) {
+  } else if (work < p.n_part_whole) {
     const int block = p.n_work + work / PARTS;
     h = block / p.n_qb;
     tile0 = (block - h * p.n_qb) * kRefreshWaves + work % PARTS * kPartWaves;
   } else {
-    const int i = work - p.n_half_whole;
-    h = i / p.n_half_head;
-    tile0 = p.n_qb * kRefreshWaves + (i - h * p.n_half_head) * kPartWaves;
+    const int i = work - p.n_part_whole;
+    h = i / p.n_part_head;
+    tile0 = p.n_qb * kRefreshWaves + (i - h * p.n_part_head) * kPartWaves;
   }
   const int q_row = (tile0 + tile) * 32 + qi;
   // Sub-tiles: n_keys of the head; a part takes those with its remainder mod PARTS, n_tiles for each of them (one may be past the end)
@@ -2219,29 +2219,48 @@ __global__ __launch_bounds__(64 * kRefreshWaves, 2) void refresh_attn_kernel(con
     l_exact = __uint_as_float(uw.x) + __uint_as_float(uw.y);
   }
   if constexpr (PARTS > 1) {  // the parts of a tile hold the same elements in the same lanes: through LDS, 16 bytes of a lane at a time
-    static_assert(PARTS == 2 && kPartWaves * 32 * D * 4 <= (int)sizeof(ringsK) && kPartWaves * 64 * 16 <= (int)sizeof(ringsV), "the tiles of one part fit");
-    floatx4* o_sh = reinterpret_cast<floatx4*>(ringsK) + tile * (32 * D / 4) + lane;
-    floatx4* ml_sh = reinterpret_cast<floatx4*>(ringsV) + tile * 64 + lane;
+    constexpr int kPartBytes = kPartWaves * 32 * D * 4;
+    static_assert(PARTS / 2 * kPartBytes <= (int)sizeof(ringsK) && (PARTS / 2 - 1) * kPartBytes + (PARTS - 1) * kPartWaves * 64 * 16 <= (int)sizeof(ringsV), "the parts fit");
+    auto o_of = [&](int other) __attribute__((always_inline)) {  // parts 1 .. PARTS / 2 in the place of the K rings, the others in that of the V rings
+      char* at = other <= PARTS / 2 ? ringsK + (other - 1) * kPartBytes : ringsV + (other - 1 - PARTS / 2) * kPartBytes;
+      return reinterpret_cast<floatx4*>(at) + tile * (32 * D / 4) + lane;
+    };
+    auto ml_of = [&](int other) __attribute__((always_inline)) {
+      return reinterpret_cast<floatx4*>(ringsV + (PARTS / 2 - 1) * kPartBytes) + ((other - 1) * kPartWaves + tile) * 64 + lane;
+    };
     __syncthreads();  // the rings have been read by everyone
     if (part != 0) {
+      floatx4* dst = o_of(part);
 #pragma unroll
       for (int i = 0; i < 4 * kDT; ++i)
-        o_sh[64 * i] = floatx4{o[i >> 2][4 * (i & 3)], o[i >> 2][4 * (i & 3) + 1], o[i >> 2][4 * (i & 3) + 2], o[i >> 2][4 * (i & 3) + 3]};
-      *ml_sh = floatx4{m_run, l, l_exact, 0.f};
+        dst[64 * i] = floatx4{o[i >> 2][4 * (i & 3)], o[i >> 2][4 * (i & 3) + 1], o[i >> 2][4 * (i & 3) + 2], o[i >> 2][4 * (i & 3) + 3]};
+      *ml_of(part) = floatx4{m_run, l, l_exact, 0.f};
     }
     __syncthreads();
     if (part != 0) return;
-    const floatx4 other = *ml_sh;
-    const float m_all = fmaxf(m_run, other[0]);
-    const float f0 = l > 0.f ? __builtin_amdgcn_exp2f(m_run - m_all) : 0.f, f1 = other[1] > 0.f ? __builtin_amdgcn_exp2f(other[0] - m_all) : 0.f;
-    m_run = m_all;
-    l = f0 * l + f1 * other[1];
-    l_exact = f0 * l_exact + f1 * other[2];
+    floatx4 ml[PARTS];
+    ml[0] = floatx4{m_run, l, l_exact, 0.f};
+    float f[PARTS];
+#pragma unroll
+    for (int w = 1; w < PARTS; ++w) {
+      ml[w] = *ml_of(w);
+      m_run = fmaxf(m_run, ml[w][0]);
+    }
+    l = 0.f;
+    l_exact = 0.f;
+#pragma unroll
+    for (int w = 0; w < PARTS; ++w) {
+      f[w] = ml[w][1] > 0.f ? __builtin_amdgcn_exp2f(ml[w][0] - m_run) : 0.f;
+      l += f[w] * ml[w][1];
+      l_exact += f[w] * ml[w][2];
+    }
 #pragma unroll
     for (int i = 0; i < 4 * kDT; ++i) {
-      const floatx4 x = o_sh[64 * i];
+      floatx4 x = floatx4{o[i >> 2][4 * (i & 3)], o[i >> 2][4 * (i & 3) + 1], o[i >> 2][4 * (i & 3) + 2], o[i >> 2][4 * (i & 3) + 3]} * f[0];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) o[i >> 2][4 * (i & 3) + j] = f0 * o[i >> 2][4 * (i & 3) + j] + f1 * x[j];
+      for (int w = 1; w < PARTS; ++w) x += f[w] * o_of(w)[64 * i];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) o[i >> 2][4 * (i & 3) + j] = x[j];
     }
   }
   if (q_row < p.n_q) {
@@ -2295,7 +2314,7 @@ __global__ __launch_bounds__(64 * kRefreshWaves, D == 64 ? 4 : 2) void refresh_t
   const int chunk = (p.n_tail + 7) >> 3;
   const int item = (int)(blockIdx.x & 7u) * chunk + (int)(blockIdx.x >> 3);
   if (item >= p.n_tail) return;  // whole workgroup
-  const int done = p.n_work * kRefreshWaves + p.n_half_whole * kHalfTiles;  // tiles of whole blocks: taken, and left
+  const int done = p.n_work * kRefreshWaves + p.n_part_whole * p.part_tiles;  // tiles of whole blocks: taken, and left
   const int n_left = p.n_heads * p.n_qb * kRefreshWaves - done;
   int h, tile;
   if (item < n_left) {
@@ -2303,7 +2322,7 @@ __global__ __launch_bounds__(64 * kRefreshWaves, D == 64 ? 4 : 2) void refresh_t
     h = block / p.n_qb;
     tile = done + item - h * p.n_qb * kRefreshWaves;
   } else {
-    const int first = p.n_qb * kRefreshWaves + p.n_half_head * kHalfTiles, per_head = (p.n_q + 31) / 32 - first;
+    const int first = p.n_qb * kRefreshWaves + p.n_part_head * p.part_tiles, per_head = (p.n_q + 31) / 32 - first;
     h = (item - n_left) / per_head;
     tile = first + (item - n_left) - h * per_head;
   }
@@ -2388,27 +2407,30 @@ __global__ __launch_bounds__(64 * kRefreshWaves, D == 64 ? 4 : 2) void refresh_t
 
 // Which query tiles go to which kernel.  Every 256-query block takes the same time, so refresh_attn_kernel runs in rounds of 256
 // blocks (one per compute unit; at d = 64 two fit, and take twice as long), and a round that is mostly empty costs as much as a
-// full one.  Half blocks of four tiles, every key sub-tile for half of the wavefronts, take two thirds of a block's time.
+// full one.  Half blocks of four tiles, every key sub-tile for half of the wavefronts, take two thirds of a block's time, quarters of two tiles
+// a little over a third (d = 64, where two single tiles share a compute unit: no gain, not built).
 // refresh_tail_kernel takes single 32-query tiles: an eighth of the key sub-tiles per wavefront, each about twice
 // (d = 64: four times) as long because eight tiles no longer share the staged rows.  At d = 64 two tiles share a compute unit and hardly
 // slow each other down, and 512 of them need not come in whole rounds.  All have a fixed part (first loads, merge).  The ways
 // to cut, the cheapest is taken (times in us, measured; the cache refresh is left out, with which the cut must not change):
 //   everything in blocks, the ragged one of each head included;
 //   whole blocks, or whole rounds of them, and of the rest
-//     all in halves, with every head's last tiles in halves, the last of them padded or not;
-//     whole rounds of halves, and single tiles; or single tiles only.
+//     all in halves (or quarters), with every head's last tiles in halves, the last of them padded or not;
+//     whole rounds of halves (or quarters), and single tiles; or single tiles only.
 // Block entry without halves and with them, d = 128: 32 heads, 2741 rows 185 -> 159 us, 2991 rows 219 -> 189, 4900 rows 487 -> 432; 8
 // heads, 4096 rows 117 -> 88, 11 691 rows 669 -> 575; 4 heads, 8192 rows 219 -> 154, 9003 rows 275 -> 240; d = 64: 32 heads, 2991 rows 122 ->
-// 116; 8 heads, 4096 rows 62.6 -> 54.6.  Where a round of blocks is full or nearly so they lose (d = 64: 8 heads, 8192 rows 166 and 185).
+// 116; 8 heads, 4096 rows 62.6 -> 54.6.  Quarters, where tiles took two rounds or more: d = 128, 8 heads, 1500 rows 31.1 -> 25.3; 4 heads, 2455 rows
+// 38.0 -> 34.6, 3000 rows 45.5 -> 39.7, 4096 rows 63.4 -> 56.2.  Where a round of blocks is full or nearly so they lose (d = 64: 8 heads, 8192 rows 166 and 185).
 // 32 heads, 8256 rows (33 blocks per head, 4.1 rounds): 1213 us all in blocks, 1106 us cut; 4 heads, 1056 rows, d = 64: 26 and 8.
+// d = 64, up to 256 tiles, which have a compute unit each, take two thirds of that (4 heads: 1266 rows 160 tiles 8.5, 2455 rows 308 tiles 19.8).
 // d = 64, block entry in blocks and in tiles: 32 heads, 1032 rows 35.1 and 29.6; 16 heads, 2032 52.4 and 39.1, 3032 71.3 and 73.2, 4032 95.5 and
 // 118; 8 heads, 4032 85 and 64, 6032 119 and 130.
 // A launch has fewer than 2^32 threads (kMaxGroups workgroups).  More tail tiles than that stay in blocks; more chunks of the cache
 // refresh than fit behind the tail tiles (2^24 of them: block 1, 32 heads, half a million rows) get the launch of their own that they
 // have where there is no tail.
 struct RefreshCut {
-  int n_qb = 0, n_work = 0, half_whole = 0, half_head = 0;
-  int64_t n_half = 0, n_tail = 0;
+  int n_qb = 0, n_work = 0, parts = 2, part_whole = 0, part_head = 0;
+  int64_t n_part = 0, n_tail = 0;
   float time = 0.f;
 };
 static RefreshCut cut_refresh(int head_dim, int n_heads, int n_q, int L) {
@@ -2418,32 +2440,36 @@ static RefreshCut cut_refresh(int head_dim, int n_heads, int n_q, int L) {
   const float sub = (float)ceil_div(L, kSubTile);
   const bool d128 = head_dim == 128;
   const float block_time = d128 ? 0.85f * sub + 5.f : 0.5f * sub + 12.f, tail_time = d128 ? 0.2f * sub + 5.f : 0.23f * sub + 3.f;
-  const float half_time = d128 ? 0.55f * sub + 10.f : 0.31f * sub + 10.f;
+  const float half_time = d128 ? 0.55f * sub + 10.f : 0.31f * sub + 10.f, quarter_time = 0.31f * sub + 10.f;
   auto rounds = [](int64_t n) { return (float)((n + kSlots - 1) / kSlots); };
-  auto tail_rounds = [&](int64_t n) { return d128 || n == 0 ? rounds(n) : std::max(1.f, (float)n / (2 * kSlots)); };
+  auto tail_rounds = [&](int64_t n) { return d128 || n == 0 ? rounds(n) : (n <= kSlots ? 0.63f : std::max(1.f, (float)n / (2 * kSlots))); };
   const int64_t whole = (int64_t)(tiles / kRefreshWaves) * n_heads, padded = (int64_t)ceil_div(tiles, kRefreshWaves) * n_heads;
   RefreshCut best;
   best.n_qb = ceil_div(tiles, kRefreshWaves);
   best.n_work = (int)padded;
   best.time = rounds(padded) * block_time;
-  auto consider = [&](int64_t work, int64_t half_whole, int half_head) {
+  auto consider = [&](int64_t work, int parts, int64_t part_whole, int part_head) {
+    const int part_tiles = kRefreshWaves / parts;
     RefreshCut c;
     c.n_qb = tiles / kRefreshWaves;
     c.n_work = (int)work;
-    c.half_whole = (int)half_whole;
-    c.half_head = half_head;
-    c.n_half = half_whole + (int64_t)half_head * n_heads;
-    c.n_tail = (2 * (whole - work) - half_whole) * kHalfTiles + (int64_t)std::max(0, last - half_head * kHalfTiles) * n_heads;
-    if (c.n_half + 7 > kMaxGroups || c.n_tail + 7 > kMaxGroups) return;
-    c.time = rounds(work) * block_time + rounds(c.n_half) * half_time + tail_rounds(c.n_tail) * tail_time;
+    c.parts = parts;
+    c.part_whole = (int)part_whole;
+    c.part_head = part_head;
+    c.n_part = part_whole + (int64_t)part_head * n_heads;
+    c.n_tail = (parts * (whole - work) - part_whole) * part_tiles + (int64_t)std::max(0, last - part_head * part_tiles) * n_heads;
+    if (c.n_part + 7 > kMaxGroups || c.n_tail + 7 > kMaxGroups) return;
+    c.time = rounds(work) * block_time + rounds(c.n_part) * (parts == 2 ? half_time : quarter_time) + tail_rounds(c.n_tail) * tail_time;
     if (c.time < best.time) best = c;
   };
   const int64_t rest = whole % kSlots;
   for (int64_t work : {whole, whole - rest}) {
-    const int64_t halves = 2 * (whole - work);
-    for (int half_head = 0; half_head <= ceil_div(last, kHalfTiles); ++half_head) consider(work, halves, half_head);
-    consider(work, halves - halves % kSlots, 0);
-    consider(work, 0, 0);
+    consider(work, 2, 0, 0);
+    for (int parts = 2; parts <= (d128 ? 4 : 2); parts *= 2) {
+      const int64_t n = parts * (whole - work);
+      for (int part_head = 0; part_head <= ceil_div(last, kRefreshWaves / parts); ++part_head) consider(work, parts, n, part_head);
+      consider(work, parts, n - n % kSlots, 0);
+    }
   }
   return best;
 }
@@ -2454,32 +2480,42 @@ static hipError_t launch_refresh_t(RefreshArgs& a, const focus_shape& s, const C
   a.n_heads = s.n_heads;
   a.n_qb = cut.n_qb;
   a.n_work = cut.n_work;
-  a.n_half_whole = cut.half_whole;
-  a.n_half_head = cut.half_head;
+  a.n_part_whole = cut.part_whole;
+  a.n_part_head = cut.part_head;
+  a.part_tiles = kRefreshWaves / cut.parts;
   a.n_tail = (int)cut.n_tail;
   const dim3 block(64 * kRefreshWaves);
   const int64_t copies = copy ? ceil_div64((int64_t)copy->n_chunks * copy->n_heads, 2) : 0;
   auto list = [](int64_t n) { return (int64_t)8 * ceil_div64(n, 8); };
-  if (copy != nullptr && list(cut.n_tail > 0 ? cut.n_tail : (cut.n_half > 0 ? cut.n_half : cut.n_work)) + copies > kMaxGroups) {
+  if (copy != nullptr && list(cut.n_tail > 0 ? cut.n_tail : (cut.n_part > 0 ? cut.n_part : cut.n_work)) + copies > kMaxGroups) {
     hipError_t e = launch_cache_refresh(*copy, D, st);
     if (e != hipSuccess) return e;
     copy = nullptr;
   }
   if (cut.n_work > 0) {
-    if (copy != nullptr && cut.n_half + cut.n_tail == 0)
+    if (copy != nullptr && cut.n_part + cut.n_tail == 0)
       hipLaunchKernelGGL((refresh_attn_kernel<D, 1, false, true>), dim3((uint32_t)(list(cut.n_work) + copies)), block, 0, st, a, *copy);
     else
       hipLaunchKernelGGL((refresh_attn_kernel<D, 1, false, false>), dim3((uint32_t)list(cut.n_work)), block, 0, st, a, CacheRefresh{});
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  if (cut.n_half > 0) {
+  if (cut.n_part > 0) {
     const bool with = copy != nullptr && cut.n_tail == 0;
-    const dim3 grid((uint32_t)(list(cut.n_half) + (with ? copies : 0)));
-    if (a.lse)
-      hipLaunchKernelGGL((refresh_attn_kernel<D, 2, true, true>), grid, block, 0, st, a, with ? *copy : CacheRefresh{});
+    const dim3 grid((uint32_t)(list(cut.n_part) + (with ? copies : 0)));
+    const CacheRefresh with_copy = with ? *copy : CacheRefresh{};
+    auto launch = [&](auto parts) {
+      if (a.lse)
+        hipLaunchKernelGGL((refresh_attn_kernel<D, decltype(parts)::value, true, true>), grid, block, 0, st, a, with_copy);
+      else
+        hipLaunchKernelGGL((refresh_attn_kernel<D, decltype(parts)::value, false, true>), grid, block, 0, st, a, with_copy);
+    };
+    if (cut.parts == 2)
+      launch(std::integral_constant<int, 2>{});
+    else if constexpr (D == 128)
+      launch(std::integral_constant<int, 4>{});
     else
-      hipLaunchKernelGGL((refresh_attn_kernel<D, 2, false, true>), grid, block, 0, st, a, with ? *copy : CacheRefresh{});
+      return hipErrorInvalidValue;
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || cut.n_tail == 0) return e;
   }

@@ -1492,6 +1492,9 @@ def test_refresh_attn_cut_into_blocks_and_tiles(G, H, n_q, L, d):
     (96, 1024, 672, 128),  # a round of blocks, then a round of half blocks; an odd number of whole sub-tiles
     (64, 512, 1100, 64),   # half blocks of 64 columns, a ragged last sub-tile of one half
     (64, 500, 1121, 64),   # ... and of the other
+    (8, 1500, 1490, 128),  # quarters, the last tile of a head missing: one part has a sub-tile less than the others,
+    (8, 1500, 1537, 128),  # ... three have, and the fourth's last one has a single row;
+    (9, 1000, 330, 128),   # ... a few sub-tiles each, the last tile ragged
 ])
 def test_refresh_attn_half_blocks(G, H, n_q, L, d, offset):
     q, k, v = (_rand_bf16(171 + i, H, r, d).to(G.DEV) for i, r in enumerate((n_q, L, L)))
