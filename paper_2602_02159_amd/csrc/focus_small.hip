@@ -888,15 +888,23 @@ struct ConfState {
   int idx;
   float s;
 };
-// merge in the order (value descending, index ascending); s is rescaled to the larger maximum
-__device__ __forceinline__ ConfState conf_merge(const ConfState& a, const ConfState& b) {
+// The states of 64 (or of each 32) lanes in the order (value descending, index ascending), the sums rescaled once to the largest maximum; every
+// lane receives the result.  s == 0 marks "nothing seen": its m is -inf.  m is never NaN.
+template <int LANES>
+__device__ __forceinline__ ConfState conf_reduce(const ConfState& st) {
+  auto reduce = [](uint32_t x, auto op) -> uint32_t {
+    if constexpr (LANES == kWave) return wave_reduce_u32(x, op);
+    x = row_reduce_u32(x, op);
+    typedef unsigned v2u __attribute__((ext_vector_type(2)));
+    const v2u b = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    return op(b.x, b.y);
+  };
+  auto of = [](uint32_t x) { return __uint_as_float(x); };
   ConfState r;
-  const bool a_first = a.m > b.m || (a.m == b.m && a.idx < b.idx);
-  r.m = a_first ? a.m : b.m;
-  r.idx = a_first ? a.idx : b.idx;
-  const float sa = a.s > 0.f ? a.s * __expf(a.m - r.m) : 0.f;  // s == 0 marks "nothing seen": its m is -inf
-  const float sb = b.s > 0.f ? b.s * __expf(b.m - r.m) : 0.f;
-  r.s = sa + sb;
+  r.m = of(reduce(__float_as_uint(st.m), [&](uint32_t x, uint32_t y) { return __float_as_uint(fmaxf(of(x), of(y))); }));
+  r.idx = (int)reduce(st.m == r.m ? (uint32_t)st.idx : 0x7fffffffu, [](uint32_t x, uint32_t y) { return min(x, y); });
+  const float mine = st.s > 0.f ? st.s * __expf(st.m - r.m) : 0.f;
+  r.s = of(reduce(__float_as_uint(mine), [&](uint32_t x, uint32_t y) { return __float_as_uint(of(x) + of(y)); }));
   return r;
 }
 
@@ -904,7 +912,10 @@ __device__ __forceinline__ ConfState conf_merge(const ConfState& a, const ConfSt
 // contiguous slice of the row once: eight bf16 per 16-byte non-temporal load; per vector the running maximum is raised
 // once and the eight exponentials are added.  Threads, then wavefronts, merge their states in a fixed order.  With
 // one split the workgroup writes the result; otherwise its state goes to part[row, split] and token_confidence_merge
-// finishes the row (splits in index order).
+// finishes the row.  Bound by latency: one memory round trip (the mask is looked at behind the request of the first vectors) and the
+// reductions: maximum, index and sum one after the other by lane moves within the vector ALU.  With whole states exchanged through the LDS
+// crossbar step by step, and the mask looked at first, both launches together took 10.8 us for 32 rows of 126 464 where they now take 6.7
+// (64 rows 12.2 -> 8.4, 8 rows 8.0 -> 5.5, 64 rows of 32 000 8.9 -> 6.2).
 __global__ __launch_bounds__(256) void token_confidence_kernel(const uint16_t* __restrict__ logits, int64_t row_stride,
                                                                const uint8_t* __restrict__ masked, int vocab, int n_split,
                                                                ConfState* __restrict__ part, int32_t* __restrict__ tokens,
@@ -915,16 +926,19 @@ __global__ __launch_bounds__(256) void token_confidence_kernel(const uint16_t* _
   st.m = -INFINITY;
   st.idx = 0x7fffffff;
   st.s = 0.f;
+  const uint16_t* x = logits + (int64_t)row * row_stride;
+  const int n_vec = vocab >> 3;
+  const int per = (n_vec + n_split - 1) / n_split;
+  const int v_begin = split * per, v_end = min(v_begin + per, n_vec);
+  auto vector = [&](int v) {  // (vectors past the end: -inf)
+    return v < v_end ? load_stream16(x + (int64_t)v * 8) : make_uint4(0xff80ff80u, 0xff80ff80u, 0xff80ff80u, 0xff80ff80u);
+  };
+  uint4 a = vector(v_begin + tid), b = vector(v_begin + tid + nt);  // two vectors in flight
+  __builtin_amdgcn_sched_barrier(0);
   const bool skip = masked != nullptr && masked[row] == 0;  // uniform over the workgroup
   if (!skip) {
-    const uint16_t* x = logits + (int64_t)row * row_stride;
-    const int n_vec = vocab >> 3;
-    const int per = (n_vec + n_split - 1) / n_split;
-    const int v_begin = split * per, v_end = min(v_begin + per, n_vec);
-    for (int v0 = v_begin + tid; v0 < v_end; v0 += nt * 2) {  // two vectors in flight
+    for (int v0 = v_begin + tid; v0 < v_end; v0 += nt * 2) {
       const int v1 = v0 + nt;
-      const uint4 a = load_stream16(x + (int64_t)v0 * 8);
-      const uint4 b = v1 < v_end ? load_stream16(x + (int64_t)v1 * 8) : make_uint4(0xff80ff80u, 0xff80ff80u, 0xff80ff80u, 0xff80ff80u);
       const uint4 vv[2] = {a, b};
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
@@ -954,6 +968,8 @@ __global__ __launch_bounds__(256) void token_confidence_kernel(const uint16_t* _
           for (int i = 0; i < 8; ++i) st.s += __expf(e[i] - st.m);
         }
       }
+      a = vector(v0 + 2 * nt);
+      b = vector(v1 + 2 * nt);
     }
     if (split == n_split - 1) {  // ragged tail of the row, one element per thread
       for (int j = (n_vec << 3) + tid; j < vocab; j += nt) {
@@ -967,19 +983,16 @@ __global__ __launch_bounds__(256) void token_confidence_kernel(const uint16_t* _
       }
     }
   }
-#pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {  // butterfly: every lane ends with the wavefront's state
-    ConfState other;
-    other.m = __shfl_xor(st.m, o, kWave);
-    other.idx = __shfl_xor(st.idx, o, kWave);
-    other.s = __shfl_xor(st.s, o, kWave);
-    st = conf_merge(st, other);
-  }
+  st = conf_reduce<kWave>(st);
   if ((tid & 63) == 0) wave_state[tid >> 6] = st;
   __syncthreads();
-  if (tid == 0) {
-    ConfState r = wave_state[0];
-    for (int w = 1; w < (nt >> 6); ++w) r = conf_merge(r, wave_state[w]);
+  if (tid < kWave) {
+    if (tid < 4)
+      st = wave_state[tid];
+    else
+      st = ConfState{-INFINITY, 0x7fffffff, 0.f};
+    const ConfState r = conf_reduce<32>(st);
+    if (tid != 0) return;
     if (n_split == 1) {
       tokens[row] = r.s > 0.f ? r.idx : -1;
       conf[row] = r.s > 0.f ? 1.f / r.s : 0.f;
@@ -999,14 +1012,8 @@ __global__ __launch_bounds__(256) void token_confidence_merge(const ConfState* _
   r.idx = 0x7fffffff;
   r.s = 0.f;
   if (row < n_rows && s < n_split) r = part[(int64_t)row * n_split + s];
-#pragma unroll
-  for (int o = 1; o < kConfMaxSplits; o <<= 1) {
-    ConfState other;
-    other.m = __shfl_xor(r.m, o, kWave);
-    other.idx = __shfl_xor(r.idx, o, kWave);
-    other.s = __shfl_xor(r.s, o, kWave);
-    r = conf_merge(r, other);
-  }
+  static_assert(kConfMaxSplits == 32, "half a wavefront per row");
+  r = conf_reduce<32>(r);
   if (row < n_rows && s == 0) {
     tokens[row] = r.s > 0.f ? r.idx : -1;
     conf[row] = r.s > 0.f ? 1.f / r.s : 0.f;
