@@ -208,7 +208,7 @@ int focus_sparse_attn(const void* Q, const int32_t* active_idx, const int32_t* c
  * attention kernel ranks the blocks itself from the partial relevances instead of waiting for a separate Top-C
  * kernel (short key lists of few heads need one launch: it forms the relevances, too, and writes the output itself).
  * kbar NULL: the first launch scans K and forms the block means on the fly.
- * With more than 2048 prompt blocks (kbar NULL: more than 256), or more than 1024 and less workspace than the sum of what
+ * With more than 2048 prompt blocks, or more than 1024 and less workspace than the sum of what
  * focus_block_scores and focus_sparse_attn need, the call falls back to the separate kernels.
  */
 int focus_sparse_layer(const void* Q, const int32_t* focus_idx, const int32_t* active_idx, const int32_t* counts,

@@ -403,7 +403,9 @@ static int sparse_layer_impl(const char* who, const void* Q, const int32_t* focu
   hipStream_t st = static_cast<hipStream_t>(stream);
   char* ws = static_cast<char*>(workspace);
   const bool apart = ws_bytes >= w.attn + w.at.total;  // (else n_b > kFusedManyBlocks)
-  const bool fused = n_b <= (kbar ? kFusedMaxBlocks : kFusedMaxBlocksPerHead) && n_keep > 0 && apart;
+  const bool fused = n_b <= kFusedMaxBlocks && n_keep > 0 && apart;
+  // The parts of a K scan are per head.  More than the attention kernel requests at once are added up by a launch in between.
+  const bool grouped = fused && !kbar && n_b > kFusedMaxBlocksPerHead && shape->n_heads > 8;
   const size_t attn = apart ? w.attn : 0;
   float* part = reinterpret_cast<float*>(ws + w.sc.part);
   float* R = scores ? scores : reinterpret_cast<float*>(ws + w.sc.scores);
@@ -432,11 +434,12 @@ static int sparse_layer_impl(const char* who, const void* Q, const int32_t* focu
     e = launch_block_means_relevance(K, Q, focus_idx, counts, n_focus_max, *shape, nullptr, part, st);
   else if (!inner)
     e = launch_block_relevance(Q, focus_idx, counts, n_focus_max, kbar, *shape, part, false, st, update);
+  if (e == hipSuccess && grouped) e = launch_group_heads(part, shape->n_heads, n_b, st);
   if (e != hipSuccess) return launch_fail("focus_sparse_layer(relevance)", e);
   if (fused) {
     FusedTopC f;
     f.rel_part = part;
-    f.per_head = kbar == nullptr;
+    f.per_head = kbar == nullptr && !grouped;
     f.scores_out = R;
     f.kept_out = kept_blocks;
     f.n_focus_max = n_focus_max;

@@ -86,6 +86,8 @@ CacheUpdate cache_update_args(void* K_cache, void* V_cache, const focus_shape& s
 hipError_t launch_block_relevance(const void* Q, const int32_t* focus_idx, const int32_t* counts, int n_focus_max,
                                   const float* kbar, const focus_shape& s, float* part, bool per_head, hipStream_t st,
                                   const CacheUpdate* update = nullptr);
+// part [n_heads, n_b] -> [ceil(n_heads / 4), n_b] in place, sums over groups of four heads
+hipError_t launch_group_heads(float* part, int n_heads, int n_b, hipStream_t st);
 // values[j] = sum_i part[i, j] / (|I_focus| n_heads) when part != nullptr (else values are read), then top-k over values[0..n):
 // out[k] ascending indices.  n_parts = n_heads, or ceil(n_heads / 4) groups
 hipError_t launch_reduce_topk(const float* part, int n_parts, int n_heads, const int32_t* counts, int n_focus_max, float* values, int n,
@@ -158,7 +160,7 @@ hipError_t launch_qk_logits(const void* Q, const int32_t* active_idx, const int3
                             const void* K, const focus_shape& s, const SplitPlan& p, int mode, float* logits,
                             float* part_ml, const float* lse2, float* colpart, hipStream_t st, const SelectArgs* select = nullptr);
 // Extra arguments of the fused layer path: the attention kernel ranks the blocks itself from the partial relevances
-// (n_b <= kFusedMaxBlocks; kFusedMaxBlocksPerHead if they come per head from a K scan).  The limits are what the prologues are built
+// (n_b <= kFusedMaxBlocks; up to kFusedMaxBlocksPerHead, or of up to eight heads, they may come per head from a K scan, else launch_group_heads adds them up first).  The limits are what the prologues are built
 // for: one, four or eight keys a thread of four wavefronts, and from a K scan, whose 32 parts per key would be read by every workgroup,
 // one.  Past them a launch of one workgroup ranks the blocks and costs more than the blocks themselves (16 queries,
 // 30 blocks of 64 kept, launch and prologue: 32 heads, 1025 blocks 36.2 and 22.0 us a layer, 2048 blocks 39.8 and 25.1; 4 heads, 2048 blocks

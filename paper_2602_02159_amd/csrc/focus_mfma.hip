@@ -916,17 +916,18 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 4 ? 2 : WAVES / 4) void sparse
   if (FUSED) {
     qrow_early = fetch_q_row(p.active_idx, 0, p.max_active, p.n_gen, lane);
     FirstParts<PER_HEAD ? 32 : 8, 64 * WAVES, BLOCKS> first;
+    const bool per_head = PER_HEAD || (BLOCKS > 256 && p.rel_per_head);
     if constexpr (INNER) {
       const int entry = lane < p.n_focus_max ? p.kept_blocks[lane] : -1;
       few_sinks = request_few_sinks(p, lane);
       load_q_tile<D>(q, Qh, p.qsn, qrow_early, lane);
       relevance_parts<D, WAVES>(first, p, entry, counted.focus, dots_sh, wave, lane);
     } else {
-      first_partials(first, p, PER_HEAD);
+      first_partials(first, p, per_head);
       few_sinks = request_few_sinks(p, lane);
       load_q_tile<D>(q, Qh, p.qsn, qrow_early, lane);
     }
-    rank_blocks(p, first, PER_HEAD, counted.focus, kept_sh, topk_sm, blockIdx.x == 0 && blockIdx.y == 0);
+    rank_blocks(p, first, per_head, counted.focus, kept_sh, topk_sm, blockIdx.x == 0 && blockIdx.y == 0);
   } else {
     few_sinks = request_few_sinks(p, lane);
   }

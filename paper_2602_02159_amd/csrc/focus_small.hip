@@ -161,6 +161,33 @@ __global__ __launch_bounds__(kTopkThreads) void reduce_topk_kernel(const float* 
   }
 }
 
+// Per-head partial relevances [H, n_b] -> sums of groups of kRelGroup heads [ceil(H / 4), n_b], in the same place (a thread owns a block's column)
+// and in the order of sum_partials.  Between a K scan and an attention kernel that ranks more than 256 blocks itself: one memory round trip in a
+// launch of many workgroups, where a launch of one read all parts and ranked them (16 heads, 2048 blocks, whole layer with the scan 139.5 -> 125
+// us; 32 heads, 512 blocks 60.8 -> 59.3).  Up to eight heads the attention kernel takes the parts as they are (with this launch and without: 8
+// heads, 1870 blocks 62.8 and 61.2, 74.8 before; 4 heads, 512 blocks 21.4 and 19.7, 22.3 before; d = 64, 313 blocks 17.9 and 16.2, 18.4).
+__global__ __launch_bounds__(64) void group_heads_kernel(float* __restrict__ part, int H, int n_b) {
+  constexpr int kHeads = 32;
+  const int b = blockIdx.x * 64 + (int)threadIdx.x;
+  if (b >= n_b) return;
+  for (int h0 = 0; h0 < H; h0 += kHeads) {
+    float v[kHeads];
+#pragma unroll
+    for (int u = 0; u < kHeads; ++u) v[u] = part[(int64_t)min(h0 + u, H - 1) * n_b + b];
+#pragma unroll
+    for (int u = 0; u < kHeads; u += kRelGroup) {
+      float g = v[u];
+#pragma unroll
+      for (int i = 1; i < kRelGroup; ++i) g = h0 + u + i < H ? g + v[u + i] : g;
+      if (h0 + u < H) part[(int64_t)((h0 + u) / kRelGroup) * n_b + b] = g;
+    }
+  }
+}
+hipError_t launch_group_heads(float* part, int n_heads, int n_b, hipStream_t st) {
+  hipLaunchKernelGGL(group_heads_kernel, dim3(ceil_div(n_b, 64)), dim3(64), 0, st, part, n_heads, n_b);
+  return hipGetLastError();
+}
+
 hipError_t launch_reduce_topk(const float* part, int n_parts, int n_heads, const int32_t* counts, int n_focus_max, float* values, int n,
                               int k, int32_t* out, hipStream_t st) {
   const int threads = n <= 64 ? 64 : (n <= 256 ? 256 : kTopkThreads);
@@ -302,20 +329,10 @@ __device__ __forceinline__ void cache_update_part(const CacheUpdate& u, int g, i
 // Two passes: eight need fewer workgroups and read the focus rows less often, and take 0.3 us more from 64 to 1024 blocks.
 // =====================================================================================================
 constexpr int kRelPasses = 2;
-// UPDATE: the grid's slices from n_slices on make a cache update, a workgroup each per head and kUpdateSlots slots.
-template <int D, bool PER_HEAD, bool UPDATE = false>
-__global__ __launch_bounds__(256) void relevance_partial_kernel(const int32_t* __restrict__ focus_idx,
-                                                                const float* __restrict__ kbar,
-                                                                const int32_t* __restrict__ counts,
-                                                                const uint16_t* __restrict__ Q, int64_t qsh, int64_t qsn, int n_b,
-                                                                int H, int n_focus_max, int n_gen, float* __restrict__ part, int n_slices,
-                                                                const CacheUpdate update) {
-  if (UPDATE && grid_yz() >= n_slices) {  // whole workgroup
-    const int64_t item = (int64_t)(grid_yz() - n_slices) * gridDim.x + blockIdx.x;
-    const int64_t g = item / update.n_heads;
-    if (g * kUpdateSlots<D> < update.max_active) cache_update_part<D>(update, (int)g, (int)(item - g * update.n_heads));
-    return;
-  }
+template <int D, bool PER_HEAD>
+__device__ __forceinline__ void relevance_partial(const int32_t* __restrict__ focus_idx, const float* __restrict__ kbar,
+                                                  const int32_t* __restrict__ counts, const uint16_t* __restrict__ Q, int64_t qsh, int64_t qsn,
+                                                  int n_b, int H, int n_focus_max, int n_gen, float* __restrict__ part) {
   constexpr int CPR = D / 8;        // lanes per block row
   constexpr int R = kWave / CPR;    // block rows per pass
   constexpr int P = kRelPasses;
@@ -361,13 +378,44 @@ __global__ __launch_bounds__(256) void relevance_partial_kernel(const int32_t* _
   }
 }
 
-template <int D, bool PER_HEAD, bool UPDATE>
+template <int D, bool PER_HEAD>
+__global__ __launch_bounds__(256) void relevance_partial_kernel(const int32_t* __restrict__ focus_idx,
+                                                                const float* __restrict__ kbar,
+                                                                const int32_t* __restrict__ counts,
+                                                                const uint16_t* __restrict__ Q, int64_t qsh, int64_t qsn, int n_b,
+                                                                int H, int n_focus_max, int n_gen, float* __restrict__ part) {
+  relevance_partial<D, PER_HEAD>(focus_idx, kbar, counts, Q, qsh, qsn, n_b, H, n_focus_max, n_gen, part);
+}
+// The grid's slices from n_slices on make a cache update, a workgroup each per head and kUpdateSlots slots.
+template <int D>
+__global__ __launch_bounds__(256) void relevance_update_kernel(const int32_t* __restrict__ focus_idx, const float* __restrict__ kbar,
+                                                               const int32_t* __restrict__ counts, const uint16_t* __restrict__ Q,
+                                                               int64_t qsh, int64_t qsn, int n_b, int H, int n_focus_max, int n_gen,
+                                                               float* __restrict__ part, int n_slices, const CacheUpdate update) {
+  if (grid_yz() >= n_slices) {  // whole workgroup
+    const int64_t item = (int64_t)(grid_yz() - n_slices) * gridDim.x + blockIdx.x;
+    const int64_t g = item / update.n_heads;
+    if (g * kUpdateSlots<D> < update.max_active) cache_update_part<D>(update, (int)g, (int)(item - g * update.n_heads));
+    return;
+  }
+  relevance_partial<D, false>(focus_idx, kbar, counts, Q, qsh, qsn, n_b, H, n_focus_max, n_gen, part);
+}
+
+template <int D>
 static void launch_block_relevance_t(const uint16_t* q, const int32_t* focus_idx, const int32_t* counts, int n_focus_max, const float* kbar,
-                                     const focus_shape& s, float* part, hipStream_t st, const CacheUpdate& u) {
+                                     const focus_shape& s, float* part, bool per_head, hipStream_t st, const CacheUpdate* u) {
   const int n_b = ceil_div(s.n_ctx, s.block), n_x = ceil_div(s.n_heads, kRelGroup), n_slices = ceil_div(n_b, kRelPasses * (512 / D));
-  const int n_update = UPDATE ? (int)ceil_div64((int64_t)ceil_div(u.max_active, kUpdateSlots<D>) * s.n_heads, n_x) : 0;
-  hipLaunchKernelGGL((relevance_partial_kernel<D, PER_HEAD, UPDATE>), grid_x_yz(n_x, n_slices + n_update), dim3(256), 0, st, focus_idx, kbar,
-                     counts, q, s.q_stride_h, s.q_stride_n, n_b, s.n_heads, n_focus_max, s.n_gen, part, n_slices, u);
+  const int n_update = u ? (int)ceil_div64((int64_t)ceil_div(u->max_active, kUpdateSlots<D>) * s.n_heads, n_x) : 0;
+  const dim3 grid = grid_x_yz(n_x, n_slices + n_update);
+  if (u)
+    hipLaunchKernelGGL(relevance_update_kernel<D>, grid, dim3(256), 0, st, focus_idx, kbar, counts, q, s.q_stride_h, s.q_stride_n, n_b, s.n_heads,
+                       n_focus_max, s.n_gen, part, n_slices, *u);
+  else if (per_head)
+    hipLaunchKernelGGL((relevance_partial_kernel<D, true>), grid, dim3(256), 0, st, focus_idx, kbar, counts, q, s.q_stride_h,
+                       s.q_stride_n, n_b, s.n_heads, n_focus_max, s.n_gen, part);
+  else
+    hipLaunchKernelGGL((relevance_partial_kernel<D, false>), grid, dim3(256), 0, st, focus_idx, kbar, counts, q, s.q_stride_h,
+                       s.q_stride_n, n_b, s.n_heads, n_focus_max, s.n_gen, part);
 }
 
 hipError_t launch_block_relevance(const void* Q, const int32_t* focus_idx, const int32_t* counts, int n_focus_max,
@@ -375,14 +423,10 @@ hipError_t launch_block_relevance(const void* Q, const int32_t* focus_idx, const
                                   const CacheUpdate* update) {
   const uint16_t* q = static_cast<const uint16_t*>(Q);
   if (per_head && update != nullptr) return hipErrorInvalidValue;
-  const bool d128 = s.head_dim == 128;
-  auto launch = [&](auto kernel) { kernel(q, focus_idx, counts, n_focus_max, kbar, s, part, st, update ? *update : CacheUpdate{}); };
-  if (per_head)
-    launch(d128 ? launch_block_relevance_t<128, true, false> : launch_block_relevance_t<64, true, false>);
-  else if (update != nullptr)
-    launch(d128 ? launch_block_relevance_t<128, false, true> : launch_block_relevance_t<64, false, true>);
+  if (s.head_dim == 128)
+    launch_block_relevance_t<128>(q, focus_idx, counts, n_focus_max, kbar, s, part, per_head, st, update);
   else
-    launch(d128 ? launch_block_relevance_t<128, false, false> : launch_block_relevance_t<64, false, false>);
+    launch_block_relevance_t<64>(q, focus_idx, counts, n_focus_max, kbar, s, part, per_head, st, update);
   return hipGetLastError();
 }
 

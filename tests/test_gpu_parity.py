@@ -1027,6 +1027,13 @@ def test_sparse_layer_of_many_blocks(G, H, M, N, d, B, n_act, n_keep, n_sink):
         torch.cuda.synchronize()
         assert torch.equal(s2, scores) and torch.equal(k2, kept)
         assert torch.equal(o2, out) and torch.equal(l2, lse)
+    for nbytes in (full, least, full):                      # the relevances from a scan of K: per head, added up by groups of four in between
+        s2, k2, l2 = torch.full_like(scores, -1.0), torch.full_like(kept, -9), torch.empty_like(lse)
+        o2.fill_(7.0)
+        fb.sparse_layer(q, focus, active, counts, k, v, None, s, n_keep, sinks, n_sink, s2, k2, o2, l2, G.ws(nbytes))
+        torch.cuda.synchronize()
+        assert torch.equal(s2, scores) and torch.equal(k2, kept)
+        assert torch.equal(o2, out) and torch.equal(l2, lse)
 
 
 @pytest.mark.parametrize("H,M,N,B,n_keep,splits", [
