@@ -2573,35 +2573,7 @@ struct LogitArgs {
   SelectArgs sel;  // SELECT only
 };
 
-// Query selection (Eq. 4: the k most confident of the still-masked positions; Eq. 5: window union) of a block of up to 64
-// positions by one wavefront, one position per lane; the focus and active sets are 64-bit masks.  Same order, ties and outputs as
-// select_queries_kernel.
-__device__ __forceinline__ unsigned long long select_positions(const SelectArgs& s, int n_gen, int max_active, int lane, bool writer) {
-  uint32_t key1 = 0u;
-  if (lane < n_gen) {
-    const uint32_t key = order_key(s.conf[lane]) + 1u;
-    key1 = s.masked == nullptr || s.masked[lane] != 0 ? key : 0u;
-  }
-  uint32_t pos, n_focus;
-  const bool sel = wave_select1(key1, s.k, pos, n_focus);
-  unsigned long long active = __ballot(sel);
-  for (int i = min(s.half, 63); i > 0; --i) active |= (active << 1) | (active >> 1);
-  active &= s.hi >= 64 ? ~0ull : (1ull << s.hi) - 1ull;
-  active &= ~((1ull << s.lo) - 1ull);  // lo < hi <= n_gen <= 64
-  if (writer) {
-    const uint32_t n_act = (uint32_t)__popcll(active);
-    if (sel) s.focus_idx[pos] = lane;
-    if (lane >= (int)n_focus && lane < s.k) s.focus_idx[lane] = -1;  // k <= n_gen
-    if ((active >> lane) & 1ull) s.active_idx[__popcll(active & ((1ull << lane) - 1ull))] = lane;
-    for (int i = (int)n_act + lane; i < max_active; i += kWave) s.active_idx[i] = -1;
-    if (lane == 0) {
-      s.counts[0] = (int32_t)n_focus;
-      s.counts[1] = (int32_t)n_act;
-    }
-  }
-  return active;
-}
-// the same; lane a of `row` receives the a-th active position (a < their number, which is returned)
+// select_positions; lane a of `row` receives the a-th active position (a < their number, which is returned)
 __device__ __forceinline__ int select_rows(const SelectArgs& s, int n_gen, int max_active, int lane, bool writer, int& row) {
   const unsigned long long active = select_positions(s, n_gen, max_active, lane, writer);
   const unsigned long long below = (1ull << lane) - 1ull;

@@ -214,6 +214,35 @@ __device__ __forceinline__ bool wave_select1(uint32_t key1, int k, uint32_t& pos
   return sel;
 }
 
+// Query selection (Eq. 4: the k most confident of the still-masked positions; Eq. 5: window union) of a block of up to 64
+// positions by one wavefront, one position per lane; the focus and active sets are 64-bit masks.  Same order, ties and outputs as
+// select_queries_kernel.
+__device__ __forceinline__ unsigned long long select_positions(const SelectArgs& s, int n_gen, int max_active, int lane, bool writer) {
+  uint32_t key1 = 0u;
+  if (lane < n_gen) {
+    const uint32_t key = order_key(s.conf[lane]) + 1u;
+    key1 = s.masked == nullptr || s.masked[lane] != 0 ? key : 0u;
+  }
+  uint32_t pos, n_focus;
+  const bool sel = wave_select1(key1, s.k, pos, n_focus);
+  unsigned long long active = __ballot(sel);
+  for (int i = min(s.half, 63); i > 0; --i) active |= (active << 1) | (active >> 1);
+  active &= s.hi >= 64 ? ~0ull : (1ull << s.hi) - 1ull;
+  active &= ~((1ull << s.lo) - 1ull);  // lo < hi <= n_gen <= 64
+  if (writer) {
+    const uint32_t n_act = (uint32_t)__popcll(active);
+    if (sel) s.focus_idx[pos] = lane;
+    if (lane >= (int)n_focus && lane < s.k) s.focus_idx[lane] = -1;  // k <= n_gen
+    if ((active >> lane) & 1ull) s.active_idx[__popcll(active & ((1ull << lane) - 1ull))] = lane;
+    for (int i = (int)n_act + lane; i < max_active; i += kWave) s.active_idx[i] = -1;
+    if (lane == 0) {
+      s.counts[0] = (int32_t)n_focus;
+      s.counts[1] = (int32_t)n_act;
+    }
+  }
+  return active;
+}
+
 // Inclusive prefix sum over the 64 lanes of a wavefront: shifts within the DPP rows of 16, then the rows' totals.
 __device__ __forceinline__ uint32_t wave_prefix_sum(uint32_t x) {
   x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, true);  // row_shr:1
