@@ -863,7 +863,8 @@ struct RoundList {
 // FUSE bit 0 set (fused layer path): the workgroup first assembles R_b from the partial relevances and ranks
 // them itself — every workgroup repeats this small computation instead of waiting for a separate Top-C kernel.
 // FUSE bit 6 set (with bit 0): and works the partial relevances out, too (relevance_parts).
-// FUSE bit 3 set (with bit 0): the partial relevances come per head, from a K scan, and not per group of four heads.
+// FUSE bit 3 set (with bit 0): the partial relevances come per head, from a K scan, and not per group of four heads (more than 256 blocks: of
+// up to eight heads; a variant of its own, because the choice at run time cost 0.9 us a layer of 32 heads and 323 blocks).
 // FUSE bit 4 set (with bit 0): more than 256 blocks to rank.
 // FUSE bit 2 set (dense probe layer): the scaled logits of every (query, key) are also written out, so that
 // the column attention mass of Eq. 6 needs no QK^T pass of its own.
@@ -915,19 +916,18 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 4 ? 2 : WAVES / 4) void sparse
   int qrow_early = -1, few_sinks = -1;
   if (FUSED) {
     qrow_early = fetch_q_row(p.active_idx, 0, p.max_active, p.n_gen, lane);
-    FirstParts<PER_HEAD ? 32 : 8, 64 * WAVES, BLOCKS> first;
-    const bool per_head = PER_HEAD || (BLOCKS > 256 && p.rel_per_head);
+    FirstParts<PER_HEAD && BLOCKS <= 256 ? 32 : 8, 64 * WAVES, BLOCKS> first;
     if constexpr (INNER) {
       const int entry = lane < p.n_focus_max ? p.kept_blocks[lane] : -1;
       few_sinks = request_few_sinks(p, lane);
       load_q_tile<D>(q, Qh, p.qsn, qrow_early, lane);
       relevance_parts<D, WAVES>(first, p, entry, counted.focus, dots_sh, wave, lane);
     } else {
-      first_partials(first, p, per_head);
+      first_partials(first, p, PER_HEAD);
       few_sinks = request_few_sinks(p, lane);
       load_q_tile<D>(q, Qh, p.qsn, qrow_early, lane);
     }
-    rank_blocks(p, first, per_head, counted.focus, kept_sh, topk_sm, blockIdx.x == 0 && blockIdx.y == 0);
+    rank_blocks(p, first, PER_HEAD, counted.focus, kept_sh, topk_sm, blockIdx.x == 0 && blockIdx.y == 0);
   } else {
     few_sinks = request_few_sinks(p, lane);
   }
@@ -1775,6 +1775,15 @@ static hipError_t launch_attn_t(const AttnArgs& a, const SplitPlan& p, bool fuse
       ATTN_LAUNCH((sparse_attn_kernel<D, 6, 4>), grid, block, st, a);
     else
       ATTN_LAUNCH((sparse_attn_kernel<D, 4, 4>), grid, block, st, a);
+  } else if (fused && a.rel_per_head && a.n_b > 256) {
+    if (p.pipelined && a.n_b > kFusedManyBlocks)
+      ATTN_LAUNCH((sparse_attn_kernel<D, 43, 4>), grid, block, st, a);
+    else if (a.n_b > kFusedManyBlocks)
+      ATTN_LAUNCH((sparse_attn_kernel<D, 41, 4>), grid, block, st, a);
+    else if (p.pipelined)
+      ATTN_LAUNCH((sparse_attn_kernel<D, 27, 4>), grid, block, st, a);
+    else
+      ATTN_LAUNCH((sparse_attn_kernel<D, 25, 4>), grid, block, st, a);
   } else if (fused && p.pipelined && a.n_b > kFusedManyBlocks)
     ATTN_LAUNCH((sparse_attn_kernel<D, 35, 4>), grid, block, st, a);
   else if (fused && a.n_b > kFusedManyBlocks)
