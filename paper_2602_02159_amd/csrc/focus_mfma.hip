@@ -2430,7 +2430,9 @@ __global__ __launch_bounds__(64 * kRefreshWaves, D == 64 ? 4 : 2) void refresh_t
 // Block entry without halves and with them, d = 128: 32 heads, 2741 rows 185 -> 159 us, 2991 rows 219 -> 189, 4900 rows 487 -> 432; 8
 // heads, 4096 rows 117 -> 88, 11 691 rows 669 -> 575; 4 heads, 8192 rows 219 -> 154, 9003 rows 275 -> 240; d = 64: 32 heads, 2991 rows 122 ->
 // 116; 8 heads, 4096 rows 62.6 -> 54.6.  Quarters, where tiles took two rounds or more: d = 128, 8 heads, 1500 rows 31.1 -> 25.3; 4 heads, 2455 rows
-// 38.0 -> 34.6, 3000 rows 45.5 -> 39.7, 4096 rows 63.4 -> 56.2.  Where a round of blocks is full or nearly so they lose (d = 64: 8 heads, 8192 rows 166 and 185).
+// 38.0 -> 34.6, 3000 rows 45.5 -> 39.7, 4096 rows 63.4 -> 56.2.  A round of halves takes 0.47 to 0.62 us per sub-tile (attention alone, d = 128, halves
+// and tiles: 4 heads, 4775 rows 80 and 94, 5100 rows 95 and 98, 5500 rows 113 and 105, 5980 rows 124 and 118, 6500 rows 110 and 169; 8 heads, 3000
+// rows 57 and 66), the long ones of few heads more, for reasons not found; hence two figures each for halves and quarters, which leave three full rounds of tiles as they are there.  Where a round of blocks is full or nearly so they lose (d = 64: 8 heads, 8192 rows 166 and 185).
 // 32 heads, 8256 rows (33 blocks per head, 4.1 rounds): 1213 us all in blocks, 1106 us cut; 4 heads, 1056 rows, d = 64: 26 and 8.
 // d = 64, up to 256 tiles, which have a compute unit each, take two thirds of that (4 heads: 1266 rows 160 tiles 8.5, 2455 rows 308 tiles 19.8).
 // d = 64, block entry in blocks and in tiles: 32 heads, 1032 rows 35.1 and 29.6; 16 heads, 2032 52.4 and 39.1, 3032 71.3 and 73.2, 4032 95.5 and
@@ -2445,12 +2447,13 @@ struct RefreshCut {
 };
 static RefreshCut cut_refresh(int head_dim, int n_heads, int n_q, int L) {
   constexpr int kSlots = 256;
+  constexpr float kLaunch = 6.f;  // of every launch behind the first: 8 heads, 3000 rows, 256 quarters and 240 tiles 70 us, 184 halves 57
   constexpr int64_t kMaxGroups = ((int64_t(1) << 32) - 1) / (64 * kRefreshWaves);
   const int tiles = ceil_div(n_q, 32), last = tiles % kRefreshWaves;
   const float sub = (float)ceil_div(L, kSubTile);
   const bool d128 = head_dim == 128;
-  const float block_time = d128 ? 0.85f * sub + 5.f : 0.5f * sub + 12.f, tail_time = d128 ? 0.2f * sub + 5.f : 0.23f * sub + 3.f;
-  const float half_time = d128 ? 0.55f * sub + 10.f : 0.31f * sub + 10.f, quarter_time = 0.31f * sub + 10.f;
+  const float block_time = d128 ? 0.85f * sub + 5.f : 0.5f * sub + 12.f, tail_time = d128 ? 0.182f * sub + 5.f : 0.23f * sub + 3.f;
+  const float half_time = d128 ? (sub <= 160.f ? 0.55f : 0.585f) * sub + 10.f : 0.31f * sub + 10.f, quarter_time = (sub <= 160.f ? 0.31f : 0.38f) * sub + 10.f;
   auto rounds = [](int64_t n) { return (float)((n + kSlots - 1) / kSlots); };
   auto tail_rounds = [&](int64_t n) { return d128 || n == 0 ? rounds(n) : (n <= kSlots ? 0.63f : std::max(1.f, (float)n / (2 * kSlots))); };
   const int64_t whole = (int64_t)(tiles / kRefreshWaves) * n_heads, padded = (int64_t)ceil_div(tiles, kRefreshWaves) * n_heads;
@@ -2470,6 +2473,7 @@ static RefreshCut cut_refresh(int head_dim, int n_heads, int n_q, int L) {
     c.n_tail = (parts * (whole - work) - part_whole) * part_tiles + (int64_t)std::max(0, last - part_head * part_tiles) * n_heads;
     if (c.n_part + 7 > kMaxGroups || c.n_tail + 7 > kMaxGroups) return;
     c.time = rounds(work) * block_time + rounds(c.n_part) * (parts == 2 ? half_time : quarter_time) + tail_rounds(c.n_tail) * tail_time;
+    c.time += kLaunch * ((c.n_work > 0) + (c.n_part > 0) + (c.n_tail > 0) - 1);
     if (c.time < best.time) best = c;
   };
   const int64_t rest = whole % kSlots;

@@ -1495,8 +1495,8 @@ def test_refresh_attn_cut_into_blocks_and_tiles(G, H, n_q, L, d):
     (64, 512, 577, 128),   # 256 half blocks: an odd number of key sub-tiles, the last of one row
     (64, 512, 640, 128),   # ... an even number of whole ones
     (64, 470, 1000, 128),  # half blocks of every head's last seven tiles as well, the last tile ragged and one missing
-    (70, 512, 3300, 128),  # a round of half blocks, the others as single tiles
-    (96, 1024, 672, 128),  # a round of blocks, then a round of half blocks; an odd number of whole sub-tiles
+    (70, 512, 5100, 128),  # a round of half blocks, the others as single tiles
+    (96, 1024, 1440, 128), # a round of blocks, then a round of half blocks; an odd number of whole sub-tiles
     (64, 512, 1100, 64),   # half blocks of 64 columns, a ragged last sub-tile of one half
     (64, 500, 1121, 64),   # ... and of the other
     (8, 1500, 1490, 128),  # quarters, the last tile of a head missing: one part has a sub-tile less than the others,
@@ -1687,7 +1687,10 @@ def test_block_entry_then_step_uses_the_refreshed_cache_and_means(G):
     (4, 1024, 32, 64, 64),      # single tiles only
     (3, 1000, 37, 128, 128),    # an odd number of chunks, ragged blocks
     (40, 1060, 40, 64, 128),    # whole blocks, then tiles
-    (256, 256, 0, 128, 64),     # no tiles: the copy has a launch of its own
+    (256, 256, 0, 128, 64),     # whole blocks only, the copy's chunks behind them
+    (32, 1000, 24, 64, 128),    # half blocks only,
+    (32, 1000, 24, 130, 64),    # ... of 64 columns, chunks of more rows than are requested at once,
+    (8, 1470, 31, 150, 128),    # ... quarters
     (128, 500, 44, 50, 64),     # whole blocks and 128 tiles of 64 columns, which get a compute unit each beside the chunks of the copy
     (129, 500, 44, 50, 64),     # 145 tiles, which share theirs
     (1, 30, 0, 32, 64),
