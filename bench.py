@@ -835,7 +835,7 @@ def main() -> int:
         "roofline_paper32k": roofline_paper,
         # not part of the step: the one MFMA-bound launch of the method (block entry, every position attends to every key)
         "roofline_block_entry": None if "full_refresh_layer" not in stages else {
-            "bound": "mfma", "kernel": f"refresh_attn_kernel<{d}> + refresh_tail_kernel<{d}, false> (one focus_refresh_attn call)", "achieved": stages["full_refresh_layer"]["TFLOPps"],
+            "bound": "mfma", "kernel": f"refresh_attn_kernel<{d}, 1, false, false> + refresh_tail_kernel<{d}, false> (one focus_refresh_attn call)", "achieved": stages["full_refresh_layer"]["TFLOPps"],
             "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": stages["full_refresh_layer"]["mfma_frac"],
             "us_per_launch": stages["full_refresh_layer"]["us_per_launch"],
             "us_per_focus_block_entry": stages["block_entry_layer"]["us_per_launch"], "flops_per_launch": stages["full_refresh_layer"]["alg_flops"]},
