@@ -29,6 +29,7 @@
 // where the contraction slot (g, e) stands for key 16*(e/4) + 4g + (e%4) of the sub-tile on both operands.
 // The V^T operand is read from the row-major staged tile with the transposing LDS read ds_read_b64_tr_b16.
 #include <algorithm>
+#include <cfloat>
 #include <cstdlib>
 #include <type_traits>
 #include <utility>
@@ -2045,7 +2046,9 @@ __global__ __launch_bounds__(64 * kRefreshWaves, 2) void refresh_attn_kernel(con
       q[ks] = as_bf16x8(q_row < p.n_q ? v : make_uint4(0u, 0u, 0u, 0u));
     }
   }
-  float m_run = -INFINITY, l_run = 0.f;  // l_run: this lane's share of the row sum (its 16 of every 32 keys)
+  // Below every finite scaled logit (the scale is less than one) but finite itself: keys with a logit of -inf, all that a lane may have seen so far,
+  // then get a probability of 0 and an alpha of 1 or 0, where a maximum of -inf would give NaN.
+  float m_run = -FLT_MAX, l_run = 0.f;   // l_run: this lane's share of the row sum (its 16 of every 32 keys)
   float u_run = 0.f;                     // LSE: the same of the probabilities before they are rounded
   floatx16 o[kDT];
 #pragma unroll
@@ -2087,7 +2090,7 @@ __global__ __launch_bounds__(64 * kRefreshWaves, 2) void refresh_attn_kernel(con
   auto rescale = [&](float mx) __attribute__((always_inline)) {
     if (__ballot(mx > m_run) != 0ull) {  // some running maximum of this wavefront moves (rare after the first sub-tiles)
       const float m_new = fmaxf(m_run, mx);
-      const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);  // 0 on the first sub-tile (m_run = -inf, m_new finite)
+      const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);  // 0 where m_new is the first finite logit
       m_run = m_new;
       l_run *= alpha;
       if (LSE) u_run *= alpha;
@@ -2136,8 +2139,6 @@ __global__ __launch_bounds__(64 * kRefreshWaves, 2) void refresh_attn_kernel(con
       else if constexpr (kMore)
         ahead[s - NS] = as_bf16x8(*reinterpret_cast<const uint4*>(sK + G::kStageBytes + koff[s - NS]));
     };
-    // (the keys of one part may all have a logit of -inf where those of the other do not)
-    const float m_use = PARTS > 1 && m_run == -INFINITY ? 0.f : m_run;
     floatx16 next;
     uint32_t pk[8];
     float mxn = 0.f;
@@ -2146,8 +2147,8 @@ __global__ __launch_bounds__(64 * kRefreshWaves, 2) void refresh_attn_kernel(con
     auto probabilities = [&](int v0, int v1) __attribute__((always_inline)) {  // logits v0 .. v1 - 1 -> packed bf16, added to the row sum
 #pragma unroll
       for (int v = v0; v < v1; v += 2) {
-        float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[v], p.scale_log2, -m_use));
-        float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[v + 1], p.scale_log2, -m_use));
+        float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[v], p.scale_log2, -m_run));
+        float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[v + 1], p.scale_log2, -m_run));
         if (kLast) {  // a ragged sub-tile: slots past the end count for nothing
           const int key = 8 * (v >> 2) + 4 * hh + (v & 3);
           p0 = key < n_valid ? p0 : 0.f;

@@ -1520,6 +1520,38 @@ def test_refresh_attn_half_blocks(G, H, n_q, L, d, offset):
     assert torch.equal(out, out2)
 
 
+@pytest.mark.parametrize("H,n_q,L,d", [
+    (64, 512, 577, 128), (64, 470, 1000, 128), (64, 500, 1121, 64),   # half blocks
+    (8, 1500, 1490, 128), (9, 1000, 330, 128),                        # quarters
+    (256, 250, 300, 128), (256, 250, 300, 64),                        # whole blocks
+    (3, 100, 300, 128), (3, 100, 300, 64),                            # single tiles
+])
+def test_refresh_attn_logits_of_minus_infinity(G, H, n_q, L, d):
+    """Some queries of every tile have logits of -inf (a product of 2^65 and -2^65) for some keys: all that one part of a block, or one
+    wavefront, sees at first or at all.  They count for nothing; a query with no other key gets a row of zeros."""
+    q, k, v = (_rand_bf16(175 + i, H, r, d) for i, r in enumerate((n_q, L, L)))
+    key, sub = torch.arange(L), torch.arange(L) // 32
+    sets = [sub % 2 == 0, sub % 2 == 1, sub % 4 != 3, sub % 8 != 5, sub < 3, key < L - 1, key >= 0]   # query i: set i mod 8, or none
+    row = torch.arange(n_q) % 8
+    dead = torch.zeros(n_q, L, dtype=torch.bool)
+    for c, keys in enumerate(sets):
+        q[:, :, c] = torch.where(row == c, 2.0 ** 65, 0.0).to(torch.bfloat16)
+        k[:, :, c] = torch.where(keys, -2.0 ** 65, 0.0).to(torch.bfloat16)
+        dead |= (row == c)[:, None] & keys
+    q, k, v, dead = (t.to(G.DEV) for t in (q, k, v, dead))
+    out = torch.full((H, n_q, d), float("nan"), dtype=torch.bfloat16, device=G.DEV)
+    lse = torch.full((H, n_q), float("nan"), dtype=torch.float32, device=G.DEV)
+    fb.refresh_attn(q, k, v, fb.make_shape(q, k, v, L, 64, out), out, lse)
+    n = len(sets)
+    for h in range(H):
+        s = torch.matmul(q[h, :, n:].double(), k[h, :, n:].double().t()).div(math.sqrt(d)).masked_fill(dead, -math.inf)
+        G.assert_attention_close(out[h], torch.matmul(torch.softmax(s, -1).nan_to_num(0.0), v[h].double()).cpu().numpy())
+        assert torch.allclose(lse[h].double(), torch.logsumexp(s, -1), atol=2.0 ** -8, rtol=1e-5)   # (bound of rounded sums)
+    out2 = torch.zeros_like(out)
+    fb.refresh_attn(q, k, v, fb.make_shape(q, k, v, L, 64, out2), out2, None)
+    assert torch.equal(out, out2)
+
+
 @pytest.mark.parametrize("offset", [0.0, 40.0])      # 40: the maximum of a row moves with nearly every sub-tile
 @pytest.mark.parametrize("H,n_q,L", [
     (8, 1024, 255),      # 256 tiles of 64 columns: one per compute unit; a sub-tile per wavefront, the last ragged
