@@ -1887,8 +1887,8 @@ hipError_t launch_sparse_attn(const void* Q, const int32_t* active_idx, const in
 // PARTS = 2: a half block of 128 queries.  Four wavefronts carry its tiles over the even key sub-tiles, four over the odd ones, each four with
 // rings of their own (half as long: a barrier per two sub-tiles), and the two states of a tile are added at the end.  (PARTS = 4: a quarter, 64
 // queries, every fourth sub-tile, a barrier each.)  A
-// workgroup then fetches and stores twice the rows per product and takes 0.55 us where a block takes 0.83 (32-row sub-tile of 256 workgroups at
-// d = 128), which is less than an empty half of a round costs.  LSE: the log-sum-exps are wanted; they are then those of the unrounded sums.
+// workgroup then fetches and stores twice the rows per product and takes 0.60 us where a block takes 1.04 (32-row sub-tile of 256 workgroups at
+// d = 128, 8192 keys), which is less than an empty half of a round costs.  LSE: the log-sum-exps are wanted; they are then those of the unrounded sums.
 // The queries that would leave a round of workgroups mostly empty go there or to refresh_tail_kernel (cut_refresh).
 // COPY: the workgroups behind those of the items make the layer's cache refresh, where this is the layer's last attention launch, instead of a
 // launch of their own (which short prompts feel: block entry, 32 heads, 1160 rows 51.6 -> 42.9 us, 8192 rows 1032 -> 1020; 8 heads, 5823 rows
@@ -2417,51 +2417,57 @@ __global__ __launch_bounds__(64 * kRefreshWaves, D == 64 ? 4 : 2) void refresh_t
 }
 
 // Which query tiles go to which kernel.  Every 256-query block takes the same time, so refresh_attn_kernel runs in rounds of 256
-// blocks (one per compute unit; at d = 64 two fit, and take twice as long), and a round that is mostly empty costs as much as a
+// blocks (one per compute unit; at d = 64 two fit, and take twice as long), and a round that is mostly empty costs more than half of a
 // full one.  Half blocks of four tiles, every key sub-tile for half of the wavefronts, take two thirds of a block's time, quarters of two tiles
 // a little over a third (d = 64, where two single tiles share a compute unit: no gain, not built).
 // refresh_tail_kernel takes single 32-query tiles: an eighth of the key sub-tiles per wavefront, each about twice
-// (d = 64: four times) as long because eight tiles no longer share the staged rows.  At d = 64 two tiles share a compute unit and hardly
-// slow each other down, and 512 of them need not come in whole rounds.  All have a fixed part (first loads, merge).  The ways
-// to cut, the cheapest is taken (times in us, measured; the cache refresh is left out, with which the cut must not change):
+// (d = 64: four times) as long because eight tiles no longer share the staged rows.  The ways
+// to cut, the cheapest is taken (the cache refresh is left out, with which the cut must not change):
 //   everything in blocks, the ragged one of each head included;
 //   whole blocks, or whole rounds of them, and of the rest
 //     all in halves (or quarters), with every head's last tiles in halves, the last of them padded or not;
 //     whole rounds of halves (or quarters), and single tiles; or single tiles only.
-// Block entry without halves and with them, d = 128: 32 heads, 2741 rows 185 -> 159 us, 2991 rows 219 -> 189, 4900 rows 487 -> 432; 8
-// heads, 4096 rows 117 -> 88, 11 691 rows 669 -> 575; 4 heads, 8192 rows 219 -> 154, 9003 rows 275 -> 240; d = 64: 32 heads, 2991 rows 122 ->
-// 116; 8 heads, 4096 rows 62.6 -> 54.6.  Quarters, where tiles took two rounds or more: d = 128, 8 heads, 1500 rows 31.1 -> 25.3; 4 heads, 2455 rows
-// 38.0 -> 34.6, 3000 rows 45.5 -> 39.7, 4096 rows 63.4 -> 56.2.  A round of halves takes 0.47 to 0.62 us per sub-tile (attention alone, d = 128, halves
-// and tiles: 4 heads, 4775 rows 80 and 94, 5100 rows 95 and 98, 5500 rows 113 and 105, 5980 rows 124 and 118, 6500 rows 110 and 169; 8 heads, 3000
-// rows 57 and 66), the long ones of few heads more, for reasons not found; hence two figures each for halves and quarters, which leave three full rounds of tiles as they are there.  Where a round of blocks is full or nearly so they lose (d = 64: 8 heads, 8192 rows 166 and 185).
+// Cost of a launch (LaunchCost, us): a fixed part, one per round, and per key sub-tile of a round what a round of few workgroups takes, up to what
+// a full one does, with the square of how full it is.  What grows is the clock's period: a full chip of matrix products on real
+// data holds a lower clock than a few compute units (8192 keys, d = 128, us per sub-tile with 32, 128 and 256 workgroups: blocks 0.80, 0.84,
+// 1.04, halves 0.49, 0.52, 0.60, quarters 0.33, 0.35, 0.39; on zeros, which hardly switch, 0.72, 0.72, 0.74, 0.44, 0.44, 0.45, 0.32, 0.30, 0.31; tiles do
+// not feel it).  The figures are those that choose best among all ways to cut 648 block entries of 4 to 32 heads and 1K to 33K rows, each way
+// timed: on average 0.03 % (d = 64: 0.3 %) above the fastest way, 2 % (7 %) at most; rounds of one price each, however full, were 1.1 %
+// above it and up to 27 % (18 %), blocks and tiles only 7.5 % (2.7 %) and up to 49 % (30 %).  Blocks and tiles only, and with halves:
+// d = 128: 32 heads, 2741 rows 185 -> 159 us, 2991 rows 219 -> 189, 4900 rows 487 -> 432; 8
+// heads, 4096 rows 117 -> 88, 11 691 rows 669 -> 575; 4 heads, 5860 rows 117 -> 100, 8192 rows 219 -> 154; d = 64: 32 heads, 2991 rows 124 ->
+// 115; 8 heads, 4096 rows 60.6 -> 52.5.  Quarters, where tiles took two rounds or more: d = 128, 8 heads, 1500 rows 31.1 -> 25.3; 4 heads, 2455 rows
+// 38.0 -> 34.6, 3000 rows 45.5 -> 39.7, 4096 rows 63.4 -> 56.2.
 // 32 heads, 8256 rows (33 blocks per head, 4.1 rounds): 1213 us all in blocks, 1106 us cut; 4 heads, 1056 rows, d = 64: 26 and 8.
-// d = 64, up to 256 tiles, which have a compute unit each, take two thirds of that (4 heads: 1266 rows 160 tiles 8.5, 2455 rows 308 tiles 19.8).
-// d = 64, block entry in blocks and in tiles: 32 heads, 1032 rows 35.1 and 29.6; 16 heads, 2032 52.4 and 39.1, 3032 71.3 and 73.2, 4032 95.5 and
-// 118; 8 heads, 4032 85 and 64, 6032 119 and 130.
-// A launch has fewer than 2^32 threads (kMaxGroups workgroups).  More tail tiles than that stay in blocks; more chunks of the cache
-// refresh than fit behind the tail tiles (2^24 of them: block 1, 32 heads, half a million rows) get the launch of their own that they
-// have where there is no tail.
+// A launch has fewer than 2^32 threads (kMaxGroups workgroups): ways to cut with more tiles or parts than that are left out.
 struct RefreshCut {
   int n_qb = 0, n_work = 0, parts = 2, part_whole = 0, part_head = 0;
   int64_t n_part = 0, n_tail = 0;
   float time = 0.f;
 };
+struct LaunchCost {
+  float fixed, round, few, full;  // few, full: of a sub-tile in a round of few workgroups, and in a full one
+  float of(int64_t n, float sub) const {  // n workgroups of `sub` key sub-tiles
+    constexpr int kSlots = 256;
+    if (n == 0) return 0.f;
+    const float whole = (float)(n / kSlots), part = (float)(n % kSlots) / kSlots;
+    return part > 0.f ? fixed + (whole + 1.f) * round + sub * (whole * full + few + (full - few) * part * part) : fixed + whole * (round + sub * full);
+  }
+};
 static RefreshCut cut_refresh(int head_dim, int n_heads, int n_q, int L) {
   constexpr int kSlots = 256;
-  constexpr float kLaunch = 6.f;  // of every launch behind the first: 8 heads, 3000 rows, 256 quarters and 240 tiles 70 us, 184 halves 57
   constexpr int64_t kMaxGroups = ((int64_t(1) << 32) - 1) / (64 * kRefreshWaves);
   const int tiles = ceil_div(n_q, 32), last = tiles % kRefreshWaves;
   const float sub = (float)ceil_div(L, kSubTile);
   const bool d128 = head_dim == 128;
-  const float block_time = d128 ? 0.85f * sub + 5.f : 0.5f * sub + 12.f, tail_time = d128 ? 0.182f * sub + 5.f : 0.23f * sub + 3.f;
-  const float half_time = d128 ? (sub <= 160.f ? 0.55f : 0.585f) * sub + 10.f : 0.31f * sub + 10.f, quarter_time = (sub <= 160.f ? 0.31f : 0.38f) * sub + 10.f;
-  auto rounds = [](int64_t n) { return (float)((n + kSlots - 1) / kSlots); };
-  auto tail_rounds = [&](int64_t n) { return d128 || n == 0 ? rounds(n) : (n <= kSlots ? 0.63f : std::max(1.f, (float)n / (2 * kSlots))); };
+  const LaunchCost block = d128 ? LaunchCost{4.f, 3.f, 0.61f, 0.96f} : LaunchCost{12.f, 0.f, 0.43f, 0.54f};
+  const LaunchCost half = d128 ? LaunchCost{7.f, 3.f, 0.4f, 0.57f} : LaunchCost{8.f, 0.f, 0.32f, 0.33f}, quarter = {6.f, 3.f, 0.28f, 0.34f};
+  const LaunchCost single = d128 ? LaunchCost{3.f, 3.f, 0.195f, 0.195f} : LaunchCost{4.5f, 0.f, 0.114f, 0.114f};
   const int64_t whole = (int64_t)(tiles / kRefreshWaves) * n_heads, padded = (int64_t)ceil_div(tiles, kRefreshWaves) * n_heads;
   RefreshCut best;
   best.n_qb = ceil_div(tiles, kRefreshWaves);
   best.n_work = (int)padded;
-  best.time = rounds(padded) * block_time;
+  best.time = block.of(padded, sub);
   auto consider = [&](int64_t work, int parts, int64_t part_whole, int part_head) {
     const int part_tiles = kRefreshWaves / parts;
     RefreshCut c;
@@ -2473,8 +2479,7 @@ static RefreshCut cut_refresh(int head_dim, int n_heads, int n_q, int L) {
     c.n_part = part_whole + (int64_t)part_head * n_heads;
     c.n_tail = (parts * (whole - work) - part_whole) * part_tiles + (int64_t)std::max(0, last - part_head * part_tiles) * n_heads;
     if (c.n_part + 7 > kMaxGroups || c.n_tail + 7 > kMaxGroups) return;
-    c.time = rounds(work) * block_time + rounds(c.n_part) * (parts == 2 ? half_time : quarter_time) + tail_rounds(c.n_tail) * tail_time;
-    c.time += kLaunch * ((c.n_work > 0) + (c.n_part > 0) + (c.n_tail > 0) - 1);
+    c.time = block.of(work, sub) + (parts == 2 ? half : quarter).of(c.n_part, sub) + single.of(c.n_tail, sub);
     if (c.time < best.time) best = c;
   };
   const int64_t rest = whole % kSlots;

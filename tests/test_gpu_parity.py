@@ -1492,11 +1492,11 @@ def test_refresh_attn_cut_into_blocks_and_tiles(G, H, n_q, L, d):
 
 @pytest.mark.parametrize("offset", [0.0, 40.0])      # 40: the maximum of a row moves with nearly every sub-tile
 @pytest.mark.parametrize("H,n_q,L,d", [
-    (64, 512, 577, 128),   # 256 half blocks: an odd number of key sub-tiles, the last of one row
-    (64, 512, 640, 128),   # ... an even number of whole ones
+    (70, 256, 577, 128),   # 140 half blocks: an odd number of key sub-tiles, the last of one row
+    (70, 256, 640, 128),   # ... an even number of whole ones
     (64, 470, 1000, 128),  # half blocks of every head's last seven tiles as well, the last tile ragged and one missing
-    (70, 512, 5100, 128),  # a round of half blocks, the others as single tiles
-    (96, 1024, 1440, 128), # a round of blocks, then a round of half blocks; an odd number of whole sub-tiles
+    (130, 263, 748, 128),  # a round of half blocks, the others as single tiles
+    (24, 3567, 1300, 128), # a round of blocks, then 160 half blocks; an odd number of sub-tiles
     (64, 512, 1100, 64),   # half blocks of 64 columns, a ragged last sub-tile of one half
     (64, 500, 1121, 64),   # ... and of the other
     (8, 1500, 1490, 128),  # quarters, the last tile of a head missing: one part has a sub-tile less than the others,
@@ -1521,7 +1521,7 @@ def test_refresh_attn_half_blocks(G, H, n_q, L, d, offset):
 
 
 @pytest.mark.parametrize("H,n_q,L,d", [
-    (64, 512, 577, 128), (64, 470, 1000, 128), (64, 500, 1121, 64),   # half blocks
+    (70, 256, 577, 128), (64, 470, 1000, 128), (64, 500, 1121, 64),   # half blocks
     (8, 1500, 1490, 128), (9, 1000, 330, 128),                        # quarters
     (256, 250, 300, 128), (256, 250, 300, 64),                        # whole blocks
     (3, 100, 300, 128), (3, 100, 300, 64),                            # single tiles
