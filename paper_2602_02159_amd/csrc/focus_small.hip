@@ -969,6 +969,11 @@ __device__ __forceinline__ ConfState conf_reduce(const ConfState& st) {
 // reductions: maximum, index and sum one after the other by lane moves within the vector ALU.  With whole states exchanged through the LDS
 // crossbar step by step, and the mask looked at first, both launches together took 10.8 us for 32 rows of 126 464 where they now take 6.7
 // (64 rows 12.2 -> 8.4, 8 rows 8.0 -> 5.5, 64 rows of 32 000 8.9 -> 6.2).
+// Rows that the mask excludes are requested as well, two vectors a thread (a short slice whole).  Against the same kernel with the mask first, which
+// reads nothing of them, that gains while few rows are excluded and costs next to nothing when most are; none, half and 95 % of the rows excluded, this
+// and mask first (us, rows that were not in a cache): 8 rows of 126 464: 4.9 and 5.0, 4.9 and 5.0, 4.4 and 4.5; 32: 6.9 and 6.8, 6.8 and 6.6, 6.5
+// and 6.4; 64: 8.5 and 8.9, 8.1 and 8.1, 7.9 and 7.9; 256: 16.5 and 17.6, 15.9 and 16.0, 15.2 and 15.2; 1024 rows of 32 000: 14.7 and 15.0, 13.6 and 13.7,
+// 10.8 and 10.5.
 __global__ __launch_bounds__(256) void token_confidence_kernel(const uint16_t* __restrict__ logits, int64_t row_stride,
                                                                const uint8_t* __restrict__ masked, int vocab, int n_split,
                                                                ConfState* __restrict__ part, int32_t* __restrict__ tokens,
