@@ -160,10 +160,10 @@ hipError_t launch_qk_logits(const void* Q, const int32_t* active_idx, const int3
                             const void* K, const focus_shape& s, const SplitPlan& p, int mode, float* logits,
                             float* part_ml, const float* lse2, float* colpart, hipStream_t st, const SelectArgs* select = nullptr);
 // Extra arguments of the fused layer path: the attention kernel ranks the blocks itself from the partial relevances
-// (n_b <= kFusedMaxBlocks; up to kFusedMaxBlocksPerHead, or of up to eight heads, they may come per head from a K scan, else launch_group_heads adds them up first).  The limits are what the prologues are built
-// for: one, four or eight keys a thread of four wavefronts, and from a K scan, whose 32 parts per key would be read by every workgroup,
-// one.  Past them a launch of one workgroup ranks the blocks and costs more than the blocks themselves (16 queries,
-// 30 blocks of 64 kept, launch and prologue: 32 heads, 1025 blocks 36.2 and 22.0 us a layer, 2048 blocks 39.8 and 25.1; 4 heads, 2048 blocks
+// (n_b <= kFusedMaxBlocks).  The limit is what the prologues are built for: one, four or eight keys a thread of four wavefronts, for each up to
+// eight parts requested at once.  The parts of a K scan come per head: up to kFusedMaxBlocksPerHead blocks, one key a thread, 32 of them are
+// requested, past that up to eight as of the groups, and of more heads launch_group_heads adds them up first.  Past the limit a launch
+// of one workgroup ranks the blocks and costs more than the blocks themselves (16 queries, 30 blocks of 64 kept, launch and prologue: 32 heads, 1025 blocks 36.2 and 22.0 us a layer, 2048 blocks 39.8 and 25.1; 4 heads, 2048 blocks
 // 28.8 and 15.5; 1024 blocks with four keys a thread 19.9).
 constexpr int kFusedManyBlocks = 1024, kFusedMaxBlocks = 2048, kFusedMaxBlocksPerHead = 256;
 struct FusedTopC {

@@ -2439,7 +2439,8 @@ __global__ __launch_bounds__(64 * kRefreshWaves, D == 64 ? 4 : 2) void refresh_t
 // 115; 8 heads, 4096 rows 60.6 -> 52.5.  Quarters, where tiles took two rounds or more: d = 128, 8 heads, 1500 rows 31.1 -> 25.3; 4 heads, 2455 rows
 // 38.0 -> 34.6, 3000 rows 45.5 -> 39.7, 4096 rows 63.4 -> 56.2.
 // 32 heads, 8256 rows (33 blocks per head, 4.1 rounds): 1213 us all in blocks, 1106 us cut; 4 heads, 1056 rows, d = 64: 26 and 8.
-// A launch has fewer than 2^32 threads (kMaxGroups workgroups): ways to cut with more tiles or parts than that are left out.
+// A launch has fewer than 2^32 threads (kMaxGroups workgroups): ways to cut with more tiles or parts than that are left out, and a cache refresh
+// whose chunks do not fit behind the last attention launch (2^24 of them: block 1, 32 heads, half a million rows) has a launch of its own.
 struct RefreshCut {
   int n_qb = 0, n_work = 0, parts = 2, part_whole = 0, part_head = 0;
   int64_t n_part = 0, n_tail = 0;
