@@ -1496,12 +1496,20 @@ def test_refresh_attn_cut_into_blocks_and_tiles(G, H, n_q, L, d):
     (70, 256, 640, 128),   # ... an even number of whole ones
     (64, 470, 1000, 128),  # half blocks of every head's last seven tiles as well, the last tile ragged and one missing
     (130, 263, 748, 128),  # a round of half blocks, the others as single tiles
+    (130, 404, 811, 128),  # half blocks of whole ones and of every head's last tiles, the others as single tiles
     (24, 3567, 1300, 128), # a round of blocks, then 160 half blocks; an odd number of sub-tiles
+    (96, 678, 836, 128),   # whole blocks, then half blocks of every head's last tiles
+    (130, 771, 1639, 128), # a round of blocks, a round of half blocks, single tiles
     (64, 512, 1100, 64),   # half blocks of 64 columns, a ragged last sub-tile of one half
     (64, 500, 1121, 64),   # ... and of the other
+    (70, 452, 2004, 64),   # half blocks of whole ones and of the last tiles, then single tiles
+    (130, 787, 2028, 64),  # a round of blocks, a round of half blocks, single tiles
     (8, 1500, 1490, 128),  # quarters, the last tile of a head missing: one part has a sub-tile less than the others,
     (8, 1500, 1537, 128),  # ... three have, and the fourth's last one has a single row;
     (9, 1000, 330, 128),   # ... a few sub-tiles each, the last tile ragged
+    (24, 3298, 645, 128),  # a round of blocks, then quarters
+    (70, 912, 475, 128),   # whole blocks, then quarters of every head's last tiles
+    (130, 546, 461, 128),  # a round of blocks, quarters of the other four and of the last tiles
 ])
 def test_refresh_attn_half_blocks(G, H, n_q, L, d, offset):
     q, k, v = (_rand_bf16(171 + i, H, r, d).to(G.DEV) for i, r in enumerate((n_q, L, L)))
@@ -1510,7 +1518,7 @@ def test_refresh_attn_half_blocks(G, H, n_q, L, d, offset):
     lse = torch.full((H, n_q), float("nan"), dtype=torch.float32, device=G.DEV)
     fb.refresh_attn(q, k, v, fb.make_shape(q, k, v, L, 64, out), out, lse)
     # float64 on the device, a head at a time: float32 would leave the large logits 2e-5 of themselves
-    for h in range(0, H, 9):
+    for h in range(H):
         s = torch.matmul(q[h].double(), k[h].double().t()) / math.sqrt(d)
         G.assert_attention_close(out[h], torch.matmul(torch.softmax(s, -1), v[h].double()).cpu().numpy())
         # sums of rounded probabilities (whole blocks) are off by up to 2^-9 of themselves; the size of a logit scales its fp32 rounding
@@ -1718,7 +1726,11 @@ def test_block_entry_then_step_uses_the_refreshed_cache_and_means(G):
 @pytest.mark.parametrize("H,M,N,B,d", [
     (4, 1024, 32, 64, 64),      # single tiles only
     (3, 1000, 37, 128, 128),    # an odd number of chunks, ragged blocks
-    (40, 1060, 40, 64, 128),    # whole blocks, then tiles
+    (40, 1060, 40, 64, 128),    # blocks, the last of each head padded
+    (129, 240, 17, 64, 128),    # whole blocks, then tiles with the copy behind them
+    (17, 1950, 41, 64, 64),     # ... half blocks, then tiles
+    (129, 1760, 33, 64, 128),   # ... blocks, half blocks, then tiles
+    (97, 700, 37, 64, 128),     # blocks, then quarters with the copy behind them
     (256, 256, 0, 128, 64),     # whole blocks only, the copy's chunks behind them
     (32, 1000, 24, 64, 128),    # half blocks only,
     (32, 1000, 24, 130, 64),    # ... of 64 columns, chunks of more rows than are requested at once,
