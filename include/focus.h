@@ -293,8 +293,8 @@ int focus_cache_update(void* K_cache, void* V_cache, const focus_shape* shape, c
                        int32_t max_active, int32_t row_base, void* stream);
 
 /* focus_cache_update and then focus_sparse_layer of one layer over the updated caches, in one call with the same results; with kbar the update
- * is made beside the relevances, which read nothing of the caches (short key lists of few heads and kbar NULL: a launch of its own).
- * shape: strides of the caches, Q and out. */
+ * is made beside the relevances, which read nothing of the caches (short key lists of few heads and kbar NULL: a launch of its own).  Q, kbar
+ * and the index lists must not share memory with the caches.  shape: strides of the caches, Q and out. */
 int focus_update_sparse_layer(void* K_cache, void* V_cache, const void* K_new, const void* V_new, int64_t new_stride_h, int64_t new_stride_n,
                               int32_t row_base, const void* Q, const int32_t* focus_idx, const int32_t* active_idx, const int32_t* counts,
                               int32_t n_focus_max, int32_t max_active, const float* kbar, const focus_shape* shape, int32_t n_keep,
